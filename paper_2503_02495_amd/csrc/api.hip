@@ -65,41 +65,25 @@ RouteWs route_ws(int b, int l, int d, int n, int m, bool bf16)
 }
 
 struct SmhaWs {
-    size_t q, k, v, o, o_lo, inv_cnt, inv_ent, total;
+    size_t q, k, v, o, o_lo, total;
 };
 SmhaWs smha_ws(const uoe_block_desc *d)
 {
     SmhaWs w;
     const size_t l_a = (((size_t)d->c * (d->l / d->m)) + 7) & ~(size_t)7;  // v may be stored transposed, rows padded to 8
-    const size_t one = up((size_t)d->b * d->k * l_a * d->width * elem_size(d->dtype));
+    const size_t one = up((size_t)d->b * d->k * l_a * smha_padded_width(d->width, d->dtype == UOE_BF16) * elem_size(d->dtype));
     size_t off = 0;
     w.q = off; off += one;
     w.k = off; off += one;
     w.v = off; off += one;
     w.o = off; off += one;
     w.o_lo = off; off += one;
-    w.inv_cnt = off; off += up((size_t)d->b * d->m * sizeof(int32_t));
-    w.inv_ent = off; off += up((size_t)d->b * d->m * d->k * sizeof(int32_t));
     w.total = off;
     return w;
 }
 
-// hidden activations: [b, l, k*d_e] (expert selection) or [b*k, l_a, d_e] (data selection, never
-// larger); behind them the inverse map of the data-selection mode
-struct UomeWs {
-    size_t hidden, inv_cnt, inv_ent, total;
-};
-UomeWs uome_ws_layout(const uoe_block_desc *d)
-{
-    UomeWs w;
-    size_t off = 0;
-    w.hidden = off; off += up((size_t)d->b * d->l * d->k * d->width * elem_size(d->dtype));
-    w.inv_cnt = off; off += up((size_t)d->b * d->m * sizeof(int32_t));
-    w.inv_ent = off; off += up((size_t)d->b * d->m * d->k * sizeof(int32_t));
-    w.total = off;
-    return w;
-}
-size_t uome_ws(const uoe_block_desc *d) { return uome_ws_layout(d).total; }
+// hidden activations: [b, l, k*d_e] (expert selection) or [b*k, l_a, d_e] (data selection, never larger)
+size_t uome_ws(const uoe_block_desc *d) { return up((size_t)d->b * d->l * d->k * d->width * elem_size(d->dtype)); }
 
 // backward pass of the UoME block: Z, dH, dZ [b,l,k*d_e]; dZ^T, H^T [b,k*d_e,l]; the two transposed
 // weight tensors; split-K tiles of one weight gradient; partial sums of the gate gradient
@@ -364,8 +348,6 @@ int do_smha(const uoe_block_desc *blk, const void *x, const void *wq, const void
     a.d_h = blk->width; a.flags = blk->flags;
     a.rope_dim = blk->rope_dim; a.pad_mask = pad_mask; a.skip = skip;
     a.q = at(ws, w.q); a.kk = at(ws, w.k); a.v = at(ws, w.v); a.o = at(ws, w.o); a.o_lo = at(ws, w.o_lo);
-    a.inv_cnt = reinterpret_cast<int32_t *>(at(ws, w.inv_cnt));
-    a.inv_ent = reinterpret_cast<int32_t *>(at(ws, w.inv_ent));
     return launch_smha(a, blk->dtype == UOE_BF16, st) == hipSuccess ? UOE_OK : UOE_ERR_DEVICE;
 }
 
@@ -383,7 +365,6 @@ int do_uome(const uoe_block_desc *blk, const void *u, const void *a_in, const vo
     if ((blk->flags & UOE_FLAG_GATE_PATCH) && !patch_gate) return UOE_ERR_INVALID_ARG;
     if (!ws || ws_bytes < uome_ws(blk) || !aligned16(ws)) return UOE_ERR_WORKSPACE;
     if (patch_idx) {
-        const UomeWs w = uome_ws_layout(blk);
         UomeDsArgs a{};
         a.u = u; a.a_in = a_in; a.a_out = a_out;
         a.expert_idx = expert_idx; a.patch_idx = patch_idx;
@@ -392,9 +373,7 @@ int do_uome(const uoe_block_desc *blk, const void *u, const void *a_in, const vo
         a.b = blk->b; a.l = blk->l; a.d = blk->d; a.n = blk->n; a.k = blk->k; a.m = blk->m; a.c = blk->c;
         a.d_e = blk->width;
         a.flags = blk->flags;
-        a.hidden = at(ws, w.hidden);
-        a.inv_cnt = reinterpret_cast<int32_t *>(at(ws, w.inv_cnt));
-        a.inv_ent = reinterpret_cast<int32_t *>(at(ws, w.inv_ent));
+        a.hidden = ws;
         return launch_uome_ds(a, blk->dtype == UOE_BF16, st) == hipSuccess ? UOE_OK : UOE_ERR_DEVICE;
     }
 

@@ -128,8 +128,8 @@ struct SmhaArgs {
     int rope_dim;                             // rotary dims at the end of a head (Eq. 32), 0 = none
     const unsigned char *pad_mask;            // [b,l] 1 = token, 0 = padding (Eq. 41), or NULL
     // workspace
-    void *q, *kk, *v, *o, *o_lo;              // [b*k, l_a, d_h] each, storage dtype (o_lo: low part of o, MFMA path)
-    int32_t *inv_cnt, *inv_ent;               // [b,m], [b,m,k]: which (slot s, pick t) chose patch p
+    void *q, *kk, *v, *o, *o_lo;              // [b*k, l_a, d_hp] each, storage dtype (o_lo: low part of o, MFMA path)
+    int d_hp;                                 // set by the launcher: smha_padded_width()
     float *lse;                               // [b*k, l_a] or NULL: base-2 log-sum-exp of each query's scaled logits
                                               // (MFMA attention only; kept for the backward pass)
     int keep_v_bf16;                          // 1: the MFMA path leaves v in bf16 (the backward pass reads it); 0: it
@@ -158,7 +158,6 @@ struct UomeDsArgs {
     int b, l, d, n, k, m, c, d_e;
     uint32_t flags;
     void *hidden;                             // [b*k, l_a, d_e], storage dtype
-    int32_t *inv_cnt, *inv_ent;               // [b,m], [b,m,k] (engines without in-kernel segment lists)
 };
 
 // Backward pass of the expert-selection UoME block (bf16 storage, MFMA shapes only)
@@ -252,6 +251,9 @@ hipError_t launch_unit_gate_grads(const SmhaBwdArgs &a, hipStream_t st);
 hipError_t launch_uome_backward_generic(const UomeBwdArgs &a, bool bf16, hipStream_t st);
 hipError_t launch_smha_backward_generic(const SmhaBwdArgs &a, bool bf16, hipStream_t st);
 hipError_t launch_route_backward(const RouteBwdArgs &a, bool bf16, hipStream_t st);
+// elements per row of q, k, v and o: the bf16 attention kernels take heads of 32, 64 or 128, other widths are padded
+// with zero columns
+int smha_padded_width(int d_h, bool bf16);
 int smha_backward_splits(int b, int n, int k, int c);
 int uome_backward_gate_chunks(int l, int d_e);
 int uome_backward_splits(int b, int l, int d, int n, int k, int d_e);

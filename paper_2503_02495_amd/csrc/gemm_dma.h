@@ -28,9 +28,26 @@
 //    K loop: a compiler-inserted wait for it would drain the whole pipeline.  Per-segment routing
 //    lookups are therefore taken once, before the loop, into a small LDS table (seg_ctx).
 //
-// Requirements (checked by the callers): kseg() % BK == 0, N % 8 == 0, at most 128 K segments; BN a
-// multiple of 64 and both operand tiles a whole number of load instructions per wave.  M and N tails are handled by clamping the load addresses to a valid row / chunk
-// of the same tile (the results of clamped rows and columns are never stored).
+//  * Variants (GEMM_* flags).  GEMM_A_KM: the left operand is given [k][m] (m contiguous; a_stride() elements
+//    between k rows): its tile is laid out and read like the B tile, so a gradient that contracts over
+//    tokens takes its operands as the other kernels wrote them.  GEMM_B_NK: the right operand is given
+//    [n][k] (k contiguous, b_stride() elements between n rows): laid out and read like the A tile, so a
+//    product with a transposed weight needs no transposed copy of it.  GEMM_TAIL: kseg() may be any
+//    length (a multiple of 8 where an operand runs along k): the pieces of A behind the end of a
+//    segment are read from a 16-byte block of zeros (every lane supplies its own address, so this is
+//    one compare and one select per load), those of B from the segment's last row or piece (finite,
+//    multiplied by zero).
+//  * fp32 storage (P::Elem = float) runs on v_mfma_f32_32x32x2_f32, exact fp32 products: 256 FLOP per
+//    clock and compute unit, twice what the vector ALU reaches without packed instructions, and the
+//    operands cost one LDS read per 32 lanes instead of one per output.  Same bytes per tile row, half
+//    the elements: a 16-byte piece is four k, the lane halves take k and k+4.  [k][n] tiles are read
+//    element by element (a lane is a column) with slot (r, pos) <- piece pos ^ (((r >> 2) & 1) << 3),
+//    which puts the two half-waves' rows k and k+4 in different halves of the banks.
+//
+// Requirements (checked by the callers): kseg() % BK == 0 without GEMM_TAIL, N % 8 == 0 (and M % 8 == 0 with
+// GEMM_A_KM), at most 128 entries in the segment table; BN (BM with GEMM_A_KM) a multiple of 64 and both operand
+// tiles a whole number of load instructions per wave.  M and N tails are handled by clamping the load
+// addresses to a valid row / chunk of the same tile (the results of clamped rows and columns are never stored).
 #pragma once
 #include "gemm_mfma.h"
 #include <type_traits>
@@ -52,30 +69,80 @@ template <int N> __device__ __forceinline__ void dma_wait()
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+constexpr int GEMM_A_KM = 1, GEMM_B_NK = 2, GEMM_TAIL = 4;
+
+// element type of a problem's operands (bf16 unless it says otherwise)
+template <typename P, typename = void> struct elem_of {
+    typedef uint16_t type;
+};
+template <typename P> struct elem_of<P, std::void_t<typename P::Elem>> {
+    typedef typename P::Elem type;
+};
+// K segments per entry of the segment table (2: a (hi, lo) pair of left operands that share the entry)
+template <typename P, typename = void> struct seg_parts {
+    static constexpr int value = 1;
+};
+template <typename P> struct seg_parts<P, std::void_t<decltype(P::kSegParts)>> {
+    static constexpr int value = P::kSegParts;
+};
+
+static __device__ __align__(16) const uint32_t gemm_zero_piece[4] = {0, 0, 0, 0};
+
+// fp32 epilogue: straight from the accumulators, 16-byte pieces of rows; the problem applies its own factors
+template <typename P, int TM, int TN>
+__device__ __forceinline__ void wave_epilogue_f32(const P &p, f32x16_t (&acc)[TM][TN], const float *coltab, const float (&rs)[TM], int g,
+                                                  int grow0, int gcol0, int wcol0, int M, int N, int lane)
+{
+    const int lr = lane & 31, lh = lane >> 5;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int grow = grow0 + i * 32 + lr;
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int qg = 0; qg < 4; ++qg) {
+                const int cl = j * 32 + qg * 8 + lh * 4, gcol = gcol0 + cl;
+                float sc = 1.0f;
+                if constexpr (P::kColScale) sc = coltab[(wcol0 + cl) >> 3];
+                if constexpr (P::kRowScale) sc *= rs[i];
+                if (grow < M && gcol < N)
+                    p.put4(g, grow, gcol, make_float4(p.epi_f32(acc[i][j][qg * 4 + 0], sc), p.epi_f32(acc[i][j][qg * 4 + 1], sc),
+                                                      p.epi_f32(acc[i][j][qg * 4 + 2], sc), p.epi_f32(acc[i][j][qg * 4 + 3], sc)));
+            }
+    }
+}
+
 // OCC = waves per SIMD the register budget is held to (workgroups per CU = OCC * 4 / waves, LDS permitting)
-template <typename P, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int OCC>
+template <typename P, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int OCC, int FLAGS>
 __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, OCC) void gemm_dma_kernel(P p, TileGrid tg)
 {
+    typedef typename elem_of<P>::type E;
+    constexpr bool F32 = std::is_same<E, float>::value;
+    constexpr bool AKM = (FLAGS & GEMM_A_KM) != 0, BNK = (FLAGS & GEMM_B_NK) != 0, TAIL = (FLAGS & GEMM_TAIL) != 0;
+    constexpr int ES = sizeof(E), EP = 16 / ES;          // element size; elements per 16-byte piece
     constexpr int NW = WAVES_M * WAVES_N;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
     constexpr int TM = WM / 32, TN = WN / 32;
-    constexpr int CA = BK / 8, CB = BN / 8;              // 16-byte chunks per A row / B row
-    constexpr int ARD = 64 / CA;                         // A rows covered by one load instruction
-    constexpr int A_INSTR = BM * CA / 64;                // load instructions that make up the A tile
+    constexpr int CK = BK / EP;                          // 16-byte chunks per row of a k-contiguous tile
+    constexpr int KRD = 64 / CK;                         // rows of such a tile covered by one load instruction
+    constexpr int CM = BM / EP, CN = BN / EP;            // chunks per row of a [k][m] / [k][n] tile
+    constexpr int A_INSTR = BM * CK / 64, B_INSTR = BN * CK / 64;   // load instructions that make up the tiles
     // instructions per wave per step; when the A tile has fewer instructions than waves the surplus
     // waves repeat one (same bytes to the same place), so that every wave counts the same loads
-    constexpr int A_DMA = (A_INSTR + NW - 1) / NW, B_DMA = BK * CB / (64 * NW);
-    constexpr int A_STAGE = BM * BK * 2, B_STAGE = BK * BN * 2, STAGE_BYTES = A_STAGE + B_STAGE;
+    constexpr int A_DMA = (A_INSTR + NW - 1) / NW, B_DMA = B_INSTR / NW;
+    constexpr int A_STAGE = BM * BK * ES, B_STAGE = BK * BN * ES, STAGE_BYTES = A_STAGE + B_STAGE;
     constexpr int SPITCH = WN + 8;                       // epilogue staging pitch in elements
-    constexpr int S_BYTES = NW * WM * SPITCH * 2;
+    constexpr int S_BYTES = F32 ? 0 : NW * WM * SPITCH * 2;
     constexpr int OPER_BYTES = STAGES * STAGE_BYTES;
     constexpr int LDS_BYTES = OPER_BYTES > S_BYTES ? OPER_BYTES : S_BYTES;
-    constexpr int MAX_SEG = 128;
+    constexpr int MAX_SEG = 128, PARTS = seg_parts<P>::value;
     static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile must be made of 32x32 MFMA tiles");
-    static_assert(BK == 32 || BK == 64, "BK is 32 or 64");
+    static_assert(BK * ES == 64 || BK * ES == 128, "64 or 128 bytes of K per row");
     static_assert(BN % 64 == 0, "BN is a multiple of 64");
-    static_assert((BM * CA) % 64 == 0 && (BK * CB) % (64 * NW) == 0, "tile does not divide into whole load instructions");
-    static_assert(A_DMA == 1 || ((NW * ARD) % 16 == 0 && A_INSTR % NW == 0), "the A chunk permutation must not depend on the instruction");
+    static_assert((BM * CK) % 64 == 0 && B_INSTR % NW == 0, "tile does not divide into whole load instructions");
+    static_assert(A_DMA == 1 || ((NW * KRD) % 16 == 0 && A_INSTR % NW == 0), "the A chunk permutation must not depend on the instruction");
+    static_assert(!AKM || (BM % 64 == 0 && A_INSTR % NW == 0 && 64 % CM == 0 && (NW * (64 / CM)) % (F32 ? 8 : 4) == 0), "[k][m] tile shape");
+    static_assert(!BNK || (NW * KRD) % 16 == 0 || B_DMA == 1, "the B chunk permutation must not depend on the instruction");
     static_assert(BN / 8 <= NW * 64, "one column-scale entry per thread");
     static_assert(STAGES >= 2 && (STAGES - 2) * (A_DMA + B_DMA) < 64, "vmcnt range");
 
@@ -99,6 +166,8 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, OCC) void gemm_dma_kernel(P 
     const int wm0 = (wave / WAVES_N) * WM, wn0 = (wave % WAVES_N) * WN;
     const int lr = lane & 31, lh = lane >> 5;
     const long bstride = p.b_stride();
+    long astride = 0;
+    if constexpr (AKM) astride = p.a_stride();
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds_raw;
 
     const int nseg = K / KSEG;
@@ -125,61 +194,111 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, OCC) void gemm_dma_kernel(P 
 
     // Load roles.  Instruction i of this wave fills block (i*NW + wave) of 1 KiB in the A (or B)
     // part of a stage; lane -> slot (row, pos) inside the block.
+    // k-contiguous tiles: one pointer per instruction (rows NW*KRD apart), one chunk for all of them.
     const int a_blk0 = wave % A_INSTR;                              // + i*NW blocks
-    const int a_row0 = a_blk0 * ARD + lane / CA, a_pos = lane % CA; // + i*NW*ARD rows
-    const int a_chunk = a_pos ^ ((a_row0 / (16 / CA)) % CA);        // independent of i: NW*ARD % 16 == 0
-    const uint16_t *a_ptr[A_DMA];
+    const int a_row0 = a_blk0 * KRD + lane / CK, a_pos = lane % CK; // + i*NW*KRD rows
+    const int a_chunk = a_pos ^ ((a_row0 / (16 / CK)) % CK);        // independent of i: NW*KRD % 16 == 0
+    // [k][n] tiles: the permutation of the chunks of a row
+    auto kn_swizzle = [](int row, int width) {
+        return F32 ? ((row >> 2) & 1) << 3 : (width % 128 == 0 ? (row & 3) : ((row >> 1) & 1)) << 2;
+    };
     // When a B row is a whole fraction of one load instruction (and the permutation does not depend
     // on the instruction) a lane keeps one column for all its instructions: one base pointer.
-    constexpr bool B_UNIFORM = 64 % CB == 0 && (NW * (64 / CB)) % 4 == 0;
+    constexpr bool B_UNIFORM = !BNK && 64 % CN == 0 && (NW * (64 / CN)) % (F32 ? 8 : 4) == 0;
     constexpr int B_PTRS = B_UNIFORM ? 1 : B_DMA;
-    constexpr int BRD = B_UNIFORM ? 64 / CB : 0;         // B rows covered by one load instruction
-    const uint16_t *b_ptr[B_PTRS];
-    auto b_swizzle = [](int row) { return (BN % 128 == 0 ? (row & 3) : ((row >> 1) & 1)) << 2; };
-    auto resolve_segment = [&](int seg, uint32_t ctx) {
+    constexpr int BRD = B_UNIFORM ? 64 / CN : 0;         // B rows covered by one load instruction
+    constexpr int A_PTRS = AKM ? 1 : A_DMA, ARD = AKM ? 64 / CM : 0;
+    const E *a_ptr[A_PTRS], *b_ptr[B_PTRS];
+    int a_krow = 0, b_krow[B_PTRS];                      // first k row of the slot ([k][m], [k][n] tiles)
+    const int bnk_row0 = wave * KRD + lane / CK, bnk_chunk = (lane % CK) ^ ((bnk_row0 / (16 / CK)) % CK);
+    if constexpr (AKM) a_krow = (wave * 64 + lane) / CM;
 #pragma unroll
-        for (int i = 0; i < A_DMA; ++i) {
-            int row = m0 + a_row0 + i * NW * ARD;
-            row = row < M ? row : M - 1;
-            a_ptr[i] = reinterpret_cast<const uint16_t *>(p.a_ptr_ctx(g, row, seg, ctx)) + a_chunk * 8;
+    for (int i = 0; i < B_PTRS; ++i) b_krow[i] = BNK ? 0 : ((i * NW + wave) * 64 + lane) / CN;
+    auto resolve_segment = [&](int seg, uint32_t ctx) {
+        if constexpr (AKM) {
+            const int pos = (wave * 64 + lane) % CM;
+            int col = m0 + (pos ^ kn_swizzle(a_krow, BM)) * EP;
+            col = col < M ? col : m0;  // M tail: any valid chunk
+            a_ptr[0] = reinterpret_cast<const E *>(p.a_ptr_ctx(g, col, seg, ctx)) + (TAIL ? 0L : (long)a_krow * astride);
+        } else {
+#pragma unroll
+            for (int i = 0; i < A_PTRS; ++i) {
+                int row = m0 + a_row0 + i * NW * KRD;
+                row = row < M ? row : M - 1;
+                a_ptr[i] = reinterpret_cast<const E *>(p.a_ptr_ctx(g, row, seg, ctx)) + a_chunk * EP;
+            }
         }
 #pragma unroll
-        for (int i = 0; i < B_PTRS; ++i) {  // B slots in row-major order: slot -> (row, pos)
-            const int slot = (i * NW + wave) * 64 + lane;
-            const int row = slot / CB, pos = slot - row * CB;
-            int col = n0 + (pos ^ b_swizzle(row)) * 8;
-            col = col < N ? col : n0;  // N tail: any valid chunk
-            b_ptr[i] = reinterpret_cast<const uint16_t *>(p.b_ptr_ctx(g, seg, col, ctx)) + (long)row * bstride;
+        for (int i = 0; i < B_PTRS; ++i) {
+            if constexpr (BNK) {
+                int col = n0 + bnk_row0 + i * NW * KRD;
+                col = col < N ? col : N - 1;
+                b_ptr[i] = reinterpret_cast<const E *>(p.b_ptr_ctx(g, seg, col, ctx)) + bnk_chunk * EP;
+            } else {  // B slots in row-major order: slot -> (row, pos)
+                const int slot = (i * NW + wave) * 64 + lane;
+                const int row = slot / CN, pos = slot - row * CN;
+                int col = n0 + (pos ^ kn_swizzle(row, BN)) * EP;
+                col = col < N ? col : n0;  // N tail: any valid chunk
+                b_ptr[i] = reinterpret_cast<const E *>(p.b_ptr_ctx(g, seg, col, ctx)) + (TAIL ? 0L : (long)row * bstride);
+            }
+        }
+    };
+    // global addresses of load instruction i of the A / B tile for the K-step at offset `off` of the segment
+    auto a_addr = [&](int i, int off) -> const void * {
+        if constexpr (AKM) {
+            const int kr = off + i * NW * ARD + (TAIL ? a_krow : 0);
+            const E *at = a_ptr[0] + (long)kr * astride;
+            if constexpr (TAIL) return kr < KSEG ? (const void *)at : (const void *)gemm_zero_piece;
+            return at;
+        } else {
+            const E *at = a_ptr[i < A_PTRS ? i : 0] + off;
+            if constexpr (TAIL) return off + a_chunk * EP < KSEG ? (const void *)at : (const void *)gemm_zero_piece;
+            return at;
+        }
+    };
+    auto b_addr = [&](int i, int off) -> const void * {
+        if constexpr (BNK) {
+            if constexpr (TAIL) off = min(off, KSEG - EP - bnk_chunk * EP);   // the last piece of the segment again
+            return b_ptr[i < B_PTRS ? i : 0] + off;
+        } else {
+            int kr = off + (B_UNIFORM ? i * NW * BRD : 0);
+            if constexpr (TAIL) kr = min(kr + b_krow[B_UNIFORM ? 0 : (i < B_PTRS ? i : 0)], KSEG - 1);
+            return b_ptr[B_UNIFORM ? 0 : (i < B_PTRS ? i : 0)] + (long)kr * bstride;
         }
     };
     auto issue = [&](int buf, int off) {  // K-step at offset `off` of the current segment -> stage buffer buf
         const uint32_t sbase = lds_base + buf * STAGE_BYTES + wave * 1024;
 #pragma unroll
-        for (int i = 0; i < A_DMA; ++i) dma_load16(a_ptr[i] + off, sbase + (a_blk0 - wave + i * NW) * 1024);
+        for (int i = 0; i < A_DMA; ++i) dma_load16(a_addr(i, off), sbase + (a_blk0 - wave + i * NW) * 1024);
 #pragma unroll
-        for (int i = 0; i < B_DMA; ++i)
-            dma_load16(b_ptr[B_UNIFORM ? 0 : i] + (long)(off + (B_UNIFORM ? i * NW * BRD : 0)) * bstride,
-                       sbase + A_STAGE + i * NW * 1024);
+        for (int i = 0; i < B_DMA; ++i) dma_load16(b_addr(i, off), sbase + A_STAGE + i * NW * 1024);
     };
 
-    const int KT = K / BK;
+    const int KT = TAIL ? nseg * ((KSEG + BK - 1) / BK) : K / BK;
     int nseg_next = 0, noff = 0, nbuf = 0;  // segment / offset / buffer of the next K-step to fetch
+    auto seg_entry = [&](int seg) {
+        const int e = seg / PARTS;
+        return segtab[e < MAX_SEG ? e : 0];
+    };
+    auto advance = [&]() {
+        nbuf = nbuf + 1 == STAGES ? 0 : nbuf + 1;
+        noff += BK;
+        if (TAIL ? noff >= KSEG : noff == KSEG) {
+            noff = 0;
+            ++nseg_next;
+        }
+    };
     // The first STAGES-1 K-steps are fetched before anything else: their segments' contexts are
     // looked up directly (every lane the same address), so that the first operand bytes are only one
     // dependent load away from the kernel's start.  The lookup tables the loop and the epilogue use
     // are filled afterwards, under those loads, and published by the loop's first barrier.
     auto fetch_next = [&]() {
         if (noff == 0) {
-            if constexpr (P::kPrepare) resolve_segment(nseg_next, segtab[nseg_next < MAX_SEG ? nseg_next : 0]);
+            if constexpr (P::kPrepare) resolve_segment(nseg_next, seg_entry(nseg_next));
             else resolve_segment(nseg_next, p.seg_ctx(g, nseg_next));
         }
         issue(nbuf, noff);
-        nbuf = nbuf + 1 == STAGES ? 0 : nbuf + 1;
-        noff += BK;
-        if (noff == KSEG) {
-            noff = 0;
-            ++nseg_next;
-        }
+        advance();
     };
 #pragma unroll
     for (int s = 0; s < STAGES - 1; ++s)
@@ -188,16 +307,32 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, OCC) void gemm_dma_kernel(P 
     if (P::kColScale && tid < BN / 8) coltab[tid] = my_scale;
 
     // fragment read offsets (bytes inside a stage)
-    uint32_t a_off[BK / 16], b_off[TN];
+    constexpr int KS = BK * ES / 32;   // sub-steps: 16 k (bf16) or 8 k (fp32) each
+    uint32_t a_off[AKM ? TM : KS], b_off[BNK ? KS : TN];
     {
-        const int swz = (lr / (16 / CA)) % CA;
-#pragma unroll
-        for (int ks = 0; ks < BK / 16; ++ks) a_off[ks] = (wm0 + lr) * (BK * 2) + (((ks * 2 + lh) ^ swz) * 16);
+        const int swz = (lr / (16 / CK)) % CK;
         const int x = (lane & 15) >> 2, colhalf = (lane >> 4) & 1;
+        auto kn_off = [&](int first, int width) -> uint32_t {   // 32 columns from `first` of a [k][n] tile of this width
+            if constexpr (F32)
+                return lh * 4 * (width * 4) + ((((first + lr) / 4) ^ (lh << 3)) * 16) + (lr & 3) * 4;
+            else {
+                const int chunk = first / 8 + colhalf * 2 + ((lane & 3) >> 1);
+                return (lh * 8 + x) * (width * 2) + ((chunk ^ kn_swizzle(x, width)) * 16) + (lane & 1) * 8;
+            }
+        };
+        if constexpr (AKM) {
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int chunk = (wn0 + j * 32) / 8 + colhalf * 2 + ((lane & 3) >> 1);
-            b_off[j] = A_STAGE + (lh * 8 + x) * (BN * 2) + ((chunk ^ b_swizzle(x)) * 16) + (lane & 1) * 8;
+            for (int i = 0; i < TM; ++i) a_off[i] = kn_off(wm0 + i * 32, BM);
+        } else {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) a_off[ks] = (wm0 + lr) * (BK * ES) + (((ks * 2 + lh) ^ swz) * 16);
+        }
+        if constexpr (BNK) {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) b_off[ks] = A_STAGE + (wn0 + lr) * (BK * ES) + (((ks * 2 + lh) ^ swz) * 16);
+        } else {
+#pragma unroll
+            for (int j = 0; j < TN; ++j) b_off[j] = A_STAGE + kn_off(wn0 + j * 32, BN);
         }
     }
 
@@ -205,40 +340,49 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, OCC) void gemm_dma_kernel(P 
     // kt+STAGES-1 are issued in between: one 1 KiB load after every TN MFMAs, so that the
     // address path (64 bytes per clock per CU) drains them in the shadow of the matrix pipe instead
     // of stalling the wave in front of it.
-    constexpr int KS = BK / 16;
     constexpr int PIECES = A_DMA + B_DMA, SLOTS = KS * TM, PPS = (PIECES + SLOTS - 1) / SLOTS;
+    typedef typename std::conditional<F32, f32x4_t, bf16x8_t>::type frag_t;   // 16 bytes: 8 k of bf16 or 4 k of fp32
     int cbuf = 0;
     auto k_step = [&](auto fetch) {
         constexpr bool FETCH = decltype(fetch)::value;
         int f_off = 0;
         uint32_t f_base = 0;
         if constexpr (FETCH) {
-            if (noff == 0) resolve_segment(nseg_next, segtab[nseg_next < MAX_SEG ? nseg_next : 0]);
+            if (noff == 0) resolve_segment(nseg_next, seg_entry(nseg_next));
             f_off = noff;
             f_base = lds_base + nbuf * STAGE_BYTES + wave * 1024;
-            nbuf = nbuf + 1 == STAGES ? 0 : nbuf + 1;
-            noff += BK;
-            if (noff == KSEG) {
-                noff = 0;
-                ++nseg_next;
-            }
+            advance();
         }
         const unsigned char *st = lds_raw + cbuf * STAGE_BYTES;
         // Fragments are double-buffered in registers: the LDS reads of sub-step ks+1 are issued
         // before the MFMAs of sub-step ks, so their latency is covered by 32*TM*TN cycles of matrix
         // work of this same wave (at one or two waves per SIMD there is little else to cover it).
         // The scheduling fences keep the compiler from sinking the reads back down to their uses.
-        bf16x8_t af[2][TM], wf[2][TN];
+        frag_t af[2][TM], wf[2][TN];
+        auto kn_frag = [&](uint32_t off, int ks, int width) -> frag_t {   // 32 columns of a [k][n] tile, the k of sub-step ks
+            if constexpr (F32) {
+                const float *src = reinterpret_cast<const float *>(st + off + ks * 8 * width * 4);
+                frag_t f;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) f[e] = src[e * width];
+                return f;
+            } else {
+                const uint16_t *src = reinterpret_cast<const uint16_t *>(st + off + ks * 16 * width * 2);
+                const uint2 lo = lds_read_tr4(src);
+                const uint2 hi = lds_read_tr4(src + 4 * width);
+                return __builtin_bit_cast(frag_t, make_uint4(lo.x, lo.y, hi.x, hi.y));
+            }
+        };
         auto load_frags = [&](int ks, int slot) {
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
-                af[slot][i] = *reinterpret_cast<const bf16x8_t *>(st + a_off[ks] + i * 32 * BK * 2);
+            for (int i = 0; i < TM; ++i) {
+                if constexpr (AKM) af[slot][i] = kn_frag(a_off[i], ks, BM);
+                else af[slot][i] = *reinterpret_cast<const frag_t *>(st + a_off[ks] + i * 32 * BK * ES);
+            }
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
-                const uint16_t *src = reinterpret_cast<const uint16_t *>(st + b_off[j] + ks * 16 * BN * 2);
-                const uint2 lo = lds_read_tr4(src);
-                const uint2 hi = lds_read_tr4(src + 4 * BN);
-                wf[slot][j] = __builtin_bit_cast(bf16x8_t, make_uint4(lo.x, lo.y, hi.x, hi.y));
+                if constexpr (BNK) wf[slot][j] = *reinterpret_cast<const frag_t *>(st + b_off[ks] + j * 32 * BK * ES);
+                else wf[slot][j] = kn_frag(b_off[j], ks, BN);
             }
         };
         load_frags(0, 0);
@@ -249,17 +393,19 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, OCC) void gemm_dma_kernel(P 
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
 #pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[ks & 1][j], af[ks & 1][i], acc[i][j], 0, 0, 0);
+                for (int j = 0; j < TN; ++j) {
+                    if constexpr (F32) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(wf[ks & 1][j][e], af[ks & 1][i][e], acc[i][j], 0, 0, 0);
+                    } else acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[ks & 1][j], af[ks & 1][i], acc[i][j], 0, 0, 0);
+                }
                 if constexpr (FETCH) {
 #pragma unroll
                     for (int u = 0; u < PPS; ++u) {
                         const int q = (ks * TM + i) * PPS + u;  // compile-time after unrolling
-                        if (q < A_DMA) dma_load16(a_ptr[q < A_DMA ? q : 0] + f_off, f_base + (a_blk0 - wave + q * NW) * 1024);
-                        else if (q < PIECES)
-                            dma_load16(b_ptr[!B_UNIFORM && q >= A_DMA && q < PIECES ? q - A_DMA : 0] +
-                                           (long)(f_off + (B_UNIFORM ? (q - A_DMA) * NW * BRD : 0)) * bstride,
-                                       f_base + A_STAGE + (q - A_DMA) * NW * 1024);
+                        if (q < A_DMA) dma_load16(a_addr(q < A_DMA ? q : 0, f_off), f_base + (a_blk0 - wave + q * NW) * 1024);
+                        else if (q < PIECES) dma_load16(b_addr(q >= A_DMA ? q - A_DMA : 0, f_off), f_base + A_STAGE + (q - A_DMA) * NW * 1024);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -283,11 +429,15 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, OCC) void gemm_dma_kernel(P 
     }
     __syncthreads();  // every wave has finished reading operands: LDS is free for the epilogue
 
-    uint16_t(*stage)[SPITCH] = reinterpret_cast<uint16_t(*)[SPITCH]>(lds_raw) + (size_t)wave * WM;
-    wave_epilogue<P, TM, TN, SPITCH>(p, acc, stage, coltab, rs, g, m0 + wm0, n0 + wn0, wn0, M, N, lane);
+    if constexpr (F32) {
+        wave_epilogue_f32<P, TM, TN>(p, acc, coltab, rs, g, m0 + wm0, n0 + wn0, wn0, M, N, lane);
+    } else {
+        uint16_t(*stage)[SPITCH] = reinterpret_cast<uint16_t(*)[SPITCH]>(lds_raw) + (size_t)wave * WM;
+        wave_epilogue<P, TM, TN, SPITCH>(p, acc, stage, coltab, rs, g, m0 + wm0, n0 + wn0, wn0, M, N, lane);
+    }
 }
 
-template <typename P, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int OCC = 1>
+template <typename P, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int OCC = 1, int FLAGS = 0>
 static hipError_t launch_gemm_dma(const P &p, int groups, int max_rows, int ncols, hipStream_t st)
 {
     if (groups <= 0 || max_rows <= 0 || ncols <= 0) return hipSuccess;
@@ -298,9 +448,34 @@ static hipError_t launch_gemm_dma(const P &p, int groups, int max_rows, int ncol
     if (total > (1L << 28)) return hipErrorInvalidValue;
     tg.total = (int)total;
     tg.per_xcd = (tg.total + 7) / 8;
-    hipLaunchKernelGGL((gemm_dma_kernel<P, BM, BN, BK, WAVES_M, WAVES_N, STAGES, OCC>), dim3(tg.per_xcd * 8),
+    hipLaunchKernelGGL((gemm_dma_kernel<P, BM, BN, BK, WAVES_M, WAVES_N, STAGES, OCC, FLAGS>), dim3(tg.per_xcd * 8),
                        dim3(WAVES_M * WAVES_N * 64), 0, st, p, tg);
     return hipGetLastError();
+}
+
+// Tile choice of the GEMM_TAIL variants: bf16 with widths or token counts that no K-step divides, and everything in fp32.
+// FLAGS: operand layouts.  128x128 tiles once they give every compute unit one (fewer operand bytes per product),
+// 64-row tiles below that, 32-row tiles where groups are that short (and in fp32 while 64x64 tiles would leave
+// compute units without work).  Against the vector-ALU engine these variants replace (64x64x8 tiles, one load and
+// two barriers per eight k): UoME up with 6 x 1000 tokens, d 360, 3 x 232 hidden columns in bf16 63 -> 14 us, the
+// lm shape's in fp32 (4096 x 512 x 1024) 82 -> 46 us (93 TFLOP/s; bound by the fp32 matrix instruction), the tiny
+// shape's 11.6 -> 5.8 us.
+template <int FLAGS, typename P> static hipError_t launch_gemm_tail(const P &p, int groups, int rows, int ncols, hipStream_t st)
+{
+    constexpr int F = FLAGS | GEMM_TAIL;
+    const long tiles128 = (long)groups * ((rows + 127) / 128) * ((ncols + 127) / 128);
+    if constexpr (std::is_same<typename elem_of<P>::type, float>::value) {
+        if (rows > 64 && tiles128 >= 256) return launch_gemm_dma<P, 128, 128, 16, 2, 2, 3, 2, F>(p, groups, rows, ncols, st);
+        if constexpr (!(FLAGS & GEMM_A_KM))
+            if (rows <= 32 || (long)groups * ((rows + 63) / 64) * ((ncols + 63) / 64) < 256)
+                return launch_gemm_dma<P, 32, 64, 32, 1, 2, 4, 2, F>(p, groups, rows, ncols, st);
+        return launch_gemm_dma<P, 64, 64, 32, 2, 2, 3, 2, F>(p, groups, rows, ncols, st);
+    } else {
+        if (rows > 64 && tiles128 >= 256) return launch_gemm_dma<P, 128, 128, 32, 2, 2, 4, 2, F>(p, groups, rows, ncols, st);
+        if constexpr (!(FLAGS & GEMM_A_KM))
+            if (rows <= 32) return launch_gemm_dma<P, 32, 128, 32, 1, 4, 4, 2, F>(p, groups, rows, ncols, st);
+        return launch_gemm_dma<P, 64, 128, 32, 2, 2, 4, 2, F>(p, groups, rows, ncols, st);
+    }
 }
 
 // Tile choice for contractions without a tuned rule of their own (the backward passes): the large

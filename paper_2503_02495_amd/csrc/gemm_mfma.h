@@ -35,6 +35,7 @@
 namespace uoe {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 typedef s16x4_t __attribute__((address_space(3))) * lds_s16x4_ptr;
@@ -166,7 +167,6 @@ __device__ __forceinline__ void wave_epilogue(const P &p, f32x16_t (&acc)[TM][TN
                                               const float (&rs)[TM], int g, int grow0, int gcol0, int wcol0, int M, int N,
                                               int lane)
 {
-    constexpr int WM = TM * 32, WN = TN * 32;
     const int lr = lane & 31, lh = lane >> 5;
     if constexpr (writes_f32<P>::value) {
         // a lane holds 4 consecutive columns of one row per register quad: 16-byte stores; the two

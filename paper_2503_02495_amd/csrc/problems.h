@@ -7,9 +7,9 @@
 //   a_seg_ptr(g, m, seg)   pointer to A[m][seg*kseg]; the segment's kseg elements are contiguous
 //   b_seg_ptr(g, seg, nn)  pointer to B[seg*kseg][nn..nn+8)  (nn % 8 == 0)
 //   b_stride()             elements between consecutive K rows of B inside a segment
-//   col_ctx(g, nn)   whatever the epilogue needs that depends on the column only
-//   store(g, m, nn, v, ctx) epilogue for one element
-// and, for the MFMA engines (which write 16-byte pieces of output rows),
+// the fp32 form of the pipelined engine writes four columns of a row at a time:
+//   epi_f32(v, scale), put4(g, m, nn, v4)   per-element math; the store (residual included)
+// and the bf16 engines 16-byte pieces of output rows:
 //   kColScale / col_scale(g, nn)  a per-column factor (constant over 8-column groups), fetched
 //                                 once per tile before the K loop
 //   epi(v, scale)                 per-element math
@@ -34,6 +34,20 @@
 
 namespace uoe {
 
+// what the engines call the elements of a storage type
+template <typename T> struct storage_elem {
+    typedef uint16_t type;
+};
+template <> struct storage_elem<float> {
+    typedef float type;
+};
+
+__device__ __forceinline__ float4 add4_f32(float4 a, const float *r)
+{
+    const float4 b = *reinterpret_cast<const float4 *>(r);
+    return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
+}
+
 // 8 bf16 (one 16-byte piece of an output row) + 8 bf16 of a residual row, added in fp32
 __device__ __forceinline__ uint4 add8_bf16(uint4 v, uint4 r)
 {
@@ -53,6 +67,7 @@ __device__ __forceinline__ uint4 add8_bf16(uint4 v, uint4 r)
 // group = active unit (b, slot s); M = l_a; K = d; N = 3*d_h laid out [q | k | v].
 // F32: the single-projection form (nout = 1) stores fp32 rows into q32 instead.
 template <typename T, bool F32 = false> struct QkvProblem {
+    typedef typename storage_elem<T>::type Elem;
     const T *x, *wq, *wk, *wv;
     const int32_t *expert_idx, *patch_idx;
     T *q, *k, *v;  // [units, l_a, d_h]
@@ -63,14 +78,16 @@ template <typename T, bool F32 = false> struct QkvProblem {
         *reinterpret_cast<float4 *>(q32 + ((size_t)g * l_a + r) * d_h + nn) = val;
     }
     int l, d, n, kact, m, c, l_p, l_a, d_h;
+    int d_hp;       // row length of q, k and v: d_h, or d_h padded to what the attention kernel takes (the columns behind
+                    // d_h are written as zeros)
     float q_scale;  // folded into q on the way out (1 for the plain layout)
     int nout;       // 3: q, k and v; 1: the first projection only (N = d_h)
     int v_f16 = 0;  // MFMA engines, bf16 storage: v is written as fp16 (what the attention kernel's P V product takes)
-    __device__ bool f16_col(int nn) const { return v_f16 && nn >= 2 * d_h; }
+    __device__ bool f16_col(int nn) const { return v_f16 && nn >= 2 * d_hp; }
 
     __device__ int rows(int) const { return l_a; }
     __device__ int kdim(int) const { return d; }
-    __device__ int ncols() const { return nout * d_h; }
+    __device__ int ncols() const { return nout * d_hp; }
     __device__ int expert(int g) const { return clampi(expert_idx[g], n); }
     __device__ int token(int g, int r) const
     {
@@ -89,25 +106,17 @@ template <typename T, bool F32 = false> struct QkvProblem {
     __device__ const T *b_seg_ptr(int g, int, int nn) const
     {
         const int i = expert(g);
-        const int which = nn / d_h, col = nn - which * d_h;
+        const int which = nn / d_hp, at = nn - which * d_hp, col = at < d_h ? at : 0;   // behind d_h: any valid piece, its products are dropped
         const T *w = which == 0 ? wq : (which == 1 ? wk : wv);
         return w + (size_t)i * d * d_h + col;
     }
-    struct ColCtx {
-        int which, col;
-    };
-    __device__ ColCtx col_ctx(int, int nn) const
+    __device__ float epi_f32(float val, float scale) const { return val * scale; }
+    __device__ void put4(int g, int r, int nn, float4 val) const
     {
-        ColCtx cc;
-        cc.which = nn / d_h;
-        cc.col = nn - cc.which * d_h;
-        return cc;
-    }
-    __device__ void store(int g, int r, int, float val, const ColCtx &cc) const
-    {
-        if (cc.which == 0) q[((size_t)g * l_a + r) * d_h + cc.col] = from_f32<T>(val * q_scale);
-        else if (cc.which == 1) k[((size_t)g * l_a + r) * d_h + cc.col] = from_f32<T>(val);
-        else v[((size_t)g * l_a + r) * d_h + cc.col] = from_f32<T>(val);
+        const int which = nn / d_hp, col = nn - which * d_hp;
+        T *o = which == 0 ? q : (which == 1 ? k : v);
+        if (col >= d_h) val = make_float4(0.f, 0.f, 0.f, 0.f);
+        *reinterpret_cast<float4 *>(o + ((size_t)g * l_a + r) * d_hp + col) = val;
     }
     // pipelined engine: K is one segment, rows and columns are resolved once before the loop
     __device__ uint32_t seg_ctx(int, int) const { return 0; }
@@ -117,15 +126,16 @@ template <typename T, bool F32 = false> struct QkvProblem {
     static constexpr bool kPrepare = false;
     static constexpr bool kRowScale = false;
     static constexpr bool kColScale = true;
-    __device__ float col_scale(int, int nn) const { return nn < d_h ? q_scale : 1.0f; }
+    __device__ float col_scale(int, int nn) const { return nn < d_hp ? q_scale : 1.0f; }
     __device__ float epi(float val, float scale) const { return val * scale; }
     __device__ bool has_residual() const { return false; }
     __device__ uint4 res8(int, int, int) const { return make_uint4(0, 0, 0, 0); }
     __device__ void put8(int g, int r, int nn, uint4 piece) const
     {
-        const int which = nn / d_h, col = nn - which * d_h;
+        const int which = nn / d_hp, col = nn - which * d_hp;
         T *o = which == 0 ? q : (which == 1 ? k : v);
-        *reinterpret_cast<uint4 *>(o + ((size_t)g * l_a + r) * d_h + col) = piece;
+        if (col >= d_h) piece = make_uint4(0, 0, 0, 0);
+        *reinterpret_cast<uint4 *>(o + ((size_t)g * l_a + r) * d_hp + col) = piece;
     }
 };
 
@@ -138,44 +148,27 @@ template <typename T, bool F32 = false> struct QkvProblem {
 // buffers, o = hi + lo, so that the attention output enters this contraction with ~16 significant
 // bits instead of 8 (the rows of W^o are simply visited twice).
 template <typename T> struct OutProjProblem {
+    typedef typename storage_elem<T>::type Elem;
     bool once = false;   // this launch streams its output (and residual) past the caches: see store16, wave_write_out
     const T *o, *o_lo, *wo, *x;
-    const int32_t *expert_idx, *patch_idx, *inv_cnt, *inv_ent;  // inv_*: engines without prepare()
+    const int32_t *expert_idx, *patch_idx;
     T *out;
     int l, d, n, kact, m, c, l_p, l_a, d_h;
+    int o_row;  // elements between rows of o (d_h, or more when its rows are padded)
     int parts;  // 1: o only; 2: o is a (hi, lo) pair of buffers, contracted as [hi | lo] x [W^o ; W^o]
     uint32_t flags;
 
     __device__ int rows(int) const { return l_p; }
-    __device__ int kdim(int g) const { return inv_cnt[g] * parts * d_h; }
+    __device__ int kdim(int) const { return 0; }  // prepare() supplies K
     __device__ int ncols() const { return d; }
     __device__ int kseg() const { return d_h; }
     __device__ long b_stride() const { return d; }
-    __device__ const T *a_seg_ptr(int g, int r, int seg) const
+    __device__ float epi_f32(float val, float) const { return val; }
+    __device__ void put4(int g, int r, int nn, float4 val) const
     {
-        const int bb = g / m;
-        const int e = clampi(parts == 2 ? seg >> 1 : seg, kact);
-        const T *src = (parts == 2 && (seg & 1)) ? o_lo : o;
-        const int ent = clampi(inv_ent[(size_t)g * kact + e], kact * c);  // slot s * c + pick t
-        const int s = ent / c, t = ent - s * c;
-        return src + (((size_t)bb * kact + s) * l_a + t * l_p + r) * d_h;
-    }
-    __device__ const T *b_seg_ptr(int g, int seg, int nn) const
-    {
-        const int bb = g / m;
-        const int e = clampi(parts == 2 ? seg >> 1 : seg, kact);
-        const int s = clampi(inv_ent[(size_t)g * kact + e], kact * c) / c;
-        const int i = clampi(expert_idx[bb * kact + s], n);
-        return wo + (size_t)i * d_h * d + nn;
-    }
-    typedef int ColCtx;
-    __device__ ColCtx col_ctx(int, int) const { return 0; }
-    __device__ void store(int g, int r, int nn, float val, const ColCtx &) const
-    {
-        const int bb = g / m, p = g - bb * m;
-        const size_t at = ((size_t)bb * l + p * l_p + r) * d + nn;
-        if (flags & F_RESIDUAL) val += to_f32(x[at]);
-        out[at] = from_f32<T>(val);
+        const size_t at = at8(g, r, nn);
+        if (flags & F_RESIDUAL) val = add4_f32(val, reinterpret_cast<const float *>(x) + at);
+        *reinterpret_cast<float4 *>(out + at) = val;
     }
     // pipelined engine: per K segment, (slot*c + pick) in bits 0-19, the expert in bits 20-25 and the
     // hi/lo part in bit 26 (needs kact*c < 2^20).  The workgroup builds the list of its group's
@@ -209,21 +202,14 @@ template <typename T> struct OutProjProblem {
         __syncthreads();
         return cnt * parts * d_h;
     }
-    __device__ uint32_t seg_ctx(int g, int seg) const
-    {
-        const int bb = g / m;
-        const int e = clampi(parts == 2 ? seg >> 1 : seg, kact);
-        const int ent = clampi(inv_ent[(size_t)g * kact + e], kact * c);
-        const int i = clampi(expert_idx[bb * kact + ent / c], n);
-        return (uint32_t)ent | ((uint32_t)i << 20) | ((parts == 2 && (seg & 1)) ? 1u << 26 : 0u);
-    }
+    __device__ uint32_t seg_ctx(int, int) const { return 0; }
     __device__ const T *a_ptr_ctx(int g, int r, int, uint32_t ctx) const
     {
         const int bb = g / m;
         const int ent = (int)(ctx & 0xFFFFFu);
         const int s = ent / c, t = ent - s * c;
         const T *src = (ctx >> 26) & 1u ? o_lo : o;
-        return src + (((size_t)bb * kact + s) * l_a + t * l_p + r) * d_h;
+        return src + (((size_t)bb * kact + s) * l_a + t * l_p + r) * o_row;
     }
     __device__ const T *b_ptr_ctx(int, int, int nn, uint32_t ctx) const { return wo + (size_t)((ctx >> 20) & 0x3Fu) * d_h * d + nn; }
     static constexpr bool kColScale = false;
@@ -246,6 +232,7 @@ template <typename T> struct OutProjProblem {
 // UoME Eq. 38: group = sample b; M = l; K = d; N = k*d_e (the sample's active experts side by
 // side); epilogue SiLU and the expert's gate.
 template <typename T, bool RAW = false> struct UomeUpProblem {
+    typedef typename storage_elem<T>::type Elem;
     bool once = false;   // this launch streams its output (and residual) past the caches: see store16, wave_write_out
     const T *u, *a_in;
     const int32_t *expert_idx;
@@ -271,20 +258,19 @@ template <typename T, bool RAW = false> struct UomeUpProblem {
     __device__ uint32_t seg_ctx(int, int) const { return 0; }
     __device__ const T *a_ptr_ctx(int g, int r, int seg, uint32_t) const { return a_seg_ptr(g, r, seg); }
     __device__ const T *b_ptr_ctx(int g, int seg, int nn, uint32_t) const { return b_seg_ptr(g, seg, nn); }
-    typedef float ColCtx;  // the gate of the column's expert
-    __device__ ColCtx col_ctx(int g, int nn) const
+    __device__ float epi_f32(float val, float gate) const { return raw ? val : silu(val) * gate; }
+    __device__ void put4(int g, int r, int nn, float4 val) const
     {
-        if (!expert_gate || raw) return 1.0f;
-        return expert_gate[(size_t)g * n + clampi(expert_idx[g * kact + nn / d_e], n)];
-    }
-    __device__ void store(int g, int r, int nn, float val, const ColCtx &gate) const
-    {
-        hidden[((size_t)g * l + r) * ((size_t)kact * d_e) + nn] = from_f32<T>(raw ? val : silu(val) * gate);
+        *reinterpret_cast<float4 *>(hidden + ((size_t)g * l + r) * ((size_t)kact * d_e) + nn) = val;
     }
     static constexpr bool kPrepare = false;
     static constexpr bool kRowScale = false;
     static constexpr bool kColScale = true;
-    __device__ float col_scale(int g, int nn) const { return col_ctx(g, nn); }
+    __device__ float col_scale(int g, int nn) const   // the gate of the column's expert
+    {
+        if (!expert_gate || raw) return 1.0f;
+        return expert_gate[(size_t)g * n + clampi(expert_idx[g * kact + nn / d_e], n)];
+    }
     __device__ float epi(float val, float gate) const { return raw ? val : silu_fast(val) * gate; }
     __device__ bool has_residual() const { return false; }
     __device__ uint4 res8(int, int, int) const { return make_uint4(0, 0, 0, 0); }
@@ -302,6 +288,7 @@ template <typename T, bool RAW = false> struct UomeUpProblem {
 // gate and/or the gate of the row's patch): the second layer is linear, so the weight can ride on
 // the hidden activations and the output-stationary second GEMM needs no per-segment scale.
 template <typename T> struct UomeDsUpProblem {
+    typedef typename storage_elem<T>::type Elem;
     const T *u, *a_in;
     const int32_t *expert_idx, *patch_idx;
     const float *expert_gate, *patch_gate;  // NULL: weight 1
@@ -330,11 +317,10 @@ template <typename T> struct UomeDsUpProblem {
         if (patch_gate) w *= patch_gate[((size_t)bb * n + i) * m + patch(g, r)];
         return w;
     }
-    typedef int ColCtx;
-    __device__ ColCtx col_ctx(int, int) const { return 0; }
-    __device__ void store(int g, int r, int nn, float val, const ColCtx &) const
+    __device__ float epi_f32(float val, float w) const { return silu(val) * w; }
+    __device__ void put4(int g, int r, int nn, float4 val) const
     {
-        hidden[((size_t)g * l_a + r) * d_e + nn] = from_f32<T>(silu(val) * row_scale(g, r));
+        *reinterpret_cast<float4 *>(hidden + ((size_t)g * l_a + r) * d_e + nn) = val;
     }
     __device__ uint32_t seg_ctx(int, int) const { return 0; }
     __device__ const T *a_ptr_ctx(int g, int r, int seg, uint32_t) const { return a_seg_ptr(g, r, seg); }
@@ -355,6 +341,7 @@ template <typename T> struct UomeDsUpProblem {
 // UoME Eq. 39 + Eq. 40: group = sample b; M = l; K = k*d_e (row slices of A^O of the active
 // experts stacked); N = d; epilogue adds the residual.  One write per output element.
 template <typename T> struct UomeDownProblem {
+    typedef typename storage_elem<T>::type Elem;
     bool once = false;   // this launch streams its output (and residual) past the caches: see store16, wave_write_out
     const T *hidden, *a_out, *u;
     const int32_t *expert_idx;
@@ -380,13 +367,12 @@ template <typename T> struct UomeDownProblem {
     __device__ uint32_t seg_ctx(int g, int seg) const { return (uint32_t)clampi(expert_idx[g * kact + clampi(seg, kact)], n); }
     __device__ const T *a_ptr_ctx(int g, int r, int seg, uint32_t) const { return a_seg_ptr(g, r, seg); }
     __device__ const T *b_ptr_ctx(int, int, int nn, uint32_t i) const { return a_out + (size_t)i * d_e * d + nn; }
-    typedef int ColCtx;
-    __device__ ColCtx col_ctx(int, int) const { return 0; }
-    __device__ void store(int g, int r, int nn, float val, const ColCtx &) const
+    __device__ float epi_f32(float val, float) const { return val; }
+    __device__ void put4(int g, int r, int nn, float4 val) const
     {
         const size_t at = ((size_t)g * l + r) * d + nn;
-        if (flags & F_RESIDUAL) val += to_f32(u[at]);
-        out[at] = from_f32<T>(val);
+        if (flags & F_RESIDUAL) val = add4_f32(val, reinterpret_cast<const float *>(u) + at);
+        *reinterpret_cast<float4 *>(out + at) = val;
     }
     static constexpr bool kPrepare = false;
     static constexpr bool kRowScale = false;

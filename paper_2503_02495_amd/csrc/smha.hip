@@ -1,8 +1,6 @@
 // Selective Multi-Head Attention on given routing results (Eq. 27-36).
 //
 // Pipeline per call (all on one stream):
-//   smha_inverse_map : for each (sample, patch) the list of (active slot s, pick t) that chose
-//                      it -- the transpose of patch_idx restricted to active experts.
 //   QKV projection   : grouped GEMM over active units, Eq. 18 gather folded into the A rows.
 //   attention        : softmax(q k^T / sqrt(d_h)) v per unit over its l_a tokens (Eq. 33-34),
 //                      rows scaled by their gate weight on the way out.
@@ -11,48 +9,10 @@
 //                      each output row once, residual included (Eq. 35-36).
 #include "common.h"
 #include "problems.h"
-#include "gemm_generic.h"
 #include "gemm_mfma.h"
 #include "gemm_dma.h"
 
 namespace uoe {
-
-// Inverse map, one workgroup per sample.  Phase 1: one thread per (active slot s, pick t) writes
-// t into an LDS table slot_of[s][patch].  Phase 2: one thread per patch walks the k slots in
-// order and lists the (s, t) pairs that chose it, so the list order (and with it the summation
-// order of the out-projection) is fixed.
-__global__ __launch_bounds__(256) void smha_inverse_map_kernel(SmhaArgs a)
-{
-    extern __shared__ __align__(16) unsigned char smem[];
-    int16_t *slot_of = reinterpret_cast<int16_t *>(smem);  // [k][m], -1 = not picked
-    const int bb = blockIdx.x, tid = threadIdx.x;
-    const int km = a.k * a.m, kc = a.k * a.c;
-    for (int idx = tid; idx < km; idx += 256) slot_of[idx] = -1;
-    __syncthreads();
-    for (int idx = tid; idx < kc; idx += 256) {
-        const int s = idx / a.c, t = idx - s * a.c;
-        const int i = clampi(a.expert_idx[bb * a.k + s], a.n);
-        const int p = clampi(a.patch_idx[((size_t)bb * a.n + i) * a.c + t], a.m);
-        slot_of[s * a.m + p] = (int16_t)t;
-    }
-    __syncthreads();
-    for (int p = tid; p < a.m; p += 256) {
-        const size_t g = (size_t)bb * a.m + p;
-        int cnt = 0;
-        for (int s = 0; s < a.k; ++s) {
-            const int t = slot_of[s * a.m + p];
-            if (t >= 0) a.inv_ent[g * a.k + cnt++] = s * a.c + t;
-        }
-        a.inv_cnt[g] = cnt;
-    }
-}
-
-static hipError_t launch_inverse_map(const SmhaArgs &a, hipStream_t st)
-{
-    const size_t sh = (size_t)a.k * a.m * sizeof(int16_t);  // <= 32 * 1024 * 2 = 64 KiB
-    hipLaunchKernelGGL(smha_inverse_map_kernel, dim3(a.b), dim3(256), sh, st, a);
-    return hipGetLastError();
-}
 
 // Partial RoPE of Eq. 32, in place on the q and k workspaces: the last rope_dim dims of a head are
 // rotated in adjacent pairs (2i, 2i+1) by position * 10000^(-2i/rope_dim); the position of a row
@@ -69,7 +29,7 @@ template <typename T> __global__ __launch_bounds__(256) void smha_rope_kernel(Sm
     const float theta = exp2f(-(2.0f * (float)i / (float)a.rope_dim) * 13.287712379549449f);  // log2(10000)
     float sn, cs;
     sincosf((float)r * theta, &sn, &cs);
-    const size_t at = (size_t)row * a.d_h + (a.d_h - a.rope_dim) + 2 * i;
+    const size_t at = (size_t)row * a.d_hp + (a.d_h - a.rope_dim) + 2 * i;
     T *q = static_cast<T *>(a.q) + at, *k = static_cast<T *>(a.kk) + at;
     const float q0 = to_f32(q[0]), q1 = to_f32(q[1]), k0 = to_f32(k[0]), k1 = to_f32(k[1]);
     q[0] = from_f32<T>(q0 * cs - q1 * sn);
@@ -94,87 +54,222 @@ __device__ __forceinline__ bool key_is_token(const SmhaArgs &a, int g, int key, 
     return a.pad_mask[(size_t)bb * a.l + p * l_p + key % l_p] != 0;
 }
 
-// Vector-ALU attention: one thread per query row, keys/values staged through LDS in tiles,
-// online softmax in fp32.  DH is d_h rounded up to a supported register-array size.
-template <typename T, int DH>
-__global__ __launch_bounds__(128) void attention_generic_kernel(SmhaArgs a)
+// Attention with fp32 operands (Eq. 33-34): fp32 storage at any head width (and bf16 units too long for the
+// 32-bit offsets of the bf16 kernels).  One wave owns 32 query rows of one unit and walks key tiles of
+// 32, online softmax in base 2.  Both products run on v_mfma_f32_32x32x2_f32: exact fp32 products, and what
+// the vector-ALU kernel before it spent per score, d_h multiply-adds and as many LDS reads for every lane, is
+// one instruction per two keys or head dims for 1024 scores (lm shape in fp32, 32 units of 128 rows, d_h
+// 64: 187 us with one thread per query row, which put 64 waves on the chip, 15 us here).
+// Layout as in the bf16 kernel: the scores are computed transposed, S^T = K Q^T, so that a lane holds one query;
+// accumulator register q is key (q/4)*8 + lh*4 + q%4, and since an operand of this MFMA is one value per lane
+// with the lane half as its k, register q IS the operand P^T of the pair of keys it holds: no packing.  V is
+// read with the same key order.  K rows are padded by 4 floats (16-byte fragment reads of 16 consecutive rows
+// hit all banks once), V rows by 8 (the half-waves' rows are 4 apart: 32 banks).
+// KSPLIT waves share a query block and take key tiles KSPLIT apart (merged through LDS) so that short grids
+// still give most SIMDs a wave.
+template <typename T, int DH, int NQ, int KSPLIT>
+__global__ __launch_bounds__(NQ *KSPLIT * 64) void attention_f32_kernel(SmhaArgs a)
 {
-    constexpr int KT = 32;  // keys per LDS tile
-    __shared__ float ks[KT][DH + 1];
-    __shared__ float vs[KT][DH + 1];
-    __shared__ unsigned char km[KT];  // key admissible under the padding mask
-    const int g = blockIdx.y;  // unit
-    const int l_p = a.l / a.m, l_a = a.c * l_p, d_h = a.d_h;
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    const bool live = r < l_a;
-    const T *q = static_cast<const T *>(a.q) + (size_t)g * l_a * d_h;
-    const T *kp = static_cast<const T *>(a.kk) + (size_t)g * l_a * d_h;
-    const T *vp = static_cast<const T *>(a.v) + (size_t)g * l_a * d_h;
-    const float scale = rsqrtf((float)d_h);
+    constexpr int BT = 32, KP = DH + 4, VP = DH + 8, NTH = NQ * 64;   // NTH: threads that stage one split's tiles
+    constexpr int EP = 16 / sizeof(T), CHUNKS = BT * DH / EP, PER_T = (CHUNKS + NTH - 1) / NTH;
+    constexpr int SPLIT_FLOATS = BT * KP + BT * VP + BT;
+    constexpr int SLOT = DH / 2 + 2, MERGE_FLOATS = (KSPLIT - 1) * NQ * 64 * SLOT;
+    constexpr int LDS_FLOATS = KSPLIT * SPLIT_FLOATS > MERGE_FLOATS ? KSPLIT * SPLIT_FLOATS : MERGE_FLOATS;
+    __shared__ __align__(16) float lds[LDS_FLOATS];
 
-    float qr[DH], acc[DH];
+    const int l_p = a.l / a.m, l_a = a.c * l_p, d_h = a.d_h, g = blockIdx.y;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int split = wave / NQ, qg = wave - split * NQ, stid = tid - split * NTH;
+    const int lr = lane & 31, lh = lane >> 5;
+    const int qrow = blockIdx.x * (32 * NQ) + qg * 32 + lr;
+    float *Ks = lds + split * SPLIT_FLOATS, *Vs = Ks + BT * KP, *Km = Vs + BT * VP;   // Km: 1 = admissible key
+    const size_t ubase = (size_t)g * l_a * d_h;
+    const T *Q = static_cast<const T *>(a.q) + ubase, *Kg = static_cast<const T *>(a.kk) + ubase, *Vg = static_cast<const T *>(a.v) + ubase;
+
+    const float scale = 1.4426950408889634f * rsqrtf((float)d_h);   // base-2 softmax
+    float qf[DH / 8][4];
 #pragma unroll
-    for (int e = 0; e < DH; ++e) {
-        qr[e] = (live && e < d_h) ? to_f32(q[(size_t)r * d_h + e]) * scale : 0.f;
-        acc[e] = 0.f;
-    }
-    float mx = -INFINITY, den = 0.f;
-    const bool causal = (a.flags & F_CAUSAL) != 0;
-    // under the causal mask no row of this block sees keys past the block's last row
-    const int key_end = causal ? min(l_a, (int)((blockIdx.x + 1) * blockDim.x)) : l_a;
-
-    for (int j0 = 0; j0 < key_end; j0 += KT) {
-        const int jn = min(KT, l_a - j0);
-        if (threadIdx.x < KT)
-            km[threadIdx.x] = (threadIdx.x < jn) && (!a.pad_mask || key_is_token(a, g, j0 + threadIdx.x, l_p));
-        for (int idx = threadIdx.x; idx < KT * DH; idx += blockDim.x) {
-            const int jj = idx / DH, e = idx - jj * DH;
-            const bool ok = jj < jn && e < d_h;
-            ks[jj][e] = ok ? to_f32(kp[(size_t)(j0 + jj) * d_h + e]) : 0.f;
-            vs[jj][e] = ok ? to_f32(vp[(size_t)(j0 + jj) * d_h + e]) : 0.f;
+    for (int ks = 0; ks < DH / 8; ++ks)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int dh = ks * 8 + lh * 4 + e;
+            qf[ks][e] = (qrow < l_a && dh < d_h) ? to_f32(Q[(size_t)qrow * d_h + dh]) * scale : 0.f;
         }
-        __syncthreads();
-        if (live) {
-            for (int jj = 0; jj < jn; ++jj) {
-                if (!km[jj] || (causal && j0 + jj > r)) continue;  // masked key
-                float s = 0.f;
+    f32x16_t oacc[DH / 32];
 #pragma unroll
-                for (int e = 0; e < DH; ++e) s = fmaf(qr[e], ks[jj][e], s);
-                const float nmx = fmaxf(mx, s);
-                const float corr = __expf(mx - nmx);  // exp(-inf) = 0 on the first key
-                const float pw = __expf(s - nmx);
-                den = den * corr + pw;
+    for (int t = 0; t < DH / 32; ++t)
 #pragma unroll
-                for (int e = 0; e < DH; ++e) acc[e] = fmaf(acc[e], corr, pw * vs[jj][e]);
-                mx = nmx;
+        for (int q = 0; q < 16; ++q) oacc[t][q] = 0.f;
+    float mrun = -INFINITY, lsum = 0.f;
+    const bool causal = (a.flags & F_CAUSAL) != 0;
+    // under the causal mask no query of this workgroup sees keys past its last row
+    const int key_end = causal ? min(l_a, (int)(blockIdx.x + 1) * 32 * NQ) : l_a;
+    const int nkt = (key_end + BT - 1) / BT, nit = (nkt + KSPLIT - 1) / KSPLIT;
+
+    uint4 kr[PER_T], vr[PER_T];
+    float kmreg = 0.f;
+    auto load_global = [&](int kt) {
+#pragma unroll
+        for (int i = 0; i < PER_T; ++i) {
+            const int c = stid + i * NTH, row = c / (DH / EP), col = (c % (DH / EP)) * EP, key = kt * BT + row;
+            kr[i] = vr[i] = make_uint4(0, 0, 0, 0);
+            if (c < CHUNKS && key < l_a && col < d_h) {
+                kr[i] = *reinterpret_cast<const uint4 *>(Kg + (size_t)key * d_h + col);
+                vr[i] = *reinterpret_cast<const uint4 *>(Vg + (size_t)key * d_h + col);
             }
         }
+        if (stid < BT) {
+            const int key = kt * BT + stid;
+            kmreg = key < l_a && (!a.pad_mask || key_is_token(a, g, key, l_p)) ? 1.f : 0.f;
+        }
+    };
+    auto put_row = [](float *dst, uint4 v) {
+        if constexpr (sizeof(T) == 4) *reinterpret_cast<uint4 *>(dst) = v;
+        else {
+            const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                dst[2 * e] = __uint_as_float(u[e] << 16);
+                dst[2 * e + 1] = __uint_as_float(u[e] & 0xFFFF0000u);
+            }
+        }
+    };
+    auto store_lds = [&]() {
+#pragma unroll
+        for (int i = 0; i < PER_T; ++i) {
+            const int c = stid + i * NTH, row = c / (DH / EP), col = (c % (DH / EP)) * EP;
+            if (c < CHUNKS) {
+                put_row(Ks + row * KP + col, kr[i]);
+                put_row(Vs + row * VP + col, vr[i]);
+            }
+        }
+        if (stid < BT) Km[stid] = kmreg;
+    };
+
+    if (split < nkt) load_global(split);
+    for (int it = 0; it < nit; ++it) {   // nit is uniform over the workgroup
+        const int kt = it * KSPLIT + split;
+        __syncthreads();   // the previous tiles have been consumed
+        if (kt < nkt) store_lds();
         __syncthreads();
+        if (kt + KSPLIT < nkt) load_global(kt + KSPLIT);
+        if (kt >= nkt) continue;
+        f32x16_t sacc;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) sacc[q] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < DH / 8; ++ks) {
+            const float4 kf = *reinterpret_cast<const float4 *>(Ks + lr * KP + ks * 8 + lh * 4);
+            sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.x, qf[ks][0], sacc, 0, 0, 0);
+            sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.y, qf[ks][1], sacc, 0, 0, 0);
+            sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.z, qf[ks][2], sacc, 0, 0, 0);
+            sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.w, qf[ks][3], sacc, 0, 0, 0);
+        }
+        float tmax = -INFINITY;
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+            const float4 ok4 = *reinterpret_cast<const float4 *>(Km + q4 * 8 + lh * 4);
+            const float okv[4] = {ok4.x, ok4.y, ok4.z, ok4.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int key = kt * BT + q4 * 8 + lh * 4 + e;
+                const bool ok = okv[e] != 0.f && (!causal || key <= qrow);
+                sacc[q4 * 4 + e] = ok ? sacc[q4 * 4 + e] : -INFINITY;
+                tmax = fmaxf(tmax, sacc[q4 * 4 + e]);
+            }
+        }
+        tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
+        const float mnew = fmaxf(mrun, tmax), msub = mnew == -INFINITY ? 0.f : mnew;   // nothing admissible yet: exp2(-inf - 0) = 0
+        const float corr = __builtin_amdgcn_exp2f(mrun - msub);   // 0 before the first admissible key
+        mrun = mnew;
+        float psum = 0.f;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            sacc[q] = __builtin_amdgcn_exp2f(sacc[q] - msub);
+            psum += sacc[q];
+        }
+        lsum = fmaf(lsum, corr, psum);
+#pragma unroll
+        for (int td = 0; td < DH / 32; ++td)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) oacc[td][q] *= corr;
+#pragma unroll
+        for (int q = 0; q < 16; ++q)
+#pragma unroll
+            for (int td = 0; td < DH / 32; ++td) {
+                const float vf = Vs[((q >> 2) * 8 + lh * 4 + (q & 3)) * VP + td * 32 + lr];
+                oacc[td] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf, sacc[q], oacc[td], 0, 0, 0);
+            }
     }
-    if (!live) return;
+    if constexpr (KSPLIT > 1) {   // split 0 folds the others' (max, sum, O) in, in split order
+        __syncthreads();
+        if (split > 0) {
+            float *dst = lds + ((size_t)((split - 1) * NQ + qg) * 64 + lane) * SLOT;
+            dst[0] = mrun;
+            dst[1] = lsum;
+#pragma unroll
+            for (int td = 0; td < DH / 32; ++td)
+#pragma unroll
+                for (int q = 0; q < 16; ++q) dst[2 + td * 16 + q] = oacc[td][q];
+        }
+        __syncthreads();
+        if (split > 0) return;
+#pragma unroll
+        for (int s = 1; s < KSPLIT; ++s) {
+            const float *src = lds + ((size_t)((s - 1) * NQ + qg) * 64 + lane) * SLOT;
+            const float m1 = src[0], mf = fmaxf(mrun, m1);
+            const float c0 = mrun == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mrun - mf);
+            const float c1 = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m1 - mf);
+            lsum = lsum * c0 + src[1] * c1;
+#pragma unroll
+            for (int td = 0; td < DH / 32; ++td)
+#pragma unroll
+                for (int q = 0; q < 16; ++q) oacc[td][q] = oacc[td][q] * c0 + src[2 + td * 16 + q] * c1;
+            mrun = mf;
+        }
+    }
+    if (qrow >= l_a) return;
+    lsum += __shfl_xor(lsum, 32, 64);
     // gate weight of this row (Eq. 36 with the optional gate flags)
     const int bb = g / a.k, i = clampi(a.expert_idx[g], a.n);
     float w = 1.0f;
     if ((a.flags & F_GATE_EXPERT) && a.expert_gate) w *= a.expert_gate[(size_t)bb * a.n + i];
     if ((a.flags & F_GATE_PATCH) && a.patch_gate) {
-        const int p = clampi(a.patch_idx[((size_t)bb * a.n + i) * a.c + r / l_p], a.m);
+        const int p = clampi(a.patch_idx[((size_t)bb * a.n + i) * a.c + qrow / l_p], a.m);
         w *= a.patch_gate[((size_t)bb * a.n + i) * a.m + p];
     }
-    const float inv = den > 0.f ? w / den : 0.f;  // a row with no admissible key contributes nothing
-    T *o = static_cast<T *>(a.o) + ((size_t)g * l_a + r) * d_h;
+    const float inv = lsum > 0.f ? w / lsum : 0.f;  // a row with no admissible key contributes nothing
+    T *o = static_cast<T *>(a.o) + ubase + (size_t)qrow * d_h;
 #pragma unroll
-    for (int e = 0; e < DH; ++e)
-        if (e < d_h) o[e] = from_f32<T>(acc[e] * inv);
+    for (int td = 0; td < DH / 32; ++td)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+            const int dh = td * 32 + q4 * 8 + lh * 4;
+            if (dh >= d_h) continue;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[dh + e] = from_f32<T>(oacc[td][q4 * 4 + e] * inv);
+        }
 }
 
-template <typename T> static hipError_t launch_attention_generic(const SmhaArgs &a, hipStream_t st)
+template <typename T, int DH> static void launch_attention_f32_dh(const SmhaArgs &a, hipStream_t st)
 {
-    const int l_a = a.c * (a.l / a.m);
-    dim3 grid((l_a + 127) / 128, a.b * a.k), block(128);
-    if (a.d_h <= 16) hipLaunchKernelGGL((attention_generic_kernel<T, 16>), grid, block, 0, st, a);
-    else if (a.d_h <= 32) hipLaunchKernelGGL((attention_generic_kernel<T, 32>), grid, block, 0, st, a);
-    else if (a.d_h <= 64) hipLaunchKernelGGL((attention_generic_kernel<T, 64>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((attention_generic_kernel<T, 128>), grid, block, 0, st, a);
+    const int l_a = a.c * (a.l / a.m), units = a.b * a.k;
+    // two query blocks per workgroup once that leaves a workgroup for every compute unit; key splits while the
+    // grid has fewer waves than the chip has SIMDs
+    const int nq = (long)((l_a + 63) / 64) * units >= 256 ? 2 : 1;
+    const int ks = (long)((l_a + 31) / 32) * units < 1024 && l_a > 32 ? 2 : 1;
+    const dim3 grid((l_a + 32 * nq - 1) / (32 * nq), units);
+    if (nq == 2 && ks == 2) hipLaunchKernelGGL((attention_f32_kernel<T, DH, 2, 2>), grid, dim3(256), 0, st, a);
+    else if (nq == 2) hipLaunchKernelGGL((attention_f32_kernel<T, DH, 2, 1>), grid, dim3(128), 0, st, a);
+    else if (ks == 2) hipLaunchKernelGGL((attention_f32_kernel<T, DH, 1, 2>), grid, dim3(128), 0, st, a);
+    else hipLaunchKernelGGL((attention_f32_kernel<T, DH, 1, 1>), grid, dim3(64), 0, st, a);
+}
+
+template <typename T> static hipError_t launch_attention_f32(const SmhaArgs &a, hipStream_t st)
+{
+    if (a.d_h <= 32) launch_attention_f32_dh<T, 32>(a, st);
+    else if (a.d_h <= 64) launch_attention_f32_dh<T, 64>(a, st);
+    else launch_attention_f32_dh<T, 128>(a, st);
     return hipGetLastError();
 }
 
@@ -738,8 +833,8 @@ template <int DH> static hipError_t launch_attention_mfma_dh(const SmhaArgs &a, 
 
 static hipError_t launch_attention_mfma(const SmhaArgs &a, hipStream_t st)
 {
-    if (a.d_h == 32) return launch_attention_mfma_dh<32>(a, st);
-    if (a.d_h == 64) return launch_attention_mfma_dh<64>(a, st);
+    if (a.d_hp == 32) return launch_attention_mfma_dh<32>(a, st);
+    if (a.d_hp == 64) return launch_attention_mfma_dh<64>(a, st);
     return launch_attention_mfma_dh<128>(a, st);
 }
 
@@ -756,7 +851,7 @@ template <typename T> static QkvProblem<T> make_qkv(const SmhaArgs &a)
     qp.k = static_cast<T *>(a.kk);
     qp.v = static_cast<T *>(a.v);
     qp.l = a.l; qp.d = a.d; qp.n = a.n; qp.kact = a.k; qp.m = a.m; qp.c = a.c;
-    qp.l_p = a.l / a.m; qp.l_a = a.c * qp.l_p; qp.d_h = a.d_h;
+    qp.l_p = a.l / a.m; qp.l_a = a.c * qp.l_p; qp.d_h = a.d_h; qp.d_hp = a.d_hp;
     qp.q_scale = 1.0f;
     qp.nout = 3;
     qp.q32 = nullptr;
@@ -773,26 +868,24 @@ template <typename T> static OutProjProblem<T> make_outproj(const SmhaArgs &a)
     op.x = static_cast<const T *>(a.x);
     op.expert_idx = a.expert_idx;
     op.patch_idx = a.patch_idx;
-    op.inv_cnt = a.inv_cnt;
-    op.inv_ent = a.inv_ent;
     op.out = static_cast<T *>(a.out);
     op.l = a.l; op.d = a.d; op.n = a.n; op.kact = a.k; op.m = a.m; op.c = a.c;
-    op.l_p = a.l / a.m; op.l_a = a.c * op.l_p; op.d_h = a.d_h; op.flags = a.flags;
+    op.l_p = a.l / a.m; op.l_a = a.c * op.l_p; op.d_h = a.d_h; op.o_row = a.d_hp; op.flags = a.flags;
     return op;
 }
 
-template <typename T> static hipError_t smha_generic(const SmhaArgs &a, hipStream_t st)
+// fp32 storage (and bf16 units too long for the bf16 attention kernels): everything on the fp32 matrix instruction
+template <typename T> static hipError_t smha_f32(const SmhaArgs &a, hipStream_t st)
 {
     const int l_p = a.l / a.m, l_a = a.c * l_p, units = a.b * a.k;
     hipError_t err;
     if (!(a.skip & SMHA_STEP_QKV)) {
-        if ((err = launch_gemm_generic<T>(make_qkv<T>(a), units, l_a, 3 * a.d_h, st)) != hipSuccess) return err;
+        if ((err = launch_gemm_tail<0>(make_qkv<T>(a), units, l_a, 3 * a.d_hp, st)) != hipSuccess) return err;
         if ((err = launch_rope<T>(a, st)) != hipSuccess) return err;
     }
-    if (!(a.skip & SMHA_STEP_ATTENTION) && (err = launch_attention_generic<T>(a, st)) != hipSuccess) return err;
+    if (!(a.skip & SMHA_STEP_ATTENTION) && (err = launch_attention_f32<T>(a, st)) != hipSuccess) return err;
     if (a.skip & SMHA_STEP_OUT) return hipSuccess;
-    if ((err = launch_inverse_map(a, st)) != hipSuccess) return err;
-    return launch_gemm_generic<T>(make_outproj<T>(a), a.b * a.m, l_p, a.d, st);
+    return launch_gemm_tail<0>(make_outproj<T>(a), a.b * a.m, l_p, a.d, st);
 }
 
 // Tile choice of the pipelined output-stationary contraction (out-projection of SMHA, second layer
@@ -819,19 +912,19 @@ static hipError_t smha_mfma_qkv_attention(const SmhaArgs &a, hipStream_t st)
     const int l_p = a.l / a.m, l_a = a.c * l_p, units = a.b * a.k;
     hipError_t err;
     QP qp = make_qkv<bf16_t>(a);
-    // the MFMA kernel addresses one unit's keys with 32-bit element offsets
-    const bool mfma_attn = (a.d_h == 32 || a.d_h == 64 || a.d_h == 128) && (long)l_a * a.d_h < (1L << 31);
-    if (mfma_attn) qp.q_scale = 1.4426950408889634f / sqrtf((float)a.d_h);  // base-2 softmax in the MFMA kernel
-    qp.v_f16 = mfma_attn && !a.keep_v_bf16;
+    qp.q_scale = 1.4426950408889634f / sqrtf((float)a.d_h);  // base-2 softmax in the MFMA kernel
+    qp.v_f16 = !a.keep_v_bf16;
     // one workgroup row-tile computes q, k and v together so the gathered rows are read once
     // 128-row tiles for long units (measured faster from l_a = 512 up), 32-row tiles for short ones
     auto projections = [&]() -> hipError_t {
     const bool tall = l_a >= 256 && (long)units * ((l_a + 127) / 128) >= 128, k64 = a.d % 64 == 0;
-    if (a.d_h == 32) {  // N = 96: 128-column tiles with the tail columns clamped
+    if (a.d % 32 != 0) {   // K ends inside a K-step
+        err = launch_gemm_tail<0>(qp, units, l_a, 3 * a.d_hp, st);
+    } else if (a.d_hp == 32) {  // N = 96: 128-column tiles with the tail columns clamped
         if (tall) err = launch_gemm_dma<QP, 128, 128, 32, 2, 2, 4, 2>(qp, units, l_a, 96, st);
         else if (k64) err = launch_gemm_dma<QP, 32, 128, 64, 1, 2, 4>(qp, units, l_a, 96, st);
         else err = launch_gemm_dma<QP, 32, 128, 32, 1, 2, 4>(qp, units, l_a, 96, st);
-    } else if (a.d_h == 64) {
+    } else if (a.d_hp == 64) {
         if (tall) err = k64 ? launch_gemm_dma<QP, 128, 192, 64, 2, 2, 3>(qp, units, l_a, 192, st)
                             : launch_gemm_dma<QP, 128, 192, 32, 2, 2, 4>(qp, units, l_a, 192, st);
         // 64-row tiles for mid-sized units (the ViT shape: 384 units of 56 rows): three 16 KB stage
@@ -847,43 +940,36 @@ static hipError_t smha_mfma_qkv_attention(const SmhaArgs &a, hipStream_t st)
         else if (k64) err = launch_gemm_dma<QP, 32, 192, 64, 1, 2, 4>(qp, units, l_a, 192, st);
         else err = launch_gemm_dma<QP, 32, 192, 32, 1, 2, 4>(qp, units, l_a, 192, st);
     } else {
-        err = launch_gemm_dma<QP, 128, 128, 32, 2, 2, 4, 2>(qp, units, l_a, 3 * a.d_h, st);
+        err = launch_gemm_dma<QP, 128, 128, 32, 2, 2, 4, 2>(qp, units, l_a, 3 * a.d_hp, st);
     }
     if (err != hipSuccess) return err;
     return launch_rope<bf16_t>(a, st);
     };
     if (!(a.skip & SMHA_STEP_QKV) && (err = projections()) != hipSuccess) return err;
     if (a.skip & SMHA_STEP_ATTENTION) return hipSuccess;
-    return mfma_attn ? launch_attention_mfma(a, st) : launch_attention_generic<bf16_t>(a, st);
+    return launch_attention_mfma(a, st);
 }
 
-hipError_t launch_smha_qkv_attention(const SmhaArgs &a, hipStream_t st) { return smha_mfma_qkv_attention(a, st); }
+hipError_t launch_smha_qkv_attention(const SmhaArgs &args, hipStream_t st)
+{
+    SmhaArgs a = args;
+    a.d_hp = a.d_h;
+    return smha_mfma_qkv_attention(a, st);
+}
 
-// MFMA path: bf16 storage, d and d_h multiples of 32 (the K segments of the two projections)
+// bf16 storage: q, k, v and o have rows of a.d_hp elements (d_h padded to 32, 64 or 128)
 static hipError_t smha_mfma(const SmhaArgs &a, hipStream_t st)
 {
     typedef OutProjProblem<bf16_t> OP;
     const int l_p = a.l / a.m;
     hipError_t err;
-    // the pipelined out-projection finds each patch's segments itself; the other engines read the
-    // inverse map
-    const bool out_dma = (long)a.k * a.c < (1L << 20);
     if ((err = smha_mfma_qkv_attention(a, st)) != hipSuccess) return err;
     if (a.skip & SMHA_STEP_OUT) return hipSuccess;
-    if (!out_dma && (err = launch_inverse_map(a, st)) != hipSuccess) return err;
-    // the MFMA kernel addresses one unit's keys with 32-bit element offsets
-    const bool mfma_attn = (a.d_h == 32 || a.d_h == 64 || a.d_h == 128) && (long)a.c * l_p * a.d_h < (1L << 31);
-
     OP op = make_outproj<bf16_t>(a);
     op.once = stream_once((size_t)a.b * a.l * a.d * sizeof(bf16_t));
-    if (mfma_attn) {  // the MFMA attention kernel writes o as a (hi, lo) bf16 pair
-        op.o_lo = static_cast<const bf16_t *>(a.o_lo);
-        op.parts = 2;
-    }
-    if (!out_dma) {  // segment context of the pipelined engine would not fit
-        if (l_p <= 32) return launch_gemm_mfma<OP, 32, 128, 32, 1, 4>(op, a.b * a.m, l_p, a.d, st);
-        return launch_gemm_mfma<OP, 64, 128, 32, 2, 2>(op, a.b * a.m, l_p, a.d, st);
-    }
+    op.o_lo = static_cast<const bf16_t *>(a.o_lo);   // the MFMA attention kernel writes o as a (hi, lo) bf16 pair
+    op.parts = 2;
+    if (a.d_h % 32 != 0) return launch_gemm_tail<0>(op, a.b * a.m, l_p, a.d, st);
     return launch_outproj_dma(op, a.b * a.m, l_p, a.d, st);
 }
 
@@ -917,30 +1003,19 @@ template <typename T> static OutProjProblem<T> make_ds_down(const UomeDsArgs &a)
     op.x = static_cast<const T *>(a.u);
     op.expert_idx = a.expert_idx;
     op.patch_idx = a.patch_idx;
-    op.inv_cnt = a.inv_cnt;
-    op.inv_ent = a.inv_ent;
     op.out = static_cast<T *>(a.out);
     op.l = a.l; op.d = a.d; op.n = a.n; op.kact = a.k; op.m = a.m; op.c = a.c;
-    op.l_p = a.l / a.m; op.l_a = a.c * op.l_p; op.d_h = a.d_e; op.flags = a.flags;
+    op.l_p = a.l / a.m; op.l_a = a.c * op.l_p; op.d_h = op.o_row = a.d_e; op.flags = a.flags;
     return op;
 }
 
-static hipError_t launch_inverse_map_ds(const UomeDsArgs &a, hipStream_t st)
-{
-    SmhaArgs s{};  // the inverse map only reads the routing fields
-    s.expert_idx = a.expert_idx; s.patch_idx = a.patch_idx;
-    s.b = a.b; s.n = a.n; s.k = a.k; s.m = a.m; s.c = a.c;
-    s.inv_cnt = a.inv_cnt; s.inv_ent = a.inv_ent;
-    return launch_inverse_map(s, st);
-}
-
-template <typename T> static hipError_t uome_ds_generic(const UomeDsArgs &a, hipStream_t st)
+// any width, either storage type
+template <typename T> static hipError_t uome_ds_tail(const UomeDsArgs &a, hipStream_t st)
 {
     const int l_p = a.l / a.m, l_a = a.c * l_p;
     hipError_t err;
-    if ((err = launch_inverse_map_ds(a, st)) != hipSuccess) return err;
-    if ((err = launch_gemm_generic<T>(make_ds_up<T>(a), a.b * a.k, l_a, a.d_e, st)) != hipSuccess) return err;
-    return launch_gemm_generic<T>(make_ds_down<T>(a), a.b * a.m, l_p, a.d, st);
+    if ((err = launch_gemm_tail<0>(make_ds_up<T>(a), a.b * a.k, l_a, a.d_e, st)) != hipSuccess) return err;
+    return launch_gemm_tail<0>(make_ds_down<T>(a), a.b * a.m, l_p, a.d, st);
 }
 
 static hipError_t uome_ds_mfma(const UomeDsArgs &a, hipStream_t st)
@@ -949,8 +1024,6 @@ static hipError_t uome_ds_mfma(const UomeDsArgs &a, hipStream_t st)
     typedef OutProjProblem<bf16_t> OP;
     const int l_p = a.l / a.m, l_a = a.c * l_p, units = a.b * a.k;
     hipError_t err;
-    const bool out_dma = (long)a.k * a.c < (1L << 20);
-    if (!out_dma && (err = launch_inverse_map_ds(a, st)) != hipSuccess) return err;
     const UP up = make_ds_up<bf16_t>(a);
     const long tiles256 = (long)units * ((l_a + 255) / 256) * ((a.d_e + 127) / 128);
     const long tiles128 = (long)units * ((l_a + 127) / 128) * ((a.d_e + 127) / 128);
@@ -962,23 +1035,26 @@ static hipError_t uome_ds_mfma(const UomeDsArgs &a, hipStream_t st)
     if (err != hipSuccess) return err;
     OP op = make_ds_down<bf16_t>(a);
     op.once = stream_once((size_t)a.b * a.l * a.d * sizeof(bf16_t));   // u's last use, the block's output
-    if (!out_dma) {
-        if (l_p <= 32) return launch_gemm_mfma<OP, 32, 128, 32, 1, 4>(op, a.b * a.m, l_p, a.d, st);
-        return launch_gemm_mfma<OP, 64, 128, 32, 2, 2>(op, a.b * a.m, l_p, a.d, st);
-    }
     return launch_outproj_dma(op, a.b * a.m, l_p, a.d, st);
 }
 
 hipError_t launch_uome_ds(const UomeDsArgs &a, bool bf16, hipStream_t st)
 {
     if (bf16 && a.d % 32 == 0 && a.d_e % 32 == 0) return uome_ds_mfma(a, st);
-    return bf16 ? uome_ds_generic<bf16_t>(a, st) : uome_ds_generic<float>(a, st);
+    return bf16 ? uome_ds_tail<bf16_t>(a, st) : uome_ds_tail<float>(a, st);
 }
 
-hipError_t launch_smha(const SmhaArgs &a, bool bf16, hipStream_t st)
+int smha_padded_width(int d_h, bool bf16) { return !bf16 ? d_h : d_h <= 32 ? 32 : d_h <= 64 ? 64 : 128; }
+
+hipError_t launch_smha(const SmhaArgs &args, bool bf16, hipStream_t st)
 {
-    if (bf16 && a.d % 32 == 0 && a.d_h % 32 == 0) return smha_mfma(a, st);
-    return bf16 ? smha_generic<bf16_t>(a, st) : smha_generic<float>(a, st);
+    SmhaArgs a = args;
+    a.d_hp = smha_padded_width(a.d_h, bf16);
+    if (!bf16) return smha_f32<float>(a, st);
+    // the bf16 attention kernels address one unit's keys with 32-bit element offsets
+    if ((long)a.c * (a.l / a.m) * a.d_hp < (1L << 31)) return smha_mfma(a, st);
+    a.d_hp = a.d_h;
+    return smha_f32<bf16_t>(a, st);
 }
 
 }  // namespace uoe

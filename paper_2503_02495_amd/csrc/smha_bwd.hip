@@ -516,7 +516,7 @@ hipError_t launch_smha_backward(const SmhaBwdArgs &a, hipStream_t st)
     dp.q = dp.k = dp.v = nullptr;
     dp.q32 = a.do_raw;
     dp.l = f.l; dp.d = f.d; dp.n = f.n; dp.kact = f.k; dp.m = f.m; dp.c = f.c;
-    dp.l_p = l_p; dp.l_a = l_a; dp.d_h = dh; dp.q_scale = 1.0f; dp.nout = 1;
+    dp.l_p = l_p; dp.l_a = l_a; dp.d_h = dp.d_hp = dh; dp.q_scale = 1.0f; dp.nout = 1;
     if ((err = launch_gemm_dma_auto(dp, units, l_a, dh, f.d, st)) != hipSuccess) return err;
 
     const dim3 rgrid(l_a / 32, units);
@@ -544,10 +544,10 @@ hipError_t launch_smha_backward(const SmhaBwdArgs &a, hipStream_t st)
     OutProjProblem<T> xp;
     xp.o = static_cast<const T *>(a.dqkv); xp.o_lo = nullptr; xp.parts = 1;
     xp.wo = static_cast<const T *>(a.wqkv_t); xp.x = static_cast<const T *>(a.d_out);
-    xp.expert_idx = f.expert_idx; xp.patch_idx = f.patch_idx; xp.inv_cnt = nullptr; xp.inv_ent = nullptr;
+    xp.expert_idx = f.expert_idx; xp.patch_idx = f.patch_idx;
     xp.out = static_cast<T *>(a.d_x);
     xp.l = f.l; xp.d = f.d; xp.n = f.n; xp.kact = f.k; xp.m = f.m; xp.c = f.c;
-    xp.l_p = l_p; xp.l_a = l_a; xp.d_h = 3 * dh; xp.flags = a.flags & F_RESIDUAL;
+    xp.l_p = l_p; xp.l_a = l_a; xp.d_h = xp.o_row = 3 * dh; xp.flags = a.flags & F_RESIDUAL;
     if (l_p <= 32) err = launch_gemm_dma<OutProjProblem<T>, 32, 128, 32, 1, 4, 4, 2>(xp, f.b * f.m, l_p, f.d, st);
     else err = launch_gemm_dma<OutProjProblem<T>, 64, 128, 32, 2, 2, 4, 2>(xp, f.b * f.m, l_p, f.d, st);
     if (err != hipSuccess) return err;

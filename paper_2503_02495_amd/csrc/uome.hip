@@ -5,13 +5,13 @@
 // output row once with the residual added: no per-expert partial outputs, no atomics.
 #include "common.h"
 #include "problems.h"
-#include "gemm_generic.h"
 #include "gemm_mfma.h"
 #include "gemm_dma.h"
 
 namespace uoe {
 
-template <typename T> static hipError_t uome_up_generic(const UomeArgs &a, hipStream_t st)
+// any width, either storage type
+template <typename T> static hipError_t uome_up_tail(const UomeArgs &a, hipStream_t st)
 {
     UomeUpProblem<T> up;
     up.u = static_cast<const T *>(a.u);
@@ -20,10 +20,10 @@ template <typename T> static hipError_t uome_up_generic(const UomeArgs &a, hipSt
     up.expert_gate = (a.flags & F_GATE_EXPERT) ? a.expert_gate : nullptr;
     up.hidden = static_cast<T *>(a.hidden);
     up.l = a.l; up.d = a.d; up.n = a.n; up.kact = a.k; up.d_e = a.d_e;
-    return launch_gemm_generic<T>(up, a.b, a.l, a.k * a.d_e, st);
+    return launch_gemm_tail<0>(up, a.b, a.l, a.k * a.d_e, st);
 }
 
-template <typename T> static hipError_t uome_down_generic(const UomeArgs &a, hipStream_t st)
+template <typename T> static hipError_t uome_down_tail(const UomeArgs &a, hipStream_t st)
 {
     UomeDownProblem<T> dn;
     dn.hidden = static_cast<const T *>(a.hidden);
@@ -32,7 +32,7 @@ template <typename T> static hipError_t uome_down_generic(const UomeArgs &a, hip
     dn.expert_idx = a.expert_idx;
     dn.out = static_cast<T *>(a.out);
     dn.l = a.l; dn.d = a.d; dn.n = a.n; dn.kact = a.k; dn.d_e = a.d_e; dn.flags = a.flags;
-    return launch_gemm_generic<T>(dn, a.b, a.l, a.d, st);
+    return launch_gemm_tail<0>(dn, a.b, a.l, a.d, st);
 }
 
 // MFMA path: bf16 storage, and every K segment (d for GEMM-1, d_e for GEMM-2) a multiple of 32
@@ -87,13 +87,13 @@ static hipError_t uome_down_mfma(const UomeArgs &a, hipStream_t st)
 hipError_t launch_uome_up(const UomeArgs &a, bool bf16, hipStream_t st)
 {
     if (uome_mfma_ok(a, bf16)) return uome_up_mfma(a, st);
-    return bf16 ? uome_up_generic<bf16_t>(a, st) : uome_up_generic<float>(a, st);
+    return bf16 ? uome_up_tail<bf16_t>(a, st) : uome_up_tail<float>(a, st);
 }
 
 hipError_t launch_uome_down(const UomeArgs &a, bool bf16, hipStream_t st)
 {
     if (uome_mfma_ok(a, bf16)) return uome_down_mfma(a, st);
-    return bf16 ? uome_down_generic<bf16_t>(a, st) : uome_down_generic<float>(a, st);
+    return bf16 ? uome_down_tail<bf16_t>(a, st) : uome_down_tail<float>(a, st);
 }
 
 hipError_t launch_uome(const UomeArgs &a, bool bf16, hipStream_t st)

@@ -291,7 +291,7 @@ hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st)
     zp.expert_idx = a.expert_idx; zp.patch_idx = a.patch_idx;
     zp.q = zp.k = zp.v = static_cast<T *>(a.z); zp.q32 = nullptr;
     zp.l = a.l; zp.d = a.d; zp.n = a.n; zp.kact = a.k; zp.m = a.m; zp.c = a.c;
-    zp.l_p = l_p; zp.l_a = l_a; zp.d_h = a.d_e; zp.q_scale = 1.0f; zp.nout = 1;
+    zp.l_p = l_p; zp.l_a = l_a; zp.d_h = zp.d_hp = a.d_e; zp.q_scale = 1.0f; zp.nout = 1;
     if ((err = launch_gemm_dma_auto(zp, units, l_a, a.d_e, a.d, st)) != hipSuccess) return err;
     QkvProblem<T> hp = zp;
     hp.x = static_cast<const T *>(a.d_out);
@@ -313,10 +313,10 @@ hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st)
     OutProjProblem<T> xp;
     xp.o = static_cast<const T *>(a.dz); xp.o_lo = nullptr; xp.parts = 1;
     xp.wo = static_cast<const T *>(a.a_in_t); xp.x = static_cast<const T *>(a.d_out);
-    xp.expert_idx = a.expert_idx; xp.patch_idx = a.patch_idx; xp.inv_cnt = nullptr; xp.inv_ent = nullptr;
+    xp.expert_idx = a.expert_idx; xp.patch_idx = a.patch_idx;
     xp.out = static_cast<T *>(a.d_u);
     xp.l = a.l; xp.d = a.d; xp.n = a.n; xp.kact = a.k; xp.m = a.m; xp.c = a.c;
-    xp.l_p = l_p; xp.l_a = l_a; xp.d_h = a.d_e; xp.flags = a.flags & F_RESIDUAL;
+    xp.l_p = l_p; xp.l_a = l_a; xp.d_h = xp.o_row = a.d_e; xp.flags = a.flags & F_RESIDUAL;
     if (l_p <= 32) err = launch_gemm_dma<OutProjProblem<T>, 32, 128, 32, 1, 4, 4, 2>(xp, a.b * a.m, l_p, a.d, st);
     else err = launch_gemm_dma<OutProjProblem<T>, 64, 128, 32, 2, 2, 4, 2>(xp, a.b * a.m, l_p, a.d, st);
     if (err != hipSuccess) return err;

@@ -1,0 +1,61 @@
+"""GPU parity of the kernels that take widths and token counts no tile divides, and of the fp32 matrix
+path, at the sizes where they can go wrong: one element past and one short of a tile, K segments that end
+inside a K-step, heads one step below and above a padded width, and both tile choices.  Same oracle,
+metric and bounds as test_gpu_parity (1e-4 in fp32, 2e-2 in bf16)."""
+import pytest
+
+import test_gpu_parity as P
+from paper_2503_02495_amd import binding as B
+from paper_2503_02495_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+R, GE, GP, CA = B.FLAG_RESIDUAL, B.FLAG_GATE_EXPERT, B.FLAG_GATE_PATCH, B.FLAG_CAUSAL
+BF = synth.BF16
+ODD = {
+    # bf16: head widths around the padded 32 / 64 / 128, K ending 8, 16 or 24 into a K-step
+    "odd_dh8": P.small(b=2, l=35, d=40, n_a=3, d_h=8, m=5, c=2, k_a=2, n_m=3, d_e=8, k_m=2, dtype=BF),
+    "odd_dh40": P.small(b=3, l=105, d=72, n_a=4, d_h=40, m=15, c=4, k_a=3, n_m=4, d_e=56, k_m=2, dtype=BF),
+    "odd_dh72": P.small(b=2, l=198, d=104, n_a=3, d_h=72, m=6, c=2, k_a=2, n_m=2, d_e=88, k_m=1, dtype=BF),
+    "odd_dh120": P.small(b=2, l=130, d=136, n_a=2, d_h=120, m=2, c=1, k_a=1, n_m=2, d_e=136, k_m=2, dtype=BF),
+    # enough 128-row tiles for the large-tile choice, rows and columns 8 past two tiles
+    "odd_big": P.small(b=32, l=264, d=136, n_a=2, d_h=16, m=8, c=8, k_a=2, n_m=2, d_e=136, k_m=2, dtype=BF),
+    # fp32: the same, and every launch shape of the fp32 attention (1 or 2 query blocks, 1 or 2 key splits)
+    "f32_big": P.small(b=32, l=264, d=136, n_a=2, d_h=16, m=8, c=8, k_a=2, n_m=2, d_e=136, k_m=2),
+    "f32_many_units": P.small(b=64, l=264, d=40, n_a=2, d_h=40, m=8, c=8, k_a=2, n_m=2, d_e=24, k_m=1),
+    "f32_one_tile": P.small(b=2, l=32, d=64, n_a=2, d_h=64, m=1, c=1, k_a=1, n_m=2, d_e=64, k_m=1),
+    "f32_dh128": P.small(b=1, l=66, d=128, n_a=2, d_h=128, m=2, c=2, k_a=1, n_m=2, d_e=128, k_m=1),
+}
+P.EDGE_CONFIGS.update(ODD)
+ODD_DS = {
+    "odd_ds": P.small(b=3, l=140, d=72, n_a=3, d_h=40, m=10, c=3, k_a=2, n_m=4, d_e=56, k_m=3, m_m=10, c_m=4, dtype=BF),
+    "f32_ds": P.small(b=2, l=330, d=40, n_a=2, d_h=8, m=5, c=2, k_a=1, n_m=3, d_e=136, k_m=2, m_m=5, c_m=3),
+}
+P.DS_CONFIGS.update(ODD_DS)
+
+
+@pytest.fixture(autouse=True)
+def _std(monkeypatch):
+    """fp32 attention logits of order one (std 0.2 weights make them ten times that at these widths)."""
+    monkeypatch.setattr(P, "w_std_for", lambda name: 0.06)
+
+
+@pytest.mark.parametrize("name", list(ODD))
+@pytest.mark.parametrize("flags,rope_dim,pad_frac", [(0, 0, 0.0), (CA | R | GE | GP, 8, 0.3)])
+def test_smha_odd_sizes(name, flags, rope_dim, pad_frac):
+    print(f"smha odd {name} flags={flags}", flush=True)
+    P.run_smha_variant(name, flags, rope_dim, pad_frac)
+
+
+@pytest.mark.parametrize("name", list(ODD))
+@pytest.mark.parametrize("flags", [0, R | GE])
+def test_uome_odd_sizes(name, flags):
+    print(f"uome odd {name} flags={flags}", flush=True)
+    P.run_uome_stage(name, flags)
+
+
+@pytest.mark.parametrize("name", list(ODD_DS))
+@pytest.mark.parametrize("flags", [0, R | GE | GP])
+def test_uome_data_selection_odd_sizes(name, flags):
+    print(f"uome data selection odd {name} flags={flags}", flush=True)
+    P.test_uome_data_selection_stage_parity(name, flags)
