@@ -273,7 +273,8 @@ int uoe_uome_down(const uoe_block_desc *blk, const void *hidden, const void *a_o
  * Two paths.  bf16 storage with l, d and d_e multiples of 32, b <= 128 (and l_p a multiple of 32 in
  * data-selection mode) runs on the matrix cores, intermediates (u A^I, d_out A^O^T) kept in bf16
  * between the kernels.  Every other expert-selection request (fp32 storage, any l, d, d_e) runs on
- * the vector ALU with fp32 intermediates: general, not fast.  Data selection outside the first path
+ * the matrix cores as well, with fp32 intermediates (bf16 storage: fp32, or pairs of bf16 values where
+ * they enter another product).  Data selection outside the first path
  * is UOE_ERR_UNSUPPORTED.  Outputs must not alias inputs.
  * Deterministic: fixed summation order, no atomics.  ws: at least
  * uoe_uome_backward_workspace_bytes(blk) bytes (0 = descriptor invalid or unsupported).
@@ -328,10 +329,10 @@ typedef struct {
  *                          off; either may be NULL
  * pad_mask [b,l] bytes or NULL as in uoe_smha_forward_masked (Eq. 41: padded keys are out of every
  * softmax).  The forward intermediates are recomputed.  Two paths: bf16 storage with d_h in
- * {32, 64, 128}, d % 32 == 0, l_p % 32 == 0 and b <= 128 runs on the matrix cores; every other
- * request (fp32 storage, a 14-token patch, d_h = 16) runs on the vector ALU with fp32 intermediates
- * and the attention probabilities of every unit materialised ([b*k, l_a, l_a] fp32 twice in ws):
- * general, not fast, and UOE_ERR_UNSUPPORTED beyond b*k*l_a*l_a = 2^31 or c > 1024.
+ * {32, 64, 128}, d % 32 == 0, l_p % 32 == 0 and b <= 128 runs on bf16 products throughout; every other
+ * request (fp32 storage, a 14-token patch, d_h = 16) keeps its intermediates in fp32 (bf16 storage:
+ * fp32, or pairs of bf16 values where they enter another product), attention in fp32 products;
+ * UOE_ERR_UNSUPPORTED there beyond b*k*l_a*l_a = 2^31 or c > 1024.
  * Deterministic: fixed summation order, no atomics.  ws: at least
  * uoe_smha_backward_workspace_bytes(blk) bytes (0 = descriptor invalid or unsupported).
  */

@@ -89,26 +89,35 @@ size_t uome_ws(const uoe_block_desc *d) { return up((size_t)d->b * d->l * d->k *
 // weight tensors; split-K tiles of one weight gradient; partial sums of the gate gradient
 struct UomeBwdWs {
     size_t z, dh, dz, dz_t, h_t, a_in_t, a_out_t, partial, gpart, rt, total;
-    int splits;
+    int splits, gchunks;
 };
 static bool uome_bwd_mfma(const uoe_block_desc *blk);
 UomeBwdWs uome_bwd_ws(const uoe_block_desc *d)
 {
     UomeBwdWs w{};
-    if (!uome_bwd_mfma(d)) {  // vector-ALU path: Z/H and dH/dZ in fp32
+    if (!uome_bwd_mfma(d)) {  // any-shape path: Z then H, dH then dZ, four bytes an element
         const size_t act32 = up((size_t)d->b * d->l * d->k * d->width * sizeof(float));
         w.z = 0; w.dh = act32; w.total = 2 * act32;
-        // weight gradients: the (sample, slot) pairs cut into ranges (at most 8) until about 4096 tiles of
-        // 64x64 exist, a few rounds of them per CU; partial tiles in fp32, added in range order
-        const long tiles = 2L * d->n * ((d->d + 63) / 64) * ((d->width + 63) / 64);
-        long s = 4096 / tiles;
-        s = s < 1 ? 1 : (s > 8 ? 8 : s);
-        if (s > (long)d->b * d->k) s = (long)d->b * d->k;
-        w.splits = (int)s;
-        if (w.splits > 1) {
-            w.partial = w.total;
-            w.total += up((size_t)2 * d->n * w.splits * d->d * d->width * sizeof(float));
+        w.h_t = w.z; w.dz_t = w.dh;
+        if (d->width > 2048 && d->dtype == UOE_BF16) {   // rows of (hi, lo) pairs longer than the kernel rewrites in place
+            w.h_t = w.total; w.dz_t = w.total + act32; w.total += 2 * act32;
         }
+        // weight gradients: chunks of 128 samples x ranges of the token axis (at most 8) until about 4096 tiles of
+        // 64x64 exist, a few rounds of them per CU; partial tiles in fp32, added in order
+        const long tiles = 2L * d->n * ((d->d + 63) / 64) * ((d->width + 63) / 64);
+        const int chunks = (d->b + 127) / 128;
+        long s = 4096 / tiles, most = (long)d->b * d->k > d->l / 256 ? (long)d->b * d->k : d->l / 256;
+        s = s < 1 ? 1 : (s > 8 ? 8 : s);
+        if (s > most) s = most;
+        w.splits = (int)(s / chunks > 1 ? s / chunks : 1) * chunks;
+        w.partial = w.total;
+        const size_t partial = (size_t)2 * d->n * w.splits * d->d * d->width;
+        w.total += up(partial * sizeof(float));
+        // the gate gradient's partial sums lie where the partial tiles go later (n >= k and d * d_e >= 64: one sum per
+        // (sample, slot) always fits)
+        w.gpart = w.partial;
+        const long fit = (long)(partial / ((size_t)d->b * d->k)), want = (d->l + 31) / 32;
+        w.gchunks = (int)(want < fit ? want : fit);
         return w;
     }
     const size_t es = elem_size(d->dtype);
@@ -128,12 +137,13 @@ UomeBwdWs uome_bwd_ws(const uoe_block_desc *d)
                            : uome_backward_splits(d->b, d->l, d->d, d->n, d->k, d->width);
     w.partial = off;
     off += up(2 * (size_t)d->n * w.splits * d->d * d->width * sizeof(float));  // both weight gradients
-    w.gpart = off; off += up((size_t)d->b * d->k * uome_backward_gate_chunks(d->l, d->width) * sizeof(float));
+    w.gchunks = uome_backward_gate_chunks(d->l, d->width);
+    w.gpart = off; off += up((size_t)d->b * d->k * w.gchunks * sizeof(float));
     w.rt = off; off += up((size_t)d->b * d->k * d->l * sizeof(float));
     w.total = off;
     return w;
 }
-// the matrix-core backward takes bf16 storage and 32-multiples; everything else goes to the vector-ALU path
+// bf16 storage with 32-multiples has kernels of its own; everything else goes to the any-shape path
 static bool uome_bwd_mfma(const uoe_block_desc *blk)
 {
     if (blk->dtype != UOE_BF16) return false;
@@ -145,7 +155,7 @@ int check_uome_bwd(const uoe_block_desc *blk)
 {
     const int rc = check_desc(blk, DESC_UOME);
     if (rc != UOE_OK) return rc;
-    // the vector-ALU path covers the expert-selection mode only
+    // the any-shape path covers the expert-selection mode only
     if (!uome_bwd_mfma(blk) && blk->c < blk->m) return UOE_ERR_UNSUPPORTED;
     return UOE_OK;
 }
@@ -154,8 +164,8 @@ int check_uome_bwd(const uoe_block_desc *blk)
 struct SmhaBwdWs {
     SmhaWs fwd;
     size_t lse, rt, dd, wo_t, wqkv_t, do_raw, d_o, o_t, dqkv, dqkv_t, partial, total;
-    size_t g_q, g_k, g_v, g_o, g_probs, g_dscores, g_wt;  // vector-ALU path (fp32 arrays)
-    int g_splits;                                           // vector-ALU path: unit ranges of the weight gradients
+    size_t g_q, g_k, g_v, g_og;  // any-shape path (four bytes an element)
+    int splits;
 };
 static bool smha_bwd_mfma(const uoe_block_desc *blk)
 {
@@ -169,27 +179,26 @@ SmhaBwdWs smha_bwd_ws(const uoe_block_desc *d)
     if (!smha_bwd_mfma(d)) {
         const size_t l_a = (size_t)d->c * (d->l / d->m), units = (size_t)d->b * d->k;
         const size_t rows = up(units * l_a * sizeof(float)), one = up(units * l_a * d->width * sizeof(float));
-        const size_t sq = up(units * l_a * l_a * sizeof(float));
         size_t off = 0;
         w.g_q = off; off += one;
         w.g_k = off; off += one;
         w.g_v = off; off += one;
-        w.g_o = off; off += one;
+        w.g_og = off; off += one;
         w.do_raw = off; off += one;
         w.dqkv = off; off += 3 * one;
         w.rt = off; off += rows;
-        w.g_probs = off; off += sq;
-        w.g_dscores = off; off += sq;
-        w.g_wt = off; off += up((size_t)4 * d->n * d->d * d->width * sizeof(float));
-        // weight gradients: the units cut into ranges until about 16 waves per SIMD are in flight, partial
-        // sums in fp32, added in range order
-        const size_t per = (size_t)d->n * d->d * d->width;
-        size_t sp = (16384 * 64 + per - 1) / per;
-        sp = sp < 1 ? 1 : (sp > 8 ? 8 : sp);
-        if (sp > units) sp = units;
-        w.g_splits = (int)sp;
+        w.lse = off; off += rows;
+        w.dd = off; off += rows;
+        // weight gradients: chunks of 128 samples x parts of an expert's (unit, pick) list, at most BWD_ANY_SEGMENTS
+        // entries in each even if every sample selected the expert
+        const int chunks = (d->b + 127) / 128, nb = d->b < 128 ? d->b : 128;
+        const int need = (nb * d->c + BWD_ANY_SEGMENTS - 1) / BWD_ANY_SEGMENTS;
+        const long avg = ((long)d->b * d->k * d->c / chunks + d->n - 1) / d->n;
+        long parts = avg / 8;
+        parts = parts < 1 ? 1 : (parts > 8 ? 8 : parts);
+        w.splits = (int)(parts > need ? parts : need) * chunks;
         w.partial = off;
-        if (sp > 1) off += up(sp * 4 * per * sizeof(float));
+        off += up((size_t)w.splits * 4 * d->n * d->d * d->width * sizeof(float));
         w.total = off;
         return w;
     }
@@ -209,7 +218,8 @@ SmhaBwdWs smha_bwd_ws(const uoe_block_desc *d)
     w.dqkv = off; off += 3 * one;
     w.dqkv_t = off; off += 3 * one;
     w.partial = off;
-    off += up((size_t)d->n * smha_backward_splits(d->b, d->n, d->k, d->c) * 4 * d->width * d->d * sizeof(float));
+    w.splits = smha_backward_splits(d->b, d->n, d->k, d->c);
+    off += up((size_t)d->n * w.splits * 4 * d->width * d->d * sizeof(float));
     w.total = off;
     return w;
 }
@@ -218,7 +228,7 @@ int check_smha_bwd(const uoe_block_desc *blk)
     const int rc = check_desc(blk, DESC_SMHA);
     if (rc != UOE_OK) return rc;
     if (!smha_bwd_mfma(blk)) {
-        // vector-ALU path: the materialised [units, l_a, l_a] arrays bound the size; the gate kernel holds c sums
+        // any-shape path: attention work of one call; the gate kernel holds c sums
         const size_t l_a = (size_t)blk->c * (blk->l / blk->m);
         if (blk->c > 1024 || (size_t)blk->b * blk->k * l_a * l_a > ((size_t)1 << 31)) return UOE_ERR_UNSUPPORTED;
     }
@@ -578,16 +588,18 @@ int uoe_uome_backward(const uoe_block_desc *blk, const void *u, const void *a_in
     a.b = blk->b; a.l = blk->l; a.d = blk->d; a.n = blk->n; a.k = blk->k; a.d_e = blk->width; a.flags = blk->flags;
     if (!uome_bwd_mfma(blk)) {
         a.z = at(ws, w.z); a.dh = at(ws, w.dh);
-        a.splits = w.splits;
-        a.partial = w.splits > 1 ? reinterpret_cast<float *>(at(ws, w.partial)) : nullptr;
-        return launch_uome_backward_generic(a, blk->dtype == UOE_BF16, static_cast<hipStream_t>(hip_stream)) == hipSuccess
+        a.h_op = at(ws, w.h_t); a.dz_op = at(ws, w.dz_t);
+        a.splits = w.splits; a.gchunks = w.gchunks;
+        a.partial = reinterpret_cast<float *>(at(ws, w.partial));
+        a.gpart = reinterpret_cast<float *>(at(ws, w.gpart));
+        return launch_uome_backward_any(a, blk->dtype == UOE_BF16, static_cast<hipStream_t>(hip_stream)) == hipSuccess
                    ? UOE_OK : UOE_ERR_DEVICE;
     }
     a.z = at(ws, w.z); a.dh = at(ws, w.dh); a.dz = at(ws, w.dz);
     a.dz_t = at(ws, w.dz_t); a.h_t = at(ws, w.h_t); a.a_in_t = at(ws, w.a_in_t); a.a_out_t = at(ws, w.a_out_t);
     a.gpart = reinterpret_cast<float *>(at(ws, w.gpart));
     a.partial = reinterpret_cast<float *>(at(ws, w.partial));
-    a.gchunks = uome_backward_gate_chunks(blk->l, blk->width);
+    a.gchunks = w.gchunks;
     a.splits = w.splits;
     a.patch_idx = patch_idx; a.patch_gate = patch_gate; a.d_patch_gate = d_patch_gate;
     a.rt = reinterpret_cast<float *>(at(ws, w.rt)); a.m = blk->m; a.c = blk->c;
@@ -626,17 +638,16 @@ int uoe_smha_backward(const uoe_block_desc *blk, const void *x, const uoe_smha_w
     f.rope_dim = blk->rope_dim; f.pad_mask = pad_mask;
     f.keep_v_bf16 = 1;   // the attention gradient kernels take v in bf16
     if (!smha_bwd_mfma(blk)) {
-        f.q = at(ws, s.g_q); f.kk = at(ws, s.g_k); f.v = at(ws, s.g_v); f.o = at(ws, s.g_o);
+        f.q = at(ws, s.g_q); f.kk = at(ws, s.g_k); f.v = at(ws, s.g_v);
+        f.lse = reinterpret_cast<float *>(at(ws, s.lse));
         a.d_out = d_out; a.expert_gate = expert_gate; a.patch_gate = patch_gate; a.flags = blk->flags;
         a.d_x = d_x; a.d_wq = dw->d_wq; a.d_wk = dw->d_wk; a.d_wv = dw->d_wv; a.d_wo = dw->d_wo;
         a.d_expert_gate = d_expert_gate; a.d_patch_gate = d_patch_gate;
-        a.do_raw = reinterpret_cast<float *>(at(ws, s.do_raw)); a.dqkv = at(ws, s.dqkv);
-        a.rt = reinterpret_cast<float *>(at(ws, s.rt));
-        a.probs = reinterpret_cast<float *>(at(ws, s.g_probs)); a.dscores = reinterpret_cast<float *>(at(ws, s.g_dscores));
-        a.wt = reinterpret_cast<float *>(at(ws, s.g_wt));
-        a.splits = s.g_splits;
-        a.partial = s.g_splits > 1 ? reinterpret_cast<float *>(at(ws, s.partial)) : nullptr;
-        return launch_smha_backward_generic(a, blk->dtype == UOE_BF16, static_cast<hipStream_t>(hip_stream)) == hipSuccess
+        a.do_raw = reinterpret_cast<float *>(at(ws, s.do_raw)); a.dqkv = at(ws, s.dqkv); a.og = at(ws, s.g_og);
+        a.rt = reinterpret_cast<float *>(at(ws, s.rt)); a.dd = reinterpret_cast<float *>(at(ws, s.dd));
+        a.splits = s.splits;
+        a.partial = reinterpret_cast<float *>(at(ws, s.partial));
+        return launch_smha_backward_any(a, blk->dtype == UOE_BF16, static_cast<hipStream_t>(hip_stream)) == hipSuccess
                    ? UOE_OK : UOE_ERR_DEVICE;
     }
     f.q = at(ws, s.fwd.q); f.kk = at(ws, s.fwd.k); f.v = at(ws, s.fwd.v); f.o = at(ws, s.fwd.o); f.o_lo = at(ws, s.fwd.o_lo);
@@ -648,7 +659,7 @@ int uoe_smha_backward(const uoe_block_desc *blk, const void *x, const uoe_smha_w
     a.o_t = at(ws, s.o_t); a.dqkv = at(ws, s.dqkv); a.dqkv_t = at(ws, s.dqkv_t);
     a.rt = reinterpret_cast<float *>(at(ws, s.rt)); a.dd = reinterpret_cast<float *>(at(ws, s.dd));
     a.partial = reinterpret_cast<float *>(at(ws, s.partial));
-    a.splits = smha_backward_splits(blk->b, blk->n, blk->k, blk->c);
+    a.splits = s.splits;
     return launch_smha_backward(a, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? UOE_OK : UOE_ERR_DEVICE;
 }
 

@@ -176,6 +176,7 @@ struct UomeBwdArgs {
     float *gpart;                             // [b, k, gchunks] partial sums of d_gate
     float *partial;                           // [2*n*splits, d_e, d] split-K tiles of the two weight gradients
     int gchunks, splits;
+    void *h_op, *dz_op;                       // any-shape path: H and dZ as left operands (may be z and dh themselves)
     // data-selection mode (patch_idx != NULL): units = (sample, slot) with l_a = c*l/m gathered rows;
     // z, dh, dz are [units, l_a, d_e], dz_t and h_t [units, d_e, l_a]
     const int32_t *patch_idx;
@@ -202,9 +203,8 @@ struct SmhaBwdArgs {
     float *rt, *dd;                           // [units, l_a] each: dL/dw_t and the softmax row term
     float *partial;                           // [4*n*splits, d_h, d] split tiles of the four weight gradients
     int splits;
-    // vector-ALU path only (any shape, any storage type): every workspace array above that it uses is fp32
-    float *probs, *dscores;                   // [units, l_a, l_a] each: softmax probabilities and score gradients
-    float *wt;                                // transposed fp32 copies of the weights: W^{q,k,v} as [3][n][d_h][d], then W^O as [n][d][d_h]
+    void *og;                                 // any-shape path: w o as a left operand [units, l_a, parts, d_h]; do_raw, q, k, v are
+                                              // fp32 there and dqkv is [units, l_a, parts, 3*d_h]
 };
 
 // Backward pass of the routers of one block
@@ -247,9 +247,14 @@ hipError_t launch_smha_backward(const SmhaBwdArgs &a, hipStream_t st);
 // gate gradients of the units of a data-selected block from the row terms a.rt (uses the routing
 // fields of a.f, a.flags, the gates and the two outputs, which it clears first)
 hipError_t launch_unit_gate_grads(const SmhaBwdArgs &a, hipStream_t st);
-// vector-ALU backward passes for the shapes and storage types the matrix-core kernels do not take
-hipError_t launch_uome_backward_generic(const UomeBwdArgs &a, bool bf16, hipStream_t st);
-hipError_t launch_smha_backward_generic(const SmhaBwdArgs &a, bool bf16, hipStream_t st);
+// d_gate from the partial sums a.gpart [b, k, gchunks]
+hipError_t launch_uome_gate_grad(const UomeBwdArgs &a, hipStream_t st);
+// rotary embedding (Eq. 32) of fp32 q and k with rows of d_h
+hipError_t launch_rope_f32(const SmhaArgs &a, hipStream_t st);
+// backward passes for the shapes and storage types the 32-multiple bf16 kernels do not take
+hipError_t launch_uome_backward_any(const UomeBwdArgs &a, bool bf16, hipStream_t st);
+hipError_t launch_smha_backward_any(const SmhaBwdArgs &a, bool bf16, hipStream_t st);
+constexpr int BWD_ANY_SEGMENTS = 1024;        // (unit, pick) entries one part of an expert's weight gradient holds
 hipError_t launch_route_backward(const RouteBwdArgs &a, bool bf16, hipStream_t st);
 // elements per row of q, k, v and o: the bf16 attention kernels take heads of 32, 64 or 128, other widths are padded
 // with zero columns

@@ -28,11 +28,11 @@
 //    K loop: a compiler-inserted wait for it would drain the whole pipeline.  Per-segment routing
 //    lookups are therefore taken once, before the loop, into a small LDS table (seg_ctx).
 //
-//  * Variants (GEMM_* flags).  GEMM_A_KM: the left operand is given [k][m] (m contiguous; a_stride() elements
+//  * Variants (GEMM_* flags).  GEMM_A_KM: the left operand is given [k][m] (m contiguous; a_stride(g) elements
 //    between k rows): its tile is laid out and read like the B tile, so a gradient that contracts over
 //    tokens takes its operands as the other kernels wrote them.  GEMM_B_NK: the right operand is given
 //    [n][k] (k contiguous, b_stride() elements between n rows): laid out and read like the A tile, so a
-//    product with a transposed weight needs no transposed copy of it.  GEMM_TAIL: kseg() may be any
+//    product with a transposed weight needs no transposed copy of it.  GEMM_TAIL: kseg(g) may be any
 //    length (a multiple of 8 where an operand runs along k): the pieces of A behind the end of a
 //    segment are read from a 16-byte block of zeros (every lane supplies its own address, so this is
 //    one compare and one select per load), those of B from the segment's last row or piece (finite,
@@ -44,8 +44,8 @@
 //    element by element (a lane is a column) with slot (r, pos) <- piece pos ^ (((r >> 2) & 1) << 3),
 //    which puts the two half-waves' rows k and k+4 in different halves of the banks.
 //
-// Requirements (checked by the callers): kseg() % BK == 0 without GEMM_TAIL, N % 8 == 0 (and M % 8 == 0 with
-// GEMM_A_KM), at most 128 entries in the segment table; BN (BM with GEMM_A_KM) a multiple of 64 and both operand
+// Requirements (checked by the callers): kseg(g) % BK == 0 without GEMM_TAIL, N % 8 == 0 (and M % 8 == 0 with
+// GEMM_A_KM), at most 128 (kMaxSegments) entries in the segment table; BN (BM with GEMM_A_KM) a multiple of 64 and both operand
 // tiles a whole number of load instructions per wave.  M and N tails are handled by clamping the load
 // addresses to a valid row / chunk of the same tile (the results of clamped rows and columns are never stored).
 #pragma once
@@ -84,6 +84,14 @@ template <typename P, typename = void> struct seg_parts {
 };
 template <typename P> struct seg_parts<P, std::void_t<decltype(P::kSegParts)>> {
     static constexpr int value = P::kSegParts;
+};
+
+// entries of the segment table
+template <typename P, typename = void> struct max_segments {
+    static constexpr int value = 128;
+};
+template <typename P> struct max_segments<P, std::void_t<decltype(P::kMaxSegments)>> {
+    static constexpr int value = P::kMaxSegments;
 };
 
 static __device__ __align__(16) const uint32_t gemm_zero_piece[4] = {0, 0, 0, 0};
@@ -135,7 +143,7 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, OCC) void gemm_dma_kernel(P 
     constexpr int S_BYTES = F32 ? 0 : NW * WM * SPITCH * 2;
     constexpr int OPER_BYTES = STAGES * STAGE_BYTES;
     constexpr int LDS_BYTES = OPER_BYTES > S_BYTES ? OPER_BYTES : S_BYTES;
-    constexpr int MAX_SEG = 128, PARTS = seg_parts<P>::value;
+    constexpr int MAX_SEG = max_segments<P>::value, PARTS = seg_parts<P>::value;
     static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile must be made of 32x32 MFMA tiles");
     static_assert(BK * ES == 64 || BK * ES == 128, "64 or 128 bytes of K per row");
     static_assert(BN % 64 == 0, "BN is a multiple of 64");
@@ -155,7 +163,7 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, OCC) void gemm_dma_kernel(P 
     const int g = tile / (tg.n_tiles * tg.m_tiles);
     const int rem = tile - g * (tg.n_tiles * tg.m_tiles);
     const int mt = rem / tg.n_tiles, nt = rem - mt * tg.n_tiles;
-    const int M = p.rows(g), N = p.ncols(), KSEG = p.kseg();
+    const int M = p.rows(g), N = p.ncols(), KSEG = p.kseg(g);
     const int m0 = mt * BM, n0 = nt * BN;
     if (m0 >= M) return;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -167,10 +175,10 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, OCC) void gemm_dma_kernel(P 
     const int lr = lane & 31, lh = lane >> 5;
     const long bstride = p.b_stride();
     long astride = 0;
-    if constexpr (AKM) astride = p.a_stride();
+    if constexpr (AKM) astride = p.a_stride(g);
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds_raw;
 
-    const int nseg = K / KSEG;
+    const int nseg = TAIL && KSEG <= 0 ? 0 : K / KSEG;   // (a group with an empty K has no segments)
     // table entries of this thread (at most one of each), requested now and stored after the first
     // operand loads have been issued
     uint32_t my_seg = 0;
@@ -295,7 +303,7 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, OCC) void gemm_dma_kernel(P 
     auto fetch_next = [&]() {
         if (noff == 0) {
             if constexpr (P::kPrepare) resolve_segment(nseg_next, seg_entry(nseg_next));
-            else resolve_segment(nseg_next, p.seg_ctx(g, nseg_next));
+            else resolve_segment(nseg_next, p.seg_ctx(g, nseg_next / PARTS));
         }
         issue(nbuf, noff);
         advance();

@@ -268,7 +268,7 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_mfma_kernel(P p, T
     const int g = tile / (tg.n_tiles * tg.m_tiles);
     const int rem = tile - g * (tg.n_tiles * tg.m_tiles);
     const int mt = rem / tg.n_tiles, nt = rem - mt * tg.n_tiles;
-    const int M = p.rows(g), N = p.ncols(), K = p.kdim(g), KSEG = p.kseg();
+    const int M = p.rows(g), N = p.ncols(), K = p.kdim(g), KSEG = p.kseg(g);
     const int m0 = mt * BM, n0 = nt * BN;
     if (m0 >= M) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;

@@ -3,7 +3,7 @@
 // the rows/columns of B are resolved through the routing indices.  A problem is a small POD
 // passed by value to a GEMM engine; engines ask it for
 //   rows(g), kdim(g), ncols()            problem extents
-//   kseg()                               length of one K segment (one expert's slice, or all of K)
+//   kseg(g)                              length of one K segment (one expert's slice, or all of K)
 //   a_seg_ptr(g, m, seg)   pointer to A[m][seg*kseg]; the segment's kseg elements are contiguous
 //   b_seg_ptr(g, seg, nn)  pointer to B[seg*kseg][nn..nn+8)  (nn % 8 == 0)
 //   b_stride()             elements between consecutive K rows of B inside a segment
@@ -65,17 +65,21 @@ __device__ __forceinline__ uint4 add8_bf16(uint4 v, uint4 r)
 // ---------------------------------------------------------------------------------------------
 // SMHA Eq. 28-30 with the index selection of Eq. 18 folded into the A-row lookup.
 // group = active unit (b, slot s); M = l_a; K = d; N = 3*d_h laid out [q | k | v].
-// F32: the single-projection form (nout = 1) stores fp32 rows into q32 instead.
+// F32: bf16 operands, fp32 rows into q32 (projection w at q32 + w * q32_plane) instead.
+// w_nk: the single projection (nout = 1) multiplies by the transpose of wq [n, d_h, d] (engine flag GEMM_B_NK).
 template <typename T, bool F32 = false> struct QkvProblem {
     typedef typename storage_elem<T>::type Elem;
     const T *x, *wq, *wk, *wv;
     const int32_t *expert_idx, *patch_idx;
     T *q, *k, *v;  // [units, l_a, d_h]
-    float *q32;    // [units, l_a, d_h] (F32 only)
+    float *q32;    // nout x [units, l_a, d_h] (F32 only)
+    size_t q32_plane = 0;
+    int w_nk = 0;
     static constexpr bool kF32Out = F32;
     __device__ void put4_f32(int g, int r, int nn, float4 val) const
     {
-        *reinterpret_cast<float4 *>(q32 + ((size_t)g * l_a + r) * d_h + nn) = val;
+        const int which = nn / d_h;
+        *reinterpret_cast<float4 *>(q32 + which * q32_plane + ((size_t)g * l_a + r) * d_h + (nn - which * d_h)) = val;
     }
     int l, d, n, kact, m, c, l_p, l_a, d_h;
     int d_hp;       // row length of q, k and v: d_h, or d_h padded to what the attention kernel takes (the columns behind
@@ -96,7 +100,7 @@ template <typename T, bool F32 = false> struct QkvProblem {
         const int t = r / l_p;
         return clampi(patch_idx[((size_t)bb * n + i) * c + t], m) * l_p + (r - t * l_p);
     }
-    __device__ int kseg() const { return d; }
+    __device__ int kseg(int) const { return d; }
     __device__ long b_stride() const { return d_h; }
     __device__ const T *a_seg_ptr(int g, int r, int) const
     {
@@ -106,6 +110,7 @@ template <typename T, bool F32 = false> struct QkvProblem {
     __device__ const T *b_seg_ptr(int g, int, int nn) const
     {
         const int i = expert(g);
+        if (w_nk) return wq + ((size_t)i * d_h + nn) * d;
         const int which = nn / d_hp, at = nn - which * d_hp, col = at < d_h ? at : 0;   // behind d_h: any valid piece, its products are dropped
         const T *w = which == 0 ? wq : (which == 1 ? wk : wv);
         return w + (size_t)i * d * d_h + col;
@@ -161,7 +166,7 @@ template <typename T> struct OutProjProblem {
     __device__ int rows(int) const { return l_p; }
     __device__ int kdim(int) const { return 0; }  // prepare() supplies K
     __device__ int ncols() const { return d; }
-    __device__ int kseg() const { return d_h; }
+    __device__ int kseg(int) const { return d_h; }
     __device__ long b_stride() const { return d; }
     __device__ float epi_f32(float val, float) const { return val; }
     __device__ void put4(int g, int r, int nn, float4 val) const
@@ -244,7 +249,7 @@ template <typename T, bool RAW = false> struct UomeUpProblem {
     __device__ int rows(int) const { return l; }
     __device__ int kdim(int) const { return d; }
     __device__ int ncols() const { return kact * d_e; }
-    __device__ int kseg() const { return d; }
+    __device__ int kseg(int) const { return d; }
     __device__ long b_stride() const { return d_e; }
     __device__ const T *a_seg_ptr(int g, int r, int) const { return u + ((size_t)g * l + r) * d; }
     __device__ const T *b_seg_ptr(int g, int, int nn) const
@@ -298,7 +303,7 @@ template <typename T> struct UomeDsUpProblem {
     __device__ int rows(int) const { return l_a; }
     __device__ int kdim(int) const { return d; }
     __device__ int ncols() const { return d_e; }
-    __device__ int kseg() const { return d; }
+    __device__ int kseg(int) const { return d; }
     __device__ long b_stride() const { return d_e; }
     __device__ int expert(int g) const { return clampi(expert_idx[g], n); }
     __device__ int patch(int g, int r) const
@@ -352,7 +357,7 @@ template <typename T> struct UomeDownProblem {
     __device__ int rows(int) const { return l; }
     __device__ int kdim(int) const { return kact * d_e; }
     __device__ int ncols() const { return d; }
-    __device__ int kseg() const { return d_e; }
+    __device__ int kseg(int) const { return d_e; }
     __device__ long b_stride() const { return d; }
     __device__ const T *a_seg_ptr(int g, int r, int seg) const
     {
@@ -414,7 +419,7 @@ template <typename T> struct WgradProblem {
     static constexpr bool kF32Out = true;
     __device__ int rows(int) const { return M; }
     __device__ int ncols() const { return N; }
-    __device__ int kseg() const { return l / splits; }
+    __device__ int kseg(int) const { return l / splits; }
     __device__ long b_stride() const { return right_stride; }
     __device__ int kdim(int) const { return 0; }  // prepare() supplies K
     static constexpr bool kPrepare = true;
@@ -489,7 +494,7 @@ template <typename T> struct SmhaWgradProblem {
     static constexpr bool kF32Out = true;
     __device__ int rows(int) const { return M; }
     __device__ int ncols() const { return d; }
-    __device__ int kseg() const { return l_p; }
+    __device__ int kseg(int) const { return l_p; }
     __device__ long b_stride() const { return d; }
     __device__ int kdim(int) const { return 0; }
     static constexpr bool kPrepare = true;

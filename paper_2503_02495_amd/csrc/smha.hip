@@ -46,6 +46,13 @@ template <typename T> static hipError_t launch_rope(const SmhaArgs &a, hipStream
     return hipGetLastError();
 }
 
+hipError_t launch_rope_f32(const SmhaArgs &args, hipStream_t st)
+{
+    SmhaArgs a = args;
+    a.d_hp = a.d_h;
+    return launch_rope<float>(a, st);
+}
+
 // padding flag of key `key` of unit g (Eq. 41: the mask is gathered with the unit's indices)
 __device__ __forceinline__ bool key_is_token(const SmhaArgs &a, int g, int key, int l_p)
 {

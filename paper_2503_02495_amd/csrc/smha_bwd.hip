@@ -567,8 +567,8 @@ hipError_t launch_smha_backward(const SmhaBwdArgs &a, hipStream_t st)
     if ((err = launch_gemm_dma_auto(wp, 4 * f.n * a.splits, dh, f.d, l_p, st)) != hipSuccess) return err;
     WgradReduceArgs ra{};
     ra.partial = a.partial; ra.n = f.n; ra.M = dh; ra.N = f.d; ra.splits = a.splits;
-    ra.dst[0] = static_cast<uint16_t *>(a.d_wq); ra.dst[1] = static_cast<uint16_t *>(a.d_wk);
-    ra.dst[2] = static_cast<uint16_t *>(a.d_wv); ra.dst[3] = static_cast<uint16_t *>(a.d_wo);
+    ra.dst[0] = a.d_wq; ra.dst[1] = a.d_wk;
+    ra.dst[2] = a.d_wv; ra.dst[3] = a.d_wo;
     ra.transposed[0] = ra.transposed[1] = ra.transposed[2] = 1; ra.transposed[3] = 0;
     return launch_wgrad_reduce(ra, 4, st);
 }

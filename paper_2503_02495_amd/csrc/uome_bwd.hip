@@ -148,6 +148,12 @@ __global__ __launch_bounds__(256) void uome_bwd_gate_kernel(UomeBwdArgs a)
     if (tid == 0) a.d_gate[(size_t)bb * a.n + clampi(a.expert_idx[bb * a.k + s], a.n)] = red[0];
 }
 
+hipError_t launch_uome_gate_grad(const UomeBwdArgs &a, hipStream_t st)
+{
+    hipLaunchKernelGGL(uome_bwd_gate_kernel, dim3(a.k, a.b), dim3(256), 0, st, a);
+    return hipGetLastError();
+}
+
 hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st);
 
 hipError_t launch_uome_backward(const UomeBwdArgs &a, hipStream_t st)
@@ -177,10 +183,7 @@ hipError_t launch_uome_backward(const UomeBwdArgs &a, hipStream_t st)
 
     hipLaunchKernelGGL(uome_bwd_mid_kernel, dim3((a.l + 63) / 64, width / 32, a.b), dim3(256), 0, st, a);
     if ((err = hipGetLastError()) != hipSuccess) return err;
-    if (a.d_gate) {
-        hipLaunchKernelGGL(uome_bwd_gate_kernel, dim3(a.k, a.b), dim3(256), 0, st, a);
-        if ((err = hipGetLastError()) != hipSuccess) return err;
-    }
+    if (a.d_gate && (err = launch_uome_gate_grad(a, st)) != hipSuccess) return err;
 
     UomeDownProblem<T> up;  // d_u = (d_out) + dZ W1_b^T: the second-layer contraction with (A^I_i)^T [d_e, d]
     up.hidden = static_cast<const T *>(a.dz); up.a_out = static_cast<const T *>(a.a_in_t);
@@ -199,8 +202,8 @@ hipError_t launch_uome_backward(const UomeBwdArgs &a, hipStream_t st)
     if ((err = launch_gemm_dma_auto(wp, 2 * a.n * a.splits, a.d_e, a.d, a.l / a.splits, st)) != hipSuccess) return err;
     WgradReduceArgs ra{};
     ra.partial = a.partial; ra.n = a.n; ra.M = a.d_e; ra.N = a.d; ra.splits = a.splits;
-    ra.dst[0] = static_cast<uint16_t *>(a.d_a_out); ra.transposed[0] = 0;
-    ra.dst[1] = static_cast<uint16_t *>(a.d_a_in); ra.transposed[1] = 1;
+    ra.dst[0] = a.d_a_out; ra.transposed[0] = 0;
+    ra.dst[1] = a.d_a_in; ra.transposed[1] = 1;
     return launch_wgrad_reduce(ra, 2, st);
 }
 
@@ -332,8 +335,8 @@ hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st)
     if ((err = launch_gemm_dma_auto(wp, 2 * a.n * a.splits, a.d_e, a.d, l_p, st)) != hipSuccess) return err;
     WgradReduceArgs ra{};
     ra.partial = a.partial; ra.n = a.n; ra.M = a.d_e; ra.N = a.d; ra.splits = a.splits;
-    ra.dst[0] = static_cast<uint16_t *>(a.d_a_out); ra.transposed[0] = 0;
-    ra.dst[1] = static_cast<uint16_t *>(a.d_a_in); ra.transposed[1] = 1;
+    ra.dst[0] = a.d_a_out; ra.transposed[0] = 0;
+    ra.dst[1] = a.d_a_in; ra.transposed[1] = 1;
     return launch_wgrad_reduce(ra, 2, st);
 }
 

@@ -9,12 +9,12 @@ namespace uoe {
 // Set s goes to dst[s], stored as [n][M][N] or transposed as [n][N][M].  32x32 tiles through LDS.
 struct WgradReduceArgs {
     const float *partial;
-    uint16_t *dst[4];
+    void *dst[4];   // storage type T of the launch
     int transposed[4];
     int n, M, N, splits;
 };
 
-template <int UNUSED = 0> __global__ __launch_bounds__(256) void wgrad_reduce_kernel(WgradReduceArgs a)
+template <typename T> __global__ __launch_bounds__(256) void wgrad_reduce_kernel(WgradReduceArgs a)
 {
     __shared__ float tile[32][33];
     const int set = blockIdx.z / a.n, e = blockIdx.z - set * a.n, r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
@@ -27,20 +27,20 @@ template <int UNUSED = 0> __global__ __launch_bounds__(256) void wgrad_reduce_ke
         tile[i][tx] = v;
     }
     __syncthreads();
-    uint16_t *dst = a.dst[set];
+    T *dst = static_cast<T *>(a.dst[set]);
     const bool tr = a.transposed[set] != 0;
     for (int i = ty; i < 32; i += 8) {
         if (tr) {
             if (c0 + i < a.N && r0 + tx < a.M)
-                dst[((size_t)e * a.N + c0 + i) * a.M + r0 + tx] = (uint16_t)(pack2_bf16(tile[tx][i], 0.f) & 0xFFFFu);
+                dst[((size_t)e * a.N + c0 + i) * a.M + r0 + tx] = from_f32<T>(tile[tx][i]);
         } else if (r0 + i < a.M && c0 + tx < a.N)
-            dst[((size_t)e * a.M + r0 + i) * a.N + c0 + tx] = (uint16_t)(pack2_bf16(tile[i][tx], 0.f) & 0xFFFFu);
+            dst[((size_t)e * a.M + r0 + i) * a.N + c0 + tx] = from_f32<T>(tile[i][tx]);
     }
 }
 
-static inline hipError_t launch_wgrad_reduce(const WgradReduceArgs &a, int sets, hipStream_t st)
+template <typename T = bf16_t> static inline hipError_t launch_wgrad_reduce(const WgradReduceArgs &a, int sets, hipStream_t st)
 {
-    hipLaunchKernelGGL((wgrad_reduce_kernel<0>), dim3((a.N + 31) / 32, (a.M + 31) / 32, sets * a.n), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((wgrad_reduce_kernel<T>), dim3((a.N + 31) / 32, (a.M + 31) / 32, sets * a.n), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 

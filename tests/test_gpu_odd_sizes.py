@@ -59,3 +59,45 @@ def test_uome_odd_sizes(name, flags):
 def test_uome_data_selection_odd_sizes(name, flags):
     print(f"uome data selection odd {name} flags={flags}", flush=True)
     P.test_uome_data_selection_stage_parity(name, flags)
+
+
+# --------------------------------------------------------------------------- backward passes
+UOME_BWD = {
+    "ub_odd": P.small(b=3, l=77, d=72, n_a=2, d_h=8, m=1, c=1, k_a=1, n_m=5, d_e=40, k_m=2, dtype=BF),
+    # two chunks of samples in the weight gradients' segment tables
+    "ub_b130": P.small(b=130, l=9, d=16, n_a=2, d_h=8, m=1, c=1, k_a=1, n_m=3, d_e=8, k_m=2, dtype=BF),
+    "ub_f32_b130": P.small(b=130, l=9, d=16, n_a=2, d_h=8, m=1, c=1, k_a=1, n_m=3, d_e=8, k_m=2),
+    # rows of (hi, lo) pairs that are rewritten in place (2048) and the first length that is not
+    "ub_in_place": P.small(b=2, l=20, d=16, n_a=2, d_h=8, m=1, c=1, k_a=1, n_m=2, d_e=2048, k_m=1, dtype=BF),
+    "ub_wide": P.small(b=2, l=20, d=16, n_a=2, d_h=8, m=1, c=1, k_a=1, n_m=2, d_e=2056, k_m=1, dtype=BF),
+    # ranges of the token axis, the last one short; one expert, one sample
+    "ub_ranges": P.small(b=1, l=1100, d=40, n_a=1, d_h=8, m=1, c=1, k_a=1, n_m=1, d_e=24, k_m=1, dtype=BF),
+    # both fp32 tile sizes
+    "ub_f32_big": P.small(b=32, l=264, d=136, n_a=2, d_h=8, m=1, c=1, k_a=1, n_m=2, d_e=136, k_m=2),
+}
+P.BWD_CONFIGS.update(UOME_BWD)
+SMHA_BWD = {
+    "sb_lp7": P.small(b=3, l=105, d=72, n_a=4, d_h=40, m=15, c=4, k_a=3, n_m=2, d_e=32, k_m=1, dtype=BF),
+    "sb_dh120": P.small(b=2, l=198, d=40, n_a=3, d_h=120, m=6, c=3, k_a=2, n_m=2, d_e=32, k_m=1, dtype=BF),
+    "sb_f32_dh128": P.small(b=1, l=200, d=64, n_a=2, d_h=128, m=4, c=3, k_a=1, n_m=2, d_e=32, k_m=1),
+    "sb_f32_b130": P.small(b=130, l=8, d=16, n_a=2, d_h=8, m=4, c=2, k_a=1, n_m=2, d_e=32, k_m=1),
+    # 1024, 512 and fewer 32-row blocks: one, two and four waves per block
+    "sb_f32_ks1": P.small(b=128, l=72, d=16, n_a=4, d_h=16, m=2, c=2, k_a=4, n_m=2, d_e=32, k_m=1),
+    "sb_f32_ks2": P.small(b=64, l=130, d=16, n_a=2, d_h=64, m=2, c=2, k_a=2, n_m=2, d_e=32, k_m=1),
+    "sb_f32_ks4": P.small(b=2, l=300, d=24, n_a=3, d_h=32, m=10, c=9, k_a=2, n_m=2, d_e=32, k_m=1),
+    # one key per query: dS is exactly zero
+    "sb_lp1_c1": P.small(b=2, l=6, d=8, n_a=2, d_h=8, m=6, c=1, k_a=1, n_m=2, d_e=8, k_m=1, dtype=BF),
+}
+P.SMHA_BWD_CONFIGS.update(SMHA_BWD)
+
+
+@pytest.mark.parametrize("name", list(UOME_BWD))
+@pytest.mark.parametrize("flags", [0, R | GE])
+def test_uome_backward_odd_sizes(name, flags):
+    P.test_uome_backward_parity(name, flags)
+
+
+@pytest.mark.parametrize("name", list(SMHA_BWD))
+@pytest.mark.parametrize("flags,rope_dim,pad_frac", [(0, 0, 0.0), (CA | R | GE | GP, 8, 0.2)])
+def test_smha_backward_odd_sizes(name, flags, rope_dim, pad_frac):
+    P.run_smha_backward(name, flags, rope_dim, pad_frac=pad_frac)
