@@ -237,24 +237,19 @@ int check_smha_bwd(const uoe_block_desc *blk)
 
 // backward pass of the routers
 struct RouteBwdWs {
-    size_t dz, dl, t1, u, wb_part, total;
-    int wb_tokens, wb_chunks;
+    size_t dl, u, t1, wb_part, wbt, total;
 };
 RouteBwdWs route_bwd_ws(const uoe_block_desc *d)
 {
     RouteBwdWs w;
-    // chunks of the token axis for dW_B: about 512 of them, 32 to 128 tokens each (the kernel stages a
-    // chunk's rows of U in LDS)
-    const size_t tokens = (size_t)d->b * d->l;
-    w.wb_tokens = (int)((tokens + 511) / 512);
-    w.wb_tokens = w.wb_tokens < 32 ? 32 : (w.wb_tokens > 128 ? 128 : w.wb_tokens);
-    w.wb_chunks = (int)((tokens + w.wb_tokens - 1) / w.wb_tokens);
+    const RouteBwdPlan p = route_bwd_plan(d->b, d->l, d->d, d->n, true, true);
+    const size_t rows = (size_t)d->b * d->l * d->n * sizeof(float);
     size_t off = 0;
-    w.dz = off; off += up((size_t)d->b * d->n * sizeof(float));
     w.dl = off; off += up((size_t)d->b * d->n * d->m * sizeof(float));
-    w.t1 = off; off += up((size_t)d->b * d->l * d->n * sizeof(float));
-    w.u = off; off += up((size_t)d->b * d->l * d->n * sizeof(float));
-    w.wb_part = off; off += up((size_t)w.wb_chunks * d->d * d->n * sizeof(float));
+    w.u = off; off += up(rows);
+    w.t1 = off; off += up(rows * p.slices);
+    w.wb_part = off; off += up((size_t)p.wb_chunks * d->d * d->n * sizeof(float));
+    w.wbt = off; off += up((size_t)d->d * d->n * elem_size(d->dtype));
     w.total = off;
     return w;
 }
@@ -263,7 +258,7 @@ int check_route_bwd(const uoe_block_desc *blk)
     const int rc = check_desc(blk, DESC_ROUTE);
     if (rc != UOE_OK) return rc;
     if (blk->b > 128 || blk->d > 2048) return UOE_ERR_UNSUPPORTED;
-    // the data router's per-token kernel stages dL [n,m], U [64,n] and W_B [d,n] in LDS
+    // size limit of the data router: dL [n,m], 64 rows of U [64,n] and W_B [d,n] together fit 64 KiB
     const size_t lds = ((size_t)blk->n * blk->m + 64 * (size_t)blk->n) * sizeof(float) + 16 + (size_t)blk->d * blk->n * elem_size(blk->dtype);
     if (lds > 64 * 1024) return UOE_ERR_UNSUPPORTED;
     return UOE_OK;
@@ -689,10 +684,9 @@ int uoe_route_backward(const uoe_block_desc *blk, const void *x, const void *w_e
     a.g_e = expert_gate; a.g_p = patch_gate; a.d_g_e = d_expert_gate; a.d_g_p = d_patch_gate;
     a.d_x = d_x; a.d_w_e = d_w_expert; a.d_w_b = d_w_b; a.d_w_a = d_w_a;
     a.b = blk->b; a.l = blk->l; a.d = blk->d; a.n = blk->n; a.m = blk->m;
-    a.dz = reinterpret_cast<float *>(at(ws, w.dz)); a.dl = reinterpret_cast<float *>(at(ws, w.dl));
-    a.t1 = reinterpret_cast<float *>(at(ws, w.t1)); a.u = reinterpret_cast<float *>(at(ws, w.u));
-    a.wb_part = reinterpret_cast<float *>(at(ws, w.wb_part));
-    a.wb_tokens = w.wb_tokens; a.wb_chunks = w.wb_chunks;
+    a.dl = reinterpret_cast<float *>(at(ws, w.dl)); a.u = reinterpret_cast<float *>(at(ws, w.u));
+    a.t1 = reinterpret_cast<float *>(at(ws, w.t1)); a.wb_part = reinterpret_cast<float *>(at(ws, w.wb_part));
+    a.wbt = at(ws, w.wbt);
     return launch_route_backward(a, blk->dtype == UOE_BF16, static_cast<hipStream_t>(hip_stream)) == hipSuccess
                ? UOE_OK : UOE_ERR_DEVICE;
 }

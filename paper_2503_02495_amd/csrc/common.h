@@ -207,6 +207,16 @@ struct SmhaBwdArgs {
                                               // fp32 there and dqkv is [units, l_a, parts, 3*d_h]
 };
 
+// Launch shape of the routers' backward pass: d_x in chunks of pieces (8 columns) x groups of samples, dW_E in chunks
+// of pieces x groups of 8 experts, t1 and dW_B in chunks of the b*l tokens x slices of columns
+constexpr int ROUTE_BWD_TILE = 32, ROUTE_BWD_SLICE = 256;
+struct RouteBwdPlan {
+    int data_blocks, wb_chunks, chunk_tokens, slices, slice_w;
+    int dx_blocks, dx_chunks, dx_groups, dx_bg, dx_pieces, dx_reps;
+    int w_blocks, w_chunks, w_groups, wsplit, w_reps;
+};
+RouteBwdPlan route_bwd_plan(int b, int l, int d, int n, bool has_e, bool has_d);
+
 // Backward pass of the routers of one block
 struct RouteBwdArgs {
     const void *x, *w_e, *w_b, *w_a;          // w_e NULL: no expert router; w_b NULL: no data router
@@ -215,11 +225,13 @@ struct RouteBwdArgs {
     void *d_x;                                // [b,l,d] in/out: the routers' contribution is added
     void *d_w_e, *d_w_b, *d_w_a;              // [n,l*d], [d,n], [l,m], storage dtype
     int b, l, d, n, m;
-    // workspace (fp32)
-    float *dz, *dl;                           // [b,n], [b,n,m]: gradients of the router logits
-    float *t1, *u;                            // [b,l,n] each: x W_B and W_A dL^T
-    float *wb_part;                           // [wb_chunks, d, n] partial sums of dW_B
-    int wb_tokens, wb_chunks;                 // tokens per chunk, chunks over the b*l tokens
+    // workspace (fp32 but wbt), used by the data router only
+    float *dl;                                // [b,n,m]: gradients of the patch logits
+    float *u;                                 // [b,l,n]: W_A dL^T
+    float *t1;                                // [slices,b,l,n]: x W_B, one part per slice of columns
+    float *wb_part;                           // [wb_chunks,d,n] partial sums of dW_B
+    void *wbt;                                // [n,d] W_B transposed, storage dtype
+    RouteBwdPlan plan;                        // set by the launcher
 };
 
 struct GatherArgs {

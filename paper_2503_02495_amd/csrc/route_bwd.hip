@@ -4,11 +4,17 @@
 //   data router:   L = (x W_B)^T W_A per sample, gate = softmax over experts for each patch:
 //                  dL = gate * (dgate - sum_i gate_i dgate_i),  U = W_A dL^T [l,n],
 //                  dW_A = sum_b (x W_B) dL,  dW_B = sum_b x^T U,  d_x += U W_B^T
-// All of it is memory-bound streaming over x, W_E and d_x with n <= 32 outputs per element, so it
-// runs on the vector ALU in fp32 (no contraction here is large enough for the matrix cores: K is
-// b, n or m).  d_x is read, updated and written in place (it arrives holding the block's own
-// gradient).  Summation orders are fixed: no atomics.
+// All of it is streaming over x, W_E, dW_E and d_x with n <= 32 outputs per element: bound by HBM on large
+// tensors and by the depth of the chain of launches on small ones.  Hence at most three launches:
+//   prep    dL, U and W_B^T (nothing of size l*d; skipped without a data router),
+//   main    three independent kinds of workgroup side by side: dW_E from x; d_x from W_E, U and W_B^T, read and
+//           written once for both routers; t1 = x W_B and partial sums of dW_B from x,
+//   finish  dW_A from t1 and dL, the ordered sum of the dW_B partials (skipped without a data router).
+// The thin contractions (K = tokens, d, m or b*n; n columns) run on v_mfma_f32_16x16x4_f32, which multiplies and
+// adds in fp32 and takes one scalar per lane and operand, so a plain row-major LDS tile serves as left operand
+// in either orientation.  Summation orders are fixed: no atomics.
 #include "common.h"
+#include <type_traits>
 
 namespace uoe {
 
@@ -47,292 +53,528 @@ template <bool ONCE> __device__ __forceinline__ void store8_w(bf16_t *p, const f
     store16<ONCE>(p, make_uint4(w[0], w[1], w[2], w[3]));
 }
 
-// Softmax backward of both routers: block = sample.  dz_i = g_i (dg_i - sum_j g_j dg_j) is
-// evaluated as g_i * sum_j g_j (dg_i - dg_j) (the gates sum to one): with one gate close to 1 the
-// first form subtracts two nearly equal numbers, the second adds small terms of mixed sign only.
-__global__ __launch_bounds__(64) void route_bwd_softmax_kernel(RouteBwdArgs a)
+typedef float rb_f32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ rb_f32x4 mfma_f32(float x, float y, rb_f32x4 c)
 {
-    const int bb = blockIdx.x, tid = threadIdx.x;
-    if (a.w_e && blockIdx.y == 0 && tid < a.n) {
-        const float *g = a.g_e + (size_t)bb * a.n, *dg = a.d_g_e + (size_t)bb * a.n;
-        const float mine = dg[tid];
-        float s = 0.f;
-        for (int i = 0; i < a.n; ++i) s = fmaf(g[i], mine - dg[i], s);
-        a.dz[(size_t)bb * a.n + tid] = g[tid] * s;
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, c, 0, 0, 0);  // lane: row / column lane & 15, k lane >> 4
+}
+
+template <typename T> struct RawPiece;   // 8 elements as loaded
+template <> struct RawPiece<bf16_t> { uint4 v[1]; };
+template <> struct RawPiece<float> { uint4 v[2]; };
+
+// Softmax backward of one logit.  dz_i = g_i (dg_i - sum_j g_j dg_j) is evaluated as g_i * sum_j g_j (dg_i - dg_j)
+// (the gates sum to one): with one gate close to 1 the first form subtracts two nearly equal numbers, the second
+// adds small terms of mixed sign only.
+__device__ __forceinline__ float softmax_bwd(const float *g, const float *dg, int n, int stride, int i)
+{
+    const float mine = dg[i * stride];
+    float s = 0.f;
+    for (int q = 0; q < n; ++q) s = fmaf(g[q * stride], mine - dg[q * stride], s);
+    return g[i * stride] * s;
+}
+
+constexpr int PREP_TOK = 64, PREP_J = 64, PREP_ST = PREP_J + 4;  // row stride = 4 mod 64 banks: 16 rows x 4 k, no conflict
+// Block (token tile, sample): the sample's dL (Eq. 14 backwards) and U = W_A dL^T for 64 tokens, 64 patches at a
+// time.  Blocks behind the last token tile write W_B^T (the d_x workgroups read 8 of its columns per 16 bytes).
+template <typename T> __global__ __launch_bounds__(256) void route_bwd_prep_kernel(RouteBwdArgs a)
+{
+    __shared__ float gs[2][32][PREP_J], dls[32][PREP_ST], was[PREP_TOK][PREP_ST];
+    const int tid = threadIdx.x, bb = blockIdx.y, tiles = (a.l + PREP_TOK - 1) / PREP_TOK;
+    if ((int)blockIdx.x >= tiles) {
+        const int step = (int)(gridDim.x - tiles) * a.b * 256;
+        for (int idx = (((int)blockIdx.x - tiles) * a.b + bb) * 256 + tid; idx < a.d * a.n; idx += step) {
+            const int i = idx / a.d, e = idx - i * a.d;
+            static_cast<T *>(a.wbt)[idx] = static_cast<const T *>(a.w_b)[(size_t)e * a.n + i];
+        }
+        return;
     }
-    if (a.w_b)
-        for (int j = blockIdx.y * 64 + tid; j < a.m; j += 64 * gridDim.y) {
-            const float *g = a.g_p + (size_t)bb * a.n * a.m + j, *dg = a.d_g_p + (size_t)bb * a.n * a.m + j;
-            for (int i = 0; i < a.n; ++i) {
-                const float mine = dg[(size_t)i * a.m];
-                float s = 0.f;
-                for (int q = 0; q < a.n; ++q) s = fmaf(g[(size_t)q * a.m], mine - dg[(size_t)q * a.m], s);
-                a.dl[((size_t)bb * a.n + i) * a.m + j] = g[(size_t)i * a.m] * s;
+    const int t0 = blockIdx.x * PREP_TOK, wave = tid >> 6, r = tid & 15, q = (tid & 63) >> 4;
+    const float *g = a.g_p + (size_t)bb * a.n * a.m, *dg = a.d_g_p + (size_t)bb * a.n * a.m;
+    const int rows = (a.n + 15) & ~15;
+    rb_f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    for (int j0 = 0; j0 < a.m; j0 += PREP_J) {
+        const int nj = min(PREP_J, a.m - j0);
+        const int jj = tid % PREP_J, row = tid / PREP_J;
+        const size_t j = j0 + min(jj, nj - 1);  // clamped, unconditional loads: all of them in flight at once
+        T wv[16];
+        float gv[8], dgv[8];
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+            const int i = min(row + 4 * v, a.n - 1);
+            gv[v] = g[i * a.m + j];
+            dgv[v] = dg[i * a.m + j];
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) wv[v] = static_cast<const T *>(a.w_a)[(size_t)min(t0 + row + 4 * v, a.l - 1) * a.m + j];
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+            gs[0][row + 4 * v][jj] = gv[v];
+            gs[1][row + 4 * v][jj] = dgv[v];
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) was[row + 4 * v][jj] = jj < nj ? to_f32(wv[v]) : 0.f;
+        __syncthreads();
+        for (int i = row; i < rows; i += 4) {
+            float v = 0.f;
+            if (i < a.n && jj < nj) {
+                v = softmax_bwd(&gs[0][0][jj], &gs[1][0][jj], a.n, PREP_J, i);
+                if (blockIdx.x == 0) a.dl[((size_t)bb * a.n + i) * a.m + j0 + jj] = v;
             }
+            dls[i][jj] = v;
+        }
+        __syncthreads();
+        for (int s = 0; s < (nj + 3) / 4; ++s) {
+            const float av = was[16 * wave + r][4 * s + q];
+            acc[0] = mfma_f32(av, dls[r][4 * s + q], acc[0]);
+            if (a.n > 16) acc[1] = mfma_f32(av, dls[16 + r][4 * s + q], acc[1]);
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int t = t0 + 16 * wave + 4 * q + e, i = 16 * nt + r;
+            if (t < a.l && i < a.n) a.u[((size_t)bb * a.l + t) * a.n + i] = acc[nt][e];
         }
 }
 
-// dW_E[i, q] = sum_b dz[b,i] x[b,q]: thread = 8 consecutive q, block.y = a group of 8 experts
-template <typename T, bool ONCE> __global__ __launch_bounds__(256) void route_bwd_wexpert_kernel(RouteBwdArgs a)
+// gates and gate gradients of nb samples into LDS: softmax_bwd walks a row n times
+__device__ __forceinline__ void stage_gates(const RouteBwdArgs &a, float *gs, int b0, int nb)
+{
+    for (int idx = threadIdx.x; idx < nb * a.n; idx += 256) {
+        gs[idx] = a.g_e[(size_t)b0 * a.n + idx];
+        gs[nb * a.n + idx] = a.d_g_e[(size_t)b0 * a.n + idx];
+    }
+    __syncthreads();
+}
+
+// ---- main launch, kind 1: dW_E[i, q] = sum_b dz[b,i] x[b,q], 8 consecutive q and 8 experts per thread.
+// With split (few columns, many samples) eight lanes of a wave share the samples of one 8-column piece and end up
+// with one expert each: three halving exchanges instead of eight times as long a chain of loads (b 128, l*d 75264:
+// the whole launch 53 + 15 -> 24 us).
+template <typename T, bool ONCE> __device__ __forceinline__ void bwd_wexpert(const RouteBwdArgs &a, float *dzs, int chunk0, int e0)
 {
     constexpr int EG = 8;
-    __shared__ float dzs[128 * EG];
-    const long ld = (long)a.l * a.d, q = ((long)blockIdx.x * 256 + threadIdx.x) * 8;
-    const int e0 = blockIdx.y * EG, ne = min(EG, a.n - e0);
-    for (int idx = threadIdx.x; idx < a.b * EG; idx += 256) {
-        const int bb = idx / EG, e = idx - bb * EG;
-        dzs[idx] = e < ne ? a.dz[(size_t)bb * a.n + e0 + e] : 0.f;
+    const long ld = (long)a.l * a.d;
+    const int tid = threadIdx.x, lane = tid & 63, ne = min(EG, a.n - e0);
+    float *gs = dzs + a.b * EG;
+    stage_gates(a, gs, 0, a.b);
+    for (int idx = tid; idx < a.b * EG; idx += 256) {
+        const int bb = idx / EG, e = idx % EG;
+        dzs[idx] = e < ne ? softmax_bwd(gs + bb * a.n, gs + (a.b + bb) * a.n, a.n, 1, e0 + e) : 0.f;
     }
     __syncthreads();
-    if (q >= ld) return;
-    float acc[EG][8];
+    const bool split = a.plan.wsplit;
+    const int last = min(chunk0 + 8 * a.plan.w_reps, a.plan.w_chunks);
+    for (int chunk = chunk0; chunk < last; chunk += 8) {
+        const long q = split ? ((long)chunk * 32 + (tid >> 6) * 8 + (lane & 7)) * 8 : ((long)chunk * 256 + tid) * 8;
+        const bool live = q < ld;
+        const T *x = static_cast<const T *>(a.x) + (live ? q : 0);
+        float acc[EG][8];
 #pragma unroll
-    for (int e = 0; e < EG; ++e)
+        for (int e = 0; e < EG; ++e)
 #pragma unroll
-        for (int c = 0; c < 8; ++c) acc[e][c] = 0.f;
-    const T *x = static_cast<const T *>(a.x) + q;
-    for (int bb = 0; bb < a.b; ++bb) {
-        float xv[8];
-        load8(x + (size_t)bb * ld, xv);
+            for (int c = 0; c < 8; ++c) acc[e][c] = 0.f;
+        const int b0 = split ? lane >> 3 : 0, bs = split ? 8 : 1;
+#pragma unroll 4
+        for (int bb = b0; bb < a.b; bb += bs) {
+            float xv[8];
+            load8(x + (size_t)bb * ld, xv);
 #pragma unroll
-        for (int e = 0; e < EG; ++e) {
-            const float w = dzs[bb * EG + e];
+            for (int e = 0; e < EG; ++e) {
+                const float w = dzs[bb * EG + e];
 #pragma unroll
-            for (int c = 0; c < 8; ++c) acc[e][c] = fmaf(w, xv[c], acc[e][c]);
+                for (int c = 0; c < 8; ++c) acc[e][c] = fmaf(w, xv[c], acc[e][c]);
+            }
         }
-    }
-    T *dw = static_cast<T *>(a.d_w_e) + q;
+        T *dw = static_cast<T *>(a.d_w_e) + q;
+        if (!split) {
 #pragma unroll
-    for (int e = 0; e < EG; ++e)
-        if (e < ne) store8_w<ONCE>(dw + (size_t)(e0 + e) * ld, acc[e]);
+            for (int e = 0; e < EG; ++e)
+                if (live && e < ne) store8_w<ONCE>(dw + (size_t)(e0 + e) * ld, acc[e]);
+            continue;
+        }
+#pragma unroll
+        for (int half = 4; half >= 1; half >>= 1) {
+            const bool upper = (lane >> 3) & half;
+#pragma unroll
+            for (int e = 0; e < half; ++e)
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    const float lo = acc[e][c], hi = acc[e + half][c];
+                    acc[e][c] = (upper ? hi : lo) + __shfl_xor(upper ? lo : hi, half * 8, 64);
+                }
+        }
+        if (live && (lane >> 3) < ne) store8_w<ONCE>(dw + (size_t)(e0 + (lane >> 3)) * ld, acc[0]);
+    }
 }
 
-// d_x[b, q] += sum_i dz[b,i] W_E[i,q]: thread = 8 consecutive q, block.y = a group of 8 samples
-template <typename T, bool ONCE> __global__ __launch_bounds__(256) void route_bwd_xexpert_kernel(RouteBwdArgs a)
+// ---- kind 2: d_x[b, (t,e)] += sum_i dz[b,i] W_E[i,(t,e)] + sum_i U[b,t,i] W_B[e,i]: 8 consecutive e and BG samples
+// per thread, so W_E is read once per BG samples and d_x read, updated and rounded once for both routers.
+template <typename T, int BG, bool ONCE> __device__ __forceinline__ void bwd_dx(const RouteBwdArgs &a, float *smem, int chunk0, int b0)
 {
-    constexpr int BG = 8;
-    __shared__ float dzs[BG * 32];
-    const long ld = (long)a.l * a.d, q = ((long)blockIdx.x * 256 + threadIdx.x) * 8;
-    const int b0 = blockIdx.y * BG, nb = min(BG, a.b - b0);
-    for (int idx = threadIdx.x; idx < BG * a.n; idx += 256) {
-        const int s = idx / a.n, i = idx - s * a.n;
-        dzs[s * 32 + i] = s < nb ? a.dz[(size_t)(b0 + s) * a.n + i] : 0.f;
+    const long ld = (long)a.l * a.d;
+    const int tid = threadIdx.x, nb = min(BG, a.b - b0), pieces = a.plan.dx_pieces, P = a.d / 8;
+    float *dzs = smem, *us = smem + a.n * BG;  // [n][BG], [n][tokens][BG]
+    if (a.w_e) {
+        stage_gates(a, us, b0, nb);
+        for (int idx = tid; idx < a.n * BG; idx += 256) {
+            const int i = idx / BG, s = idx % BG;
+            dzs[idx] = s < nb ? softmax_bwd(us + s * a.n, us + (nb + s) * a.n, a.n, 1, i) : 0.f;
+        }
+        __syncthreads();
     }
-    __syncthreads();
-    if (q >= ld) return;
-    float acc[BG][8];
-#pragma unroll
-    for (int s = 0; s < BG; ++s)
-#pragma unroll
-        for (int c = 0; c < 8; ++c) acc[s][c] = 0.f;
-    const T *w = static_cast<const T *>(a.w_e) + q;
-    for (int i = 0; i < a.n; ++i) {
-        float wv[8];
-        load8_w<ONCE>(w + (size_t)i * ld, wv);
+    const int last = min(chunk0 + 8 * a.plan.dx_reps, a.plan.dx_chunks);
+    for (int chunk = chunk0; chunk < last; chunk += 8) {
+        const long p0 = (long)chunk * pieces, p = p0 + tid, q = p * 8;
+        const int t0 = (int)(p0 / P), t1 = (int)min((p0 + pieces - 1) / P, (long)a.l - 1), nt = t1 - t0 + 1;
+        if (a.w_b) {
+            if (chunk != chunk0) __syncthreads();
+            for (int idx = tid; idx < nt * a.n * BG; idx += 256) {
+                const int s = idx / (nt * a.n), k = idx - s * nt * a.n, tk = k / a.n, i = k - tk * a.n;
+                us[(i * nt + tk) * BG + s] = a.u[((size_t)(b0 + min(s, nb - 1)) * a.l + t0) * a.n + k];
+            }
+            __syncthreads();
+        }
+        if (tid >= pieces || q >= ld) continue;
+        const int t = (int)(p / P), e = (int)(p - (long)t * P) * 8;
+        T *dx = static_cast<T *>(a.d_x) + (size_t)b0 * ld + q;
+        RawPiece<T> cur[BG];
+        float de[BG][8];
 #pragma unroll
         for (int s = 0; s < BG; ++s) {
-            const float z = dzs[s * 32 + i];
 #pragma unroll
-            for (int c = 0; c < 8; ++c) acc[s][c] = fmaf(z, wv[c], acc[s][c]);
+            for (int c = 0; c < 8; ++c) de[s][c] = 0.f;
+            cur[s] = *reinterpret_cast<const RawPiece<T> *>(dx + (size_t)(s < nb ? s : 0) * ld);
         }
-    }
-    T *dx = static_cast<T *>(a.d_x) + q;
+        if (a.w_e) {
+            const T *w = static_cast<const T *>(a.w_e) + q;
+#pragma unroll 4
+            for (int i = 0; i < a.n; ++i) {
+                float wv[8];
+                load8_w<ONCE>(w + (size_t)i * ld, wv);
 #pragma unroll
-    for (int s = 0; s < BG; ++s)
-        if (s < nb) {
-            float cur[8];
-            load8(dx + (size_t)(b0 + s) * ld, cur);
+                for (int s = 0; s < BG; ++s) {
+                    const float z = dzs[i * BG + s];
 #pragma unroll
-            for (int c = 0; c < 8; ++c) cur[c] += acc[s][c];
-            store8<T>(dx + (size_t)(b0 + s) * ld, cur);
-        }
-}
-
-// Data router, per token: U[t,:] = W_A[t,:] dL^T, then one pass over the token's row of x that
-// forms (x W_B)[t,:] and adds U[t,:] W_B^T to d_x.  Block = 256/LPT tokens of one sample, LPT lanes
-// per token (16 when 4 would leave compute units without a block); the sample's dL and W_B^T
-// ([n][d], so that the 8 weights a piece of x meets are one 16-byte read) are staged in LDS.
-template <typename T, int LPT> __global__ __launch_bounds__(256) void route_bwd_data_token_kernel(RouteBwdArgs a)
-{
-    constexpr int TPB = 256 / LPT;  // tokens per block
-    extern __shared__ __align__(16) unsigned char smem[];
-    float *dls = reinterpret_cast<float *>(smem);                       // [n][m]
-    float *us = dls + (size_t)a.n * a.m;                                // [64][n] (TPB <= 64 rows used)
-    T *wbt = reinterpret_cast<T *>(smem + ((((size_t)a.n * a.m + 64 * (size_t)a.n) * sizeof(float) + 15) & ~(size_t)15));  // [n][d]
-    const int bb = blockIdx.y, tid = threadIdx.x, tl = tid / LPT, part = tid % LPT;
-    const int t = blockIdx.x * TPB + tl;
-    for (int idx = tid; idx < a.n * a.m; idx += 256) dls[idx] = a.dl[(size_t)bb * a.n * a.m + idx];
-    for (int idx = tid; idx < a.d * a.n; idx += 256) {
-        const int e = idx / a.n, i = idx - e * a.n;
-        wbt[(size_t)i * a.d + e] = static_cast<const T *>(a.w_b)[idx];
-    }
-    __syncthreads();
-    if (t < a.l) {
-        const T *wa = static_cast<const T *>(a.w_a) + (size_t)t * a.m;
-        for (int i = part; i < a.n; i += LPT) {
-            float s = 0.f;
-            for (int j = 0; j < a.m; ++j) s = fmaf(to_f32(wa[j]), dls[i * a.m + j], s);
-            us[tl * a.n + i] = s;
-            a.u[((size_t)bb * a.l + t) * a.n + i] = s;
-        }
-    }
-    __syncthreads();
-    float t1[32];
-#pragma unroll
-    for (int i = 0; i < 32; ++i) t1[i] = 0.f;
-    if (t < a.l) {
-        const T *xr = static_cast<const T *>(a.x) + ((size_t)bb * a.l + t) * a.d;
-        T *dxr = static_cast<T *>(a.d_x) + ((size_t)bb * a.l + t) * a.d;
-        for (int pc = part; pc < a.d / 8; pc += LPT) {
-            float xv[8], dv[8];
-            load8(xr + pc * 8, xv);
-            load8(dxr + pc * 8, dv);
-#pragma unroll
-            for (int i = 0; i < 32; ++i) {
-                if (i < a.n) {
-                    const float ui = us[tl * a.n + i];
-                    float wv[8];
-                    load8(wbt + (size_t)i * a.d + pc * 8, wv);
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        t1[i] = fmaf(xv[e], wv[e], t1[i]);
-                        dv[e] = fmaf(ui, wv[e], dv[e]);
-                    }
+                    for (int c = 0; c < 8; ++c) de[s][c] = fmaf(z, wv[c], de[s][c]);
                 }
             }
-            store8<T>(dxr + pc * 8, dv);
         }
-    }
+        if (a.w_b) {
+            const T *w = static_cast<const T *>(a.wbt) + e;
+            const float *ut = us + (t - t0) * BG;
+#pragma unroll 4
+            for (int i = 0; i < a.n; ++i) {
+                float wv[8];
+                load8(w + (size_t)i * a.d, wv);
 #pragma unroll
-    for (int i = 0; i < 32; ++i)
+                for (int s = 0; s < BG; ++s) {
+                    const float z = ut[i * nt * BG + s];
 #pragma unroll
-        for (int off = 1; off < LPT; off <<= 1) t1[i] += __shfl_xor(t1[i], off, 64);
-    if (t < a.l && part == 0)
-        for (int i = 0; i < a.n; ++i) a.t1[((size_t)bb * a.l + t) * a.n + i] = t1[i];
-}
-
-// dW_A[t,j] = sum_b sum_i (x W_B)[b,t,i] dL[b,i,j]: thread = (t, j)
-template <typename T> __global__ __launch_bounds__(256) void route_bwd_wa_kernel(RouteBwdArgs a)
-{
-    const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (long)a.l * a.m) return;
-    const int t = (int)(idx / a.m), j = (int)(idx - (long)t * a.m);
-    float s = 0.f;
-    for (int bb = 0; bb < a.b; ++bb) {
-        const float *t1 = a.t1 + ((size_t)bb * a.l + t) * a.n, *dl = a.dl + (size_t)bb * a.n * a.m + j;
-        for (int i = 0; i < a.n; ++i) s = fmaf(t1[i], dl[(size_t)i * a.m], s);
-    }
-    static_cast<T *>(a.d_w_a)[idx] = from_f32<T>(s);
-}
-
-// dW_B[e,i] = sum over all b*l tokens of x[token,e] U[token,i].  Block = a chunk of tokens; thread =
-// (8 consecutive e, row lane).  The row lanes' sums are added in lane order through LDS, one
-// expert at a time, so that a block leaves one partial [d][n]; the final kernel adds the chunks
-// in order.  block.y = a group of 16 experts.
-template <typename T> __global__ __launch_bounds__(256) void route_bwd_wb_partial_kernel(RouteBwdArgs a)
-{
-    constexpr int IG = 16;
-    __shared__ float red[256][9];
-    __shared__ float us[128 * IG];  // the chunk's rows of U (at most 128 tokens per chunk)
-    const int P = a.d / 8, R = 256 / P, tid = threadIdx.x;
-    const int pc = tid % P, rl = tid / P;
-    const int i0 = blockIdx.y * IG, ni = min(IG, a.n - i0);
-    const bool live = rl < R;
-    float acc[IG][8];
-#pragma unroll
-    for (int i = 0; i < IG; ++i)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[i][e] = 0.f;
-    const long tokens = (long)a.b * a.l, tok0 = (long)blockIdx.x * a.wb_tokens;
-    const long tok1 = min(tokens, tok0 + a.wb_tokens);
-    const T *x = static_cast<const T *>(a.x);
-    const int ntok = (int)(tok1 - tok0);
-    for (int idx = tid; idx < ntok * IG; idx += 256) {
-        const int tk = idx / IG, i = idx - tk * IG;
-        us[idx] = i < ni ? a.u[(tok0 + tk) * a.n + i0 + i] : 0.f;
-    }
-    __syncthreads();
-    if (live) {
-        for (int tk = rl; tk < ntok; tk += R) {
-            float xv[8];
-            load8(x + (tok0 + tk) * a.d + pc * 8, xv);
-#pragma unroll
-            for (int i = 0; i < IG; ++i) {
-                const float ui = us[tk * IG + i];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) acc[i][e] = fmaf(xv[e], ui, acc[i][e]);
+                    for (int c = 0; c < 8; ++c) de[s][c] = fmaf(z, wv[c], de[s][c]);
+                }
             }
         }
-    }
-    float *dst = a.wb_part + (size_t)blockIdx.x * a.d * a.n;
 #pragma unroll
-    for (int i = 0; i < IG; ++i) {  // fully unrolled: acc stays in registers; the skip is uniform
-        if (i < ni) {
-        if (live)
+        for (int s = 0; s < BG; ++s)
+            if (s < nb) {
+                float o[8];
+                load8(reinterpret_cast<const T *>(cur[s].v), o);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) red[tid][e] = acc[i][e];
-        __syncthreads();
-        if (rl == 0) {
-            float s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-            for (int q = 0; q < R; ++q)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) s[e] += red[q * P + pc][e];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) dst[(size_t)(pc * 8 + e) * a.n + i0 + i] = s[e];
-        }
-        __syncthreads();
-        }
+                for (int c = 0; c < 8; ++c) o[c] += de[s][c];
+                store8<T>(dx + (size_t)s * ld, o);
+            }
     }
 }
 
-// adds the chunks' partials in chunk order: block = 32 outputs x 8 part lanes (lane q takes chunks
-// q, q+8, ...), then the 8 lanes in lane order
-template <typename T> __global__ __launch_bounds__(256) void route_bwd_wb_reduce_kernel(RouteBwdArgs a)
+// ---- kind 3: a chunk of tokens (all b*l in one row) x a slice of at most 256 columns of x: the slice's part of
+// t1 = x W_B and the chunk's part of dW_B = x^T U.  32 tokens at a time go through one fp32 LDS tile that both
+// products read; a wave owns every fourth 16-column tile, keeps its W_B fragments and dW_B sums in registers, and
+// the next tile's loads are in flight under the matrix instructions.
+constexpr int BT = ROUTE_BWD_TILE, BS = ROUTE_BWD_SLICE, BST = BS + 20;  // stride = 20 mod 64 banks: conflict-free by rows, 2-way by columns
+template <typename T, int NT> __device__ __forceinline__ void bwd_data(const RouteBwdArgs &a, float *xs, int chunk, int slice)
 {
-    __shared__ float red[8][33];
-    const int ol = threadIdx.x & 31, ql = threadIdx.x >> 5;
-    const int idx = blockIdx.x * 32 + ol, total = a.d * a.n;
+    const int tid = threadIdx.x, wave = tid >> 6, r = tid & 15, q = (tid & 63) >> 4;
+    const int e0 = slice * a.plan.slice_w, ew = min(a.plan.slice_w, a.d - e0), rst = ((a.n + 15) & ~15) + 1;
+    const long tokens = (long)a.b * a.l, tok0 = (long)chunk * a.plan.chunk_tokens;
+    const long tok1 = min(tokens, tok0 + a.plan.chunk_tokens);
+    float *red = xs + BT * BST;  // [4 waves][BT][rst]
+    float *t1 = a.t1 + (size_t)slice * tokens * a.n;
+    float wb[4][4][NT];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const int e = (wave + 4 * k) * 16 + 4 * s + q, i = 16 * nt + r;
+                const float v = to_f32(static_cast<const T *>(a.w_b)[(size_t)(e0 + min(e, ew - 1)) * a.n + min(i, a.n - 1)]);
+                wb[k][s][nt] = (e < ew && i < a.n) ? v : 0.f;
+            }
+    rb_f32x4 wacc[4][NT];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) wacc[k][nt] = {0.f, 0.f, 0.f, 0.f};
+    RawPiece<T> pre[4];
+    const int row0 = tid / 32, pc = (tid % 32) * 8;
+    auto fetch = [&](long t) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const long tk = t + row0 + 8 * v;
+            const bool in = tk < tok1 && pc < ew;
+            const uint4 *src = reinterpret_cast<const uint4 *>(static_cast<const T *>(a.x) + (size_t)(in ? tk : tok0) * a.d + (in ? e0 + pc : 0));
+#pragma unroll
+            for (int h = 0; h < (int)(sizeof(RawPiece<T>) / 16); ++h) {
+                const uint4 w = src[h];
+                pre[v].v[h] = in ? w : make_uint4(0, 0, 0, 0);
+            }
+        }
+    };
+    fetch(tok0);
+    for (long t = tok0; t < tok1; t += BT) {
+        float ub[8][NT];
+#pragma unroll
+        for (int s = 0; s < 8; ++s)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const long tk = t + 4 * s + q;
+                const int i = 16 * nt + r;
+                const float v = a.u[min(tk, tok1 - 1) * a.n + min(i, a.n - 1)];
+                ub[s][nt] = (tk < tok1 && i < a.n) ? v : 0.f;
+            }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            float o[8];
+            load8(reinterpret_cast<const T *>(pre[v].v), o);
+            float *dst = xs + (row0 + 8 * v) * BST + pc;
+            *reinterpret_cast<float4 *>(dst) = make_float4(o[0], o[1], o[2], o[3]);
+            *reinterpret_cast<float4 *>(dst + 4) = make_float4(o[4], o[5], o[6], o[7]);
+        }
+        __syncthreads();
+        if (t + BT < tok1) fetch(t + BT);
+        rb_f32x4 ta[2][NT];
+#pragma unroll
+        for (int tt = 0; tt < 2; ++tt)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) ta[tt][nt] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int et = (wave + 4 * k) * 16;
+            if (et >= ew) continue;
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int tt = 0; tt < 2; ++tt) {
+                    const float xv = xs[(tt * 16 + r) * BST + et + 4 * s + q];
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) ta[tt][nt] = mfma_f32(xv, wb[k][s][nt], ta[tt][nt]);
+                }
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+                const float xv = xs[(4 * s + q) * BST + et + r];
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) wacc[k][nt] = mfma_f32(xv, ub[s][nt], wacc[k][nt]);
+            }
+        }
+#pragma unroll
+        for (int tt = 0; tt < 2; ++tt)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) red[(wave * BT + tt * 16 + 4 * q + e) * rst + nt * 16 + r] = ta[tt][nt][e];
+        __syncthreads();
+        const int ntok = (int)min((long)BT, tok1 - t);
+        for (int idx = tid; idx < ntok * a.n; idx += 256) {
+            const int tk = idx / a.n, i = idx - tk * a.n;
+            float s = 0.f;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) s += red[(w * BT + tk) * rst + i];
+            t1[(size_t)t * a.n + idx] = s;
+        }
+    }
+    float *dst = a.wb_part + (size_t)chunk * a.d * a.n;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int ee = (wave + 4 * k) * 16 + 4 * q + e, i = 16 * nt + r;
+                if (ee < ew && i < a.n) dst[(size_t)(e0 + ee) * a.n + i] = wacc[k][nt][e];
+            }
+}
+
+// The three kinds side by side.  Consecutive groups of a column chunk (experts of dW_E, samples of d_x) get block
+// ids 8 apart, so that they run on one XCD and its L2 serves the second reading of x or W_E.
+// NT: 16-expert tiles of the data router, 0 without one.  Registers are capped so that a compute unit holds 16 waves
+// of the 4-sample form and 12 of the 8-sample form (fewer in fp32 and with a second expert tile, which would spill):
+// the two streaming kinds live on loads in flight.
+constexpr int main_waves(int bg, bool f32, int nt) { return (bg == 4 ? 4 : 3) - f32 - (nt == 2) < 2 ? 2 : (bg == 4 ? 4 : 3) - f32 - (nt == 2); }
+template <typename T, int BG, bool ONCE, int NT>
+__global__ __launch_bounds__(256, main_waves(BG, sizeof(T) == 4, NT)) void route_bwd_main_kernel(RouteBwdArgs a)
+{
+    extern __shared__ __align__(16) float smem[];
+    const RouteBwdPlan &p = a.plan;
+    int id = blockIdx.x;
+    if constexpr (NT > 0) {  // first: its chains are the longest (last: 211 -> 235 us on the largest shape)
+        if (id < p.data_blocks) {
+            if (id < p.wb_chunks * p.slices) bwd_data<T, NT>(a, smem, id / p.slices, id % p.slices);
+            return;
+        }
+        id -= p.data_blocks;
+    }
+    if (id < p.dx_blocks) {
+        const int o = id / 8, chunk = (o / p.dx_groups) * 8 * p.dx_reps + id % 8;
+        if (chunk < p.dx_chunks) bwd_dx<T, BG, ONCE>(a, smem, chunk, (o % p.dx_groups) * BG);
+        return;
+    }
+    id -= p.dx_blocks;
+    const int o = id / 8, chunk = (o / p.w_groups) * 8 * p.w_reps + id % 8;
+    if (chunk < p.w_chunks) bwd_wexpert<T, ONCE>(a, smem, chunk, (o % p.w_groups) * 8);
+}
+
+// dW_A[t,j] = sum over k = (sample, expert) of t1[t,k] dL[k,j]: block = 16 tokens x up to 128 patches; its 8 waves
+// are 1, 2 or 4 pairs of 16-patch tiles x parts of k, added in order.  The blocks behind them add the chunks'
+// partials of dW_B: 32 outputs x 16 lanes (lane q takes chunks q, q+16, ...), then the lanes in order.
+template <typename T> __global__ __launch_bounds__(512) void route_bwd_finish_kernel(RouteBwdArgs a, int wa_x, int wa_y, int jw)
+{
+    __shared__ float red[8][16][33];
+    const int tid = threadIdx.x, id = blockIdx.x;
+    if (id < wa_x * wa_y) {
+        const int wave = tid >> 6, r = tid & 15, q = (tid & 63) >> 4, K = a.b * a.n, slices = a.plan.slices;
+        const int kw = 8 / jw, t0 = (id % wa_x) * 16, j00 = (id / wa_x) * 32 * jw, j0 = j00 + 32 * (wave % jw);
+        const int t = min(t0 + r, a.l - 1), ja = min(j0 + r, a.m - 1), jb = min(j0 + 16 + r, a.m - 1);
+        const size_t slice = (size_t)a.b * a.l * a.n;
+        rb_f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+        for (int k0 = 4 * (wave / jw); k0 < K; k0 += 16 * kw) {  // four steps' loads in flight
+            float v[4] = {0.f, 0.f, 0.f, 0.f}, da[4], db[4];
+            const float *src[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int k = min(k0 + q + 4 * kw * u, K - 1), bb = k / a.n, i = k - bb * a.n;
+                src[u] = a.t1 + ((size_t)bb * a.l + t) * a.n + i;
+                da[u] = a.dl[(size_t)k * a.m + ja];
+                db[u] = a.dl[(size_t)k * a.m + jb];
+            }
+            for (int s = 0; s < slices; ++s)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v[u] += src[u][(size_t)s * slice];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (k0 + q + 4 * kw * u >= K) v[u] = da[u] = db[u] = 0.f;
+                acc[0] = mfma_f32(v[u], da[u], acc[0]);
+                acc[1] = mfma_f32(v[u], db[u], acc[1]);
+            }
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) red[wave][4 * q + e][16 * h + r] = acc[h][e];
+        __syncthreads();
+        for (int idx = tid; idx < 16 * 32 * jw; idx += 512) {
+            const int tk = idx / (32 * jw), jj = idx - tk * 32 * jw;
+            if (t0 + tk >= a.l || j00 + jj >= a.m) continue;
+            float s = 0.f;
+            for (int w = 0; w < kw; ++w) s += red[w * jw + jj / 32][tk][jj % 32];
+            static_cast<T *>(a.d_w_a)[(size_t)(t0 + tk) * a.m + j00 + jj] = from_f32<T>(s);
+        }
+        return;
+    }
+    const int ol = tid & 31, ql = tid >> 5, total = a.d * a.n, idx = (id - wa_x * wa_y) * 32 + ol, chunks = a.plan.wb_chunks;
+    const float *part = a.wb_part + min(idx, total - 1);
     float s = 0.f;
-    if (idx < total)
-        for (int p = ql; p < a.wb_chunks; p += 8) s += a.wb_part[(size_t)p * total + idx];
-    red[ql][ol] = s;
+    for (int p = ql; p < chunks; p += 8 * 16) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = part[(size_t)min(p + 16 * u, chunks - 1) * total];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += p + 16 * u < chunks ? v[u] : 0.f;
+    }
+    float *col = &red[0][0][0];
+    col[ql * 33 + ol] = s;
     __syncthreads();
     if (ql == 0 && idx < total) {
         float v = 0.f;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) v += red[q][ol];
+        for (int q = 0; q < 16; ++q) v += col[q * 33 + ol];
         static_cast<T *>(a.d_w_b)[idx] = from_f32<T>(v);
     }
 }
 
-template <typename T> static hipError_t route_backward(const RouteBwdArgs &a, hipStream_t st)
+// Launch shape: chunks and groups of the three kinds of workgroup.
+RouteBwdPlan route_bwd_plan(int b, int l, int d, int n, bool has_e, bool has_d)
+{
+    RouteBwdPlan p{};
+    const long pieces = (long)l * d / 8, tokens = (long)b * l;
+    const int P = d / 8;
+    auto up8 = [](long v) { return (int)((v + 7) & ~7L); };
+    // chunks per block: the gates are staged once for all of them; 2048 blocks keep every compute unit's slots filled
+    auto reps = [](long blocks) { return (int)(blocks < 4096 ? 1 : (blocks > 8 * 2048 ? 8 : blocks / 2048)); };
+    // d_x: 8 samples per thread, 4 where that leaves compute units without a block or half of the lanes' work to
+    // absent samples; at most 32 tokens per block (their rows of U are staged in LDS)
+    p.dx_pieces = 30 * P < 256 ? 30 * P : 256;
+    p.dx_chunks = (int)((pieces + p.dx_pieces - 1) / p.dx_pieces);
+    p.dx_bg = (b <= 4 || (long)p.dx_chunks * ((b + 7) / 8) < 256) ? 4 : 8;
+    p.dx_groups = (b + p.dx_bg - 1) / p.dx_bg;
+    p.dx_reps = reps((long)p.dx_chunks * p.dx_groups);
+    p.dx_blocks = up8((p.dx_chunks + p.dx_reps - 1) / p.dx_reps) * p.dx_groups;
+    if (has_e) {
+        p.w_groups = (n + 7) / 8;
+        p.wsplit = b >= 16 && pieces * p.w_groups < 512L * 256;
+        p.w_chunks = (int)((pieces + (p.wsplit ? 31 : 255)) / (p.wsplit ? 32 : 256));
+        p.w_reps = reps((long)p.w_chunks * p.w_groups);
+        p.w_blocks = up8((p.w_chunks + p.w_reps - 1) / p.w_reps) * p.w_groups;
+    }
+    if (has_d) {
+        p.slices = (d + ROUTE_BWD_SLICE - 1) / ROUTE_BWD_SLICE;
+        p.slice_w = ((d + p.slices - 1) / p.slices + 15) & ~15;
+        // about 512 workgroups, each at least one tile of tokens
+        const long want = (tokens * p.slices + 511) / 512;
+        p.chunk_tokens = (int)((want + ROUTE_BWD_TILE - 1) / ROUTE_BWD_TILE) * ROUTE_BWD_TILE;
+        p.wb_chunks = (int)((tokens + p.chunk_tokens - 1) / p.chunk_tokens);
+        p.data_blocks = up8((long)p.wb_chunks * p.slices);
+    }
+    return p;
+}
+
+template <typename T> static hipError_t route_backward(RouteBwdArgs a, hipStream_t st)
 {
     hipError_t err;
-    hipLaunchKernelGGL(route_bwd_softmax_kernel, dim3(a.b, a.w_b ? (a.m + 63) / 64 : 1), dim3(64), 0, st, a);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-    const long pieces = (long)a.l * a.d / 8;
-    const unsigned pblocks = (unsigned)((pieces + 255) / 256);
-    if (a.w_e) {
-        const bool once = stream_once((size_t)a.n * a.l * a.d * sizeof(T));
-        if (once) hipLaunchKernelGGL((route_bwd_wexpert_kernel<T, true>), dim3(pblocks, (a.n + 7) / 8), dim3(256), 0, st, a);
-        else hipLaunchKernelGGL((route_bwd_wexpert_kernel<T, false>), dim3(pblocks, (a.n + 7) / 8), dim3(256), 0, st, a);
-        if ((err = hipGetLastError()) != hipSuccess) return err;
-        if (once) hipLaunchKernelGGL((route_bwd_xexpert_kernel<T, true>), dim3(pblocks, (a.b + 7) / 8), dim3(256), 0, st, a);
-        else hipLaunchKernelGGL((route_bwd_xexpert_kernel<T, false>), dim3(pblocks, (a.b + 7) / 8), dim3(256), 0, st, a);
+    a.plan = route_bwd_plan(a.b, a.l, a.d, a.n, a.w_e != nullptr, a.w_b != nullptr);
+    const RouteBwdPlan &p = a.plan;
+    if (a.w_b) {
+        const int extra = (a.d * a.n + 2048 * a.b - 1) / (2048 * a.b);  // 8 elements of W_B^T per thread
+        hipLaunchKernelGGL((route_bwd_prep_kernel<T>), dim3((a.l + PREP_TOK - 1) / PREP_TOK + extra, a.b), dim3(256), 0, st, a);
         if ((err = hipGetLastError()) != hipSuccess) return err;
     }
+    size_t floats = 0;
+    auto need = [&](size_t v) { floats = v > floats ? v : floats; };
+    if (a.w_e) need((size_t)a.b * 8 + 2 * (size_t)a.b * a.n);
+    if (a.w_e) need((size_t)a.n * p.dx_bg * 3);
+    const int P = a.d / 8, ntok = (p.dx_pieces + P - 2) / P + 1;  // tokens a d_x block can touch
+    need((size_t)a.n * p.dx_bg * (1 + (a.w_b ? ntok : 0)));
+    if (a.w_b) need((size_t)BT * BST + 4 * BT * (((a.n + 15) & ~15) + 1));
+    const dim3 grid(p.data_blocks + p.dx_blocks + p.w_blocks);
+    const bool once = a.w_e && sizeof(T) == 2 && stream_once((size_t)a.n * a.l * a.d * sizeof(T));
+    const size_t lds = floats * sizeof(float);
+    auto launch = [&](auto bg, auto hint) {
+        constexpr int BG = decltype(bg)::value;
+        constexpr bool ONCE = decltype(hint)::value && sizeof(T) == 2;
+        if (!a.w_b) hipLaunchKernelGGL((route_bwd_main_kernel<T, BG, ONCE, 0>), grid, dim3(256), lds, st, a);
+        else if (a.n <= 16) hipLaunchKernelGGL((route_bwd_main_kernel<T, BG, ONCE, 1>), grid, dim3(256), lds, st, a);
+        else hipLaunchKernelGGL((route_bwd_main_kernel<T, BG, ONCE, 2>), grid, dim3(256), lds, st, a);
+    };
+    using std::integral_constant;
+    if (p.dx_bg == 4) once ? launch(integral_constant<int, 4>{}, std::true_type{}) : launch(integral_constant<int, 4>{}, std::false_type{});
+    else once ? launch(integral_constant<int, 8>{}, std::true_type{}) : launch(integral_constant<int, 8>{}, std::false_type{});
+    if ((err = hipGetLastError()) != hipSuccess) return err;
     if (a.w_b) {
-        const size_t smem = ((((size_t)a.n * a.m + 64 * (size_t)a.n) * sizeof(float) + 15) & ~(size_t)15) + (size_t)a.d * a.n * sizeof(T);
-        if ((long)((a.l + 63) / 64) * a.b >= 256)
-            hipLaunchKernelGGL((route_bwd_data_token_kernel<T, 4>), dim3((a.l + 63) / 64, a.b), dim3(256), smem, st, a);
-        else
-            hipLaunchKernelGGL((route_bwd_data_token_kernel<T, 16>), dim3((a.l + 15) / 16, a.b), dim3(256), smem, st, a);
-        if ((err = hipGetLastError()) != hipSuccess) return err;
-        hipLaunchKernelGGL((route_bwd_wa_kernel<T>), dim3((unsigned)(((long)a.l * a.m + 255) / 256)), dim3(256), 0, st, a);
-        if ((err = hipGetLastError()) != hipSuccess) return err;
-        hipLaunchKernelGGL((route_bwd_wb_partial_kernel<T>), dim3(a.wb_chunks, (a.n + 15) / 16), dim3(256), 0, st, a);
-        if ((err = hipGetLastError()) != hipSuccess) return err;
-        hipLaunchKernelGGL((route_bwd_wb_reduce_kernel<T>), dim3((a.d * a.n + 31) / 32), dim3(256), 0, st, a);
+        const int jw = a.m <= 32 ? 1 : (a.m <= 64 ? 2 : 4), wa_x = (a.l + 15) / 16, wa_y = (a.m + 32 * jw - 1) / (32 * jw);
+        hipLaunchKernelGGL((route_bwd_finish_kernel<T>), dim3(wa_x * wa_y + (a.d * a.n + 31) / 32), dim3(512), 0, st, a, wa_x, wa_y, jw);
         if ((err = hipGetLastError()) != hipSuccess) return err;
     }
     return hipSuccess;

@@ -101,3 +101,56 @@ def test_uome_backward_odd_sizes(name, flags):
 @pytest.mark.parametrize("flags,rope_dim,pad_frac", [(0, 0, 0.0), (CA | R | GE | GP, 8, 0.2)])
 def test_smha_backward_odd_sizes(name, flags, rope_dim, pad_frac):
     P.run_smha_backward(name, flags, rope_dim, pad_frac=pad_frac)
+
+
+# --------------------------------------------------------------------------- router backward
+ROUTE_BWD = {
+    # one sample and 8 samples or fewer per d_x thread, columns below one 16-tile, one patch
+    "rb_one": P.small(b=1, l=3, d=8, n_a=1, d_h=8, m=1, c=1, k_a=1, n_m=1, d_e=8, k_m=1),
+    "rb_d24": P.small(b=5, l=130, d=24, n_a=3, d_h=8, m=10, c=2, k_a=2, n_m=2, d_e=8, k_m=1, dtype=BF),
+    # samples shared by eight lanes of dW_E (b >= 8), second expert tile, two column slices, the last one short
+    "rb_n17": P.small(b=9, l=65, d=264, n_a=17, d_h=8, m=65, c=2, k_a=2, n_m=2, d_e=8, k_m=1, dtype=BF),
+    "rb_f32_n32": P.small(b=13, l=66, d=264, n_a=32, d_h=8, m=33, c=2, k_a=2, n_m=2, d_e=8, k_m=1),
+    # eight samples per d_x thread (256 column chunks and more), the last group of one; chunks of more than one tile
+    "rb_b9_long": P.small(b=9, l=2100, d=256, n_a=4, d_h=8, m=70, c=2, k_a=2, n_m=2, d_e=8, k_m=1, dtype=BF),
+    # 2048 columns: eight slices
+    "rb_d2048": P.small(b=2, l=40, d=2048, n_a=5, d_h=8, m=8, c=2, k_a=2, n_m=2, d_e=8, k_m=1, dtype=BF),
+}
+P.EDGE_CONFIGS.update(ROUTE_BWD)
+
+
+@pytest.mark.parametrize("name", list(ROUTE_BWD))
+@pytest.mark.parametrize("routers", ["both", "expert", "data"])
+def test_route_backward_odd_sizes(name, routers, monkeypatch):
+    """A call with one router only leaves the other one's outputs alone and adds its own part to d_x."""
+    if routers == "both":
+        P.test_route_backward_parity(name)
+        return
+    print(f"route backward {name} {routers}", flush=True)
+    monkeypatch.setenv("UOE_STREAM_ONCE_MIN_BYTES", "0")  # the hinted accesses as well
+    cfg = P.get_cfg(name)
+    inp = synth.make_inputs(cfg, w_std=0.02)
+    inp.a_w_expert = inp.a_w_expert * P.np.float32(0.25)
+    e, d = (inp.a_w_expert, None) if routers == "expert" else (None, inp.a_w_b)
+    wa = None if d is None else inp.a_w_a
+    ref = P.oracle.route(inp.x, cfg.n_a, cfg.k_a, cfg.m, cfg.c, inp.a_w_expert, inp.a_w_b, inp.a_w_a, None, None)
+    ge, gp = ref.expert_gate.astype("float32"), ref.patch_gate.astype("float32")
+    d_ge, d_gp = synth.make_gate_grads(cfg, cfg.n_a, cfg.m)
+    d_x0 = synth.make_upstream_grad(cfg)
+    dev = P.DeviceLayer(inp, R, R)
+    f32 = lambda a: P.to_device(a, synth.F32, dev.device)
+    d_x = P.to_device(d_x0, cfg.dtype, dev.device)
+    d_we, d_wb, d_wa = (P.torch.full_like(t, 7.0) for t in (dev.a_w_expert, dev.a_w_b, dev.a_w_a))
+    ws = P.torch.empty(B.route_backward_workspace_bytes(dev.smha), dtype=P.torch.uint8, device=dev.device)
+    B.route_backward(dev.smha, dev.x, None if e is None else dev.a_w_expert, None if d is None else dev.a_w_b,
+                     None if d is None else dev.a_w_a, f32(ge), f32(gp), f32(d_ge), f32(d_gp), d_x, d_we, d_wb, d_wa, ws)
+    P.torch.cuda.synchronize()
+    want = P.oracle.route_backward(inp.x, e, d, wa, ge, gp, d_ge, d_gp)
+    errs = [P.scaled_err(P.to_host(d_x), d_x0.astype("float64") + want.d_x)]
+    if d is None:
+        errs.append(P.grad_err(P.to_host(d_we), want.d_w_expert))
+        assert bool((d_wb == 7.0).all()) and bool((d_wa == 7.0).all())
+    else:
+        errs += [P.grad_err(P.to_host(d_wb).T, want.d_w_b.T), P.grad_err(P.to_host(d_wa).T, want.d_w_a.T)]
+        assert bool((d_we == 7.0).all())
+    assert max(errs) <= P.TOL[cfg.dtype], errs
