@@ -88,7 +88,7 @@ size_t uome_ws(const uoe_block_desc *d) { return up((size_t)d->b * d->l * d->k *
 // backward pass of the UoME block: Z, dH, dZ [b,l,k*d_e]; dZ^T, H^T [b,k*d_e,l]; the two transposed
 // weight tensors; split-K tiles of one weight gradient; partial sums of the gate gradient
 struct UomeBwdWs {
-    size_t z, dh, dz, dz_t, h_t, a_in_t, a_out_t, partial, gpart, rt, total;
+    size_t z, dh, dz, h, h_op, dz_op, partial, gpart, rt, total;
     int splits, gchunks;
 };
 static bool uome_bwd_mfma(const uoe_block_desc *blk);
@@ -98,9 +98,9 @@ UomeBwdWs uome_bwd_ws(const uoe_block_desc *d)
     if (!uome_bwd_mfma(d)) {  // any-shape path: Z then H, dH then dZ, four bytes an element
         const size_t act32 = up((size_t)d->b * d->l * d->k * d->width * sizeof(float));
         w.z = 0; w.dh = act32; w.total = 2 * act32;
-        w.h_t = w.z; w.dz_t = w.dh;
+        w.h_op = w.z; w.dz_op = w.dh;
         if (d->width > 2048 && d->dtype == UOE_BF16) {   // rows of (hi, lo) pairs longer than the kernel rewrites in place
-            w.h_t = w.total; w.dz_t = w.total + act32; w.total += 2 * act32;
+            w.h_op = w.total; w.dz_op = w.total + act32; w.total += 2 * act32;
         }
         // weight gradients: chunks of 128 samples x ranges of the token axis (at most 8) until about 4096 tiles of
         // 64x64 exist, a few rounds of them per CU; partial tiles in fp32, added in order
@@ -122,15 +122,10 @@ UomeBwdWs uome_bwd_ws(const uoe_block_desc *d)
     }
     const size_t es = elem_size(d->dtype);
     const size_t act = up((size_t)d->b * d->l * d->k * d->width * es);
-    const size_t wt = up((size_t)d->n * d->d * d->width * es);
     size_t off = 0;
     w.z = off; off += act;
-    w.dh = off; off += act;
     w.dz = off; off += act;
-    w.dz_t = off; off += act;
-    w.h_t = off; off += act;
-    w.a_in_t = off; off += wt;
-    w.a_out_t = off; off += wt;
+    w.h = off; off += act;
     // data-selection mode (c < m) works on at most as many rows (units * l_a <= b * k * l) in the same
     // buffers; its weight gradients are cut by (unit, pick) segments instead of token ranges
     w.splits = d->c < d->m ? smha_backward_splits(d->b, d->n, d->k, d->c)
@@ -139,7 +134,7 @@ UomeBwdWs uome_bwd_ws(const uoe_block_desc *d)
     off += up(2 * (size_t)d->n * w.splits * d->d * d->width * sizeof(float));  // both weight gradients
     w.gchunks = uome_backward_gate_chunks(d->l, d->width);
     w.gpart = off; off += up((size_t)d->b * d->k * w.gchunks * sizeof(float));
-    w.rt = off; off += up((size_t)d->b * d->k * d->l * sizeof(float));
+    w.rt = off; off += up((size_t)((d->width + 63) / 64) * d->b * d->k * d->l * sizeof(float));
     w.total = off;
     return w;
 }
@@ -163,7 +158,7 @@ int check_uome_bwd(const uoe_block_desc *blk)
 // backward pass of the SMHA block: the forward's scratch, then the backward's own
 struct SmhaBwdWs {
     SmhaWs fwd;
-    size_t lse, rt, dd, wo_t, wqkv_t, do_raw, d_o, o_t, dqkv, dqkv_t, partial, total;
+    size_t lse, rt, dd, wqkv_t, do_raw, d_o, og, dqkv, partial, total;
     size_t g_q, g_k, g_v, g_og;  // any-shape path (four bytes an element)
     int splits;
 };
@@ -210,13 +205,11 @@ SmhaBwdWs smha_bwd_ws(const uoe_block_desc *d)
     w.lse = off; off += rows;
     w.rt = off; off += rows;
     w.dd = off; off += rows;
-    w.wo_t = off; off += up((size_t)d->n * d->d * d->width * es);
     w.wqkv_t = off; off += up(3 * (size_t)d->n * d->d * d->width * es);
     w.do_raw = off; off += up(units * l_a * d->width * sizeof(float));
     w.d_o = off; off += one;
-    w.o_t = off; off += one;
+    w.og = off; off += one;
     w.dqkv = off; off += 3 * one;
-    w.dqkv_t = off; off += 3 * one;
     w.partial = off;
     w.splits = smha_backward_splits(d->b, d->n, d->k, d->c);
     off += up((size_t)d->n * w.splits * 4 * d->width * d->d * sizeof(float));
@@ -583,15 +576,14 @@ int uoe_uome_backward(const uoe_block_desc *blk, const void *u, const void *a_in
     a.b = blk->b; a.l = blk->l; a.d = blk->d; a.n = blk->n; a.k = blk->k; a.d_e = blk->width; a.flags = blk->flags;
     if (!uome_bwd_mfma(blk)) {
         a.z = at(ws, w.z); a.dh = at(ws, w.dh);
-        a.h_op = at(ws, w.h_t); a.dz_op = at(ws, w.dz_t);
+        a.h_op = at(ws, w.h_op); a.dz_op = at(ws, w.dz_op);
         a.splits = w.splits; a.gchunks = w.gchunks;
         a.partial = reinterpret_cast<float *>(at(ws, w.partial));
         a.gpart = reinterpret_cast<float *>(at(ws, w.gpart));
         return launch_uome_backward_any(a, blk->dtype == UOE_BF16, static_cast<hipStream_t>(hip_stream)) == hipSuccess
                    ? UOE_OK : UOE_ERR_DEVICE;
     }
-    a.z = at(ws, w.z); a.dh = at(ws, w.dh); a.dz = at(ws, w.dz);
-    a.dz_t = at(ws, w.dz_t); a.h_t = at(ws, w.h_t); a.a_in_t = at(ws, w.a_in_t); a.a_out_t = at(ws, w.a_out_t);
+    a.z = at(ws, w.z); a.dz = at(ws, w.dz); a.h = at(ws, w.h);
     a.gpart = reinterpret_cast<float *>(at(ws, w.gpart));
     a.partial = reinterpret_cast<float *>(at(ws, w.partial));
     a.gchunks = w.gchunks;
@@ -650,8 +642,8 @@ int uoe_smha_backward(const uoe_block_desc *blk, const void *x, const uoe_smha_w
     a.d_out = d_out; a.expert_gate = expert_gate; a.patch_gate = patch_gate; a.flags = blk->flags;
     a.d_x = d_x; a.d_wq = dw->d_wq; a.d_wk = dw->d_wk; a.d_wv = dw->d_wv; a.d_wo = dw->d_wo;
     a.d_expert_gate = d_expert_gate; a.d_patch_gate = d_patch_gate;
-    a.wo_t = at(ws, s.wo_t); a.wqkv_t = at(ws, s.wqkv_t); a.do_raw = reinterpret_cast<float *>(at(ws, s.do_raw)); a.d_o = at(ws, s.d_o);
-    a.o_t = at(ws, s.o_t); a.dqkv = at(ws, s.dqkv); a.dqkv_t = at(ws, s.dqkv_t);
+    a.wqkv_t = at(ws, s.wqkv_t); a.do_raw = reinterpret_cast<float *>(at(ws, s.do_raw)); a.d_o = at(ws, s.d_o);
+    a.og = at(ws, s.og); a.dqkv = at(ws, s.dqkv);
     a.rt = reinterpret_cast<float *>(at(ws, s.rt)); a.dd = reinterpret_cast<float *>(at(ws, s.dd));
     a.partial = reinterpret_cast<float *>(at(ws, s.partial));
     a.splits = s.splits;

@@ -170,19 +170,18 @@ struct UomeBwdArgs {
     int b, l, d, n, k, d_e;
     uint32_t flags;
     // workspace, storage dtype unless noted
-    void *z, *dh, *dz;                        // [b, l, k*d_e] each
-    void *dz_t, *h_t;                         // [b, k*d_e, l] each
-    void *a_in_t, *a_out_t;                   // [n, d_e, d], [n, d, d_e]
+    void *z, *dz, *h;                         // [b, l, k*d_e] each
+    void *dh;                                 // any-shape path: dH, fp32
     float *gpart;                             // [b, k, gchunks] partial sums of d_gate
     float *partial;                           // [2*n*splits, d_e, d] split-K tiles of the two weight gradients
     int gchunks, splits;
     void *h_op, *dz_op;                       // any-shape path: H and dZ as left operands (may be z and dh themselves)
     // data-selection mode (patch_idx != NULL): units = (sample, slot) with l_a = c*l/m gathered rows;
-    // z, dh, dz are [units, l_a, d_e], dz_t and h_t [units, d_e, l_a]
+    // z, dz, h are [units, l_a, d_e]
     const int32_t *patch_idx;
     const float *patch_gate;                  // NULL when GATE_PATCH is off
     float *d_patch_gate;                      // [b,n,m] or NULL
-    float *rt;                                // [units, l_a]: dL/d(weight of row t)
+    float *rt;                                // [ceil(d_e/64), units, l_a]: parts of dL/d(weight of row t)
     int m, c;
 };
 
@@ -195,15 +194,15 @@ struct SmhaBwdArgs {
     void *d_x, *d_wq, *d_wk, *d_wv, *d_wo;    // [b,l,d], 3 x [n,d,d_h], [n,d_h,d], storage dtype
     float *d_expert_gate, *d_patch_gate;      // [b,n], [b,n,m], or NULL
     // workspace, storage dtype unless noted
-    void *wo_t, *wqkv_t;                      // [n, d, d_h], [n, 3*d_h, d]
+    void *wqkv_t;                             // [n, 3*d_h, d]
     float *do_raw;                            // [units, l_a, d_h] fp32
     void *d_o;                                // [units, l_a, d_h]
-    void *o_t;                                // [units, d_h, l_a]
-    void *dqkv, *dqkv_t;                      // [units, l_a, 3*d_h], [units, 3*d_h, l_a]
+    void *dqkv;                               // [units, l_a, 3*d_h]
     float *rt, *dd;                           // [units, l_a] each: dL/dw_t and the softmax row term
+    int rt_parts;                             // rt is that many arrays to be added (0: one)
     float *partial;                           // [4*n*splits, d_h, d] split tiles of the four weight gradients
     int splits;
-    void *og;                                 // any-shape path: w o as a left operand [units, l_a, parts, d_h]; do_raw, q, k, v are
+    void *og;                                 // w o [units, l_a, d_h]; any-shape path: [units, l_a, parts, d_h], do_raw, q, k, v are
                                               // fp32 there and dqkv is [units, l_a, parts, 3*d_h]
 };
 

@@ -124,6 +124,10 @@ __device__ __forceinline__ uint32_t pack2_f16_rn(float a, float b)
 template <typename P, typename = void> struct streams_once : std::false_type {};
 template <typename P> struct streams_once<P, std::void_t<decltype(std::declval<P>().once)>> : std::true_type {};
 
+// problems with a second half of their own: write_out<TM, TN, SPITCH>(stage, coltab + first 8-column group, rs, ...)
+template <typename P, typename = void> struct writes_itself : std::false_type {};
+template <typename P> struct writes_itself<P, std::void_t<decltype(P::kWriteOut)>> : std::true_type {};
+
 // second half of the epilogue: the staged wave tile back out of LDS in 16-byte pieces, the residual
 // added, the pieces stored (ONCE: through the problem's non-temporal accessors)
 template <typename P, int TM, int TN, int SPITCH, bool ONCE>
@@ -211,7 +215,9 @@ __device__ __forceinline__ void wave_epilogue(const P &p, f32x16_t (&acc)[TM][TN
     // Problems with a `once` member choose per launch whether the residual read and the output store carry
     // the non-temporal hint; the choice is made here, once per wave, so that each version keeps its
     // batch of residual loads in flight (a test per access would put a branch between them).
-    if constexpr (streams_once<P>::value) {
+    if constexpr (writes_itself<P>::value) {
+        p.template write_out<TM, TN, SPITCH>(stage, coltab + (wcol0 >> 3), rs, g, grow0, gcol0, M, N, lane);
+    } else if constexpr (streams_once<P>::value) {
         if (p.once) wave_write_out<P, TM, TN, SPITCH, true>(p, stage, g, grow0, gcol0, M, N, lane);
         else wave_write_out<P, TM, TN, SPITCH, false>(p, stage, g, grow0, gcol0, M, N, lane);
     } else {

@@ -162,6 +162,7 @@ template <typename T> struct OutProjProblem {
     int o_row;  // elements between rows of o (d_h, or more when its rows are padded)
     int parts;  // 1: o only; 2: o is a (hi, lo) pair of buffers, contracted as [hi | lo] x [W^o ; W^o]
     uint32_t flags;
+    int w_nk = 0;   // wo is [n, d, d_h] (engine flag GEMM_B_NK)
 
     __device__ int rows(int) const { return l_p; }
     __device__ int kdim(int) const { return 0; }  // prepare() supplies K
@@ -216,7 +217,10 @@ template <typename T> struct OutProjProblem {
         const T *src = (ctx >> 26) & 1u ? o_lo : o;
         return src + (((size_t)bb * kact + s) * l_a + t * l_p + r) * o_row;
     }
-    __device__ const T *b_ptr_ctx(int, int, int nn, uint32_t ctx) const { return wo + (size_t)((ctx >> 20) & 0x3Fu) * d_h * d + nn; }
+    __device__ const T *b_ptr_ctx(int, int, int nn, uint32_t ctx) const
+    {
+        return wo + (size_t)((ctx >> 20) & 0x3Fu) * d_h * d + (size_t)nn * (w_nk ? d_h : 1);
+    }
     static constexpr bool kColScale = false;
     __device__ float col_scale(int, int) const { return 1.0f; }
     __device__ float epi(float val, float) const { return val; }
@@ -353,6 +357,7 @@ template <typename T> struct UomeDownProblem {
     T *out;
     int l, d, n, kact, d_e;
     uint32_t flags;
+    int w_nk = 0;        // a_out is [n, d, d_e] (engine flag GEMM_B_NK)
 
     __device__ int rows(int) const { return l; }
     __device__ int kdim(int) const { return kact * d_e; }
@@ -371,7 +376,7 @@ template <typename T> struct UomeDownProblem {
     // pipelined engine: the segment's expert, looked up once before the loop
     __device__ uint32_t seg_ctx(int g, int seg) const { return (uint32_t)clampi(expert_idx[g * kact + clampi(seg, kact)], n); }
     __device__ const T *a_ptr_ctx(int g, int r, int seg, uint32_t) const { return a_seg_ptr(g, r, seg); }
-    __device__ const T *b_ptr_ctx(int, int, int nn, uint32_t i) const { return a_out + (size_t)i * d_e * d + nn; }
+    __device__ const T *b_ptr_ctx(int, int, int nn, uint32_t i) const { return a_out + (size_t)i * d_e * d + (size_t)nn * (w_nk ? d_e : 1); }
     __device__ float epi_f32(float val, float) const { return val; }
     __device__ void put4(int g, int r, int nn, float4 val) const
     {
@@ -396,31 +401,29 @@ template <typename T> struct UomeDownProblem {
 // Weight gradients of the backward passes, as split contractions over the tokens with fp32 partial
 // tiles.  A launch covers up to four gradient tensors ("sets") of the same shape [n][M][N] at once:
 // group = (set * n + expert) * splits + part, partial tile [group][M][N]; a reduction kernel adds
-// the parts in order.  The left factor of a set is given TRANSPOSED, token-minor (rows are
-// K-contiguous like every A operand); the right factor in its natural token-major layout.
+// the parts in order.  Both factors are read as the other kernels wrote them, token-major (engine flag GEMM_A_KM):
+// a transposed copy of the left one cost its writer 2-byte scattered LDS or memory stores and a third of its traffic.
 //
 // Expert-selection UoME: for expert i,
 //   dW[M, N] = sum over the (sample b, slot s) pairs with expert_idx[b,s] == i of  L_{b,s}^T R_b
 // contracted over the l tokens of the sample.  K segments = the pairs, found by the workgroup itself
 // (prepare), in sample order, which fixes the summation order; the token axis is cut into `splits`
 // equal ranges, part j contracts range j of every pair.
-//   set 0: dA^O_i   [d_e, d]:  left = H^T  [b][k*d_e][l] (rows s*d_e + e of the pair), right = d_out [b][l][d]
-//   set 1: dA^I_i^T [d_e, d]:  left = dZ^T [b][k*d_e][l] (the same rows),              right = u     [b][l][d]
+//   set 0: dA^O_i   [d_e, d]:  left = H  [b][l][k*d_e] (columns s*d_e + e of the pair), right = d_out [b][l][d]
+//   set 1: dA^I_i^T [d_e, d]:  left = dZ [b][l][k*d_e] (the same columns),              right = u     [b][l][d]
 template <typename T> struct WgradProblem {
-    const T *left_t[2], *right[2];
+    const T *left[2], *right[2];
     const int32_t *expert_idx;
     float *partial;        // [sets*n*splits, M, N]
     int b, l, n, kact, splits;
-    int M, N;              // rows and columns of one expert's gradient
-    int left_rows;         // rows of one sample in left_t (k*d_e)
-    int left_slot_rows;    // rows of one slot (d_e)
-    int right_stride;      // elements between token rows of right
+    int M, N;              // rows and columns of one expert's gradient (d_e and d)
 
     static constexpr bool kF32Out = true;
     __device__ int rows(int) const { return M; }
     __device__ int ncols() const { return N; }
     __device__ int kseg(int) const { return l / splits; }
-    __device__ long b_stride() const { return right_stride; }
+    __device__ long a_stride(int) const { return (long)kact * M; }
+    __device__ long b_stride() const { return N; }
     __device__ int kdim(int) const { return 0; }  // prepare() supplies K
     static constexpr bool kPrepare = true;
     // thread bb looks up which slot of sample bb (if any) holds the expert; the samples that do are
@@ -450,14 +453,14 @@ template <typename T> struct WgradProblem {
     __device__ const T *a_ptr_ctx(int g, int r, int, uint32_t ctx) const
     {
         const int bb = (int)(ctx >> 8), s = (int)(ctx & 0xFFu);
-        const T *base = g < n * splits ? left_t[0] : left_t[1];
-        return base + ((size_t)bb * left_rows + (size_t)s * left_slot_rows + r) * l + (g % splits) * (l / splits);
+        const T *base = g < n * splits ? left[0] : left[1];
+        return base + (((size_t)bb * l + (size_t)(g % splits) * (l / splits)) * kact + s) * M + r;
     }
     __device__ const T *b_ptr_ctx(int g, int, int nn, uint32_t ctx) const
     {
         const int bb = (int)(ctx >> 8);
         const T *base = g < n * splits ? right[0] : right[1];
-        return base + ((size_t)bb * l + (size_t)(g % splits) * (l / splits)) * right_stride + nn;
+        return base + ((size_t)bb * l + (size_t)(g % splits) * (l / splits)) * N + nn;
     }
     static constexpr bool kRowScale = false;
     static constexpr bool kColScale = false;
@@ -474,18 +477,18 @@ template <typename T> struct WgradProblem {
 
 // Blocks with patch-wise data selection (SMHA; the data-selected UoME): for expert i,
 //   dW[M, d] = sum over the units (b, slot s) of expert i and their c picks t of
-//              L^T[unit][M rows][tokens of pick t]  x  R[b][tokens of the picked patch][d]
-// i.e. the left factor is a per-unit tensor in token-minor layout [unit][rows][l_a] (the set's M
-// rows start at row0 of the unit's rows) and the right factor is a [b, l, d] tensor (x, u or the
+//              L^T[unit][M columns][tokens of pick t]  x  R[b][tokens of the picked patch][d]
+// i.e. the left factor is a per-unit tensor [unit][l_a][columns] (the set's M columns start at col0)
+// and the right factor is a [b, l, d] tensor (x, u or the
 // upstream gradient) whose rows are gathered patch by patch (Eq. 18), never copied.  K segments =
 // (unit, pick) of l_p tokens, in (sample, pick) order; the list is cut into `splits` consecutive
 // parts.
-//   SMHA, M = d_h:  sets 0-2: dW^{q,k,v}_i^T, left = [dq|dk|dv]^T [unit][3d_h][l_a] rows set*d_h.., right = x
-//                   set 3:    dW^O_i,         left = (gated o)^T  [unit][d_h][l_a],                  right = d_out
-//   UoME, M = d_e:  set 0: dA^O_i, left = H^T [unit][d_e][l_a], right = d_out;  set 1: dA^I_i^T, left = dZ^T, right = u
+//   SMHA, M = d_h:  sets 0-2: dW^{q,k,v}_i^T, left = [dq|dk|dv] [unit][l_a][3d_h] columns set*d_h.., right = x
+//                   set 3:    dW^O_i,         left = gated o    [unit][l_a][d_h],                    right = d_out
+//   UoME, M = d_e:  set 0: dA^O_i, left = H [unit][l_a][d_e], right = d_out;  set 1: dA^I_i^T, left = dZ, right = u
 template <typename T> struct SmhaWgradProblem {
-    const T *left_t[4], *right[4];
-    int unit_rows[4], row0[4];  // rows of one unit in left_t[set]; first row of the set's M rows
+    const T *left[4], *right[4];
+    int row_len[4], col0[4];    // elements of a row of left[set]; first column of the set's M
     const int32_t *expert_idx, *patch_idx;
     float *partial;             // [sets*n*splits, M, d]
     int b, l, d, n, kact, m, c, l_p, l_a, splits;
@@ -495,6 +498,7 @@ template <typename T> struct SmhaWgradProblem {
     __device__ int rows(int) const { return M; }
     __device__ int ncols() const { return d; }
     __device__ int kseg(int) const { return l_p; }
+    __device__ long a_stride(int g) const { return row_len[g / (n * splits)]; }
     __device__ long b_stride() const { return d; }
     __device__ int kdim(int) const { return 0; }
     static constexpr bool kPrepare = true;
@@ -533,7 +537,7 @@ template <typename T> struct SmhaWgradProblem {
     {
         const int bb = (int)(ctx & 0x7Fu), s = (int)((ctx >> 7) & 0x1Fu), t = (int)((ctx >> 12) & 0x3FFu);
         const int set = g / (n * splits);
-        return left_t[set] + (((size_t)bb * kact + s) * unit_rows[set] + row0[set] + r) * l_a + (size_t)t * l_p;
+        return left[set] + (((size_t)bb * kact + s) * l_a + (size_t)t * l_p) * row_len[set] + col0[set] + r;
     }
     __device__ const T *b_ptr_ctx(int g, int, int nn, uint32_t ctx) const
     {

@@ -21,12 +21,11 @@
 
 namespace uoe {
 
-// Set-up in one launch.  Blocks z < 4n transpose one 32x32 tile of a weight (2-byte elements):
-// job 0 turns W^O_i [d_h, d] into [d, d_h]; jobs 1-3 turn W^q_i, W^k_i, W^v_i [d, d_h] into row
-// blocks of [3*d_h, d].  Blocks z == 4n clear the two gate-gradient outputs.
+// Set-up in one launch.  Blocks z < 3n transpose one 32x32 tile of a weight (2-byte elements): W^q_i, W^k_i, W^v_i
+// [d, d_h] become row blocks of [3*d_h, d].  Blocks z == 3n clear the two gate-gradient outputs.
 struct SmhaBwdPrepArgs {
-    const uint16_t *w[4];  // wo, wq, wk, wv
-    uint16_t *wo_t, *wqkv_t;
+    const uint16_t *w[3];  // wq, wk, wv
+    uint16_t *wqkv_t;
     float *zero[2];
     long zero_count[2];
     int n, d, d_h;
@@ -36,21 +35,17 @@ __global__ __launch_bounds__(256) void smha_bwd_prep_kernel(SmhaBwdPrepArgs a)
 {
     __shared__ uint16_t tile[32][33];
     const int z = blockIdx.z;
-    if (z == 4 * a.n) {
+    if (z == 3 * a.n) {
         const long at = ((long)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x, step = (long)gridDim.x * gridDim.y * 256;
         for (int q = 0; q < 2; ++q)
             if (a.zero[q])
                 for (long i = at; i < a.zero_count[q]; i += step) a.zero[q][i] = 0.f;
         return;
     }
-    const int job = z / a.n, e = z - job * a.n;
-    const int rows = job == 0 ? a.d_h : a.d, cols = job == 0 ? a.d : a.d_h;
-    // the grid covers the larger of the two tile counts in each direction
-    const int r0 = (job == 0 ? blockIdx.x : blockIdx.y) * 32, c0 = (job == 0 ? blockIdx.y : blockIdx.x) * 32;
-    if (r0 >= rows || c0 >= cols) return;
+    const int job = z / a.n, e = z - job * a.n, rows = a.d, cols = a.d_h;
+    const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
     const uint16_t *src = a.w[job] + (size_t)e * a.d * a.d_h;
-    uint16_t *dst = job == 0 ? a.wo_t + (size_t)e * a.d * a.d_h
-                             : a.wqkv_t + (size_t)e * 3 * a.d * a.d_h + (size_t)(job - 1) * a.d * a.d_h;
+    uint16_t *dst = a.wqkv_t + ((size_t)e * 3 + job) * a.d * a.d_h;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
     for (int i = ty; i < 32; i += 8)
         if (r0 + i < rows && c0 + tx < cols) tile[i][tx] = src[(size_t)(r0 + i) * cols + c0 + tx];
@@ -61,11 +56,10 @@ __global__ __launch_bounds__(256) void smha_bwd_prep_kernel(SmhaBwdPrepArgs a)
 
 // Row pass between the out-projection gradient and the attention gradient.  Block = 32 rows of one
 // unit, thread = one 8-element piece of a row.  r_t (fp32), dO = w * dO_raw (token-major, rounded
-// once from the fp32 product), (w * o)^T (token-minor, through an LDS tile).
+// once from the fp32 product), w * o (the left operand of dW^O).
 template <int DH> __global__ __launch_bounds__(4 * DH) void smha_bwd_row_kernel(SmhaBwdArgs a)
 {
     constexpr int PPR = DH / 8;  // pieces (= threads) per row
-    __shared__ __align__(16) uint16_t tl[DH][40];
     const int g = blockIdx.y, tid = threadIdx.x;
     const int l_p = a.f.l / a.f.m, l_a = a.f.c * l_p;
     const int r = tid / PPR, pc = tid % PPR, row = blockIdx.x * 32 + r;
@@ -82,25 +76,20 @@ template <int DH> __global__ __launch_bounds__(4 * DH) void smha_bwd_row_kernel(
     load8(static_cast<const bf16_t *>(a.f.o) + at, oh);
     load8(static_cast<const bf16_t *>(a.f.o_lo) + at, ol);
     float dot = 0.f;
-    uint32_t od[4];
+    uint32_t od[4], og[4];
 #pragma unroll
     for (int e = 0; e < 8; e += 2) {
         const float o0 = oh[e] + ol[e], o1 = oh[e + 1] + ol[e + 1];
         dot = fmaf(dor[e], o0, dot);
         dot = fmaf(dor[e + 1], o1, dot);
         od[e / 2] = pack2_bf16(dor[e] * w, dor[e + 1] * w);
-        const uint32_t og = pack2_bf16(o0 * w, o1 * w);
-        tl[pc * 8 + e][r] = (uint16_t)(og & 0xFFFFu);
-        tl[pc * 8 + e + 1][r] = (uint16_t)(og >> 16);
+        og[e / 2] = pack2_bf16(o0 * w, o1 * w);
     }
+    *reinterpret_cast<uint4 *>(static_cast<bf16_t *>(a.og) + at) = make_uint4(og[0], og[1], og[2], og[3]);
     *reinterpret_cast<uint4 *>(static_cast<bf16_t *>(a.d_o) + at) = make_uint4(od[0], od[1], od[2], od[3]);
 #pragma unroll
     for (int off = PPR / 2; off >= 1; off >>= 1) dot += __shfl_xor(dot, off, 64);
     if (pc == 0) a.rt[(size_t)g * l_a + row] = dot;
-    __syncthreads();
-    const int col = tid >> 2, tp = tid & 3;
-    *reinterpret_cast<uint4 *>(static_cast<bf16_t *>(a.o_t) + ((size_t)g * DH + col) * l_a + blockIdx.x * 32 + tp * 8) =
-        *reinterpret_cast<const uint4 *>(&tl[col][tp * 8]);
 }
 
 // Gate gradients of one unit from the row sums r_t: wave w takes picks w, w+4, ...; the pick sums
@@ -112,9 +101,12 @@ __global__ __launch_bounds__(256) void smha_bwd_gate_kernel(SmhaBwdArgs a)
     const int l_p = a.f.l / a.f.m, l_a = a.f.c * l_p;
     const int bb = g / a.f.k, i = clampi(a.f.expert_idx[g], a.f.n);
     const float *rt = a.rt + (size_t)g * l_a;
+    const int parts = a.rt_parts > 1 ? a.rt_parts : 1;
+    const size_t part_stride = (size_t)a.f.b * a.f.k * l_a;
     for (int t = wave; t < a.f.c; t += 4) {
         float v = 0.f;
-        for (int q = lane; q < l_p; q += 64) v += rt[t * l_p + q];
+        for (int q = lane; q < l_p; q += 64)
+            for (int part = 0; part < parts; ++part) v += rt[part * part_stride + t * l_p + q];
         v = wave_sum(v);
         if (lane == 0) ps[t] = v;
     }
@@ -145,13 +137,12 @@ __global__ __launch_bounds__(256) void smha_bwd_gate_kernel(SmhaBwdArgs a)
 // scaled by log2(e)/sqrt(d_h) (base-2 softmax), so dK = ln 2 * accA and dQ = accA / sqrt(d_h).
 // P^T and dS^T, rounded to bf16 in place, are the B operands of the second products; the A
 // operands come out of the [row][d_h] LDS tiles through the transposing read.  Outputs go to the
-// [dq | dk | dv] buffer in token-major layout (left operand of the d_x contraction) and in
-// token-minor layout (left operand of the weight gradients).
+// [dq | dk | dv] buffer, token-major: the left operand of the d_x contraction and of the weight gradients.
 struct AttnBwdArgs {
     const bf16_t *q, *k, *v, *d_o;
     const float *lse;
     float *dd;              // [units, l_a]: written by the query-owning kernel, read by the key-owning one
-    bf16_t *dqkv, *dqkv_t;  // [units, l_a, 3*d_h], [units, 3*d_h, l_a]
+    bf16_t *dqkv;           // [units, l_a, 3*d_h]
     int l_a, causal;
     int rope_dim;           // Eq. 32: dq and dk are rotated back (the transposed rotation) on the way out
     // Eq. 41: padded keys are out of every softmax.  pad_mask [b,l] (1 = token) or NULL, looked up
@@ -387,7 +378,6 @@ template <int DH, int NW, bool KV, bool PAD> __global__ __launch_bounds__(NW * 6
     // accumulator register q of tile td is head-dim index td*32 + (q/4)*8 + lh*4 + q%4
     const float scale_a = KV ? 0.6931471805599453f : rsqrtf((float)DH);
     bf16_t *row_out = a.dqkv + ((size_t)g * l_a + orow) * (3 * DH);
-    bf16_t *col_out = a.dqkv_t + (size_t)g * (3 * DH) * l_a + orow;
     // q and k were rotated in adjacent pairs (2i, 2i+1) of the last rope_dim dims, row r by r * theta_i;
     // the gradient of the unrotated projection is the gradient rotated by -r * theta_i.  A lane's four
     // consecutive head dims hold two whole pairs (rope_dim and d_h are even).
@@ -417,11 +407,6 @@ template <int DH, int NW, bool KV, bool PAD> __global__ __launch_bounds__(NW * 6
                 const uint32_t w0 = pack2_bf16(v[0], v[1]);
                 const uint32_t w1 = pack2_bf16(v[2], v[3]);
                 *reinterpret_cast<uint2 *>(row_out + block * DH + dh0) = make_uint2(w0, w1);
-                uint16_t *ct = reinterpret_cast<uint16_t *>(col_out) + (size_t)(block * DH + dh0) * l_a;
-                ct[0] = (uint16_t)(w0 & 0xFFFFu);
-                ct[l_a] = (uint16_t)(w0 >> 16);
-                ct[2 * (size_t)l_a] = (uint16_t)(w1 & 0xFFFFu);
-                ct[3 * (size_t)l_a] = (uint16_t)(w1 >> 16);
             }
     };
     if (KV) {
@@ -495,13 +480,13 @@ hipError_t launch_smha_backward(const SmhaBwdArgs &a, hipStream_t st)
 
     {   // weights with K contiguous, cleared gate outputs
         SmhaBwdPrepArgs pa;
-        pa.w[0] = static_cast<const uint16_t *>(f.wo); pa.w[1] = static_cast<const uint16_t *>(f.wq);
-        pa.w[2] = static_cast<const uint16_t *>(f.wk); pa.w[3] = static_cast<const uint16_t *>(f.wv);
-        pa.wo_t = static_cast<uint16_t *>(a.wo_t); pa.wqkv_t = static_cast<uint16_t *>(a.wqkv_t);
+        pa.w[0] = static_cast<const uint16_t *>(f.wq); pa.w[1] = static_cast<const uint16_t *>(f.wk);
+        pa.w[2] = static_cast<const uint16_t *>(f.wv);
+        pa.wqkv_t = static_cast<uint16_t *>(a.wqkv_t);
         pa.zero[0] = a.d_expert_gate; pa.zero_count[0] = (long)f.b * f.n;
         pa.zero[1] = a.d_patch_gate; pa.zero_count[1] = (long)f.b * f.n * f.m;
         pa.n = f.n; pa.d = f.d; pa.d_h = dh;
-        hipLaunchKernelGGL(smha_bwd_prep_kernel, dim3((dh + 31) / 32, (f.d + 31) / 32, 4 * f.n + 1), dim3(256), 0, st, pa);
+        hipLaunchKernelGGL(smha_bwd_prep_kernel, dim3((dh + 31) / 32, (f.d + 31) / 32, 3 * f.n + 1), dim3(256), 0, st, pa);
         if ((err = hipGetLastError()) != hipSuccess) return err;
     }
 
@@ -511,13 +496,13 @@ hipError_t launch_smha_backward(const SmhaBwdArgs &a, hipStream_t st)
     // dO_raw = G[T] W^O^T: the forward's gathered projection with one output block
     QkvProblem<T, true> dp;
     dp.x = static_cast<const T *>(a.d_out);
-    dp.wq = dp.wk = dp.wv = static_cast<const T *>(a.wo_t);
+    dp.wq = dp.wk = dp.wv = static_cast<const T *>(f.wo); dp.w_nk = 1;   // W^O_i [d_h, d] as [n][k]
     dp.expert_idx = f.expert_idx; dp.patch_idx = f.patch_idx;
     dp.q = dp.k = dp.v = nullptr;
     dp.q32 = a.do_raw;
     dp.l = f.l; dp.d = f.d; dp.n = f.n; dp.kact = f.k; dp.m = f.m; dp.c = f.c;
     dp.l_p = l_p; dp.l_a = l_a; dp.d_h = dp.d_hp = dh; dp.q_scale = 1.0f; dp.nout = 1;
-    if ((err = launch_gemm_dma_auto(dp, units, l_a, dh, f.d, st)) != hipSuccess) return err;
+    if ((err = launch_gemm_dma_auto<GEMM_B_NK>(dp, units, l_a, dh, f.d, st)) != hipSuccess) return err;
 
     const dim3 rgrid(l_a / 32, units);
     if (dh == 32) hipLaunchKernelGGL((smha_bwd_row_kernel<32>), rgrid, dim3(128), 0, st, a);
@@ -532,7 +517,7 @@ hipError_t launch_smha_backward(const SmhaBwdArgs &a, hipStream_t st)
     AttnBwdArgs ab;
     ab.q = static_cast<const T *>(f.q); ab.k = static_cast<const T *>(f.kk); ab.v = static_cast<const T *>(f.v);
     ab.d_o = static_cast<const T *>(a.d_o); ab.lse = f.lse; ab.dd = a.dd;
-    ab.dqkv = static_cast<T *>(a.dqkv); ab.dqkv_t = static_cast<T *>(a.dqkv_t);
+    ab.dqkv = static_cast<T *>(a.dqkv);
     ab.l_a = l_a; ab.causal = (f.flags & F_CAUSAL) ? 1 : 0; ab.rope_dim = f.rope_dim;
     ab.pad_mask = f.pad_mask; ab.expert_idx = f.expert_idx; ab.patch_idx = f.patch_idx;
     ab.l = f.l; ab.n = f.n; ab.kact = f.k; ab.c = f.c; ab.m = f.m; ab.l_p = l_p;
@@ -553,18 +538,18 @@ hipError_t launch_smha_backward(const SmhaBwdArgs &a, hipStream_t st)
     if (err != hipSuccess) return err;
 
     // weight gradients, all four in one launch (M = d_h each): sets 0-2 = (dW^q, dW^k, dW^v)^T from
-    // the rows of [dq|dk|dv]^T against gathered x, set 3 = dW^O from (w*o)^T against gathered d_out
+    // [dq|dk|dv]^T against gathered x, set 3 = dW^O from (w*o)^T against gathered d_out
     SmhaWgradProblem<T> wp;
     for (int q = 0; q < 3; ++q) {
-        wp.left_t[q] = static_cast<const T *>(a.dqkv_t); wp.right[q] = static_cast<const T *>(f.x);
-        wp.unit_rows[q] = 3 * dh; wp.row0[q] = q * dh;
+        wp.left[q] = static_cast<const T *>(a.dqkv); wp.right[q] = static_cast<const T *>(f.x);
+        wp.row_len[q] = 3 * dh; wp.col0[q] = q * dh;
     }
-    wp.left_t[3] = static_cast<const T *>(a.o_t); wp.right[3] = static_cast<const T *>(a.d_out);
-    wp.unit_rows[3] = dh; wp.row0[3] = 0;
+    wp.left[3] = static_cast<const T *>(a.og); wp.right[3] = static_cast<const T *>(a.d_out);
+    wp.row_len[3] = dh; wp.col0[3] = 0;
     wp.expert_idx = f.expert_idx; wp.patch_idx = f.patch_idx; wp.partial = a.partial;
     wp.b = f.b; wp.l = f.l; wp.d = f.d; wp.n = f.n; wp.kact = f.k; wp.m = f.m; wp.c = f.c;
     wp.l_p = l_p; wp.l_a = l_a; wp.splits = a.splits; wp.M = dh;
-    if ((err = launch_gemm_dma_auto(wp, 4 * f.n * a.splits, dh, f.d, l_p, st)) != hipSuccess) return err;
+    if ((err = launch_gemm_dma_auto<GEMM_A_KM>(wp, 4 * f.n * a.splits, dh, f.d, l_p, st)) != hipSuccess) return err;
     WgradReduceArgs ra{};
     ra.partial = a.partial; ra.n = f.n; ra.M = dh; ra.N = f.d; ra.splits = a.splits;
     ra.dst[0] = a.d_wq; ra.dst[1] = a.d_wk;

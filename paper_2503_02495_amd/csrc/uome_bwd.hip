@@ -10,13 +10,13 @@
 //   d_u = (d_out) + dZ W1_b^T                            GEMM
 //   dA^O_i = sum_{(b,s): i(s) = i} H_{b,s}^T d_out_b     GEMM over the tokens of those samples
 //   dA^I_i = sum_{(b,s): i(s) = i} u_b^T dZ_{b,s}        GEMM over the tokens of those samples
-// All five contractions run on the pipelined MFMA engine through the forward problems (the raw
-// mode of UomeUpProblem, UomeDownProblem) and WgradProblem.  The engine wants every left operand
-// K-contiguous: the two weight tensors are transposed by a plain tiled copy (small), the
-// elementwise kernel writes H and dZ directly in token-minor layout, and dA^I is formed as its
-// transpose (dZ^T u, so that u is the natural-layout right operand) and turned back by the
-// reduction that adds the split-K partials.  Z and dH are kept in the storage dtype between the
-// kernels.
+// All five contractions run on the pipelined MFMA engine, on operands as they lie in memory: the products with a
+// transposed weight read it as [n][k], the weight gradients read H, dZ, u and d_out token-major ([k][m], [k][n]); dA^I
+// is formed as its transpose (dZ^T u) and turned back by the reduction that adds the split-K partials.  The
+// elementwise middle (dZ, H and the gate gradient from Z and dH) is the epilogue of the dH contraction: dH never
+// reaches memory, Z is read there and nowhere else.  Z, dZ and H are kept in the storage dtype between the kernels.
+// Against separate dH, middle and weight-transposing launches with token-minor copies of dZ and H (b 4, l 8192,
+// d 1024, 8 of 16 experts of 256): 15.7 + 144.5 + 131.8 us -> 212 us, and the weight gradients 317 -> 285 us.
 #include "common.h"
 #include "problems.h"
 #include "gemm_mfma.h"
@@ -25,28 +25,7 @@
 
 namespace uoe {
 
-// [rows][cols] -> [cols][rows] per expert, 2-byte elements, 32x32 tiles through LDS; both weight
-// tensors in one launch
-__global__ __launch_bounds__(256) void transpose_weights_kernel(const uint16_t *a_out, uint16_t *a_out_t, const uint16_t *a_in,
-                                                                uint16_t *a_in_t, int n, int d, int d_e)
-{
-    __shared__ uint16_t tile[32][33];
-    const bool second = (int)blockIdx.z >= n;
-    const int e = second ? blockIdx.z - n : blockIdx.z;
-    const int rows = second ? d : d_e, cols = second ? d_e : d;
-    const uint16_t *src = (second ? a_in : a_out) + (size_t)e * rows * cols;
-    uint16_t *dst = (second ? a_in_t : a_out_t) + (size_t)e * rows * cols;
-    const int ctiles = (cols + 31) / 32;
-    const int r0 = (blockIdx.x / ctiles) * 32, c0 = (blockIdx.x % ctiles) * 32;
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    for (int i = ty; i < 32; i += 8)
-        if (r0 + i < rows && c0 + tx < cols) tile[i][tx] = src[(size_t)(r0 + i) * cols + c0 + tx];
-    __syncthreads();
-    for (int i = ty; i < 32; i += 8)
-        if (c0 + i < cols && r0 + tx < rows) dst[(size_t)(c0 + i) * rows + r0 + tx] = tile[tx][i];
-}
-
-int uome_backward_gate_chunks(int l, int d_e) { return ((l + 63) / 64) * (d_e / 32); }
+int uome_backward_gate_chunks(int l, int d_e) { return (l / 32) * (d_e / 32); }
 int uome_backward_splits(int b, int l, int d, int n, int k, int d_e)
 {
     // cut the token axis until the launch has 512 large tiles, while a workgroup keeps on average
@@ -57,78 +36,116 @@ int uome_backward_splits(int b, int l, int d, int n, int k, int d_e)
     return s;
 }
 
-// Elementwise middle of the backward pass.  Block = (64 token rows, 32 columns of one slot,
-// sample b), one 8-element piece per thread.  Writes dZ in token-major layout (the left operand of
-// the d_u contraction) and dZ^T, H^T in token-minor layout [b][k*d_e][l] (the left operands of the
-// weight gradients) through LDS tiles, and the block's partial sum of dH * SiLU(Z) (fixed tree;
-// the partials are then added in index order by uome_bwd_gate_kernel).
-__global__ __launch_bounds__(256) void uome_bwd_mid_kernel(UomeBwdArgs a)
+// Elementwise middle for 8 elements: dZ, H and the sum of dH * SiLU(Z).  The sigmoid's reciprocal is the hardware's
+// (1 ulp of fp32; the results are rounded to bf16): the exact division was a quarter of the epilogue's instructions.
+__device__ __forceinline__ float uome_mid8(uint4 z8, uint4 dh8, float w, uint4 &dz8, uint4 &h8)
 {
-    constexpr int TP = 72;  // tile pitch in elements: 16-byte aligned rows
-    __shared__ float red[256];
-    __shared__ __align__(16) uint16_t tz[32][TP], th[32][TP];
-    const int chunk = blockIdx.x, cb = blockIdx.y, bb = blockIdx.z, tid = threadIdx.x;
-    const int per_slot = a.d_e / 32, s = cb / per_slot;
-    const int i = clampi(a.expert_idx[bb * a.k + s], a.n);
-    const float w = ((a.flags & F_GATE_EXPERT) && a.expert_gate) ? a.expert_gate[(size_t)bb * a.n + i] : 1.0f;
-    const int t0 = chunk * 64, rows = min(64, a.l - t0), c0 = cb * 32;
-    const size_t width = (size_t)a.k * a.d_e;
-    const bf16_t *z = static_cast<const bf16_t *>(a.z), *dh = static_cast<const bf16_t *>(a.dh);
-    bf16_t *dz = static_cast<bf16_t *>(a.dz);
+    const uint32_t z[4] = {z8.x, z8.y, z8.z, z8.w}, dh[4] = {dh8.x, dh8.y, dh8.z, dh8.w};
+    uint32_t oz[4], oh[4];
     float part = 0.f;
-    {
-        const int r = tid >> 2, pc = tid & 3;
-        float zv[8] = {0, 0, 0, 0, 0, 0, 0, 0}, dv[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        const size_t at = ((size_t)bb * a.l + t0 + r) * width + c0 + pc * 8;
-        if (r < rows) {
-            load8(z + at, zv);
-            load8(dh + at, dv);
-        }
-        uint32_t oz[4];
 #pragma unroll
-        for (int q = 0; q < 8; q += 2) {
-            float dzv[2], hv[2];
+    for (int q = 0; q < 4; ++q) {
+        float dzv[2], hv[2];
 #pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const float sig = 1.0f / (1.0f + __expf(-zv[q + e]));
-                const float v = zv[q + e] * sig;
-                part = fmaf(dv[q + e], v, part);
-                hv[e] = v * w;
-                dzv[e] = dv[q + e] * w * (sig * (1.0f + zv[q + e] * (1.0f - sig)));
-            }
-            oz[q / 2] = pack2_bf16(dzv[0], dzv[1]);
-            const uint32_t oh = pack2_bf16(hv[0], hv[1]);
-            tz[pc * 8 + q][r] = (uint16_t)(oz[q / 2] & 0xFFFFu);
-            tz[pc * 8 + q + 1][r] = (uint16_t)(oz[q / 2] >> 16);
-            th[pc * 8 + q][r] = (uint16_t)(oh & 0xFFFFu);
-            th[pc * 8 + q + 1][r] = (uint16_t)(oh >> 16);
+        for (int e = 0; e < 2; ++e) {
+            const float zv = __uint_as_float(e ? z[q] & 0xFFFF0000u : z[q] << 16);
+            const float dv = __uint_as_float(e ? dh[q] & 0xFFFF0000u : dh[q] << 16);
+            const float sig = __builtin_amdgcn_rcpf(1.0f + __expf(-zv));
+            const float v = zv * sig;
+            part = fmaf(dv, v, part);
+            hv[e] = v * w;
+            dzv[e] = dv * w * (sig * (1.0f + zv * (1.0f - sig)));
         }
-        if (r < rows) *reinterpret_cast<uint4 *>(dz + at) = make_uint4(oz[0], oz[1], oz[2], oz[3]);
+        oz[q] = pack2_bf16(dzv[0], dzv[1]);
+        oh[q] = pack2_bf16(hv[0], hv[1]);
     }
-    red[tid] = part;
-    __syncthreads();
-    {
-        const int col = tid >> 3, tp = tid & 7;  // 8 consecutive tokens of one column
-        if (tp * 8 < rows) {
-            const size_t at = ((size_t)bb * width + c0 + col) * a.l + t0 + tp * 8;
-            *reinterpret_cast<uint4 *>(static_cast<bf16_t *>(a.dz_t) + at) = *reinterpret_cast<const uint4 *>(&tz[col][tp * 8]);
-            *reinterpret_cast<uint4 *>(static_cast<bf16_t *>(a.h_t) + at) = *reinterpret_cast<const uint4 *>(&th[col][tp * 8]);
-        }
-    }
-    for (int st = 128; st > 0; st >>= 1) {
-        if (tid < st) red[tid] += red[tid + st];
-        __syncthreads();
-    }
-    if (tid == 0) a.gpart[((size_t)bb * a.k + s) * a.gchunks + chunk * per_slot + (cb - s * per_slot)] = red[0];
+    dz8 = make_uint4(oz[0], oz[1], oz[2], oz[3]);
+    h8 = make_uint4(oh[0], oh[1], oh[2], oh[3]);
+    return part;
 }
+
+// dH = d_out W2_b^T (A^O_i [d_e, d] read as [n][k]) with the middle as its epilogue: the wave's tile of dH is staged in
+// LDS in bf16 as for a plain store; each lane then walks its 16-byte pieces, with the matching pieces of Z a batch
+// ahead, and stores pieces of dZ and H.  A lane's pieces lie in one 8-column group, four neighbouring lanes in one
+// 32-column block of one expert: the block's sum for the gate gradient goes to gpart, one entry per 32 rows of the
+// sample (tiles of 64 and 128 rows leave zeros in the entries behind their first).
+template <typename T> struct UomeDhProblem {
+    typedef typename storage_elem<T>::type Elem;
+    const T *d_out, *a_out, *z;
+    const int32_t *expert_idx;
+    const float *expert_gate;   // NULL: weight 1
+    T *dz, *h;                  // [b, l, k*d_e]
+    float *gpart;               // [b, k, gchunks]
+    int l, d, n, kact, d_e, gchunks;
+    int once;                   // Z, dZ and H are larger than the caches: Z (its last use) is read past them
+    static constexpr bool kWriteOut = true, kPrepare = false, kRowScale = false, kColScale = true;
+    __device__ int rows(int) const { return l; }
+    __device__ int kdim(int) const { return d; }
+    __device__ int ncols() const { return kact * d_e; }
+    __device__ int kseg(int) const { return d; }
+    __device__ long b_stride() const { return 0; }
+    __device__ uint32_t seg_ctx(int, int) const { return 0; }
+    __device__ int expert(int g, int nn) const { return clampi(expert_idx[g * kact + nn / d_e], n); }
+    __device__ const T *a_ptr_ctx(int g, int r, int, uint32_t) const { return d_out + ((size_t)g * l + r) * d; }
+    __device__ const T *b_ptr_ctx(int g, int, int nn, uint32_t) const
+    {
+        return a_out + ((size_t)expert(g, nn) * d_e + nn % d_e) * d;
+    }
+    __device__ float col_scale(int g, int nn) const { return expert_gate ? expert_gate[(size_t)g * n + expert(g, nn)] : 1.0f; }
+    __device__ float epi(float v, float) const { return v; }
+    template <int TM, int TN, int SPITCH>
+    __device__ void write_out(uint16_t (*stage)[SPITCH], const float *colw, const float (&)[TM], int g, int grow0, int gcol0, int M, int N, int lane) const
+    {
+        constexpr int WM = TM * 32, WC = TN * 4, NPIECE = WM * WC / 64, BATCH = largest_divisor_upto(NPIECE, 8);
+        static_assert(WC == 8, "a lane keeps its 8-column group");
+        const int pc = lane % WC, gcol = gcol0 + pc * 8;
+        const bool col_ok = gcol < N;
+        const float w = colw[pc];
+        const size_t width = (size_t)kact * d_e;
+        float part = 0.f;
+#pragma unroll
+        for (int t0 = 0; t0 < NPIECE; t0 += BATCH) {
+            uint4 zp[BATCH];
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) {
+                const int grow = min(grow0 + (lane + (t0 + u) * 64) / WC, M - 1);
+                const T *src = z + ((size_t)g * l + grow) * width + (col_ok ? gcol : 0);
+                zp[u] = once ? load16<true>(src) : load16<false>(src);
+            }
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) {
+                const int row = (lane + (t0 + u) * 64) / WC, grow = grow0 + row;
+                uint4 dz8, h8;
+                const float s = uome_mid8(zp[u], *reinterpret_cast<const uint4 *>(&stage[row][pc * 8]), w, dz8, h8);
+                if (grow < M && col_ok) {
+                    part += s;
+                    const size_t at = ((size_t)g * l + grow) * width + gcol;
+                    store16<false>(dz + at, dz8);
+                    store16<false>(h + at, h8);
+                }
+            }
+        }
+        part += __shfl_xor(part, 1, 64);
+        part += __shfl_xor(part, 2, 64);
+#pragma unroll
+        for (int off = 8; off < 64; off <<= 1) part += __shfl_xor(part, off, 64);
+        if (lane < WC && lane % 4 == 0 && col_ok) {
+            const int s = gcol / d_e, blocks = d_e / 32;
+            float *dst = gpart + ((size_t)g * kact + s) * gchunks + (gcol - s * d_e) / 32;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+                if (grow0 + i * 32 < M) dst[(grow0 / 32 + i) * blocks] = i == 0 ? part : 0.f;
+        }
+    }
+};
 
 // d_gate [b,n]: block (slot s, sample b) adds the slot's partial sums (each thread a strided
 // subset in index order, then a fixed tree) into the entry of the slot's expert; the block of slot 0
 // also writes the zeros of the experts the sample did not select (all of them without the gate flag).
-__global__ __launch_bounds__(256) void uome_bwd_gate_kernel(UomeBwdArgs a)
+__device__ __forceinline__ void uome_bwd_gate_block(const UomeBwdArgs &a, int s, int bb)
 {
     __shared__ float red[256];
-    const int s = blockIdx.x, bb = blockIdx.y, tid = threadIdx.x;
+    const int tid = threadIdx.x;
     const bool gated = a.flags & F_GATE_EXPERT;
     if (s == 0 && tid < a.n) {
         bool chosen = false;
@@ -148,6 +165,19 @@ __global__ __launch_bounds__(256) void uome_bwd_gate_kernel(UomeBwdArgs a)
     if (tid == 0) a.d_gate[(size_t)bb * a.n + clampi(a.expert_idx[bb * a.k + s], a.n)] = red[0];
 }
 
+__global__ __launch_bounds__(256) void uome_bwd_gate_kernel(UomeBwdArgs a) { uome_bwd_gate_block(a, blockIdx.x, blockIdx.y); }
+
+// the last launch of the expert-selection pass: weight-gradient tiles, and behind them the gate gradient's blocks
+__global__ __launch_bounds__(256) void uome_bwd_finish_kernel(WgradReduceArgs ra, UomeBwdArgs a, int nx, int ny, int tiles)
+{
+    const int id = blockIdx.x;
+    if (id < tiles) {
+        wgrad_reduce_tile<bf16_t>(ra, id % nx, id / nx % ny, id / (nx * ny));
+        return;
+    }
+    uome_bwd_gate_block(a, (id - tiles) % a.k, (id - tiles) / a.k);
+}
+
 hipError_t launch_uome_gate_grad(const UomeBwdArgs &a, hipStream_t st)
 {
     hipLaunchKernelGGL(uome_bwd_gate_kernel, dim3(a.k, a.b), dim3(256), 0, st, a);
@@ -162,49 +192,42 @@ hipError_t launch_uome_backward(const UomeBwdArgs &a, hipStream_t st)
     if (a.patch_idx) return launch_uome_ds_backward(a, st);
     hipError_t err;
     const int width = a.k * a.d_e;
-    // weights with K contiguous for the two data-gradient GEMMs
-    {   // one launch: blocks z < n take A^O [d_e, d] -> [d, d_e], the others A^I [d, d_e] -> [d_e, d]
-        const int tiles = ((a.d + 31) / 32) * ((a.d_e + 31) / 32);
-        hipLaunchKernelGGL(transpose_weights_kernel, dim3(tiles, 1, 2 * a.n), dim3(256), 0, st,
-                           static_cast<const uint16_t *>(a.a_out), static_cast<uint16_t *>(a.a_out_t),
-                           static_cast<const uint16_t *>(a.a_in), static_cast<uint16_t *>(a.a_in_t), a.n, a.d, a.d_e);
-        if ((err = hipGetLastError()) != hipSuccess) return err;
-    }
-
     UomeUpProblem<T, true> zp;  // Z = u W1_b (plain product)
     zp.u = static_cast<const T *>(a.u); zp.a_in = static_cast<const T *>(a.a_in);
     zp.expert_idx = a.expert_idx; zp.expert_gate = nullptr; zp.hidden = static_cast<T *>(a.z);
     zp.l = a.l; zp.d = a.d; zp.n = a.n; zp.kact = a.k; zp.d_e = a.d_e;
-    zp.once = stream_once((size_t)a.b * a.l * width * sizeof(T));   // Z and dH: written here, read once by the next kernel
+    zp.once = stream_once((size_t)a.b * a.l * width * sizeof(T));   // Z: written here, read once by the next kernel
     if ((err = launch_gemm_dma_auto(zp, a.b, a.l, width, a.d, st)) != hipSuccess) return err;
-    UomeUpProblem<T, true> hp = zp;  // dH = d_out W2_b^T: the same contraction with (A^O_i)^T [d, d_e] as the weight
-    hp.u = static_cast<const T *>(a.d_out); hp.a_in = static_cast<const T *>(a.a_out_t); hp.hidden = static_cast<T *>(a.dh);
-    if ((err = launch_gemm_dma_auto(hp, a.b, a.l, width, a.d, st)) != hipSuccess) return err;
 
-    hipLaunchKernelGGL(uome_bwd_mid_kernel, dim3((a.l + 63) / 64, width / 32, a.b), dim3(256), 0, st, a);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-    if (a.d_gate && (err = launch_uome_gate_grad(a, st)) != hipSuccess) return err;
+    UomeDhProblem<T> hp;        // dH = d_out W2_b^T, and dZ, H and the gate gradient's partial sums from Z and it
+    hp.d_out = static_cast<const T *>(a.d_out); hp.a_out = static_cast<const T *>(a.a_out); hp.z = static_cast<const T *>(a.z);
+    hp.expert_idx = a.expert_idx; hp.expert_gate = (a.flags & F_GATE_EXPERT) ? a.expert_gate : nullptr;
+    hp.dz = static_cast<T *>(a.dz); hp.h = static_cast<T *>(a.h); hp.gpart = a.gpart; hp.gchunks = a.gchunks;
+    hp.l = a.l; hp.d = a.d; hp.n = a.n; hp.kact = a.k; hp.d_e = a.d_e; hp.once = zp.once;
+    if ((err = launch_gemm_dma_auto<GEMM_B_NK>(hp, a.b, a.l, width, a.d, st)) != hipSuccess) return err;
 
-    UomeDownProblem<T> up;  // d_u = (d_out) + dZ W1_b^T: the second-layer contraction with (A^I_i)^T [d_e, d]
-    up.hidden = static_cast<const T *>(a.dz); up.a_out = static_cast<const T *>(a.a_in_t);
+    UomeDownProblem<T> up;  // d_u = (d_out) + dZ W1_b^T: the second-layer contraction with A^I_i [d, d_e] as [n][k]
+    up.hidden = static_cast<const T *>(a.dz); up.a_out = static_cast<const T *>(a.a_in); up.w_nk = 1;
     up.u = static_cast<const T *>(a.d_out); up.expert_idx = a.expert_idx; up.out = static_cast<T *>(a.d_u);
     up.l = a.l; up.d = a.d; up.n = a.n; up.kact = a.k; up.d_e = a.d_e; up.flags = a.flags;
-    if ((err = launch_gemm_dma_auto(up, a.b, a.l, a.d, a.d_e, st)) != hipSuccess) return err;
+    if ((err = launch_gemm_dma_auto<GEMM_B_NK>(up, a.b, a.l, a.d, a.d_e, st)) != hipSuccess) return err;
 
     // weight gradients, both in one launch: [d_e, d] tiles per expert, token axis cut into a.splits
     // ranges; (dA^I_i)^T = sum dZ_{b,s}^T u_b is stored back as [d, d_e] by the reduction
     WgradProblem<T> wp;
-    wp.left_t[0] = static_cast<const T *>(a.h_t); wp.right[0] = static_cast<const T *>(a.d_out);  // dA^O_i
-    wp.left_t[1] = static_cast<const T *>(a.dz_t); wp.right[1] = static_cast<const T *>(a.u);     // (dA^I_i)^T
+    wp.left[0] = static_cast<const T *>(a.h); wp.right[0] = static_cast<const T *>(a.d_out);  // dA^O_i
+    wp.left[1] = static_cast<const T *>(a.dz); wp.right[1] = static_cast<const T *>(a.u);     // (dA^I_i)^T
     wp.expert_idx = a.expert_idx; wp.partial = a.partial;
     wp.b = a.b; wp.l = a.l; wp.n = a.n; wp.kact = a.k; wp.splits = a.splits;
-    wp.M = a.d_e; wp.N = a.d; wp.left_rows = width; wp.left_slot_rows = a.d_e; wp.right_stride = a.d;
-    if ((err = launch_gemm_dma_auto(wp, 2 * a.n * a.splits, a.d_e, a.d, a.l / a.splits, st)) != hipSuccess) return err;
+    wp.M = a.d_e; wp.N = a.d;
+    if ((err = launch_gemm_dma_auto<GEMM_A_KM>(wp, 2 * a.n * a.splits, a.d_e, a.d, a.l / a.splits, st)) != hipSuccess) return err;
     WgradReduceArgs ra{};
     ra.partial = a.partial; ra.n = a.n; ra.M = a.d_e; ra.N = a.d; ra.splits = a.splits;
     ra.dst[0] = a.d_a_out; ra.transposed[0] = 0;
     ra.dst[1] = a.d_a_in; ra.transposed[1] = 1;
-    return launch_wgrad_reduce(ra, 2, st);
+    const int nx = (a.d + 31) / 32, ny = (a.d_e + 31) / 32, tiles = nx * ny * 2 * a.n;
+    hipLaunchKernelGGL(uome_bwd_finish_kernel, dim3(tiles + (a.d_gate ? a.b * a.k : 0)), dim3(256), 0, st, ra, a, nx, ny, tiles);
+    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -214,80 +237,60 @@ hipError_t launch_uome_backward(const UomeBwdArgs &a, hipStream_t st)
 // per-patch contraction for d_u, patch-gathered right operands for the weight gradients) and the
 // row weight w_t = expert gate and/or the gate of the row's patch.
 
-// Elementwise middle, data-selection mode.  Block = 32 rows of one unit; it walks the d_e columns in
-// tiles of 64 (one 8-element piece per thread and tile), writes dZ token-major, dZ^T and H^T
-// token-minor through LDS tiles, and the rows' dL/dw_t = sum_j dH_raw * SiLU(Z).
-__global__ __launch_bounds__(256) void uome_ds_bwd_mid_kernel(UomeBwdArgs a)
-{
-    __shared__ __align__(16) uint16_t tz[64][40], th[64][40];
-    const int g = blockIdx.y, tid = threadIdx.x, r = tid >> 3, pc = tid & 7;
-    const int l_p = a.l / a.m, l_a = a.c * l_p, row = blockIdx.x * 32 + r;
-    const int bb = g / a.k, i = clampi(a.expert_idx[g], a.n);
-    float w = 1.0f;
-    if ((a.flags & F_GATE_EXPERT) && a.expert_gate) w *= a.expert_gate[(size_t)bb * a.n + i];
-    if ((a.flags & F_GATE_PATCH) && a.patch_gate) {
-        const int p = clampi(a.patch_idx[((size_t)bb * a.n + i) * a.c + row / l_p], a.m);
-        w *= a.patch_gate[((size_t)bb * a.n + i) * a.m + p];
-    }
-    const bf16_t *z = static_cast<const bf16_t *>(a.z), *dh = static_cast<const bf16_t *>(a.dh);
-    bf16_t *dz = static_cast<bf16_t *>(a.dz);
-    float part = 0.f;
-    for (int c0 = 0; c0 < a.d_e; c0 += 64) {
-        const int col = c0 + pc * 8;
-        float zv[8] = {0, 0, 0, 0, 0, 0, 0, 0}, dv[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        const size_t at = ((size_t)g * l_a + row) * a.d_e + col;
-        if (col < a.d_e) {
-            load8(z + at, zv);
-            load8(dh + at, dv);
-        }
-        uint32_t oz[4];
+// dH_raw = d_out[T] A^O_i^T with the middle as its epilogue (see UomeDhProblem): the row weight arrives per row
+// (fetched before the K loop, one row per lane, handed round by a shuffle), and a row's dL/dw_t = sum_j dH_raw * SiLU(Z)
+// leaves one part per 64 columns.
+template <typename T> struct UomeDsDhProblem : UomeDsUpProblem<T> {   // u = d_out, a_in = A^O, hidden unused
+    const T *z;
+    T *dz, *h;                  // [units, l_a, d_e]
+    float *rt;                  // [parts][units*l_a]
+    size_t rt_stride;
+    static constexpr bool kWriteOut = true;
+    __device__ const T *b_ptr_ctx(int g, int, int nn, uint32_t) const { return this->a_in + ((size_t)this->expert(g) * this->d_e + nn) * this->d; }
+    __device__ float epi(float v, float) const { return v; }
+    template <int TM, int TN, int SPITCH>
+    __device__ void write_out(uint16_t (*stage)[SPITCH], const float *, const float (&rs)[TM], int g, int grow0, int gcol0, int M, int N, int lane) const
+    {
+        constexpr int WM = TM * 32, WC = TN * 4, NPIECE = WM * WC / 64, BATCH = largest_divisor_upto(NPIECE, 8);
+        static_assert(WC == 8, "eight lanes of a row");
+        const int pc = lane % WC, gcol = gcol0 + pc * 8;
+        const bool col_ok = gcol < N;
+        if (gcol0 >= N) return;
 #pragma unroll
-        for (int q = 0; q < 8; q += 2) {
-            float dzv[2], hv[2];
+        for (int t0 = 0; t0 < NPIECE; t0 += BATCH) {
+            uint4 zp[BATCH];
 #pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const float sig = 1.0f / (1.0f + __expf(-zv[q + e]));
-                const float v = zv[q + e] * sig;
-                part = fmaf(dv[q + e], v, part);
-                hv[e] = v * w;
-                dzv[e] = dv[q + e] * w * (sig * (1.0f + zv[q + e] * (1.0f - sig)));
+            for (int u = 0; u < BATCH; ++u) {
+                const int grow = min(grow0 + (lane + (t0 + u) * 64) / WC, M - 1);
+                zp[u] = load16<false>(z + ((size_t)g * M + grow) * N + (col_ok ? gcol : 0));
             }
-            oz[q / 2] = pack2_bf16(dzv[0], dzv[1]);
-            const uint32_t oh = pack2_bf16(hv[0], hv[1]);
-            tz[pc * 8 + q][r] = (uint16_t)(oz[q / 2] & 0xFFFFu);
-            tz[pc * 8 + q + 1][r] = (uint16_t)(oz[q / 2] >> 16);
-            th[pc * 8 + q][r] = (uint16_t)(oh & 0xFFFFu);
-            th[pc * 8 + q + 1][r] = (uint16_t)(oh >> 16);
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) {
+                const int row = (lane + (t0 + u) * 64) / WC, grow = grow0 + row;   // 8 rows per piece: row / 32 is uniform
+                const float w = __shfl(rs[(t0 + u) * (64 / WC) / 32], row & 31, 64);
+                uint4 dz8, h8;
+                float s = uome_mid8(zp[u], *reinterpret_cast<const uint4 *>(&stage[row][pc * 8]), w, dz8, h8);
+                if (!col_ok) s = 0.f;
+                s += __shfl_xor(s, 1, 64);
+                s += __shfl_xor(s, 2, 64);
+                s += __shfl_xor(s, 4, 64);
+                if (grow < M && col_ok) {
+                    const size_t at = ((size_t)g * M + grow) * N + gcol;
+                    store16<false>(dz + at, dz8);
+                    store16<false>(h + at, h8);
+                    if (pc == 0) rt[gcol0 / 64 * rt_stride + (size_t)g * M + grow] = s;
+                }
+            }
         }
-        if (col < a.d_e) *reinterpret_cast<uint4 *>(dz + at) = make_uint4(oz[0], oz[1], oz[2], oz[3]);
-        __syncthreads();
-        const int tc = tid >> 2, tp = tid & 3;  // column of the tile, 8 consecutive rows
-        if (c0 + tc < a.d_e) {
-            const size_t to = ((size_t)g * a.d_e + c0 + tc) * l_a + blockIdx.x * 32 + tp * 8;
-            *reinterpret_cast<uint4 *>(static_cast<bf16_t *>(a.dz_t) + to) = *reinterpret_cast<const uint4 *>(&tz[tc][tp * 8]);
-            *reinterpret_cast<uint4 *>(static_cast<bf16_t *>(a.h_t) + to) = *reinterpret_cast<const uint4 *>(&th[tc][tp * 8]);
-        }
-        __syncthreads();
     }
-    part += __shfl_xor(part, 1, 64);
-    part += __shfl_xor(part, 2, 64);
-    part += __shfl_xor(part, 4, 64);
-    if (pc == 0) a.rt[(size_t)g * l_a + row] = part;
-}
+};
 
 hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st)
 {
     typedef bf16_t T;
     hipError_t err;
     const int l_p = a.l / a.m, l_a = a.c * l_p, units = a.b * a.k;
-    {
-        const int tiles = ((a.d + 31) / 32) * ((a.d_e + 31) / 32);
-        hipLaunchKernelGGL(transpose_weights_kernel, dim3(tiles, 1, 2 * a.n), dim3(256), 0, st,
-                           static_cast<const uint16_t *>(a.a_out), static_cast<uint16_t *>(a.a_out_t),
-                           static_cast<const uint16_t *>(a.a_in), static_cast<uint16_t *>(a.a_in_t), a.n, a.d, a.d_e);
-        if ((err = hipGetLastError()) != hipSuccess) return err;
-    }
-    // Z = u[T] A^I_i and dH_raw = d_out[T] A^O_i^T: the gathered projection with one output block
+    // Z = u[T] A^I_i: the gathered projection with one output block
     QkvProblem<T> zp;
     zp.x = static_cast<const T *>(a.u);
     zp.wq = zp.wk = zp.wv = static_cast<const T *>(a.a_in);
@@ -296,43 +299,46 @@ hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st)
     zp.l = a.l; zp.d = a.d; zp.n = a.n; zp.kact = a.k; zp.m = a.m; zp.c = a.c;
     zp.l_p = l_p; zp.l_a = l_a; zp.d_h = zp.d_hp = a.d_e; zp.q_scale = 1.0f; zp.nout = 1;
     if ((err = launch_gemm_dma_auto(zp, units, l_a, a.d_e, a.d, st)) != hipSuccess) return err;
-    QkvProblem<T> hp = zp;
-    hp.x = static_cast<const T *>(a.d_out);
-    hp.wq = hp.wk = hp.wv = static_cast<const T *>(a.a_out_t);
-    hp.q = hp.k = hp.v = static_cast<T *>(a.dh);
-    if ((err = launch_gemm_dma_auto(hp, units, l_a, a.d_e, a.d, st)) != hipSuccess) return err;
 
-    hipLaunchKernelGGL(uome_ds_bwd_mid_kernel, dim3(l_a / 32, units), dim3(256), 0, st, a);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
+    UomeDsDhProblem<T> hp;      // dH_raw, and dZ, H and the row terms from Z and it
+    hp.u = static_cast<const T *>(a.d_out); hp.a_in = static_cast<const T *>(a.a_out); hp.hidden = nullptr;
+    hp.expert_idx = a.expert_idx; hp.patch_idx = a.patch_idx;
+    hp.expert_gate = (a.flags & F_GATE_EXPERT) ? a.expert_gate : nullptr;
+    hp.patch_gate = (a.flags & F_GATE_PATCH) ? a.patch_gate : nullptr;
+    hp.l = a.l; hp.d = a.d; hp.n = a.n; hp.kact = a.k; hp.m = a.m; hp.c = a.c; hp.l_p = l_p; hp.l_a = l_a; hp.d_e = a.d_e;
+    hp.z = static_cast<const T *>(a.z); hp.dz = static_cast<T *>(a.dz); hp.h = static_cast<T *>(a.h);
+    hp.rt = a.rt; hp.rt_stride = (size_t)units * l_a;
+    if ((err = launch_gemm_dma_auto<GEMM_B_NK>(hp, units, l_a, a.d_e, a.d, st)) != hipSuccess) return err;
 
     SmhaBwdArgs ga{};  // the unit gate kernel reads its routing fields, the row terms and the gates
     ga.f.expert_idx = a.expert_idx; ga.f.patch_idx = a.patch_idx;
     ga.f.b = a.b; ga.f.l = a.l; ga.f.d = a.d; ga.f.n = a.n; ga.f.k = a.k; ga.f.m = a.m; ga.f.c = a.c;
     ga.expert_gate = a.expert_gate; ga.patch_gate = a.patch_gate; ga.flags = a.flags;
     ga.d_expert_gate = a.d_gate; ga.d_patch_gate = a.d_patch_gate; ga.rt = a.rt;
+    ga.rt_parts = (a.d_e + 63) / 64;
     if ((err = launch_unit_gate_grads(ga, st)) != hipSuccess) return err;
 
     // d_u = (d_out) + scatter-add of dZ A^I_i^T: the output-stationary per-patch contraction
     OutProjProblem<T> xp;
     xp.o = static_cast<const T *>(a.dz); xp.o_lo = nullptr; xp.parts = 1;
-    xp.wo = static_cast<const T *>(a.a_in_t); xp.x = static_cast<const T *>(a.d_out);
+    xp.wo = static_cast<const T *>(a.a_in); xp.w_nk = 1; xp.x = static_cast<const T *>(a.d_out);
     xp.expert_idx = a.expert_idx; xp.patch_idx = a.patch_idx;
     xp.out = static_cast<T *>(a.d_u);
     xp.l = a.l; xp.d = a.d; xp.n = a.n; xp.kact = a.k; xp.m = a.m; xp.c = a.c;
     xp.l_p = l_p; xp.l_a = l_a; xp.d_h = xp.o_row = a.d_e; xp.flags = a.flags & F_RESIDUAL;
-    if (l_p <= 32) err = launch_gemm_dma<OutProjProblem<T>, 32, 128, 32, 1, 4, 4, 2>(xp, a.b * a.m, l_p, a.d, st);
-    else err = launch_gemm_dma<OutProjProblem<T>, 64, 128, 32, 2, 2, 4, 2>(xp, a.b * a.m, l_p, a.d, st);
+    if (l_p <= 32) err = launch_gemm_dma<OutProjProblem<T>, 32, 128, 32, 1, 4, 4, 2, GEMM_B_NK>(xp, a.b * a.m, l_p, a.d, st);
+    else err = launch_gemm_dma<OutProjProblem<T>, 64, 128, 32, 2, 2, 4, 2, GEMM_B_NK>(xp, a.b * a.m, l_p, a.d, st);
     if (err != hipSuccess) return err;
 
     SmhaWgradProblem<T> wp;  // both weight gradients in one launch
-    wp.left_t[0] = static_cast<const T *>(a.h_t); wp.right[0] = static_cast<const T *>(a.d_out);  // dA^O_i
-    wp.left_t[1] = static_cast<const T *>(a.dz_t); wp.right[1] = static_cast<const T *>(a.u);     // (dA^I_i)^T
-    wp.left_t[2] = wp.left_t[3] = wp.right[2] = wp.right[3] = nullptr;
-    for (int q = 0; q < 4; ++q) { wp.unit_rows[q] = a.d_e; wp.row0[q] = 0; }
+    wp.left[0] = static_cast<const T *>(a.h); wp.right[0] = static_cast<const T *>(a.d_out);  // dA^O_i
+    wp.left[1] = static_cast<const T *>(a.dz); wp.right[1] = static_cast<const T *>(a.u);     // (dA^I_i)^T
+    wp.left[2] = wp.left[3] = wp.right[2] = wp.right[3] = nullptr;
+    for (int q = 0; q < 4; ++q) { wp.row_len[q] = a.d_e; wp.col0[q] = 0; }
     wp.expert_idx = a.expert_idx; wp.patch_idx = a.patch_idx; wp.partial = a.partial;
     wp.b = a.b; wp.l = a.l; wp.d = a.d; wp.n = a.n; wp.kact = a.k; wp.m = a.m; wp.c = a.c;
     wp.l_p = l_p; wp.l_a = l_a; wp.splits = a.splits; wp.M = a.d_e;
-    if ((err = launch_gemm_dma_auto(wp, 2 * a.n * a.splits, a.d_e, a.d, l_p, st)) != hipSuccess) return err;
+    if ((err = launch_gemm_dma_auto<GEMM_A_KM>(wp, 2 * a.n * a.splits, a.d_e, a.d, l_p, st)) != hipSuccess) return err;
     WgradReduceArgs ra{};
     ra.partial = a.partial; ra.n = a.n; ra.M = a.d_e; ra.N = a.d; ra.splits = a.splits;
     ra.dst[0] = a.d_a_out; ra.transposed[0] = 0;

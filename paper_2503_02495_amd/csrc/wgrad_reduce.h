@@ -14,12 +14,12 @@ struct WgradReduceArgs {
     int n, M, N, splits;
 };
 
-template <typename T> __global__ __launch_bounds__(256) void wgrad_reduce_kernel(WgradReduceArgs a)
+template <typename T> __device__ __forceinline__ void wgrad_reduce_tile(const WgradReduceArgs &a, int bx, int by, int bz)
 {
     __shared__ float tile[32][33];
-    const int set = blockIdx.z / a.n, e = blockIdx.z - set * a.n, r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
+    const int set = bz / a.n, e = bz - set * a.n, r0 = by * 32, c0 = bx * 32;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    const float *src = a.partial + (size_t)blockIdx.z * a.splits * a.M * a.N;
+    const float *src = a.partial + (size_t)bz * a.splits * a.M * a.N;
     for (int i = ty; i < 32; i += 8) {
         float v = 0.f;
         if (r0 + i < a.M && c0 + tx < a.N)
@@ -36,6 +36,11 @@ template <typename T> __global__ __launch_bounds__(256) void wgrad_reduce_kernel
         } else if (r0 + i < a.M && c0 + tx < a.N)
             dst[((size_t)e * a.M + r0 + i) * a.N + c0 + tx] = from_f32<T>(tile[i][tx]);
     }
+}
+
+template <typename T> __global__ __launch_bounds__(256) void wgrad_reduce_kernel(WgradReduceArgs a)
+{
+    wgrad_reduce_tile<T>(a, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 template <typename T = bf16_t> static inline hipError_t launch_wgrad_reduce(const WgradReduceArgs &a, int sets, hipStream_t st)
