@@ -138,6 +138,11 @@ __global__ __launch_bounds__(256) void smha_bwd_gate_kernel(SmhaBwdArgs a)
 // P^T and dS^T, rounded to bf16 in place, are the B operands of the second products; the A
 // operands come out of the [row][d_h] LDS tiles through the transposing read.  Outputs go to the
 // [dq | dk | dv] buffer, token-major: the left operand of the d_x contraction and of the weight gradients.
+// KS = 2: two groups of NW waves own the same rows and take the streamed tiles in turn, each with LDS tiles of its own;
+// their sums (D, then the accumulators) meet in LDS in group order.  A wave alternates between matrix, exponential and
+// packing phases, so a SIMD needs two of them, and with one wave per 32 own rows most shapes give it one or none.
+// (32 units of 1024 rows, d_h 64: 76.6 + 64.3 -> 55.0 + 47.8 us for the two kernels; 32 units of 128 rows 15.8 + 13.9 ->
+// 14.3 + 12.7 us.)
 struct AttnBwdArgs {
     const bf16_t *q, *k, *v, *d_o;
     const float *lse;
@@ -159,19 +164,27 @@ __device__ __forceinline__ bool bwd_key_is_token(const AttnBwdArgs &a, int g, in
     return a.pad_mask[(size_t)bb * a.l + p * a.l_p + key % a.l_p] != 0;
 }
 
-template <int DH, int NW, bool KV, bool PAD> __global__ __launch_bounds__(NW * 64) void attention_bwd_kernel(AttnBwdArgs a)
+template <int DH, int NW, int KS, bool KV, bool PAD> __global__ __launch_bounds__(NW * KS * 64, DH <= 64 && NW == 4 ? 2 : 1) void attention_bwd_kernel(AttnBwdArgs a)
 {
     constexpr int BT = 64, KP = DH + 8, VP = 2 * b_pitch_dwords(DH), NT = NW * 64;
     constexpr int CHUNKS = BT * DH / 8, PER_T = (CHUNKS + NT - 1) / NT;
-    __shared__ __align__(16) uint16_t TAr[BT][KP];
-    __shared__ __align__(16) uint16_t TAt[BT][VP];
-    __shared__ __align__(16) uint16_t TBr[BT][KP];
-    __shared__ __align__(16) uint16_t TBt[KV ? BT : 1][VP];
-    __shared__ __align__(16) float Ls[BT], Ds[BT];
-    __shared__ unsigned char Km[PAD ? BT : 1];  // streamed key admissible under the padding mask (KV = false)
+    struct alignas(16) Tiles {
+        uint16_t TAr[BT][KP], TAt[BT][VP], TBr[BT][KP], TBt[KV ? BT : 1][VP];
+        float Ls[BT], Ds[BT];
+        unsigned char Km[PAD ? BT : 16];  // streamed key admissible under the padding mask (KV = false)
+    };
+    constexpr int ACCS = KV ? 2 : 1, MERGE = NW * (DH / 32) * 16 * 64;  // floats of one accumulator of a group
+    static_assert(sizeof(Tiles) % 16 == 0, "the groups' tiles keep 16-byte rows");
+    static_assert(KS == 1 || (KS == 2 && ACCS * MERGE * sizeof(float) <= KS * sizeof(Tiles)), "accumulators meet in the tiles' space");
+    __shared__ __align__(16) unsigned char lds[KS * sizeof(Tiles)];
+    __shared__ float Dred[KV ? 1 : KS][NW * 32];
 
     const int g = blockIdx.y, l_a = a.l_a;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int split = KS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / NT) : 0;
+    const int tid = threadIdx.x - split * NT, lane = tid & 63, wave = tid >> 6;   // within the group
+    Tiles &T = reinterpret_cast<Tiles *>(lds)[split];
+    auto &TAr = T.TAr; auto &TAt = T.TAt; auto &TBr = T.TBr; auto &TBt = T.TBt;
+    auto &Ls = T.Ls; auto &Ds = T.Ds; auto &Km = T.Km;
     const int lr = lane & 31, lh = lane >> 5;
     const int orow = blockIdx.x * (32 * NW) + wave * 32 + lr;
     const size_t ubase = (size_t)g * l_a * DH;
@@ -294,12 +307,14 @@ template <int DH, int NW, bool KV, bool PAD> __global__ __launch_bounds__(NW * 6
     // difference of two separately rounded numbers); it is kept for the key-owning kernel.
     if (!KV) {
         float dsum = 0.f;
-        if (t_begin < t_end) load_global(t_begin * BT);
-        for (int kt = t_begin; kt < t_end; ++kt) {
+        if (t_begin + split < t_end) load_global((t_begin + split) * BT);
+        for (int kt0 = t_begin; kt0 < t_end; kt0 += KS) {
+            const int kt = kt0 + split;
             __syncthreads();
-            store_lds();
+            if (kt < t_end) store_lds();
             __syncthreads();
-            if (kt + 1 < t_end) load_global((kt + 1) * BT);
+            if (kt >= t_end) continue;
+            if (kt + KS < t_end) load_global((kt + KS) * BT);
             f32x16_t sacc[2], pacc[2];
             scores(kt, sacc, pacc);
 #pragma unroll
@@ -308,16 +323,23 @@ template <int DH, int NW, bool KV, bool PAD> __global__ __launch_bounds__(NW * 6
                 for (int q = 0; q < 16; ++q) dsum = fmaf(sacc[t][q], pacc[t][q], dsum);
         }
         dsum += __shfl_xor(dsum, 32, 64);
+        if constexpr (KS > 1) {
+            if (lh == 0) Dred[split][wave * 32 + lr] = dsum;
+            __syncthreads();
+            dsum = Dred[0][wave * 32 + lr] + Dred[KS - 1][wave * 32 + lr];
+        }
         d_own = dsum;
-        if (orow < l_a && lh == 0) a.dd[(size_t)g * l_a + orow] = dsum;
+        if (orow < l_a && lh == 0 && split == 0) a.dd[(size_t)g * l_a + orow] = dsum;
     }
 
-    if (t_begin < t_end) load_global(t_begin * BT);
-    for (int kt = t_begin; kt < t_end; ++kt) {
+    if (t_begin + split < t_end) load_global((t_begin + split) * BT);
+    for (int kt0 = t_begin; kt0 < t_end; kt0 += KS) {
+        const int kt = kt0 + split;
         __syncthreads();  // the previous tile has been consumed
-        store_lds();
+        if (kt < t_end) store_lds();
         __syncthreads();
-        if (kt + 1 < t_end) load_global((kt + 1) * BT);
+        if (kt >= t_end) continue;
+        if (kt + KS < t_end) load_global((kt + KS) * BT);
 
         f32x16_t sacc[2], pacc[2];
         scores(kt, sacc, pacc);
@@ -374,6 +396,28 @@ template <int DH, int NW, bool KV, bool PAD> __global__ __launch_bounds__(NW * 6
         }
     }
 
+    if constexpr (KS > 1) {
+        float *meet = reinterpret_cast<float *>(lds) + wave * (DH / 32) * 16 * 64 + lane;
+        __syncthreads();  // every wave is done with the tiles
+        if (split != 0) {
+#pragma unroll
+            for (int td = 0; td < DH / 32; ++td)
+#pragma unroll
+                for (int q = 0; q < 16; ++q) {
+                    meet[(td * 16 + q) * 64] = acc_a[td][q];
+                    if (KV) meet[MERGE + (td * 16 + q) * 64] = acc_b[td][q];
+                }
+        }
+        __syncthreads();
+        if (split != 0) return;
+#pragma unroll
+        for (int td = 0; td < DH / 32; ++td)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                acc_a[td][q] += meet[(td * 16 + q) * 64];
+                if (KV) acc_b[td][q] += meet[MERGE + (td * 16 + q) * 64];
+            }
+    }
     if (orow >= l_a) return;
     // accumulator register q of tile td is head-dim index td*32 + (q/4)*8 + lh*4 + q%4
     const float scale_a = KV ? 0.6931471805599453f : rsqrtf((float)DH);
@@ -417,23 +461,30 @@ template <int DH, int NW, bool KV, bool PAD> __global__ __launch_bounds__(NW * 6
     }
 }
 
+template <int DH, int NW, int KS, bool PAD> static hipError_t launch_attention_bwd_as(const AttnBwdArgs &a, int units, hipStream_t st)
+{
+    const dim3 grid((a.l_a + 32 * NW - 1) / (32 * NW), units);
+    hipLaunchKernelGGL((attention_bwd_kernel<DH, NW, KS, false, PAD>), grid, dim3(NW * KS * 64), 0, st, a);
+    hipLaunchKernelGGL((attention_bwd_kernel<DH, NW, KS, true, PAD>), grid, dim3(NW * KS * 64), 0, st, a);
+    return hipGetLastError();
+}
+
+// Two groups of waves per own block while one would leave SIMDs with less than two waves (2048 on the chip) and there
+// is a second tile to stream; then as many own blocks per workgroup (they share the streamed tiles) as still give every
+// compute unit a workgroup.  Heads of 128 stay with one group: two would not fit the register file.
 template <int DH, bool PAD> static hipError_t launch_attention_bwd_dh(const AttnBwdArgs &a, int units, hipStream_t st)
 {
-    const int l_a = a.l_a;
-    if ((long)((l_a + 127) / 128) * units >= 128) {
-        const dim3 grid((l_a + 127) / 128, units);
-        hipLaunchKernelGGL((attention_bwd_kernel<DH, 4, false, PAD>), grid, dim3(256), 0, st, a);
-        hipLaunchKernelGGL((attention_bwd_kernel<DH, 4, true, PAD>), grid, dim3(256), 0, st, a);
-    } else if ((long)((l_a + 63) / 64) * units >= 64) {
-        const dim3 grid((l_a + 63) / 64, units);
-        hipLaunchKernelGGL((attention_bwd_kernel<DH, 2, false, PAD>), grid, dim3(128), 0, st, a);
-        hipLaunchKernelGGL((attention_bwd_kernel<DH, 2, true, PAD>), grid, dim3(128), 0, st, a);
-    } else {
-        const dim3 grid((l_a + 31) / 32, units);
-        hipLaunchKernelGGL((attention_bwd_kernel<DH, 1, false, PAD>), grid, dim3(64), 0, st, a);
-        hipLaunchKernelGGL((attention_bwd_kernel<DH, 1, true, PAD>), grid, dim3(64), 0, st, a);
+    const long wide = (long)((a.l_a + 127) / 128) * units, mid = (long)((a.l_a + 63) / 64) * units;
+    if constexpr (DH <= 64) {
+        if (a.l_a > 64 && (long)((a.l_a + 31) / 32) * units < 2048) {
+            if (wide >= 256) return launch_attention_bwd_as<DH, 4, 2, PAD>(a, units, st);
+            if (mid >= 256) return launch_attention_bwd_as<DH, 2, 2, PAD>(a, units, st);
+            return launch_attention_bwd_as<DH, 1, 2, PAD>(a, units, st);
+        }
     }
-    return hipGetLastError();
+    if (wide >= 128) return launch_attention_bwd_as<DH, 4, 1, PAD>(a, units, st);
+    if (mid >= 64) return launch_attention_bwd_as<DH, 2, 1, PAD>(a, units, st);
+    return launch_attention_bwd_as<DH, 1, 1, PAD>(a, units, st);
 }
 
 template <bool PAD> static hipError_t launch_attention_bwd(const AttnBwdArgs &a, int dh, int units, hipStream_t st)
