@@ -158,7 +158,7 @@ int check_uome_bwd(const uoe_block_desc *blk)
 // backward pass of the SMHA block: the forward's scratch, then the backward's own
 struct SmhaBwdWs {
     SmhaWs fwd;
-    size_t lse, rt, dd, wqkv_t, do_raw, d_o, og, dqkv, partial, total;
+    size_t lse, rt, dd, do_raw, d_o, og, dqkv, partial, total;
     size_t g_q, g_k, g_v, g_og;  // any-shape path (four bytes an element)
     int splits;
 };
@@ -203,10 +203,8 @@ SmhaBwdWs smha_bwd_ws(const uoe_block_desc *d)
     const size_t rows = up(units * l_a * sizeof(float)), one = up(units * l_a * d->width * es);
     size_t off = w.fwd.total;
     w.lse = off; off += rows;
-    w.rt = off; off += rows;
+    w.rt = off; off += rows * ((d->width + 31) / 32);  // parts of 32 columns
     w.dd = off; off += rows;
-    w.wqkv_t = off; off += up(3 * (size_t)d->n * d->d * d->width * es);
-    w.do_raw = off; off += up(units * l_a * d->width * sizeof(float));
     w.d_o = off; off += one;
     w.og = off; off += one;
     w.dqkv = off; off += 3 * one;
@@ -642,7 +640,7 @@ int uoe_smha_backward(const uoe_block_desc *blk, const void *x, const uoe_smha_w
     a.d_out = d_out; a.expert_gate = expert_gate; a.patch_gate = patch_gate; a.flags = blk->flags;
     a.d_x = d_x; a.d_wq = dw->d_wq; a.d_wk = dw->d_wk; a.d_wv = dw->d_wv; a.d_wo = dw->d_wo;
     a.d_expert_gate = d_expert_gate; a.d_patch_gate = d_patch_gate;
-    a.wqkv_t = at(ws, s.wqkv_t); a.do_raw = reinterpret_cast<float *>(at(ws, s.do_raw)); a.d_o = at(ws, s.d_o);
+    a.d_o = at(ws, s.d_o);
     a.og = at(ws, s.og); a.dqkv = at(ws, s.dqkv);
     a.rt = reinterpret_cast<float *>(at(ws, s.rt)); a.dd = reinterpret_cast<float *>(at(ws, s.dd));
     a.partial = reinterpret_cast<float *>(at(ws, s.partial));

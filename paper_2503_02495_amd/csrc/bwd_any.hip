@@ -673,27 +673,6 @@ template <typename T, int DH> void launch_attention_bwd_f32_dh(const SmhaBwdArgs
 #undef UOE_ABW
 }
 
-// d_x = (G) + sum over the experts that picked the patch of [dq|dk|dv] [W^q|W^k|W^v]^T: the out-projection's
-// output-stationary contraction; K segments of an entry: parts x (q, k, v) of d_h, W [d, d_h] is [n][k]
-template <typename T> struct SmhaDxProblem : OutProjProblem<T> {
-    const T *w[3];   // wq, wk, wv
-    static constexpr int kSegParts = 3 * parts_of<T>::value;
-    __device__ int prepare(int g, uint32_t *segtab, int tid, int nthreads) const
-    {
-        return OutProjProblem<T>::prepare(g, segtab, tid, nthreads) * kSegParts;   // this->parts is 1: one table entry per expert
-    }
-    __device__ const T *a_ptr_ctx(int g, int r, int seg, uint32_t ctx) const
-    {
-        return OutProjProblem<T>::a_ptr_ctx(g, r, seg, ctx) + (size_t)(seg % kSegParts) * this->d_h;   // [parts][3][d_h] in a row
-    }
-    __device__ const T *b_ptr_ctx(int, int seg, int nn, uint32_t ctx) const
-    {
-        const int which = (seg % kSegParts) % 3;
-        const T *base = which == 0 ? w[0] : which == 1 ? w[1] : w[2];
-        return base + ((size_t)((ctx >> 20) & 0x3Fu) * this->d + nn) * this->d_h;
-    }
-};
-
 // Weight gradients of the SMHA block: sets 0-2 (dW^{q,k,v}_i)^T [d_h, d] = sum d{Q,K,V}^T x[T], set 3 dW^O_i [d_h, d] =
 // sum (w o)^T G[T], both operands token-major, right rows gathered patch by patch.  K segments = (unit, pick) of
 // l_p tokens x parts, in order; parts of an expert's list: chunks of 128 samples x consecutive ranges of the
@@ -792,9 +771,8 @@ template <typename T> hipError_t smha_backward_any(const SmhaBwdArgs &a, hipStre
     else if (dh <= 64) launch_attention_bwd_f32_dh<T, 64>(a, st);
     else launch_attention_bwd_f32_dh<T, 128>(a, st);
     if ((err = hipGetLastError()) != hipSuccess) return err;
-    if ((err = launch_unit_gate_grads(a, st)) != hipSuccess) return err;
 
-    SmhaDxProblem<T> xp;
+    SmhaDxProblem<T, parts_of<T>::value> xp;
     xp.o = static_cast<const T *>(a.dqkv); xp.o_lo = nullptr; xp.parts = 1; xp.wo = nullptr;
     xp.w[0] = static_cast<const T *>(f.wq); xp.w[1] = static_cast<const T *>(f.wk); xp.w[2] = static_cast<const T *>(f.wv);
     xp.x = static_cast<const T *>(a.d_out);
@@ -814,7 +792,7 @@ template <typename T> hipError_t smha_backward_any(const SmhaBwdArgs &a, hipStre
     ra.partial = a.partial; ra.n = f.n; ra.M = dh; ra.N = f.d; ra.splits = a.splits;
     ra.dst[0] = a.d_wq; ra.dst[1] = a.d_wk; ra.dst[2] = a.d_wv; ra.dst[3] = a.d_wo;
     ra.transposed[0] = ra.transposed[1] = ra.transposed[2] = 1; ra.transposed[3] = 0;
-    return launch_wgrad_reduce<T>(ra, 4, st);
+    return launch_wgrad_reduce_gates<T>(ra, 4, a, st);
 }
 
 }  // namespace

@@ -194,12 +194,11 @@ struct SmhaBwdArgs {
     void *d_x, *d_wq, *d_wk, *d_wv, *d_wo;    // [b,l,d], 3 x [n,d,d_h], [n,d_h,d], storage dtype
     float *d_expert_gate, *d_patch_gate;      // [b,n], [b,n,m], or NULL
     // workspace, storage dtype unless noted
-    void *wqkv_t;                             // [n, 3*d_h, d]
-    float *do_raw;                            // [units, l_a, d_h] fp32
+    float *do_raw;                            // any-shape path: [units, l_a, d_h] fp32
     void *d_o;                                // [units, l_a, d_h]
     void *dqkv;                               // [units, l_a, 3*d_h]
     float *rt, *dd;                           // [units, l_a] each: dL/dw_t and the softmax row term
-    int rt_parts;                             // rt is that many arrays to be added (0: one)
+    int rt_parts;                             // rt is that many arrays to be added (0: one), set by the launcher
     float *partial;                           // [4*n*splits, d_h, d] split tiles of the four weight gradients
     int splits;
     void *og;                                 // w o [units, l_a, d_h]; any-shape path: [units, l_a, parts, d_h], do_raw, q, k, v are
@@ -255,9 +254,6 @@ hipError_t launch_uome_down(const UomeArgs &a, bool bf16, hipStream_t st);  // E
 hipError_t launch_uome_ds(const UomeDsArgs &a, bool bf16, hipStream_t st);
 hipError_t launch_uome_backward(const UomeBwdArgs &a, hipStream_t st);
 hipError_t launch_smha_backward(const SmhaBwdArgs &a, hipStream_t st);
-// gate gradients of the units of a data-selected block from the row terms a.rt (uses the routing
-// fields of a.f, a.flags, the gates and the two outputs, which it clears first)
-hipError_t launch_unit_gate_grads(const SmhaBwdArgs &a, hipStream_t st);
 // d_gate from the partial sums a.gpart [b, k, gchunks]
 hipError_t launch_uome_gate_grad(const UomeBwdArgs &a, hipStream_t st);
 // rotary embedding (Eq. 32) of fp32 q and k with rows of d_h

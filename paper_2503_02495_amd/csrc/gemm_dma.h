@@ -439,6 +439,8 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, OCC) void gemm_dma_kernel(P 
 
     if constexpr (F32) {
         wave_epilogue_f32<P, TM, TN>(p, acc, coltab, rs, g, m0 + wm0, n0 + wn0, wn0, M, N, lane);
+    } else if constexpr (takes_acc<P>::value) {
+        p.template acc_out<TM, TN>(acc, rs, g, m0 + wm0, n0 + wn0, M, N, lane);
     } else {
         uint16_t(*stage)[SPITCH] = reinterpret_cast<uint16_t(*)[SPITCH]>(lds_raw) + (size_t)wave * WM;
         wave_epilogue<P, TM, TN, SPITCH>(p, acc, stage, coltab, rs, g, m0 + wm0, n0 + wn0, wn0, M, N, lane);

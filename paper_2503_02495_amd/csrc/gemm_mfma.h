@@ -124,6 +124,9 @@ __device__ __forceinline__ uint32_t pack2_f16_rn(float a, float b)
 template <typename P, typename = void> struct streams_once : std::false_type {};
 template <typename P> struct streams_once<P, std::void_t<decltype(std::declval<P>().once)>> : std::true_type {};
 
+// problems that take the accumulators themselves: acc_out<TM, TN>(acc, rs, g, first row, first column, M, N, lane)
+template <typename P, typename = void> struct takes_acc : std::false_type {};
+template <typename P> struct takes_acc<P, std::void_t<decltype(P::kAccOut)>> : std::true_type {};
 // problems with a second half of their own: write_out<TM, TN, SPITCH>(stage, coltab + first 8-column group, rs, ...)
 template <typename P, typename = void> struct writes_itself : std::false_type {};
 template <typename P> struct writes_itself<P, std::void_t<decltype(P::kWriteOut)>> : std::true_type {};

@@ -237,6 +237,28 @@ template <typename T> struct OutProjProblem {
     template <bool ONCE> __device__ void put8_as(int g, int r, int nn, uint4 piece) const { store16<ONCE>(out + at8(g, r, nn), piece); }
 };
 
+// d_x = (G) + sum over the experts that picked the patch of [dq|dk|dv] [W^q|W^k|W^v]^T: the out-projection's
+// output-stationary contraction; K segments of an entry: parts x (q, k, v) of d_h, W [d, d_h] is [n][k].  PARTS = 2:
+// rows of dqkv are (hi, lo) pairs.
+template <typename T, int PARTS> struct SmhaDxProblem : OutProjProblem<T> {
+    const T *w[3];   // wq, wk, wv
+    static constexpr int kSegParts = 3 * PARTS;
+    __device__ int prepare(int g, uint32_t *segtab, int tid, int nthreads) const
+    {
+        return OutProjProblem<T>::prepare(g, segtab, tid, nthreads) * kSegParts;   // this->parts is 1: one table entry per expert
+    }
+    __device__ const T *a_ptr_ctx(int g, int r, int seg, uint32_t ctx) const
+    {
+        return OutProjProblem<T>::a_ptr_ctx(g, r, seg, ctx) + (size_t)(seg % kSegParts) * this->d_h;   // [parts][3][d_h] in a row
+    }
+    __device__ const T *b_ptr_ctx(int, int seg, int nn, uint32_t ctx) const
+    {
+        const int which = (seg % kSegParts) % 3;
+        const T *base = which == 0 ? w[0] : which == 1 ? w[1] : w[2];
+        return base + ((size_t)((ctx >> 20) & 0x3Fu) * this->d + nn) * this->d_h;
+    }
+};
+
 // ---------------------------------------------------------------------------------------------
 // UoME Eq. 38: group = sample b; M = l; K = d; N = k*d_e (the sample's active experts side by
 // side); epilogue SiLU and the expert's gate.

@@ -21,108 +21,81 @@
 
 namespace uoe {
 
-// Set-up in one launch.  Blocks z < 3n transpose one 32x32 tile of a weight (2-byte elements): W^q_i, W^k_i, W^v_i
-// [d, d_h] become row blocks of [3*d_h, d].  Blocks z == 3n clear the two gate-gradient outputs.
-struct SmhaBwdPrepArgs {
-    const uint16_t *w[3];  // wq, wk, wv
-    uint16_t *wqkv_t;
-    float *zero[2];
-    long zero_count[2];
-    int n, d, d_h;
+// dO_raw = G[T] W^O_i^T (W^O_i [d_h, d] read as [n][k]) and what the attention gradient and dW^O need of it, straight
+// from the fp32 accumulators: r_t = dO_raw_t . o_t (one part per WN columns), dO = w dO_raw (rounded once) and w o.  A lane
+// owns a row and groups of 4 columns of it, so o arrives and dO leaves in 8-byte pieces that complete 64-byte runs of a
+// row in L2.  (A row kernel between the two contractions read dO_raw back in fp32: 9.2 + 3.9 us on the lm shape.)
+template <typename T> struct SmhaDoProblem {
+    typedef typename storage_elem<T>::type Elem;
+    const T *d_out, *wo, *o, *o_lo;
+    const int32_t *expert_idx, *patch_idx;
+    const float *expert_gate, *patch_gate;   // NULL: weight 1
+    T *d_o, *og;                             // [units, l_a, d_h]
+    float *rt;                               // [ceil(d_h / WN)][units*l_a]
+    size_t rt_stride;
+    int l, d, n, kact, m, c, l_p, l_a, d_h;
+    static constexpr bool kAccOut = true, kPrepare = false, kRowScale = true, kColScale = false;
+    __device__ int rows(int) const { return l_a; }
+    __device__ int kdim(int) const { return d; }
+    __device__ int ncols() const { return d_h; }
+    __device__ int kseg(int) const { return d; }
+    __device__ long b_stride() const { return 0; }
+    __device__ uint32_t seg_ctx(int, int) const { return 0; }
+    __device__ int expert(int g) const { return clampi(expert_idx[g], n); }
+    __device__ int patch(int g, int r) const { return clampi(patch_idx[((size_t)(g / kact) * n + expert(g)) * c + r / l_p], m); }
+    __device__ const T *a_ptr_ctx(int g, int r, int, uint32_t) const
+    {
+        return d_out + ((size_t)(g / kact) * l + patch(g, r) * l_p + r % l_p) * d;
+    }
+    __device__ const T *b_ptr_ctx(int g, int, int nn, uint32_t) const { return wo + ((size_t)expert(g) * d_h + nn) * d; }
+    __device__ float row_scale(int g, int r) const
+    {
+        const size_t e = (size_t)(g / kact) * n + expert(g);
+        return (expert_gate ? expert_gate[e] : 1.0f) * (patch_gate ? patch_gate[e * m + patch(g, r)] : 1.0f);
+    }
+    template <int TM, int TN>
+    __device__ void acc_out(f32x16_t (&acc)[TM][TN], const float (&rs)[TM], int g, int grow0, int gcol0, int M, int N, int lane) const
+    {
+        const int lr = lane & 31, lh = lane >> 5;
+        if (gcol0 >= N) return;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int grow = grow0 + i * 32 + lr;
+            const size_t base = ((size_t)g * M + min(grow, M - 1)) * N + gcol0 + lh * 4;
+            uint2 oh[TN * 4], ol[TN * 4];
+#pragma unroll
+            for (int q = 0; q < TN * 4; ++q) {   // 8-column group q of the wave tile (N is a multiple of 32)
+                const size_t at = base + (gcol0 + q * 8 < N ? q * 8 : 0);
+                oh[q] = *reinterpret_cast<const uint2 *>(o + at);
+                ol[q] = *reinterpret_cast<const uint2 *>(o_lo + at);
+            }
+            float dot = 0.f;
+#pragma unroll
+            for (int q = 0; q < TN * 4; ++q) {
+                if (gcol0 + q * 8 >= N) continue;
+                const float w = rs[i];
+                const uint32_t h[2] = {oh[q].x, oh[q].y}, lo[2] = {ol[q].x, ol[q].y};
+                uint32_t od[2], ov[2];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const float d0 = acc[i][q / 4][(q % 4) * 4 + 2 * e], d1 = acc[i][q / 4][(q % 4) * 4 + 2 * e + 1];
+                    const float o0 = __uint_as_float(h[e] << 16) + __uint_as_float(lo[e] << 16);
+                    const float o1 = __uint_as_float(h[e] & 0xFFFF0000u) + __uint_as_float(lo[e] & 0xFFFF0000u);
+                    dot = fmaf(d0, o0, dot);
+                    dot = fmaf(d1, o1, dot);
+                    od[e] = pack2_bf16(d0 * w, d1 * w);
+                    ov[e] = pack2_bf16(o0 * w, o1 * w);
+                }
+                if (grow < M) {
+                    *reinterpret_cast<uint2 *>(d_o + base + q * 8) = make_uint2(od[0], od[1]);
+                    *reinterpret_cast<uint2 *>(og + base + q * 8) = make_uint2(ov[0], ov[1]);
+                }
+            }
+            dot += __shfl_xor(dot, 32, 64);
+            if (grow < M && lh == 0) rt[gcol0 / (TN * 32) * rt_stride + (size_t)g * M + grow] = dot;
+        }
+    }
 };
-
-__global__ __launch_bounds__(256) void smha_bwd_prep_kernel(SmhaBwdPrepArgs a)
-{
-    __shared__ uint16_t tile[32][33];
-    const int z = blockIdx.z;
-    if (z == 3 * a.n) {
-        const long at = ((long)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x, step = (long)gridDim.x * gridDim.y * 256;
-        for (int q = 0; q < 2; ++q)
-            if (a.zero[q])
-                for (long i = at; i < a.zero_count[q]; i += step) a.zero[q][i] = 0.f;
-        return;
-    }
-    const int job = z / a.n, e = z - job * a.n, rows = a.d, cols = a.d_h;
-    const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
-    const uint16_t *src = a.w[job] + (size_t)e * a.d * a.d_h;
-    uint16_t *dst = a.wqkv_t + ((size_t)e * 3 + job) * a.d * a.d_h;
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    for (int i = ty; i < 32; i += 8)
-        if (r0 + i < rows && c0 + tx < cols) tile[i][tx] = src[(size_t)(r0 + i) * cols + c0 + tx];
-    __syncthreads();
-    for (int i = ty; i < 32; i += 8)
-        if (c0 + i < cols && r0 + tx < rows) dst[(size_t)(c0 + i) * rows + r0 + tx] = tile[tx][i];
-}
-
-// Row pass between the out-projection gradient and the attention gradient.  Block = 32 rows of one
-// unit, thread = one 8-element piece of a row.  r_t (fp32), dO = w * dO_raw (token-major, rounded
-// once from the fp32 product), w * o (the left operand of dW^O).
-template <int DH> __global__ __launch_bounds__(4 * DH) void smha_bwd_row_kernel(SmhaBwdArgs a)
-{
-    constexpr int PPR = DH / 8;  // pieces (= threads) per row
-    const int g = blockIdx.y, tid = threadIdx.x;
-    const int l_p = a.f.l / a.f.m, l_a = a.f.c * l_p;
-    const int r = tid / PPR, pc = tid % PPR, row = blockIdx.x * 32 + r;
-    const int bb = g / a.f.k, i = clampi(a.f.expert_idx[g], a.f.n);
-    float w = 1.0f;
-    if (a.flags & F_GATE_EXPERT) w *= a.expert_gate[(size_t)bb * a.f.n + i];
-    if (a.flags & F_GATE_PATCH) {
-        const int p = clampi(a.f.patch_idx[((size_t)bb * a.f.n + i) * a.f.c + row / l_p], a.f.m);
-        w *= a.patch_gate[((size_t)bb * a.f.n + i) * a.f.m + p];
-    }
-    const size_t at = ((size_t)g * l_a + row) * DH + pc * 8;
-    float dor[8], oh[8], ol[8];
-    load8(a.do_raw + at, dor);
-    load8(static_cast<const bf16_t *>(a.f.o) + at, oh);
-    load8(static_cast<const bf16_t *>(a.f.o_lo) + at, ol);
-    float dot = 0.f;
-    uint32_t od[4], og[4];
-#pragma unroll
-    for (int e = 0; e < 8; e += 2) {
-        const float o0 = oh[e] + ol[e], o1 = oh[e + 1] + ol[e + 1];
-        dot = fmaf(dor[e], o0, dot);
-        dot = fmaf(dor[e + 1], o1, dot);
-        od[e / 2] = pack2_bf16(dor[e] * w, dor[e + 1] * w);
-        og[e / 2] = pack2_bf16(o0 * w, o1 * w);
-    }
-    *reinterpret_cast<uint4 *>(static_cast<bf16_t *>(a.og) + at) = make_uint4(og[0], og[1], og[2], og[3]);
-    *reinterpret_cast<uint4 *>(static_cast<bf16_t *>(a.d_o) + at) = make_uint4(od[0], od[1], od[2], od[3]);
-#pragma unroll
-    for (int off = PPR / 2; off >= 1; off >>= 1) dot += __shfl_xor(dot, off, 64);
-    if (pc == 0) a.rt[(size_t)g * l_a + row] = dot;
-}
-
-// Gate gradients of one unit from the row sums r_t: wave w takes picks w, w+4, ...; the pick sums
-// are then combined in pick order.  The outputs were zero-filled before.
-__global__ __launch_bounds__(256) void smha_bwd_gate_kernel(SmhaBwdArgs a)
-{
-    __shared__ float ps[1024];
-    const int g = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int l_p = a.f.l / a.f.m, l_a = a.f.c * l_p;
-    const int bb = g / a.f.k, i = clampi(a.f.expert_idx[g], a.f.n);
-    const float *rt = a.rt + (size_t)g * l_a;
-    const int parts = a.rt_parts > 1 ? a.rt_parts : 1;
-    const size_t part_stride = (size_t)a.f.b * a.f.k * l_a;
-    for (int t = wave; t < a.f.c; t += 4) {
-        float v = 0.f;
-        for (int q = lane; q < l_p; q += 64)
-            for (int part = 0; part < parts; ++part) v += rt[part * part_stride + t * l_p + q];
-        v = wave_sum(v);
-        if (lane == 0) ps[t] = v;
-    }
-    __syncthreads();
-    const int32_t *pid = a.f.patch_idx + ((size_t)bb * a.f.n + i) * a.f.c;
-    const float *gp = (a.flags & F_GATE_PATCH) ? a.patch_gate + ((size_t)bb * a.f.n + i) * a.f.m : nullptr;
-    if ((a.flags & F_GATE_PATCH) && a.d_patch_gate) {
-        const float ge = (a.flags & F_GATE_EXPERT) ? a.expert_gate[(size_t)bb * a.f.n + i] : 1.0f;
-        for (int t = tid; t < a.f.c; t += 256) a.d_patch_gate[((size_t)bb * a.f.n + i) * a.f.m + clampi(pid[t], a.f.m)] = ge * ps[t];
-    }
-    if ((a.flags & F_GATE_EXPERT) && a.d_expert_gate && tid == 0) {
-        float v = 0.f;
-        for (int t = 0; t < a.f.c; ++t) v += (gp ? gp[clampi(pid[t], a.f.m)] : 1.0f) * ps[t];
-        a.d_expert_gate[(size_t)bb * a.f.n + i] = v;
-    }
-}
 
 // ---------------------------------------------------------------------------------------------
 // Attention backward.  One wave owns 32 rows of one unit ("own" rows) and walks the unit's other
@@ -494,23 +467,6 @@ template <bool PAD> static hipError_t launch_attention_bwd(const AttnBwdArgs &a,
     return launch_attention_bwd_dh<128, PAD>(a, units, st);
 }
 
-hipError_t launch_unit_gate_grads(const SmhaBwdArgs &a, hipStream_t st)
-{
-    const SmhaArgs &f = a.f;
-    SmhaBwdPrepArgs pa{};  // only its clearing blocks run: n = 0 puts them at z = 0
-    pa.zero[0] = a.d_expert_gate; pa.zero_count[0] = (long)f.b * f.n;
-    pa.zero[1] = a.d_patch_gate; pa.zero_count[1] = (long)f.b * f.n * f.m;
-    pa.n = 0; pa.d = f.d; pa.d_h = 32;
-    hipLaunchKernelGGL(smha_bwd_prep_kernel, dim3(8, 8, 1), dim3(256), 0, st, pa);
-    hipError_t err = hipGetLastError();
-    if (err != hipSuccess) return err;
-    if (a.flags & (F_GATE_EXPERT | F_GATE_PATCH)) {
-        hipLaunchKernelGGL(smha_bwd_gate_kernel, dim3(f.b * f.k), dim3(256), 0, st, a);
-        err = hipGetLastError();
-    }
-    return err;
-}
-
 int smha_backward_splits(int b, int n, int k, int c)
 {
     // parts of an expert's (unit, pick) list: about 8 segments each, at most 8 parts, and never more
@@ -522,48 +478,36 @@ int smha_backward_splits(int b, int n, int k, int c)
     return s > need ? s : need;
 }
 
-hipError_t launch_smha_backward(const SmhaBwdArgs &a, hipStream_t st)
+hipError_t launch_smha_backward(const SmhaBwdArgs &a_in, hipStream_t st)
 {
     typedef bf16_t T;
+    SmhaBwdArgs a = a_in;
     const SmhaArgs &f = a.f;
     const int l_p = f.l / f.m, l_a = f.c * l_p, units = f.b * f.k, dh = f.d_h;
     hipError_t err;
 
-    {   // weights with K contiguous, cleared gate outputs
-        SmhaBwdPrepArgs pa;
-        pa.w[0] = static_cast<const uint16_t *>(f.wq); pa.w[1] = static_cast<const uint16_t *>(f.wk);
-        pa.w[2] = static_cast<const uint16_t *>(f.wv);
-        pa.wqkv_t = static_cast<uint16_t *>(a.wqkv_t);
-        pa.zero[0] = a.d_expert_gate; pa.zero_count[0] = (long)f.b * f.n;
-        pa.zero[1] = a.d_patch_gate; pa.zero_count[1] = (long)f.b * f.n * f.m;
-        pa.n = f.n; pa.d = f.d; pa.d_h = dh;
-        hipLaunchKernelGGL(smha_bwd_prep_kernel, dim3((dh + 31) / 32, (f.d + 31) / 32, 3 * f.n + 1), dim3(256), 0, st, pa);
-        if ((err = hipGetLastError()) != hipSuccess) return err;
-    }
-
     // forward intermediates: q (scaled for the base-2 softmax), k, v, ungated o = hi + lo, lse
     if ((err = launch_smha_qkv_attention(f, st)) != hipSuccess) return err;
 
-    // dO_raw = G[T] W^O^T: the forward's gathered projection with one output block
-    QkvProblem<T, true> dp;
-    dp.x = static_cast<const T *>(a.d_out);
-    dp.wq = dp.wk = dp.wv = static_cast<const T *>(f.wo); dp.w_nk = 1;   // W^O_i [d_h, d] as [n][k]
+    SmhaDoProblem<T> dp;
+    dp.d_out = static_cast<const T *>(a.d_out); dp.wo = static_cast<const T *>(f.wo);
+    dp.o = static_cast<const T *>(f.o); dp.o_lo = static_cast<const T *>(f.o_lo);
     dp.expert_idx = f.expert_idx; dp.patch_idx = f.patch_idx;
-    dp.q = dp.k = dp.v = nullptr;
-    dp.q32 = a.do_raw;
-    dp.l = f.l; dp.d = f.d; dp.n = f.n; dp.kact = f.k; dp.m = f.m; dp.c = f.c;
-    dp.l_p = l_p; dp.l_a = l_a; dp.d_h = dp.d_hp = dh; dp.q_scale = 1.0f; dp.nout = 1;
-    if ((err = launch_gemm_dma_auto<GEMM_B_NK>(dp, units, l_a, dh, f.d, st)) != hipSuccess) return err;
-
-    const dim3 rgrid(l_a / 32, units);
-    if (dh == 32) hipLaunchKernelGGL((smha_bwd_row_kernel<32>), rgrid, dim3(128), 0, st, a);
-    else if (dh == 64) hipLaunchKernelGGL((smha_bwd_row_kernel<64>), rgrid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((smha_bwd_row_kernel<128>), rgrid, dim3(512), 0, st, a);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-    if (a.flags & (F_GATE_EXPERT | F_GATE_PATCH)) {
-        hipLaunchKernelGGL(smha_bwd_gate_kernel, dim3(units), dim3(256), 0, st, a);
-        if ((err = hipGetLastError()) != hipSuccess) return err;
+    dp.expert_gate = (a.flags & F_GATE_EXPERT) ? a.expert_gate : nullptr;
+    dp.patch_gate = (a.flags & F_GATE_PATCH) ? a.patch_gate : nullptr;
+    dp.d_o = static_cast<T *>(a.d_o); dp.og = static_cast<T *>(a.og);
+    dp.rt = a.rt; dp.rt_stride = (size_t)units * l_a;
+    dp.l = f.l; dp.d = f.d; dp.n = f.n; dp.kact = f.k; dp.m = f.m; dp.c = f.c; dp.l_p = l_p; dp.l_a = l_a; dp.d_h = dh;
+    // 32x64 tiles of two 32-column waves while 64-row tiles would leave compute units without one
+    if ((long)units * ((l_a + 63) / 64) < 256) {
+        a.rt_parts = (dh + 31) / 32;
+        err = f.d % 64 == 0 ? launch_gemm_dma<SmhaDoProblem<T>, 32, 64, 64, 1, 2, 4, 2, GEMM_B_NK>(dp, units, l_a, dh, st)
+                            : launch_gemm_dma<SmhaDoProblem<T>, 32, 64, 32, 1, 2, 4, 2, GEMM_B_NK>(dp, units, l_a, dh, st);
+    } else {
+        a.rt_parts = (dh + 63) / 64;
+        err = launch_gemm_dma_auto<GEMM_B_NK>(dp, units, l_a, dh, f.d, st);
     }
+    if (err != hipSuccess) return err;
 
     AttnBwdArgs ab;
     ab.q = static_cast<const T *>(f.q); ab.k = static_cast<const T *>(f.kk); ab.v = static_cast<const T *>(f.v);
@@ -575,17 +519,17 @@ hipError_t launch_smha_backward(const SmhaBwdArgs &a, hipStream_t st)
     err = ab.pad_mask ? launch_attention_bwd<true>(ab, dh, units, st) : launch_attention_bwd<false>(ab, dh, units, st);
     if (err != hipSuccess) return err;
 
-    // d_x = (G) + scatter-add of [dq|dk|dv] [W^q|W^k|W^v]^T: the out-projection's output-stationary
-    // contraction with 3*d_h as the expert's K segment
-    OutProjProblem<T> xp;
-    xp.o = static_cast<const T *>(a.dqkv); xp.o_lo = nullptr; xp.parts = 1;
-    xp.wo = static_cast<const T *>(a.wqkv_t); xp.x = static_cast<const T *>(a.d_out);
+    // d_x = (G) + scatter-add of dq W^q^T + dk W^k^T + dv W^v^T
+    SmhaDxProblem<T, 1> xp;
+    xp.o = static_cast<const T *>(a.dqkv); xp.o_lo = nullptr; xp.parts = 1; xp.wo = nullptr;
+    xp.w[0] = static_cast<const T *>(f.wq); xp.w[1] = static_cast<const T *>(f.wk); xp.w[2] = static_cast<const T *>(f.wv);
+    xp.x = static_cast<const T *>(a.d_out);
     xp.expert_idx = f.expert_idx; xp.patch_idx = f.patch_idx;
     xp.out = static_cast<T *>(a.d_x);
     xp.l = f.l; xp.d = f.d; xp.n = f.n; xp.kact = f.k; xp.m = f.m; xp.c = f.c;
-    xp.l_p = l_p; xp.l_a = l_a; xp.d_h = xp.o_row = 3 * dh; xp.flags = a.flags & F_RESIDUAL;
-    if (l_p <= 32) err = launch_gemm_dma<OutProjProblem<T>, 32, 128, 32, 1, 4, 4, 2>(xp, f.b * f.m, l_p, f.d, st);
-    else err = launch_gemm_dma<OutProjProblem<T>, 64, 128, 32, 2, 2, 4, 2>(xp, f.b * f.m, l_p, f.d, st);
+    xp.l_p = l_p; xp.l_a = l_a; xp.d_h = dh; xp.o_row = 3 * dh; xp.flags = a.flags & F_RESIDUAL;
+    if (l_p <= 32) err = launch_gemm_dma<SmhaDxProblem<T, 1>, 32, 128, 32, 1, 4, 4, 2, GEMM_B_NK>(xp, f.b * f.m, l_p, f.d, st);
+    else err = launch_gemm_dma<SmhaDxProblem<T, 1>, 64, 128, 32, 2, 2, 4, 2, GEMM_B_NK>(xp, f.b * f.m, l_p, f.d, st);
     if (err != hipSuccess) return err;
 
     // weight gradients, all four in one launch (M = d_h each): sets 0-2 = (dW^q, dW^k, dW^v)^T from
@@ -606,7 +550,7 @@ hipError_t launch_smha_backward(const SmhaBwdArgs &a, hipStream_t st)
     ra.dst[0] = a.d_wq; ra.dst[1] = a.d_wk;
     ra.dst[2] = a.d_wv; ra.dst[3] = a.d_wo;
     ra.transposed[0] = ra.transposed[1] = ra.transposed[2] = 1; ra.transposed[3] = 0;
-    return launch_wgrad_reduce(ra, 4, st);
+    return launch_wgrad_reduce_gates<T>(ra, 4, a, st);
 }
 
 }  // namespace uoe

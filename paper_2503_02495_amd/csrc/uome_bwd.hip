@@ -149,6 +149,7 @@ __device__ __forceinline__ void uome_bwd_gate_block(const UomeBwdArgs &a, int s,
     const bool gated = a.flags & F_GATE_EXPERT;
     if (s == 0 && tid < a.n) {
         bool chosen = false;
+#pragma unroll 8
         for (int q = 0; q < a.k; ++q) chosen |= clampi(a.expert_idx[bb * a.k + q], a.n) == tid;
         if (!chosen || !gated) a.d_gate[(size_t)bb * a.n + tid] = 0.f;
     }
@@ -167,15 +168,12 @@ __device__ __forceinline__ void uome_bwd_gate_block(const UomeBwdArgs &a, int s,
 
 __global__ __launch_bounds__(256) void uome_bwd_gate_kernel(UomeBwdArgs a) { uome_bwd_gate_block(a, blockIdx.x, blockIdx.y); }
 
-// the last launch of the expert-selection pass: weight-gradient tiles, and behind them the gate gradient's blocks
-__global__ __launch_bounds__(256) void uome_bwd_finish_kernel(WgradReduceArgs ra, UomeBwdArgs a, int nx, int ny, int tiles)
+// the last launch of the expert-selection pass: the gate gradient's blocks and the weight-gradient tiles
+__global__ __launch_bounds__(256) void uome_bwd_finish_kernel(WgradReduceArgs ra, UomeBwdArgs a, int nx, int ny, int gates)
 {
-    const int id = blockIdx.x;
-    if (id < tiles) {
-        wgrad_reduce_tile<bf16_t>(ra, id % nx, id / nx % ny, id / (nx * ny));
-        return;
-    }
-    uome_bwd_gate_block(a, (id - tiles) % a.k, (id - tiles) / a.k);
+    const int id = (int)blockIdx.x - gates;
+    if (id >= 0) wgrad_reduce_tile<bf16_t>(ra, id % nx, id / nx % ny, id / (nx * ny));
+    else uome_bwd_gate_block(a, blockIdx.x % a.k, blockIdx.x / a.k);
 }
 
 hipError_t launch_uome_gate_grad(const UomeBwdArgs &a, hipStream_t st)
@@ -225,8 +223,9 @@ hipError_t launch_uome_backward(const UomeBwdArgs &a, hipStream_t st)
     ra.partial = a.partial; ra.n = a.n; ra.M = a.d_e; ra.N = a.d; ra.splits = a.splits;
     ra.dst[0] = a.d_a_out; ra.transposed[0] = 0;
     ra.dst[1] = a.d_a_in; ra.transposed[1] = 1;
-    const int nx = (a.d + 31) / 32, ny = (a.d_e + 31) / 32, tiles = nx * ny * 2 * a.n;
-    hipLaunchKernelGGL(uome_bwd_finish_kernel, dim3(tiles + (a.d_gate ? a.b * a.k : 0)), dim3(256), 0, st, ra, a, nx, ny, tiles);
+    const int nx = (a.d + RED_T - 1) / RED_T, ny = (a.d_e + RED_T - 1) / RED_T, tiles = nx * ny * 2 * a.n;
+    const int gates = a.d_gate ? a.b * a.k : 0;
+    hipLaunchKernelGGL(uome_bwd_finish_kernel, dim3(tiles + gates), dim3(256), 0, st, ra, a, nx, ny, gates);
     return hipGetLastError();
 }
 
@@ -310,13 +309,12 @@ hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st)
     hp.rt = a.rt; hp.rt_stride = (size_t)units * l_a;
     if ((err = launch_gemm_dma_auto<GEMM_B_NK>(hp, units, l_a, a.d_e, a.d, st)) != hipSuccess) return err;
 
-    SmhaBwdArgs ga{};  // the unit gate kernel reads its routing fields, the row terms and the gates
+    SmhaBwdArgs ga{};  // the gate gradients' blocks read its routing fields, the row terms and the gates
     ga.f.expert_idx = a.expert_idx; ga.f.patch_idx = a.patch_idx;
     ga.f.b = a.b; ga.f.l = a.l; ga.f.d = a.d; ga.f.n = a.n; ga.f.k = a.k; ga.f.m = a.m; ga.f.c = a.c;
     ga.expert_gate = a.expert_gate; ga.patch_gate = a.patch_gate; ga.flags = a.flags;
     ga.d_expert_gate = a.d_gate; ga.d_patch_gate = a.d_patch_gate; ga.rt = a.rt;
     ga.rt_parts = (a.d_e + 63) / 64;
-    if ((err = launch_unit_gate_grads(ga, st)) != hipSuccess) return err;
 
     // d_u = (d_out) + scatter-add of dZ A^I_i^T: the output-stationary per-patch contraction
     OutProjProblem<T> xp;
@@ -343,7 +341,7 @@ hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st)
     ra.partial = a.partial; ra.n = a.n; ra.M = a.d_e; ra.N = a.d; ra.splits = a.splits;
     ra.dst[0] = a.d_a_out; ra.transposed[0] = 0;
     ra.dst[1] = a.d_a_in; ra.transposed[1] = 1;
-    return launch_wgrad_reduce(ra, 2, st);
+    return launch_wgrad_reduce_gates<T>(ra, 2, ga, st);
 }
 
 }  // namespace uoe
