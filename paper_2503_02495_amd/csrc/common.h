@@ -97,6 +97,23 @@ __device__ __forceinline__ float silu_fast(float z)
     return z * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * z));
 }
 
+// sine and cosine of the rotary angle pos * theta (Eq. 32) for results that are rounded to bf16: the angle rounded to
+// fp32 as for sincosf, taken to revolutions with the product's error kept (angles reach thousands of radians) and
+// handed to the hardware's sine and cosine of a fraction of a revolution
+__device__ __forceinline__ void rope_sincos(float pos, float theta, float &sn, float &cs)
+{
+    constexpr float c_hi = 0.15915494f, c_lo = (float)(0.15915494309189533576888 - (double)c_hi);
+    const float angle = pos * theta, rev = angle * c_hi;
+    const float fr = __builtin_amdgcn_fractf(rev) + fmaf(angle, c_lo, fmaf(angle, c_hi, -rev));
+    sn = __builtin_amdgcn_sinf(fr);
+    cs = __builtin_amdgcn_cosf(fr);
+}
+// theta_i of the pair at offset 2i of the rotary part
+__device__ __forceinline__ float rope_theta(int offset, int rope_dim)
+{
+    return exp2f(-((float)offset / (float)rope_dim) * 13.287712379549449f);  // log2(10000)
+}
+
 // ---------------------------------------------------------------- flags (mirror of the ABI values)
 constexpr uint32_t F_RESIDUAL = 1u, F_GATE_EXPERT = 2u, F_GATE_PATCH = 4u, F_CAUSAL = 8u;
 

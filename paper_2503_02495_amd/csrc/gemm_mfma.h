@@ -114,6 +114,9 @@ template <typename P, typename = void> struct has_f16_cols {
 template <typename P> struct has_f16_cols<P, std::void_t<decltype(&P::f16_col)>> {
     static constexpr bool value = true;
 };
+// problems that rotate pairs of columns on the way out: rotates(first column of 8), rotate(row, column, 4 values)
+template <typename P, typename = void> struct has_rotation : std::false_type {};
+template <typename P> struct has_rotation<P, std::void_t<decltype(&P::rotates)>> : std::true_type {};
 // two fp32 -> packed fp16, round to nearest even
 __device__ __forceinline__ uint32_t pack2_f16_rn(float a, float b)
 {
@@ -202,11 +205,16 @@ __device__ __forceinline__ void wave_epilogue(const P &p, f32x16_t (&acc)[TM][TN
             if constexpr (P::kColScale) sc = coltab[(wcol0 + cl) >> 3];
             bool half = false;   // uniform over the wave: a column block's format
             if constexpr (has_f16_cols<P>::value) half = p.f16_col(gcol0 + j * 32 + qg * 8);
+            bool rot = false;    // uniform as well
+            if constexpr (has_rotation<P>::value) rot = p.rotates(gcol0 + j * 32 + qg * 8);
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
                 const float s2 = P::kRowScale ? sc * rs[i] : sc;
-                const float e0 = p.epi(acc[i][j][qg * 4 + 0], s2), e1 = p.epi(acc[i][j][qg * 4 + 1], s2);
-                const float e2 = p.epi(acc[i][j][qg * 4 + 2], s2), e3 = p.epi(acc[i][j][qg * 4 + 3], s2);
+                float e0 = p.epi(acc[i][j][qg * 4 + 0], s2), e1 = p.epi(acc[i][j][qg * 4 + 1], s2);
+                float e2 = p.epi(acc[i][j][qg * 4 + 2], s2), e3 = p.epi(acc[i][j][qg * 4 + 3], s2);
+                if constexpr (has_rotation<P>::value) {
+                    if (rot) p.rotate(grow0 + i * 32 + lr, gcol0 + cl, e0, e1, e2, e3);
+                }
                 const uint32_t w0 = half ? pack2_f16_rn(e0, e1) : pack2_bf16(e0, e1);
                 const uint32_t w1 = half ? pack2_f16_rn(e2, e3) : pack2_bf16(e2, e3);
                 *reinterpret_cast<uint2 *>(&stage[i * 32 + lr][cl]) = make_uint2(w0, w1);

@@ -86,6 +86,28 @@ template <typename T, bool F32 = false> struct QkvProblem {
                     // d_h are written as zeros)
     float q_scale;  // folded into q on the way out (1 for the plain layout)
     int nout;       // 3: q, k and v; 1: the first projection only (N = d_h)
+    // bf16 rows: the last rope_dim dims of q and k rotated by the row's position in the compacted sequence (Eq. 32),
+    // in fp32 before the one rounding (an in-place kernel behind the projection took 2.8-3.7 us and rounded twice)
+    int rope_dim = 0;
+    __device__ bool rotates(int col8) const
+    {
+        if (rope_dim <= 0) return false;
+        const int which = col8 / d_hp, dh = col8 - which * d_hp;
+        return which < 2 && dh + 8 > d_h - rope_dim && dh < d_h;
+    }
+    __device__ void rotate(int r, int col, float &e0, float &e1, float &e2, float &e3) const
+    {
+        const int dh = col % d_hp, first = d_h - rope_dim;
+        float sn, cs, t;
+        if (dh >= first && dh < d_h) {
+            rope_sincos((float)r, rope_theta(dh - first, rope_dim), sn, cs);
+            t = e0; e0 = t * cs - e1 * sn; e1 = t * sn + e1 * cs;
+        }
+        if (dh + 2 >= first && dh + 2 < d_h) {
+            rope_sincos((float)r, rope_theta(dh + 2 - first, rope_dim), sn, cs);
+            t = e2; e2 = t * cs - e3 * sn; e3 = t * sn + e3 * cs;
+        }
+    }
     int v_f16 = 0;  // MFMA engines, bf16 storage: v is written as fp16 (what the attention kernel's P V product takes)
     __device__ bool f16_col(int nn) const { return v_f16 && nn >= 2 * d_hp; }
 

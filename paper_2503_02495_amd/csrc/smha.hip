@@ -14,7 +14,8 @@
 
 namespace uoe {
 
-// Partial RoPE of Eq. 32, in place on the q and k workspaces: the last rope_dim dims of a head are
+// Partial RoPE of Eq. 32 of the fp32 attention path, in place on the q and k workspaces (the bf16 projections rotate
+// in their epilogue): the last rope_dim dims of a head are
 // rotated in adjacent pairs (2i, 2i+1) by position * 10000^(-2i/rope_dim); the position of a row
 // is its index in the unit's compacted sequence.  One thread per (unit row, pair).
 template <typename T> __global__ __launch_bounds__(256) void smha_rope_kernel(SmhaArgs a)
@@ -921,6 +922,7 @@ static hipError_t smha_mfma_qkv_attention(const SmhaArgs &a, hipStream_t st)
     QP qp = make_qkv<bf16_t>(a);
     qp.q_scale = 1.4426950408889634f / sqrtf((float)a.d_h);  // base-2 softmax in the MFMA kernel
     qp.v_f16 = !a.keep_v_bf16;
+    qp.rope_dim = a.rope_dim;
     // one workgroup row-tile computes q, k and v together so the gathered rows are read once
     // 128-row tiles for long units (measured faster from l_a = 512 up), 32-row tiles for short ones
     auto projections = [&]() -> hipError_t {
@@ -949,8 +951,7 @@ static hipError_t smha_mfma_qkv_attention(const SmhaArgs &a, hipStream_t st)
     } else {
         err = launch_gemm_dma<QP, 128, 128, 32, 2, 2, 4, 2>(qp, units, l_a, 3 * a.d_hp, st);
     }
-    if (err != hipSuccess) return err;
-    return launch_rope<bf16_t>(a, st);
+    return err;
     };
     if (!(a.skip & SMHA_STEP_QKV) && (err = projections()) != hipSuccess) return err;
     if (a.skip & SMHA_STEP_ATTENTION) return hipSuccess;

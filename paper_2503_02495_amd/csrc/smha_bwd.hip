@@ -412,9 +412,8 @@ template <int DH, int NW, int KS, bool KV, bool PAD> __global__ __launch_bounds_
                     for (int h = 0; h < 2; ++h) {
                         const int dh = dh0 + 2 * h;
                         if (dh >= rope_first) {
-                            const float theta = exp2f(-((float)(dh - rope_first) / (float)a.rope_dim) * 13.287712379549449f);
                             float sn, cs;
-                            sincosf((float)orow * theta, &sn, &cs);
+                            rope_sincos((float)orow, rope_theta(dh - rope_first, a.rope_dim), sn, cs);
                             const float ga = v[2 * h], gb = v[2 * h + 1];
                             v[2 * h] = ga * cs + gb * sn;
                             v[2 * h + 1] = gb * cs - ga * sn;
