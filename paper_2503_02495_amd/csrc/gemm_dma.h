@@ -120,9 +120,17 @@ __device__ __forceinline__ void wave_epilogue_f32(const P &p, f32x16_t (&acc)[TM
     }
 }
 
-// OCC = waves per SIMD the register budget is held to (workgroups per CU = OCC * 4 / waves, LDS permitting)
-template <typename P, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int OCC, int FLAGS>
-__global__ __launch_bounds__(WAVES_M *WAVES_N * 64, OCC) void gemm_dma_kernel(P p, TileGrid tg)
+// LDS of one workgroup: stage buffers (the bf16 epilogue reuses them), segment table, column factors
+template <typename P, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES> struct GemmLds {
+    static constexpr int ES = sizeof(typename elem_of<P>::type);
+    static constexpr int EPI = ES == 4 ? 0 : WAVES_M * WAVES_N * (BM / WAVES_M) * (BN / WAVES_N + 8) * 2;
+    static constexpr int OPER = STAGES * (BM + BN) * BK * ES;
+    static constexpr int BYTES = OPER > EPI ? OPER : EPI, SEGS = max_segments<P>::value, COLS = BN / 8;
+};
+
+// One workgroup's tile; `block` is its id within the launch (or within its part of a paired launch).
+template <typename P, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int FLAGS>
+__device__ __forceinline__ void gemm_dma_tile(const P &p, const TileGrid &tg, const int block, unsigned char *lds_raw, uint32_t *segtab, float *coltab)
 {
     typedef typename elem_of<P>::type E;
     constexpr bool F32 = std::is_same<E, float>::value;
@@ -140,9 +148,6 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, OCC) void gemm_dma_kernel(P 
     constexpr int A_DMA = (A_INSTR + NW - 1) / NW, B_DMA = B_INSTR / NW;
     constexpr int A_STAGE = BM * BK * ES, B_STAGE = BK * BN * ES, STAGE_BYTES = A_STAGE + B_STAGE;
     constexpr int SPITCH = WN + 8;                       // epilogue staging pitch in elements
-    constexpr int S_BYTES = F32 ? 0 : NW * WM * SPITCH * 2;
-    constexpr int OPER_BYTES = STAGES * STAGE_BYTES;
-    constexpr int LDS_BYTES = OPER_BYTES > S_BYTES ? OPER_BYTES : S_BYTES;
     constexpr int MAX_SEG = max_segments<P>::value, PARTS = seg_parts<P>::value;
     static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile must be made of 32x32 MFMA tiles");
     static_assert(BK * ES == 64 || BK * ES == 128, "64 or 128 bytes of K per row");
@@ -154,11 +159,7 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, OCC) void gemm_dma_kernel(P 
     static_assert(BN / 8 <= NW * 64, "one column-scale entry per thread");
     static_assert(STAGES >= 2 && (STAGES - 2) * (A_DMA + B_DMA) < 64, "vmcnt range");
 
-    __shared__ __align__(1024) unsigned char lds_raw[LDS_BYTES];
-    __shared__ uint32_t segtab[MAX_SEG];
-    __shared__ float coltab[BN / 8];
-
-    const int tile = (blockIdx.x & 7) * tg.per_xcd + (blockIdx.x >> 3);
+    const int tile = (block & 7) * tg.per_xcd + (block >> 3);
     if (tile >= tg.total) return;
     const int g = tile / (tg.n_tiles * tg.m_tiles);
     const int rem = tile - g * (tg.n_tiles * tg.m_tiles);
@@ -447,17 +448,72 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64, OCC) void gemm_dma_kernel(P 
     }
 }
 
-template <typename P, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int OCC = 1, int FLAGS = 0>
-static hipError_t launch_gemm_dma(const P &p, int groups, int max_rows, int ncols, hipStream_t st)
+// OCC = waves per SIMD the register budget is held to (workgroups per CU = OCC * 4 / waves, LDS permitting)
+template <typename P, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int OCC, int FLAGS>
+__global__ __launch_bounds__(WAVES_M *WAVES_N * 64, OCC) void gemm_dma_kernel(P p, TileGrid tg)
 {
-    if (groups <= 0 || max_rows <= 0 || ncols <= 0) return hipSuccess;
-    TileGrid tg;
+    typedef GemmLds<P, BM, BN, BK, WAVES_M, WAVES_N, STAGES> L;
+    __shared__ __align__(1024) unsigned char lds_raw[L::BYTES];
+    __shared__ uint32_t segtab[L::SEGS];
+    __shared__ float coltab[L::COLS];
+    gemm_dma_tile<P, BM, BN, BK, WAVES_M, WAVES_N, STAGES, FLAGS>(p, tg, blockIdx.x, lds_raw, segtab, coltab);
+}
+
+template <int BM, int BN> static inline hipError_t make_tile_grid(TileGrid &tg, int groups, int max_rows, int ncols)
+{
     tg.n_tiles = (ncols + BN - 1) / BN;
     tg.m_tiles = (max_rows + BM - 1) / BM;
     const long total = (long)tg.n_tiles * tg.m_tiles * groups;
     if (total > (1L << 28)) return hipErrorInvalidValue;
     tg.total = (int)total;
     tg.per_xcd = (tg.total + 7) / 8;
+    return hipSuccess;
+}
+
+// Two independent contractions in one launch, the first one's workgroups in front.  For backward passes on small
+// shapes: an input gradient and the weight gradients read the same operands and neither fills the chip, so one after the
+// other they pay two ramps and two tails with one workgroup per compute unit.
+// Tile shapes as types: GemmTile<P, BM, BN, BK, WAVES_M, WAVES_N, STAGES, FLAGS>
+template <typename P_, int BM_, int BN_, int BK_, int WM_, int WN_, int S_, int F_> struct GemmTile {
+    typedef P_ P;
+    typedef GemmLds<P, BM_, BN_, BK_, WM_, WN_, S_> Lds;
+    static constexpr int BM = BM_, BN = BN_, THREADS = WM_ * WN_ * 64;
+    static __device__ __forceinline__ void run(const P &p, const TileGrid &tg, int block, unsigned char *lds, uint32_t *seg, float *col)
+    {
+        gemm_dma_tile<P, BM_, BN_, BK_, WM_, WN_, S_, F_>(p, tg, block, lds, seg, col);
+    }
+};
+template <typename A, typename B, int OCC>
+__global__ __launch_bounds__(A::THREADS, OCC) void gemm_dma_pair_kernel(typename A::P pa, TileGrid ta, typename B::P pb, TileGrid tb)
+{
+    typedef typename A::Lds LA;
+    typedef typename B::Lds LB;
+    __shared__ __align__(1024) unsigned char lds_raw[LA::BYTES > LB::BYTES ? LA::BYTES : LB::BYTES];
+    __shared__ uint32_t segtab[LA::SEGS > LB::SEGS ? LA::SEGS : LB::SEGS];
+    __shared__ float coltab[LA::COLS > LB::COLS ? LA::COLS : LB::COLS];
+    const int first = ta.per_xcd * 8;
+    if ((int)blockIdx.x < first) A::run(pa, ta, blockIdx.x, lds_raw, segtab, coltab);
+    else B::run(pb, tb, (int)blockIdx.x - first, lds_raw, segtab, coltab);
+}
+template <typename A, typename B, int OCC>
+static hipError_t launch_gemm_dma_pair(const typename A::P &pa, int ga, int ra, int ca, const typename B::P &pb, int gb, int rb, int cb, hipStream_t st)
+{
+    static_assert(A::THREADS == B::THREADS, "one block size");
+    TileGrid ta, tb;
+    hipError_t err;
+    if ((err = make_tile_grid<A::BM, A::BN>(ta, ga, ra, ca)) != hipSuccess) return err;
+    if ((err = make_tile_grid<B::BM, B::BN>(tb, gb, rb, cb)) != hipSuccess) return err;
+    hipLaunchKernelGGL((gemm_dma_pair_kernel<A, B, OCC>), dim3((ta.per_xcd + tb.per_xcd) * 8), dim3(A::THREADS), 0, st, pa, ta, pb, tb);
+    return hipGetLastError();
+}
+
+template <typename P, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int OCC = 1, int FLAGS = 0>
+static hipError_t launch_gemm_dma(const P &p, int groups, int max_rows, int ncols, hipStream_t st)
+{
+    if (groups <= 0 || max_rows <= 0 || ncols <= 0) return hipSuccess;
+    TileGrid tg;
+    const hipError_t err = make_tile_grid<BM, BN>(tg, groups, max_rows, ncols);
+    if (err != hipSuccess) return err;
     hipLaunchKernelGGL((gemm_dma_kernel<P, BM, BN, BK, WAVES_M, WAVES_N, STAGES, OCC, FLAGS>), dim3(tg.per_xcd * 8),
                        dim3(WAVES_M * WAVES_N * 64), 0, st, p, tg);
     return hipGetLastError();

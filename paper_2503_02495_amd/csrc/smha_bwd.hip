@@ -527,9 +527,6 @@ hipError_t launch_smha_backward(const SmhaBwdArgs &a_in, hipStream_t st)
     xp.out = static_cast<T *>(a.d_x);
     xp.l = f.l; xp.d = f.d; xp.n = f.n; xp.kact = f.k; xp.m = f.m; xp.c = f.c;
     xp.l_p = l_p; xp.l_a = l_a; xp.d_h = dh; xp.o_row = 3 * dh; xp.flags = a.flags & F_RESIDUAL;
-    if (l_p <= 32) err = launch_gemm_dma<SmhaDxProblem<T, 1>, 32, 128, 32, 1, 4, 4, 2, GEMM_B_NK>(xp, f.b * f.m, l_p, f.d, st);
-    else err = launch_gemm_dma<SmhaDxProblem<T, 1>, 64, 128, 32, 2, 2, 4, 2, GEMM_B_NK>(xp, f.b * f.m, l_p, f.d, st);
-    if (err != hipSuccess) return err;
 
     // weight gradients, all four in one launch (M = d_h each): sets 0-2 = (dW^q, dW^k, dW^v)^T from
     // [dq|dk|dv]^T against gathered x, set 3 = dW^O from (w*o)^T against gathered d_out
@@ -543,7 +540,20 @@ hipError_t launch_smha_backward(const SmhaBwdArgs &a_in, hipStream_t st)
     wp.expert_idx = f.expert_idx; wp.patch_idx = f.patch_idx; wp.partial = a.partial;
     wp.b = f.b; wp.l = f.l; wp.d = f.d; wp.n = f.n; wp.kact = f.k; wp.m = f.m; wp.c = f.c;
     wp.l_p = l_p; wp.l_a = l_a; wp.splits = a.splits; wp.M = dh;
-    if ((err = launch_gemm_dma_auto<GEMM_A_KM>(wp, 4 * f.n * a.splits, dh, f.d, l_p, st)) != hipSuccess) return err;
+    // one launch with d_x while the weight gradients do not fill the chip's slots (two per compute unit)
+    const int groups = 4 * f.n * a.splits;
+    typedef GemmTile<SmhaDxProblem<T, 1>, 32, 128, 32, 1, 4, 4, GEMM_B_NK> Dx32;
+    typedef GemmTile<SmhaDxProblem<T, 1>, 64, 128, 32, 2, 2, 4, GEMM_B_NK> Dx64;
+    typedef GemmTile<SmhaWgradProblem<T>, 64, 128, 32, 2, 2, 4, GEMM_A_KM> Wg;
+    if ((long)groups * ((dh + 63) / 64) * ((f.d + 127) / 128) <= 512)
+        err = l_p <= 32 ? launch_gemm_dma_pair<Wg, Dx32, 2>(wp, groups, dh, f.d, xp, f.b * f.m, l_p, f.d, st)
+                        : launch_gemm_dma_pair<Wg, Dx64, 2>(wp, groups, dh, f.d, xp, f.b * f.m, l_p, f.d, st);
+    else {
+        if (l_p <= 32) err = launch_gemm_dma<SmhaDxProblem<T, 1>, 32, 128, 32, 1, 4, 4, 2, GEMM_B_NK>(xp, f.b * f.m, l_p, f.d, st);
+        else err = launch_gemm_dma<SmhaDxProblem<T, 1>, 64, 128, 32, 2, 2, 4, 2, GEMM_B_NK>(xp, f.b * f.m, l_p, f.d, st);
+        if (err == hipSuccess) err = launch_gemm_dma_auto<GEMM_A_KM>(wp, groups, dh, f.d, l_p, st);
+    }
+    if (err != hipSuccess) return err;
     WgradReduceArgs ra{};
     ra.partial = a.partial; ra.n = f.n; ra.M = dh; ra.N = f.d; ra.splits = a.splits;
     ra.dst[0] = a.d_wq; ra.dst[1] = a.d_wk;

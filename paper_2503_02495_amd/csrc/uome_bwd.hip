@@ -208,7 +208,6 @@ hipError_t launch_uome_backward(const UomeBwdArgs &a, hipStream_t st)
     up.hidden = static_cast<const T *>(a.dz); up.a_out = static_cast<const T *>(a.a_in); up.w_nk = 1;
     up.u = static_cast<const T *>(a.d_out); up.expert_idx = a.expert_idx; up.out = static_cast<T *>(a.d_u);
     up.l = a.l; up.d = a.d; up.n = a.n; up.kact = a.k; up.d_e = a.d_e; up.flags = a.flags;
-    if ((err = launch_gemm_dma_auto<GEMM_B_NK>(up, a.b, a.l, a.d, a.d_e, st)) != hipSuccess) return err;
 
     // weight gradients, both in one launch: [d_e, d] tiles per expert, token axis cut into a.splits
     // ranges; (dA^I_i)^T = sum dZ_{b,s}^T u_b is stored back as [d, d_e] by the reduction
@@ -218,7 +217,16 @@ hipError_t launch_uome_backward(const UomeBwdArgs &a, hipStream_t st)
     wp.expert_idx = a.expert_idx; wp.partial = a.partial;
     wp.b = a.b; wp.l = a.l; wp.n = a.n; wp.kact = a.k; wp.splits = a.splits;
     wp.M = a.d_e; wp.N = a.d;
-    if ((err = launch_gemm_dma_auto<GEMM_A_KM>(wp, 2 * a.n * a.splits, a.d_e, a.d, a.l / a.splits, st)) != hipSuccess) return err;
+    // one launch for d_u and the weight gradients while neither fills the chip's slots (two per compute unit) by itself
+    const int groups = 2 * a.n * a.splits;
+    const long du64 = (long)a.b * ((a.l + 63) / 64) * ((a.d + 127) / 128), wg128 = (long)groups * ((a.d_e + 127) / 128) * ((a.d + 127) / 128);
+    if (a.d_e % 64 == 0 && (a.l / a.splits) % 64 == 0 && a.d_e > 64 && du64 <= 512 && wg128 <= 512) {
+        typedef GemmTile<UomeDownProblem<T>, 64, 128, 64, 2, 2, 3, GEMM_B_NK> Du;
+        typedef GemmTile<WgradProblem<T>, 128, 128, 64, 2, 2, 2, GEMM_A_KM> Wg;
+        err = launch_gemm_dma_pair<Wg, Du, 2>(wp, groups, a.d_e, a.d, up, a.b, a.l, a.d, st);
+    } else if ((err = launch_gemm_dma_auto<GEMM_B_NK>(up, a.b, a.l, a.d, a.d_e, st)) == hipSuccess)
+        err = launch_gemm_dma_auto<GEMM_A_KM>(wp, groups, a.d_e, a.d, a.l / a.splits, st);
+    if (err != hipSuccess) return err;
     WgradReduceArgs ra{};
     ra.partial = a.partial; ra.n = a.n; ra.M = a.d_e; ra.N = a.d; ra.splits = a.splits;
     ra.dst[0] = a.d_a_out; ra.transposed[0] = 0;
@@ -324,9 +332,6 @@ hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st)
     xp.out = static_cast<T *>(a.d_u);
     xp.l = a.l; xp.d = a.d; xp.n = a.n; xp.kact = a.k; xp.m = a.m; xp.c = a.c;
     xp.l_p = l_p; xp.l_a = l_a; xp.d_h = xp.o_row = a.d_e; xp.flags = a.flags & F_RESIDUAL;
-    if (l_p <= 32) err = launch_gemm_dma<OutProjProblem<T>, 32, 128, 32, 1, 4, 4, 2, GEMM_B_NK>(xp, a.b * a.m, l_p, a.d, st);
-    else err = launch_gemm_dma<OutProjProblem<T>, 64, 128, 32, 2, 2, 4, 2, GEMM_B_NK>(xp, a.b * a.m, l_p, a.d, st);
-    if (err != hipSuccess) return err;
 
     SmhaWgradProblem<T> wp;  // both weight gradients in one launch
     wp.left[0] = static_cast<const T *>(a.h); wp.right[0] = static_cast<const T *>(a.d_out);  // dA^O_i
@@ -336,7 +341,20 @@ hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st)
     wp.expert_idx = a.expert_idx; wp.patch_idx = a.patch_idx; wp.partial = a.partial;
     wp.b = a.b; wp.l = a.l; wp.d = a.d; wp.n = a.n; wp.kact = a.k; wp.m = a.m; wp.c = a.c;
     wp.l_p = l_p; wp.l_a = l_a; wp.splits = a.splits; wp.M = a.d_e;
-    if ((err = launch_gemm_dma_auto<GEMM_A_KM>(wp, 2 * a.n * a.splits, a.d_e, a.d, l_p, st)) != hipSuccess) return err;
+    // one launch with d_u while the weight gradients do not fill the chip's slots (two per compute unit)
+    const int groups = 2 * a.n * a.splits;
+    typedef GemmTile<OutProjProblem<T>, 32, 128, 32, 1, 4, 4, GEMM_B_NK> Du32;
+    typedef GemmTile<OutProjProblem<T>, 64, 128, 32, 2, 2, 4, GEMM_B_NK> Du64;
+    typedef GemmTile<SmhaWgradProblem<T>, 128, 128, 32, 2, 2, 4, GEMM_A_KM> Wg;
+    if (a.d_e > 64 && (long)groups * ((a.d_e + 127) / 128) * ((a.d + 127) / 128) <= 512)
+        err = l_p <= 32 ? launch_gemm_dma_pair<Wg, Du32, 2>(wp, groups, a.d_e, a.d, xp, a.b * a.m, l_p, a.d, st)
+                        : launch_gemm_dma_pair<Wg, Du64, 2>(wp, groups, a.d_e, a.d, xp, a.b * a.m, l_p, a.d, st);
+    else {
+        if (l_p <= 32) err = launch_gemm_dma<OutProjProblem<T>, 32, 128, 32, 1, 4, 4, 2, GEMM_B_NK>(xp, a.b * a.m, l_p, a.d, st);
+        else err = launch_gemm_dma<OutProjProblem<T>, 64, 128, 32, 2, 2, 4, 2, GEMM_B_NK>(xp, a.b * a.m, l_p, a.d, st);
+        if (err == hipSuccess) err = launch_gemm_dma_auto<GEMM_A_KM>(wp, groups, a.d_e, a.d, l_p, st);
+    }
+    if (err != hipSuccess) return err;
     WgradReduceArgs ra{};
     ra.partial = a.partial; ra.n = a.n; ra.M = a.d_e; ra.N = a.d; ra.splits = a.splits;
     ra.dst[0] = a.d_a_out; ra.transposed[0] = 0;
