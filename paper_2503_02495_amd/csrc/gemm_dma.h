@@ -94,6 +94,10 @@ template <typename P> struct max_segments<P, std::void_t<decltype(P::kMaxSegment
     static constexpr int value = P::kMaxSegments;
 };
 
+// problems some of whose left rows are absent from a K segment (a_ptr_ctx returns NULL): those rows read zeros
+template <typename P, typename = void> struct has_row_gaps : std::false_type {};
+template <typename P> struct has_row_gaps<P, std::void_t<decltype(P::kRowGaps)>> : std::true_type {};
+
 static __device__ __align__(16) const uint32_t gemm_zero_piece[4] = {0, 0, 0, 0};
 
 // fp32 epilogue: straight from the accumulators, 16-byte pieces of rows; the problem applies its own factors
@@ -217,7 +221,10 @@ __device__ __forceinline__ void gemm_dma_tile(const P &p, const TileGrid &tg, co
     constexpr int B_PTRS = B_UNIFORM ? 1 : B_DMA;
     constexpr int BRD = B_UNIFORM ? 64 / CN : 0;         // B rows covered by one load instruction
     constexpr int A_PTRS = AKM ? 1 : A_DMA, ARD = AKM ? 64 / CM : 0;
+    constexpr bool GAPS = has_row_gaps<P>::value;
+    static_assert(!(GAPS && AKM), "row gaps are for k-contiguous left operands");
     const E *a_ptr[A_PTRS], *b_ptr[B_PTRS];
+    int a_live[A_PTRS];                                  // GAPS: all ones, or zero for a row that reads the piece of zeros
     int a_krow = 0, b_krow[B_PTRS];                      // first k row of the slot ([k][m], [k][n] tiles)
     const int bnk_row0 = wave * KRD + lane / CK, bnk_chunk = (lane % CK) ^ ((bnk_row0 / (16 / CK)) % CK);
     if constexpr (AKM) a_krow = (wave * 64 + lane) / CM;
@@ -234,7 +241,11 @@ __device__ __forceinline__ void gemm_dma_tile(const P &p, const TileGrid &tg, co
             for (int i = 0; i < A_PTRS; ++i) {
                 int row = m0 + a_row0 + i * NW * KRD;
                 row = row < M ? row : M - 1;
-                a_ptr[i] = reinterpret_cast<const E *>(p.a_ptr_ctx(g, row, seg, ctx)) + a_chunk * EP;
+                const E *at = reinterpret_cast<const E *>(p.a_ptr_ctx(g, row, seg, ctx));
+                if constexpr (GAPS) {
+                    a_live[i] = at ? -1 : 0;
+                    a_ptr[i] = at ? at + a_chunk * EP : reinterpret_cast<const E *>(gemm_zero_piece);
+                } else a_ptr[i] = at + a_chunk * EP;
             }
         }
 #pragma unroll
@@ -260,7 +271,7 @@ __device__ __forceinline__ void gemm_dma_tile(const P &p, const TileGrid &tg, co
             if constexpr (TAIL) return kr < KSEG ? (const void *)at : (const void *)gemm_zero_piece;
             return at;
         } else {
-            const E *at = a_ptr[i < A_PTRS ? i : 0] + off;
+            const E *at = a_ptr[i < A_PTRS ? i : 0] + (GAPS ? off & a_live[i < A_PTRS ? i : 0] : off);
             if constexpr (TAIL) return off + a_chunk * EP < KSEG ? (const void *)at : (const void *)gemm_zero_piece;
             return at;
         }

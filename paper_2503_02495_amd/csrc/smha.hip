@@ -893,7 +893,9 @@ template <typename T> static hipError_t smha_f32(const SmhaArgs &a, hipStream_t 
     }
     if (!(a.skip & SMHA_STEP_ATTENTION) && (err = launch_attention_f32<T>(a, st)) != hipSuccess) return err;
     if (a.skip & SMHA_STEP_OUT) return hipSuccess;
-    return launch_gemm_tail<0>(make_outproj<T>(a), a.b * a.m, l_p, a.d, st);
+    OutProjProblem<T> op = make_outproj<T>(a);
+    const int groups = a.b * op.set_patch_groups(32);
+    return launch_gemm_tail<0>(op, groups, op.gp * l_p, a.d, st);
 }
 
 // Tile choice of the pipelined output-stationary contraction (out-projection of SMHA, second layer
@@ -977,8 +979,9 @@ static hipError_t smha_mfma(const SmhaArgs &a, hipStream_t st)
     op.once = stream_once((size_t)a.b * a.l * a.d * sizeof(bf16_t));
     op.o_lo = static_cast<const bf16_t *>(a.o_lo);   // the MFMA attention kernel writes o as a (hi, lo) bf16 pair
     op.parts = 2;
-    if (a.d_h % 32 != 0) return launch_gemm_tail<0>(op, a.b * a.m, l_p, a.d, st);
-    return launch_outproj_dma(op, a.b * a.m, l_p, a.d, st);
+    const int groups = a.b * op.set_patch_groups(32);
+    if (a.d_h % 32 != 0) return launch_gemm_tail<0>(op, groups, op.gp * l_p, a.d, st);
+    return launch_outproj_dma(op, groups, op.gp * l_p, a.d, st);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1023,7 +1026,9 @@ template <typename T> static hipError_t uome_ds_tail(const UomeDsArgs &a, hipStr
     const int l_p = a.l / a.m, l_a = a.c * l_p;
     hipError_t err;
     if ((err = launch_gemm_tail<0>(make_ds_up<T>(a), a.b * a.k, l_a, a.d_e, st)) != hipSuccess) return err;
-    return launch_gemm_tail<0>(make_ds_down<T>(a), a.b * a.m, l_p, a.d, st);
+    OutProjProblem<T> op = make_ds_down<T>(a);
+    const int groups = a.b * op.set_patch_groups(32);
+    return launch_gemm_tail<0>(op, groups, op.gp * l_p, a.d, st);
 }
 
 static hipError_t uome_ds_mfma(const UomeDsArgs &a, hipStream_t st)
@@ -1043,7 +1048,8 @@ static hipError_t uome_ds_mfma(const UomeDsArgs &a, hipStream_t st)
     if (err != hipSuccess) return err;
     OP op = make_ds_down<bf16_t>(a);
     op.once = stream_once((size_t)a.b * a.l * a.d * sizeof(bf16_t));   // u's last use, the block's output
-    return launch_outproj_dma(op, a.b * a.m, l_p, a.d, st);
+    const int groups = a.b * op.set_patch_groups(32);
+    return launch_outproj_dma(op, groups, op.gp * l_p, a.d, st);
 }
 
 hipError_t launch_uome_ds(const UomeDsArgs &a, bool bf16, hipStream_t st)
