@@ -118,40 +118,35 @@ template <typename T> struct UomeBwdDu : PlainEpilogue {
 
 // Weight gradients: dA^O_i [d_e, d] = sum H_{b,s}^T d_out_b (set 0), (dA^I_i)^T [d_e, d] = sum dZ_{b,s}^T u_b (set 1)
 // over the (sample, slot) pairs of expert i, both operands token-major ([k][m] and [k][n]).  Parts of an expert's
-// sum: chunks of 128 samples (the segment table) x ranges of the token axis; fp32 partial tiles.
+// sum: chunks of 128 samples (the segment table) x ranges, either of the chunk's list of pairs (each with all its tokens)
+// or, where an expert has few pairs, of the token axis; fp32 partial tiles.  A K segment costs its lookups and
+// addresses once, so long ones pay: 128 samples of 196 tokens in 8 ranges of pairs instead of 32 tokens 150 -> 103 us.
 template <typename T> struct UomeBwdWgrad : PlainEpilogue {
     typedef typename storage_elem<T>::type Elem;
     static constexpr int kSegParts = parts_of<T>::value;
     const T *left[2], *right[2];   // left [b, l, k, parts, d_e], right [b, l, d]
     const int32_t *expert_idx;
     float *partial;                // [2*n*splits, d_e, d]
-    int b, l, d, n, kact, d_e, splits, ranges, range;   // splits = sample chunks * ranges; range: tokens per range
+    int b, l, d, n, kact, d_e, splits, ranges, range;   // splits = sample chunks * ranges; range: tokens per range, 0: ranges of pairs
     static constexpr bool kF32Out = true, kPrepare = true;
     __device__ int rows(int) const { return d_e; }
     __device__ int ncols() const { return d; }
     __device__ int first_token(int g) const { return (g % splits) % ranges * range; }
-    __device__ int kseg(int g) const { return max(0, min(range, l - first_token(g))); }
+    __device__ int kseg(int g) const { return range == 0 ? l : max(0, min(range, l - first_token(g))); }
     __device__ int kdim(int) const { return 0; }
     __device__ long b_stride() const { return d; }
     __device__ long a_stride(int) const { return (long)kact * kSegParts * d_e; }
     __device__ int prepare(int g, uint32_t *segtab, int tid, int) const
     {
-        __shared__ int slot_of[128];
-        const int expert = (g / splits) % n, base = (g % splits) / ranges * 128, nb = min(128, b - base);
-        if (tid < nb) {
-            int slot = -1;
-            for (int s = 0; s < kact; ++s)
-                if (clampi(expert_idx[(base + tid) * kact + s], n) == expert) slot = slot < 0 ? s : slot;
-            slot_of[tid] = slot;
+        __shared__ SampleList list;
+        const int expert = (g / splits) % n, part = g % splits, base = part / ranges * 128, nb = min(128, b - base);
+        list.fill(expert_idx + (size_t)base * kact, nb, kact, n, expert, tid);
+        const int total = list.count(), per = range == 0 ? (total + ranges - 1) / ranges : total;
+        const int first = range == 0 ? part % ranges * per : 0, cnt = max(0, min(total - first, per));
+        if (tid < nb && list.slot_of[tid] >= 0) {
+            const int pos = list.before(tid) - first;
+            if (pos >= 0 && pos < cnt) segtab[pos] = ((uint32_t)tid << 8) | (uint32_t)list.slot_of[tid];
         }
-        __syncthreads();
-        int before = 0, cnt = 0;
-        for (int q = 0; q < nb; ++q) {  // every thread counts: cnt is uniform
-            const bool has = slot_of[q] >= 0;
-            before += (has && q < tid) ? 1 : 0;
-            cnt += has ? 1 : 0;
-        }
-        if (tid < nb && slot_of[tid] >= 0) segtab[before] = ((uint32_t)tid << 8) | (uint32_t)slot_of[tid];
         __syncthreads();
         return cnt * kSegParts * kseg(g);
     }
@@ -264,7 +259,8 @@ template <typename T> hipError_t uome_backward_any(const UomeBwdArgs &a, hipStre
     wp.expert_idx = a.expert_idx; wp.partial = a.partial;
     wp.b = a.b; wp.l = a.l; wp.d = a.d; wp.n = a.n; wp.kact = a.k; wp.d_e = a.d_e; wp.splits = a.splits;
     wp.ranges = a.splits / ((a.b + 127) / 128);
-    wp.range = ((a.l + wp.ranges - 1) / wp.ranges + 31) / 32 * 32;
+    // ranges of pairs once an expert has four per range on the average
+    wp.range = (long)a.b * a.k >= 4L * a.n * wp.ranges ? 0 : ((a.l + wp.ranges - 1) / wp.ranges + 31) / 32 * 32;
     if ((err = launch_gemm_tail<GEMM_A_KM>(wp, 2 * a.n * a.splits, a.d_e, a.d, st)) != hipSuccess) return err;
     WgradReduceArgs ra{};
     ra.partial = a.partial; ra.n = a.n; ra.M = a.d_e; ra.N = a.d; ra.splits = a.splits;
@@ -697,28 +693,18 @@ template <typename T> struct SmhaBwdWgrad : PlainEpilogue {
     // context of a segment: sample of the chunk in bits 0-6, slot in bits 7-11, pick in bits 12-21, patch in bits 22-31
     __device__ int prepare(int g, uint32_t *segtab, int tid, int nthreads) const
     {
-        __shared__ int slot_of[128];
+        __shared__ SampleList list;
         const int expert = (g / splits) % n, part = g % splits, base = part / ranges * 128, nb = min(128, b - base);
-        if (tid < nb) {
-            int slot = -1;
-            for (int s = 0; s < kact; ++s)
-                if (clampi(expert_idx[(base + tid) * kact + s], n) == expert) slot = slot < 0 ? s : slot;
-            slot_of[tid] = slot;
-        }
-        __syncthreads();
-        int units = 0;
-        for (int q = 0; q < nb; ++q) units += slot_of[q] >= 0 ? 1 : 0;
-        const int total = units * c, per = (total + ranges - 1) / ranges;
+        list.fill(expert_idx + (size_t)base * kact, nb, kact, n, expert, tid);
+        const int total = list.count() * c, per = (total + ranges - 1) / ranges;
         const int first = part % ranges * per, last = min(total, first + per);
         for (int idx = tid; idx < nb * c; idx += nthreads) {
             const int bb = idx / c, t = idx - bb * c;
-            if (slot_of[bb] < 0) continue;
-            int before = 0;
-            for (int q = 0; q < bb; ++q) before += slot_of[q] >= 0 ? 1 : 0;
-            const int pos = before * c + t;
+            if (list.slot_of[bb] < 0) continue;
+            const int pos = list.before(bb) * c + t;
             if (pos < first || pos >= last || pos - first >= kMaxSegments) continue;
             const int p = clampi(patch_idx[((size_t)(base + bb) * n + expert) * c + t], m);
-            segtab[pos - first] = (uint32_t)bb | ((uint32_t)slot_of[bb] << 7) | ((uint32_t)t << 12) | ((uint32_t)p << 22);
+            segtab[pos - first] = (uint32_t)bb | ((uint32_t)list.slot_of[bb] << 7) | ((uint32_t)t << 12) | ((uint32_t)p << 22);
         }
         __syncthreads();
         return max(0, min(last - first, kMaxSegments)) * kSegParts * l_p;

@@ -464,6 +464,32 @@ template <typename T> struct UomeDownProblem {
     template <bool ONCE> __device__ void put8_as(int g, int r, int nn, uint4 piece) const { store16<ONCE>(out + ((size_t)g * l + r) * d + nn, piece); }
 };
 
+// Which of up to 128 samples selected an expert, and in which slot: the segment lists of the weight gradients.  Two ballots
+// give every sample's place in the list (counting through LDS sample by sample took longer than a short contraction).
+// Called by the whole workgroup of at least 128 threads; ends on a barrier.
+struct SampleList {
+    uint64_t mask[2];
+    int16_t slot_of[128];
+    __device__ void fill(const int32_t *expert_idx, int nb, int kact, int n, int expert, int tid)
+    {
+        int slot = -1;
+        if (tid < nb) {
+#pragma unroll 4
+            for (int s = 0; s < kact; ++s)
+                if (clampi(expert_idx[tid * kact + s], n) == expert) slot = slot < 0 ? s : slot;
+            slot_of[tid] = (int16_t)slot;
+        }
+        const uint64_t m = __ballot(slot >= 0);
+        if (tid < 128 && (tid & 63) == 0) mask[tid >> 6] = m;
+        __syncthreads();
+    }
+    __device__ int count() const { return __popcll(mask[0]) + __popcll(mask[1]); }
+    __device__ int before(int q) const   // listed samples below sample q
+    {
+        return q < 64 ? __popcll(mask[0] & ((1ull << q) - 1)) : __popcll(mask[0]) + __popcll(mask[1] & ((1ull << (q - 64)) - 1));
+    }
+};
+
 // ---------------------------------------------------------------------------------------------
 // Weight gradients of the backward passes, as split contractions over the tokens with fp32 partial
 // tiles.  A launch covers up to four gradient tensors ("sets") of the same shape [n][M][N] at once:
@@ -493,28 +519,14 @@ template <typename T> struct WgradProblem {
     __device__ long b_stride() const { return N; }
     __device__ int kdim(int) const { return 0; }  // prepare() supplies K
     static constexpr bool kPrepare = true;
-    // thread bb looks up which slot of sample bb (if any) holds the expert; the samples that do are
-    // listed in sample order (b <= 128 = the engine's segment table)
+    // the samples that selected the expert, in sample order (b <= 128 = the engine's segment table)
     __device__ int prepare(int g, uint32_t *segtab, int tid, int) const
     {
-        __shared__ int slot_of[128];
-        const int expert = (g % (n * splits)) / splits;
-        if (tid < b) {
-            int slot = -1;
-            for (int s = 0; s < kact; ++s)
-                if (expert_idx[tid * kact + s] == expert) slot = slot < 0 ? s : slot;
-            slot_of[tid] = slot;
-        }
+        __shared__ SampleList list;
+        list.fill(expert_idx, b, kact, n, (g % (n * splits)) / splits, tid);
+        if (tid < b && list.slot_of[tid] >= 0) segtab[list.before(tid)] = ((uint32_t)tid << 8) | (uint32_t)list.slot_of[tid];
         __syncthreads();
-        int before = 0, cnt = 0;
-        for (int bb = 0; bb < b; ++bb) {  // every thread counts: cnt is uniform
-            const bool has = slot_of[bb] >= 0;
-            before += (has && bb < tid) ? 1 : 0;
-            cnt += has ? 1 : 0;
-        }
-        if (tid < b && slot_of[tid] >= 0) segtab[before] = ((uint32_t)tid << 8) | (uint32_t)slot_of[tid];
-        __syncthreads();
-        return cnt * (l / splits);
+        return list.count() * (l / splits);
     }
     __device__ uint32_t seg_ctx(int, int) const { return 0; }
     __device__ const T *a_ptr_ctx(int g, int r, int, uint32_t ctx) const
@@ -572,29 +584,19 @@ template <typename T> struct SmhaWgradProblem {
     // context of a segment: sample in bits 0-6, slot in bits 7-11, pick in bits 12-21, patch in bits 22-31
     __device__ int prepare(int g, uint32_t *segtab, int tid, int nthreads) const
     {
-        __shared__ int slot_of[128];
+        __shared__ SampleList list;
         const int ge = g % (n * splits), expert = ge / splits, part = ge - expert * splits;
-        if (tid < b) {
-            int slot = -1;
-            for (int s = 0; s < kact; ++s)
-                if (expert_idx[tid * kact + s] == expert) slot = slot < 0 ? s : slot;
-            slot_of[tid] = slot;
-        }
-        __syncthreads();
-        int units = 0;
-        for (int bb = 0; bb < b; ++bb) units += slot_of[bb] >= 0 ? 1 : 0;
-        const int total = units * c, per = (total + splits - 1) / splits;
+        list.fill(expert_idx, b, kact, n, expert, tid);
+        const int total = list.count() * c, per = (total + splits - 1) / splits;
         const int first = part * per, last = min(total, first + per);  // this part's segments
         // thread (sample bb, pick t): its position in the full list is (units before bb) * c + t
         for (int idx = tid; idx < b * c; idx += nthreads) {
             const int bb = idx / c, t = idx - bb * c;
-            if (slot_of[bb] < 0) continue;
-            int before = 0;
-            for (int q = 0; q < bb; ++q) before += slot_of[q] >= 0 ? 1 : 0;
-            const int pos = before * c + t;
+            if (list.slot_of[bb] < 0) continue;
+            const int pos = list.before(bb) * c + t;
             if (pos < first || pos >= last || pos - first >= 128) continue;
             const int p = clampi(patch_idx[((size_t)bb * n + expert) * c + t], m);
-            segtab[pos - first] = (uint32_t)bb | ((uint32_t)slot_of[bb] << 7) | ((uint32_t)t << 12) | ((uint32_t)p << 22);
+            segtab[pos - first] = (uint32_t)bb | ((uint32_t)list.slot_of[bb] << 7) | ((uint32_t)t << 12) | ((uint32_t)p << 22);
         }
         __syncthreads();
         return max(0, min(last - first, 128)) * l_p;
