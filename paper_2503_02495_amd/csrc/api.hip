@@ -85,8 +85,8 @@ SmhaWs smha_ws(const uoe_block_desc *d)
 // hidden activations: [b, l, k*d_e] (expert selection) or [b*k, l_a, d_e] (data selection, never larger)
 size_t uome_ws(const uoe_block_desc *d) { return up((size_t)d->b * d->l * d->k * d->width * elem_size(d->dtype)); }
 
-// backward pass of the UoME block: Z, dH, dZ [b,l,k*d_e]; dZ^T, H^T [b,k*d_e,l]; the two transposed
-// weight tensors; split-K tiles of one weight gradient; partial sums of the gate gradient
+// backward pass of the UoME block: Z, dZ, H [b,l,k*d_e]; split-K tiles of the weight gradients; partial sums of the
+// gate gradient
 struct UomeBwdWs {
     size_t z, dh, dz, h, h_op, dz_op, partial, gpart, rt, total;
     int splits, gchunks;
@@ -134,7 +134,7 @@ UomeBwdWs uome_bwd_ws(const uoe_block_desc *d)
     off += up(2 * (size_t)d->n * w.splits * d->d * d->width * sizeof(float));  // both weight gradients
     w.gchunks = uome_backward_gate_chunks(d->l, d->width);
     w.gpart = off; off += up((size_t)d->b * d->k * w.gchunks * sizeof(float));
-    w.rt = off; off += up((size_t)((d->width + 63) / 64) * d->b * d->k * d->l * sizeof(float));
+    w.rt = off; off += up((size_t)((d->width + 31) / 32) * d->b * d->k * d->l * sizeof(float));
     w.total = off;
     return w;
 }

@@ -198,7 +198,7 @@ struct UomeBwdArgs {
     const int32_t *patch_idx;
     const float *patch_gate;                  // NULL when GATE_PATCH is off
     float *d_patch_gate;                      // [b,n,m] or NULL
-    float *rt;                                // [ceil(d_e/64), units, l_a]: parts of dL/d(weight of row t)
+    float *rt;                                // [parts, units, l_a]: parts of dL/d(weight of row t)
     int m, c;
 };
 

@@ -531,7 +531,8 @@ static hipError_t launch_gemm_dma(const P &p, int groups, int max_rows, int ncol
 }
 
 // Tile choice of the GEMM_TAIL variants: bf16 with widths or token counts that no K-step divides, and everything in fp32.
-// FLAGS: operand layouts.  128x128 tiles once they give every compute unit one (fewer operand bytes per product),
+// FLAGS: operand layouts.  128x128 tiles (bf16: eight waves of 64x32, 16 waves a compute unit; four waves of 64x64 took
+// 32.5 against 29.5 us on 128 x 196 x 768 x 384) once they give every compute unit one (fewer operand bytes per product),
 // 64-row tiles below that, 32-row tiles where groups are that short (and in fp32 while 64x64 tiles would leave
 // compute units without work).  Against the vector-ALU engine these variants replace (64x64x8 tiles, one load and
 // two barriers per eight k): UoME up with 6 x 1000 tokens, d 360, 3 x 232 hidden columns in bf16 63 -> 14 us, the
@@ -548,25 +549,52 @@ template <int FLAGS, typename P> static hipError_t launch_gemm_tail(const P &p, 
                 return launch_gemm_dma<P, 32, 64, 32, 1, 2, 4, 2, F>(p, groups, rows, ncols, st);
         return launch_gemm_dma<P, 64, 64, 32, 2, 2, 3, 2, F>(p, groups, rows, ncols, st);
     } else {
-        if (rows > 64 && tiles128 >= 256) return launch_gemm_dma<P, 128, 128, 32, 2, 2, 4, 2, F>(p, groups, rows, ncols, st);
+        if (rows > 64 && tiles128 >= 256) return launch_gemm_dma<P, 128, 128, 32, 2, 4, 3, 4, F>(p, groups, rows, ncols, st);
         if constexpr (!(FLAGS & GEMM_A_KM))
             if (rows <= 32) return launch_gemm_dma<P, 32, 128, 32, 1, 4, 4, 2, F>(p, groups, rows, ncols, st);
         return launch_gemm_dma<P, 64, 128, 32, 2, 2, 4, 2, F>(p, groups, rows, ncols, st);
     }
 }
 
-// Tile choice for contractions without a tuned rule of their own (the backward passes): the large
-// tile when it still gives 512 workgroups, short tiles when the launch would not fill the chip.
-template <int FLAGS = 0, typename P> static hipError_t launch_gemm_dma_auto(const P &p, int groups, int rows, int ncols, int kseg, hipStream_t st)
+// Tile choice of the 32-multiple bf16 contractions (UoME forward and backward, weight gradients).  kdim: length of K
+// (an estimate where the workgroup finds it itself), kseg: of one segment; *wave_cols: the columns of a wave's tile, for
+// problems that leave a value per row and wave tile.  A sweep of 14 tile shapes over 12 problem sizes (2048 x 512 to
+// 4 x 8192 x 2048) gave the order; us for up / down of the MLP, this choice against 256x128x32 with four waves (large
+// launches) or 128x128x64 with four waves (the others):
+//   256x256x64, 8 waves of 128x64   K >= 768 and a tile per compute unit: fewest operand bytes per product
+//                                   (4 x 8192 x 2048 x 1024: 137 / 129 against 152 / 139)
+//                                   not for weight gradients: an expert's K follows its samples, and with one tile a
+//                                   compute unit the longest ends the launch (largest shape 285 -> 307)
+//   128x256x32, 8 waves of 64x64    N a multiple of 256, 384 tiles and more: two workgroups, 16 waves a compute unit
+//                                   (128 x 196 x 768 x 384: 28 against 31; 16 x 4096 x 256 x 256: 18.6 against 20.1)
+//   128x128x32, 8 waves of 64x32    more tiles than slots of the four-wave form (16 x 1024 x 768 x 1024: 34.4 against 36.4;
+//                                   128 x 196 x 384 x 768: 25.9 against 29.9)
+//   128x128x64, 4 waves of 64x64    257 to 512 tiles, one round of two a compute unit (m 8 x 2048: 23.8 against 26.5)
+//   64x128x64, 8 waves of 32x32     fewer (8 x 512 x 1024 x 512: 9.4 against 10.0), and short groups
+//   64x64x64, 4 waves of 32x32      fewer than 160 of those (2 x 640 x 384 x 1024: 6.7 against 8.2)
+template <int FLAGS = 0, typename P>
+static hipError_t launch_gemm_dma_auto(const P &p, int groups, int rows, int ncols, long kdim, int kseg, hipStream_t st, int *wave_cols = nullptr)
 {
-    const long tiles128 = (long)groups * ((rows + 127) / 128) * ((ncols + 127) / 128);
-    if (rows > 128 && (long)groups * ((rows + 255) / 256) * ((ncols + 127) / 128) >= 512)
-        return launch_gemm_dma<P, 256, 128, 32, 2, 2, 3, 2, FLAGS>(p, groups, rows, ncols, st);
-    if (tiles128 < 256 || rows <= 64)
-        return kseg % 64 == 0 ? launch_gemm_dma<P, 64, 128, 64, 2, 2, 3, 2, FLAGS>(p, groups, rows, ncols, st)
-                              : launch_gemm_dma<P, 64, 128, 32, 2, 2, 4, 2, FLAGS>(p, groups, rows, ncols, st);
-    return kseg % 64 == 0 ? launch_gemm_dma<P, 128, 128, 64, 2, 2, 2, 2, FLAGS>(p, groups, rows, ncols, st)
-                          : launch_gemm_dma<P, 128, 128, 32, 2, 2, 4, 2, FLAGS>(p, groups, rows, ncols, st);
+    const auto tiles = [&](int bm, int bn) { return (long)groups * ((rows + bm - 1) / bm) * ((ncols + bn - 1) / bn); };
+    const bool k64 = kseg % 64 == 0, wide = ncols % 256 == 0 || ncols >= 1024;
+    int unused;
+    int &wc = wave_cols ? *wave_cols : unused;
+    wc = 64;
+    if (!(FLAGS & GEMM_A_KM) && rows > 128 && wide && k64 && kdim >= 768 && tiles(256, 256) >= 256)
+        return launch_gemm_dma<P, 256, 256, 64, 2, 4, 2, 2, FLAGS>(p, groups, rows, ncols, st);
+    if (rows > 64 && wide && tiles(128, 256) >= 384) return launch_gemm_dma<P, 128, 256, 32, 2, 4, 3, 4, FLAGS>(p, groups, rows, ncols, st);
+    const long t128 = tiles(128, 128);
+    if (rows > 64 && k64 && t128 > 256 && t128 <= 512) return launch_gemm_dma<P, 128, 128, 64, 2, 2, 2, 2, FLAGS>(p, groups, rows, ncols, st);
+    wc = 32;
+    if (rows > 64 && t128 > 256) return launch_gemm_dma<P, 128, 128, 32, 2, 4, 3, 4, FLAGS>(p, groups, rows, ncols, st);
+    if (!k64) {
+        if constexpr (FLAGS & GEMM_A_KM) {   // a [k][m] tile of 64 x 32 has one load instruction for each of four waves
+            wc = 64;
+            return launch_gemm_dma<P, 64, 128, 32, 2, 2, 4, 2, FLAGS>(p, groups, rows, ncols, st);
+        } else return launch_gemm_dma<P, 64, 128, 32, 2, 4, 4, 4, FLAGS>(p, groups, rows, ncols, st);
+    }
+    if (tiles(64, 128) < 160) return launch_gemm_dma<P, 64, 64, 64, 2, 2, 3, 3, FLAGS>(p, groups, rows, ncols, st);
+    return launch_gemm_dma<P, 64, 128, 64, 2, 4, 3, 4, FLAGS>(p, groups, rows, ncols, st);
 }
 
 }  // namespace uoe

@@ -1,31 +1,14 @@
-// MFMA grouped GEMM engine for bf16 storage (gfx950): C[M,N] = A[M,K] * B[K,N] per group, fp32
-// accumulation in v_mfma_f32_32x32x16_bf16, any problem from problems.h.
+// What the grouped GEMMs (gemm_dma.h) and the attention kernels share on the matrix cores (gfx950): fragment reads, the
+// epilogue of a wave tile, the workgroup order.
 //
-// Tiling.  A workgroup of WAVES_M x WAVES_N wavefronts owns a BM x BN output tile; each wave owns
-// (BM/WAVES_M) x (BN/WAVES_N), a TM x TN grid of 32x32 MFMA tiles.  K advances in steps of BK
-// (32 or 64) through double-buffered LDS: the global loads of step t+1 are issued before the
-// MFMAs of step t and land in the other buffer, one barrier per step.
-//
-// Addressing.  K is a concatenation of segments of length kseg() (one expert's slice, or all of
-// K).  Row and column base pointers are resolved through the routing indices once per segment
-// and kept in registers; inside a segment a tile is base + offset.
-//
-// Operand layout.  The MFMA wants, per lane, 8 K-consecutive values of one row of its first
-// operand and of one column of its second.  Activations A are [M,K] with K contiguous: a 16-byte
-// LDS read of a row is already a fragment.  Weights B are [K,N] with N contiguous (the paper's
-// [n,d,width] layout); they are copied to LDS as they are, [k][n], and the fragments are taken
-// with the gfx950 transposing LDS read (ds_read_b64_tr_b16): in a group of 16 lanes, lane j points
+// Operand layout.  The MFMA wants, per lane, 8 K-consecutive values of one row of its first operand and of one column
+// of its second.  Activations A are [M,K] with K contiguous: a 16-byte LDS read of a row is already a fragment.
+// Weights B are [K,N] with N contiguous (the paper's [n,d,width] layout); they are copied to LDS as they are, [k][n], and
+// the fragments are taken with the gfx950 transposing LDS read (ds_read_b64_tr_b16): in a group of 16 lanes, lane j points
 // at row k0 + j/4, columns c0 + 4*(j%4)..+3, and lane i receives column c0 + i, rows k0..k0+3.
-// The product is computed transposed, D = B^T A^T (weights as the first MFMA operand), so that an
-// accumulator lane is one output ROW and its registers run along N in groups of four: the
-// epilogue can then hand 8-byte row pieces to LDS and write 16-byte row pieces to memory.
-//
-// LDS pitches.  A rows are padded to BK+8 elements (16-byte fragment reads of 16 consecutive rows
-// hit 64 distinct banks).  B rows are padded so that the pitch in dwords is 16 or 48 mod 64: the
-// four 64-byte row pieces a half-wave touches in one transposing read are then bank-disjoint.
-//
-// Requirements (checked by the callers): kseg() % BK == 0, N segments multiples of 8.  M and N
-// tails are masked.
+// The product is computed transposed, D = B^T A^T (weights as the first MFMA operand), so that an accumulator lane is one
+// output ROW and its registers run along N in groups of four: the epilogue can then hand 8-byte row pieces to LDS and
+// write 16-byte row pieces to memory.
 #pragma once
 #include <type_traits>
 #include <utility>
@@ -252,174 +235,5 @@ __host__ __device__ constexpr int b_pitch_dwords(int cols)
 struct TileGrid {
     int n_tiles, m_tiles, total, per_xcd;
 };
-
-template <typename P, int BM, int BN, int BK, int WAVES_M, int WAVES_N>
-__global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_mfma_kernel(P p, TileGrid tg)
-{
-    constexpr int NT = WAVES_M * WAVES_N * 64;
-    constexpr int APITCH = BK + 8;                     // A row pitch in elements
-    constexpr int BPITCH = 2 * b_pitch_dwords(BN);     // B row pitch in elements
-    constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
-    constexpr int TM = WM / 32, TN = WN / 32;
-    constexpr int KC = BK / 8;                         // 16-byte chunks per A row
-    constexpr int A_CHUNKS = BM * KC;
-    constexpr int A_PER_T = (A_CHUNKS + NT - 1) / NT;
-    constexpr int NC = BN / 8;                         // 16-byte chunks per B row
-    constexpr int B_CHUNKS = BK * NC;
-    constexpr int B_PER_T = (B_CHUNKS + NT - 1) / NT;
-    constexpr int SPITCH = WN + 8;                     // epilogue staging pitch in elements
-    constexpr int A_BYTES = 2 * BM * APITCH * 2, B_BYTES = 2 * BK * BPITCH * 2;
-    constexpr int S_BYTES = (NT / 64) * WM * SPITCH * 2;
-    constexpr int LDS_BYTES = (A_BYTES + B_BYTES) > S_BYTES ? (A_BYTES + B_BYTES) : S_BYTES;
-    static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile must be made of 32x32 MFMA tiles");
-    static_assert(BK == 32 || BK == 64, "BK is 32 or 64");
-    static_assert(BN % 8 == 0, "BN is a multiple of 8");
-
-    __shared__ __align__(16) unsigned char lds_raw[LDS_BYTES];
-    uint16_t(*As)[BM][APITCH] = reinterpret_cast<uint16_t(*)[BM][APITCH]>(lds_raw);
-    uint16_t(*Bs)[BK][BPITCH] = reinterpret_cast<uint16_t(*)[BK][BPITCH]>(lds_raw + A_BYTES);
-    __shared__ float coltab[BN / 8];
-
-    const int tile = (blockIdx.x & 7) * tg.per_xcd + (blockIdx.x >> 3);
-    if (tile >= tg.total) return;
-    const int g = tile / (tg.n_tiles * tg.m_tiles);
-    const int rem = tile - g * (tg.n_tiles * tg.m_tiles);
-    const int mt = rem / tg.n_tiles, nt = rem - mt * tg.n_tiles;
-    const int M = p.rows(g), N = p.ncols(), K = p.kdim(g), KSEG = p.kseg(g);
-    const int m0 = mt * BM, n0 = nt * BN;
-    if (m0 >= M) return;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm0 = (wave / WAVES_N) * WM, wn0 = (wave % WAVES_N) * WN;
-    const int lr = lane & 31, lh = lane >> 5;
-    const long bstride = p.b_stride();
-
-    fill_col_scale<P, BN>(p, coltab, g, n0, N, tid, NT);  // published by the barrier before the K loop
-    float rs[TM];
-    load_row_scale<P, TM>(p, rs, g, m0 + wm0, M, lane);
-
-    f32x16_t acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
-
-    // per-thread load assignments and their per-segment base pointers
-    const uint16_t *a_base[A_PER_T];
-    const uint16_t *b_base[B_PER_T];
-    auto resolve_segment = [&](int seg) {
-#pragma unroll
-        for (int i = 0; i < A_PER_T; ++i) {
-            const int c = tid + i * NT;
-            const int row = c / KC, kc = c % KC;
-            a_base[i] = (c < A_CHUNKS && m0 + row < M)
-                            ? reinterpret_cast<const uint16_t *>(p.a_seg_ptr(g, m0 + row, seg)) + kc * 8
-                            : nullptr;
-        }
-#pragma unroll
-        for (int i = 0; i < B_PER_T; ++i) {
-            const int c = tid + i * NT;
-            const int row = c / NC, nc = c % NC;
-            b_base[i] = (c < B_CHUNKS && n0 + nc * 8 < N)
-                            ? reinterpret_cast<const uint16_t *>(p.b_seg_ptr(g, seg, n0 + nc * 8)) + (long)row * bstride
-                            : nullptr;
-        }
-    };
-
-    uint4 a_reg[A_PER_T], b_reg[B_PER_T];
-    auto load_global = [&](int off) {  // tile at offset `off` inside the current segment
-#pragma unroll
-        for (int i = 0; i < A_PER_T; ++i) {
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if (a_base[i]) v = *reinterpret_cast<const uint4 *>(a_base[i] + off);
-            a_reg[i] = v;
-        }
-#pragma unroll
-        for (int i = 0; i < B_PER_T; ++i) {
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if (b_base[i]) v = *reinterpret_cast<const uint4 *>(b_base[i] + (long)off * bstride);
-            b_reg[i] = v;
-        }
-    };
-    auto store_lds = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < A_PER_T; ++i) {
-            const int c = tid + i * NT;
-            if (c < A_CHUNKS) *reinterpret_cast<uint4 *>(&As[buf][c / KC][(c % KC) * 8]) = a_reg[i];
-        }
-#pragma unroll
-        for (int i = 0; i < B_PER_T; ++i) {
-            const int c = tid + i * NT;
-            if (c < B_CHUNKS) *reinterpret_cast<uint4 *>(&Bs[buf][c / NC][(c % NC) * 8]) = b_reg[i];
-        }
-    };
-
-    const int KT = K / BK;
-    int nseg_next = 0, noff = 0;  // segment / offset of the next tile to fetch
-    auto fetch_next = [&]() {
-        if (noff == 0) resolve_segment(nseg_next);
-        load_global(noff);
-        noff += BK;
-        if (noff == KSEG) {
-            noff = 0;
-            ++nseg_next;
-        }
-    };
-    if (KT > 0) {
-        fetch_next();
-        store_lds(0);
-    }
-    __syncthreads();
-    // transposing-read lane roles: group gl = lane/16 -> column half (gl & 1), k half (gl >> 1 == lh)
-    const int tr_row = lh * 8 + ((lane & 15) >> 2);
-    const int tr_col = ((lane >> 4) & 1) * 16 + (lane & 3) * 4;
-    for (int kt = 0; kt < KT; ++kt) {
-        const int buf = kt & 1;
-        if (kt + 1 < KT) fetch_next();
-#pragma unroll
-        for (int ks = 0; ks < BK / 16; ++ks) {
-            bf16x8_t af[TM], wf[TN];
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-                af[i] = *reinterpret_cast<const bf16x8_t *>(&As[buf][wm0 + i * 32 + lr][ks * 16 + lh * 8]);
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const uint16_t *src = &Bs[buf][ks * 16 + tr_row][wn0 + j * 32 + tr_col];
-                const uint2 lo = lds_read_tr4(src);
-                const uint2 hi = lds_read_tr4(src + 4 * BPITCH);
-                wf[j] = __builtin_bit_cast(bf16x8_t, make_uint4(lo.x, lo.y, hi.x, hi.y));
-            }
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[j], af[i], acc[i][j], 0, 0, 0);
-        }
-        if (kt + 1 < KT) store_lds(buf ^ 1);
-        __syncthreads();
-    }
-
-    // Epilogue: the operand buffers are free now (the loop ended on a barrier); each wave stages its
-    // own tile there.
-    uint16_t(*stage)[SPITCH] = reinterpret_cast<uint16_t(*)[SPITCH]>(lds_raw) + (size_t)wave * WM;
-    wave_epilogue<P, TM, TN, SPITCH>(p, acc, stage, coltab, rs, g, m0 + wm0, n0 + wn0, wn0, M, N, lane);
-}
-
-template <typename P, int BM, int BN, int BK, int WAVES_M, int WAVES_N>
-static hipError_t launch_gemm_mfma(const P &p, int groups, int max_rows, int ncols, hipStream_t st)
-{
-    if (groups <= 0 || max_rows <= 0 || ncols <= 0) return hipSuccess;
-    TileGrid tg;
-    tg.n_tiles = (ncols + BN - 1) / BN;
-    tg.m_tiles = (max_rows + BM - 1) / BM;
-    const long total = (long)tg.n_tiles * tg.m_tiles * groups;
-    if (total > (1L << 28)) return hipErrorInvalidValue;
-    tg.total = (int)total;
-    tg.per_xcd = (tg.total + 7) / 8;
-    hipLaunchKernelGGL((gemm_mfma_kernel<P, BM, BN, BK, WAVES_M, WAVES_N>), dim3(tg.per_xcd * 8), dim3(WAVES_M * WAVES_N * 64), 0,
-                       st, p, tg);
-    return hipGetLastError();
-}
 
 }  // namespace uoe

@@ -1038,14 +1038,7 @@ static hipError_t uome_ds_mfma(const UomeDsArgs &a, hipStream_t st)
     const int l_p = a.l / a.m, l_a = a.c * l_p, units = a.b * a.k;
     hipError_t err;
     const UP up = make_ds_up<bf16_t>(a);
-    const long tiles256 = (long)units * ((l_a + 255) / 256) * ((a.d_e + 127) / 128);
-    const long tiles128 = (long)units * ((l_a + 127) / 128) * ((a.d_e + 127) / 128);
-    if (l_a > 128 && tiles256 >= 512) err = launch_gemm_dma<UP, 256, 128, 32, 2, 2, 3, 2>(up, units, l_a, a.d_e, st);
-    else if (l_a > 64 && a.d % 64 == 0 && tiles128 < 256) err = launch_gemm_dma<UP, 64, 128, 64, 2, 2, 3, 2>(up, units, l_a, a.d_e, st);
-    else if (l_a > 64) err = a.d % 64 == 0 ? launch_gemm_dma<UP, 128, 128, 64, 2, 2, 2, 2>(up, units, l_a, a.d_e, st)
-                                           : launch_gemm_dma<UP, 128, 128, 32, 2, 2, 4, 2>(up, units, l_a, a.d_e, st);
-    else err = launch_gemm_mfma<UP, 64, 64, 32, 2, 2>(up, units, l_a, a.d_e, st);
-    if (err != hipSuccess) return err;
+    if ((err = launch_gemm_dma_auto(up, units, l_a, a.d_e, a.d, a.d, st)) != hipSuccess) return err;
     OP op = make_ds_down<bf16_t>(a);
     op.once = stream_once((size_t)a.b * a.l * a.d * sizeof(bf16_t));   // u's last use, the block's output
     const int groups = a.b * op.set_patch_groups(32);

@@ -503,8 +503,9 @@ hipError_t launch_smha_backward(const SmhaBwdArgs &a_in, hipStream_t st)
         err = f.d % 64 == 0 ? launch_gemm_dma<SmhaDoProblem<T>, 32, 64, 64, 1, 2, 4, 2, GEMM_B_NK>(dp, units, l_a, dh, st)
                             : launch_gemm_dma<SmhaDoProblem<T>, 32, 64, 32, 1, 2, 4, 2, GEMM_B_NK>(dp, units, l_a, dh, st);
     } else {
-        a.rt_parts = (dh + 63) / 64;
-        err = launch_gemm_dma_auto<GEMM_B_NK>(dp, units, l_a, dh, f.d, st);
+        int wave_cols;
+        err = launch_gemm_dma_auto<GEMM_B_NK>(dp, units, l_a, dh, f.d, f.d, st, &wave_cols);
+        a.rt_parts = (dh + wave_cols - 1) / wave_cols;
     }
     if (err != hipSuccess) return err;
 
@@ -551,7 +552,7 @@ hipError_t launch_smha_backward(const SmhaBwdArgs &a_in, hipStream_t st)
     else {
         if (l_p <= 32) err = launch_gemm_dma<SmhaDxProblem<T, 1>, 32, 128, 32, 1, 4, 4, 2, GEMM_B_NK>(xp, f.b * f.m, l_p, f.d, st);
         else err = launch_gemm_dma<SmhaDxProblem<T, 1>, 64, 128, 32, 2, 2, 4, 2, GEMM_B_NK>(xp, f.b * f.m, l_p, f.d, st);
-        if (err == hipSuccess) err = launch_gemm_dma_auto<GEMM_A_KM>(wp, groups, dh, f.d, l_p, st);
+        if (err == hipSuccess) err = launch_gemm_dma_auto<GEMM_A_KM>(wp, groups, dh, f.d, (long)units * l_a / (f.n * a.splits), l_p, st);
     }
     if (err != hipSuccess) return err;
     WgradReduceArgs ra{};

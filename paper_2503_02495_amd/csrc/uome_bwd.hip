@@ -97,7 +97,7 @@ template <typename T> struct UomeDhProblem {
     __device__ void write_out(uint16_t (*stage)[SPITCH], const float *colw, const float (&)[TM], int g, int grow0, int gcol0, int M, int N, int lane) const
     {
         constexpr int WM = TM * 32, WC = TN * 4, NPIECE = WM * WC / 64, BATCH = largest_divisor_upto(NPIECE, 8);
-        static_assert(WC == 8, "a lane keeps its 8-column group");
+        static_assert(64 % WC == 0, "a lane keeps its 8-column group");
         const int pc = lane % WC, gcol = gcol0 + pc * 8;
         const bool col_ok = gcol < N;
         const float w = colw[pc];
@@ -128,7 +128,7 @@ template <typename T> struct UomeDhProblem {
         part += __shfl_xor(part, 1, 64);
         part += __shfl_xor(part, 2, 64);
 #pragma unroll
-        for (int off = 8; off < 64; off <<= 1) part += __shfl_xor(part, off, 64);
+        for (int off = WC; off < 64; off <<= 1) part += __shfl_xor(part, off, 64);
         if (lane < WC && lane % 4 == 0 && col_ok) {
             const int s = gcol / d_e, blocks = d_e / 32;
             float *dst = gpart + ((size_t)g * kact + s) * gchunks + (gcol - s * d_e) / 32;
@@ -195,14 +195,14 @@ hipError_t launch_uome_backward(const UomeBwdArgs &a, hipStream_t st)
     zp.expert_idx = a.expert_idx; zp.expert_gate = nullptr; zp.hidden = static_cast<T *>(a.z);
     zp.l = a.l; zp.d = a.d; zp.n = a.n; zp.kact = a.k; zp.d_e = a.d_e;
     zp.once = stream_once((size_t)a.b * a.l * width * sizeof(T));   // Z: written here, read once by the next kernel
-    if ((err = launch_gemm_dma_auto(zp, a.b, a.l, width, a.d, st)) != hipSuccess) return err;
+    if ((err = launch_gemm_dma_auto(zp, a.b, a.l, width, a.d, a.d, st)) != hipSuccess) return err;
 
     UomeDhProblem<T> hp;        // dH = d_out W2_b^T, and dZ, H and the gate gradient's partial sums from Z and it
     hp.d_out = static_cast<const T *>(a.d_out); hp.a_out = static_cast<const T *>(a.a_out); hp.z = static_cast<const T *>(a.z);
     hp.expert_idx = a.expert_idx; hp.expert_gate = (a.flags & F_GATE_EXPERT) ? a.expert_gate : nullptr;
     hp.dz = static_cast<T *>(a.dz); hp.h = static_cast<T *>(a.h); hp.gpart = a.gpart; hp.gchunks = a.gchunks;
     hp.l = a.l; hp.d = a.d; hp.n = a.n; hp.kact = a.k; hp.d_e = a.d_e; hp.once = zp.once;
-    if ((err = launch_gemm_dma_auto<GEMM_B_NK>(hp, a.b, a.l, width, a.d, st)) != hipSuccess) return err;
+    if ((err = launch_gemm_dma_auto<GEMM_B_NK>(hp, a.b, a.l, width, a.d, a.d, st)) != hipSuccess) return err;
 
     UomeDownProblem<T> up;  // d_u = (d_out) + dZ W1_b^T: the second-layer contraction with A^I_i [d, d_e] as [n][k]
     up.hidden = static_cast<const T *>(a.dz); up.a_out = static_cast<const T *>(a.a_in); up.w_nk = 1;
@@ -224,8 +224,8 @@ hipError_t launch_uome_backward(const UomeBwdArgs &a, hipStream_t st)
         typedef GemmTile<UomeDownProblem<T>, 64, 128, 64, 2, 2, 3, GEMM_B_NK> Du;
         typedef GemmTile<WgradProblem<T>, 128, 128, 64, 2, 2, 2, GEMM_A_KM> Wg;
         err = launch_gemm_dma_pair<Wg, Du, 2>(wp, groups, a.d_e, a.d, up, a.b, a.l, a.d, st);
-    } else if ((err = launch_gemm_dma_auto<GEMM_B_NK>(up, a.b, a.l, a.d, a.d_e, st)) == hipSuccess)
-        err = launch_gemm_dma_auto<GEMM_A_KM>(wp, groups, a.d_e, a.d, a.l / a.splits, st);
+    } else if ((err = launch_gemm_dma_auto<GEMM_B_NK>(up, a.b, a.l, a.d, width, a.d_e, st)) == hipSuccess)
+        err = launch_gemm_dma_auto<GEMM_A_KM>(wp, groups, a.d_e, a.d, (long)a.b * a.k * a.l / (a.n * a.splits), a.l / a.splits, st);
     if (err != hipSuccess) return err;
     WgradReduceArgs ra{};
     ra.partial = a.partial; ra.n = a.n; ra.M = a.d_e; ra.N = a.d; ra.splits = a.splits;
@@ -246,7 +246,7 @@ hipError_t launch_uome_backward(const UomeBwdArgs &a, hipStream_t st)
 
 // dH_raw = d_out[T] A^O_i^T with the middle as its epilogue (see UomeDhProblem): the row weight arrives per row
 // (fetched before the K loop, one row per lane, handed round by a shuffle), and a row's dL/dw_t = sum_j dH_raw * SiLU(Z)
-// leaves one part per 64 columns.
+// leaves one part per wave tile's columns.
 template <typename T> struct UomeDsDhProblem : UomeDsUpProblem<T> {   // u = d_out, a_in = A^O, hidden unused
     const T *z;
     T *dz, *h;                  // [units, l_a, d_e]
@@ -259,7 +259,7 @@ template <typename T> struct UomeDsDhProblem : UomeDsUpProblem<T> {   // u = d_o
     __device__ void write_out(uint16_t (*stage)[SPITCH], const float *, const float (&rs)[TM], int g, int grow0, int gcol0, int M, int N, int lane) const
     {
         constexpr int WM = TM * 32, WC = TN * 4, NPIECE = WM * WC / 64, BATCH = largest_divisor_upto(NPIECE, 8);
-        static_assert(WC == 8, "eight lanes of a row");
+        static_assert(64 % WC == 0, "a row lies in WC neighbouring lanes");
         const int pc = lane % WC, gcol = gcol0 + pc * 8;
         const bool col_ok = gcol < N;
         if (gcol0 >= N) return;
@@ -273,19 +273,18 @@ template <typename T> struct UomeDsDhProblem : UomeDsUpProblem<T> {   // u = d_o
             }
 #pragma unroll
             for (int u = 0; u < BATCH; ++u) {
-                const int row = (lane + (t0 + u) * 64) / WC, grow = grow0 + row;   // 8 rows per piece: row / 32 is uniform
+                const int row = (lane + (t0 + u) * 64) / WC, grow = grow0 + row;   // 64 / WC rows at a time: row / 32 is uniform
                 const float w = __shfl(rs[(t0 + u) * (64 / WC) / 32], row & 31, 64);
                 uint4 dz8, h8;
                 float s = uome_mid8(zp[u], *reinterpret_cast<const uint4 *>(&stage[row][pc * 8]), w, dz8, h8);
                 if (!col_ok) s = 0.f;
-                s += __shfl_xor(s, 1, 64);
-                s += __shfl_xor(s, 2, 64);
-                s += __shfl_xor(s, 4, 64);
+#pragma unroll
+                for (int off = 1; off < WC; off <<= 1) s += __shfl_xor(s, off, 64);
                 if (grow < M && col_ok) {
                     const size_t at = ((size_t)g * M + grow) * N + gcol;
                     store16<false>(dz + at, dz8);
                     store16<false>(h + at, h8);
-                    if (pc == 0) rt[gcol0 / 64 * rt_stride + (size_t)g * M + grow] = s;
+                    if (pc == 0) rt[gcol0 / (TN * 32) * rt_stride + (size_t)g * M + grow] = s;
                 }
             }
         }
@@ -305,7 +304,7 @@ hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st)
     zp.q = zp.k = zp.v = static_cast<T *>(a.z); zp.q32 = nullptr;
     zp.l = a.l; zp.d = a.d; zp.n = a.n; zp.kact = a.k; zp.m = a.m; zp.c = a.c;
     zp.l_p = l_p; zp.l_a = l_a; zp.d_h = zp.d_hp = a.d_e; zp.q_scale = 1.0f; zp.nout = 1;
-    if ((err = launch_gemm_dma_auto(zp, units, l_a, a.d_e, a.d, st)) != hipSuccess) return err;
+    if ((err = launch_gemm_dma_auto(zp, units, l_a, a.d_e, a.d, a.d, st)) != hipSuccess) return err;
 
     UomeDsDhProblem<T> hp;      // dH_raw, and dZ, H and the row terms from Z and it
     hp.u = static_cast<const T *>(a.d_out); hp.a_in = static_cast<const T *>(a.a_out); hp.hidden = nullptr;
@@ -315,14 +314,15 @@ hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st)
     hp.l = a.l; hp.d = a.d; hp.n = a.n; hp.kact = a.k; hp.m = a.m; hp.c = a.c; hp.l_p = l_p; hp.l_a = l_a; hp.d_e = a.d_e;
     hp.z = static_cast<const T *>(a.z); hp.dz = static_cast<T *>(a.dz); hp.h = static_cast<T *>(a.h);
     hp.rt = a.rt; hp.rt_stride = (size_t)units * l_a;
-    if ((err = launch_gemm_dma_auto<GEMM_B_NK>(hp, units, l_a, a.d_e, a.d, st)) != hipSuccess) return err;
+    int wave_cols;
+    if ((err = launch_gemm_dma_auto<GEMM_B_NK>(hp, units, l_a, a.d_e, a.d, a.d, st, &wave_cols)) != hipSuccess) return err;
 
     SmhaBwdArgs ga{};  // the gate gradients' blocks read its routing fields, the row terms and the gates
     ga.f.expert_idx = a.expert_idx; ga.f.patch_idx = a.patch_idx;
     ga.f.b = a.b; ga.f.l = a.l; ga.f.d = a.d; ga.f.n = a.n; ga.f.k = a.k; ga.f.m = a.m; ga.f.c = a.c;
     ga.expert_gate = a.expert_gate; ga.patch_gate = a.patch_gate; ga.flags = a.flags;
     ga.d_expert_gate = a.d_gate; ga.d_patch_gate = a.d_patch_gate; ga.rt = a.rt;
-    ga.rt_parts = (a.d_e + 63) / 64;
+    ga.rt_parts = (a.d_e + wave_cols - 1) / wave_cols;
 
     // d_u = (d_out) + scatter-add of dZ A^I_i^T: the output-stationary per-patch contraction
     OutProjProblem<T> xp;
@@ -352,7 +352,7 @@ hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st)
     else {
         if (l_p <= 32) err = launch_gemm_dma<OutProjProblem<T>, 32, 128, 32, 1, 4, 4, 2, GEMM_B_NK>(xp, a.b * a.m, l_p, a.d, st);
         else err = launch_gemm_dma<OutProjProblem<T>, 64, 128, 32, 2, 2, 4, 2, GEMM_B_NK>(xp, a.b * a.m, l_p, a.d, st);
-        if (err == hipSuccess) err = launch_gemm_dma_auto<GEMM_A_KM>(wp, groups, a.d_e, a.d, l_p, st);
+        if (err == hipSuccess) err = launch_gemm_dma_auto<GEMM_A_KM>(wp, groups, a.d_e, a.d, (long)units * l_a / (a.n * a.splits), l_p, st);
     }
     if (err != hipSuccess) return err;
     WgradReduceArgs ra{};
