@@ -765,7 +765,7 @@ template <typename T> hipError_t smha_backward_any(const SmhaBwdArgs &a, hipStre
     xp.expert_idx = f.expert_idx; xp.patch_idx = f.patch_idx; xp.out = static_cast<T *>(a.d_x);
     xp.l = f.l; xp.d = f.d; xp.n = f.n; xp.kact = f.k; xp.m = f.m; xp.c = f.c;
     xp.l_p = l_p; xp.l_a = l_a; xp.d_h = dh; xp.o_row = parts_of<T>::value * 3 * dh; xp.flags = a.flags & F_RESIDUAL;
-    const int groups = f.b * xp.set_patch_groups(32);
+    const int groups = f.b * xp.set_patch_groups(f.b);
     if ((err = launch_gemm_tail<GEMM_B_NK>(xp, groups, xp.gp * l_p, f.d, st)) != hipSuccess) return err;
 
     SmhaBwdWgrad<T> wp;

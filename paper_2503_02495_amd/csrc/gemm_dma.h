@@ -563,8 +563,6 @@ template <int FLAGS, typename P> static hipError_t launch_gemm_tail(const P &p, 
 // launches) or 128x128x64 with four waves (the others):
 //   256x256x64, 8 waves of 128x64   K >= 768 and a tile per compute unit: fewest operand bytes per product
 //                                   (4 x 8192 x 2048 x 1024: 137 / 129 against 152 / 139)
-//                                   not for weight gradients: an expert's K follows its samples, and with one tile a
-//                                   compute unit the longest ends the launch (largest shape 285 -> 307)
 //   128x256x32, 8 waves of 64x64    N a multiple of 256, 384 tiles and more: two workgroups, 16 waves a compute unit
 //                                   (128 x 196 x 768 x 384: 28 against 31; 16 x 4096 x 256 x 256: 18.6 against 20.1)
 //   128x128x32, 8 waves of 64x32    more tiles than slots of the four-wave form (16 x 1024 x 768 x 1024: 34.4 against 36.4;
@@ -572,6 +570,9 @@ template <int FLAGS, typename P> static hipError_t launch_gemm_tail(const P &p, 
 //   128x128x64, 4 waves of 64x64    257 to 512 tiles, one round of two a compute unit (m 8 x 2048: 23.8 against 26.5)
 //   64x128x64, 8 waves of 32x32     fewer (8 x 512 x 1024 x 512: 9.4 against 10.0), and short groups
 //   64x64x64, 4 waves of 32x32      fewer than 160 of those (2 x 640 x 384 x 1024: 6.7 against 8.2)
+// Weight gradients (GEMM_A_KM) keep 256x128x32 with four waves: an expert's K follows its samples, so the finer launch ends
+// more evenly, and the [k][m] operand's fragments come in pairs of transposing reads (largest shape: 285 us, 307 and 296
+// with the first two).
 template <int FLAGS = 0, typename P>
 static hipError_t launch_gemm_dma_auto(const P &p, int groups, int rows, int ncols, long kdim, int kseg, hipStream_t st, int *wave_cols = nullptr)
 {
@@ -580,7 +581,9 @@ static hipError_t launch_gemm_dma_auto(const P &p, int groups, int rows, int nco
     int unused;
     int &wc = wave_cols ? *wave_cols : unused;
     wc = 64;
-    if (!(FLAGS & GEMM_A_KM) && rows > 128 && wide && k64 && kdim >= 768 && tiles(256, 256) >= 256)
+    if constexpr (FLAGS & GEMM_A_KM) {
+        if (rows > 128 && tiles(256, 128) >= 512) return launch_gemm_dma<P, 256, 128, 32, 2, 2, 3, 2, FLAGS>(p, groups, rows, ncols, st);
+    } else if (rows > 128 && wide && k64 && kdim >= 768 && tiles(256, 256) >= 256)
         return launch_gemm_dma<P, 256, 256, 64, 2, 4, 2, 2, FLAGS>(p, groups, rows, ncols, st);
     if (rows > 64 && wide && tiles(128, 256) >= 384) return launch_gemm_dma<P, 128, 256, 32, 2, 4, 3, 4, FLAGS>(p, groups, rows, ncols, st);
     const long t128 = tiles(128, 128);

@@ -169,8 +169,8 @@ template <typename T, bool F32 = false> struct QkvProblem {
 // ---------------------------------------------------------------------------------------------
 // SMHA Eq. 35 + Eq. 36, output-stationary: group = (b, gp consecutive patches); M = gp * l_p; N = d;
 // K = (number of active experts that picked any of them) * d_h, rows of the patches an expert did not pick read zeros.
-// gp > 1 for patches of at most 16 tokens, so that a 32-row tile is not half empty (set_patch_groups: out-projection with
-// 14-token patches of 128 samples 25.8 -> 23.0 us, its input gradient 66.4 -> 56.8 us).  The per-expert products o_i W^o_i that land
+// gp > 1 (set_patch_groups) where patches are shorter than a tile is high: one 14-token patch in a 32-row tile left half of it
+// empty.  The per-expert products o_i W^o_i that land
 // on the same patch are summed as one contraction over the concatenated K, so each output row is
 // written exactly once (residual added in the epilogue) and no atomics are needed.
 // o already carries the gate weight of its row.  In the bf16 MFMA path o arrives as two bf16
@@ -190,11 +190,24 @@ template <typename T> struct OutProjProblem {
     int gp = 1;     // patches per group, at most 32
     static constexpr bool kRowGaps = true;
 
-    // groups for tiles of `tile` rows; returns their number per sample
-    __host__ int set_patch_groups(int tile)
+    // Patches per group for 32-row tiles, or for 128-row ones where those still fill the chip's slots (two workgroups of
+    // eight waves per compute unit) and the experts' rows are not spread too thin: a group multiplies all its rows
+    // with every expert that picked any of its patches, 1 - (1 - c/m)^gp of them.  Up to twice the products of 32-row
+    // groups are repaid by a quarter of the workgroups and of their lookup chains (128 samples of 14 x 14 tokens, 4 of 14
+    // patches, three experts: 21.6 us with two patches, 17.8 us with nine); patches that fill a 64-row tile gain nothing (two
+    // of 64 tokens on the largest shape 37 -> 51 us).  Returns the groups per sample.
+    __host__ int set_patch_groups(int b)
     {
-        gp = 2 * l_p <= tile ? tile / l_p : 1;
-        gp = gp < m ? gp : m;
+        const auto fit = [&](int tile) { const int g = 2 * l_p <= tile ? tile / l_p : 1; return g < m ? g : m; };
+        const auto products = [&](int g, int tile) {
+            double none = 1.0;
+            for (int i = 0; i < g && none > 1e-3; ++i) none *= 1.0 - (double)c / m;
+            return (double)((g * l_p + tile - 1) / tile * tile) / g * (1.0 - none);
+        };
+        gp = fit(32);
+        const int g128 = fit(128) < 32 ? fit(128) : 32;
+        const long tiles = (long)b * ((m + g128 - 1) / g128) * ((d + 127) / 128);
+        if (l_p <= 32 && g128 > gp && g128 * l_p > 64 && tiles >= 512 && products(g128, 128) <= 2.0 * products(gp, 32)) gp = g128;
         return groups_per_sample();
     }
     __host__ __device__ int groups_per_sample() const { return (m + gp - 1) / gp; }

@@ -894,25 +894,24 @@ template <typename T> static hipError_t smha_f32(const SmhaArgs &a, hipStream_t 
     if (!(a.skip & SMHA_STEP_ATTENTION) && (err = launch_attention_f32<T>(a, st)) != hipSuccess) return err;
     if (a.skip & SMHA_STEP_OUT) return hipSuccess;
     OutProjProblem<T> op = make_outproj<T>(a);
-    const int groups = a.b * op.set_patch_groups(32);
+    const int groups = a.b * op.set_patch_groups(a.b);
     return launch_gemm_tail<0>(op, groups, op.gp * l_p, a.d, st);
 }
 
 // Tile choice of the pipelined output-stationary contraction (out-projection of SMHA, second layer
-// of the data-selected UoME).  A (sample, patch) group is a short chain of dependent steps (find the
-// experts that picked the patch, fetch their rows, a few K-steps, add the residual), so with many
-// short groups what counts is how many of them a CU holds at once: two-wave workgroups with two
-// stage buffers (five per CU) beat four-wave ones on the ViT shape (out-projection 30 -> 22 us; one
-// workgroup over the whole row width, one-wave workgroups and 64-column tiles were all slower),
-// while the LM shape's 128 groups are better off with four waves and every K-step in flight.
-template <typename OP> static hipError_t launch_outproj_dma(const OP &op, int groups, int l_p, int d, hipStream_t st)
+// of the data-selected UoME).  A group is a short chain of dependent steps (find the experts that picked its patches,
+// fetch their rows, a few K-steps, add the residual), so with many groups what counts is how many of them a CU holds at
+// once, and with few that every K-step is in flight.  us, out-projection alone, looped:
+//   groups of 65 rows and more (several short patches): 128x128, eight waves (14-token patches 17.8, 32-row tiles 21.6)
+//   64-row patches: two stage buffers and four workgroups a CU while that gives 2048 of them, else four stage buffers
+//   32-row tiles: 512 groups and more two-wave workgroups with two stage buffers, else four waves and four buffers
+template <typename OP> static hipError_t launch_outproj_dma(const OP &op, int groups, int rows, int d, hipStream_t st)
 {
-    if (groups >= 512 && l_p <= 32) return launch_gemm_dma<OP, 32, 128, 32, 1, 2, 2, 4>(op, groups, l_p, d, st);
-    if (l_p <= 32) return launch_gemm_dma<OP, 32, 128, 32, 1, 4, 4, 2>(op, groups, l_p, d, st);
-    // many 64-row groups: four workgroups per CU with two stage buffers each (more of the short dependent
-    // chains in flight: out-projection of the large shape 40.5 -> 35.9 us)
-    if ((long)groups * ((d + 127) / 128) >= 2048) return launch_gemm_dma<OP, 64, 128, 32, 2, 2, 2, 4>(op, groups, l_p, d, st);
-    return launch_gemm_dma<OP, 64, 128, 32, 2, 2, 4, 2>(op, groups, l_p, d, st);
+    if (rows > 64) return launch_gemm_dma<OP, 128, 128, 32, 2, 4, 3, 4>(op, groups, rows, d, st);
+    if (rows <= 32 && groups >= 512) return launch_gemm_dma<OP, 32, 128, 32, 1, 2, 2, 4>(op, groups, rows, d, st);
+    if (rows <= 32) return launch_gemm_dma<OP, 32, 128, 32, 1, 4, 4, 2>(op, groups, rows, d, st);
+    if ((long)groups * ((d + 127) / 128) >= 2048) return launch_gemm_dma<OP, 64, 128, 32, 2, 2, 2, 4>(op, groups, rows, d, st);
+    return launch_gemm_dma<OP, 64, 128, 32, 2, 2, 4, 2>(op, groups, rows, d, st);
 }
 
 // projections, rotary embedding and attention of the MFMA path
@@ -925,35 +924,28 @@ static hipError_t smha_mfma_qkv_attention(const SmhaArgs &a, hipStream_t st)
     qp.q_scale = 1.4426950408889634f / sqrtf((float)a.d_h);  // base-2 softmax in the MFMA kernel
     qp.v_f16 = !a.keep_v_bf16;
     qp.rope_dim = a.rope_dim;
-    // one workgroup row-tile computes q, k and v together so the gathered rows are read once
-    // 128-row tiles for long units (measured faster from l_a = 512 up), 32-row tiles for short ones
+    // 64x64 tiles (one 64-column stretch of q, k or v: the gathered rows are read three times, out of L2, for three times
+    // the workgroups, three per compute unit) up to 1024 of them; one workgroup for q, k and v beyond.  us, looped:
+    // 32 units of 128 rows x 512 x 192 5.9 (32x64 tiles 7.0), 32 of 512 x 256 x 96 5.9 (128x128 8.9), 64 of 256 x 768 x 192 11.6
+    // (64x192 13.2), 384 of 56 x 384 x 192 11.9 against 11.7, 32 of 1024 x 1024 x 192 24.2 with 128x192 (64x64 26.5)
     auto projections = [&]() -> hipError_t {
-    const bool tall = l_a >= 256 && (long)units * ((l_a + 127) / 128) >= 128, k64 = a.d % 64 == 0;
-    if (a.d % 32 != 0) {   // K ends inside a K-step
-        err = launch_gemm_tail<0>(qp, units, l_a, 3 * a.d_hp, st);
-    } else if (a.d_hp == 32) {  // N = 96: 128-column tiles with the tail columns clamped
-        if (tall) err = launch_gemm_dma<QP, 128, 128, 32, 2, 2, 4, 2>(qp, units, l_a, 96, st);
-        else if (k64) err = launch_gemm_dma<QP, 32, 128, 64, 1, 2, 4>(qp, units, l_a, 96, st);
-        else err = launch_gemm_dma<QP, 32, 128, 32, 1, 2, 4>(qp, units, l_a, 96, st);
-    } else if (a.d_hp == 64) {
-        if (tall) err = k64 ? launch_gemm_dma<QP, 128, 192, 64, 2, 2, 3>(qp, units, l_a, 192, st)
-                            : launch_gemm_dma<QP, 128, 192, 32, 2, 2, 4>(qp, units, l_a, 192, st);
-        // 64-row tiles for mid-sized units (the ViT shape: 384 units of 56 rows): three 16 KB stage
-        // buffers, so that two workgroups share a CU and the 384 of them run in one round (with
-        // 64-deep K-steps and one workgroup per CU the second round ran half empty: SMHA stage 50 -> 46 us)
-        else if (k64 && l_a > 32 && (long)units * ((l_a + 63) / 64) >= 256)
-            err = launch_gemm_dma<QP, 64, 192, 32, 2, 2, 3, 2>(qp, units, l_a, 192, st);
-        // fewer row tiles than compute units: one workgroup per projection (64 columns), three
-        // times the workgroups for three reads of the gathered rows out of L2 (the LM shape: 128 row
-        // tiles, the stage 26 -> 22.4 us)
-        else if (k64 && (long)units * ((l_a + 31) / 32) < 256)
-            err = launch_gemm_dma<QP, 32, 64, 64, 1, 2, 4>(qp, units, l_a, 192, st);
-        else if (k64) err = launch_gemm_dma<QP, 32, 192, 64, 1, 2, 4>(qp, units, l_a, 192, st);
-        else err = launch_gemm_dma<QP, 32, 192, 32, 1, 2, 4>(qp, units, l_a, 192, st);
-    } else {
-        err = launch_gemm_dma<QP, 128, 128, 32, 2, 2, 4, 2>(qp, units, l_a, 3 * a.d_hp, st);
-    }
-    return err;
+        const int N = 3 * a.d_hp;
+        if (a.d % 32 != 0) return launch_gemm_tail<0>(qp, units, l_a, N, st);   // K ends inside a K-step
+        const bool k64 = a.d % 64 == 0;
+        const long t64 = (long)units * ((l_a + 63) / 64) * ((N + 63) / 64);
+        if (k64 && l_a > 32 && t64 <= 1024) return launch_gemm_dma<QP, 64, 64, 64, 2, 2, 3, 3>(qp, units, l_a, N, st);
+        if (a.d_hp == 64) {
+            if (l_a >= 256) return k64 ? launch_gemm_dma<QP, 128, 192, 64, 2, 2, 3>(qp, units, l_a, N, st)
+                                       : launch_gemm_dma<QP, 128, 192, 32, 2, 2, 3, 2>(qp, units, l_a, N, st);
+            if (l_a > 32) return launch_gemm_dma<QP, 64, 192, 32, 2, 2, 3, 2>(qp, units, l_a, N, st);
+            if (k64 && (long)units < 256) return launch_gemm_dma<QP, 32, 64, 64, 1, 2, 4>(qp, units, l_a, N, st);
+            return k64 ? launch_gemm_dma<QP, 32, 192, 64, 1, 2, 4>(qp, units, l_a, N, st)
+                       : launch_gemm_dma<QP, 32, 192, 32, 1, 2, 4>(qp, units, l_a, N, st);
+        }
+        if (l_a > 32) return l_a > 64 ? launch_gemm_dma<QP, 128, 128, 32, 2, 4, 3, 4>(qp, units, l_a, N, st)
+                                      : launch_gemm_dma<QP, 64, 128, 32, 2, 4, 4, 4>(qp, units, l_a, N, st);
+        return k64 ? launch_gemm_dma<QP, 32, 128, 64, 1, 2, 4>(qp, units, l_a, N, st)
+                   : launch_gemm_dma<QP, 32, 128, 32, 1, 2, 4>(qp, units, l_a, N, st);
     };
     if (!(a.skip & SMHA_STEP_QKV) && (err = projections()) != hipSuccess) return err;
     if (a.skip & SMHA_STEP_ATTENTION) return hipSuccess;
@@ -979,7 +971,7 @@ static hipError_t smha_mfma(const SmhaArgs &a, hipStream_t st)
     op.once = stream_once((size_t)a.b * a.l * a.d * sizeof(bf16_t));
     op.o_lo = static_cast<const bf16_t *>(a.o_lo);   // the MFMA attention kernel writes o as a (hi, lo) bf16 pair
     op.parts = 2;
-    const int groups = a.b * op.set_patch_groups(32);
+    const int groups = a.b * op.set_patch_groups(a.b);
     if (a.d_h % 32 != 0) return launch_gemm_tail<0>(op, groups, op.gp * l_p, a.d, st);
     return launch_outproj_dma(op, groups, op.gp * l_p, a.d, st);
 }
@@ -1027,7 +1019,7 @@ template <typename T> static hipError_t uome_ds_tail(const UomeDsArgs &a, hipStr
     hipError_t err;
     if ((err = launch_gemm_tail<0>(make_ds_up<T>(a), a.b * a.k, l_a, a.d_e, st)) != hipSuccess) return err;
     OutProjProblem<T> op = make_ds_down<T>(a);
-    const int groups = a.b * op.set_patch_groups(32);
+    const int groups = a.b * op.set_patch_groups(a.b);
     return launch_gemm_tail<0>(op, groups, op.gp * l_p, a.d, st);
 }
 
@@ -1041,7 +1033,7 @@ static hipError_t uome_ds_mfma(const UomeDsArgs &a, hipStream_t st)
     if ((err = launch_gemm_dma_auto(up, units, l_a, a.d_e, a.d, a.d, st)) != hipSuccess) return err;
     OP op = make_ds_down<bf16_t>(a);
     op.once = stream_once((size_t)a.b * a.l * a.d * sizeof(bf16_t));   // u's last use, the block's output
-    const int groups = a.b * op.set_patch_groups(32);
+    const int groups = a.b * op.set_patch_groups(a.b);
     return launch_outproj_dma(op, groups, op.gp * l_p, a.d, st);
 }
 
