@@ -321,10 +321,16 @@ int do_route(const uoe_block_desc *blk, int m, int c, const void *x, const void 
     return launch_route(a, blk->dtype == UOE_BF16, st) == hipSuccess ? UOE_OK : UOE_ERR_DEVICE;
 }
 
+// What a forward SMHA call can leave for the backward pass of the same inputs: q, k, v as that pass reads them and, on the
+// bf16 matrix-core path, the ungated attention output and the log-sum-exp of its rows.
+struct SmhaKept {
+    void *q, *k, *v, *o, *o_lo;
+    float *lse;
+};
 int do_smha(const uoe_block_desc *blk, const void *x, const void *wq, const void *wk, const void *wv,
             const void *wo, const int32_t *expert_idx, const float *expert_gate, const int32_t *patch_idx,
             const float *patch_gate, const uint8_t *pad_mask, void *out, void *ws, size_t ws_bytes, hipStream_t st,
-            uint32_t skip = 0)
+            uint32_t skip = 0, const SmhaKept *keep = nullptr)
 {
     if (!x || !wq || !wk || !wv || !wo || !expert_idx || !patch_idx || !out) return UOE_ERR_INVALID_ARG;
     if (!aligned16(x) || !aligned16(wq) || !aligned16(wk) || !aligned16(wv) || !aligned16(wo) || !aligned16(out))
@@ -344,6 +350,12 @@ int do_smha(const uoe_block_desc *blk, const void *x, const void *wq, const void
     a.d_h = blk->width; a.flags = blk->flags;
     a.rope_dim = blk->rope_dim; a.pad_mask = pad_mask; a.skip = skip;
     a.q = at(ws, w.q); a.kk = at(ws, w.k); a.v = at(ws, w.v); a.o = at(ws, w.o); a.o_lo = at(ws, w.o_lo);
+    if (keep) {
+        a.q = keep->q; a.kk = keep->k;
+        if (blk->dtype == UOE_BF16) {
+            a.v_copy = keep->v; a.o_raw = keep->o; a.o_raw_lo = keep->o_lo; a.lse = keep->lse;
+        } else a.v = keep->v;
+    }
     return launch_smha(a, blk->dtype == UOE_BF16, st) == hipSuccess ? UOE_OK : UOE_ERR_DEVICE;
 }
 
@@ -596,7 +608,7 @@ size_t uoe_smha_backward_workspace_bytes(const uoe_block_desc *blk)
     return check_smha_bwd(blk) == UOE_OK ? smha_bwd_ws(blk).total : 0;
 }
 
-int uoe_smha_backward(const uoe_block_desc *blk, const void *x, const uoe_smha_weights *w, const int32_t *expert_idx,
+static int smha_backward(const SmhaKept *kept, const uoe_block_desc *blk, const void *x, const uoe_smha_weights *w, const int32_t *expert_idx,
                       const float *expert_gate, const int32_t *patch_idx, const float *patch_gate, const uint8_t *pad_mask,
                       const void *d_out, void *d_x, const uoe_smha_weight_grads *dw, float *d_expert_gate,
                       float *d_patch_gate, void *ws, size_t ws_bytes, void *hip_stream)
@@ -622,8 +634,9 @@ int uoe_smha_backward(const uoe_block_desc *blk, const void *x, const uoe_smha_w
     f.d_h = blk->width; f.flags = blk->flags & UOE_FLAG_CAUSAL;  // the recomputed o carries no gate
     f.rope_dim = blk->rope_dim; f.pad_mask = pad_mask;
     f.keep_v_bf16 = 1;   // the attention gradient kernels take v in bf16
+    a.kept = kept != nullptr;
     if (!smha_bwd_mfma(blk)) {
-        f.q = at(ws, s.g_q); f.kk = at(ws, s.g_k); f.v = at(ws, s.g_v);
+        f.q = kept ? kept->q : at(ws, s.g_q); f.kk = kept ? kept->k : at(ws, s.g_k); f.v = kept ? kept->v : at(ws, s.g_v);
         f.lse = reinterpret_cast<float *>(at(ws, s.lse));
         a.d_out = d_out; a.expert_gate = expert_gate; a.patch_gate = patch_gate; a.flags = blk->flags;
         a.d_x = d_x; a.d_wq = dw->d_wq; a.d_wk = dw->d_wk; a.d_wv = dw->d_wv; a.d_wo = dw->d_wo;
@@ -637,6 +650,10 @@ int uoe_smha_backward(const uoe_block_desc *blk, const void *x, const uoe_smha_w
     }
     f.q = at(ws, s.fwd.q); f.kk = at(ws, s.fwd.k); f.v = at(ws, s.fwd.v); f.o = at(ws, s.fwd.o); f.o_lo = at(ws, s.fwd.o_lo);
     f.lse = reinterpret_cast<float *>(at(ws, s.lse));
+    if (kept) {
+        f.q = kept->q; f.kk = kept->k; f.v = kept->v; f.o = kept->o; f.o_lo = kept->o_lo;
+        f.lse = kept->lse;
+    }
     a.d_out = d_out; a.expert_gate = expert_gate; a.patch_gate = patch_gate; a.flags = blk->flags;
     a.d_x = d_x; a.d_wq = dw->d_wq; a.d_wk = dw->d_wk; a.d_wv = dw->d_wv; a.d_wo = dw->d_wo;
     a.d_expert_gate = d_expert_gate; a.d_patch_gate = d_patch_gate;
@@ -646,6 +663,15 @@ int uoe_smha_backward(const uoe_block_desc *blk, const void *x, const uoe_smha_w
     a.partial = reinterpret_cast<float *>(at(ws, s.partial));
     a.splits = s.splits;
     return launch_smha_backward(a, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? UOE_OK : UOE_ERR_DEVICE;
+}
+
+int uoe_smha_backward(const uoe_block_desc *blk, const void *x, const uoe_smha_weights *w, const int32_t *expert_idx,
+                      const float *expert_gate, const int32_t *patch_idx, const float *patch_gate, const uint8_t *pad_mask,
+                      const void *d_out, void *d_x, const uoe_smha_weight_grads *dw, float *d_expert_gate,
+                      float *d_patch_gate, void *ws, size_t ws_bytes, void *hip_stream)
+{
+    return smha_backward(nullptr, blk, x, w, expert_idx, expert_gate, patch_idx, patch_gate, pad_mask, d_out, d_x, dw,
+                         d_expert_gate, d_patch_gate, ws, ws_bytes, hip_stream);
 }
 
 size_t uoe_route_backward_workspace_bytes(const uoe_block_desc *blk)
@@ -810,10 +836,19 @@ int uoe_layer_forward_masked(const uoe_block_desc *smha, const uoe_smha_weights 
     return do_uome(uome, u, wm->a_in, wm->a_out, m_eidx, m_egate, nullptr, nullptr, out, uome_scratch, uome_bytes, st);
 }
 
-// workspace of the layer backward: [u][d_u][gate gradients][the largest of the stages' own scratch]
+// workspace of the layer backward: [u][d_u][gate gradients][kept by the recomputation of u][the largest of the stages' own scratch]
 struct LayerBwdWs {
     size_t u, d_u, d_gate_m, d_pgate_m, d_gate_a, d_pgate_a, stage, stage_bytes, total;
+    size_t keep_q, keep_k, keep_v, keep_o, keep_o_lo, keep_lse;
 };
+// The recomputation of u leaves q, k, v (and the attention's results) to the SMHA backward where both passes hold them in the
+// same form: fp32 storage, and the bf16 matrix-core path (whose projections and attention would otherwise run twice:
+// 55 us of the largest shape's pass, 16 us of lm's).
+static bool layer_bwd_keeps(const uoe_block_desc *smha)
+{
+    if (smha->dtype != UOE_BF16) return true;
+    return smha_bwd_mfma(smha) && (long)smha->c * (smha->l / smha->m) * smha->width < (1L << 31);
+}
 // the descriptor the UoME routers ran with: one patch = the sample in expert-selection mode
 static uoe_block_desc uome_route_desc(const uoe_block_desc *uome)
 {
@@ -823,7 +858,7 @@ static uoe_block_desc uome_route_desc(const uoe_block_desc *uome)
 }
 static LayerBwdWs layer_bwd_ws(const uoe_block_desc *smha, const uoe_block_desc *uome)
 {
-    LayerBwdWs w;
+    LayerBwdWs w{};
     const size_t act = up((size_t)smha->b * smha->l * smha->d * elem_size(smha->dtype));
     const uoe_block_desc um = uome_route_desc(uome);
     size_t off = 0;
@@ -833,6 +868,18 @@ static LayerBwdWs layer_bwd_ws(const uoe_block_desc *smha, const uoe_block_desc 
     w.d_pgate_m = off; off += up((size_t)uome->b * uome->n * uome->m * sizeof(float));
     w.d_gate_a = off; off += up((size_t)smha->b * smha->n * sizeof(float));
     w.d_pgate_a = off; off += up((size_t)smha->b * smha->n * smha->m * sizeof(float));
+    if (layer_bwd_keeps(smha)) {
+        const size_t rows = (size_t)smha->b * smha->k * smha->c * (smha->l / smha->m);
+        const size_t one = up(rows * smha->width * elem_size(smha->dtype));
+        w.keep_q = off; off += one;
+        w.keep_k = off; off += one;
+        w.keep_v = off; off += one;
+        if (smha->dtype == UOE_BF16) {
+            w.keep_o = off; off += one;
+            w.keep_o_lo = off; off += one;
+            w.keep_lse = off; off += up(rows * sizeof(float));
+        }
+    }
     size_t stage = smha_ws(smha).total;
     const size_t others[] = {uoe_uome_backward_workspace_bytes(uome), uoe_smha_backward_workspace_bytes(smha),
                              uoe_route_backward_workspace_bytes(smha), uoe_route_backward_workspace_bytes(&um)};
@@ -901,10 +948,13 @@ int uoe_layer_backward_masked(const uoe_block_desc *smha, const uoe_smha_weights
     float *d_gate_a = reinterpret_cast<float *>(at(ws, w.d_gate_a));
     float *d_pgate_a = reinterpret_cast<float *>(at(ws, w.d_pgate_a));
 
+    const SmhaKept store = {at(ws, w.keep_q), at(ws, w.keep_k), at(ws, w.keep_v), at(ws, w.keep_o), at(ws, w.keep_o_lo),
+                            reinterpret_cast<float *>(at(ws, w.keep_lse))};
+    const SmhaKept *kept = !u && layer_bwd_keeps(smha) ? &store : nullptr;
     if (!u) {  // u = SMHA(x) with the given routing
         void *u_ws = at(ws, w.u);
         rc = do_smha(smha, x, wa->wq, wa->wk, wa->wv, wa->wo, routing_a->expert_idx, routing_a->expert_gate,
-                     routing_a->patch_idx, routing_a->patch_gate, pad_mask, u_ws, stage, w.stage_bytes, st);
+                     routing_a->patch_idx, routing_a->patch_gate, pad_mask, u_ws, stage, w.stage_bytes, st, 0, kept);
         if (rc != UOE_OK) return rc;
         u = u_ws;
     }
@@ -921,8 +971,8 @@ int uoe_layer_backward_masked(const uoe_block_desc *smha, const uoe_smha_weights
         if (rc != UOE_OK) return rc;
     }
     // SMHA block and its routers: d_u -> d_x
-    rc = uoe_smha_backward(smha, x, wa, routing_a->expert_idx, routing_a->expert_gate, routing_a->patch_idx,
-                           routing_a->patch_gate, pad_mask, d_u, d_x, dwa, d_gate_a, d_pgate_a, stage, w.stage_bytes, hip_stream);
+    rc = smha_backward(kept, smha, x, wa, routing_a->expert_idx, routing_a->expert_gate, routing_a->patch_idx,
+                       routing_a->patch_gate, pad_mask, d_u, d_x, dwa, d_gate_a, d_pgate_a, stage, w.stage_bytes, hip_stream);
     if (rc != UOE_OK) return rc;
     if (route_a)
         rc = uoe_route_backward(smha, x, wa->w_expert, wa->w_b, wa->w_a, routing_a->expert_gate, routing_a->patch_gate,

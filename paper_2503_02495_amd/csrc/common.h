@@ -149,6 +149,9 @@ struct SmhaArgs {
     int d_hp;                                 // set by the launcher: smha_padded_width()
     float *lse;                               // [b*k, l_a] or NULL: base-2 log-sum-exp of each query's scaled logits
                                               // (MFMA attention only; kept for the backward pass)
+    // also written when not NULL (bf16 MFMA path): a bf16 copy of v and the attention output without its gate weight as a
+    // (hi, lo) pair.  With lse they are what the backward pass of the same call needs of the forward one
+    void *v_copy, *o_raw, *o_raw_lo;
     int keep_v_bf16;                          // 1: the MFMA path leaves v in bf16 (the backward pass reads it); 0: it
                                               // writes v as fp16, the operand format of the attention kernel's P V
     uint32_t skip;                            // steps NOT to run (SMHA_STEP_* bits; 0 = the whole block): a caller
@@ -205,6 +208,7 @@ struct UomeBwdArgs {
 // Backward pass of the SMHA block
 struct SmhaBwdArgs {
     SmhaArgs f;                               // the forward call that is recomputed: no gates in f.flags, f.lse set
+    int kept;                                 // 1: its q, k, v (and o, o_lo, lse on the bf16 path) are there already
     const void *d_out;                        // [b,l,d]
     const float *expert_gate, *patch_gate;    // as in the forward call (NULL when the flag is off)
     uint32_t flags;                           // the block's flags

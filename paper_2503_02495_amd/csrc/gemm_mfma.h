@@ -201,6 +201,10 @@ __device__ __forceinline__ void wave_epilogue(const P &p, f32x16_t (&acc)[TM][TN
                 const uint32_t w0 = half ? pack2_f16_rn(e0, e1) : pack2_bf16(e0, e1);
                 const uint32_t w1 = half ? pack2_f16_rn(e2, e3) : pack2_bf16(e2, e3);
                 *reinterpret_cast<uint2 *>(&stage[i * 32 + lr][cl]) = make_uint2(w0, w1);
+                if constexpr (has_f16_cols<P>::value) {
+                    const int grow = grow0 + i * 32 + lr;
+                    if (half && p.v_copy && grow < M && gcol0 + cl < N) p.put4_copy(g, grow, gcol0 + cl, make_uint2(pack2_bf16(e0, e1), pack2_bf16(e2, e3)));
+                }
             }
         }
     // no workgroup barrier: a wave reads back only what it staged itself, and the LDS executes one

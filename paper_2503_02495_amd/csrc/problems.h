@@ -110,6 +110,11 @@ template <typename T, bool F32 = false> struct QkvProblem {
     }
     int v_f16 = 0;  // MFMA engines, bf16 storage: v is written as fp16 (what the attention kernel's P V product takes)
     __device__ bool f16_col(int nn) const { return v_f16 && nn >= 2 * d_hp; }
+    T *v_copy = nullptr;   // with v_f16: v in bf16 as well (the backward pass's operand), no padded heads
+    __device__ void put4_copy(int g, int r, int nn, uint2 piece) const
+    {
+        *reinterpret_cast<uint2 *>(v_copy + ((size_t)g * l_a + r) * d_hp + (nn - 2 * d_hp)) = piece;
+    }
 
     __device__ int rows(int) const { return l_a; }
     __device__ int kdim(int) const { return d; }

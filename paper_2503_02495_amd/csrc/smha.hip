@@ -461,6 +461,25 @@ __device__ __forceinline__ void attention_finish(const SmhaArgs &a, unsigned cha
     lsum += __shfl_xor(lsum, 32, 64);
     const float inv = lsum > 0.f ? w / lsum : 0.f;  // a row with no admissible key contributes nothing
     if (a.lse && lh == 0) a.lse[(size_t)g * l_a + qrow] = lsum > 0.f ? mrun + log2f(lsum) : 0.f;
+    if (a.o_raw) {
+        const float raw = lsum > 0.f ? 1.0f / lsum : 0.f;
+        const size_t row = ((size_t)g * l_a + qrow) * DH;
+        bf16_t *r_hi = static_cast<bf16_t *>(a.o_raw) + row, *r_lo = static_cast<bf16_t *>(a.o_raw_lo) + row;
+#pragma unroll
+        for (int td = 0; td < DH / 32; ++td)
+#pragma unroll
+            for (int i4 = 0; i4 < 4; ++i4) {
+                uint32_t hi[2], lo[2];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const float v0 = oacc[td][i4 * 4 + 2 * e] * raw, v1 = oacc[td][i4 * 4 + 2 * e + 1] * raw;
+                    hi[e] = pack2_bf16(v0, v1);
+                    lo[e] = pack2_bf16(v0 - __uint_as_float(hi[e] << 16), v1 - __uint_as_float(hi[e] & 0xFFFF0000u));
+                }
+                *reinterpret_cast<uint2 *>(r_hi + td * 32 + i4 * 8 + lh * 4) = make_uint2(hi[0], hi[1]);
+                *reinterpret_cast<uint2 *>(r_lo + td * 32 + i4 * 8 + lh * 4) = make_uint2(lo[0], lo[1]);
+            }
+    }
     bf16_t *o = static_cast<bf16_t *>(a.o) + ((size_t)g * l_a + qrow) * DH;
     bf16_t *o_lo = static_cast<bf16_t *>(a.o_lo) + ((size_t)g * l_a + qrow) * DH;
     // accumulator register q of tile td is head-dim index td*32 + (q/4)*8 + lh*4 + q%4.
@@ -924,6 +943,7 @@ static hipError_t smha_mfma_qkv_attention(const SmhaArgs &a, hipStream_t st)
     qp.q_scale = 1.4426950408889634f / sqrtf((float)a.d_h);  // base-2 softmax in the MFMA kernel
     qp.v_f16 = !a.keep_v_bf16;
     qp.rope_dim = a.rope_dim;
+    qp.v_copy = static_cast<bf16_t *>(a.v_copy);
     // 64x64 tiles (one 64-column stretch of q, k or v: the gathered rows are read three times, out of L2, for three times
     // the workgroups, three per compute unit) up to 1024 of them; one workgroup for q, k and v beyond.  us, looped:
     // 32 units of 128 rows x 512 x 192 5.9 (32x64 tiles 7.0), 32 of 512 x 256 x 96 5.9 (128x128 8.9), 64 of 256 x 768 x 192 11.6

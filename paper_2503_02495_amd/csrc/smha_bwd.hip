@@ -486,7 +486,7 @@ hipError_t launch_smha_backward(const SmhaBwdArgs &a_in, hipStream_t st)
     hipError_t err;
 
     // forward intermediates: q (scaled for the base-2 softmax), k, v, ungated o = hi + lo, lse
-    if ((err = launch_smha_qkv_attention(f, st)) != hipSuccess) return err;
+    if (!a.kept && (err = launch_smha_qkv_attention(f, st)) != hipSuccess) return err;
 
     SmhaDoProblem<T> dp;
     dp.d_out = static_cast<const T *>(a.d_out); dp.wo = static_cast<const T *>(f.wo);
