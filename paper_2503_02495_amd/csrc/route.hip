@@ -65,24 +65,17 @@ static int data_mfma_waves(int, int)
     return 4;  // 64 tokens per workgroup: the W_B staging is shared by four waves
 }
 // LDS of the MFMA data router: W_B as it is, [d][np] in blocks of 8 rows (see the kernel), then t1.
-__host__ __device__ static size_t data_mfma_wb_bytes(int n, int d)
+static size_t data_mfma_wb_bytes(int n, int d)
 {
     const int np = (n + 15) & ~15;
     return (size_t)((d + 7) / 8) * (8 * np * 2 + (np == 16 ? 128 : 32));
 }
-__host__ __device__ static size_t data_mfma_lds(int n, int d, int waves)
+static size_t data_mfma_lds(int n, int d, int waves)
 {
     const int np = (n + 15) & ~15;
     // W_B, t1 [waves*16][np], and the fold's per-token-group partial sums (at most 8 per thread)
     return data_mfma_wb_bytes(n, d) + (size_t)waves * 16 * np * sizeof(float) + (size_t)waves * 64 * 8 * sizeof(float);
 }
-// the chunk's rows of W_A as well, where they are short and the sum stays within 64 KiB
-constexpr int DATA_WA_MAX = 128;
-__host__ __device__ static bool data_mfma_wa(int n, int d, int m)
-{
-    return m <= DATA_WA_MAX && data_mfma_lds(n, d, 4) + (size_t)64 * m * 2 <= 64 * 1024;
-}
-static size_t data_mfma_launch_lds(int n, int d, int m) { return data_mfma_lds(n, d, 4) + (data_mfma_wa(n, d, m) ? (size_t)64 * m * 2 : 0); }
 bool route_data_uses_mfma(int b, int l, int d, int n, bool bf16)
 {
     return bf16 && data_mfma_lds(n, d, data_mfma_waves(b, l)) <= 60 * 1024;
@@ -322,13 +315,7 @@ __device__ __forceinline__ void route_fold(const RouteArgs &a, int chunk, int bb
         __syncthreads();
         for (int o = tid; o < nm; o += NTHREADS) {
             float t = 0.f;
-            for (int q0 = 0; q0 < tg_n; q0 += 8) {
-                float v[8];
-#pragma unroll
-                for (int q = 0; q < 8; ++q) v[q] = part[(size_t)min(q0 + q, tg_n - 1) * nm + o];
-#pragma unroll
-                for (int q = 0; q < 8; ++q) t += q0 + q < tg_n ? v[q] : 0.f;
-            }
+            for (int q = 0; q < tg_n; ++q) t += part[(size_t)q * nm + o];
             gout[o] = t;
         }
     } else {
@@ -395,7 +382,7 @@ __device__ __forceinline__ void route_data_mfma_body(const RouteArgs &a, int chu
     const int r = lane & 15, ksl = (lane >> 4) * 8;
     const int trow = min(t0 + wave * 16 + r, l - 1);  // rows past the end repeat the last token; never used
     const uint16_t *xr = static_cast<const uint16_t *>(a.x) + ((size_t)bb * l + trow) * d;
-    constexpr int UN = 8;  // k-steps whose A fragments are in flight together
+    constexpr int UN = 4;  // k-steps whose A fragments are in flight together
     auto load_a = [&](int k0, uint4 (&av)[UN]) {
 #pragma unroll
         for (int u = 0; u < UN; ++u) {
@@ -407,29 +394,9 @@ __device__ __forceinline__ void route_data_mfma_body(const RouteArgs &a, int chu
     };
     uint4 av[UN];
     load_a(0, av);
-    // and so are the chunk's rows of W_A, which the fold behind the contraction reads (data_mfma_wa: where they fit)
-    uint16_t *wa_rows = reinterpret_cast<uint16_t *>(t1s + TC * np + NTHREADS * 8);
-    constexpr int WA_PIECES = TC * DATA_WA_MAX / 8 / NTHREADS;
-    static_assert(WAVES == 4, "data_mfma_wa");
-    const bool wa_staged = data_mfma_wa(a.n, d, a.m);
-    uint4 wa[WA_PIECES];
-    if (wa_staged) {
-        const uint16_t *src = static_cast<const uint16_t *>(a.w_a) + (size_t)t0 * a.m;   // 16-byte aligned: t0 is a multiple of 16
-        const int whole = tcur * a.m / 8, rest = tcur * a.m & 7;
-#pragma unroll
-        for (int q = 0; q < WA_PIECES; ++q)
-            if (tid + q * NTHREADS < whole) wa[q] = *reinterpret_cast<const uint4 *>(src + (size_t)(tid + q * NTHREADS) * 8);
-        if (tid < rest) wa_rows[whole * 8 + tid] = src[whole * 8 + tid];
-    }
 
     auto row_at = [&](int e) { return wb + (size_t)(e >> 3) * BLK + (e & 7) * ROWB; };
     stage_w_b<NP, NTHREADS>(a, wb);
-    if (wa_staged) {
-        const int whole = tcur * a.m / 8;
-#pragma unroll
-        for (int q = 0; q < WA_PIECES; ++q)
-            if (tid + q * NTHREADS < whole) *reinterpret_cast<uint4 *>(wa_rows + (tid + q * NTHREADS) * 8) = wa[q];
-    }
     __syncthreads();
 
     rt_f32x4 acc[NTILE];  // NTILE tiles of 16 experts
@@ -466,8 +433,7 @@ __device__ __forceinline__ void route_data_mfma_body(const RouteArgs &a, int chu
         for (int q = 0; q < 4; ++q) t1s[(wave * 16 + (lane >> 4) * 4 + q) * np + t * 16 + r] = acc[t][q];
     __syncthreads();
 
-    if (wa_staged) route_fold<NTHREADS>(a, chunk, bb, 0, tcur, t1s, np, t1s + TC * np, wa_rows);
-    else route_fold<NTHREADS>(a, chunk, bb, t0, tcur, t1s, np, t1s + TC * np);
+    route_fold<NTHREADS>(a, chunk, bb, t0, tcur, t1s, np, t1s + TC * np);
 }
 
 template <int WAVES, int NTILE>
@@ -1372,7 +1338,7 @@ hipError_t launch_route(const RouteArgs &a_in, bool bf16, hipStream_t st)
     if (has_e && bf16 && data_mfma && (double)a.b * a.l * a.d * 2 <= 48e6) {
         const int n_data = a.nchunks_d * a.b;
         const dim3 grid(n_data + a.nchunks * groups_e);
-        const size_t shd = data_mfma_launch_lds(a.n, a.d, a.m);
+        const size_t shd = data_mfma_lds(a.n, a.d, 4);
 #define UOE_FUSED(RT, CT)                                                                                         \
     do {                                                                                                          \
         const size_t she = route_expert_mfma_lds<RT, CT>();                                                       \
@@ -1408,7 +1374,7 @@ hipError_t launch_route(const RouteArgs &a_in, bool bf16, hipStream_t st)
             if ((err = launch_partial_n<float>(a, true, has_d, st)) != hipSuccess) return err;
         }
         if (data_mfma) {
-            const size_t sh = data_mfma_launch_lds(a.n, a.d, a.m);
+            const size_t sh = data_mfma_lds(a.n, a.d, 4);
             const dim3 grid(a.nchunks_d, a.b);
             if (a.n <= 16) hipLaunchKernelGGL((route_data_mfma_kernel<4, 1>), grid, dim3(256), sh, st, a);
             else hipLaunchKernelGGL((route_data_mfma_kernel<4, 2>), grid, dim3(256), sh, st, a);
