@@ -669,9 +669,10 @@ __global__ __launch_bounds__(NQ *KSPLIT * 64) void attention_mfma_kernel(SmhaArg
 // The same kernel with K and V tiles copied from global memory straight into LDS (global_load_lds_dwordx4:
 // 16 bytes per lane, the 64 lanes of an instruction fill 1 KiB of consecutive LDS), three tiles deep: no
 // staging registers, no LDS store instructions and no converts in the loop, and a wave waits for a tile only
-// when it needs it.  What that takes: V already in fp16 in memory (the projection kernel writes it so), no
-// padding mask (its per-key lookups are ordinary loads, whose compiler-placed waits would drain the copies in
-// flight: masked calls take the register-staged kernel), and unpadded tiles, so bank conflicts are avoided
+// when it needs it.  What that takes: V already in fp16 in memory (the projection kernel writes it so), the
+// padding flags of all the unit's keys in LDS before the loop (PAD, up to DMA_PAD_KEYS of them: their lookups are ordinary
+// loads, whose compiler-placed waits would drain the copies in flight; longer masked units take the register-staged
+// kernel), and unpadded tiles, so bank conflicts are avoided
 // by permuting which 16-byte piece of a row an LDS slot receives (every lane supplies its own global
 // address): K slot (r, pos) <- piece pos ^ ((r / (16/CK)) % CK), the rule for tiles read as row fragments; V
 // slot (r, pos) <- piece pos ^ ((r & 3) << 2) for 256-byte rows (d_h = 128) and pos ^ (((r >> 1) & 1) << 2) for
@@ -680,7 +681,10 @@ __global__ __launch_bounds__(NQ *KSPLIT * 64) void attention_mfma_kernel(SmhaArg
 // issue order): at the top of an iteration at most the copies of the STAGES-2 younger tiles may be
 // outstanding, then one barrier publishes every wave's part of the tile and frees the buffer of the tile
 // before for the copies issued right after it.
-template <int DH, int NQ, int KSPLIT>
+// 4096 flags: past that a byte per key would cost the second workgroup of a compute unit (160 KiB: 2 x (64 + 4) KiB
+// fit, and so do the shapes of 128 KiB); the masked lm forward, 32 units of 128 keys at d_h 64, goes 65.6 -> 64.4 us in all.
+constexpr int DMA_PAD_KEYS = 4096;
+template <int DH, int NQ, int KSPLIT, bool PAD>
 __global__ __launch_bounds__(NQ *KSPLIT * 64) void attention_dma_kernel(SmhaArgs a)
 {
     static_assert(DH == 64 || DH == 128, "piece permutations are written for 128- and 256-byte rows");
@@ -694,6 +698,7 @@ __global__ __launch_bounds__(NQ *KSPLIT * 64) void attention_dma_kernel(SmhaArgs
     constexpr int MERGE_BYTES = (KSPLIT - 1) * NQ * 64 * (DH / 2 + 2) * 4;
     constexpr int LDS_BYTES = KSPLIT * SPLIT_BYTES > MERGE_BYTES ? KSPLIT * SPLIT_BYTES : MERGE_BYTES;
     __shared__ __align__(1024) unsigned char lds_raw[LDS_BYTES];
+    __shared__ __align__(16) unsigned char Km[PAD ? DMA_PAD_KEYS : 16];   // key admissible under the padding mask
 
     const int l_p = a.l / a.m, l_a = a.c * l_p;
     int g, qblk;   // workgroup -> (unit, query block): the query blocks of a unit share an XCD (see attention_mfma_kernel)
@@ -776,6 +781,8 @@ __global__ __launch_bounds__(NQ *KSPLIT * 64) void attention_dma_kernel(SmhaArgs
     };
 #pragma unroll
     for (int q = 0; q < STAGES - 1; ++q) issue(q, q);
+    if constexpr (PAD)   // under the first copies; published by the loop's first barrier
+        for (int key = tid; key < nkt_all * BKV; key += NQ * KSPLIT * 64) Km[key] = key < l_a && key_is_token(a, g, min(key, l_a - 1), l_p);
     // fragment offsets (bytes inside a stage): K row fragments, V^T through the transposing read
     const int vx = (lane & 15) >> 2;   // row of the 4-row group this lane points at
     int stage = 0, fill = STAGES - 1;
@@ -786,7 +793,7 @@ __global__ __launch_bounds__(NQ *KSPLIT * 64) void attention_dma_kernel(SmhaArgs
         const int kt = tile_of(it);
         if (kt < nkt) {
             const unsigned char *kb = sbase + stage * (2 * TILE_BYTES), *vb = kb + TILE_BYTES;
-            attention_tile<DH>(qf, oacc, mrun, lsum, kt, l_a, qrow, qblk * (32 * NQ) + qg * 32, causal, nullptr, lane,
+            attention_tile<DH>(qf, oacc, mrun, lsum, kt, l_a, qrow, qblk * (32 * NQ) + qg * 32, causal, PAD ? Km + kt * BKV : nullptr, lane,
                                [&](int t, int ks) {
                                    const int r = t * 32 + lr;
                                    return *reinterpret_cast<const bf16x8_t *>(kb + r * (DH * 2) + (((ks * 2 + lh) ^ ((r / (16 / CK)) % CK)) * 16));
@@ -824,8 +831,12 @@ template <int DH, int NQ, int KSPLIT> static void launch_attention_shape(const S
     // (LDS: stages x (K + V tile) per split; every wave the same number of copies; the wait count fits its field)
     if constexpr ((DH == 64 || DH == 128) && KSPLIT * 4 * 2 * 64 * DH * 2 <= 160 * 1024 && (64 * DH * 2 / 1024) % NQ == 0 &&
                   2 * 2 * (64 * DH * 2 / 1024 / NQ) <= 63) {
-        if (!a.pad_mask) {   // V in fp16, no padding mask: tiles copied straight into LDS
-            hipLaunchKernelGGL((attention_dma_kernel<DH, NQ, KSPLIT>), grid, block, 0, st, a);
+        if (!a.pad_mask) {   // V in fp16: tiles copied straight into LDS
+            hipLaunchKernelGGL((attention_dma_kernel<DH, NQ, KSPLIT, false>), grid, block, 0, st, a);
+            return;
+        }
+        if (l_a <= DMA_PAD_KEYS) {
+            hipLaunchKernelGGL((attention_dma_kernel<DH, NQ, KSPLIT, true>), grid, block, 0, st, a);
             return;
         }
     }

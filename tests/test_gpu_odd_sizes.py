@@ -18,6 +18,10 @@ ODD = {
     "odd_dh40": P.small(b=3, l=105, d=72, n_a=4, d_h=40, m=15, c=4, k_a=3, n_m=4, d_e=56, k_m=2, dtype=BF),
     "odd_dh72": P.small(b=2, l=198, d=104, n_a=3, d_h=72, m=6, c=2, k_a=2, n_m=2, d_e=88, k_m=1, dtype=BF),
     "odd_dh120": P.small(b=2, l=130, d=136, n_a=2, d_h=120, m=2, c=1, k_a=1, n_m=2, d_e=136, k_m=2, dtype=BF),
+    # units of 4096 keys (the last whose padding flags fit LDS), one patch more, and a last key tile of 8
+    "flags_4096": P.small(b=1, l=8192, d=64, n_a=2, d_h=64, m=64, c=32, k_a=1, n_m=2, d_e=64, k_m=1, dtype=BF),
+    "flags_4224": P.small(b=1, l=8192, d=64, n_a=2, d_h=64, m=64, c=33, k_a=1, n_m=2, d_e=64, k_m=1, dtype=BF),
+    "flags_tail": P.small(b=2, l=272, d=64, n_a=2, d_h=128, m=2, c=1, k_a=1, n_m=2, d_e=64, k_m=1, dtype=BF),
     # enough 128-row tiles for the large-tile choice, rows and columns 8 past two tiles
     "odd_big": P.small(b=32, l=264, d=136, n_a=2, d_h=16, m=8, c=8, k_a=2, n_m=2, d_e=136, k_m=2, dtype=BF),
     # fp32: the same, and every launch shape of the fp32 attention (1 or 2 query blocks, 1 or 2 key splits)
