@@ -47,20 +47,6 @@ __host__ __device__ constexpr int largest_divisor_upto(int n, int cap)
     return b;
 }
 
-// Per-column factors of a tile, one per 8-column group, fetched by the whole workgroup before the
-// K loop (the lookups behind col_scale are dependent global loads: taken per column group inside
-// the epilogue they would serialise their latency).  The caller's next barrier publishes them.
-template <typename P, int BN>
-__device__ __forceinline__ void fill_col_scale(const P &p, float *coltab, int g, int n0, int N, int tid, int nthreads)
-{
-    if constexpr (P::kColScale) {
-        for (int c = tid; c < BN / 8; c += nthreads) {
-            const int col = n0 + c * 8;
-            coltab[c] = p.col_scale(g, col < N ? col : 0);
-        }
-    }
-}
-
 // Epilogue of one wave.  acc is the transposed-product accumulator of a TM x TN grid of 32x32
 // tiles: register q of lane (lr, lh) in tile (i, j) is output row i*32 + lr, column
 // j*32 + (q/4)*8 + lh*4 + q%4 of the wave tile.  The wave stages its tile in LDS (stage: WM rows

@@ -108,7 +108,7 @@ template <typename T> struct SmhaDoProblem {
 //   accB^T [d_h x own] += TB^T P^T         (KV only: dV = dO^T-contraction)
 // with (TA, TB, fa, fb) = (k, v, q, dO) for KV = false and (q, dO, k, v) for KV = true.  q arrives
 // scaled by log2(e)/sqrt(d_h) (base-2 softmax), so dK = ln 2 * accA and dQ = accA / sqrt(d_h).
-// P^T and dS^T, rounded to bf16 in place, are the B operands of the second products; the A
+// P^T and dS^T, as (hi, lo) bf16 pairs made in place, are the B operands of the second products; the A
 // operands come out of the [row][d_h] LDS tiles through the transposing read.  Outputs go to the
 // [dq | dk | dv] buffer, token-major: the left operand of the d_x contraction and of the weight gradients.
 // KS = 2: two groups of NW waves own the same rows and take the streamed tiles in turn, each with LDS tiles of its own;
