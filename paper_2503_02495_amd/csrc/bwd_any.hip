@@ -82,6 +82,104 @@ template <typename T, bool NK> struct UomeBwdProj : PlainEpilogue {
     __device__ void put4_f32(int g, int r, int nn, float4 v) const { put4(g, r, nn, v); }
 };
 
+// dH again, with the tile of Z in the accumulators beside it: H = w SiLU(Z), dZ = w dH SiLU'(Z) (operand layout [b, l, k,
+// parts, d_e]) and the sums of dH SiLU(Z) for the gate gradient, one per wave's rows and 8 columns (a wave's 32 columns may
+// belong to several experts, 8 never do).  Neither Z nor dH reaches memory: 8 bytes written per element instead of
+// 8 written, 8 read and 8 written (uome_bwd_any_mid): 128 x 196 x 384 x 768 in bf16 34.9 + 42.9 + 56.9 -> 100.7 us, bound by the
+// epilogue's arithmetic (exact exponential and division) and its stores; with 8-byte stores straight from the
+// accumulators, 16 bytes of a row at a time, the vit layer's forward + backward gained 11 us instead of 34.
+template <typename T> struct UomeBwdDhPair : UomeBwdProj<T, true> {
+    static constexpr bool kPairOut = true, kColScale = true;
+    const float *expert_gate;   // NULL: weight 1
+    T *h, *dz;
+    float *gpart;               // [b, k, gchunks], gchunks = row blocks * d_e / 8
+    int gchunks;
+    __device__ float col_scale(int g, int nn) const
+    {
+        return expert_gate ? expert_gate[(size_t)g * this->n + clampi(this->expert_idx[g * this->kact + nn / this->d_e], this->n)] : 1.0f;
+    }
+    template <int TM, int TN, int SPITCH>
+    __device__ void pair_out(f32x16_t (&acc)[TM][TN], f32x16_t *z, uint16_t (*stage)[SPITCH], const float *colw, int g, int grow0, int gcol0, int M, int N,
+                             int lane) const
+    {
+        constexpr int PARTS = parts_of<T>::value;
+        const int lr = lane & 31, lh = lane >> 5, d_e = this->d_e;
+        auto at = [&](int grow, int col) {   // operand layout, first part
+            const int s = col / d_e;
+            return (((size_t)g * this->l + grow) * this->kact + s) * PARTS * d_e + (col - s * d_e);
+        };
+        // in place: z becomes H, the accumulators dZ
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int c8 = gcol0 + j * 32 + q * 8;   // uniform over the wave
+                if (c8 >= N) continue;
+                const float w = colw[j * 4 + q];
+                float part = 0.f;
+#pragma unroll
+                for (int i = 0; i < TM; ++i) {
+                    const int grow = grow0 + i * 32 + lr;
+                    float ps = 0.f;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float zv = z[i * TN + j][q * 4 + e], dv = acc[i][j][q * 4 + e];
+                        const float sig = 1.0f / (1.0f + expf(-zv)), v = zv * sig;
+                        ps = fmaf(dv, v, ps);
+                        z[i * TN + j][q * 4 + e] = v * w;
+                        acc[i][j][q * 4 + e] = dv * w * (sig * (1.0f + zv * (1.0f - sig)));
+                    }
+                    if (grow < M) part += ps;
+                }
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) part += __shfl_xor(part, off, 64);
+                if (lane == 0 && grow0 < M) {
+                    const int s = c8 / d_e;
+                    gpart[((size_t)g * this->kact + s) * gchunks + (size_t)(grow0 / (TM * 32)) * (d_e / 8) + (c8 - s * d_e) / 8] = part;
+                }
+            }
+        if constexpr (PARTS == 1) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) {
+                        const int grow = grow0 + i * 32 + lr, col = gcol0 + j * 32 + q * 8 + lh * 4;
+                        if (grow >= M || col >= N) continue;
+                        const f32x16_t &hv = z[i * TN + j], &gv = acc[i][j];
+                        *reinterpret_cast<float4 *>(h + at(grow, col)) = make_float4(hv[q * 4], hv[q * 4 + 1], hv[q * 4 + 2], hv[q * 4 + 3]);
+                        *reinterpret_cast<float4 *>(dz + at(grow, col)) = make_float4(gv[q * 4], gv[q * 4 + 1], gv[q * 4 + 2], gv[q * 4 + 3]);
+                    }
+        } else {
+            auto plane = [&](T *dst, auto value, bool low) {
+                stage_plane<TM, TN, SPITCH>(
+                    stage, lane,
+                    [&](int i, int j, int q) {
+                        const f32x16_t &v = value(i, j);
+                        uint32_t o[2];
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) {
+                            const float a = v[q * 4 + 2 * e], b = v[q * 4 + 2 * e + 1];
+                            o[e] = pack2_bf16(a, b);
+                            if (low) o[e] = pack2_bf16(a - __uint_as_float(o[e] << 16), b - __uint_as_float(o[e] & 0xFFFF0000u));
+                        }
+                        return make_uint2(o[0], o[1]);
+                    },
+                    [&](int row, int col, uint4 piece) {
+                        if (grow0 + row < M && gcol0 + col < N) store16<false>(dst + at(grow0 + row, gcol0 + col) + (low ? d_e : 0), piece);
+                    });
+            };
+            auto hv = [&](int i, int j) -> const f32x16_t & { return z[i * TN + j]; };
+            auto gv = [&](int i, int j) -> const f32x16_t & { return acc[i][j]; };
+            plane(h, hv, false);
+            plane(h, hv, true);
+            plane(dz, gv, false);
+            plane(dz, gv, true);
+        }
+    }
+};
+
 // d_u = (d_out) + dZ W1_b^T: group = sample, M = l, N = d, K segments = (slot, part) of d_e; A^I_i [d, d_e] is [n][k]
 template <typename T> struct UomeBwdDu : PlainEpilogue {
     typedef typename storage_elem<T>::type Elem;
@@ -168,7 +266,7 @@ template <typename T> struct UomeBwdWgrad : PlainEpilogue {
     __device__ void put4_f32(int g, int r, int nn, float4 v) const { put4(g, r, nn, v); }
 };
 
-// Elementwise middle: H = w SiLU(Z) into `h`, dZ = w dH SiLU'(Z) into `dz` (operand layout [b, l, k, parts, d_e]) and
+// Where Z and dH are formed by two launches.  Elementwise middle: H = w SiLU(Z) into `h`, dZ = w dH SiLU'(Z) into `dz` (operand layout [b, l, k, parts, d_e]) and
 // the slot's partial sums of dH SiLU(Z).  Block = (chunk of tokens, slot, sample); a group of `lpr` lanes of one
 // wave takes a (token, slot) row of d_e values in blocks of 4*8*lpr columns: a row of at most one block (d_e <= 2048)
 // is read by its lanes before they write it, so it may be written in place (h == z, dz == dh: an fp32 value and a
@@ -234,19 +332,39 @@ template <typename T> hipError_t uome_backward_any(const UomeBwdArgs &a, hipStre
     UomeBwdProj<T, false> zp;
     zp.left = u; zp.w = a_in; zp.expert_idx = a.expert_idx; zp.out = static_cast<float *>(a.z);
     zp.l = a.l; zp.d = a.d; zp.n = a.n; zp.kact = a.k; zp.d_e = a.d_e;
-    if ((err = launch_gemm_tail<0>(zp, a.b, a.l, W, st)) != hipSuccess) return err;
-    UomeBwdProj<T, true> hp;
+    UomeBwdDhPair<T> hp;
     hp.left = d_out; hp.w = a_out; hp.expert_idx = a.expert_idx; hp.out = static_cast<float *>(a.dh);
     hp.l = a.l; hp.d = a.d; hp.n = a.n; hp.kact = a.k; hp.d_e = a.d_e;
-    if ((err = launch_gemm_tail<GEMM_B_NK>(hp, a.b, a.l, W, st)) != hipSuccess) return err;
 
     T *h = static_cast<T *>(a.h_op), *dz = static_cast<T *>(a.dz_op);
-    int lpr = 2;
-    while (lpr < 64 && lpr * 4 < a.d_e) lpr *= 2;
-    const int per_chunk = (a.l + a.gchunks - 1) / a.gchunks;
-    hipLaunchKernelGGL((uome_bwd_any_mid<T>), dim3(a.gchunks, a.k, a.b), dim3(256), 0, st, a, h, dz, lpr, per_chunk);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-    if (a.d_gate && (err = launch_uome_gate_grad(a, st)) != hipSuccess) return err;
+    UomeBwdArgs ga = a;   // for the gate gradient
+    constexpr bool F32 = std::is_same<T, float>::value;
+    constexpr int FZ = GEMM_TAIL, FH = GEMM_TAIL | GEMM_B_NK;
+    const bool large = a.l > 64 && (long)a.b * ((a.l + 127) / 128) * ((W + 127) / 128) >= 256;
+    // one launch for Z, dH and what becomes of them, where tiles of 64 rows and more are the choice anyway and the gate
+    // gradient's sums fit the room they have (a wave's rows: 64 of the large tiles, 32 of the small ones)
+    const long row_blocks = large ? (a.l + 63) / 64 : (a.l + 31) / 32;
+    const long sums = row_blocks * (a.d_e / 8), room = (long)2 * a.n * a.splits * a.d * a.d_e / ((long)a.b * a.k);
+    if (a.l > 32 && sums <= room) {
+        hp.expert_gate = (a.flags & F_GATE_EXPERT) ? a.expert_gate : nullptr;
+        hp.h = h; hp.dz = dz; hp.gpart = a.gpart; hp.gchunks = ga.gchunks = (int)sums;
+        if constexpr (F32)
+            err = large ? launch_gemm_dma_dual<FZ, FH, 128, 128, 16, 2, 2, 3, 2>(zp, hp, a.b, a.l, W, st)
+                        : launch_gemm_dma_dual<FZ, FH, 64, 64, 32, 2, 2, 3, 2>(zp, hp, a.b, a.l, W, st);
+        else
+            err = large ? launch_gemm_dma_dual<FZ, FH, 128, 128, 32, 2, 4, 3, 4>(zp, hp, a.b, a.l, W, st)
+                        : launch_gemm_dma_dual<FZ, FH, 64, 128, 32, 2, 2, 4, 2>(zp, hp, a.b, a.l, W, st);
+        if (err != hipSuccess) return err;
+    } else {
+        if ((err = launch_gemm_tail<0>(zp, a.b, a.l, W, st)) != hipSuccess) return err;
+        if ((err = launch_gemm_tail<GEMM_B_NK>(static_cast<const UomeBwdProj<T, true> &>(hp), a.b, a.l, W, st)) != hipSuccess) return err;
+        int lpr = 2;
+        while (lpr < 64 && lpr * 4 < a.d_e) lpr *= 2;
+        const int per_chunk = (a.l + a.gchunks - 1) / a.gchunks;
+        hipLaunchKernelGGL((uome_bwd_any_mid<T>), dim3(a.gchunks, a.k, a.b), dim3(256), 0, st, a, h, dz, lpr, per_chunk);
+        if ((err = hipGetLastError()) != hipSuccess) return err;
+    }
+    if (a.d_gate && (err = launch_uome_gate_grad(ga, st)) != hipSuccess) return err;
 
     UomeBwdDu<T> up;
     up.dz = dz; up.a_in = a_in; up.d_out = d_out; up.expert_idx = a.expert_idx; up.d_u = static_cast<T *>(a.d_u);

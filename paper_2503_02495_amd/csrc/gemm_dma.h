@@ -132,9 +132,11 @@ template <typename P, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAG
     static constexpr int BYTES = OPER > EPI ? OPER : EPI, SEGS = max_segments<P>::value, COLS = BN / 8;
 };
 
-// One workgroup's tile; `block` is its id within the launch (or within its part of a paired launch).
-template <typename P, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int FLAGS>
-__device__ __forceinline__ void gemm_dma_tile(const P &p, const TileGrid &tg, const int block, unsigned char *lds_raw, uint32_t *segtab, float *coltab)
+// One workgroup's tile; `block` is its id within the launch (or within its part of a paired launch).  KEEP: the accumulators
+// go to `first` [TM*TN] and nothing is written; a problem with pair_out gets them beside its own (see gemm_dma_dual_kernel).
+template <typename P, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int FLAGS, bool KEEP = false>
+__device__ __forceinline__ void gemm_dma_tile(const P &p, const TileGrid &tg, const int block, unsigned char *lds_raw, uint32_t *segtab, float *coltab,
+                                              f32x16_t *first = nullptr)
 {
     typedef typename elem_of<P>::type E;
     constexpr bool F32 = std::is_same<E, float>::value;
@@ -449,7 +451,15 @@ __device__ __forceinline__ void gemm_dma_tile(const P &p, const TileGrid &tg, co
     }
     __syncthreads();  // every wave has finished reading operands: LDS is free for the epilogue
 
-    if constexpr (F32) {
+    if constexpr (KEEP) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) first[i * TN + j] = acc[i][j];
+    } else if constexpr (takes_pair<P>::value) {
+        uint16_t(*stage)[SPITCH] = reinterpret_cast<uint16_t(*)[SPITCH]>(lds_raw) + (size_t)wave * WM;   // (not there in fp32)
+        p.template pair_out<TM, TN, SPITCH>(acc, first, stage, coltab + (wn0 >> 3), g, m0 + wm0, n0 + wn0, M, N, lane);
+    } else if constexpr (F32) {
         wave_epilogue_f32<P, TM, TN>(p, acc, coltab, rs, g, m0 + wm0, n0 + wn0, wn0, M, N, lane);
     } else if constexpr (takes_acc<P>::value) {
         p.template acc_out<TM, TN>(acc, rs, g, m0 + wm0, n0 + wn0, M, N, lane);
@@ -515,6 +525,31 @@ static hipError_t launch_gemm_dma_pair(const typename A::P &pa, int ga, int ra, 
     if ((err = make_tile_grid<A::BM, A::BN>(ta, ga, ra, ca)) != hipSuccess) return err;
     if ((err = make_tile_grid<B::BM, B::BN>(tb, gb, rb, cb)) != hipSuccess) return err;
     hipLaunchKernelGGL((gemm_dma_pair_kernel<A, B, OCC>), dim3((ta.per_xcd + tb.per_xcd) * 8), dim3(A::THREADS), 0, st, pa, ta, pb, tb);
+    return hipGetLastError();
+}
+
+// Two contractions of the same rows and columns in one workgroup, the first one's tile left in the accumulators for the
+// second one's epilogue: for a pair whose results meet element by element and are not needed by themselves.
+template <typename PA, int FA, typename PB, int FB, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int OCC>
+__global__ __launch_bounds__(WAVES_M *WAVES_N * 64, OCC) void gemm_dma_dual_kernel(PA pa, PB pb, TileGrid tg)
+{
+    typedef GemmLds<PB, BM, BN, BK, WAVES_M, WAVES_N, STAGES> L;
+    static_assert(!PA::kPrepare && !PB::kPrepare && GemmLds<PA, BM, BN, BK, WAVES_M, WAVES_N, STAGES>::OPER <= L::BYTES, "one LDS layout");
+    __shared__ __align__(1024) unsigned char lds_raw[L::BYTES];
+    __shared__ uint32_t segtab[max_segments<PA>::value > L::SEGS ? max_segments<PA>::value : L::SEGS];
+    __shared__ float coltab[L::COLS];
+    f32x16_t first[(BM / WAVES_M / 32) * (BN / WAVES_N / 32)];
+    gemm_dma_tile<PA, BM, BN, BK, WAVES_M, WAVES_N, STAGES, FA, true>(pa, tg, blockIdx.x, lds_raw, segtab, coltab, first);
+    gemm_dma_tile<PB, BM, BN, BK, WAVES_M, WAVES_N, STAGES, FB>(pb, tg, blockIdx.x, lds_raw, segtab, coltab, first);
+}
+template <int FA, int FB, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int OCC, typename PA, typename PB>
+static hipError_t launch_gemm_dma_dual(const PA &pa, const PB &pb, int groups, int rows, int ncols, hipStream_t st)
+{
+    TileGrid tg;
+    const hipError_t err = make_tile_grid<BM, BN>(tg, groups, rows, ncols);
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL((gemm_dma_dual_kernel<PA, FA, PB, FB, BM, BN, BK, WAVES_M, WAVES_N, STAGES, OCC>), dim3(tg.per_xcd * 8),
+                       dim3(WAVES_M * WAVES_N * 64), 0, st, pa, pb, tg);
     return hipGetLastError();
 }
 
@@ -598,6 +633,27 @@ static hipError_t launch_gemm_dma_auto(const P &p, int groups, int rows, int nco
     }
     if (tiles(64, 128) < 160) return launch_gemm_dma<P, 64, 64, 64, 2, 2, 3, 3, FLAGS>(p, groups, rows, ncols, st);
     return launch_gemm_dma<P, 64, 128, 64, 2, 4, 3, 4, FLAGS>(p, groups, rows, ncols, st);
+}
+
+// The same choice for two contractions of one tile (gemm_dma_dual_kernel), K-contiguous or [k][n] right operands; false: the
+// tiles would be the 256-column ones, whose accumulators leave no room for a second set at two workgroups a compute unit.
+static bool gemm_dma_dual_fits(int groups, int rows, int ncols, long kdim, int kseg)
+{
+    const auto tiles = [&](int bm, int bn) { return (long)groups * ((rows + bm - 1) / bm) * ((ncols + bn - 1) / bn); };
+    const bool wide = ncols % 256 == 0 || ncols >= 1024;
+    return !(rows > 128 && wide && kseg % 64 == 0 && kdim >= 768 && tiles(256, 256) >= 256) && !(rows > 64 && wide && tiles(128, 256) >= 384);
+}
+template <int FA, int FB, typename PA, typename PB>
+static hipError_t launch_gemm_dma_dual_auto(const PA &pa, const PB &pb, int groups, int rows, int ncols, int kseg, hipStream_t st)
+{
+    const auto tiles = [&](int bm, int bn) { return (long)groups * ((rows + bm - 1) / bm) * ((ncols + bn - 1) / bn); };
+    const bool k64 = kseg % 64 == 0;
+    const long t128 = tiles(128, 128);
+    if (rows > 64 && k64 && t128 > 256 && t128 <= 512) return launch_gemm_dma_dual<FA, FB, 128, 128, 64, 2, 2, 2, 2>(pa, pb, groups, rows, ncols, st);
+    if (rows > 64 && t128 > 256) return launch_gemm_dma_dual<FA, FB, 128, 128, 32, 2, 4, 3, 4>(pa, pb, groups, rows, ncols, st);
+    if (!k64) return launch_gemm_dma_dual<FA, FB, 64, 128, 32, 2, 4, 4, 4>(pa, pb, groups, rows, ncols, st);
+    if (tiles(64, 128) < 160) return launch_gemm_dma_dual<FA, FB, 64, 64, 64, 2, 2, 3, 3>(pa, pb, groups, rows, ncols, st);
+    return launch_gemm_dma_dual<FA, FB, 64, 128, 64, 2, 4, 3, 4>(pa, pb, groups, rows, ncols, st);
 }
 
 }  // namespace uoe

@@ -99,6 +99,9 @@ template <typename P> struct streams_once<P, std::void_t<decltype(std::declval<P
 // problems that take the accumulators themselves: acc_out<TM, TN>(acc, rs, g, first row, first column, M, N, lane)
 template <typename P, typename = void> struct takes_acc : std::false_type {};
 template <typename P> struct takes_acc<P, std::void_t<decltype(P::kAccOut)>> : std::true_type {};
+// problems that take the tile of another contraction beside their own: pair_out<TM, TN, SPITCH>(acc, first, stage, column factors, g, ...)
+template <typename P, typename = void> struct takes_pair : std::false_type {};
+template <typename P> struct takes_pair<P, std::void_t<decltype(P::kPairOut)>> : std::true_type {};
 // problems with a second half of their own: write_out<TM, TN, SPITCH>(stage, coltab + first 8-column group, rs, ...)
 template <typename P, typename = void> struct writes_itself : std::false_type {};
 template <typename P> struct writes_itself<P, std::void_t<decltype(P::kWriteOut)>> : std::true_type {};
@@ -139,6 +142,29 @@ __device__ __forceinline__ void wave_write_out(const P &p, uint16_t (*stage)[SPI
             }
         }
     }
+}
+
+// One 16-bit plane of a wave tile from the accumulators' layout to rows, through the wave's staging tile: words(i, j, q) are
+// the lane's 4 values of row i*32 + lr, columns j*32 + q*8 + lh*4; put(row, first column, 8 values) takes 16-byte pieces, whose
+// neighbouring lanes complete 64 bytes and more of a row (straight from the accumulators two lanes complete 16).
+template <int TM, int TN, int SPITCH, typename Words, typename Put>
+__device__ __forceinline__ void stage_plane(uint16_t (*stage)[SPITCH], int lane, Words words, Put put)
+{
+    constexpr int WC = TN * 4, NPIECE = TM * 32 * WC / 64;
+    const int lr = lane & 31, lh = lane >> 5;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) *reinterpret_cast<uint2 *>(&stage[i * 32 + lr][j * 32 + q * 8 + lh * 4]) = words(i, j, q);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int t = 0; t < NPIECE; ++t) {
+        const int c = lane + t * 64, row = c / WC, col = c % WC * 8;
+        put(row, col, *reinterpret_cast<const uint4 *>(&stage[row][col]));
+    }
+    __builtin_amdgcn_wave_barrier();
 }
 
 template <typename P, int TM, int TN, int SPITCH>

@@ -78,6 +78,15 @@ UOME_BWD = {
     "ub_ranges": P.small(b=1, l=1100, d=40, n_a=1, d_h=8, m=1, c=1, k_a=1, n_m=1, d_e=24, k_m=1, dtype=BF),
     # both fp32 tile sizes
     "ub_f32_big": P.small(b=32, l=264, d=136, n_a=2, d_h=8, m=1, c=1, k_a=1, n_m=2, d_e=136, k_m=2),
+    # Z and dH in one launch: large tiles with waves that straddle experts; no room for the gate's sums: two launches
+    "ub_dual_large": P.small(b=44, l=150, d=40, n_a=1, d_h=8, m=1, c=1, k_a=1, n_m=3, d_e=88, k_m=3, dtype=BF),
+    "ub_dual_no_room": P.small(b=128, l=1000, d=8, n_a=1, d_h=8, m=1, c=1, k_a=1, n_m=1, d_e=8, k_m=1, dtype=BF),
+    # the same on the 32-grid, every tile shape, K-steps of 64 and of 32, rows and columns that end inside a tile
+    "ub_dual_128x64": P.small(b=44, l=224, d=64, n_a=1, d_h=32, m=1, c=1, k_a=1, n_m=3, d_e=160, k_m=2, dtype=BF),
+    "ub_dual_128x32": P.small(b=44, l=224, d=96, n_a=1, d_h=32, m=1, c=1, k_a=1, n_m=3, d_e=160, k_m=2, dtype=BF),
+    "ub_dual_32": P.small(b=2, l=96, d=32, n_a=1, d_h=32, m=1, c=1, k_a=1, n_m=3, d_e=96, k_m=2, dtype=BF),
+    "ub_dual_64x64": P.small(b=2, l=96, d=64, n_a=1, d_h=32, m=1, c=1, k_a=1, n_m=3, d_e=96, k_m=2, dtype=BF),
+    "ub_dual_64x128": P.small(b=40, l=224, d=64, n_a=1, d_h=32, m=1, c=1, k_a=1, n_m=3, d_e=96, k_m=2, dtype=BF),
 }
 P.BWD_CONFIGS.update(UOME_BWD)
 SMHA_BWD = {
