@@ -71,7 +71,7 @@ SmhaWs smha_ws(const uoe_block_desc *d)
 {
     SmhaWs w;
     const size_t l_a = (((size_t)d->c * (d->l / d->m)) + 7) & ~(size_t)7;  // v may be stored transposed, rows padded to 8
-    const size_t one = up((size_t)d->b * d->k * l_a * smha_padded_width(d->width, d->dtype == UOE_BF16) * elem_size(d->dtype));
+    const size_t one = up((size_t)d->b * d->k * l_a * d->width * elem_size(d->dtype));
     size_t off = 0;
     w.q = off; off += one;
     w.k = off; off += one;

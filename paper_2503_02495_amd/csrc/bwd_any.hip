@@ -859,7 +859,7 @@ template <typename T> hipError_t smha_backward_any(const SmhaBwdArgs &a, hipStre
     qp.q = static_cast<T *>(f.q); qp.k = static_cast<T *>(f.kk); qp.v = static_cast<T *>(f.v);
     qp.q32 = static_cast<float *>(f.q); qp.q32_plane = static_cast<float *>(f.kk) - static_cast<float *>(f.q);
     qp.l = f.l; qp.d = f.d; qp.n = f.n; qp.kact = f.k; qp.m = f.m; qp.c = f.c;
-    qp.l_p = l_p; qp.l_a = l_a; qp.d_h = qp.d_hp = dh; qp.q_scale = 1.0f; qp.nout = 3;
+    qp.l_p = l_p; qp.l_a = l_a; qp.d_h = dh; qp.q_scale = 1.0f; qp.nout = 3;
     if (!a.kept) {
         if ((err = launch_gemm_tail<0>(qp, units, l_a, 3 * dh, st)) != hipSuccess) return err;
         if ((err = launch_rope_f32(f, st)) != hipSuccess) return err;

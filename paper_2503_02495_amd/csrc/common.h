@@ -145,8 +145,7 @@ struct SmhaArgs {
     int rope_dim;                             // rotary dims at the end of a head (Eq. 32), 0 = none
     const unsigned char *pad_mask;            // [b,l] 1 = token, 0 = padding (Eq. 41), or NULL
     // workspace
-    void *q, *kk, *v, *o, *o_lo;              // [b*k, l_a, d_hp] each, storage dtype (o_lo: low part of o, MFMA path)
-    int d_hp;                                 // set by the launcher: smha_padded_width()
+    void *q, *kk, *v, *o, *o_lo;              // [b*k, l_a, d_h] each, storage dtype (o_lo: low part of o, bf16 storage)
     float *lse;                               // [b*k, l_a] or NULL: base-2 log-sum-exp of each query's scaled logits
                                               // (MFMA attention only; kept for the backward pass)
     // also written when not NULL (bf16 MFMA path): a bf16 copy of v and the attention output without its gate weight as a
@@ -284,9 +283,6 @@ hipError_t launch_uome_backward_any(const UomeBwdArgs &a, bool bf16, hipStream_t
 hipError_t launch_smha_backward_any(const SmhaBwdArgs &a, bool bf16, hipStream_t st);
 constexpr int BWD_ANY_SEGMENTS = 1024;        // (unit, pick) entries one part of an expert's weight gradient holds
 hipError_t launch_route_backward(const RouteBwdArgs &a, bool bf16, hipStream_t st);
-// elements per row of q, k, v and o: the bf16 attention kernels take heads of 32, 64 or 128, other widths are padded
-// with zero columns
-int smha_padded_width(int d_h, bool bf16);
 int smha_backward_splits(int b, int n, int k, int c);
 int uome_backward_gate_chunks(int l, int d_e);
 int uome_backward_splits(int b, int l, int d, int n, int k, int d_e);

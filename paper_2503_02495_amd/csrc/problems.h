@@ -82,8 +82,6 @@ template <typename T, bool F32 = false> struct QkvProblem {
         *reinterpret_cast<float4 *>(q32 + which * q32_plane + ((size_t)g * l_a + r) * d_h + (nn - which * d_h)) = val;
     }
     int l, d, n, kact, m, c, l_p, l_a, d_h;
-    int d_hp;       // row length of q, k and v: d_h, or d_h padded to what the attention kernel takes (the columns behind
-                    // d_h are written as zeros)
     float q_scale;  // folded into q on the way out (1 for the plain layout)
     int nout;       // 3: q, k and v; 1: the first projection only (N = d_h)
     // bf16 rows: the last rope_dim dims of q and k rotated by the row's position in the compacted sequence (Eq. 32),
@@ -92,33 +90,33 @@ template <typename T, bool F32 = false> struct QkvProblem {
     __device__ bool rotates(int col8) const
     {
         if (rope_dim <= 0) return false;
-        const int which = col8 / d_hp, dh = col8 - which * d_hp;
-        return which < 2 && dh + 8 > d_h - rope_dim && dh < d_h;
+        const int which = col8 / d_h, dh = col8 - which * d_h;
+        return which < 2 && dh + 8 > d_h - rope_dim;
     }
     __device__ void rotate(int r, int col, float &e0, float &e1, float &e2, float &e3) const
     {
-        const int dh = col % d_hp, first = d_h - rope_dim;
+        const int dh = col % d_h, first = d_h - rope_dim;
         float sn, cs, t;
-        if (dh >= first && dh < d_h) {
+        if (dh >= first) {
             rope_sincos((float)r, rope_theta(dh - first, rope_dim), sn, cs);
             t = e0; e0 = t * cs - e1 * sn; e1 = t * sn + e1 * cs;
         }
-        if (dh + 2 >= first && dh + 2 < d_h) {
+        if (dh + 2 >= first) {
             rope_sincos((float)r, rope_theta(dh + 2 - first, rope_dim), sn, cs);
             t = e2; e2 = t * cs - e3 * sn; e3 = t * sn + e3 * cs;
         }
     }
     int v_f16 = 0;  // MFMA engines, bf16 storage: v is written as fp16 (what the attention kernel's P V product takes)
-    __device__ bool f16_col(int nn) const { return v_f16 && nn >= 2 * d_hp; }
-    T *v_copy = nullptr;   // with v_f16: v in bf16 as well (the backward pass's operand), no padded heads
+    __device__ bool f16_col(int nn) const { return v_f16 && nn >= 2 * d_h; }
+    T *v_copy = nullptr;   // with v_f16: v in bf16 as well (the backward pass's operand)
     __device__ void put4_copy(int g, int r, int nn, uint2 piece) const
     {
-        *reinterpret_cast<uint2 *>(v_copy + ((size_t)g * l_a + r) * d_hp + (nn - 2 * d_hp)) = piece;
+        *reinterpret_cast<uint2 *>(v_copy + ((size_t)g * l_a + r) * d_h + (nn - 2 * d_h)) = piece;
     }
 
     __device__ int rows(int) const { return l_a; }
     __device__ int kdim(int) const { return d; }
-    __device__ int ncols() const { return nout * d_hp; }
+    __device__ int ncols() const { return nout * d_h; }
     __device__ int expert(int g) const { return clampi(expert_idx[g], n); }
     __device__ int token(int g, int r) const
     {
@@ -138,17 +136,16 @@ template <typename T, bool F32 = false> struct QkvProblem {
     {
         const int i = expert(g);
         if (w_nk) return wq + ((size_t)i * d_h + nn) * d;
-        const int which = nn / d_hp, at = nn - which * d_hp, col = at < d_h ? at : 0;   // behind d_h: any valid piece, its products are dropped
+        const int which = nn / d_h;
         const T *w = which == 0 ? wq : (which == 1 ? wk : wv);
-        return w + (size_t)i * d * d_h + col;
+        return w + (size_t)i * d * d_h + (nn - which * d_h);
     }
     __device__ float epi_f32(float val, float scale) const { return val * scale; }
     __device__ void put4(int g, int r, int nn, float4 val) const
     {
-        const int which = nn / d_hp, col = nn - which * d_hp;
+        const int which = nn / d_h;
         T *o = which == 0 ? q : (which == 1 ? k : v);
-        if (col >= d_h) val = make_float4(0.f, 0.f, 0.f, 0.f);
-        *reinterpret_cast<float4 *>(o + ((size_t)g * l_a + r) * d_hp + col) = val;
+        *reinterpret_cast<float4 *>(o + ((size_t)g * l_a + r) * d_h + (nn - which * d_h)) = val;
     }
     // pipelined engine: K is one segment, rows and columns are resolved once before the loop
     __device__ uint32_t seg_ctx(int, int) const { return 0; }
@@ -158,16 +155,15 @@ template <typename T, bool F32 = false> struct QkvProblem {
     static constexpr bool kPrepare = false;
     static constexpr bool kRowScale = false;
     static constexpr bool kColScale = true;
-    __device__ float col_scale(int, int nn) const { return nn < d_hp ? q_scale : 1.0f; }
+    __device__ float col_scale(int, int nn) const { return nn < d_h ? q_scale : 1.0f; }
     __device__ float epi(float val, float scale) const { return val * scale; }
     __device__ bool has_residual() const { return false; }
     __device__ uint4 res8(int, int, int) const { return make_uint4(0, 0, 0, 0); }
     __device__ void put8(int g, int r, int nn, uint4 piece) const
     {
-        const int which = nn / d_hp, col = nn - which * d_hp;
+        const int which = nn / d_h;
         T *o = which == 0 ? q : (which == 1 ? k : v);
-        if (col >= d_h) piece = make_uint4(0, 0, 0, 0);
-        *reinterpret_cast<uint4 *>(o + ((size_t)g * l_a + r) * d_hp + col) = piece;
+        *reinterpret_cast<uint4 *>(o + ((size_t)g * l_a + r) * d_h + (nn - which * d_h)) = piece;
     }
 };
 
@@ -188,7 +184,7 @@ template <typename T> struct OutProjProblem {
     const int32_t *expert_idx, *patch_idx;
     T *out;
     int l, d, n, kact, m, c, l_p, l_a, d_h;
-    int o_row;  // elements between rows of o (d_h, or more when its rows are padded)
+    int o_row;  // elements between rows of o (d_h, or more where they hold other columns too)
     int parts;  // 1: o only; 2: o is a (hi, lo) pair of buffers, contracted as [hi | lo] x [W^o ; W^o]
     uint32_t flags;
     int w_nk = 0;   // wo is [n, d, d_h] (engine flag GEMM_B_NK)

@@ -14,11 +14,11 @@
 
 namespace uoe {
 
-// Partial RoPE of Eq. 32 of the fp32 attention path, in place on the q and k workspaces (the bf16 projections rotate
-// in their epilogue): the last rope_dim dims of a head are
+// Partial RoPE of Eq. 32 for fp32 storage, in place on the q and k workspaces (the projections of bf16 storage rotate in
+// their epilogue): the last rope_dim dims of a head are
 // rotated in adjacent pairs (2i, 2i+1) by position * 10000^(-2i/rope_dim); the position of a row
 // is its index in the unit's compacted sequence.  One thread per (unit row, pair).
-template <typename T> __global__ __launch_bounds__(256) void smha_rope_kernel(SmhaArgs a)
+__global__ __launch_bounds__(256) void smha_rope_kernel(SmhaArgs a)
 {
     const int l_a = a.c * (a.l / a.m), half = a.rope_dim >> 1;
     const long total = (long)a.b * a.k * l_a * half;
@@ -30,28 +30,21 @@ template <typename T> __global__ __launch_bounds__(256) void smha_rope_kernel(Sm
     const float theta = exp2f(-(2.0f * (float)i / (float)a.rope_dim) * 13.287712379549449f);  // log2(10000)
     float sn, cs;
     sincosf((float)r * theta, &sn, &cs);
-    const size_t at = (size_t)row * a.d_hp + (a.d_h - a.rope_dim) + 2 * i;
-    T *q = static_cast<T *>(a.q) + at, *k = static_cast<T *>(a.kk) + at;
-    const float q0 = to_f32(q[0]), q1 = to_f32(q[1]), k0 = to_f32(k[0]), k1 = to_f32(k[1]);
-    q[0] = from_f32<T>(q0 * cs - q1 * sn);
-    q[1] = from_f32<T>(q0 * sn + q1 * cs);
-    k[0] = from_f32<T>(k0 * cs - k1 * sn);
-    k[1] = from_f32<T>(k0 * sn + k1 * cs);
+    const size_t at = (size_t)row * a.d_h + (a.d_h - a.rope_dim) + 2 * i;
+    float *q = static_cast<float *>(a.q) + at, *k = static_cast<float *>(a.kk) + at;
+    const float q0 = q[0], q1 = q[1], k0 = k[0], k1 = k[1];
+    q[0] = q0 * cs - q1 * sn;
+    q[1] = q0 * sn + q1 * cs;
+    k[0] = k0 * cs - k1 * sn;
+    k[1] = k0 * sn + k1 * cs;
 }
 
-template <typename T> static hipError_t launch_rope(const SmhaArgs &a, hipStream_t st)
+hipError_t launch_rope_f32(const SmhaArgs &a, hipStream_t st)
 {
     if (a.rope_dim <= 0) return hipSuccess;
     const long total = (long)a.b * a.k * a.c * (a.l / a.m) * (a.rope_dim >> 1);
-    hipLaunchKernelGGL((smha_rope_kernel<T>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(smha_rope_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, a);
     return hipGetLastError();
-}
-
-hipError_t launch_rope_f32(const SmhaArgs &args, hipStream_t st)
-{
-    SmhaArgs a = args;
-    a.d_hp = a.d_h;
-    return launch_rope<float>(a, st);
 }
 
 // padding flag of key `key` of unit g (Eq. 41: the mask is gathered with the unit's indices)
@@ -62,8 +55,8 @@ __device__ __forceinline__ bool key_is_token(const SmhaArgs &a, int g, int key, 
     return a.pad_mask[(size_t)bb * a.l + p * l_p + key % l_p] != 0;
 }
 
-// Attention with fp32 operands (Eq. 33-34): fp32 storage at any head width (and bf16 units too long for the
-// 32-bit offsets of the bf16 kernels).  One wave owns 32 query rows of one unit and walks key tiles of
+// Attention with fp32 products and fp32 probabilities (Eq. 33-34): fp32 storage, and bf16 storage where the bf16 kernels do
+// not apply (launch_smha), whose q, k and v are widened on the way into LDS and whose o leaves as a (hi, lo) pair.  One wave owns 32 query rows of one unit and walks key tiles of
 // 32, online softmax in base 2.  Both products run on v_mfma_f32_32x32x2_f32: exact fp32 products, and what
 // the vector-ALU kernel before it spent per score, d_h multiply-adds and as many LDS reads for every lane, is
 // one instruction per two keys or head dims for 1024 scores (lm shape in fp32, 32 units of 128 rows, d_h
@@ -247,15 +240,25 @@ __global__ __launch_bounds__(NQ *KSPLIT * 64) void attention_f32_kernel(SmhaArgs
         w *= a.patch_gate[((size_t)bb * a.n + i) * a.m + p];
     }
     const float inv = lsum > 0.f ? w / lsum : 0.f;  // a row with no admissible key contributes nothing
-    T *o = static_cast<T *>(a.o) + ubase + (size_t)qrow * d_h;
+    const size_t row = ubase + (size_t)qrow * d_h;
 #pragma unroll
     for (int td = 0; td < DH / 32; ++td)
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
             const int dh = td * 32 + q4 * 8 + lh * 4;
             if (dh >= d_h) continue;
+            const float v[4] = {oacc[td][q4 * 4] * inv, oacc[td][q4 * 4 + 1] * inv, oacc[td][q4 * 4 + 2] * inv, oacc[td][q4 * 4 + 3] * inv};
+            if constexpr (sizeof(T) == 4) *reinterpret_cast<float4 *>(static_cast<float *>(a.o) + row + dh) = make_float4(v[0], v[1], v[2], v[3]);
+            else {   // hi = bf16(o), lo = bf16(o - hi): the out-projection contracts both
+                uint32_t hi[2], lo[2];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[dh + e] = from_f32<T>(oacc[td][q4 * 4 + e] * inv);
+                for (int e = 0; e < 2; ++e) {
+                    hi[e] = pack2_bf16(v[2 * e], v[2 * e + 1]);
+                    lo[e] = pack2_bf16(v[2 * e] - __uint_as_float(hi[e] << 16), v[2 * e + 1] - __uint_as_float(hi[e] & 0xFFFF0000u));
+                }
+                *reinterpret_cast<uint2 *>(static_cast<bf16_t *>(a.o) + row + dh) = make_uint2(hi[0], hi[1]);
+                *reinterpret_cast<uint2 *>(static_cast<bf16_t *>(a.o_lo) + row + dh) = make_uint2(lo[0], lo[1]);
+            }
         }
 }
 
@@ -871,8 +874,8 @@ template <int DH> static hipError_t launch_attention_mfma_dh(const SmhaArgs &a, 
 
 static hipError_t launch_attention_mfma(const SmhaArgs &a, hipStream_t st)
 {
-    if (a.d_hp == 32) return launch_attention_mfma_dh<32>(a, st);
-    if (a.d_hp == 64) return launch_attention_mfma_dh<64>(a, st);
+    if (a.d_h == 32) return launch_attention_mfma_dh<32>(a, st);
+    if (a.d_h == 64) return launch_attention_mfma_dh<64>(a, st);
     return launch_attention_mfma_dh<128>(a, st);
 }
 
@@ -889,7 +892,7 @@ template <typename T> static QkvProblem<T> make_qkv(const SmhaArgs &a)
     qp.k = static_cast<T *>(a.kk);
     qp.v = static_cast<T *>(a.v);
     qp.l = a.l; qp.d = a.d; qp.n = a.n; qp.kact = a.k; qp.m = a.m; qp.c = a.c;
-    qp.l_p = a.l / a.m; qp.l_a = a.c * qp.l_p; qp.d_h = a.d_h; qp.d_hp = a.d_hp;
+    qp.l_p = a.l / a.m; qp.l_a = a.c * qp.l_p; qp.d_h = a.d_h;
     qp.q_scale = 1.0f;
     qp.nout = 3;
     qp.q32 = nullptr;
@@ -908,22 +911,30 @@ template <typename T> static OutProjProblem<T> make_outproj(const SmhaArgs &a)
     op.patch_idx = a.patch_idx;
     op.out = static_cast<T *>(a.out);
     op.l = a.l; op.d = a.d; op.n = a.n; op.kact = a.k; op.m = a.m; op.c = a.c;
-    op.l_p = a.l / a.m; op.l_a = a.c * op.l_p; op.d_h = a.d_h; op.o_row = a.d_hp; op.flags = a.flags;
+    op.l_p = a.l / a.m; op.l_a = a.c * op.l_p; op.d_h = op.o_row = a.d_h; op.flags = a.flags;
     return op;
 }
 
-// fp32 storage (and bf16 units too long for the bf16 attention kernels): everything on the fp32 matrix instruction
+// fp32 storage, and bf16 storage where the bf16 attention kernels do not apply: any width, attention on the fp32 matrix
+// instruction
 template <typename T> static hipError_t smha_f32(const SmhaArgs &a, hipStream_t st)
 {
+    constexpr bool BF = std::is_same<T, bf16_t>::value;
     const int l_p = a.l / a.m, l_a = a.c * l_p, units = a.b * a.k;
     hipError_t err;
     if (!(a.skip & SMHA_STEP_QKV)) {
-        if ((err = launch_gemm_tail<0>(make_qkv<T>(a), units, l_a, 3 * a.d_hp, st)) != hipSuccess) return err;
-        if ((err = launch_rope<T>(a, st)) != hipSuccess) return err;
+        QkvProblem<T> qp = make_qkv<T>(a);
+        qp.rope_dim = BF ? a.rope_dim : 0;
+        if ((err = launch_gemm_tail<0>(qp, units, l_a, 3 * a.d_h, st)) != hipSuccess) return err;
+        if (!BF && (err = launch_rope_f32(a, st)) != hipSuccess) return err;
     }
     if (!(a.skip & SMHA_STEP_ATTENTION) && (err = launch_attention_f32<T>(a, st)) != hipSuccess) return err;
     if (a.skip & SMHA_STEP_OUT) return hipSuccess;
     OutProjProblem<T> op = make_outproj<T>(a);
+    if (BF) {
+        op.o_lo = static_cast<const T *>(a.o_lo);
+        op.parts = 2;
+    }
     const int groups = a.b * op.set_patch_groups(a.b);
     return launch_gemm_tail<0>(op, groups, op.gp * l_p, a.d, st);
 }
@@ -945,7 +956,7 @@ template <typename OP> static hipError_t launch_outproj_dma(const OP &op, int gr
 }
 
 // projections, rotary embedding and attention of the MFMA path
-static hipError_t smha_mfma_qkv_attention(const SmhaArgs &a, hipStream_t st)
+hipError_t launch_smha_qkv_attention(const SmhaArgs &a, hipStream_t st)
 {
     typedef QkvProblem<bf16_t> QP;
     const int l_p = a.l / a.m, l_a = a.c * l_p, units = a.b * a.k;
@@ -960,12 +971,11 @@ static hipError_t smha_mfma_qkv_attention(const SmhaArgs &a, hipStream_t st)
     // 32 units of 128 rows x 512 x 192 5.9 (32x64 tiles 7.0), 32 of 512 x 256 x 96 5.9 (128x128 8.9), 64 of 256 x 768 x 192 11.6
     // (64x192 13.2), 384 of 56 x 384 x 192 11.9 against 11.7, 32 of 1024 x 1024 x 192 24.2 with 128x192 (64x64 26.5)
     auto projections = [&]() -> hipError_t {
-        const int N = 3 * a.d_hp;
-        if (a.d % 32 != 0) return launch_gemm_tail<0>(qp, units, l_a, N, st);   // K ends inside a K-step
+        const int N = 3 * a.d_h;
         const bool k64 = a.d % 64 == 0;
         const long t64 = (long)units * ((l_a + 63) / 64) * ((N + 63) / 64);
         if (k64 && l_a > 32 && t64 <= 1024) return launch_gemm_dma<QP, 64, 64, 64, 2, 2, 3, 3>(qp, units, l_a, N, st);
-        if (a.d_hp == 64) {
+        if (a.d_h == 64) {
             if (l_a >= 256) return k64 ? launch_gemm_dma<QP, 128, 192, 64, 2, 2, 3>(qp, units, l_a, N, st)
                                        : launch_gemm_dma<QP, 128, 192, 32, 2, 2, 3, 2>(qp, units, l_a, N, st);
             if (l_a > 32) return launch_gemm_dma<QP, 64, 192, 32, 2, 2, 3, 2>(qp, units, l_a, N, st);
@@ -983,27 +993,18 @@ static hipError_t smha_mfma_qkv_attention(const SmhaArgs &a, hipStream_t st)
     return launch_attention_mfma(a, st);
 }
 
-hipError_t launch_smha_qkv_attention(const SmhaArgs &args, hipStream_t st)
-{
-    SmhaArgs a = args;
-    a.d_hp = a.d_h;
-    return smha_mfma_qkv_attention(a, st);
-}
-
-// bf16 storage: q, k, v and o have rows of a.d_hp elements (d_h padded to 32, 64 or 128)
 static hipError_t smha_mfma(const SmhaArgs &a, hipStream_t st)
 {
     typedef OutProjProblem<bf16_t> OP;
     const int l_p = a.l / a.m;
     hipError_t err;
-    if ((err = smha_mfma_qkv_attention(a, st)) != hipSuccess) return err;
+    if ((err = launch_smha_qkv_attention(a, st)) != hipSuccess) return err;
     if (a.skip & SMHA_STEP_OUT) return hipSuccess;
     OP op = make_outproj<bf16_t>(a);
     op.once = stream_once((size_t)a.b * a.l * a.d * sizeof(bf16_t));
     op.o_lo = static_cast<const bf16_t *>(a.o_lo);   // the MFMA attention kernel writes o as a (hi, lo) bf16 pair
     op.parts = 2;
     const int groups = a.b * op.set_patch_groups(a.b);
-    if (a.d_h % 32 != 0) return launch_gemm_tail<0>(op, groups, op.gp * l_p, a.d, st);
     return launch_outproj_dma(op, groups, op.gp * l_p, a.d, st);
 }
 
@@ -1074,16 +1075,15 @@ hipError_t launch_uome_ds(const UomeDsArgs &a, bool bf16, hipStream_t st)
     return bf16 ? uome_ds_tail<bf16_t>(a, st) : uome_ds_tail<float>(a, st);
 }
 
-int smha_padded_width(int d_h, bool bf16) { return !bf16 ? d_h : d_h <= 32 ? 32 : d_h <= 64 ? 64 : 128; }
-
-hipError_t launch_smha(const SmhaArgs &args, bool bf16, hipStream_t st)
+// The bf16 kernels (bf16 products, probabilities and v in fp16) take widths that are multiples of 32, heads of 32, 64 or 128
+// and units whose keys 32-bit element offsets reach.  Everything else runs on fp32 products: padding the other heads
+// into the bf16 kernels is faster (6 x 1000 tokens, d 360, heads of 40: the layer's forward 76 us against 87), but it held their
+// probabilities in 16 bits and v in fp16, where |v| above 65504 is infinite and below 6e-8 zero.
+hipError_t launch_smha(const SmhaArgs &a, bool bf16, hipStream_t st)
 {
-    SmhaArgs a = args;
-    a.d_hp = smha_padded_width(a.d_h, bf16);
     if (!bf16) return smha_f32<float>(a, st);
-    // the bf16 attention kernels address one unit's keys with 32-bit element offsets
-    if ((long)a.c * (a.l / a.m) * a.d_hp < (1L << 31)) return smha_mfma(a, st);
-    a.d_hp = a.d_h;
+    const bool heads = a.d_h == 32 || a.d_h == 64 || a.d_h == 128;
+    if (a.d % 32 == 0 && heads && (long)a.c * (a.l / a.m) * a.d_h < (1L << 31)) return smha_mfma(a, st);
     return smha_f32<bf16_t>(a, st);
 }
 

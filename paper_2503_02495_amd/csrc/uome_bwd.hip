@@ -363,7 +363,7 @@ hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st)
     zp.expert_idx = a.expert_idx; zp.patch_idx = a.patch_idx;
     zp.q = zp.k = zp.v = static_cast<T *>(a.z); zp.q32 = nullptr;
     zp.l = a.l; zp.d = a.d; zp.n = a.n; zp.kact = a.k; zp.m = a.m; zp.c = a.c;
-    zp.l_p = l_p; zp.l_a = l_a; zp.d_h = zp.d_hp = a.d_e; zp.q_scale = 1.0f; zp.nout = 1;
+    zp.l_p = l_p; zp.l_a = l_a; zp.d_h = a.d_e; zp.q_scale = 1.0f; zp.nout = 1;
     if ((err = launch_gemm_dma_auto(zp, units, l_a, a.d_e, a.d, a.d, st)) != hipSuccess) return err;
 
     UomeDsDhProblem<T> hp;      // dH_raw, and dZ, H and the row terms from Z and it
