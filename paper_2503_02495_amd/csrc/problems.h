@@ -320,8 +320,8 @@ template <typename T, int PARTS> struct SmhaDxProblem : OutProjProblem<T> {
 
 // ---------------------------------------------------------------------------------------------
 // UoME Eq. 38: group = sample b; M = l; K = d; N = k*d_e (the sample's active experts side by
-// side); epilogue SiLU and the expert's gate.
-template <typename T, bool RAW = false> struct UomeUpProblem {
+// side); epilogue SiLU and the expert's gate.  EXACT: SiLU by a division also for bf16 storage.
+template <typename T, bool RAW = false, bool EXACT = false> struct UomeUpProblem {
     typedef typename storage_elem<T>::type Elem;
     bool once = false;   // this launch streams its output (and residual) past the caches: see store16, wave_write_out
     const T *u, *a_in;
@@ -361,7 +361,7 @@ template <typename T, bool RAW = false> struct UomeUpProblem {
         if (!expert_gate || raw) return 1.0f;
         return expert_gate[(size_t)g * n + clampi(expert_idx[g * kact + nn / d_e], n)];
     }
-    __device__ float epi(float val, float gate) const { return raw ? val : silu_fast(val) * gate; }
+    __device__ float epi(float val, float gate) const { return raw ? val : (EXACT ? silu(val) : silu_fast(val)) * gate; }
     __device__ bool has_residual() const { return false; }
     __device__ uint4 res8(int, int, int) const { return make_uint4(0, 0, 0, 0); }
     __device__ void put8(int g, int r, int nn, uint4 piece) const { put8_as<false>(g, r, nn, piece); }
@@ -377,7 +377,7 @@ template <typename T, bool RAW = false> struct UomeUpProblem {
 // for QKV); K = d; N = d_e.  Epilogue: SiLU, times the weight of the row's contribution (expert
 // gate and/or the gate of the row's patch): the second layer is linear, so the weight can ride on
 // the hidden activations and the output-stationary second GEMM needs no per-segment scale.
-template <typename T> struct UomeDsUpProblem {
+template <typename T, bool EXACT = false> struct UomeDsUpProblem {
     typedef typename storage_elem<T>::type Elem;
     const T *u, *a_in;
     const int32_t *expert_idx, *patch_idx;
@@ -419,7 +419,7 @@ template <typename T> struct UomeDsUpProblem {
     static constexpr bool kRowScale = true;
     static constexpr bool kColScale = false;
     __device__ float col_scale(int, int) const { return 1.0f; }
-    __device__ float epi(float val, float w) const { return silu_fast(val) * w; }
+    __device__ float epi(float val, float w) const { return (EXACT ? silu(val) : silu_fast(val)) * w; }
     __device__ bool has_residual() const { return false; }
     __device__ uint4 res8(int, int, int) const { return make_uint4(0, 0, 0, 0); }
     __device__ void put8(int g, int r, int nn, uint4 piece) const

@@ -1013,9 +1013,9 @@ static hipError_t smha_mfma(const SmhaArgs &a, hipStream_t st)
 // first layer per active unit on its gathered rows (UomeDsUpProblem), second layer + index add as
 // the output-stationary contraction over the experts that picked each patch (OutProjProblem with
 // A^O in the place of W^o and the hidden activations in the place of o).
-template <typename T> static UomeDsUpProblem<T> make_ds_up(const UomeDsArgs &a)
+template <typename T, bool EXACT> static UomeDsUpProblem<T, EXACT> make_ds_up(const UomeDsArgs &a)
 {
-    UomeDsUpProblem<T> up;
+    UomeDsUpProblem<T, EXACT> up;
     up.u = static_cast<const T *>(a.u);
     up.a_in = static_cast<const T *>(a.a_in);
     up.expert_idx = a.expert_idx;
@@ -1044,12 +1044,12 @@ template <typename T> static OutProjProblem<T> make_ds_down(const UomeDsArgs &a)
     return op;
 }
 
-// any width, either storage type
+// any width, either storage type; SiLU by a division
 template <typename T> static hipError_t uome_ds_tail(const UomeDsArgs &a, hipStream_t st)
 {
     const int l_p = a.l / a.m, l_a = a.c * l_p;
     hipError_t err;
-    if ((err = launch_gemm_tail<0>(make_ds_up<T>(a), a.b * a.k, l_a, a.d_e, st)) != hipSuccess) return err;
+    if ((err = launch_gemm_tail<0>(make_ds_up<T, true>(a), a.b * a.k, l_a, a.d_e, st)) != hipSuccess) return err;
     OutProjProblem<T> op = make_ds_down<T>(a);
     const int groups = a.b * op.set_patch_groups(a.b);
     return launch_gemm_tail<0>(op, groups, op.gp * l_p, a.d, st);
@@ -1061,7 +1061,7 @@ static hipError_t uome_ds_mfma(const UomeDsArgs &a, hipStream_t st)
     typedef OutProjProblem<bf16_t> OP;
     const int l_p = a.l / a.m, l_a = a.c * l_p, units = a.b * a.k;
     hipError_t err;
-    const UP up = make_ds_up<bf16_t>(a);
+    const UP up = make_ds_up<bf16_t, false>(a);
     if ((err = launch_gemm_dma_auto(up, units, l_a, a.d_e, a.d, a.d, st)) != hipSuccess) return err;
     OP op = make_ds_down<bf16_t>(a);
     op.once = stream_once((size_t)a.b * a.l * a.d * sizeof(bf16_t));   // u's last use, the block's output

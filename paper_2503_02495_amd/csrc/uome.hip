@@ -10,10 +10,11 @@
 
 namespace uoe {
 
-// any width, either storage type
+// any width, either storage type (SiLU by a division: the reciprocal of silu_fast is zero where the sigmoid is no normal
+// number, z <= -87.4; 6 x 1000 tokens, d 360, 3 x 232 hidden columns: 2 us of 89 for the layer's forward)
 template <typename T> static hipError_t uome_up_tail(const UomeArgs &a, hipStream_t st)
 {
-    UomeUpProblem<T> up;
+    UomeUpProblem<T, false, true> up;
     up.u = static_cast<const T *>(a.u);
     up.a_in = static_cast<const T *>(a.a_in);
     up.expert_idx = a.expert_idx;

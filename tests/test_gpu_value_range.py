@@ -1,6 +1,8 @@
-"""Values at the ends of what the storage types hold."""
+"""Values at the ends of what the storage types hold: heads whose v leaves the range of fp16, pre-activations where the
+sigmoid is as small as fp32 can hold."""
 import numpy as np
 import pytest
+import torch
 
 import test_gpu_parity as P
 from paper_2503_02495_amd import binding as B
@@ -37,3 +39,44 @@ def test_smha_range_of_v(name, power, monkeypatch):
     print(f"range of v {name} 2^{power}", flush=True)
     P.run_smha_stage(name, 0)
     P.run_smha_variant(name, CA, 8, 0.2)
+
+
+# bf16 values at which exp(-z) is between 2^126 and the largest fp32: its reciprocal is no normal number, z times it is
+TAIL = [-88.5, -88.0, -87.5]
+
+
+def silu64(z):
+    return z / (1.0 + np.exp(-z))
+
+
+def one_hot(shape, at, value):
+    t = torch.zeros(shape, dtype=torch.bfloat16, device="cuda")
+    t[at] = value
+    return t
+
+
+@pytest.mark.parametrize("select", [False, True])
+def test_silu_tail_off_32(select):
+    """The MLP's activation where widths are no multiple of 32: division and exponential in fp32, rounded once, for
+    pre-activations down to -88 (relative error of a bf16 result: 2^-9, bound 2^-8)."""
+    z = np.array(TAIL + [-60.0, -1.5, 0.5, 30.0])
+    l, d, d_e = len(z), 72, 40
+    u = torch.zeros((1, l, d), dtype=torch.bfloat16, device="cuda")
+    u[0, :, 0] = torch.tensor(z, dtype=torch.float32).to(torch.bfloat16).cuda()
+    a_in = one_hot((1, d, d_e), (0, 0), 1.0)
+    idx = torch.zeros((1, 1), dtype=torch.int32, device="cuda")
+    if not select:
+        blk = B.block_desc(1, l, d, 1, 1, 1, 1, d_e, B.BF16, 0)
+        hidden = torch.empty((1, l, d_e), dtype=torch.bfloat16, device="cuda")
+        B.uome_up(blk, u, a_in, idx, None, hidden)
+        got = hidden[0].float().cpu().numpy()
+    else:   # out = hidden A^O with a single one in A^O: the first hidden column
+        blk = B.block_desc(1, l, d, 1, 1, l, l - 1, d_e, B.BF16, 0)
+        pidx = torch.arange(l - 1, dtype=torch.int32, device="cuda").reshape(1, 1, l - 1)
+        out = torch.empty_like(u)
+        ws = torch.empty(B.workspace_bytes(None, blk), dtype=torch.uint8, device="cuda")
+        B.uome_forward(blk, u, a_in, one_hot((1, d_e, d), (0, 0, 0), 1.0), idx, None, pidx, None, out, ws)
+        got = out[0, :-1, :1].float().cpu().numpy()
+        z = z[:-1]
+    want = silu64(z)[:, None]
+    assert np.all(np.abs(got - want) <= 2.0 ** -8 * np.abs(want)), (got[:, 0], want[:, 0])
