@@ -90,6 +90,9 @@ __device__ __forceinline__ float wave_sum(float v)
 __device__ __forceinline__ int clampi(int v, int count) { return min(max(v, 0), count - 1); }
 
 __device__ __forceinline__ float silu(float z) { return z / (1.0f + __expf(-z)); }
+// the backward passes' sigmoid: a division, not the hardware reciprocal, which is zero where the result is no normal number
+// (z <= -87.4) and an ulp off elsewhere; layer forward + backward of the lm shape 223.0 -> 225.6 us, of the largest 2108 -> 2122
+__device__ __forceinline__ float sigmoid(float z) { return 1.0f / (1.0f + __expf(-z)); }
 // SiLU with the hardware exp2 and reciprocal (about 1 ulp each): for epilogues that round the
 // result to bf16 anyway
 __device__ __forceinline__ float silu_fast(float z)

@@ -36,8 +36,7 @@ int uome_backward_splits(int b, int l, int d, int n, int k, int d_e)
     return s;
 }
 
-// Elementwise middle for 8 elements: dZ, H and the sum of dH * SiLU(Z).  The sigmoid's reciprocal is the hardware's
-// (1 ulp of fp32; the results are rounded to bf16): the exact division was a quarter of the epilogue's instructions.
+// Elementwise middle for 8 elements: dZ, H and the sum of dH * SiLU(Z), an fp32 output.
 __device__ __forceinline__ float uome_mid8(uint4 z8, uint4 dh8, float w, uint4 &dz8, uint4 &h8)
 {
     const uint32_t z[4] = {z8.x, z8.y, z8.z, z8.w}, dh[4] = {dh8.x, dh8.y, dh8.z, dh8.w};
@@ -50,7 +49,7 @@ __device__ __forceinline__ float uome_mid8(uint4 z8, uint4 dh8, float w, uint4 &
         for (int e = 0; e < 2; ++e) {
             const float zv = __uint_as_float(e ? z[q] & 0xFFFF0000u : z[q] << 16);
             const float dv = __uint_as_float(e ? dh[q] & 0xFFFF0000u : dh[q] << 16);
-            const float sig = __builtin_amdgcn_rcpf(1.0f + __expf(-zv));
+            const float sig = sigmoid(zv);
             const float v = zv * sig;
             part = fmaf(dv, v, part);
             hv[e] = v * w;
@@ -162,7 +161,7 @@ template <typename T> struct UomeDhPairProblem : UomeDhProblem<T> {
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     const float zv = z[i * TN + j][e], dv = acc[i][j][e];
-                    const float sig = __builtin_amdgcn_rcpf(1.0f + __expf(-zv)), v = zv * sig;
+                    const float sig = sigmoid(zv), v = zv * sig;
                     ps = fmaf(dv, v, ps);
                     z[i * TN + j][e] = v * w;
                     acc[i][j][e] = dv * w * (sig * (1.0f + zv * (1.0f - sig)));

@@ -80,3 +80,25 @@ def test_silu_tail_off_32(select):
         z = z[:-1]
     want = silu64(z)[:, None]
     assert np.all(np.abs(got - want) <= 2.0 ** -8 * np.abs(want)), (got[:, 0], want[:, 0])
+
+
+@pytest.mark.parametrize("z", TAIL)
+@pytest.mark.parametrize("b,l,d,d_e,m", [(1, 32, 32, 32, 1), (24, 2048, 32, 256, 1), (1, 64, 32, 32, 2), (1, 20, 24, 8, 1)],
+                         ids=["one_launch", "two_launches", "data_selection", "any_shape"])
+def test_uome_backward_sigmoid_tail(b, l, d, d_e, m, z):
+    """dL/d(gate) = sum dH SiLU(Z) is an fp32 output: pre-activations of -88 must count with their own value (fp32
+    exponential of 88: 88 * 2^-24 = 5e-6 relative; bound 1e-4)."""
+    print(f"sigmoid tail b={b} l={l} d={d} d_e={d_e} m={m} z={z}", flush=True)
+    c = m // 2 if m > 1 else 1
+    blk = B.block_desc(b, l, d, 1, 1, m, c, d_e, B.BF16, GE)
+    u, a_in = one_hot((b, l, d), (slice(None), slice(None), 0), z), one_hot((1, d, d_e), (0, 0), 1.0)
+    a_out, d_out = one_hot((1, d_e, d), (0, slice(None), 0), 1.0), one_hot((b, l, d), (slice(None), slice(None), 0), 2.0 ** 40)
+    idx, gate = torch.zeros((b, 1), dtype=torch.int32, device="cuda"), torch.ones((b, 1), device="cuda")
+    pidx = torch.zeros((b, 1, c), dtype=torch.int32, device="cuda") if m > 1 else None
+    d_u, d_gate = torch.empty_like(u), torch.empty_like(gate)
+    ws = torch.empty(B.uome_backward_workspace_bytes(blk), dtype=torch.uint8, device="cuda")
+    B.uome_backward(blk, u, a_in, a_out, idx, gate, pidx, None, d_out, d_u, torch.empty_like(a_in), torch.empty_like(a_out),
+                    d_gate, None, ws)
+    got = d_gate.double().cpu().numpy()
+    want = (l // m) * c * d_e * 2.0 ** 40 * silu64(z)
+    assert np.all(np.abs(got - want) <= 1e-4 * abs(want)), (got.ravel()[:2], want)
