@@ -63,14 +63,19 @@ template <typename T> struct RawPiece;   // 8 elements as loaded
 template <> struct RawPiece<bf16_t> { uint4 v[1]; };
 template <> struct RawPiece<float> { uint4 v[2]; };
 
-// Softmax backward of one logit.  dz_i = g_i (dg_i - sum_j g_j dg_j) is evaluated as g_i * sum_j g_j (dg_i - dg_j)
-// (the gates sum to one): with one gate close to 1 the first form subtracts two nearly equal numbers, the second
-// adds small terms of mixed sign only.
+// Softmax backward of one logit, dz_i = g_i (dg_i - sum_j g_j dg_j) for any gates, evaluated as
+// g_i (sum_j g_j (dg_i - dg_j) + (1 - sum_j g_j) dg_i): with one gate close to 1 the first form subtracts two nearly equal
+// numbers, the second adds small terms of mixed sign only.  Gates of a softmax sum to one up to their rounding, (n + 1) 2^-23 at
+// most (a division, and the sums in the forward pass and here); that much of the last term is rounding, not gate, and left out.
 __device__ __forceinline__ float softmax_bwd(const float *g, const float *dg, int n, int stride, int i)
 {
     const float mine = dg[i * stride];
-    float s = 0.f;
-    for (int q = 0; q < n; ++q) s = fmaf(g[q * stride], mine - dg[q * stride], s);
+    float s = 0.f, rest = 1.f;
+    for (int q = 0; q < n; ++q) {
+        s = fmaf(g[q * stride], mine - dg[q * stride], s);
+        rest -= g[q * stride];
+    }
+    if (fabsf(rest) > (float)(n + 1) * 1.1920929e-7f) s = fmaf(mine, rest, s);
     return g[i * stride] * s;
 }
 

@@ -1,5 +1,5 @@
 """Values at the ends of what the storage types hold: heads whose v leaves the range of fp16, pre-activations where the
-sigmoid is as small as fp32 can hold."""
+sigmoid is as small as fp32 can hold, gates that are no softmax of anything."""
 import numpy as np
 import pytest
 import torch
@@ -102,3 +102,30 @@ def test_uome_backward_sigmoid_tail(b, l, d, d_e, m, z):
     got = d_gate.double().cpu().numpy()
     want = (l // m) * c * d_e * 2.0 ** 40 * silu64(z)
     assert np.all(np.abs(got - want) <= 1e-4 * abs(want)), (got.ravel()[:2], want)
+
+
+@pytest.mark.parametrize("name", ["tiny", "bf16_noise", "bf16_n32"])
+def test_route_backward_any_gates(name):
+    """The formula of uoe_route_backward holds for whatever gates a caller hands over, not only for rows that sum to one."""
+    cfg = P.get_cfg(name)
+    print(f"route backward, gates that do not sum to one: {name}", flush=True)
+    inp = synth.make_inputs(cfg, w_std=0.06)
+    rng = np.random.default_rng(3)
+    ge = rng.uniform(0.1, 1.0, (cfg.b, cfg.n_a)).astype(np.float32)
+    gp = rng.uniform(0.1, 1.0, (cfg.b, cfg.n_a, cfg.m)).astype(np.float32)
+    d_ge, d_gp = synth.make_gate_grads(cfg, cfg.n_a, cfg.m)
+    d_x0 = synth.make_upstream_grad(cfg)
+    dev = P.DeviceLayer(inp, R, R)
+    f32 = lambda a: P.to_device(a, synth.F32, dev.device)
+    d_x = P.to_device(d_x0, cfg.dtype, dev.device)
+    d_we, d_wb, d_wa = (torch.empty_like(t) for t in (dev.a_w_expert, dev.a_w_b, dev.a_w_a))
+    ws = torch.empty(B.route_backward_workspace_bytes(dev.smha), dtype=torch.uint8, device=dev.device)
+    B.route_backward(dev.smha, dev.x, dev.a_w_expert, dev.a_w_b, dev.a_w_a, f32(ge), f32(gp), f32(d_ge), f32(d_gp),
+                     d_x, d_we, d_wb, d_wa, ws)
+    torch.cuda.synchronize()
+    want = P.oracle.route_backward(inp.x, inp.a_w_expert, inp.a_w_b, inp.a_w_a, ge, gp, d_ge, d_gp)
+    errs = {"d_x": P.scaled_err(P.to_host(d_x), d_x0.astype(np.float64) + want.d_x),
+            "d_w_expert": P.grad_err(P.to_host(d_we), want.d_w_expert),
+            "d_w_b": P.grad_err(P.to_host(d_wb).T, want.d_w_b.T), "d_w_a": P.grad_err(P.to_host(d_wa).T, want.d_w_a.T)}
+    print(" ".join(f"{k} {v:.3e}" for k, v in errs.items()), flush=True)
+    assert max(errs.values()) <= P.TOL[cfg.dtype], errs
