@@ -159,7 +159,7 @@ int check_uome_bwd(const uoe_block_desc *blk)
 struct SmhaBwdWs {
     SmhaWs fwd;
     size_t lse, rt, dd, do_raw, d_o, og, dqkv, partial, total;
-    size_t g_q, g_k, g_v, g_og;  // any-shape path (four bytes an element)
+    size_t g_q, g_k, g_v, g_og, g_inv;  // any-shape path (four bytes an element)
     int splits;
 };
 static bool smha_bwd_mfma(const uoe_block_desc *blk)
@@ -183,6 +183,7 @@ SmhaBwdWs smha_bwd_ws(const uoe_block_desc *d)
         w.dqkv = off; off += 3 * one;
         w.rt = off; off += rows;
         w.lse = off; off += rows;
+        w.g_inv = off; off += rows;
         w.dd = off; off += rows;
         // weight gradients: chunks of 128 samples x parts of an expert's (unit, pick) list, at most BWD_ANY_SEGMENTS
         // entries in each even if every sample selected the expert
@@ -643,6 +644,7 @@ static int smha_backward(const SmhaKept *kept, const uoe_block_desc *blk, const 
         a.d_expert_gate = d_expert_gate; a.d_patch_gate = d_patch_gate;
         a.do_raw = reinterpret_cast<float *>(at(ws, s.do_raw)); a.dqkv = at(ws, s.dqkv); a.og = at(ws, s.g_og);
         a.rt = reinterpret_cast<float *>(at(ws, s.rt)); a.dd = reinterpret_cast<float *>(at(ws, s.dd));
+        a.inv_sum = reinterpret_cast<float *>(at(ws, s.g_inv));
         a.splits = s.splits;
         a.partial = reinterpret_cast<float *>(at(ws, s.partial));
         return launch_smha_backward_any(a, blk->dtype == UOE_BF16, static_cast<hipStream_t>(hip_stream)) == hipSuccess

@@ -389,7 +389,7 @@ template <typename T> hipError_t uome_backward_any(const UomeBwdArgs &a, hipStre
 
 // ------------------------------------------------------------------------------------------ SMHA
 // Workspace: q, k, v and do_raw fp32 [units, l_a, d_h]; og = w o, operand layout [units, l_a, parts, d_h]; dqkv, operand
-// layout [units, l_a, parts, 3*d_h] as [dq | dk | dv]; lse, dd, rt fp32 [units, l_a].
+// layout [units, l_a, parts, 3*d_h] as [dq | dk | dv]; f.lse, inv_sum, dd, rt fp32 [units, l_a].
 
 // weight of row r of unit g in the block's output (Eq. 36 with the gate flags)
 __device__ __forceinline__ float row_weight(const SmhaBwdArgs &a, int g, int r, int l_p)
@@ -426,14 +426,16 @@ __device__ __forceinline__ bool any_key_ok(const SmhaArgs &f, int g, int key, in
 // holds one own row; an accumulator register of a [streamed x own] tile is by itself the second operand of the
 // next product (attention_f32_kernel).  q enters scaled by log2(e)/sqrt(d_h), dO as w * dO_raw with the row's
 // weight applied to the products; P and dP are formed the same way in both kernels and by both walks that use
-// them, so that the rows of dS cancel as in exact arithmetic (a row that attends to one key has dS = 0).
+// them, so that the rows of dS cancel as in exact arithmetic (a row that attends to one key has dS = 0).  P is formed from the
+// row's maximum and the reciprocal of its sum: a log-sum-exp of 10 is held to 2^-21, which every P of the row would be off
+// by (weight gradients 2 to 3 percent further from fp64 over 18 drawn fp32 shapes).
 // KS waves share an own block and take streamed tiles KS apart; sums are merged through LDS in wave order: with one
 // wave per block the lm shape in fp32 has 128 of them for 1024 SIMDs.
 template <typename T, int DH, int NQ, int KS, bool KV>
 __global__ __launch_bounds__(NQ *KS * 64) void attention_bwd_f32_kernel(SmhaBwdArgs a)
 {
     constexpr int BT = 32, P = DH + 4, NTH = NQ * 64, NP = BT * DH / 4 / NTH;   // NP: 16-byte pieces per staging thread
-    constexpr int SPLIT = 2 * BT * P + 3 * BT, SLOT = (KV ? DH : DH / 2) + 2, MERGE = (KS - 1) * NQ * 64 * SLOT;
+    constexpr int SPLIT = 2 * BT * P + 4 * BT, SLOT = (KV ? DH : DH / 2) + 2, MERGE = (KS - 1) * NQ * 64 * SLOT;
     __shared__ __align__(16) float lds[KS * SPLIT > MERGE ? KS * SPLIT : MERGE];
     constexpr int PARTS = parts_of<T>::value;
     const SmhaArgs &f = a.f;
@@ -442,7 +444,7 @@ __global__ __launch_bounds__(NQ *KS * 64) void attention_bwd_f32_kernel(SmhaBwdA
     const int split = wave / NQ, qg = wave - split * NQ, stid = tid - split * NTH;
     const int lr = lane & 31, lh = lane >> 5;
     const int own = blockIdx.x * (32 * NQ) + qg * 32 + lr, own_c = min(own, l_a - 1);
-    float *TA = lds + split * SPLIT, *TB = TA + BT * P, *R0 = TB + BT * P, *R1 = R0 + BT, *R2 = R1 + BT;
+    float *TA = lds + split * SPLIT, *TB = TA + BT * P, *R0 = TB + BT * P, *R1 = R0 + BT, *R2 = R1 + BT, *R3 = R2 + BT;
     const size_t ubase = (size_t)g * l_a * d_h;
     const float *Q = static_cast<const float *>(f.q) + ubase, *K = static_cast<const float *>(f.kk) + ubase;
     const float *V = static_cast<const float *>(f.v) + ubase, *DO = a.do_raw + ubase;
@@ -479,7 +481,7 @@ __global__ __launch_bounds__(NQ *KS * 64) void attention_bwd_f32_kernel(SmhaBwdA
     auto tile_of = [&](int it) { return t_begin + it * KS + split; };
 
     float4 ra[NP], rb[NP];
-    float r0 = 0.f, r1 = 0.f, r2 = 0.f;
+    float r0 = 0.f, r1 = 0.f, r2 = 0.f, r3 = 0.f;
     auto load_global = [&](int kt) {
 #pragma unroll
         for (int q = 0; q < NP; ++q) {
@@ -492,8 +494,9 @@ __global__ __launch_bounds__(NQ *KS * 64) void attention_bwd_f32_kernel(SmhaBwdA
         }
         if (stid < BT) {
             const int row = kt * BT + stid;
-            if (KV) {   // streamed queries: log-sum-exp, D, weight
+            if (KV) {   // streamed queries: softmax maximum, D, weight, softmax 1 / sum
                 r0 = row < l_a ? a.f.lse[(size_t)g * l_a + row] : 0.f;
+                r3 = row < l_a ? a.inv_sum[(size_t)g * l_a + row] : 0.f;
                 r1 = row < l_a ? a.dd[(size_t)g * l_a + row] : 0.f;
                 r2 = row < l_a ? row_weight(a, g, row, l_p) : 0.f;
             } else r0 = row < l_a && any_key_ok(f, g, row, l_p) ? 1.f : 0.f;   // streamed keys: admissible
@@ -513,6 +516,7 @@ __global__ __launch_bounds__(NQ *KS * 64) void attention_bwd_f32_kernel(SmhaBwdA
             if (KV) {
                 R1[stid] = r1;
                 R2[stid] = r2;
+                R3[stid] = r3;
             }
         }
     };
@@ -585,7 +589,7 @@ __global__ __launch_bounds__(NQ *KS * 64) void attention_bwd_f32_kernel(SmhaBwdA
             acc_a[t][q] = 0.f;
             if (KV) acc_b[t][q] = 0.f;
         }
-    float lse_own = 0.f, d_own = 0.f;
+    float max_own = 0.f, inv_own = 0.f, d_own = 0.f;
 
     if constexpr (!KV) {
         // walk 1: softmax statistics and o
@@ -651,9 +655,10 @@ __global__ __launch_bounds__(NQ *KS * 64) void attention_bwd_f32_kernel(SmhaBwdA
 #pragma unroll
                 for (int q = 0; q < 16; ++q) acc_a[td][q] = o[td * 16 + q];
         }
-        lse_own = lsum > 0.f ? mrun + log2f(lsum) : 0.f;
+        max_own = lsum > 0.f ? mrun : 0.f;
+        inv_own = lsum > 0.f ? 1.0f / lsum : 0.f;
         if (split == 0) {
-            const float inv = lsum > 0.f ? 1.0f / lsum : 0.f;
+            const float inv = inv_own;
             const size_t row = (size_t)g * l_a + own_c;
             float dot = 0.f;
 #pragma unroll
@@ -676,7 +681,8 @@ __global__ __launch_bounds__(NQ *KS * 64) void attention_bwd_f32_kernel(SmhaBwdA
             dot += __shfl_xor(dot, 32, 64);
             if (own < l_a && lh == 0) {
                 a.rt[row] = dot;
-                a.f.lse[row] = lse_own;
+                a.f.lse[row] = max_own;
+                a.inv_sum[row] = inv_own;
             }
         }
         // walk 2: D = sum_j P_j dP_j
@@ -691,7 +697,7 @@ __global__ __launch_bounds__(NQ *KS * 64) void attention_bwd_f32_kernel(SmhaBwdA
             const f32x16_t s = product(TA, fa), dp = product(TB, fb);
 #pragma unroll
             for (int q = 0; q < 16; ++q)
-                d_own = fmaf(admissible(kt, q, R0) ? __builtin_amdgcn_exp2f(s[q] - lse_own) : 0.f, mul_rounded(dp[q], w_own), d_own);
+                d_own = fmaf(admissible(kt, q, R0) ? __builtin_amdgcn_exp2f(s[q] - max_own) * inv_own : 0.f, mul_rounded(dp[q], w_own), d_own);
         }
         d_own += __shfl_xor(d_own, 32, 64);
         float v[1] = {d_own};
@@ -717,8 +723,8 @@ __global__ __launch_bounds__(NQ *KS * 64) void attention_bwd_f32_kernel(SmhaBwdA
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
             const int at = (q >> 2) * 8 + lh * 4 + (q & 3);
-            const float lse = KV ? R0[at] : lse_own, dd = KV ? R1[at] : d_own, w = KV ? R2[at] : w_own;
-            const float p = admissible(kt, q, R0) ? __builtin_amdgcn_exp2f(s[q] - lse) : 0.f;
+            const float mx = KV ? R0[at] : max_own, inv = KV ? R3[at] : inv_own, dd = KV ? R1[at] : d_own, w = KV ? R2[at] : w_own;
+            const float p = admissible(kt, q, R0) ? __builtin_amdgcn_exp2f(s[q] - mx) * inv : 0.f;
             dp[q] = p * (mul_rounded(dp[q], w) - dd);
             s[q] = p * w;   // dV contracts P with dO = w dO_raw
         }

@@ -229,6 +229,7 @@ struct SmhaBwdArgs {
     void *d_o;                                // [units, l_a, d_h]
     void *dqkv;                               // [units, l_a, 3*d_h]
     float *rt, *dd;                           // [units, l_a] each: dL/dw_t and the softmax row term
+    float *inv_sum;                           // any-shape path: [units, l_a] 1 / softmax row sum; f.lse holds the row maximum there
     int rt_parts;                             // rt is that many arrays to be added (0: one), set by the launcher
     float *partial;                           // [4*n*splits, d_h, d] split tiles of the four weight gradients
     int splits;

@@ -129,3 +129,26 @@ def test_route_backward_any_gates(name):
             "d_w_b": P.grad_err(P.to_host(d_wb).T, want.d_w_b.T), "d_w_a": P.grad_err(P.to_host(d_wa).T, want.d_w_a.T)}
     print(" ".join(f"{k} {v:.3e}" for k, v in errs.items()), flush=True)
     assert max(errs.values()) <= P.TOL[cfg.dtype], errs
+
+
+@pytest.mark.parametrize("flags", [0, R | GE | GP | CA])
+def test_smha_backward_equal_keys_large_logits(flags):
+    """fp32: every key of a unit is the same, with logits around 200.  The probabilities are then 1 / (number of keys) to the
+    last bit, whatever the logits are; a softmax held as a log-sum-exp of 300 is off by 2^-16.  d_wv and d_wo take the
+    probabilities times sums of at most 120 terms: 2e-6 (sqrt(120) * 2^-24 = 7e-7)."""
+    cfg = P.small(b=2, l=60, d=40, n_a=2, d_h=24, m=6, c=5, k_a=1, n_m=2, d_e=8, k_m=1)
+    print(f"equal keys, large logits, flags={flags}", flush=True)
+    inp = synth.make_inputs(cfg, w_std=0.1)
+    inp.x[:] = inp.x[:, :1]
+    q = np.einsum("bd,ndh->bnh", inp.x[:, 0], inp.wq)
+    inp.wq = inp.wk = (inp.wq * np.sqrt(200.0 * np.sqrt(cfg.d_h) / np.mean(np.sum(q * q, -1)))).astype(np.float32)
+    d_out = synth.make_upstream_grad(cfg)
+    dev = P.DeviceLayer(inp, flags, R)
+    ref = P.oracle.route(inp.x, cfg.n_a, cfg.k_a, cfg.m, cfg.c, inp.a_w_expert, inp.a_w_b, inp.a_w_a, None, None)
+    ge, gp = ref.expert_gate.astype(np.float32), ref.patch_gate.astype(np.float32)
+    i32, f32 = (lambda a: torch.from_numpy(a).to(dev.device)), (lambda a: P.to_device(a, synth.F32, dev.device))
+    got = dev.smha_backward(f32(d_out), i32(ref.expert_id), f32(ge), i32(ref.patch_id), f32(gp))
+    want = P.oracle.smha_backward(inp.x, inp.wq, inp.wk, inp.wv, inp.wo, ref.expert_id, ge, ref.patch_id, gp, cfg.m, d_out, flags)
+    errs = {"d_wv": P.fro_err(P.to_host(got[3]), want.d_wv), "d_wo": P.fro_err(P.to_host(got[4]), want.d_wo)}
+    print(errs, flush=True)
+    assert max(errs.values()) <= 2e-6, errs
