@@ -2,6 +2,8 @@
 path, at the sizes where they can go wrong: one element past and one short of a tile, K segments that end
 inside a K-step, heads one step below and above a padded width, and both tile choices.  Same oracle,
 metric and bounds as test_gpu_parity (1e-4 in fp32, 2e-2 in bf16)."""
+import math
+
 import pytest
 
 import test_gpu_parity as P
@@ -40,8 +42,15 @@ P.DS_CONFIGS.update(ODD_DS)
 
 @pytest.fixture(autouse=True)
 def _std(monkeypatch):
-    """fp32 attention logits of order one (std 0.2 weights make them ten times that at these widths)."""
+    """Weights of std 0.06: attention logits of std 0.06^2 d, 0.14 at d = 40 and 0.5 at d = 136, a nearly uniform softmax
+    (test_smha_f32_logits_of_order_one has the other kind)."""
     monkeypatch.setattr(P, "w_std_for", lambda name: 0.06)
+
+
+def order_one_logits(monkeypatch):
+    """Weights of std sqrt(1.5 / d): attention logits of std 1.5, running maxima that move and key splits that differ."""
+    plain = synth.make_inputs
+    monkeypatch.setattr(synth, "make_inputs", lambda cfg, **kw: plain(cfg, w_std=math.sqrt(1.5 / cfg.d)))
 
 
 @pytest.mark.parametrize("name", list(ODD))
@@ -49,6 +58,14 @@ def _std(monkeypatch):
 def test_smha_odd_sizes(name, flags, rope_dim, pad_frac):
     print(f"smha odd {name} flags={flags}", flush=True)
     P.run_smha_variant(name, flags, rope_dim, pad_frac)
+
+
+@pytest.mark.parametrize("name", [n for n in ODD if n.startswith("f32")])
+@pytest.mark.parametrize("flags,pad_frac", [(0, 0.0), (CA | R | GE | GP, 0.3)])
+def test_smha_f32_logits_of_order_one(name, flags, pad_frac, monkeypatch):
+    order_one_logits(monkeypatch)
+    print(f"smha logits of order one {name} flags={flags}", flush=True)
+    P.run_smha_variant(name, flags, 0, pad_frac)
 
 
 @pytest.mark.parametrize("name", list(ODD))
@@ -76,8 +93,12 @@ UOME_BWD = {
     "ub_wide": P.small(b=2, l=20, d=16, n_a=2, d_h=8, m=1, c=1, k_a=1, n_m=2, d_e=2056, k_m=1, dtype=BF),
     # ranges of the token axis, the last one short; one expert, one sample
     "ub_ranges": P.small(b=1, l=1100, d=40, n_a=1, d_h=8, m=1, c=1, k_a=1, n_m=1, d_e=24, k_m=1, dtype=BF),
-    # both fp32 tile sizes
+    # fp32, 128x128 tiles: in the launch of Z and dH; in the weight gradients (256 of them, five of the eight token ranges
+    # empty, the last one of 13 tokens inside a K-step); in d_u
     "ub_f32_big": P.small(b=32, l=264, d=136, n_a=2, d_h=8, m=1, c=1, k_a=1, n_m=2, d_e=136, k_m=2),
+    "ub_f32_wgrad": P.small(b=8, l=77, d=136, n_a=2, d_h=8, m=1, c=1, k_a=1, n_m=4, d_e=136, k_m=2),
+    "ub_f32_du": P.small(b=64, l=264, d=136, n_a=2, d_h=8, m=1, c=1, k_a=1, n_m=2, d_e=24, k_m=1),
+    "ub_wgrad": P.small(b=8, l=77, d=136, n_a=2, d_h=8, m=1, c=1, k_a=1, n_m=4, d_e=136, k_m=2, dtype=BF),
     # Z and dH in one launch: large tiles with waves that straddle experts; no room for the gate's sums: two launches
     "ub_dual_large": P.small(b=44, l=150, d=40, n_a=1, d_h=8, m=1, c=1, k_a=1, n_m=3, d_e=88, k_m=3, dtype=BF),
     "ub_dual_no_room": P.small(b=128, l=1000, d=8, n_a=1, d_h=8, m=1, c=1, k_a=1, n_m=1, d_e=8, k_m=1, dtype=BF),
@@ -98,6 +119,14 @@ SMHA_BWD = {
     "sb_f32_ks1": P.small(b=128, l=72, d=16, n_a=4, d_h=16, m=2, c=2, k_a=4, n_m=2, d_e=32, k_m=1),
     "sb_f32_ks2": P.small(b=64, l=130, d=16, n_a=2, d_h=64, m=2, c=2, k_a=2, n_m=2, d_e=32, k_m=1),
     "sb_f32_ks4": P.small(b=2, l=300, d=24, n_a=3, d_h=32, m=10, c=9, k_a=2, n_m=2, d_e=32, k_m=1),
+    # 128-column heads in 128x128 weight-gradient tiles (8 experts in 8 parts)
+    "sb_f32_wgrad": P.small(b=32, l=72, d=40, n_a=8, d_h=128, m=9, c=8, k_a=2, n_m=2, d_e=32, k_m=1),
+    "sb_wgrad": P.small(b=32, l=72, d=40, n_a=8, d_h=120, m=9, c=8, k_a=2, n_m=2, d_e=32, k_m=1, dtype=BF),
+    # 32-grid: dO on 128-row tiles with K-steps of 64 and of 32
+    "sb_do_128x64": P.small(b=65, l=512, d=64, n_a=4, d_h=64, m=8, c=4, k_a=2, n_m=2, d_e=32, k_m=1, dtype=BF),
+    "sb_do_128x32": P.small(b=65, l=512, d=96, n_a=4, d_h=64, m=8, c=4, k_a=2, n_m=2, d_e=32, k_m=1, dtype=BF),
+    # one wave group per own block with two streamed tiles (2048 blocks); d_x of 32-row patches as a launch of its own
+    "sb_one_group": P.small(b=128, l=128, d=32, n_a=17, d_h=32, m=4, c=4, k_a=4, n_m=2, d_e=32, k_m=1, dtype=BF),
     # one key per query: dS is exactly zero
     "sb_lp1_c1": P.small(b=2, l=6, d=8, n_a=2, d_h=8, m=6, c=1, k_a=1, n_m=2, d_e=8, k_m=1, dtype=BF),
 }
@@ -114,6 +143,31 @@ def test_uome_backward_odd_sizes(name, flags):
 @pytest.mark.parametrize("flags,rope_dim,pad_frac", [(0, 0, 0.0), (CA | R | GE | GP, 8, 0.2)])
 def test_smha_backward_odd_sizes(name, flags, rope_dim, pad_frac):
     P.run_smha_backward(name, flags, rope_dim, pad_frac=pad_frac)
+
+
+@pytest.mark.parametrize("name", [n for n in SMHA_BWD if n.startswith("sb_f32")])
+def test_smha_backward_f32_logits_of_order_one(name, monkeypatch):
+    order_one_logits(monkeypatch)
+    P.run_smha_backward(name, R | GE | GP, 0)
+
+
+# data selection on the 32-grid: every tile of dH (256, 128 and 64 rows, wave tiles of 64 and of 32 columns) and d_u and
+# the weight gradients as launches of their own (64-row patches; 256-row weight-gradient tiles)
+DS_BWD = {
+    "dsb_256x256x64": P.small(b=64, l=192, d=768, n_a=2, d_h=32, m=2, c=1, k_a=1, n_m=4, d_e=256, k_m=4, m_m=6, c_m=5, dtype=BF),
+    "dsb_128x256x32": P.small(b=48, l=192, d=96, n_a=2, d_h=32, m=2, c=1, k_a=1, n_m=4, d_e=256, k_m=4, m_m=6, c_m=5, dtype=BF),
+    "dsb_128x128x64": P.small(b=20, l=192, d=64, n_a=2, d_h=32, m=2, c=1, k_a=1, n_m=5, d_e=160, k_m=4, m_m=6, c_m=5, dtype=BF),
+    "dsb_128x128x32": P.small(b=20, l=192, d=96, n_a=2, d_h=32, m=2, c=1, k_a=1, n_m=5, d_e=160, k_m=4, m_m=6, c_m=5, dtype=BF),
+    "dsb_64x128x64": P.small(b=10, l=192, d=64, n_a=2, d_h=32, m=2, c=1, k_a=1, n_m=5, d_e=160, k_m=4, m_m=6, c_m=5, dtype=BF),
+    "dsb_own_launches": P.small(b=32, l=512, d=192, n_a=2, d_h=32, m=2, c=1, k_a=1, n_m=16, d_e=160, k_m=8, m_m=8, c_m=4, dtype=BF),
+}
+P.DS_BWD_CONFIGS.update(DS_BWD)
+
+
+@pytest.mark.parametrize("name", list(DS_BWD))
+@pytest.mark.parametrize("flags", [0, R | GE | GP])
+def test_uome_data_selection_backward_tiles(name, flags):
+    P.test_uome_data_selection_backward_parity(name, flags)
 
 
 # --------------------------------------------------------------------------- router backward
