@@ -684,8 +684,9 @@ __global__ __launch_bounds__(NQ *KSPLIT * 64) void attention_mfma_kernel(SmhaArg
 // issue order): at the top of an iteration at most the copies of the STAGES-2 younger tiles may be
 // outstanding, then one barrier publishes every wave's part of the tile and frees the buffer of the tile
 // before for the copies issued right after it.
-// 4096 flags: past that a byte per key would cost the second workgroup of a compute unit (160 KiB: 2 x (64 + 4) KiB
-// fit, and so do the shapes of 128 KiB); the masked lm forward, 32 units of 128 keys at d_h 64, goes 65.6 -> 64.4 us in all.
+// 4096 flags: a choice, not a bound (160 KiB hold 128 KiB of tiles and four times as many); longer masked units were not
+// measured on this kernel and stay on the register-staged one.  The masked lm forward, 32 units of 128 keys at d_h 64, goes
+// 65.6 -> 64.4 us in all.
 constexpr int DMA_PAD_KEYS = 4096;
 template <int DH, int NQ, int KSPLIT, bool PAD>
 __global__ __launch_bounds__(NQ *KSPLIT * 64) void attention_dma_kernel(SmhaArgs a)
@@ -831,8 +832,8 @@ template <int DH, int NQ, int KSPLIT> static void launch_attention_shape(const S
         hipLaunchKernelGGL((attention_mfma_kernel<DH, NQ, KSPLIT, false>), grid, block, 0, st, a);
         return;
     }
-    // (LDS: stages x (K + V tile) per split; every wave the same number of copies; the wait count fits its field)
-    if constexpr ((DH == 64 || DH == 128) && KSPLIT * 4 * 2 * 64 * DH * 2 <= 160 * 1024 && (64 * DH * 2 / 1024) % NQ == 0 &&
+    // (LDS: stages x (K + V tile) per split, and the flags; every wave the same number of copies; the wait count fits its field)
+    if constexpr ((DH == 64 || DH == 128) && KSPLIT * 4 * 2 * 64 * DH * 2 + DMA_PAD_KEYS <= 160 * 1024 && (64 * DH * 2 / 1024) % NQ == 0 &&
                   2 * 2 * (64 * DH * 2 / 1024 / NQ) <= 63) {
         if (!a.pad_mask) {   // V in fp16: tiles copied straight into LDS
             hipLaunchKernelGGL((attention_dma_kernel<DH, NQ, KSPLIT, false>), grid, block, 0, st, a);
