@@ -1,7 +1,6 @@
-// Pipelined MFMA grouped GEMM engine for bf16 storage (gfx950), for the large contractions.
-// Same contract and the same MFMA/epilogue arrangement as gemm_mfma.h (transposed product,
-// weights read from a [k][n] LDS tile with the transposing LDS read, LDS-staged 16-byte stores);
-// what differs is how operands reach LDS and how deep the prefetch is:
+// The grouped GEMM engine (gfx950): every contraction of the layer and of its backward passes, in both storage types.
+// Fragment layout and epilogue are those of gemm_mfma.h (transposed product, weights read from a [k][n] LDS tile with the
+// transposing LDS read, LDS-staged 16-byte stores); here is how operands reach LDS and how deep the prefetch is:
 //
 //  * Operand tiles go from global memory straight into LDS (global_load_lds_dwordx4: 16 bytes per
 //    lane, the 64 lanes of one instruction fill 1 KiB of consecutive LDS bytes starting at M0).

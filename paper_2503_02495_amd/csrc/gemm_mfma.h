@@ -12,7 +12,6 @@
 #pragma once
 #include <type_traits>
 #include <utility>
-#include <type_traits>
 #include "common.h"
 
 namespace uoe {

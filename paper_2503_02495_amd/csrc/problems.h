@@ -1,15 +1,19 @@
-// The four contractions of the layer, each stated as a grouped GEMM "problem":
+// The contractions of the layer, each stated as a grouped GEMM "problem":
 // for a group g, C[M(g), N] = A[M(g), K(g)] * B[K(g), N] with an epilogue, where the rows of A and
 // the rows/columns of B are resolved through the routing indices.  A problem is a small POD
-// passed by value to a GEMM engine; engines ask it for
+// passed by value to the engine (gemm_dma.h), which asks it for
 //   rows(g), kdim(g), ncols()            problem extents
 //   kseg(g)                              length of one K segment (one expert's slice, or all of K)
-//   a_seg_ptr(g, m, seg)   pointer to A[m][seg*kseg]; the segment's kseg elements are contiguous
-//   b_seg_ptr(g, seg, nn)  pointer to B[seg*kseg][nn..nn+8)  (nn % 8 == 0)
-//   b_stride()             elements between consecutive K rows of B inside a segment
-// the fp32 form of the pipelined engine writes four columns of a row at a time:
+//   seg_ctx(g, seg)                      32 bits of routing context of a K segment, looked up once per tile (the engine may not
+//                                        touch global memory through the compiler inside its K loop)
+//   a_ptr_ctx(g, m, seg, ctx)            pointer to A[m][seg*kseg], from that context; the segment's elements are contiguous
+//   b_ptr_ctx(g, seg, nn, ctx)           pointer to B[seg*kseg][nn..nn+8)  (nn % 8 == 0)
+//   b_stride()                           elements between consecutive K rows of B inside a segment
+//   kPrepare / prepare(g, segtab, tid, nthreads)  the workgroup builds its segment list itself and
+//                                        returns K (out-projection: which experts picked this patch)
+// Its fp32 form writes four columns of a row at a time:
 //   epi_f32(v, scale), put4(g, m, nn, v4)   per-element math; the store (residual included)
-// and the bf16 engines 16-byte pieces of output rows:
+// and its bf16 form 16-byte pieces of output rows:
 //   kColScale / col_scale(g, nn)  a per-column factor (constant over 8-column groups), fetched
 //                                 once per tile before the K loop
 //   epi(v, scale)                 per-element math
@@ -21,12 +25,6 @@
 //                                 non-temporal versions of the two accesses above, for outputs and
 //                                 residuals that this call touches exactly once and that are too large
 //                                 for the caches
-// and, for the pipelined engine (which may not touch global memory through the compiler inside
-// its K loop),
-//   seg_ctx(g, seg)               32 bits of routing context of a K segment, looked up once per tile
-//   a_ptr_ctx / b_ptr_ctx         a_seg_ptr / b_seg_ptr computed from that context, no lookups
-//   kPrepare / prepare(g, segtab, tid, nthreads)  the workgroup builds its segment list itself and
-//                                 returns K (out-projection: which experts picked this patch)
 // K and N are concatenations of per-expert segments of length `width`; since width % 8 == 0 an
 // 8-element run never straddles two experts.
 #pragma once
@@ -106,7 +104,7 @@ template <typename T, bool F32 = false> struct QkvProblem {
             t = e2; e2 = t * cs - e3 * sn; e3 = t * sn + e3 * cs;
         }
     }
-    int v_f16 = 0;  // MFMA engines, bf16 storage: v is written as fp16 (what the attention kernel's P V product takes)
+    int v_f16 = 0;  // bf16 storage: v is written as fp16 (what the attention kernel's P V product takes)
     __device__ bool f16_col(int nn) const { return v_f16 && nn >= 2 * d_h; }
     T *v_copy = nullptr;   // with v_f16: v in bf16 as well (the backward pass's operand)
     __device__ void put4_copy(int g, int r, int nn, uint2 piece) const
@@ -127,12 +125,14 @@ template <typename T, bool F32 = false> struct QkvProblem {
     }
     __device__ int kseg(int) const { return d; }
     __device__ long b_stride() const { return d_h; }
-    __device__ const T *a_seg_ptr(int g, int r, int) const
+    // K is one segment, rows and columns are resolved once before the loop
+    __device__ uint32_t seg_ctx(int, int) const { return 0; }
+    __device__ const T *a_ptr_ctx(int g, int r, int, uint32_t) const
     {
         const int bb = g / kact;
         return x + ((size_t)bb * l + token(g, r)) * d;
     }
-    __device__ const T *b_seg_ptr(int g, int, int nn) const
+    __device__ const T *b_ptr_ctx(int g, int, int nn, uint32_t) const
     {
         const int i = expert(g);
         if (w_nk) return wq + ((size_t)i * d_h + nn) * d;
@@ -147,11 +147,6 @@ template <typename T, bool F32 = false> struct QkvProblem {
         T *o = which == 0 ? q : (which == 1 ? k : v);
         *reinterpret_cast<float4 *>(o + ((size_t)g * l_a + r) * d_h + (nn - which * d_h)) = val;
     }
-    // pipelined engine: K is one segment, rows and columns are resolved once before the loop
-    __device__ uint32_t seg_ctx(int, int) const { return 0; }
-    __device__ const T *a_ptr_ctx(int g, int r, int seg, uint32_t) const { return a_seg_ptr(g, r, seg); }
-    __device__ const T *b_ptr_ctx(int g, int seg, int nn, uint32_t) const { return b_seg_ptr(g, seg, nn); }
-    // vector epilogue (MFMA engines)
     static constexpr bool kPrepare = false;
     static constexpr bool kRowScale = false;
     static constexpr bool kColScale = true;
@@ -225,7 +220,7 @@ template <typename T> struct OutProjProblem {
         if (flags & F_RESIDUAL) val = add4_f32(val, reinterpret_cast<const float *>(x) + at);
         *reinterpret_cast<float4 *>(out + at) = val;
     }
-    // pipelined engine: per K segment, the slot in bits 0-4, the expert in bits 20-25 and the hi/lo part in bit 26.
+    // per K segment, the slot in bits 0-4, the expert in bits 20-25 and the hi/lo part in bit 26.
     // The workgroup builds the list of its group's segments itself (prepare), straight from the routing indices:
     // thread (slot s, pick t) notes which of the group's patches slot s picked as which pick (at most one t per slot and
     // patch), then the slots that picked any are listed in slot order, which fixes the summation order.  Returns K;
@@ -336,18 +331,15 @@ template <typename T, bool RAW = false, bool EXACT = false> struct UomeUpProblem
     __device__ int ncols() const { return kact * d_e; }
     __device__ int kseg(int) const { return d; }
     __device__ long b_stride() const { return d_e; }
-    __device__ const T *a_seg_ptr(int g, int r, int) const { return u + ((size_t)g * l + r) * d; }
-    __device__ const T *b_seg_ptr(int g, int, int nn) const
+    // no per-segment lookups (K is one segment; the column's expert is resolved once, before the loop)
+    __device__ uint32_t seg_ctx(int, int) const { return 0; }
+    __device__ const T *a_ptr_ctx(int g, int r, int, uint32_t) const { return u + ((size_t)g * l + r) * d; }
+    __device__ const T *b_ptr_ctx(int g, int, int nn, uint32_t) const
     {
         const int s = nn / d_e;
         const int i = clampi(expert_idx[g * kact + s], n);
         return a_in + (size_t)i * d * d_e + (nn - s * d_e);
     }
-    // pipelined engine: no per-segment lookups (K is one segment; the column's expert is resolved
-    // once, before the loop)
-    __device__ uint32_t seg_ctx(int, int) const { return 0; }
-    __device__ const T *a_ptr_ctx(int g, int r, int seg, uint32_t) const { return a_seg_ptr(g, r, seg); }
-    __device__ const T *b_ptr_ctx(int g, int seg, int nn, uint32_t) const { return b_seg_ptr(g, seg, nn); }
     __device__ float epi_f32(float val, float gate) const { return raw ? val : silu(val) * gate; }
     __device__ void put4(int g, int r, int nn, float4 val) const
     {
@@ -395,11 +387,12 @@ template <typename T, bool EXACT = false> struct UomeDsUpProblem {
     {
         return clampi(patch_idx[((size_t)(g / kact) * n + expert(g)) * c + r / l_p], m);
     }
-    __device__ const T *a_seg_ptr(int g, int r, int) const
+    __device__ uint32_t seg_ctx(int, int) const { return 0; }
+    __device__ const T *a_ptr_ctx(int g, int r, int, uint32_t) const
     {
         return u + ((size_t)(g / kact) * l + patch(g, r) * l_p + r % l_p) * d;
     }
-    __device__ const T *b_seg_ptr(int g, int, int nn) const { return a_in + (size_t)expert(g) * d * d_e + nn; }
+    __device__ const T *b_ptr_ctx(int g, int, int nn, uint32_t) const { return a_in + (size_t)expert(g) * d * d_e + nn; }
     __device__ float row_scale(int g, int r) const
     {
         const int bb = g / kact, i = expert(g);
@@ -412,9 +405,6 @@ template <typename T, bool EXACT = false> struct UomeDsUpProblem {
     {
         *reinterpret_cast<float4 *>(hidden + ((size_t)g * l_a + r) * d_e + nn) = val;
     }
-    __device__ uint32_t seg_ctx(int, int) const { return 0; }
-    __device__ const T *a_ptr_ctx(int g, int r, int seg, uint32_t) const { return a_seg_ptr(g, r, seg); }
-    __device__ const T *b_ptr_ctx(int g, int seg, int nn, uint32_t) const { return b_seg_ptr(g, seg, nn); }
     static constexpr bool kPrepare = false;
     static constexpr bool kRowScale = true;
     static constexpr bool kColScale = false;
@@ -445,18 +435,12 @@ template <typename T> struct UomeDownProblem {
     __device__ int ncols() const { return d; }
     __device__ int kseg(int) const { return d_e; }
     __device__ long b_stride() const { return d; }
-    __device__ const T *a_seg_ptr(int g, int r, int seg) const
+    // the segment's expert, looked up once before the loop
+    __device__ uint32_t seg_ctx(int g, int seg) const { return (uint32_t)clampi(expert_idx[g * kact + clampi(seg, kact)], n); }
+    __device__ const T *a_ptr_ctx(int g, int r, int seg, uint32_t) const
     {
         return hidden + ((size_t)g * l + r) * ((size_t)kact * d_e) + (size_t)clampi(seg, kact) * d_e;
     }
-    __device__ const T *b_seg_ptr(int g, int seg, int nn) const
-    {
-        const int i = clampi(expert_idx[g * kact + clampi(seg, kact)], n);
-        return a_out + (size_t)i * d_e * d + nn;
-    }
-    // pipelined engine: the segment's expert, looked up once before the loop
-    __device__ uint32_t seg_ctx(int g, int seg) const { return (uint32_t)clampi(expert_idx[g * kact + clampi(seg, kact)], n); }
-    __device__ const T *a_ptr_ctx(int g, int r, int seg, uint32_t) const { return a_seg_ptr(g, r, seg); }
     __device__ const T *b_ptr_ctx(int, int, int nn, uint32_t i) const { return a_out + (size_t)i * d_e * d + (size_t)nn * (w_nk ? d_e : 1); }
     __device__ float epi_f32(float val, float) const { return val; }
     __device__ void put4(int g, int r, int nn, float4 val) const
