@@ -192,6 +192,9 @@ int uoe_gather(const uoe_block_desc *blk, const void *x, const int32_t *expert_i
  *   UOE_FLAG_CAUSAL     every expert uses the leading l_a x l_a lower-triangular mask: key
  *                       position <= query position in the compacted sequence (Fig. 4)
  * A query row with no admissible key contributes nothing.
+ * Arithmetic.  fp32 storage, and bf16 storage with d % 32 != 0 or d_h not in {32, 64, 128}: attention in fp32 products and
+ * probabilities (bf16 storage: q, k and v rounded to bf16).  bf16 storage otherwise: bf16 products for the scores, fp16
+ * probabilities (11 bits) and v in fp16, so that |v| must stay below 65504 (a larger value is infinite there).
  */
 int uoe_smha_forward(const uoe_block_desc *blk, const void *x, const void *wq, const void *wk,
                      const void *wv, const void *wo, const int32_t *expert_idx,
@@ -270,12 +273,13 @@ int uoe_uome_down(const uoe_block_desc *blk, const void *hidden, const void *a_o
  *                       everywhere without UOE_FLAG_GATE_EXPERT; may be NULL
  *   d_patch_gate [b,n,m] fp32 (data selection) dL/d(patch_gate) on the selected patches of the
  *                       active experts, zero elsewhere and without UOE_FLAG_GATE_PATCH; may be NULL
- * Two paths.  bf16 storage with l, d and d_e multiples of 32, b <= 128 (and l_p a multiple of 32 in
- * data-selection mode) runs on the matrix cores, intermediates (u A^I, d_out A^O^T) kept in bf16
- * between the kernels.  Every other expert-selection request (fp32 storage, any l, d, d_e) runs on
- * the matrix cores as well, with fp32 intermediates (bf16 storage: fp32, or pairs of bf16 values where
- * they enter another product).  Data selection outside the first path
- * is UOE_ERR_UNSUPPORTED.  Outputs must not alias inputs.
+ * Two paths, both on the matrix cores.  bf16 storage with l, d and d_e multiples of 32, b <= 128 (and l_p a
+ * multiple of 32 in data-selection mode) runs on bf16 operands: dL/d(u A^I) and the hidden activations are rounded to
+ * bf16 between the kernels, u A^I and d_out A^O^T too in data-selection mode and in launches large enough for 256-column
+ * tiles (else they stay in fp32 registers).  Every other expert-selection request (fp32 storage, any l, d, d_e) has fp32
+ * intermediates (bf16 storage: fp32, or pairs of bf16 values where they enter another product); its workspace holds one set
+ * of fp32 partial tiles of both weight gradients per 128 samples, at least, and at most 8 of them up to b = 1024.
+ * Data selection outside the first path is UOE_ERR_UNSUPPORTED.  Outputs must not alias inputs.
  * Deterministic: fixed summation order, no atomics.  ws: at least
  * uoe_uome_backward_workspace_bytes(blk) bytes (0 = descriptor invalid or unsupported).
  */
@@ -301,7 +305,8 @@ typedef struct {
  *   dL = gate * (dgate - sum over experts of gate * dgate) per patch
  * A router whose weights are NULL is skipped (its gate and gradient pointers are ignored); at
  * least one must be present; w_b and w_a come together.  Storage dtype fp32 or bf16, fp32
- * arithmetic.  Limits of this build: b <= 128, d <= 2048, (n*m + 64*n) * 4 + d*n*elem <= 64 KiB.
+ * arithmetic.  Limits of the call: b <= 128, d <= 2048, (n*m + 64*n) * 4 + d*n*elem <= 64 KiB.  The formulas hold for any
+ * gates; where a row's gates sum to one up to rounding, as the forward call's do, the sum is taken to be one.
  * ws: at least uoe_route_backward_workspace_bytes(blk) bytes (0 = invalid or unsupported).
  */
 size_t uoe_route_backward_workspace_bytes(const uoe_block_desc *blk);
@@ -332,7 +337,7 @@ typedef struct {
  * {32, 64, 128}, d % 32 == 0, l_p % 32 == 0 and b <= 128 runs on bf16 products throughout; every other
  * request (fp32 storage, a 14-token patch, d_h = 16) keeps its intermediates in fp32 (bf16 storage:
  * fp32, or pairs of bf16 values where they enter another product), attention in fp32 products;
- * UOE_ERR_UNSUPPORTED there beyond b*k*l_a*l_a = 2^31 or c > 1024.
+ * UOE_ERR_UNSUPPORTED there beyond b*k*l_a*l_a = 2^31 (a limit on the attention work of one call).
  * Deterministic: fixed summation order, no atomics.  ws: at least
  * uoe_smha_backward_workspace_bytes(blk) bytes (0 = descriptor invalid or unsupported).
  */
@@ -400,7 +405,8 @@ typedef struct {
  *   routing_a / routing_m: the routing results of the forward call (its uoe_routing_out copies),
  *       read only; expert_idx and, for SMHA, patch_idx are required, a gate is required when its
  *       flag is set.
- *   u: the SMHA output of the forward pass, or NULL to have it recomputed from x.
+ *   u: the SMHA output of the forward pass, or NULL to have it recomputed from x (the workspace is the same size either way:
+ *       it has room for the q, k, v and attention results that a recomputation leaves to the SMHA backward).
  *   dwa, d_a_in, d_a_out: gradients of the block weights; dra / drm: gradients of the routers'
  *       weights (required when the block has a router; a router's gate flag must then be set,
  *       otherwise its weights have no influence on the output: UOE_ERR_INVALID_ARG).

@@ -70,8 +70,7 @@ struct SmhaWs {
 SmhaWs smha_ws(const uoe_block_desc *d)
 {
     SmhaWs w;
-    const size_t l_a = (((size_t)d->c * (d->l / d->m)) + 7) & ~(size_t)7;  // v may be stored transposed, rows padded to 8
-    const size_t one = up((size_t)d->b * d->k * l_a * d->width * elem_size(d->dtype));
+    const size_t l_a = (size_t)d->c * (d->l / d->m), one = up((size_t)d->b * d->k * l_a * d->width * elem_size(d->dtype));
     size_t off = 0;
     w.q = off; off += one;
     w.k = off; off += one;
@@ -220,7 +219,7 @@ int check_smha_bwd(const uoe_block_desc *blk)
     const int rc = check_desc(blk, DESC_SMHA);
     if (rc != UOE_OK) return rc;
     if (!smha_bwd_mfma(blk)) {
-        // any-shape path: attention work of one call; the gate kernel holds c sums
+        // any-shape path: a limit of the call, on its attention work (nothing is sized by l_a^2); the gate kernel holds c sums
         const size_t l_a = (size_t)blk->c * (blk->l / blk->m);
         if (blk->c > 1024 || (size_t)blk->b * blk->k * l_a * l_a > ((size_t)1 << 31)) return UOE_ERR_UNSUPPORTED;
     }
@@ -250,7 +249,7 @@ int check_route_bwd(const uoe_block_desc *blk)
     const int rc = check_desc(blk, DESC_ROUTE);
     if (rc != UOE_OK) return rc;
     if (blk->b > 128 || blk->d > 2048) return UOE_ERR_UNSUPPORTED;
-    // size limit of the data router: dL [n,m], 64 rows of U [64,n] and W_B [d,n] together fit 64 KiB
+    // a limit of the call (dL [n,m], 64 rows of U [64,n] and W_B [d,n] together within 64 KiB); the kernels hold less at a time
     const size_t lds = ((size_t)blk->n * blk->m + 64 * (size_t)blk->n) * sizeof(float) + 16 + (size_t)blk->d * blk->n * elem_size(blk->dtype);
     if (lds > 64 * 1024) return UOE_ERR_UNSUPPORTED;
     return UOE_OK;
@@ -844,8 +843,9 @@ struct LayerBwdWs {
     size_t keep_q, keep_k, keep_v, keep_o, keep_o_lo, keep_lse;
 };
 // The recomputation of u leaves q, k, v (and the attention's results) to the SMHA backward where both passes hold them in the
-// same form: fp32 storage, and the bf16 matrix-core path (whose projections and attention would otherwise run twice:
-// 55 us of the largest shape's pass, 16 us of lm's).
+// same form: fp32 storage, and the bf16 path of the 32-multiples (whose projections and attention would otherwise run twice:
+// 55 us of the largest shape's pass, 16 us of lm's).  The room is there also when the caller passes u: the sizing call does
+// not know.
 static bool layer_bwd_keeps(const uoe_block_desc *smha)
 {
     if (smha->dtype != UOE_BF16) return true;

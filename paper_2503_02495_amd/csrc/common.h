@@ -305,7 +305,7 @@ hipError_t launch_probe_copy(const void *src, void *dst, size_t bytes, hipStream
 hipError_t launch_probe_read(const void *src, size_t bytes, uint32_t *sink, hipStream_t st);
 hipError_t launch_probe_mfma(const void *operands, int iters, float *sink, hipStream_t st);
 
-// host-side sizing shared by api.cpp and the launchers
+// host-side sizing shared by api.hip and the launchers
 int route_tokens_per_chunk(int b, int l);
 int route_expert_mfma_tokens_per_chunk(int b, int l, int d, int n);
 int route_data_tokens_per_chunk(int b, int l, int d, int n, bool bf16);

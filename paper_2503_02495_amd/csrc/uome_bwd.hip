@@ -5,7 +5,7 @@
 //   H = SiLU(Z) * w      (column block s scaled by w_s)
 //   h = (u) + H W2_b     W2_b = [A^O_i(0); ...; A^O_i(k-1)]              [l, d]
 // Backward for an upstream gradient d_out = dL/dh:
-//   dH  = d_out W2_b^T                                   GEMM, weights transposed once per call
+//   dH  = d_out W2_b^T                                   GEMM, A^O_i read as [n][k]
 //   dZ  = dH * w * SiLU'(Z),  H as above,  d_gate[b,i(s)] = sum over block s of dH * SiLU(Z)
 //   d_u = (d_out) + dZ W1_b^T                            GEMM
 //   dA^O_i = sum_{(b,s): i(s) = i} H_{b,s}^T d_out_b     GEMM over the tokens of those samples
@@ -13,8 +13,10 @@
 // All five contractions run on the pipelined MFMA engine, on operands as they lie in memory: the products with a
 // transposed weight read it as [n][k], the weight gradients read H, dZ, u and d_out token-major ([k][m], [k][n]); dA^I
 // is formed as its transpose (dZ^T u) and turned back by the reduction that adds the split-K partials.  The
-// elementwise middle (dZ, H and the gate gradient from Z and dH) is the epilogue of the dH contraction: dH never
-// reaches memory, Z is read there and nowhere else.  Z, dZ and H are kept in the storage dtype between the kernels.
+// elementwise middle (dZ, H and the gate gradient from Z and dH) is the epilogue of the dH contraction, and dH never
+// reaches memory.  Where the tiles leave room (gemm_dma_dual_fits) Z is formed by the same workgroup and does not
+// either; otherwise (256-column tiles, data selection) it is written in the storage dtype and read there and nowhere else.
+// dZ and H are kept in the storage dtype between the kernels.
 // Against separate dH, middle and weight-transposing launches with token-minor copies of dZ and H (b 4, l 8192,
 // d 1024, 8 of 16 experts of 256): 15.7 + 144.5 + 131.8 us -> 212 us, and the weight gradients 317 -> 285 us.
 #include "common.h"

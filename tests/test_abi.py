@@ -173,7 +173,7 @@ def test_smha_uome_layer_argument_validation():
 def test_backward_argument_validation():
     """The backward entry points: unsupported shapes give a zero workspace size and
     UOE_ERR_UNSUPPORTED, bad pointer combinations UOE_ERR_INVALID_ARG, all before any launch.  Shapes
-    off the matrix-core grid and fp32 storage are taken by the vector-ALU path, except the UoME block
+    off the 32-multiples and fp32 storage are taken by the any-shape path, except the UoME block
     with patch-wise data selection."""
     assert ctypes.sizeof(B.SmhaWeightGrads) == 4 * 8 and ctypes.sizeof(B.RouterGrads) == 3 * 8
     big = 1 << 40
@@ -181,7 +181,7 @@ def test_backward_argument_validation():
     # UoME backward, expert-selection mode: every shape and both storage types
     u = B.block_desc(2, 64, 64, 4, 2, 1, 1, 64, B.BF16, fl)
     assert B.uome_backward_workspace_bytes(u) > 0
-    # vector-ALU path (fp32 storage): Z/H and dH/dZ in fp32, plus the weight gradients' partial tiles, here
+    # any-shape path (fp32 storage): Z/H and dH/dZ in fp32, plus the weight gradients' partial tiles, here
     # 4 ranges of (sample, slot) pairs (b * k = 4 caps the 8 that so few tiles would ask for)
     assert B.uome_backward_workspace_bytes(B.block_desc(2, 64, 64, 4, 2, 1, 1, 64, B.F32, fl)) == \
         2 * (2 * 64 * 2 * 64 * 4) + 2 * 4 * 4 * 64 * 64 * 4
@@ -207,8 +207,8 @@ def test_backward_argument_validation():
     assert dsb(*bad, ws_bytes=big) == B.ERR_INVALID_ARG
     bad = list(okd); bad[6] = None                      # patch gate flag without patch gates
     assert dsb(*bad, ws_bytes=big) == B.ERR_INVALID_ARG
-    # SMHA backward: every shape and both storage types (d_h in {32, 64, 128} with l_p a multiple of 32 on the
-    # matrix cores, the rest on the vector ALU, whose [units, l_a, l_a] arrays bound the size)
+    # SMHA backward: every shape and both storage types (bf16 with d_h in {32, 64, 128} and l_p a multiple of 32 on kernels
+    # of its own, the rest on the any-shape path, where b * k * l_a^2 is limited)
     a = B.block_desc(2, 128, 64, 4, 2, 4, 2, 32, B.BF16, fl | B.FLAG_GATE_PATCH)
     assert B.smha_backward_workspace_bytes(a) > 0
     assert B.smha_backward_workspace_bytes(B.block_desc(2, 128, 64, 4, 2, 8, 2, 32, B.BF16, fl)) > 0    # l_p = 16

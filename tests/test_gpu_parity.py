@@ -380,12 +380,12 @@ def test_uome_backward_parity(name, flags):
 
 
 def test_uome_backward_rejects_unsupported():
-    """Shapes off the matrix-core grid and fp32 storage run on the vector-ALU path in expert-selection
+    """Shapes off the 32-multiples and fp32 storage run on the any-shape path in expert-selection
     mode; with patch-wise data selection they are refused (no workspace size, UNSUPPORTED)."""
     blk = B.block_desc(2, 40, 64, 2, 1, 1, 1, 32, B.BF16, R)
-    assert B.uome_backward_workspace_bytes(blk) > 0        # l % 32 != 0, expert selection: vector-ALU path
+    assert B.uome_backward_workspace_bytes(blk) > 0        # l % 32 != 0, expert selection: any-shape path
     blk = B.block_desc(2, 64, 64, 2, 1, 1, 1, 32, B.F32, R)
-    assert B.uome_backward_workspace_bytes(blk) > 0        # fp32 storage, expert selection: vector-ALU path
+    assert B.uome_backward_workspace_bytes(blk) > 0        # fp32 storage, expert selection: any-shape path
     blk = B.block_desc(2, 64, 64, 2, 1, 4, 2, 32, B.F32, R)
     assert B.uome_backward_workspace_bytes(blk) == 0       # fp32 storage with data selection
     blk = B.block_desc(2, 56, 64, 2, 1, 4, 2, 32, B.BF16, R)
@@ -417,7 +417,7 @@ CA = B.FLAG_CAUSAL
 # gates, hence a bound of 3e-2 on the worst element and of 6e-3 on the average.
 SMHA_BWD_TOL = 3e-2
 BWD_FRO_TOL = 6e-3
-# fp32 storage (the vector-ALU backward: fp32 arithmetic and fp32 intermediates): each of the ~6 chained
+# fp32 storage (the any-shape backward: fp32 arithmetic and fp32 intermediates): each of the ~6 chained
 # contractions of up to d terms adds sqrt(d) * 2^-24 = 1e-6 relative rms, the worst of 10^5 elements sits
 # 5 sigma out: 1e-5 expected, bound 1e-4 on the worst element (the forward's fp32 bound) and 1e-5 on the
 # average.  bf16 storage on that path rounds only the outputs, so the bf16 bounds hold with room to spare.
@@ -447,7 +447,7 @@ ROUTER_GRAD_TOL = 5e-2
                                         for fl in (0, R | GE | GP, R | GE | GP | CA)]
                          + [("vit", R | GE | GP), ("bf16_ragged", R | GE | GP | CA), ("longrange", R | GE | GP),
                             ("large", R | GE | GP | CA),
-                            ("b1_n1", R | GE | GP)])   # one unit: the weight gradients of the vector-ALU path in one range
+                            ("b1_n1", R | GE | GP)])   # one unit: the weight gradients of the any-shape path in one part
 def test_smha_backward_parity(name, flags):
     run_smha_backward(name, flags, 0)
 
@@ -835,7 +835,7 @@ def test_balance_loss_parity(name):
 import dataclasses
 
 DS_CONFIGS = {
-    # fp32 (vector-ALU path), ragged patch length
+    # fp32, ragged patch length
     "ds_f32_lp14": small(b=3, l=56, d=24, n_a=3, d_h=8, m=4, c=3, k_a=2, n_m=3, d_e=16, k_m=2, m_m=4, c_m=3),
     "ds_f32_lp1": small(b=2, l=12, d=8, n_a=2, d_h=8, m=6, c=1, k_a=1, n_m=4, d_e=8, k_m=4, m_m=12, c_m=5),
     # bf16: units of 128 rows, patches of 32 rows
@@ -844,7 +844,7 @@ DS_CONFIGS = {
     # bf16: patches of 80 rows (not a tile multiple), K of the first layer not a multiple of 64
     "ds_bf16_lp80": small(b=2, l=320, d=96, n_a=4, d_h=32, m=4, c=2, k_a=2, n_m=5, d_e=32, k_m=3, m_m=4, c_m=2,
                           dtype=synth.BF16),
-    # bf16: units of at most 64 rows (register-staged engine for the first layer), noise on the routers
+    # bf16: units of at most 64 rows (64-row tiles in the first layer), noise on the routers
     "ds_bf16_small_units": small(b=4, l=96, d=128, n_a=4, d_h=32, m=6, c=2, k_a=2, n_m=8, d_e=96, k_m=5, m_m=12,
                                  c_m=3, dtype=synth.BF16, router_noise=True),
     # the language-modeling shape with half of the patches kept per MLP expert
