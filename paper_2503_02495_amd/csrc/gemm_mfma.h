@@ -82,9 +82,9 @@ template <typename P, typename = void> struct has_f16_cols {
 template <typename P> struct has_f16_cols<P, std::void_t<decltype(&P::f16_col)>> {
     static constexpr bool value = true;
 };
-// problems that rotate pairs of columns on the way out: rotates(first column of 8), rotate(row, column, 4 values)
+// problems that rotate pairs of columns on the way out: kRotates, rotates(first column of 8), rotate(row, column, 4 values)
 template <typename P, typename = void> struct has_rotation : std::false_type {};
-template <typename P> struct has_rotation<P, std::void_t<decltype(&P::rotates)>> : std::true_type {};
+template <typename P> struct has_rotation<P, std::void_t<decltype(P::kRotates)>> : std::bool_constant<P::kRotates> {};
 // two fp32 -> packed fp16, round to nearest even
 __device__ __forceinline__ uint32_t pack2_f16_rn(float a, float b)
 {

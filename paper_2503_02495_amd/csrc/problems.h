@@ -65,7 +65,7 @@ __device__ __forceinline__ uint4 add8_bf16(uint4 v, uint4 r)
 // group = active unit (b, slot s); M = l_a; K = d; N = 3*d_h laid out [q | k | v].
 // F32: bf16 operands, fp32 rows into q32 (projection w at q32 + w * q32_plane) instead.
 // w_nk: the single projection (nout = 1) multiplies by the transpose of wq [n, d_h, d] (engine flag GEMM_B_NK).
-template <typename T, bool F32 = false> struct QkvProblem {
+template <typename T, bool F32 = false, bool ROPE = false> struct QkvProblem {
     typedef typename storage_elem<T>::type Elem;
     const T *x, *wq, *wk, *wv;
     const int32_t *expert_idx, *patch_idx;
@@ -82,12 +82,12 @@ template <typename T, bool F32 = false> struct QkvProblem {
     int l, d, n, kact, m, c, l_p, l_a, d_h;
     float q_scale;  // folded into q on the way out (1 for the plain layout)
     int nout;       // 3: q, k and v; 1: the first projection only (N = d_h)
-    // bf16 rows: the last rope_dim dims of q and k rotated by the row's position in the compacted sequence (Eq. 32),
+    // ROPE, bf16 rows: the last rope_dim dims of q and k rotated by the row's position in the compacted sequence (Eq. 32),
     // in fp32 before the one rounding (an in-place kernel behind the projection took 2.8-3.7 us and rounded twice)
+    static constexpr bool kRotates = ROPE;
     int rope_dim = 0;
     __device__ bool rotates(int col8) const
     {
-        if (rope_dim <= 0) return false;
         const int which = col8 / d_h, dh = col8 - which * d_h;
         return which < 2 && dh + 8 > d_h - rope_dim;
     }

@@ -880,9 +880,9 @@ static hipError_t launch_attention_mfma(const SmhaArgs &a, hipStream_t st)
     return launch_attention_mfma_dh<128>(a, st);
 }
 
-template <typename T> static QkvProblem<T> make_qkv(const SmhaArgs &a)
+template <typename T, bool ROPE> static QkvProblem<T, false, ROPE> make_qkv(const SmhaArgs &a)
 {
-    QkvProblem<T> qp;
+    QkvProblem<T, false, ROPE> qp;
     qp.x = static_cast<const T *>(a.x);
     qp.wq = static_cast<const T *>(a.wq);
     qp.wk = static_cast<const T *>(a.wk);
@@ -896,6 +896,7 @@ template <typename T> static QkvProblem<T> make_qkv(const SmhaArgs &a)
     qp.l_p = a.l / a.m; qp.l_a = a.c * qp.l_p; qp.d_h = a.d_h;
     qp.q_scale = 1.0f;
     qp.nout = 3;
+    qp.rope_dim = ROPE ? a.rope_dim : 0;
     qp.q32 = nullptr;
     return qp;
 }
@@ -924,9 +925,9 @@ template <typename T> static hipError_t smha_f32(const SmhaArgs &a, hipStream_t 
     const int l_p = a.l / a.m, l_a = a.c * l_p, units = a.b * a.k;
     hipError_t err;
     if (!(a.skip & SMHA_STEP_QKV)) {
-        QkvProblem<T> qp = make_qkv<T>(a);
-        qp.rope_dim = BF ? a.rope_dim : 0;
-        if ((err = launch_gemm_tail<0>(qp, units, l_a, 3 * a.d_h, st)) != hipSuccess) return err;
+        if (BF && a.rope_dim > 0) err = launch_gemm_tail<0>(make_qkv<T, BF>(a), units, l_a, 3 * a.d_h, st);
+        else err = launch_gemm_tail<0>(make_qkv<T, false>(a), units, l_a, 3 * a.d_h, st);
+        if (err != hipSuccess) return err;
         if (!BF && (err = launch_rope_f32(a, st)) != hipSuccess) return err;
     }
     if (!(a.skip & SMHA_STEP_ATTENTION) && (err = launch_attention_f32<T>(a, st)) != hipSuccess) return err;
@@ -956,40 +957,44 @@ template <typename OP> static hipError_t launch_outproj_dma(const OP &op, int gr
     return launch_gemm_dma<OP, 64, 128, 32, 2, 2, 4, 2>(op, groups, rows, d, st);
 }
 
-// projections, rotary embedding and attention of the MFMA path
-hipError_t launch_smha_qkv_attention(const SmhaArgs &a, hipStream_t st)
+// Projections of the MFMA path.  ROPE apart at compile time: with the rotation behind a run-time test calls without it were
+// 1.2 % slower (the layer at 8 x 512 x 512 62.2 -> 62.9 us; apart 61.0).
+template <bool ROPE> static hipError_t launch_projections(const SmhaArgs &a, hipStream_t st)
 {
-    typedef QkvProblem<bf16_t> QP;
+    typedef QkvProblem<bf16_t, false, ROPE> QP;
     const int l_p = a.l / a.m, l_a = a.c * l_p, units = a.b * a.k;
-    hipError_t err;
-    QP qp = make_qkv<bf16_t>(a);
+    QP qp = make_qkv<bf16_t, ROPE>(a);
     qp.q_scale = 1.4426950408889634f / sqrtf((float)a.d_h);  // base-2 softmax in the MFMA kernel
     qp.v_f16 = !a.keep_v_bf16;
-    qp.rope_dim = a.rope_dim;
     qp.v_copy = static_cast<bf16_t *>(a.v_copy);
     // 64x64 tiles (one 64-column stretch of q, k or v: the gathered rows are read three times, out of L2, for three times
     // the workgroups, three per compute unit) up to 1024 of them; one workgroup for q, k and v beyond.  us, looped:
     // 32 units of 128 rows x 512 x 192 5.9 (32x64 tiles 7.0), 32 of 512 x 256 x 96 5.9 (128x128 8.9), 64 of 256 x 768 x 192 11.6
     // (64x192 13.2), 384 of 56 x 384 x 192 11.9 against 11.7, 32 of 1024 x 1024 x 192 24.2 with 128x192 (64x64 26.5)
-    auto projections = [&]() -> hipError_t {
-        const int N = 3 * a.d_h;
-        const bool k64 = a.d % 64 == 0;
-        const long t64 = (long)units * ((l_a + 63) / 64) * ((N + 63) / 64);
-        if (k64 && l_a > 32 && t64 <= 1024) return launch_gemm_dma<QP, 64, 64, 64, 2, 2, 3, 3>(qp, units, l_a, N, st);
-        if (a.d_h == 64) {
-            if (l_a >= 256) return k64 ? launch_gemm_dma<QP, 128, 192, 64, 2, 2, 3>(qp, units, l_a, N, st)
-                                       : launch_gemm_dma<QP, 128, 192, 32, 2, 2, 3, 2>(qp, units, l_a, N, st);
-            if (l_a > 32) return launch_gemm_dma<QP, 64, 192, 32, 2, 2, 3, 2>(qp, units, l_a, N, st);
-            if (k64 && (long)units < 256) return launch_gemm_dma<QP, 32, 64, 64, 1, 2, 4>(qp, units, l_a, N, st);
-            return k64 ? launch_gemm_dma<QP, 32, 192, 64, 1, 2, 4>(qp, units, l_a, N, st)
-                       : launch_gemm_dma<QP, 32, 192, 32, 1, 2, 4>(qp, units, l_a, N, st);
-        }
-        if (l_a > 32) return l_a > 64 ? launch_gemm_dma<QP, 128, 128, 32, 2, 4, 3, 4>(qp, units, l_a, N, st)
-                                      : launch_gemm_dma<QP, 64, 128, 32, 2, 4, 4, 4>(qp, units, l_a, N, st);
-        return k64 ? launch_gemm_dma<QP, 32, 128, 64, 1, 2, 4>(qp, units, l_a, N, st)
-                   : launch_gemm_dma<QP, 32, 128, 32, 1, 2, 4>(qp, units, l_a, N, st);
-    };
-    if (!(a.skip & SMHA_STEP_QKV) && (err = projections()) != hipSuccess) return err;
+    const int N = 3 * a.d_h;
+    const bool k64 = a.d % 64 == 0;
+    const long t64 = (long)units * ((l_a + 63) / 64) * ((N + 63) / 64);
+    if (k64 && l_a > 32 && t64 <= 1024) return launch_gemm_dma<QP, 64, 64, 64, 2, 2, 3, 3>(qp, units, l_a, N, st);
+    if (a.d_h == 64) {
+        if (l_a >= 256) return k64 ? launch_gemm_dma<QP, 128, 192, 64, 2, 2, 3>(qp, units, l_a, N, st)
+                                   : launch_gemm_dma<QP, 128, 192, 32, 2, 2, 3, 2>(qp, units, l_a, N, st);
+        if (l_a > 32) return launch_gemm_dma<QP, 64, 192, 32, 2, 2, 3, 2>(qp, units, l_a, N, st);
+        if (k64 && (long)units < 256) return launch_gemm_dma<QP, 32, 64, 64, 1, 2, 4>(qp, units, l_a, N, st);
+        return k64 ? launch_gemm_dma<QP, 32, 192, 64, 1, 2, 4>(qp, units, l_a, N, st)
+                   : launch_gemm_dma<QP, 32, 192, 32, 1, 2, 4>(qp, units, l_a, N, st);
+    }
+    if (l_a > 32) return l_a > 64 ? launch_gemm_dma<QP, 128, 128, 32, 2, 4, 3, 4>(qp, units, l_a, N, st)
+                                  : launch_gemm_dma<QP, 64, 128, 32, 2, 4, 4, 4>(qp, units, l_a, N, st);
+    return k64 ? launch_gemm_dma<QP, 32, 128, 64, 1, 2, 4>(qp, units, l_a, N, st)
+               : launch_gemm_dma<QP, 32, 128, 32, 1, 2, 4>(qp, units, l_a, N, st);
+}
+
+// projections, rotary embedding and attention of the MFMA path
+hipError_t launch_smha_qkv_attention(const SmhaArgs &a, hipStream_t st)
+{
+    hipError_t err;
+    if (!(a.skip & SMHA_STEP_QKV)
+        && (err = a.rope_dim > 0 ? launch_projections<true>(a, st) : launch_projections<false>(a, st)) != hipSuccess) return err;
     if (a.skip & SMHA_STEP_ATTENTION) return hipSuccess;
     return launch_attention_mfma(a, st);
 }
