@@ -190,7 +190,7 @@ struct UomeDsArgs {
     void *hidden;                             // [b*k, l_a, d_e], storage dtype
 };
 
-// Backward pass of the expert-selection UoME block (bf16 storage, MFMA shapes only)
+// Backward pass of the expert-selection UoME block
 struct UomeBwdArgs {
     const void *u, *a_in, *a_out, *d_out;
     const int32_t *expert_idx;

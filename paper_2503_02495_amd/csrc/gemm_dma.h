@@ -596,7 +596,8 @@ template <int FLAGS, typename P> static hipError_t launch_gemm_tail(const P &p, 
 // 4 x 8192 x 2048) gave the order; us for up / down of the MLP, this choice against 256x128x32 with four waves (large
 // launches) or 128x128x64 with four waves (the others):
 //   256x256x64, 8 waves of 128x64   K >= 768 and a tile per compute unit: fewest operand bytes per product
-//                                   (4 x 8192 x 2048 x 1024: 137 / 129 against 152 / 139)
+//                                   (4 x 8192 x 2048 x 1024: 137 / 129 against 152 / 139 looped back to back; as single calls
+//                                   141 to 144 / 125 to 128)
 //   128x256x32, 8 waves of 64x64    N a multiple of 256, 384 tiles and more: two workgroups, 16 waves a compute unit
 //                                   (128 x 196 x 768 x 384: 28 against 31; 16 x 4096 x 256 x 256: 18.6 against 20.1)
 //   128x128x32, 8 waves of 64x32    more tiles than slots of the four-wave form (16 x 1024 x 768 x 1024: 34.4 against 36.4;
