@@ -62,13 +62,15 @@ __device__ __forceinline__ bool key_is_token(const SmhaArgs &a, int g, int key, 
 // accumulator register q is key (q/4)*8 + lh*4 + q%4, and that key order is the one of both operands of the second
 // product, P^T and V.  K rows are padded by 4 floats (16-byte fragment reads of 16 consecutive rows
 // hit all banks once), V rows by 8 (the half-waves' rows are 4 apart: 32 banks).
-// Products: fp32 operands as three bf16 parts (SplitF32, six products); q, k and v of bf16 storage are one part, so that a score is
-// one exact bf16 product (q enters unscaled, the score is scaled) and P V three.  As in the engine the bf16 instruction's
-// rounding towards minus infinity is cancelled by sign: odd pairs of sub-steps of a score are summed negated, and O changes
-// its sign with every tile (in the multiplication that rescales it anyway).  The fp32 instruction (v_mfma_f32_32x32x2_f32) took
-// 512 cycles for what takes 192, 96 or 32: 6 x 1000 x 360 in bf16 with heads of 40 (18 units of 240 rows): 19.9 -> 12.5 us, lm shape in
-// fp32 (32 units of 128 rows, d_h 64): 15.5 -> 13.0 us, both with four key splits instead of two.  What is left is the chain of a tile:
-// staging, scores, maximum, exponentials, split, second product, two barriers.
+// Products.  fp32 storage: v_mfma_f32_32x32x2_f32 (six bf16 products of operands split in three took registers, two waves a SIMD
+// became one: 384 units of 56 rows, d_h 64, 18.9 us against 14.3, 64 units of 400 rows 50 against 46, though 32 of 1600 rows 221
+// against 271; and they lost the last bits of v below 2^-110).  bf16 storage: q, k and v are exact as one bf16 part, so that a score is one bf16
+// product (q enters unscaled, the score is scaled) and P V three, P in three parts (SplitF32): 32 and 96 cycles of the matrix pipe
+// for what takes 512.  The bf16 instruction rounds its sum towards minus infinity: odd pairs of sub-steps of a score are summed negated, and
+// O changes its sign with every tile of a wave (in the multiplication that rescales it anyway).
+// us, before -> now (four key splits instead of two on short grids in both types): 6 x 1000 x 360 in bf16, heads of 40 (18 units of 240 rows)
+// 18.6 -> 11.4, 384 units of 112 rows, d_h 56, 28.4 -> 19.7; fp32, 32 units of 128 rows, d_h 64: 13.8 -> 11.1, 18 of 240 19.5 -> 13.2.  What is
+// left is the chain of a tile: staging, scores, maximum, exponentials, second product, two barriers.
 // KSPLIT waves share a query block and take key tiles KSPLIT apart (merged through LDS) so that short grids
 // still give most SIMDs a wave.
 template <typename T, int DH, int NQ, int KSPLIT>
@@ -143,28 +145,27 @@ __global__ __launch_bounds__(NQ *KSPLIT * 64) void attention_f32_kernel(SmhaArgs
     };
 
     auto walk = [&](auto exact_c) __attribute__((always_inline)) {
-        constexpr bool EXACT = decltype(exact_c)::value, B16 = sizeof(T) == 2;
-        // the query as second operand: fp32 and scaled; split, scaled, odd pairs of sub-steps negated; or as it is in bf16, odd
-        // pairs negated, the scores scaled instead
+        constexpr bool EXACT = decltype(exact_c)::value;
+        static_assert(EXACT || sizeof(T) == 2, "one bf16 part holds q, k and v");
+        // the query as second operand: fp32 and scaled; or as it is in bf16, odd pairs of sub-steps negated, the scores scaled instead
         float qf[EXACT ? DH / 8 : 1][4];
-        SplitF32 qs[!EXACT && !B16 ? DH / 16 : 1];
-        bf16x8_t qb[!EXACT && B16 ? DH / 16 : 1];
+        bf16x8_t qb[EXACT ? 1 : DH / 16];
+        if constexpr (EXACT) {
 #pragma unroll
-        for (int s = 0; s < DH / 16; ++s) {
-            f32x4_t q0, q1;
+            for (int ks = 0; ks < DH / 8; ++ks)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                q0[e] = q_at(2 * s, e);
-                q1[e] = q_at(2 * s + 1, e);
-            }
-            if constexpr (EXACT) {
+                for (int e = 0; e < 4; ++e) qf[ks][e] = q_at(ks, e) * scale;
+        } else {
+#pragma unroll
+            for (int s = 0; s < DH / 16; ++s) {
+                f32x4_t q0, q1;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    qf[2 * s][e] = q0[e] * scale;
-                    qf[2 * s + 1][e] = q1[e] * scale;
+                    q0[e] = q_at(2 * s, e);
+                    q1[e] = q_at(2 * s + 1, e);
                 }
-            } else if constexpr (B16) qb[s] = pack8_bf16(q0, q1, s & 1 ? -1.0f : 1.0f);
-            else qs[s].set(q0, q1, s & 1 ? -scale : scale);
+                qb[s] = pack8_bf16(q0, q1, s & 1 ? -1.0f : 1.0f);
+            }
         }
 #pragma unroll
         for (int t = 0; t < DH / 32; ++t)
@@ -195,17 +196,12 @@ __global__ __launch_bounds__(NQ *KSPLIT * 64) void attention_f32_kernel(SmhaArgs
                     for (int e = 0; e < 4; ++e) sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(k1[e], qf[2 * s + 1][e], sacc, 0, 0, 0);
                 } else {
                     f32x16_t &sum = s & 1 ? sneg : sacc;
-                    if constexpr (B16) sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pack8_bf16(k0, k1, 1.0f), qb[s], sum, 0, 0, 0);
-                    else {
-                        SplitF32 kk;
-                        kk.set(k0, k1, 1.0f);
-                        sum = mfma_split(kk, qs[s], sum);
-                    }
+                    sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pack8_bf16(k0, k1, 1.0f), qb[s], sum, 0, 0, 0);
                 }
             }
             if constexpr (!EXACT) {
 #pragma unroll
-                for (int q = 0; q < 16; ++q) sacc[q] = (sacc[q] - sneg[q]) * (B16 ? scale : 1.0f);
+                for (int q = 0; q < 16; ++q) sacc[q] = (sacc[q] - sneg[q]) * scale;
             }
             float tmax = -INFINITY;
 #pragma unroll
@@ -263,29 +259,25 @@ __global__ __launch_bounds__(NQ *KSPLIT * 64) void attention_f32_kernel(SmhaArgs
                             v0[e] = v_at(h * 8 + e, td);
                             v1[e] = v_at(h * 8 + 4 + e, td);
                         }
-                        if constexpr (B16) oacc[td] = mfma_split(pack8_bf16(v0, v1, 1.0f), pp, oacc[td]);
-                        else {
-                            SplitF32 vv;
-                            vv.set(v0, v1, 1.0f);
-                            oacc[td] = mfma_split(vv, pp, oacc[td]);
-                        }
+                        oacc[td] = mfma_split(pack8_bf16(v0, v1, 1.0f), pp, oacc[td]);
                     }
                 }
             }
         }
         float bad = 0.f;
+        if constexpr (!EXACT) {
 #pragma unroll
-        for (int td = 0; td < DH / 32; ++td)
+            for (int td = 0; td < DH / 32; ++td)
 #pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                oacc[td][q] *= sign;
-                bad = fmaf(oacc[td][q], 0.f, bad);
-            }
+                for (int q = 0; q < 16; ++q) {
+                    oacc[td][q] *= sign;
+                    bad = fmaf(oacc[td][q], 0.f, bad);
+                }
+        }
         return bad != bad;
     };
-    // parts of an infinity are infinity and NaN: with such a value among q, k, v or the scores the walk is taken again on fp32
-    // products.  fp32 heads past 64 stay on those: q's parts (96 registers) and a tile in flight do not fit beside O.
-    if constexpr (sizeof(T) == 4 && DH > 64) walk(std::true_type{});
+    // bf16: parts of an infinity are infinity and NaN: a block whose O is not finite is walked again on fp32 products
+    if constexpr (sizeof(T) == 4) walk(std::true_type{});
     else if (__builtin_expect(__syncthreads_or(walk(std::false_type{})), 0)) walk(std::true_type{});
     if constexpr (KSPLIT > 1) {   // split 0 folds the others' (max, sum, O) in, in split order
         __syncthreads();

@@ -80,3 +80,31 @@ def test_attention_values_that_are_not_finite():
     B.smha_forward(blk, x, wq, wk, wv, wo, zero, one, zero.reshape(1, 1, 1), one.reshape(1, 1, 1), out, ws)
     want = torch.where(wo[0, 3] > 0, float("inf"), -float("inf")).expand(l, d)
     assert torch.equal(out[0], want)
+
+
+def one_unit(x, wq, wk, wv, wo):
+    """The SMHA block without residual and gates where one expert takes the whole sample."""
+    b, l, d = x.shape
+    d_h = wq.shape[2]
+    blk = B.block_desc(b, l, d, 1, 1, 1, 1, d_h, B.F32 if x.dtype == torch.float32 else B.BF16, 0)
+    zero, one = torch.zeros((b, 1), dtype=torch.int32, device="cuda"), torch.ones((b, 1), device="cuda")
+    out = torch.empty_like(x)
+    ws = torch.empty(B.workspace_bytes(blk, None), dtype=torch.uint8, device="cuda")
+    B.smha_forward(blk, x, wq, wk, wv, wo, zero, one, zero.reshape(b, 1, 1), one.reshape(b, 1, 1), out, ws)
+    return out
+
+
+@pytest.mark.parametrize("l", [20, 64, 100, 300])
+@pytest.mark.parametrize("v_size", [1.0, 1e-36])
+def test_fp32_attention_keeps_the_bits_of_small_values(l, v_size):
+    """fp32 heads whose v are near the bottom of the range: the bits of a sum of l terms, as for v of order one (2^-25 of the
+    sum per rounding, some l of them at random, three products in a row: 2e-6)."""
+    d, d_h = 96, 40
+    g = torch.Generator(device="cuda").manual_seed(11)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
+    x, wq, wk, wv, wo = rnd(2, l, d), 0.1 * rnd(1, d, d_h), 0.1 * rnd(1, d, d_h), 0.1 * rnd(1, d, d_h), rnd(1, d_h, d)
+    got = one_unit(x, wq, wk, (v_size * wv).contiguous(), wo).double()
+    q, k, v = (x.double() @ w[0].double() for w in (wq, wk, v_size * wv))
+    p = torch.softmax(torch.bmm(q, k.transpose(1, 2).contiguous()) / d_h ** 0.5, -1)
+    want = torch.bmm(p, v) @ wo[0].double()
+    assert (got - want).norm() <= 2e-6 * want.norm()
