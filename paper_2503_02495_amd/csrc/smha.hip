@@ -67,7 +67,8 @@ __device__ __forceinline__ bool key_is_token(const SmhaArgs &a, int g, int key, 
 // against 271; and they lost the last bits of v below 2^-110).  bf16 storage: q, k and v are exact as one bf16 part, so that a score is one bf16
 // product (q enters unscaled, the score is scaled) and P V three, P in three parts (SplitF32): 32 and 96 cycles of the matrix pipe
 // for what takes 512.  The bf16 instruction rounds its sum towards minus infinity: odd pairs of sub-steps of a score are summed negated, and
-// O changes its sign with every tile of a wave (in the multiplication that rescales it anyway).
+// O takes half of its key tiles with each sign, whatever the number of splits (in the multiplication that rescales it anyway).  P
+// is multiplied by 2^24 and O divided by it, so that no part of P times v falls below the normal numbers.
 // us, before -> now (four key splits instead of two on short grids in both types): 6 x 1000 x 360 in bf16, heads of 40 (18 units of 240 rows)
 // 18.6 -> 11.4, 384 units of 112 rows, d_h 56, 28.4 -> 19.7; fp32, 32 units of 128 rows, d_h 64: 13.8 -> 11.1, 18 of 240 19.5 -> 13.2.  What is
 // left is the chain of a tile: staging, scores, maximum, exponentials, second product, two barriers.
@@ -93,6 +94,7 @@ __global__ __launch_bounds__(NQ *KSPLIT * 64) void attention_f32_kernel(SmhaArgs
     const T *Q = static_cast<const T *>(a.q) + ubase, *Kg = static_cast<const T *>(a.kk) + ubase, *Vg = static_cast<const T *>(a.v) + ubase;
 
     const float scale = 1.4426950408889634f * rsqrtf((float)d_h);   // base-2 softmax
+    constexpr float P_SCALE = 16777216.0f;
     auto q_at = [&](int ks, int e) -> float {   // own query, k of sub-step ks of the fp32 instruction
         const int dh = ks * 8 + lh * 4 + e;
         return qrow < l_a && dh < d_h ? to_f32(Q[(size_t)qrow * d_h + dh]) : 0.f;
@@ -173,7 +175,7 @@ __global__ __launch_bounds__(NQ *KSPLIT * 64) void attention_f32_kernel(SmhaArgs
             for (int q = 0; q < 16; ++q) oacc[t][q] = 0.f;
         mrun = -INFINITY;
         lsum = 0.f;
-        float sign = 1.0f;   // of O in its accumulators
+        float sign = split & 1 ? -1.0f : 1.0f;   // of O in its accumulators
         if (split < nkt) load_global(split);
         for (int it = 0; it < nit; ++it) {   // nit is uniform over the workgroup
             const int kt = it * KSPLIT + split;
@@ -250,7 +252,7 @@ __global__ __launch_bounds__(NQ *KSPLIT * 64) void attention_f32_kernel(SmhaArgs
                         p1[e] = sacc[h * 8 + 4 + e];
                     }
                     SplitF32 pp;
-                    pp.set(p0, p1, sign);
+                    pp.set(p0, p1, sign * P_SCALE);
 #pragma unroll
                     for (int td = 0; td < DH / 32; ++td) {
                         f32x4_t v0, v1;
@@ -270,7 +272,7 @@ __global__ __launch_bounds__(NQ *KSPLIT * 64) void attention_f32_kernel(SmhaArgs
             for (int td = 0; td < DH / 32; ++td)
 #pragma unroll
                 for (int q = 0; q < 16; ++q) {
-                    oacc[td][q] *= sign;
+                    oacc[td][q] *= sign * (1.0f / P_SCALE);
                     bad = fmaf(oacc[td][q], 0.f, bad);
                 }
         }

@@ -108,3 +108,17 @@ def test_fp32_attention_keeps_the_bits_of_small_values(l, v_size):
     p = torch.softmax(torch.bmm(q, k.transpose(1, 2).contiguous()) / d_h ** 0.5, -1)
     want = torch.bmm(p, v) @ wo[0].double()
     assert (got - want).norm() <= 2e-6 * want.norm()
+
+
+@pytest.mark.parametrize("rows", [30, 128, 200])
+def test_bf16_attention_off_the_grid_with_small_values(rows):
+    """v of 1e-36 in bf16 heads of 40: the probabilities' lowest parts times v are below the normal numbers, o is not (v, o and the
+    output are rounded to bf16 once each: 1e-2)."""
+    d, d_h = 96, 40
+    g = torch.Generator(device="cuda").manual_seed(13)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
+    x, wq, wk, wv, wo = (t.bfloat16() for t in (rnd(1, rows, d), 0.1 * rnd(1, d, d_h), 0.1 * rnd(1, d, d_h), 1e-37 * rnd(1, d, d_h), rnd(1, d_h, d)))
+    got = one_unit(x, wq, wk, wv, wo).double()
+    q, k, v = (x[0].double() @ w[0].double() for w in (wq, wk, wv))
+    want = torch.softmax(q.bfloat16().double() @ k.bfloat16().double().T / d_h ** 0.5, -1) @ v @ wo[0].double()
+    assert (got[0] - want).norm() <= 1e-2 * want.norm()
