@@ -176,6 +176,7 @@ __global__ __launch_bounds__(NQ *KSPLIT * 64) void attention_f32_kernel(SmhaArgs
         mrun = -INFINITY;
         lsum = 0.f;
         float sign = split & 1 ? -1.0f : 1.0f;   // of O in its accumulators
+        bool unseen = false;                     // an admissible key, and none with a score above -inf
         if (split < nkt) load_global(split);
         for (int it = 0; it < nit; ++it) {   // nit is uniform over the workgroup
             const int kt = it * KSPLIT + split;
@@ -220,6 +221,15 @@ __global__ __launch_bounds__(NQ *KSPLIT * 64) void attention_f32_kernel(SmhaArgs
             }
             tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
             const float mnew = fmaxf(mrun, tmax), msub = mnew == -INFINITY ? 0.f : mnew;   // nothing admissible yet: exp2(-inf - 0) = 0
+            if constexpr (!EXACT) {
+                if (mnew == -INFINITY) {
+#pragma unroll
+                    for (int q = 0; q < 16; ++q) {
+                        const int at = (q >> 2) * 8 + lh * 4 + (q & 3);
+                        unseen |= Km[at] != 0.f && (!causal || kt * BT + at <= qrow);
+                    }
+                } else unseen = false;
+            }
             const float corr = __builtin_amdgcn_exp2f(mrun - msub);   // 0 before the first admissible key
             mrun = mnew;
             float psum = 0.f;
@@ -266,7 +276,7 @@ __global__ __launch_bounds__(NQ *KSPLIT * 64) void attention_f32_kernel(SmhaArgs
                 }
             }
         }
-        float bad = 0.f;
+        float bad = unseen ? NAN : 0.f;
         if constexpr (!EXACT) {
 #pragma unroll
             for (int td = 0; td < DH / 32; ++td)
@@ -278,7 +288,8 @@ __global__ __launch_bounds__(NQ *KSPLIT * 64) void attention_f32_kernel(SmhaArgs
         }
         return bad != bad;
     };
-    // bf16: parts of an infinity are infinity and NaN: a block whose O is not finite is walked again on fp32 products
+    // bf16: parts of an infinity are infinity and NaN, and an unscaled score may overflow where the scaled one does not: a block whose O
+    // is not finite, or with a row whose scores are all -inf, is walked again on fp32 products
     if constexpr (sizeof(T) == 4) walk(std::true_type{});
     else if (__builtin_expect(__syncthreads_or(walk(std::false_type{})), 0)) walk(std::true_type{});
     if constexpr (KSPLIT > 1) {   // split 0 folds the others' (max, sum, O) in, in split order

@@ -122,3 +122,21 @@ def test_bf16_attention_off_the_grid_with_small_values(rows):
     q, k, v = (x[0].double() @ w[0].double() for w in (wq, wk, wv))
     want = torch.softmax(q.bfloat16().double() @ k.bfloat16().double().T / d_h ** 0.5, -1) @ v @ wo[0].double()
     assert (got[0] - want).norm() <= 1e-2 * want.norm()
+
+
+@pytest.mark.parametrize("sign,first", [(1.0, False), (-1.0, True)])
+def test_bf16_scores_that_overflow_before_they_are_scaled(sign, first):
+    """q k of 2^128 and more times log2(e) / sqrt(d_h) is a finite fp32 number: every query takes the key with the largest score."""
+    l, d, d_h = 40, 72, 40
+    g = torch.Generator(device="cuda").manual_seed(12)
+    x = torch.randn((1, l, d), generator=g, device="cuda")
+    x[0, :, 0], x[0, :, 1] = 1.0, 1.0 + torch.arange(l, device="cuda") / 64.0
+    wq, wk, wv = (torch.zeros((1, d, d_h), device="cuda") for _ in range(3))
+    wq[0, 0, 0], wk[0, 1, 0] = 2.0 ** 64, sign * 2.0 ** 64
+    wv[0, 2:] = 0.1 * torch.randn((d - 2, d_h), generator=g, device="cuda")
+    wo = torch.randn((1, d_h, d), generator=g, device="cuda")
+    x, wq, wk, wv, wo = (t.bfloat16().contiguous() for t in (x, wq, wk, wv, wo))
+    got = one_unit(x, wq, wk, wv, wo).double()
+    want = (x[0, 0 if first else l - 1].double() @ wv[0].double()) @ wo[0].double()
+    # bf16: v and the output are rounded once each
+    assert (got - want).norm() <= 1e-2 * (want.norm() * l ** 0.5)
