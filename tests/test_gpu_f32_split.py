@@ -140,3 +140,50 @@ def test_bf16_scores_that_overflow_before_they_are_scaled(sign, first):
     want = (x[0, 0 if first else l - 1].double() @ wv[0].double()) @ wo[0].double()
     # bf16: v and the output are rounded once each
     assert (got - want).norm() <= 1e-2 * (want.norm() * l ** 0.5)
+
+
+def one_expert_grads(x, d_out, wq, wk, wv, wo, l_p, c):
+    """Weight gradients of the SMHA block (expert 0 of one, the first c patches of every sample) and the same in fp64."""
+    b, l, d = x.shape
+    d_h, m = wq.shape[2], l // l_p
+    blk = B.block_desc(b, l, d, 1, 1, m, c, d_h, B.F32, 0)
+    zero, one = torch.zeros((b, 1), dtype=torch.int32, device="cuda"), torch.ones((b, 1), device="cuda")
+    pidx = torch.arange(c, dtype=torch.int32, device="cuda").expand(b, 1, c).contiguous()
+    got = [torch.empty_like(t) for t in (wq, wk, wv, wo)]
+    ws = torch.empty(B.smha_backward_workspace_bytes(blk), dtype=torch.uint8, device="cuda")
+    B.smha_backward(blk, x, B.smha_weights(None, None, None, wq, wk, wv, wo), zero, one, pidx, torch.ones((b, 1, m), device="cuda"), None, d_out,
+                    torch.empty_like(x), B.smha_weight_grads(*got), torch.empty((b, 1), device="cuda"), torch.empty((b, 1, m), device="cuda"), ws)
+    leaves = [w[0].double().requires_grad_(True) for w in (wq, wk, wv, wo)]
+    h = x[:, :c * l_p].double()
+    q, k, v = (h @ w for w in leaves[:3])
+    out = torch.softmax(q @ k.transpose(1, 2) / d_h ** 0.5, -1) @ v @ leaves[3]
+    return [g[0].double() for g in got], torch.autograd.grad((out * d_out[:, :c * l_p].double()).sum(), leaves)
+
+
+@pytest.mark.parametrize("l_p", [1, 7, 8, 9, 14, 16, 17, 24, 32, 40])
+def test_weight_gradients_of_short_patches(l_p):
+    """K segments of one K-step and less, some hundred of them: every part of an expert's sum rounds some 100 times in both directions
+    (3e-8 of the sum each: 1e-6 at random), and the mean over the outputs of a one-sided rounding would be that of each output."""
+    b, c, d, d_h = 24, 8, 96, 64
+    g = torch.Generator(device="cuda").manual_seed(21)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
+    x, d_out = rnd(b, c * l_p, d), rnd(b, c * l_p, d)
+    ws = [0.1 * rnd(1, d, d_h) for _ in range(3)] + [0.1 * rnd(1, d_h, d)]
+    got, want = one_expert_grads(x, d_out, *ws, l_p, c)
+    for name, y, r in zip(("wq", "wk", "wv", "wo"), got, want):
+        rms = r.pow(2).mean().sqrt()
+        err, bias = (y - r).norm() / r.norm(), (y - r).mean().abs() / rms
+        print(f"l_p={l_p} d_{name} error {err:.2e} mean {bias:.2e}", flush=True)
+        assert err <= 1e-6
+        # the mean of 6144 errors of 6e-7 at random: 1e-8 (one-sided: 6e-8 and more)
+        assert bias <= 3e-8
+
+
+@pytest.mark.parametrize("d_e,k", [(8, 16), (16, 16), (24, 12), (40, 8)])
+def test_contractions_over_short_segments(d_e, k):
+    """The experts' slices of K one K-step long or less."""
+    u, _, w_out, idx = make(8, 130, 264, 16, k, d_e)
+    x = torch.randn((8, 130, k * d_e), generator=torch.Generator(device="cuda").manual_seed(6), device="cuda")
+    got, want = down(x, w_out, idx, u).double(), down64(x, w_out, idx)
+    assert (got - want).norm() <= 1e-6 * want.norm()
+    assert (got - want).mean().abs() <= 5e-9 * want.pow(2).mean().sqrt()   # 274560 errors of 3e-7: 6e-10; one-sided: 1.5e-8
