@@ -187,3 +187,35 @@ def test_contractions_over_short_segments(d_e, k):
     got, want = down(x, w_out, idx, u).double(), down64(x, w_out, idx)
     assert (got - want).norm() <= 1e-6 * want.norm()
     assert (got - want).mean().abs() <= 5e-9 * want.pow(2).mean().sqrt()   # 274560 errors of 3e-7: 6e-10; one-sided: 1.5e-8
+
+
+@pytest.mark.parametrize("x_size,w_size", [(1e-36, 1.0), (1.0, 1e-36), (1e-19, 1e-18), (1e30, 1.0), (1e19, 1e15), (1e-36, 1e36)])
+def test_contractions_at_the_ends_of_the_range(x_size, w_size):
+    """Operands of which the lowest parts are below the smallest normal bf16 number or the largest past the split's scale: the bits of
+    operands of order one (a sum below 1e-35 is held to 2^-149 absolutely)."""
+    u, _, w_out, idx = make(2, 130, 264, 4, 2, 136)
+    x = torch.randn((2, 130, 272), generator=torch.Generator(device="cuda").manual_seed(6), device="cuda") * x_size
+    w_out = (w_out * w_size).contiguous()
+    got, want = down(x, w_out, idx, u).double(), down64(x, w_out, idx)
+    assert (got - want).norm() <= 2e-6 * want.norm() + 1e-44 * want.numel() ** 0.5
+
+
+def test_experts_of_small_gates_keep_their_gradients():
+    """Saturated routers give selected experts gates of 1e-38: their part of d_u is a contraction of numbers of that size."""
+    u, w_in, w_out, idx = make(4, 100, 264, 4, 2, 136)
+    g = torch.Generator(device="cuda").manual_seed(8)
+    d_out, gate = torch.randn(u.shape, generator=g, device="cuda"), 1e-37 * (0.5 + torch.rand((4, 4), generator=g, device="cuda"))
+    blk = B.block_desc(4, 100, 264, 4, 2, 1, 1, 136, B.F32, B.FLAG_GATE_EXPERT)
+    d_u = torch.empty_like(u)
+    ws = torch.empty(B.uome_backward_workspace_bytes(blk), dtype=torch.uint8, device="cuda")
+    B.uome_backward(blk, u, w_in, w_out, idx, gate, None, None, d_out, d_u, torch.empty_like(w_in), torch.empty_like(w_out), torch.empty_like(gate),
+                    None, ws)
+    leaf = u.double().requires_grad_(True)
+    out = 0
+    for s in range(2):
+        e = idx[:, s].long()
+        z = torch.bmm(leaf, w_in.double()[e].contiguous())
+        out = out + torch.bmm(z * torch.sigmoid(z) * gate.double().gather(1, e[:, None])[:, :, None], w_out.double()[e].contiguous())
+    want, = torch.autograd.grad((out * d_out.double()).sum(), leaf)
+    # factors of 1e-38 in the epilogue are subnormal in part: 2^-149 of 1e-38 each
+    assert (d_u.double() - want).norm() <= 1e-5 * want.norm()
