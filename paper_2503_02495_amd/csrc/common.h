@@ -41,6 +41,48 @@ inline bool stream_once(size_t bytes)
     return (double)bytes >= min_bytes;
 }
 
+// Tile of a contraction of any size or in fp32 (launch_gemm_tail).  km: both operands along rows and columns (weight gradients);
+// gaps_nk: rows that are absent from K segments, against [n][k] (d_x).
+// bf16: 128x128 tiles (eight waves of 64x32, 16 waves a compute unit; four waves of 64x64 took 32.5 against 29.5 us on 128 x 196 x 768 x
+// 384) once they give every compute unit one (fewer operand bytes per product), 64-row tiles below that, 32-row tiles where groups are
+// that short.
+// fp32, us on rows x K x columns (x: on the fp32 instruction); no tile that pads more than a tenth beyond 64x64:
+//   128x128, four waves  512 and more: 16384 x 512 x 1024 114, 64x128 133, 64x64 143, with eight waves 147.  Two sets of accumulators leave 44
+//                        to 60 bytes of scratch a lane, against [n][k] 164 to 224: a backward pass with d_u on it still 677 against 693 and
+//                        704, but d_x, whose segments are two K-steps long, not (128 samples of 14 x 14 tokens 333 against 308 and 304)
+//   64x128               512 and more: 4096 x 512 x 1024 38.1, 128x128 38.7, 64x64 40.8 (x 45.5)
+//   64x64                4096 x 1024 x 512 39.5, 64x128 42.9 (x 44.7); 128 groups of 128 x 512 x 192 32.7, 64x128 40.2; groups of up to 64 rows: 512 of
+//                        64 x 256 37.5, 64x128 41.5
+//   64x64 x              up to 256 of them: a wave a SIMD cannot hide the chain read -> split -> product (1280 x 384 x 512 11.6 against 12.2; 24
+//                        groups of 240 x 360 x 120 12.9 against 14.7)
+//   32x64 x              up to 128 (2048 x 512 x 256 13.7 against 14.0; 160 of them 17.2 against 11.6), and short groups
+// fp32 weight gradients (whole backward passes): 64x128 from 385 of them (504: 318 against 333 with 64x64; 512 of 32 rows 189 against 199; 216: 163
+// against 158), 128x128 as above; the fp32 instruction gains nothing on few tiles.
+struct TailTile {
+    int rows, cols;
+    bool exact;   // fp32: on the fp32 instruction
+};
+inline TailTile tail_tile(bool f32, bool km, bool gaps_nk, long groups, int rows, int cols)
+{
+    const auto up = [](int v, int to) { return (long)((v + to - 1) / to); };
+    const auto tiles = [&](int bm, int bn) { return groups * up(rows, bm) * up(cols, bn); };
+    if (!f32) {
+        if (rows > 64 && tiles(128, 128) >= 256) return {128, 128, false};
+        return {rows <= 32 && !km ? 32 : 64, 128, false};
+    }
+    const auto padded = [&](int bm, int bn) { return (double)tiles(bm, bn) * bm * bn / ((double)tiles(64, 64) * 64 * 64); };
+    if (km) {
+        if (rows > 64 && tiles(128, 128) >= 512 && padded(128, 128) <= 1.1) return {128, 128, false};
+        if (tiles(64, 128) > 384 && padded(64, 128) <= 1.25) return {64, 128, false};
+        return {64, 64, false};
+    }
+    if (rows <= 32 || tiles(64, 64) <= 128) return {32, 64, true};
+    if (tiles(64, 64) <= 256) return {64, 64, true};
+    if (rows > 64 && tiles(128, 128) >= 512 && padded(128, 128) <= 1.1 && !gaps_nk) return {128, 128, false};
+    if (rows > 64 && tiles(64, 128) >= 512 && padded(64, 128) <= 1.1) return {64, 128, false};
+    return {64, 64, false};
+}
+
 __device__ __forceinline__ float to_f32(float x) { return x; }
 __device__ __forceinline__ float to_f32(bf16_t x) { return __uint_as_float(((uint32_t)x.v) << 16); }
 

@@ -219,3 +219,95 @@ def test_experts_of_small_gates_keep_their_gradients():
     want, = torch.autograd.grad((out * d_out.double()).sum(), leaf)
     # factors of 1e-38 in the epilogue are subnormal in part: 2^-149 of 1e-38 each
     assert (d_u.double() - want).norm() <= 1e-5 * want.norm()
+
+
+# --------------------------------------------------------------------------- tiles and layouts
+def tile(km, gaps_nk, groups, rows, cols):
+    """The fp32 half of tail_tile (common.h): rows and columns of the tile, and whether it is on the fp32 instruction."""
+    up = lambda v, to: -(-v // to)
+    n = lambda bm, bn: groups * up(rows, bm) * up(cols, bn)
+    padded = lambda bm, bn: n(bm, bn) * bm * bn / (n(64, 64) * 4096)
+    if km:
+        if rows > 64 and n(128, 128) >= 512 and padded(128, 128) <= 1.1:
+            return 128, 128, False
+        return (64, 128, False) if n(64, 128) > 384 and padded(64, 128) <= 1.25 else (64, 64, False)
+    if rows <= 32 or n(64, 64) <= 128:
+        return 32, 64, True
+    if n(64, 64) <= 256:
+        return 64, 64, True
+    if rows > 64 and n(128, 128) >= 512 and padded(128, 128) <= 1.1 and not gaps_nk:
+        return 128, 128, False
+    return (64, 128, False) if rows > 64 and n(64, 128) >= 512 and padded(64, 128) <= 1.1 else (64, 64, False)
+
+
+FORWARD_TILES = [((2, 40, 72, 2, 136), (32, 64, True)), ((8, 300, 264, 1, 264), (64, 64, True)), ((12, 300, 264, 1, 264), (64, 64, False)),
+                 ((9, 700, 520, 1, 264), (64, 64, False)), ((16, 500, 504, 1, 264), (64, 128, False)), ((32, 500, 504, 1, 264), (128, 128, False))]
+
+
+@pytest.mark.parametrize("x_size", [1.0, 1e33])
+@pytest.mark.parametrize("shape,want_tile", FORWARD_TILES)
+def test_every_forward_tile(shape, want_tile, x_size):
+    """x of 1e33 overflows in the split: every tile is contracted twice."""
+    b, l, d, k, d_e = shape
+    assert tile(False, False, b, l, d) == want_tile
+    print(f"fp32 down {shape} tile {want_tile} x {x_size}", flush=True)
+    u, _, w_out, idx = make(b, l, d, 4, k, d_e)
+    x = torch.randn((b, l, k * d_e), generator=torch.Generator(device="cuda").manual_seed(6), device="cuda") * x_size
+    got, want = down(x, w_out, idx, u).double(), down64(x, w_out, idx)
+    assert (got - want).norm() <= 2e-6 * want.norm()
+
+
+# b, patches, tokens of one, d, n, k, c, d_h; tiles of q, k, v, of the out-projection and of d_x
+SMHA_TILES = [((4, 6, 9, 136, 4, 2, 3, 40), (32, 64, True), (32, 64, True), (32, 64, True)),
+              ((16, 10, 20, 200, 4, 3, 6, 128), (64, 64, False), (32, 64, True), (32, 64, True)),
+              ((96, 14, 14, 384, 6, 3, 4, 64), (64, 64, False), (128, 128, False), (64, 128, False)),
+              ((40, 4, 120, 264, 4, 3, 3, 72), (128, 128, False), (64, 64, False), (64, 64, False)),
+              ((48, 5, 110, 384, 4, 2, 4, 120), (64, 128, False), (128, 128, False), (64, 128, False))]
+
+
+def patch_groups(b, l_p, m, c, d):
+    """set_patch_groups (problems.h): patches in a group."""
+    fit = lambda t: min(t // l_p if 2 * l_p <= t else 1, m)
+    none = lambda g: (1 - c / m) ** g
+    products = lambda g, t: -(-g * l_p // t) * t / g * (1 - none(g))
+    g32, g128 = fit(32), min(fit(128), 32)
+    many = b * -(-m // g128) * -(-d // 128) >= 512
+    return g128 if l_p <= 32 and g128 > g32 and g128 * l_p > 64 and many and products(g128, 128) <= 2 * products(g32, 32) else g32
+
+
+@pytest.mark.parametrize("g_size", [1.0, 1e32])
+@pytest.mark.parametrize("shape,qkv,proj,dx_tile", SMHA_TILES)
+def test_every_smha_tile(shape, qkv, proj, dx_tile, g_size):
+    """Forward and backward of the block with rows that are absent from K segments (out-projection, d_x); a gradient of 1e32 as above."""
+    b, m, l_p, d, n, k, c, d_h = shape
+    print(f"fp32 smha {shape} gradient {g_size}", flush=True)
+    gp, l_a, l = patch_groups(b, l_p, m, c, d), c * l_p, m * l_p
+    groups = b * -(-m // gp)
+    assert qkv == tile(False, False, b * k, l_a, 3 * d_h)
+    assert proj == tile(False, False, groups, gp * l_p, d) and dx_tile == tile(False, True, groups, gp * l_p, d)
+    g = torch.Generator(device="cuda").manual_seed(31)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
+    x, d_out = rnd(b, l, d), g_size * rnd(b, l, d)
+    w = [0.1 * rnd(n, d, d_h) for _ in range(3)] + [0.1 * rnd(n, d_h, d)]
+    idx = torch.stack([torch.randperm(n, generator=g, device="cuda")[:k].sort().values for _ in range(b)]).int().contiguous()
+    pidx = torch.stack([torch.randperm(m, generator=g, device="cuda")[:c].sort().values for _ in range(b * n)]).int().reshape(b, n, c).contiguous()
+    eg, pg = torch.ones((b, n), device="cuda"), torch.ones((b, n, m), device="cuda")
+    blk = B.block_desc(b, l, d, n, k, m, c, d_h, B.F32, 0)
+    out, dx, dw = torch.empty_like(x), torch.empty_like(x), [torch.empty_like(t) for t in w]
+    room = lambda nbytes: torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    B.smha_forward(blk, x, *w, idx, eg, pidx, pg, out, room(B.workspace_bytes(blk, None)))
+    B.smha_backward(blk, x, B.smha_weights(None, None, None, *w), idx, eg, pidx, pg, None, d_out, dx, B.smha_weight_grads(*dw),
+                    torch.empty_like(eg), torch.empty_like(pg), room(B.smha_backward_workspace_bytes(blk)))
+    leaves = [t.double().requires_grad_(True) for t in (x, *w)]
+    sample, e = torch.arange(b, device="cuda")[:, None], idx.long()
+    tok = (pidx[sample, e].long()[..., None] * l_p + torch.arange(l_p, device="cuda")).reshape(b, k, l_a)
+    flat = (sample[..., None] * l + tok).reshape(-1)
+    h = leaves[0].reshape(b * l, d)[flat].reshape(b * k, l_a, d)
+    q, kk, v = (torch.bmm(h, t[e.reshape(-1)].contiguous()) for t in leaves[1:4])
+    o = torch.bmm(torch.softmax(torch.bmm(q, kk.transpose(1, 2).contiguous()) / d_h ** 0.5, -1), v)
+    ref = torch.zeros((b * l, d), dtype=torch.float64, device="cuda").index_add(0, flat, torch.bmm(o, leaves[4][e.reshape(-1)].contiguous()).reshape(-1, d))
+    grads = torch.autograd.grad((ref * d_out.double().reshape(-1, d)).sum(), leaves)
+    for name, y, r in zip(("out", "d_x", "d_wq", "d_wk", "d_wv", "d_wo"), (out, dx, *dw), (ref.detach().reshape(b, l, d), *grads)):
+        err = ((y.double() - r).norm() / r.norm()).item()
+        print(f"  {name} {err:.2e}", flush=True)
+        assert err <= 2e-6   # four contractions and a softmax in a row
