@@ -91,20 +91,20 @@ struct UomeBwdWs {
     int splits, gchunks;
 };
 static bool uome_bwd_mfma(const uoe_block_desc *blk);
-// Parts of the any-shape weight gradients: at most `parts`, fewer where that saves a round of workgroups (two a compute
-// unit) worth more than the longer sums of each: 128 samples of 14 x 14 tokens, 6 experts: 7 parts, 504 workgroups, instead of
-// 8 and 576: UoME 107 -> 96 us, SMHA 53 -> 49.
-long wgrad_parts(int sets, int n, int rows, int cols, long parts)
+// Parts of the any-shape weight gradients: at most `parts`, fewer where the compute unit with the most workgroups has less to do then.
+// UoME backward of 128 samples of 14 x 14 tokens, d 384, d_e 256, bf16: 6 experts 8 parts 257 us (576 workgroups, three on some units), 7 parts 240 (504,
+// two); 8 experts 8 parts 318 (768, three on each), 5 parts 323 (480); fp32, 24 samples of 500 tokens, d 768, d_e 192, 4 experts: 5 parts 447, 6 parts 405.
+long wgrad_parts(bool f32, int sets, int n, int rows, int cols, long parts)
 {
-    const auto workgroups = [&](long s) {   // the tiles launch_gemm_tail takes
-        const long groups = sets * n * s, wide = (cols + 127) / 128, t128 = groups * ((rows + 127) / 128) * wide;
-        return rows > 64 && t128 >= 256 ? t128 : groups * ((rows + 63) / 64) * wide;
+    const auto longest = [&](long s) {
+        const long groups = sets * n * s;
+        const TailTile t = tail_tile(f32, true, false, groups, rows, cols);
+        const long a_unit = (groups * ((rows + t.rows - 1) / t.rows) * ((cols + t.cols - 1) / t.cols) + 255) / 256;
+        return (a_unit > 1 ? (double)a_unit : 1.5) * t.rows * t.cols / s;   // (one by itself waits for its loads)
     };
     long best = parts;
-    for (long s = parts - 1; s >= 1; --s) {
-        const long rounds = (workgroups(s) + 511) / 512, best_rounds = (workgroups(best) + 511) / 512;
-        if (rounds * best < best_rounds * s) best = s;
-    }
+    for (long s = parts - 1; s >= 1; --s)
+        if (longest(s) < longest(best)) best = s;
     return best;
 }
 UomeBwdWs uome_bwd_ws(const uoe_block_desc *d)
@@ -124,7 +124,7 @@ UomeBwdWs uome_bwd_ws(const uoe_block_desc *d)
         long s = 4096 / tiles, most = (long)d->b * d->k > d->l / 256 ? (long)d->b * d->k : d->l / 256;
         s = s < 1 ? 1 : (s > 8 ? 8 : s);
         if (s > most) s = most;
-        s = wgrad_parts(2 * chunks, d->n, d->width, d->d, s / chunks > 1 ? s / chunks : 1);
+        s = wgrad_parts(d->dtype == UOE_F32, 2 * chunks, d->n, d->width, d->d, s / chunks > 1 ? s / chunks : 1);
         w.splits = (int)s * chunks;
         w.partial = w.total;
         const size_t partial = (size_t)2 * d->n * w.splits * d->d * d->width;
@@ -207,7 +207,7 @@ SmhaBwdWs smha_bwd_ws(const uoe_block_desc *d)
         const int need = (nb * d->c + BWD_ANY_SEGMENTS - 1) / BWD_ANY_SEGMENTS;
         const long avg = ((long)d->b * d->k * d->c / chunks + d->n - 1) / d->n;
         long parts = avg / 8;
-        parts = wgrad_parts(4 * chunks, d->n, d->width, d->d, parts < 1 ? 1 : (parts > 8 ? 8 : parts));
+        parts = wgrad_parts(d->dtype == UOE_F32, 4 * chunks, d->n, d->width, d->d, parts < 1 ? 1 : (parts > 8 ? 8 : parts));
         w.splits = (int)(parts > need ? parts : need) * chunks;
         w.partial = off;
         off += up((size_t)w.splits * 4 * d->n * d->d * d->width * sizeof(float));

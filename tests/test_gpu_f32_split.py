@@ -257,6 +257,44 @@ def test_every_forward_tile(shape, want_tile, x_size):
     assert (got - want).norm() <= 2e-6 * want.norm()
 
 
+# b, l, d, n, k, d_e; tiles of Z / dH, of d_u, of the weight gradients
+UOME_BACKWARD_TILES = [((8, 77, 200, 4, 2, 136), (64, 64, True), (32, 64, True), (64, 64, False)),
+                       ((8, 200, 504, 8, 2, 248), (64, 64, True), (64, 64, True), (128, 128, False)),
+                       ((32, 250, 504, 4, 2, 136), (64, 64, False), (64, 128, False), (64, 128, False)),
+                       ((64, 250, 504, 2, 2, 264), (128, 128, False), (128, 128, False), (64, 128, False)),
+                       ((40, 140, 136, 2, 1, 72), (64, 64, True), (64, 64, False), (64, 64, False))]
+
+
+@pytest.mark.parametrize("g_size", [1.0, 1e32])
+@pytest.mark.parametrize("shape,dual,du,wgrad", UOME_BACKWARD_TILES)
+def test_every_uome_backward_tile(shape, dual, du, wgrad, g_size):
+    """The dual launch, [n][k] right operands and weight gradients; an upstream gradient of 1e32 takes each of them through the second
+    contraction (it overflows in the split)."""
+    b, l, d, n, k, d_e = shape
+    print(f"fp32 uome backward {shape} gradient {g_size}", flush=True)
+    large, few = l > 64 and b * -(-l // 128) * -(-k * d_e // 128) >= 256, b * -(-l // 64) * -(-k * d_e // 64) <= 256
+    assert dual == ((128, 128, False) if large else (64, 64, few)) and du == tile(False, False, b, l, d)
+    u, w_in, w_out, idx = make(b, l, d, n, k, d_e)
+    blk = B.block_desc(b, l, d, n, k, 1, 1, d_e, B.F32, 0)
+    nbytes = B.uome_backward_workspace_bytes(blk)
+    parts = (nbytes - 2 * b * l * k * d_e * 4) // (2 * n * d * d_e * 4)   # one chunk of samples
+    assert wgrad == tile(True, False, 2 * n * parts, d_e, d)
+    d_out = g_size * torch.randn(u.shape, generator=torch.Generator(device="cuda").manual_seed(8), device="cuda")
+    got, gate = [torch.empty_like(t) for t in (u, w_in, w_out)], torch.ones((b, n), device="cuda")
+    B.uome_backward(blk, u, w_in, w_out, idx, gate, None, None, d_out, *got, torch.empty_like(gate), None,
+                    torch.empty(nbytes, dtype=torch.uint8, device="cuda"))
+    leaves = [t.double().requires_grad_(True) for t in (u, w_in, w_out)]
+    out = 0
+    for s in range(k):
+        e = idx[:, s].long()
+        z = torch.bmm(leaves[0], leaves[1][e].contiguous())
+        out = out + torch.bmm(z * torch.sigmoid(z), leaves[2][e].contiguous())
+    for name, y, r in zip(("u", "in", "out"), got, torch.autograd.grad((out * d_out.double()).sum(), leaves)):
+        err = ((y.double() - r).norm() / r.norm()).item()
+        print(f"  d_{name} {err:.2e}", flush=True)
+        assert err <= 2e-6
+
+
 # b, patches, tokens of one, d, n, k, c, d_h; tiles of q, k, v, of the out-projection and of d_x
 SMHA_TILES = [((4, 6, 9, 136, 4, 2, 3, 40), (32, 64, True), (32, 64, True), (32, 64, True)),
               ((16, 10, 20, 200, 4, 3, 6, 128), (64, 64, False), (32, 64, True), (32, 64, True)),
