@@ -11,7 +11,7 @@
 //    fp64 as with fp32 operands, to four digits; the gate gradients, outputs in fp32, are formed before the split.
 //  * attention: both products of every tile in fp32 (v_mfma_f32_32x32x2_f32), probabilities never stored.
 // The vector-ALU kernels before it took one thread per output element (SMHA) or 64x64 tiles fetched element by
-// element (UoME): vit shape, bf16, layer forward + backward 4617 us, lm shape in fp32 2423 us; here 695 and 550 us.
+// element (UoME): vit shape, bf16, layer forward + backward 4617 us, lm shape in fp32 2423 us; here 700 and 558 us.
 // Every sum has a fixed order (no atomics: results do not depend on scheduling).
 #include "common.h"
 #include "problems.h"
@@ -438,9 +438,9 @@ __device__ __forceinline__ bool any_key_ok(const SmhaArgs &f, int g, int key, in
 // wave per block the lm shape in fp32 has 128 of them for 1024 SIMDs.
 // ONE: one tile a wave (units of up to 32 KS rows).  The query-owning kernel stages it once (the merges take the place of TB, which
 // only the first walk reads) and keeps its scores and dP in registers: four products instead of seven, the same bits.  No tile is
-// in flight during the products, so that two waves fit a SIMD where the general form's registers let one:
-// 340 / 423 registers -> 169 at d_h 64 (no scratch at 128, 156 / 884 bytes before); 384 units of 56 rows, d_h 64: 44.4 -> 27.3 us owning
-// queries, 27.1 -> 22.0 owning keys.  vit shape forward + backward 712 -> 698 us, lm in fp32 556 -> 547.
+// in flight during the products: 302 / 423 registers -> 156 to 158 at d_h 64, where LDS lets two waves on a SIMD (36 KiB for two waves, 72
+// for four) and the general form's registers one (at 128 no scratch, 156 / 884 bytes before); 384 units of 56 rows, d_h 64: 44.4 -> 27.3
+// us owning queries, 27.1 -> 22.0 owning keys.  vit shape forward + backward 712 -> 698 us.
 template <typename T, int DH, int NQ, int KS, bool KV, bool ONE>
 __global__ __launch_bounds__(NQ *KS * 64, (ONE && DH <= 64) || DH == 32 ? 2 : 1) void attention_bwd_f32_kernel(SmhaBwdArgs a)
 {
@@ -817,8 +817,10 @@ template <typename T, int DH> void launch_attention_bwd_f32_dh(const SmhaBwdArgs
     const long blocks = (long)((l_a + 31) / 32) * units;
     // up to 128 rows a wave for every streamed tile, however many blocks there are (owning queries / keys, us; a wave per block
     // with all tiles -> this): 768 units of 56 rows 82 / 48 -> 50 / 44, 384 of 112 136 / 76 -> 80 / 64, 768 of 126 and d_h 40 202 / 108
-    // -> 125 / 106, 768 of 56 and d_h 128 169 / 157 -> 102 / 84; 192 of 112, two waves -> four, 81 / 41 -> 51 / 41.  Longer
-    // units: splits while the launch has fewer waves than SIMDs.
+    // -> 125 / 106, 768 of 56 and d_h 128 169 / 157 -> 102 / 84; 192 of 112, two waves -> four, 81 / 41 -> 51 / 41.  From 65 rows on some
+    // of four waves have no tile, and under the causal mask more: the whole backward pass in bf16, d_h 40, 384 units of 65 rows, one wave a
+    // block 207, two 214, four 154; causal 169, 182, 155; 768 units, causal 229, 271, 222; in fp32, d_h 120, causal 615, 701, 604.  Longer units:
+    // splits while the launch has fewer waves than SIMDs.
     const int ks = l_a <= 32 ? 1 : l_a <= 64 ? 2 : l_a <= 128 || blocks < 512 ? 4 : blocks < 1024 ? 2 : 1;
     const dim3 grid((l_a + 31) / 32, units);
 #define UOE_ABW(KS, ONE)                                                                                       \

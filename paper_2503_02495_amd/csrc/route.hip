@@ -1286,7 +1286,8 @@ static hipError_t launch_stream(const RouteArgs &a, const RouteStreamPlan &sp, d
 }
 
 // a kernel of its own, behind the others: as two instances of one template where route_select_kernel stands the lm forward took 0.5
-// to 1 percent more with the same instructions (the kernels of one pass share an instruction cache that does not hold them all)
+// to 1 percent more with the same instructions in each kernel (measured; why was not found, and other changes of the code's size move
+// single calls by up to 1.5 percent either way)
 __global__ __launch_bounds__(SELECT_THREADS) void route_select_all_kernel(RouteArgs a, int has_e, int has_d, int fuse_reduce, int rows)
 {
     route_select<true>(a, has_e, has_d, fuse_reduce, rows);
