@@ -1,6 +1,6 @@
 """fp32 attention backward at the line between a tile a wave and several: 32, 64 and 128 rows with one, two and four waves per
 block, one row less (a partly empty last tile) and one more (a wave with two tiles, the others with one), for each padded
-width, and launches of more than 1024 blocks on either side.  Same oracle and bounds as the other backward tests."""
+width, and launches of more than 1024 blocks on either side (one wave with all tiles of longer units, for each padded width).  Same oracle and bounds as the other backward tests."""
 import pytest
 
 import test_gpu_parity as P
@@ -20,6 +20,8 @@ CONFIGS = {f"one_{rows}_dh{d_h}": shape(2, rows, d_h, dtype=BF if rows % 2 else 
            for rows in (31, 32, 33, 64, 65, 127, 128, 129) for d_h in (24, 64, 128)}
 CONFIGS["one_520_units"] = shape(130, 60, 64, n=4)
 CONFIGS["several_206_units"] = shape(103, 130, 24)
+CONFIGS["several_206_units_dh64"] = shape(103, 130, 64)
+CONFIGS["several_206_units_dh128"] = shape(103, 130, 128, dtype=BF)
 
 
 @pytest.mark.parametrize("name", list(CONFIGS))

@@ -1,5 +1,6 @@
-"""The fp32 contractions on split bf16 products: K one step past the fp32 instruction's range and inside a step, every tile
-choice with rows and columns past a tile, and operands that are not finite; the same for the fp32 attention."""
+"""The fp32 contractions on split bf16 products: K one step past the fp32 instruction's range and inside a step, segments of a
+K-step and less, values at the ends of the range, every tile and operand layout, and operands that are not finite (or overflow in the
+split: every tile's second contraction).  The fp32 attention, and what the bf16 one off the 32-grid does with such values."""
 import pytest
 import torch
 

@@ -26,7 +26,8 @@ ODD = {
     "flags_tail": P.small(b=2, l=272, d=64, n_a=2, d_h=128, m=2, c=1, k_a=1, n_m=2, d_e=64, k_m=1, dtype=BF),
     # enough 128-row tiles for the large-tile choice, rows and columns 8 past two tiles
     "odd_big": P.small(b=32, l=264, d=136, n_a=2, d_h=16, m=8, c=8, k_a=2, n_m=2, d_e=136, k_m=2, dtype=BF),
-    # fp32: the same, and every launch shape of the fp32 attention (1 or 2 query blocks, 1 or 2 key splits)
+    # fp32: the same sizes (64x64 tiles there; every fp32 tile: test_gpu_f32_split.py), and the launch shapes of the fp32 attention: one or two
+    # query blocks, one, two or four key splits
     "f32_big": P.small(b=32, l=264, d=136, n_a=2, d_h=16, m=8, c=8, k_a=2, n_m=2, d_e=136, k_m=2),
     "f32_many_units": P.small(b=64, l=264, d=40, n_a=2, d_h=40, m=8, c=8, k_a=2, n_m=2, d_e=24, k_m=1),
     "f32_one_tile": P.small(b=2, l=32, d=64, n_a=2, d_h=64, m=1, c=1, k_a=1, n_m=2, d_e=64, k_m=1),
@@ -93,8 +94,8 @@ UOME_BWD = {
     "ub_wide": P.small(b=2, l=20, d=16, n_a=2, d_h=8, m=1, c=1, k_a=1, n_m=2, d_e=2056, k_m=1, dtype=BF),
     # ranges of the token axis, the last one short; one expert, one sample
     "ub_ranges": P.small(b=1, l=1100, d=40, n_a=1, d_h=8, m=1, c=1, k_a=1, n_m=1, d_e=24, k_m=1, dtype=BF),
-    # fp32, 128x128 tiles: in the launch of Z and dH; in the weight gradients (256 of them, five of the eight token ranges
-    # empty, the last one of 13 tokens inside a K-step); in d_u
+    # fp32: 128x128 tiles in the launch of Z and dH; weight gradients with five of the eight token ranges empty, the last one of 13
+    # tokens inside a K-step; d_u of one short K-step
     "ub_f32_big": P.small(b=32, l=264, d=136, n_a=2, d_h=8, m=1, c=1, k_a=1, n_m=2, d_e=136, k_m=2),
     "ub_f32_wgrad": P.small(b=8, l=77, d=136, n_a=2, d_h=8, m=1, c=1, k_a=1, n_m=4, d_e=136, k_m=2),
     "ub_f32_du": P.small(b=64, l=264, d=136, n_a=2, d_h=8, m=1, c=1, k_a=1, n_m=2, d_e=24, k_m=1),
@@ -115,11 +116,12 @@ SMHA_BWD = {
     "sb_dh120": P.small(b=2, l=198, d=40, n_a=3, d_h=120, m=6, c=3, k_a=2, n_m=2, d_e=32, k_m=1, dtype=BF),
     "sb_f32_dh128": P.small(b=1, l=200, d=64, n_a=2, d_h=128, m=4, c=3, k_a=1, n_m=2, d_e=32, k_m=1),
     "sb_f32_b130": P.small(b=130, l=8, d=16, n_a=2, d_h=8, m=4, c=2, k_a=1, n_m=2, d_e=32, k_m=1),
-    # 1024, 512 and fewer 32-row blocks: one, two and four waves per block
+    # 72 rows in four waves of at most a tile each, however many blocks; longer units: two waves from 512 32-row blocks on, four below
+    # (one from 1024 on: test_gpu_attention_one_tile.py)
     "sb_f32_ks1": P.small(b=128, l=72, d=16, n_a=4, d_h=16, m=2, c=2, k_a=4, n_m=2, d_e=32, k_m=1),
     "sb_f32_ks2": P.small(b=64, l=130, d=16, n_a=2, d_h=64, m=2, c=2, k_a=2, n_m=2, d_e=32, k_m=1),
     "sb_f32_ks4": P.small(b=2, l=300, d=24, n_a=3, d_h=32, m=10, c=9, k_a=2, n_m=2, d_e=32, k_m=1),
-    # 128-column heads in 128x128 weight-gradient tiles (8 experts in 8 parts)
+    # 128-column heads, weight gradients of 8 experts in 8 parts (bf16: 128x128 tiles)
     "sb_f32_wgrad": P.small(b=32, l=72, d=40, n_a=8, d_h=128, m=9, c=8, k_a=2, n_m=2, d_e=32, k_m=1),
     "sb_wgrad": P.small(b=32, l=72, d=40, n_a=8, d_h=120, m=9, c=8, k_a=2, n_m=2, d_e=32, k_m=1, dtype=BF),
     # 32-grid: dO on 128-row tiles with K-steps of 64 and of 32
