@@ -353,7 +353,7 @@ hipError_t launch_probe_mfma(const void *operands, int iters, float *sink, hipSt
 // host-side sizing shared by api.hip and the launchers
 int route_tokens_per_chunk(int b, int l);
 int route_expert_mfma_tokens_per_chunk(int b, int l, int d, int n);
-int route_data_tokens_per_chunk(int b, int l, int d, int n, bool bf16);
+int route_data_tokens_per_chunk(int b, int l, int d, int n, int m, bool bf16);
 // streaming router kernel: applicability and launch shape (host side)
 constexpr int ROUTE_STREAM_CHUNKS = 256;      // one workgroup per compute unit
 struct RouteStreamPlan {

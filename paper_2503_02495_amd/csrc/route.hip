@@ -12,8 +12,9 @@
 //                       of the n W_E slices and keeps n running dot products per lane (a W_E chunk
 //                       is shared by the b samples through L2).
 //   route_data_mfma   : data router, bf16.  t1 = x W_B for 16 tokens per wave as
-//                       v_mfma_f32_16x16x32_bf16 (A fragments straight from global, W_B^T staged in
-//                       LDS), then the chunk's rows of W_A fold t1 into a partial [n,m] logit tile.
+//                       v_mfma_f32_16x16x32_bf16 (A fragments straight from global, W_B staged in
+//                       LDS), then the tokens' rows of W_A fold t1, still in the accumulators, into a partial
+//                       [n,m] logit tile as v_mfma_f32_16x16x4_f32.
 //   route_partial<D>  : the same data router on the vector ALU (fp32 storage, or W_B too large
 //                       for LDS next to the MFMA staging).
 //   route_reduce      : sums the data router's per-chunk partials in a fixed order (deterministic).
@@ -58,27 +59,16 @@ int route_expert_mfma_tokens_per_chunk(int b, int l, int d, int n)
     return tc < 1 ? 1 : tc;
 }
 
-// Data router: tokens per chunk and whether the MFMA kernel applies.  waves*16 tokens per chunk for
-// the MFMA kernel, else the expert router's chunking.
-static int data_mfma_waves(int, int)
-{
-    return 4;  // 64 tokens per workgroup: the W_B staging is shared by four waves
-}
-// LDS of the MFMA data router: W_B as it is, [d][np] in blocks of 8 rows (see the kernel), then t1.
-static size_t data_mfma_wb_bytes(int n, int d)
-{
-    const int np = (n + 15) & ~15;
-    return (size_t)((d + 7) / 8) * (8 * np * 2 + (np == 16 ? 128 : 32));
-}
-static size_t data_mfma_lds(int n, int d, int waves)
-{
-    const int np = (n + 15) & ~15;
-    // W_B, t1 [waves*16][np], and the fold's per-token-group partial sums (at most 8 per thread)
-    return data_mfma_wb_bytes(n, d) + (size_t)waves * 16 * np * sizeof(float) + (size_t)waves * 64 * 8 * sizeof(float);
-}
+constexpr int DATA_TOKENS = 64;    // tokens the data router's MFMA kernel takes at a time,
+constexpr int DATA_FOLD_TILES = 4; // and 16-patch tiles it folds them onto at a time
+// Whether the data router's MFMA kernel applies: W_B, 64 tokens' t1 and the fold's partial sums side by side within 60 KiB (what
+// the kernel holds at a time is less).
 bool route_data_uses_mfma(int b, int l, int d, int n, bool bf16)
 {
-    return bf16 && data_mfma_lds(n, d, data_mfma_waves(b, l)) <= 60 * 1024;
+    (void)b; (void)l;
+    const int np = (n + 15) & ~15;
+    const size_t wb = (size_t)((d + 7) / 8) * (8 * np * 2 + (np == 16 ? 128 : 32));
+    return bf16 && wb + (size_t)64 * np * sizeof(float) + 256 * 8 * sizeof(float) <= 60 * 1024;
 }
 // Plan of the streaming router kernel (route_stream_kernel): one workgroup per compute unit, each
 // owning a contiguous run of whole tokens.
@@ -125,10 +115,19 @@ bool route_stream_pays(int b, int l, int d, int n)
     const double min_bytes = env ? atof(env) : 100e6;
     return ((double)b + n) * l * d * 2 >= min_bytes;
 }
-int route_data_tokens_per_chunk(int b, int l, int d, int n, bool bf16)
+// Tokens per chunk of the data router: the MFMA kernel's workgroup, also the chunks of route_fold_kernel.  16 (the waves split the
+// columns) up to 256 workgroups, while route_select adds that many partial tiles up by itself: 64 workgroups of 64 keep a quarter of the
+// compute units on x (8 x 512 x 512: 8.7 -> 6.5 us; 6 x 1000 x 360 6.7 with 64, 7.3 with 16).  Two times 64 where the workgroups still
+// fill the chip twice: half of the partial tiles, and on 16 x 4096 x 256, 8 x 64 logits, no launch of route_reduce (119.4 us for the
+// layer's forward against 124.6).
+int route_data_tokens_per_chunk(int b, int l, int d, int n, int m, bool bf16)
 {
-    if (route_stream_plan(b, l, d, n, bf16, true).ok) return 64;  // chunks of route_fold_kernel
-    if (route_data_uses_mfma(b, l, d, n, bf16)) return 16 * data_mfma_waves(b, l);
+    if (route_data_uses_mfma(b, l, d, n, bf16)) {
+        const long tokens = (long)b * l;
+        if (tokens <= 4096 && n * m <= 512 && (long)n * m * ((l + 15) / 16) <= 16384) return DATA_TOKENS / 4;
+        return tokens > 48 * 1024 && m <= DATA_FOLD_TILES * 16 ? 2 * DATA_TOKENS : DATA_TOKENS;
+    }
+    if (route_stream_plan(b, l, d, n, bf16, true).ok) return 64;
     return route_tokens_per_chunk(b, l);
 }
 
@@ -268,22 +267,20 @@ typedef float rt_f32x4 __attribute__((ext_vector_type(4)));
 typedef short rt_s16x4 __attribute__((ext_vector_type(4)));
 typedef rt_s16x4 __attribute__((address_space(3))) * rt_lds_s16x4_ptr;
 
-// Second half of the data router (Eq. 13): fold per-token expert scores with the chunk's rows of W_A,
-// g[i][j] = sum_t t1[t][i] * W_A[t0 + t][j], for the tokens t0 .. t0 + tcur of sample bb, into the
-// chunk's partial logit tile gpart[chunk][bb][n*m].  t1s: LDS, [token][np] fp32.  A thread owns
+// Second half of the data router (Eq. 13) behind the streaming kernel, any m: fold per-token expert scores with the chunk's rows of W_A,
+// g[i][j] = sum_t t1[t][i] * W_A[t][j], for the tcur tokens of the chunk, into sample bb's
+// partial logit tile gpart[chunk][bb][n*m].  t1s: LDS, [token][np] fp32.  A thread owns
 // (token group tg, output group og): one expert i and VEC consecutive patches, for the tokens
 // tg, tg + TG, ...; the TG partial sums of an output are then added in group order.  (With few
 // outputs per sample, one thread per output would leave most of the workgroup idle behind a
 // serial walk over all the chunk's tokens.)  part: LDS scratch of NTHREADS * 8 floats.
-// gpart is indexed with the chunk number, W_A with t0 + token unless w_a_rows is given.
+// w_a: LDS copy of the chunk's rows.
 template <int NTHREADS>
-__device__ __forceinline__ void route_fold(const RouteArgs &a, int chunk, int bb, int t0, int tcur, const float *t1s, int np,
-                                           float *part, const uint16_t *w_a_rows = nullptr)
+__device__ __forceinline__ void route_fold(const RouteArgs &a, int chunk, int bb, int tcur, const float *t1s, int np,
+                                           float *part, const uint16_t *w_a)
 {
     const int tid = threadIdx.x;
     const int n = a.n, m = a.m;
-    // rows of W_A: global memory (row t0 + tl), or a copy of the chunk's rows (row tl; the caller passes t0 = 0)
-    const uint16_t *w_a = w_a_rows ? w_a_rows : static_cast<const uint16_t *>(a.w_a);
     const int nm = n * m;
     float *gout = a.gpart + ((size_t)chunk * a.b + bb) * nm;
     const int vec = (m & 7) == 0 ? 8 : 1, mv = m / vec, og_n = n * mv;
@@ -297,7 +294,7 @@ __device__ __forceinline__ void route_fold(const RouteArgs &a, int chunk, int bb
 #pragma unroll 4
             for (int tl = tl0; tl < tcur; tl += tstep) {
                 float wv[8];
-                load8(reinterpret_cast<const bf16_t *>(w_a) + (size_t)(t0 + tl) * m + j0, wv);
+                load8(reinterpret_cast<const bf16_t *>(w_a) + (size_t)tl * m + j0, wv);
                 const float t1 = t1s[tl * np + i];
 #pragma unroll
                 for (int q = 0; q < 8; ++q) sacc[q] = fmaf(t1, wv[q], sacc[q]);
@@ -305,9 +302,11 @@ __device__ __forceinline__ void route_fold(const RouteArgs &a, int chunk, int bb
         } else {
 #pragma unroll 4
             for (int tl = tl0; tl < tcur; tl += tstep)
-                sacc[0] = fmaf(t1s[tl * np + i], __uint_as_float((uint32_t)w_a[(size_t)(t0 + tl) * m + j0] << 16), sacc[0]);
+                sacc[0] = fmaf(t1s[tl * np + i], __uint_as_float((uint32_t)w_a[(size_t)tl * m + j0] << 16), sacc[0]);
         }
-        for (int q = 0; q < vec; ++q) dst[i * m + j0 + q] = sacc[q];
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (q < vec) dst[i * m + j0 + q] = sacc[q];
     };
     if (tg_n > 1) {
         const int og = tid % og_n, tg = tid / og_n;
@@ -333,114 +332,216 @@ __device__ __forceinline__ void stage_w_b(const RouteArgs &a, unsigned char *wb)
     constexpr int ROWB = NP * 2, BLK = 8 * ROWB + (NP == 16 ? 128 : 32);
     const int tid = threadIdx.x, n = a.n, d = a.d;
     const uint16_t *w_b = static_cast<const uint16_t *>(a.w_b);
-    auto row_at = [&](int e) { return wb + (size_t)(e >> 3) * BLK + (e & 7) * ROWB; };
-    if ((n & 7) == 0) {  // 16-byte pieces never straddle a row
-        const int pr = n >> 3;
-#pragma unroll 4
-        for (int idx = tid; idx < d * pr; idx += NTHREADS) {
-            const int e = idx / pr, pc = idx - e * pr;
-            *reinterpret_cast<uint4 *>(row_at(e) + pc * 16) = *reinterpret_cast<const uint4 *>(w_b + (size_t)idx * 8);
+    // the widest piece that never straddles a row; several of them a thread in flight together (a loop's remainder, one at a time, waits
+    // out a memory round trip each)
+    auto stage = [&](auto piece, int pr) __attribute__((always_inline)) {   // pr pieces a row
+        typedef decltype(piece) P;
+        constexpr int BATCH = sizeof(P) == 16 ? 4 : 8;
+        const int pieces = d * pr;
+        // piece / pr by the reciprocal rounded up: exact below 2^16 pieces (d * n <= 24576)
+        const uint32_t inv = pr > 1 ? 0xFFFFFFFFu / (uint32_t)pr + 1u : 0u;
+        for (int i0 = tid; i0 < pieces; i0 += BATCH * NTHREADS) {
+            P v[BATCH];
+#pragma unroll
+            for (int q = 0; q < BATCH; ++q) v[q] = reinterpret_cast<const P *>(w_b)[min(i0 + q * NTHREADS, pieces - 1)];
+#pragma unroll
+            for (int q = 0; q < BATCH; ++q) {
+                const int idx = i0 + q * NTHREADS, e = pr > 1 ? (int)__umulhi((uint32_t)idx, inv) : idx;
+                if (idx < pieces) *reinterpret_cast<P *>(wb + (e >> 3) * BLK + (e & 7) * ROWB + (idx - e * pr) * (int)sizeof(P)) = v[q];
+            }
         }
-    } else if ((n & 1) == 0) {
-        const int pr = n >> 1;
-#pragma unroll 4
-        for (int idx = tid; idx < d * pr; idx += NTHREADS) {
-            const int e = idx / pr, pc = idx - e * pr;
-            *reinterpret_cast<uint32_t *>(row_at(e) + pc * 4) = *reinterpret_cast<const uint32_t *>(w_b + (size_t)idx * 2);
-        }
-    } else {
-#pragma unroll 4
-        for (int idx = tid; idx < d * n; idx += NTHREADS) {
-            const int e = idx / n, i = idx - e * n;
-            *reinterpret_cast<uint16_t *>(row_at(e) + i * 2) = w_b[idx];
-        }
-    }
+    };
+    if ((n & 7) == 0) stage(once_u32x4{}, n >> 3);
+    else if ((n & 1) == 0) stage(uint32_t{}, n >> 1);
+    else stage(uint16_t{}, n);
 }
 
-// Data router (Eq. 13), bf16, MFMA.  Workgroup = WAVES waves = WAVES*16 tokens of one sample.
+// Data router (Eq. 13), bf16, MFMA.  Workgroup = four waves = a.tc_d tokens of one sample, 64 at a time (16 per wave), or KS = 4: 16
+// tokens, of which each wave takes a quarter of the columns.
 // MFMA 16x16x32 operand layout: lane = (row r = lane%16, k-slice 8*(lane/16)); accumulator register q
 // of a lane is output row 4*(lane/16)+q, column lane%16.
-// W_B [d, n] is copied to LDS as it is (rows of np = 16 or 32 columns; columns >= n are left as
-// they are: they only feed output columns that are never read) and the B fragments (8 consecutive k
+// t1 = x W_B: rows = tokens, columns = experts.  W_B [d, n] is copied to LDS as it is (rows of np = 16 or 32 columns; columns >= n are
+// left as they are: they only feed output columns that are never read) and the B fragments (8 consecutive k
 // of one expert column) are taken with the transposing LDS read: in a group of 16 lanes, lane j
 // points at row k0 + j/4, columns 4*(j%4)..+3, and lane i receives column i, rows k0..k0+3.  Rows are
 // stored in blocks of 8 with a pad after each block (128 bytes for 32-byte rows, 32 bytes for
 // 64-byte rows) so that the row groups of the four k-slices fall into different banks.
-template <int WAVES, int NTILE>
-__device__ __forceinline__ void route_data_mfma_body(const RouteArgs &a, int chunk, int bb, unsigned char *smem)
+// The fold g = t1^T W_A takes t1 where it is: register j of a lane is token 4*(lane/16)+j of expert lane%16, which is the A operand of
+// v_mfma_f32_16x16x4_f32 for the four tokens j, 4+j, 8+j, 12+j, so that four of them, exact fp32 products, fold 16 tokens onto 16
+// patches; their W_A values are one 2-byte load each, for any m.  The waves' tiles are added in wave order.
+// What bounds it is the chain of dependent steps, on 64 to 512 workgroups: a memory round trip costs 2 us at the start of a launch, so
+// 512 columns of x, W_B and the first 64 columns of W_A are in flight together, and the k-steps' fragments are read four steps ahead of their products.
+// Both routers' launch, us, against W_A fetched for a fold on the vector ALU behind the products and one set of 128 columns in flight:
+// 8 x 512 x 512, n 8, m 16: 10.2 -> 6.5; 6 x 1000 x 360, n 6, m 25: 12.2 -> 6.7; 128 x 196 x 384, n 6, m 14: 13.7 -> 11.3.
+// LDS: W_B, and in its place at the end the four waves' tiles of n x 64 sums
+static size_t data_lds(int n, int d)
 {
-    constexpr int NTHREADS = WAVES * 64, TC = WAVES * 16;
-    constexpr int NP = NTILE * 16, ROWB = NP * 2, BLK = 8 * ROWB + (NP == 16 ? 128 : 32);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int d = a.d, l = a.l;
-    const int np = NP;
-    const int t0 = chunk * TC, tcur = min(TC, l - t0);
-    unsigned char *wb = smem;                                   // W_B rows, blocked
-    float *t1s = reinterpret_cast<float *>(smem + (size_t)((d + 7) / 8) * BLK);  // [TC][np]
-
-    // A fragments of the first steps are requested before the staging copy so both are in flight together
-    const int r = lane & 15, ksl = (lane >> 4) * 8;
-    const int trow = min(t0 + wave * 16 + r, l - 1);  // rows past the end repeat the last token; never used
-    const uint16_t *xr = static_cast<const uint16_t *>(a.x) + ((size_t)bb * l + trow) * d;
-    constexpr int UN = 4;  // k-steps whose A fragments are in flight together
-    auto load_a = [&](int k0, uint4 (&av)[UN]) {
-#pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            const int kk = k0 + u * 32 + ksl;
-            const bool ok = kk < d;  // slices past d (d % 128 != 0) contribute zero
-            av[u] = *reinterpret_cast<const uint4 *>(xr + (ok ? kk : 0));
-            if (!ok) av[u] = make_uint4(0, 0, 0, 0);
-        }
-    };
-    uint4 av[UN];
-    load_a(0, av);
-
-    auto row_at = [&](int e) { return wb + (size_t)(e >> 3) * BLK + (e & 7) * ROWB; };
-    stage_w_b<NP, NTHREADS>(a, wb);
-    __syncthreads();
-
-    rt_f32x4 acc[NTILE];  // NTILE tiles of 16 experts
-#pragma unroll
-    for (int t = 0; t < NTILE; ++t)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) acc[t][q] = 0.f;
-    // transposing-read lane roles: k-slice group lane/16, row (lane%16)/4 of the group's 4, 4 columns
-    const int tr_row = (lane >> 4) * 8 + ((lane & 15) >> 2), tr_col = (lane & 3) * 4;
-    for (int k0 = 0; k0 < d; k0 += 32 * UN) {
-        uint4 nv[UN] = {};
-        if (k0 + 32 * UN < d) load_a(k0 + 32 * UN, nv);
-#pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            // rows past d: the A side is zero; read a valid row so that the product stays finite
-            const int kr = min(k0 + u * 32 + tr_row, d - 8 + ((lane & 15) >> 2));
-            const rt_bf16x8 af = __builtin_bit_cast(rt_bf16x8, av[u]);
-#pragma unroll
-            for (int t = 0; t < NTILE; ++t) {
-                const unsigned char *src = row_at(kr) + (t * 16 + tr_col) * 2;
-                const rt_s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((rt_lds_s16x4_ptr)(src));
-                const rt_s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((rt_lds_s16x4_ptr)(row_at(kr + 4) + (t * 16 + tr_col) * 2));
-                const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
-                const rt_bf16x8 bfr = __builtin_bit_cast(rt_bf16x8, make_uint4(l2.x, l2.y, h2.x, h2.y));
-                acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bfr, acc[t], 0, 0, 0);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < UN; ++u) av[u] = nv[u];
-    }
-#pragma unroll
-    for (int t = 0; t < NTILE; ++t)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) t1s[(wave * 16 + (lane >> 4) * 4 + q) * np + t * 16 + r] = acc[t][q];
-    __syncthreads();
-
-    route_fold<NTHREADS>(a, chunk, bb, t0, tcur, t1s, np, t1s + TC * np);
+    const int np = (n + 15) & ~15;
+    const size_t wb = (size_t)((d + 7) / 8) * (8 * np * 2 + (np == 16 ? 128 : 32));
+    const size_t sums = (size_t)4 * np * (DATA_FOLD_TILES * 16 + 4) * sizeof(float);
+    return wb > sums ? wb : sums;
 }
 
-template <int WAVES, int NTILE>
-__global__ __launch_bounds__(WAVES * 64) void route_data_mfma_kernel(RouteArgs a)
+template <int NTILE, int KS>
+__device__ __forceinline__ void route_data_mfma_body(const RouteArgs &a, int chunk, int bb, unsigned char *smem)
+{
+    constexpr int NP = NTILE * 16, ROWB = NP * 2, BLK = 8 * ROWB + (NP == 16 ? 128 : 32);
+    constexpr int UN = KS == 1 ? 8 : 4, SPAN = UN * 32, UB = 4;   // k-steps of one register set (two sets are in flight); fragments read ahead
+    constexpr int TOK = DATA_TOKENS / KS;                   // tokens at a time
+    constexpr int FT = DATA_FOLD_TILES, RP = FT * 16 + 4;   // row pitch of the sums in LDS
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int d = a.d, l = a.l, n = a.n, m = a.m, nm = n * m;
+    unsigned char *wb = smem;
+    float *sums = reinterpret_cast<float *>(smem);               // [wave][NP][RP], once W_B is done with
+    const int begin = chunk * a.tc_d, end = min(l, begin + a.tc_d);
+    // this wave's columns of x and the first of its 16 tokens
+    const int kq = KS == 1 ? d : ((d + 31) / 32 + KS - 1) / KS * 32, kb = KS == 1 ? 0 : min(wave * kq, d), ke = min(d, kb + kq);
+    const int tw = KS == 1 ? wave * 16 : 0;
+    const int reps = (end - begin + TOK - 1) / TOK, spans = (kq + SPAN - 1) / SPAN, sets = reps * spans;
+    const int tiles = (m + 15) / 16;                             // reps > 1 only with at most FT of them
+
+    const int r = lane & 15, q4 = lane >> 4, ksl = q4 * 8;
+    const uint16_t *xb = static_cast<const uint16_t *>(a.x) + (size_t)bb * l * d;
+    struct Set {
+        uint4 v[UN];
+    } set0, set1;
+    int lrep = 0, lspan = 0;   // the set to load next
+    auto load_set = [&](Set &t) __attribute__((always_inline)) {
+        const int trow = min(begin + lrep * TOK + tw + r, l - 1);  // rows past the end repeat the last token; never used
+        const uint16_t *xr = xb + (size_t)trow * d;
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const int kk = kb + lspan * SPAN + u * 32 + ksl;
+            t.v[u] = *reinterpret_cast<const uint4 *>(xr + (kk < ke ? kk : 0));   // slices past the wave's: any piece, zeroed below
+        }
+        if (++lspan == spans) {
+            lspan = 0;
+            ++lrep;
+        }
+    };
+    // W_A of this lane's tokens 4 q4 + j and patch tile * 16 + r (past m or the tokens: any value, never used)
+    uint16_t wa[FT][4] = {};
+    auto load_wa = [&](int rep, int tile0) __attribute__((always_inline)) {
+        const int t0 = begin + rep * TOK + tw + q4 * 4;
+#pragma unroll
+        for (int t = 0; t < FT; ++t) {
+            if (tile0 + t >= tiles) break;   // uniform
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                wa[t][j] = static_cast<const uint16_t *>(a.w_a)[(size_t)min(t0 + j, l - 1) * m + min((tile0 + t) * 16 + r, m - 1)];
+        }
+    };
+    load_set(set0);
+    if (sets > 1) load_set(set1);
+    load_wa(0, 0);
+    stage_w_b<NP, ROUTE_THREADS>(a, wb);
+    __syncthreads();
+
+    rt_f32x4 acc[NTILE], g[NTILE][FT];
+#pragma unroll
+    for (int c = 0; c < NTILE; ++c)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            acc[c][q] = 0.f;
+#pragma unroll
+            for (int t = 0; t < FT; ++t) g[c][t][q] = 0.f;
+        }
+    // transposing-read lane roles: k-slice group lane/16, row (lane%16)/4 of the group's 4, 4 columns
+    const int tr_row = ksl + ((lane & 15) >> 2), tr_col = (lane & 3) * 4;
+    auto fragment = [&](int row, int c) __attribute__((always_inline)) -> rt_bf16x8 {   // rows row..+3 and row+4..+7: one block of 8
+        const unsigned char *src = wb + (row >> 3) * BLK + (row & 7) * ROWB + (c * 16 + tr_col) * 2;
+        const rt_s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((rt_lds_s16x4_ptr)(src));
+        const rt_s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((rt_lds_s16x4_ptr)(src + 4 * ROWB));
+        const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
+        return __builtin_bit_cast(rt_bf16x8, make_uint4(l2.x, l2.y, h2.x, h2.y));
+    };
+    auto fold = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < FT; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float w = __uint_as_float((uint32_t)wa[t][j] << 16);
+#pragma unroll
+                for (int c = 0; c < NTILE; ++c) g[c][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(acc[c][j], w, g[c][t], 0, 0, 0);
+            }
+    };
+    int rep = 0, span = 0;   // of the set to multiply next
+    auto use_set = [&](Set &t, bool next) __attribute__((always_inline)) {   // next: a set to load into these registers
+        const int k0 = kb + span * SPAN;
+#pragma unroll
+        for (int u0 = 0; u0 < UN; u0 += UB) {
+            if (k0 + u0 * 32 >= ke) break;   // uniform
+            rt_bf16x8 f[UB][NTILE];
+#pragma unroll
+            for (int u = 0; u < UB; ++u)
+#pragma unroll
+                for (int c = 0; c < NTILE; ++c)   // slices past the wave's: W_B at a valid row, so that the product with zero stays zero
+                    f[u][c] = fragment(min(k0 + (u0 + u) * 32 + tr_row, d - 8 + ((lane & 15) >> 2)), c);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < UB; ++u) {
+                if (k0 + (u0 + u) * 32 >= ke) break;   // uniform
+                const uint4 xv = k0 + (u0 + u) * 32 + ksl < ke ? t.v[u0 + u] : make_uint4(0, 0, 0, 0);
+#pragma unroll
+                for (int c = 0; c < NTILE; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(rt_bf16x8, xv), f[u][c], acc[c], 0, 0, 0);
+            }
+        }
+        if (next) load_set(t);
+        if (++span < spans) return;
+        span = 0;
+        const int left = end - begin - rep * TOK - tw - q4 * 4;   // of this lane's four tokens
+#pragma unroll
+        for (int c = 0; c < NTILE; ++c)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[c][j] = j < left ? acc[c][j] : 0.f;
+        if (++rep < reps) {
+            fold();
+            load_wa(rep, 0);
+#pragma unroll
+            for (int c = 0; c < NTILE; ++c)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[c][j] = 0.f;
+        }
+    };
+    for (int s = 0; s < sets; s += 2) {
+        use_set(set0, s + 2 < sets);
+        if (s + 1 < sets) use_set(set1, s + 3 < sets);
+    }
+    // the last tokens' fold, tile group by tile group
+    float *gout = a.gpart + ((size_t)chunk * a.b + bb) * nm;
+    for (int tile0 = 0; tile0 < tiles; tile0 += FT) {
+        if (tile0) {
+            load_wa(reps - 1, tile0);
+#pragma unroll
+            for (int c = 0; c < NTILE; ++c)
+#pragma unroll
+                for (int t = 0; t < FT; ++t)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) g[c][t][q] = 0.f;
+        }
+        fold();
+        __syncthreads();   // W_B, or the sums of the group before, are done with
+#pragma unroll
+        for (int c = 0; c < NTILE; ++c)
+#pragma unroll
+            for (int t = 0; t < FT; ++t)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) sums[(wave * NP + c * 16 + q4 * 4 + q) * RP + t * 16 + r] = g[c][t][q];
+        __syncthreads();
+        const int cols = min(FT * 16, m - tile0 * 16);
+        for (int o = tid; o < n * FT * 16; o += ROUTE_THREADS) {
+            const int i = o / (FT * 16), j = o % (FT * 16);
+            const float *at = sums + i * RP + j;
+            if (j < cols) gout[i * m + tile0 * 16 + j] = (at[0] + at[NP * RP]) + (at[2 * NP * RP] + at[3 * NP * RP]);
+        }
+    }
+}
+
+template <int NTILE, int KS>
+__global__ __launch_bounds__(ROUTE_THREADS, NTILE == 1 ? 3 : 2) void route_data_mfma_kernel(RouteArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    route_data_mfma_body<WAVES, NTILE>(a, blockIdx.x, blockIdx.y, smem);
+    route_data_mfma_body<NTILE, KS>(a, blockIdx.x, blockIdx.y, smem);
 }
 
 // Expert router (Eq. 21), bf16, MFMA.  Workgroup = 4 waves = (chunk of a.tc tokens, i.e. a.tc*d
@@ -457,7 +558,7 @@ template <int RT, int CT>
 __device__ __forceinline__ void route_expert_mfma_body(const RouteArgs &a, int chunk, int b0, unsigned char *smem)
 {
     float(*zsh)[RT * 16][CT * 16 + 1] = reinterpret_cast<float(*)[RT * 16][CT * 16 + 1]>(smem);  // [4 waves]
-    constexpr int U = 4;  // steps whose loads are in flight together
+    constexpr int U = RT == 4 ? 2 : 4;  // steps whose loads are in flight together (four: no third wave a SIMD beside 64 samples' rows)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r = lane & 15, q = lane >> 4;
     const int b = a.b, n = a.n;
@@ -544,13 +645,13 @@ __global__ __launch_bounds__(256) void route_expert_mfma_kernel(RouteArgs a)
 // [0, n_data) run the data router with four waves (chunk = id % nchunks_d, sample = id / nchunks_d) -
 // first, because each is a longer chain of dependent steps - and the rest the expert router
 // (chunk = id' % nchunks, sample group = id' / nchunks).
-template <int RT, int CT>
-__global__ __launch_bounds__(256) void route_expert_data_kernel(RouteArgs a, int n_data)
+template <int RT, int CT, int KS>
+__global__ __launch_bounds__(256, CT == 1 ? 3 : 2) void route_expert_data_kernel(RouteArgs a, int n_data)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const int id = blockIdx.x;
     if (id < n_data) {
-        route_data_mfma_body<4, CT>(a, id % a.nchunks_d, id / a.nchunks_d, smem);
+        route_data_mfma_body<CT, KS>(a, id % a.nchunks_d, id / a.nchunks_d, smem);
     } else {
         const int f = id - n_data;
         route_expert_mfma_body<RT, CT>(a, f % a.nchunks, (f / a.nchunks) * RT * 16, smem);
@@ -772,7 +873,7 @@ __global__ __launch_bounds__(256) void route_fold_kernel(RouteArgs a)
     const float *src = a.t1 + ((size_t)bb * a.l + t0) * n;
     for (int o = threadIdx.x; o < tcur * n; o += 256) t1s[o] = src[o];
     __syncthreads();
-    route_fold<256>(a, chunk, bb, 0, tcur, t1s, n, t1s + (size_t)a.tc_d * n, wa_s);
+    route_fold<256>(a, chunk, bb, tcur, t1s, n, t1s + (size_t)a.tc_d * n, wa_s);
 }
 
 // The fold of the one-pass routing on the matrix cores (n*m outputs per sample, l products each: 67 M
@@ -1299,6 +1400,7 @@ hipError_t launch_route(const RouteArgs &a_in, bool bf16, hipStream_t st)
     const bool has_e = a.w_e != nullptr, has_d = a.w_b != nullptr;
     hipError_t err = hipSuccess;
     const bool data_mfma = has_d && route_data_uses_mfma(a.b, a.l, a.d, a.n, bf16);
+    const bool split = a.tc_d < DATA_TOKENS;   // the data router's waves split the columns of x
     const int rt = a.b > 32 ? 4 : (a.b > 16 ? 2 : 1);
     const int groups_e = (a.b + rt * 16 - 1) / (rt * 16);
     int fold_ranges = 0;   // > 0: partial tiles of route_fold_mfma, few enough for route_select to add up
@@ -1356,11 +1458,12 @@ hipError_t launch_route(const RouteArgs &a_in, bool bf16, hipStream_t st)
     if (has_e && bf16 && data_mfma && (double)a.b * a.l * a.d * 2 <= 48e6) {
         const int n_data = a.nchunks_d * a.b;
         const dim3 grid(n_data + a.nchunks * groups_e);
-        const size_t shd = data_mfma_lds(a.n, a.d, 4);
+        const size_t shd = data_lds(a.n, a.d);
 #define UOE_FUSED(RT, CT)                                                                                         \
     do {                                                                                                          \
         const size_t she = route_expert_mfma_lds<RT, CT>();                                                       \
-        hipLaunchKernelGGL((route_expert_data_kernel<RT, CT>), grid, dim3(256), she > shd ? she : shd, st, a, n_data);   \
+        if (split) hipLaunchKernelGGL((route_expert_data_kernel<RT, CT, 4>), grid, dim3(256), she > shd ? she : shd, st, a, n_data);   \
+        else hipLaunchKernelGGL((route_expert_data_kernel<RT, CT, 1>), grid, dim3(256), she > shd ? she : shd, st, a, n_data);   \
     } while (0)
         if (a.n <= 16) {
             if (rt == 4) UOE_FUSED(4, 1);
@@ -1392,10 +1495,12 @@ hipError_t launch_route(const RouteArgs &a_in, bool bf16, hipStream_t st)
             if ((err = launch_partial_n<float>(a, true, has_d, st)) != hipSuccess) return err;
         }
         if (data_mfma) {
-            const size_t sh = data_mfma_lds(a.n, a.d, 4);
+            const size_t sh = data_lds(a.n, a.d);
             const dim3 grid(a.nchunks_d, a.b);
-            if (a.n <= 16) hipLaunchKernelGGL((route_data_mfma_kernel<4, 1>), grid, dim3(256), sh, st, a);
-            else hipLaunchKernelGGL((route_data_mfma_kernel<4, 2>), grid, dim3(256), sh, st, a);
+            if (a.n <= 16 && split) hipLaunchKernelGGL((route_data_mfma_kernel<1, 4>), grid, dim3(256), sh, st, a);
+            else if (a.n <= 16) hipLaunchKernelGGL((route_data_mfma_kernel<1, 1>), grid, dim3(256), sh, st, a);
+            else if (split) hipLaunchKernelGGL((route_data_mfma_kernel<2, 4>), grid, dim3(256), sh, st, a);
+            else hipLaunchKernelGGL((route_data_mfma_kernel<2, 1>), grid, dim3(256), sh, st, a);
             if ((err = hipGetLastError()) != hipSuccess) return err;
         } else if (has_d && (bf16 || !has_e)) {
             err = bf16 ? launch_partial_n<bf16_t>(a, false, true, st) : launch_partial_n<float>(a, false, true, st);
