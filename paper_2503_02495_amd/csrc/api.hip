@@ -87,8 +87,9 @@ size_t uome_ws(const uoe_block_desc *d) { return up((size_t)d->b * d->l * d->k *
 // backward pass of the UoME block: Z, dZ, H [b,l,k*d_e]; split-K tiles of the weight gradients; partial sums of the
 // gate gradient
 struct UomeBwdWs {
-    size_t z, dh, dz, h, h_op, dz_op, partial, gpart, rt, total;
-    int splits, gchunks;
+    size_t z, dh, dz, h, h_op, dz_op, partial, part_end, gpart, rt, total;
+    int gchunks;
+    WgradPlan wgrad;
 };
 static bool uome_bwd_mfma(const uoe_block_desc *blk);
 // Parts of the any-shape weight gradients: at most `parts`, fewer where the compute unit with the most workgroups has less to do then.
@@ -125,9 +126,13 @@ UomeBwdWs uome_bwd_ws(const uoe_block_desc *d)
         s = s < 1 ? 1 : (s > 8 ? 8 : s);
         if (s > most) s = most;
         s = wgrad_parts(d->dtype == UOE_F32, 2 * chunks, d->n, d->width, d->d, s / chunks > 1 ? s / chunks : 1);
-        w.splits = (int)s * chunks;
+        // pairs are cut into ranges of tokens until a part has two items
+        const long pairs = (long)(d->b < 128 ? d->b : 128) * d->k;
+        long items = (2 * d->n * s + pairs - 1) / pairs;
+        if (items > 1) items = (d->l + uome_any_range(d->l, (int)items) - 1) / uome_any_range(d->l, (int)items);   // (as many as there are)
+        w.wgrad = wgrad_plan(d->b, d->n, d->k, (int)s, (int)items, 128);
         w.partial = w.total;
-        const size_t partial = (size_t)2 * d->n * w.splits * d->d * d->width;
+        const size_t partial = (size_t)2 * chunks * w.wgrad.parts * d->d * d->width;
         w.total += up(partial * sizeof(float));
         // the gate gradient's partial sums lie where the partial tiles go later (n >= k and d * d_e >= 64: one sum per
         // (sample, slot) always fits)
@@ -144,10 +149,10 @@ UomeBwdWs uome_bwd_ws(const uoe_block_desc *d)
     w.h = off; off += act;
     // data-selection mode (c < m) works on at most as many rows (units * l_a <= b * k * l) in the same
     // buffers; its weight gradients are cut by (unit, pick) segments instead of token ranges
-    w.splits = d->c < d->m ? smha_backward_splits(d->b, d->n, d->k, d->c)
-                           : uome_backward_splits(d->b, d->l, d->d, d->n, d->k, d->width);
+    w.wgrad = d->c < d->m ? smha_backward_wgrad(d->b, d->n, d->k, d->c, 2, d->width, d->d) : uome_backward_wgrad(d->b, d->l, d->d, d->n, d->k, d->width);
     w.partial = off;
-    off += up(2 * (size_t)d->n * w.splits * d->d * d->width * sizeof(float));  // both weight gradients
+    off += up(2 * (size_t)w.wgrad.parts * d->d * d->width * sizeof(float));  // both weight gradients
+    w.part_end = off; off += up(32 * sizeof(int32_t));
     w.gchunks = uome_backward_gate_chunks(d->l, d->width);
     w.gpart = off; off += up((size_t)d->b * d->k * w.gchunks * sizeof(float));
     w.rt = off; off += up((size_t)((d->width + 31) / 32) * d->b * d->k * d->l * sizeof(float));
@@ -174,9 +179,9 @@ int check_uome_bwd(const uoe_block_desc *blk)
 // backward pass of the SMHA block: the forward's scratch, then the backward's own
 struct SmhaBwdWs {
     SmhaWs fwd;
-    size_t lse, rt, dd, do_raw, d_o, og, dqkv, partial, total;
+    size_t lse, rt, dd, do_raw, d_o, og, dqkv, partial, part_end, total;
     size_t g_q, g_k, g_v, g_og, g_inv;  // any-shape path (four bytes an element)
-    int splits;
+    WgradPlan wgrad;
 };
 static bool smha_bwd_mfma(const uoe_block_desc *blk)
 {
@@ -203,14 +208,14 @@ SmhaBwdWs smha_bwd_ws(const uoe_block_desc *d)
         w.dd = off; off += rows;
         // weight gradients: chunks of 128 samples x parts of an expert's (unit, pick) list, at most BWD_ANY_SEGMENTS
         // entries in each even if every sample selected the expert
-        const int chunks = (d->b + 127) / 128, nb = d->b < 128 ? d->b : 128;
-        const int need = (nb * d->c + BWD_ANY_SEGMENTS - 1) / BWD_ANY_SEGMENTS;
+        const int chunks = (d->b + 127) / 128;
         const long avg = ((long)d->b * d->k * d->c / chunks + d->n - 1) / d->n;
         long parts = avg / 8;
         parts = wgrad_parts(d->dtype == UOE_F32, 4 * chunks, d->n, d->width, d->d, parts < 1 ? 1 : (parts > 8 ? 8 : parts));
-        w.splits = (int)(parts > need ? parts : need) * chunks;
+        w.wgrad = wgrad_plan(d->b, d->n, d->k, (int)parts, d->c, BWD_ANY_SEGMENTS);
         w.partial = off;
-        off += up((size_t)w.splits * 4 * d->n * d->d * d->width * sizeof(float));
+        off += up((size_t)4 * chunks * w.wgrad.parts * d->d * d->width * sizeof(float));
+        w.part_end = off; off += up((size_t)chunks * 32 * sizeof(int32_t));
         w.total = off;
         return w;
     }
@@ -226,8 +231,9 @@ SmhaBwdWs smha_bwd_ws(const uoe_block_desc *d)
     w.og = off; off += one;
     w.dqkv = off; off += 3 * one;
     w.partial = off;
-    w.splits = smha_backward_splits(d->b, d->n, d->k, d->c);
-    off += up((size_t)d->n * w.splits * 4 * d->width * d->d * sizeof(float));
+    w.wgrad = smha_backward_wgrad(d->b, d->n, d->k, d->c, 4, d->width, d->d);
+    off += up((size_t)4 * w.wgrad.parts * d->width * d->d * sizeof(float));
+    w.part_end = off; off += up(32 * sizeof(int32_t));
     w.total = off;
     return w;
 }
@@ -604,7 +610,7 @@ int uoe_uome_backward(const uoe_block_desc *blk, const void *u, const void *a_in
     if (!uome_bwd_mfma(blk)) {
         a.z = at(ws, w.z); a.dh = at(ws, w.dh);
         a.h_op = at(ws, w.h_op); a.dz_op = at(ws, w.dz_op);
-        a.splits = w.splits; a.gchunks = w.gchunks;
+        a.wgrad = w.wgrad; a.gchunks = w.gchunks;
         a.partial = reinterpret_cast<float *>(at(ws, w.partial));
         a.gpart = reinterpret_cast<float *>(at(ws, w.gpart));
         return launch_uome_backward_any(a, blk->dtype == UOE_BF16, static_cast<hipStream_t>(hip_stream)) == hipSuccess
@@ -614,7 +620,7 @@ int uoe_uome_backward(const uoe_block_desc *blk, const void *u, const void *a_in
     a.gpart = reinterpret_cast<float *>(at(ws, w.gpart));
     a.partial = reinterpret_cast<float *>(at(ws, w.partial));
     a.gchunks = w.gchunks;
-    a.splits = w.splits;
+    a.wgrad = w.wgrad; a.part_end = reinterpret_cast<int32_t *>(at(ws, w.part_end));
     a.patch_idx = patch_idx; a.patch_gate = patch_gate; a.d_patch_gate = d_patch_gate;
     a.rt = reinterpret_cast<float *>(at(ws, w.rt)); a.m = blk->m; a.c = blk->c;
     return launch_uome_backward(a, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? UOE_OK : UOE_ERR_DEVICE;
@@ -661,7 +667,7 @@ static int smha_backward(const SmhaKept *kept, const uoe_block_desc *blk, const 
         a.do_raw = reinterpret_cast<float *>(at(ws, s.do_raw)); a.dqkv = at(ws, s.dqkv); a.og = at(ws, s.g_og);
         a.rt = reinterpret_cast<float *>(at(ws, s.rt)); a.dd = reinterpret_cast<float *>(at(ws, s.dd));
         a.inv_sum = reinterpret_cast<float *>(at(ws, s.g_inv));
-        a.splits = s.splits;
+        a.wgrad = s.wgrad; a.part_end = reinterpret_cast<int32_t *>(at(ws, s.part_end));
         a.partial = reinterpret_cast<float *>(at(ws, s.partial));
         return launch_smha_backward_any(a, blk->dtype == UOE_BF16, static_cast<hipStream_t>(hip_stream)) == hipSuccess
                    ? UOE_OK : UOE_ERR_DEVICE;
@@ -679,7 +685,7 @@ static int smha_backward(const SmhaKept *kept, const uoe_block_desc *blk, const 
     a.og = at(ws, s.og); a.dqkv = at(ws, s.dqkv);
     a.rt = reinterpret_cast<float *>(at(ws, s.rt)); a.dd = reinterpret_cast<float *>(at(ws, s.dd));
     a.partial = reinterpret_cast<float *>(at(ws, s.partial));
-    a.splits = s.splits;
+    a.wgrad = s.wgrad; a.part_end = reinterpret_cast<int32_t *>(at(ws, s.part_end));
     return launch_smha_backward(a, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? UOE_OK : UOE_ERR_DEVICE;
 }
 

@@ -216,53 +216,54 @@ template <typename T> struct UomeBwdDu : PlainEpilogue {
 };
 
 // Weight gradients: dA^O_i [d_e, d] = sum H_{b,s}^T d_out_b (set 0), (dA^I_i)^T [d_e, d] = sum dZ_{b,s}^T u_b (set 1)
-// over the (sample, slot) pairs of expert i, both operands token-major ([k][m] and [k][n]).  Parts of an expert's
-// sum: chunks of 128 samples (the segment table) x ranges, either of the chunk's list of pairs (each with all its tokens)
-// or, where an expert has few pairs, of the token axis; fp32 partial tiles.  A K segment costs its lookups and
-// addresses once, so long ones pay: 128 samples of 196 tokens in 8 ranges of pairs instead of 32 tokens 150 -> 103 us.
+// over the (sample, slot) pairs of expert i, both operands token-major ([k][m] and [k][n]), in parts of the expert's list of ranges of
+// tokens (WgradPlan; a whole pair is one range where there are many).  A K segment costs its lookups and
+// addresses once, so long ones pay: 128 samples of 196 tokens in 8 parts of pairs instead of 32 tokens 150 -> 103 us.
 template <typename T> struct UomeBwdWgrad : PlainEpilogue {
     typedef typename storage_elem<T>::type Elem;
     static constexpr int kSegParts = parts_of<T>::value;
     const T *left[2], *right[2];   // left [b, l, k, parts, d_e], right [b, l, d]
     const int32_t *expert_idx;
-    float *partial;                // [2*n*splits, d_e, d]
-    int b, l, d, n, kact, d_e, splits, ranges, range;   // splits = sample chunks * ranges; range: tokens per range, 0: ranges of pairs
+    float *partial;                // [2*chunks*parts, d_e, d]
+    int b, l, d, n, kact, d_e, range;   // range: tokens of an item, fewer in a pair's last one
+    WgradOrder parts;
     static constexpr bool kF32Out = true, kPrepare = true;
     __device__ int rows(int) const { return d_e; }
     __device__ int ncols() const { return d; }
-    __device__ int first_token(int g) const { return (g % splits) % ranges * range; }
-    __device__ int kseg(int g) const { return range == 0 ? l : max(0, min(range, l - first_token(g))); }
+    __device__ int kseg(int) const { return range; }
+    __device__ int seg_len(uint32_t ctx) const { return min(range, l - (int)(ctx >> 12) * range); }
     __device__ int kdim(int) const { return 0; }
     __device__ long b_stride() const { return d; }
     __device__ long a_stride(int) const { return (long)kact * kSegParts * d_e; }
-    __device__ int prepare(int g, uint32_t *segtab, int tid, int) const
+    // context of a segment: slot in bits 0-4, sample of the chunk in bits 5-11, range above
+    __device__ int decode(int g) const { return parts.decode(g); }
+    __device__ int prepare(int &g, uint32_t *segtab, void *scratch, int tid, int) const
     {
-        __shared__ SampleList list;
-        const int expert = (g / splits) % n, part = g % splits, base = part / ranges * 128, nb = min(128, b - base);
-        list.fill(expert_idx + (size_t)base * kact, nb, kact, n, expert, tid);
-        const int total = list.count(), per = range == 0 ? (total + ranges - 1) / ranges : total;
-        const int first = range == 0 ? part % ranges * per : 0, cnt = max(0, min(total - first, per));
+        PartList &list = *static_cast<PartList *>(scratch);
+        const int base = parts.chunk(g) * 128, nb = min(128, b - base);
+        int expert, first, last;
+        if (!list.fill(expert_idx + (size_t)base * kact, nb, kact, n, parts, g, tid, expert, first, last)) return -1;
         if (tid < nb && list.slot_of[tid] >= 0) {
-            const int pos = list.before(tid) - first;
-            if (pos >= 0 && pos < cnt) segtab[pos] = ((uint32_t)tid << 8) | (uint32_t)list.slot_of[tid];
+            const int at = list.before(expert, tid) * parts.w.items - first;
+            for (int r = 0; r < parts.w.items; ++r)
+                if (at + r >= 0 && at + r < last - first) segtab[at + r] = ((uint32_t)r << 12) | ((uint32_t)tid << 5) | (uint32_t)list.slot_of[tid];
         }
         __syncthreads();
-        return cnt * kSegParts * kseg(g);
+        return (last - first) * kSegParts * range;
     }
     __device__ uint32_t seg_ctx(int, int) const { return 0; }
-    __device__ size_t sample(int g, uint32_t ctx) const { return (size_t)((g % splits) / ranges * 128) + (ctx >> 8); }
+    __device__ size_t token(int g, uint32_t ctx) const
+    {
+        return (size_t)(parts.chunk(g) * 128 + (int)(ctx >> 5 & 0x7Fu)) * l + (size_t)(ctx >> 12) * range;
+    }
     __device__ const T *a_ptr_ctx(int g, int m, int seg, uint32_t ctx) const
     {
-        const size_t row = sample(g, ctx) * l + first_token(g);
-        return left[g >= n * splits] + ((row * kact + (ctx & 0xFFu)) * kSegParts + seg % kSegParts) * d_e + m;
+        return (parts.set(g) ? left[1] : left[0]) + ((token(g, ctx) * kact + (ctx & 0x1Fu)) * kSegParts + seg % kSegParts) * d_e + m;
     }
-    __device__ const T *b_ptr_ctx(int g, int, int nn, uint32_t ctx) const
-    {
-        return right[g >= n * splits] + (sample(g, ctx) * l + first_token(g)) * d + nn;
-    }
+    __device__ const T *b_ptr_ctx(int g, int, int nn, uint32_t ctx) const { return (parts.set(g) ? right[1] : right[0]) + token(g, ctx) * d + nn; }
     __device__ void put4(int g, int r, int nn, float4 v) const
     {
-        *reinterpret_cast<float4 *>(partial + ((size_t)g * d_e + r) * d + nn) = v;
+        *reinterpret_cast<float4 *>(partial + (parts.tile(g) * d_e + r) * d + nn) = v;
     }
     __device__ void put4_f32(int g, int r, int nn, float4 v) const { put4(g, r, nn, v); }
 };
@@ -345,7 +346,7 @@ template <typename T> hipError_t uome_backward_any(const UomeBwdArgs &a, hipStre
     // one launch for Z, dH and what becomes of them, where tiles of 64 rows and more are the choice anyway and the gate
     // gradient's sums fit the room they have (a wave's rows: 64 of the large tiles, 32 of the small ones)
     const long row_blocks = large ? (a.l + 63) / 64 : (a.l + 31) / 32;
-    const long sums = row_blocks * (a.d_e / 8), room = (long)2 * a.n * a.splits * a.d * a.d_e / ((long)a.b * a.k);
+    const long sums = row_blocks * (a.d_e / 8), room = (long)2 * a.wgrad.chunks * a.wgrad.parts * a.d * a.d_e / ((long)a.b * a.k);
     if (a.l > 32 && sums <= room) {
         hp.expert_gate = (a.flags & F_GATE_EXPERT) ? a.expert_gate : nullptr;
         hp.h = h; hp.dz = dz; hp.gpart = a.gpart; hp.gchunks = ga.gchunks = (int)sums;
@@ -380,13 +381,12 @@ template <typename T> hipError_t uome_backward_any(const UomeBwdArgs &a, hipStre
     wp.left[0] = h; wp.right[0] = d_out;
     wp.left[1] = dz; wp.right[1] = u;
     wp.expert_idx = a.expert_idx; wp.partial = a.partial;
-    wp.b = a.b; wp.l = a.l; wp.d = a.d; wp.n = a.n; wp.kact = a.k; wp.d_e = a.d_e; wp.splits = a.splits;
-    wp.ranges = a.splits / ((a.b + 127) / 128);
-    // ranges of pairs once an expert has four per range on the average
-    wp.range = (long)a.b * a.k >= 4L * a.n * wp.ranges ? 0 : ((a.l + wp.ranges - 1) / wp.ranges + 31) / 32 * 32;
-    if ((err = launch_gemm_tail<GEMM_A_KM>(wp, 2 * a.n * a.splits, a.d_e, a.d, st)) != hipSuccess) return err;
+    wp.b = a.b; wp.l = a.l; wp.d = a.d; wp.n = a.n; wp.kact = a.k; wp.d_e = a.d_e; wp.parts = WgradOrder(2, WgradOrder::BY_SAMPLE, a.wgrad, nullptr);
+    wp.range = uome_any_range(a.l, a.wgrad.items);
+    if ((err = launch_gemm_tail<GEMM_A_KM>(wp, wp.parts.groups(), a.d_e, a.d, st)) != hipSuccess) return err;
     WgradReduceArgs ra{};
-    ra.partial = a.partial; ra.n = a.n; ra.M = a.d_e; ra.N = a.d; ra.splits = a.splits;
+    ra.partial = a.partial; ra.n = a.n; ra.M = a.d_e; ra.N = a.d;
+    ra.w = a.wgrad; ra.expert_idx = a.expert_idx; ra.b = a.b; ra.kact = a.k;
     ra.dst[0] = a.d_a_out; ra.transposed[0] = 0;
     ra.dst[1] = a.d_a_in; ra.transposed[1] = 1;
     return launch_wgrad_reduce<T>(ra, 2, st);
@@ -838,15 +838,15 @@ template <typename T, int DH> void launch_attention_bwd_f32_dh(const SmhaBwdArgs
 
 // Weight gradients of the SMHA block: sets 0-2 (dW^{q,k,v}_i)^T [d_h, d] = sum d{Q,K,V}^T x[T], set 3 dW^O_i [d_h, d] =
 // sum (w o)^T G[T], both operands token-major, right rows gathered patch by patch.  K segments = (unit, pick) of
-// l_p tokens x parts, in order; parts of an expert's list: chunks of 128 samples x consecutive ranges of the
-// chunk's list (at most kMaxSegments entries each).
+// l_p tokens x parts, in order, cut as WgradPlan says.
 template <typename T> struct SmhaBwdWgrad : PlainEpilogue {
     typedef typename storage_elem<T>::type Elem;
     static constexpr int kSegParts = parts_of<T>::value;
     const T *dqkv, *og, *x, *d_out;   // dqkv [units, l_a, parts, 3*d_h], og [units, l_a, parts, d_h]
     const int32_t *expert_idx, *patch_idx;
-    float *partial;                   // [4*n*splits, d_h, d]
-    int b, l, d, n, kact, m, c, l_p, l_a, d_h, splits, ranges;
+    float *partial;                   // [4*chunks*parts, d_h, d]
+    int b, l, d, n, kact, m, c, l_p, l_a, d_h;
+    WgradOrder parts;
     static constexpr bool kF32Out = true, kPrepare = true;
     static constexpr int kMaxSegments = BWD_ANY_SEGMENTS;
     __device__ int rows(int) const { return d_h; }
@@ -854,43 +854,42 @@ template <typename T> struct SmhaBwdWgrad : PlainEpilogue {
     __device__ int kseg(int) const { return l_p; }
     __device__ int kdim(int) const { return 0; }
     __device__ long b_stride() const { return d; }
-    __device__ int set(int g) const { return g / (n * splits); }
-    __device__ int width(int g) const { return set(g) < 3 ? 3 * d_h : d_h; }
+    __device__ int width(int g) const { return parts.set(g) < 3 ? 3 * d_h : d_h; }
     __device__ long a_stride(int g) const { return (long)kSegParts * width(g); }
     // context of a segment: sample of the chunk in bits 0-6, slot in bits 7-11, pick in bits 12-21, patch in bits 22-31
-    __device__ int prepare(int g, uint32_t *segtab, int tid, int nthreads) const
+    __device__ int decode(int g) const { return parts.decode(g); }
+    __device__ int prepare(int &g, uint32_t *segtab, void *scratch, int tid, int nthreads) const
     {
-        __shared__ SampleList list;
-        const int expert = (g / splits) % n, part = g % splits, base = part / ranges * 128, nb = min(128, b - base);
-        list.fill(expert_idx + (size_t)base * kact, nb, kact, n, expert, tid);
-        const int total = list.count() * c, per = (total + ranges - 1) / ranges;
-        const int first = part % ranges * per, last = min(total, first + per);
+        PartList &list = *static_cast<PartList *>(scratch);
+        const int base = parts.chunk(g) * 128, nb = min(128, b - base);
+        int expert, first, last;
+        if (!list.fill(expert_idx + (size_t)base * kact, nb, kact, n, parts, g, tid, expert, first, last)) return -1;
         for (int idx = tid; idx < nb * c; idx += nthreads) {
             const int bb = idx / c, t = idx - bb * c;
             if (list.slot_of[bb] < 0) continue;
-            const int pos = list.before(bb) * c + t;
-            if (pos < first || pos >= last || pos - first >= kMaxSegments) continue;
+            const int pos = list.before(expert, bb) * c + t;
+            if (pos < first || pos >= last) continue;
             const int p = clampi(patch_idx[((size_t)(base + bb) * n + expert) * c + t], m);
             segtab[pos - first] = (uint32_t)bb | ((uint32_t)list.slot_of[bb] << 7) | ((uint32_t)t << 12) | ((uint32_t)p << 22);
         }
         __syncthreads();
-        return max(0, min(last - first, kMaxSegments)) * kSegParts * l_p;
+        return (last - first) * kSegParts * l_p;
     }
     __device__ uint32_t seg_ctx(int, int) const { return 0; }
-    __device__ size_t sample(int g, uint32_t ctx) const { return (size_t)(g % splits / ranges * 128) + (ctx & 0x7Fu); }
+    __device__ size_t sample(int g, uint32_t ctx) const { return (size_t)(parts.chunk(g) * 128) + (ctx & 0x7Fu); }
     __device__ const T *a_ptr_ctx(int g, int mm, int seg, uint32_t ctx) const
     {
         const size_t row = (sample(g, ctx) * kact + ((ctx >> 7) & 0x1Fu)) * l_a + (size_t)((ctx >> 12) & 0x3FFu) * l_p;
-        const int st = set(g);
+        const int st = parts.set(g);
         return (st < 3 ? dqkv + st * d_h : og) + (row * kSegParts + seg % kSegParts) * width(g) + mm;
     }
     __device__ const T *b_ptr_ctx(int g, int, int nn, uint32_t ctx) const
     {
-        return (set(g) < 3 ? x : d_out) + (sample(g, ctx) * l + (size_t)(ctx >> 22) * l_p) * d + nn;
+        return (parts.set(g) < 3 ? x : d_out) + (sample(g, ctx) * l + (size_t)(ctx >> 22) * l_p) * d + nn;
     }
     __device__ void put4(int g, int r, int nn, float4 v) const
     {
-        *reinterpret_cast<float4 *>(partial + ((size_t)g * d_h + r) * d + nn) = v;
+        *reinterpret_cast<float4 *>(partial + (parts.tile(g) * d_h + r) * d + nn) = v;
     }
     __device__ void put4_f32(int g, int r, int nn, float4 v) const { put4(g, r, nn, v); }
 };
@@ -942,10 +941,11 @@ template <typename T> hipError_t smha_backward_any(const SmhaBwdArgs &a, hipStre
     wp.x = static_cast<const T *>(f.x); wp.d_out = static_cast<const T *>(a.d_out);
     wp.expert_idx = f.expert_idx; wp.patch_idx = f.patch_idx; wp.partial = a.partial;
     wp.b = f.b; wp.l = f.l; wp.d = f.d; wp.n = f.n; wp.kact = f.k; wp.m = f.m; wp.c = f.c;
-    wp.l_p = l_p; wp.l_a = l_a; wp.d_h = dh; wp.splits = a.splits; wp.ranges = a.splits / ((f.b + 127) / 128);
-    if ((err = launch_gemm_tail<GEMM_A_KM>(wp, 4 * f.n * a.splits, dh, f.d, st)) != hipSuccess) return err;
+    wp.l_p = l_p; wp.l_a = l_a; wp.d_h = dh; wp.parts = WgradOrder(4, WgradOrder::DEALT, a.wgrad, a.part_end);
+    if ((err = launch_gemm_tail<GEMM_A_KM>(wp, wp.parts.groups(), dh, f.d, st)) != hipSuccess) return err;
     WgradReduceArgs ra{};
-    ra.partial = a.partial; ra.n = f.n; ra.M = dh; ra.N = f.d; ra.splits = a.splits;
+    ra.partial = a.partial; ra.n = f.n; ra.M = dh; ra.N = f.d;
+    ra.w = a.wgrad; ra.part_end = a.part_end;
     ra.dst[0] = a.d_wq; ra.dst[1] = a.d_wk; ra.dst[2] = a.d_wv; ra.dst[3] = a.d_wo;
     ra.transposed[0] = ra.transposed[1] = ra.transposed[2] = 1; ra.transposed[3] = 0;
     return launch_wgrad_reduce_gates<T>(ra, 4, a, st);

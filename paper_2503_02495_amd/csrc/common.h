@@ -83,6 +83,41 @@ inline TailTile tail_tile(bool f32, bool km, bool gaps_nk, long groups, int rows
     return {64, 64, false};
 }
 
+// How the sums of the weight gradients over an expert's tokens are cut into parts, one fp32 partial tile (or grid of them) each.  The
+// samples go in chunks of 128 (a workgroup's tables); within a chunk an expert has `items` items for each (sample, slot) pair that
+// selected it (picked patches, or ranges of the token axis), in sample order, and its list is cut evenly into parts of at most `per`.
+// Experts are not selected equally often: with the same number of parts for each the launch took as long as the most popular one
+// (4 x 8192 tokens, 8 of 16 experts of 1024 x 256: 352 us, 255 to 268 with equal parts; 8 x 512, fp32, 4 of 8 of 512 x 256: 102 and 74).
+// Finding them takes about 1 us, so experts with 32 pairs and more on the average keep one number (`each`): 128 samples, 3 of 6
+// experts, are within 10 % of each other, and 96 us became 112 and 99 in the two orders there are for unequal parts.
+// `per` is the least for which no more than `parts` parts come of it, found by every workgroup from the selection (PartScan).
+struct WgradPlan {
+    int chunks, items, parts;
+    int lo, hi;        // bounds of `per`: all parts full; feasible for any selection
+    int each;          // not 0: an expert has so many parts, whatever its list (experts with many pairs: their lists hardly differ)
+};
+// `splits`: parts of an expert with the average number of pairs; `cap`: entries of a workgroup's segment table
+inline WgradPlan wgrad_plan(int b, int n, int k, int splits, int items, int cap)
+{
+    const int nb = b < 128 ? b : 128, most = nb * items;   // most: an expert every sample selected
+    const int need = (most + cap - 1) / cap;
+    splits = splits > need ? splits : need;                // (with `cap` items a part an expert has at most `splits` of them)
+    const long total = (long)nb * k * items, parts = (long)n * splits;
+    const long lo = (total + parts - 1) / parts;
+    // sum over experts of ceil(items of the expert / per) <= total / per + n
+    long hi = splits > 1 ? (total + parts - n - 1) / (parts - n) : most;
+    hi = hi < most ? hi : most;
+    hi = hi < cap ? hi : cap;
+    WgradPlan w;
+    w.chunks = (b + 127) / 128;
+    w.items = items;
+    w.parts = (int)parts;
+    w.each = (long)nb * k >= 32L * n ? splits : 0;
+    w.lo = (int)(lo < hi ? lo : hi);
+    w.hi = (int)hi;
+    return w;
+}
+
 __device__ __forceinline__ float to_f32(float x) { return x; }
 __device__ __forceinline__ float to_f32(bf16_t x) { return __uint_as_float(((uint32_t)x.v) << 16); }
 
@@ -248,8 +283,10 @@ struct UomeBwdArgs {
     void *z, *dz, *h;                         // [b, l, k*d_e] each
     void *dh;                                 // any-shape path: dH, fp32
     float *gpart;                             // [b, k, gchunks] partial sums of d_gate
-    float *partial;                           // [2*n*splits, d_e, d] split-K tiles of the two weight gradients
-    int gchunks, splits;
+    float *partial;                           // [2*chunks*parts, d_e, d] partial tiles of the two weight gradients
+    int32_t *part_end;                        // [chunks, 32] first part id behind an expert's (NULL on the UoME's any-shape path)
+    int gchunks;
+    WgradPlan wgrad;
     void *h_op, *dz_op;                       // any-shape path: H and dZ as left operands (may be z and dh themselves)
     // data-selection mode (patch_idx != NULL): units = (sample, slot) with l_a = c*l/m gathered rows;
     // z, dz, h are [units, l_a, d_e]
@@ -276,8 +313,9 @@ struct SmhaBwdArgs {
     float *rt, *dd;                           // [units, l_a] each: dL/dw_t and the softmax row term
     float *inv_sum;                           // any-shape path: [units, l_a] 1 / softmax row sum; f.lse holds the row maximum there
     int rt_parts;                             // rt is that many arrays to be added (0: one), set by the launcher
-    float *partial;                           // [4*n*splits, d_h, d] split tiles of the four weight gradients
-    int splits;
+    float *partial;                           // [4*chunks*parts, d_h, d] partial tiles of the four weight gradients
+    int32_t *part_end;                        // [chunks, 32] first part id behind an expert's (NULL on the UoME's any-shape path)
+    WgradPlan wgrad;
     void *og;                                 // w o [units, l_a, d_h]; any-shape path: [units, l_a, parts, d_h], do_raw, q, k, v are
                                               // fp32 there and dqkv is [units, l_a, parts, 3*d_h]
 };
@@ -340,9 +378,11 @@ hipError_t launch_uome_backward_any(const UomeBwdArgs &a, bool bf16, hipStream_t
 hipError_t launch_smha_backward_any(const SmhaBwdArgs &a, bool bf16, hipStream_t st);
 constexpr int BWD_ANY_SEGMENTS = 1024;        // (unit, pick) entries one part of an expert's weight gradient holds
 hipError_t launch_route_backward(const RouteBwdArgs &a, bool bf16, hipStream_t st);
-int smha_backward_splits(int b, int n, int k, int c);
+WgradPlan smha_backward_wgrad(int b, int n, int k, int c, int sets, int rows, int cols);
 int uome_backward_gate_chunks(int l, int d_e);
-int uome_backward_splits(int b, int l, int d, int n, int k, int d_e);
+WgradPlan uome_backward_wgrad(int b, int l, int d, int n, int k, int d_e);
+// tokens of an item of the any-shape UoME weight gradients, pairs cut into `items`
+inline int uome_any_range(int l, int items) { return items == 1 ? l : ((l + items - 1) / items + 31) / 32 * 32; }
 
 // measurement probes (probe.hip)
 constexpr unsigned PROBE_READ_BLOCKS = 256 * 16, PROBE_MFMA_BLOCKS = 256 * 2;

@@ -9,8 +9,10 @@
 //   a_ptr_ctx(g, m, seg, ctx)            pointer to A[m][seg*kseg], from that context; the segment's elements are contiguous
 //   b_ptr_ctx(g, seg, nn, ctx)           pointer to B[seg*kseg][nn..nn+8)  (nn % 8 == 0)
 //   b_stride()                           elements between consecutive K rows of B inside a segment
-//   kPrepare / prepare(g, segtab, tid, nthreads)  the workgroup builds its segment list itself and
-//                                        returns K (out-projection: which experts picked this patch)
+//   kPrepare / prepare(g, segtab, scratch, tid, nthreads)  the workgroup builds its segment list itself (scratch: the stage buffers' LDS,
+//                                        behind a last barrier theirs again) and returns K (out-projection: which experts picked this patch); -1: there is no such tile
+//   decode(g)                            (optional) what the problem calls the launch's group g
+//   seg_len(ctx)                         (optional, GEMM_A_KM and GEMM_TAIL) a segment's own length, at most kseg(g)
 // Its fp32 form writes four columns of a row at a time:
 //   epi_f32(v, scale), put4(g, m, nn, v4)   per-element math; the store (residual included)
 // and its bf16 form 16-byte pieces of output rows:
@@ -232,7 +234,7 @@ template <typename T> struct OutProjProblem {
         __shared__ int16_t tab[32 * 32];
         return tab;
     }
-    __device__ int prepare(int g, uint32_t *segtab, int tid, int nthreads) const
+    __device__ int prepare(int g, uint32_t *segtab, void *, int tid, int nthreads) const
     {
         __shared__ int slot_any[32], slot_e[32];
         int16_t *pick = pick_table();
@@ -296,9 +298,9 @@ template <typename T> struct OutProjProblem {
 template <typename T, int PARTS> struct SmhaDxProblem : OutProjProblem<T> {
     const T *w[3];   // wq, wk, wv
     static constexpr int kSegParts = 3 * PARTS;
-    __device__ int prepare(int g, uint32_t *segtab, int tid, int nthreads) const
+    __device__ int prepare(int g, uint32_t *segtab, void *scratch, int tid, int nthreads) const
     {
-        return OutProjProblem<T>::prepare(g, segtab, tid, nthreads) * kSegParts;   // this->parts is 1: one table entry per expert
+        return OutProjProblem<T>::prepare(g, segtab, scratch, tid, nthreads) * kSegParts;   // this->parts is 1: one table entry per expert
     }
     __device__ const T *a_ptr_ctx(int g, int r, int seg, uint32_t ctx) const
     {
@@ -462,83 +464,250 @@ template <typename T> struct UomeDownProblem {
     template <bool ONCE> __device__ void put8_as(int g, int r, int nn, uint4 piece) const { store16<ONCE>(out + ((size_t)g * l + r) * d + nn, piece); }
 };
 
-// Which of up to 128 samples selected an expert, and in which slot: the segment lists of the weight gradients.  Two ballots
-// give every sample's place in the list (counting through LDS sample by sample took longer than a short contraction).
-// Called by the whole workgroup of at least 128 threads; ends on a barrier.
-struct SampleList {
-    uint64_t mask[2];
-    int16_t slot_of[128];
-    __device__ void fill(const int32_t *expert_idx, int nb, int kact, int n, int expert, int tid)
-    {
-        int slot = -1;
-        if (tid < nb) {
-#pragma unroll 4
-            for (int s = 0; s < kact; ++s)
-                if (clampi(expert_idx[tid * kact + s], n) == expert) slot = slot < 0 ? s : slot;
-            slot_of[tid] = (int16_t)slot;
-        }
-        const uint64_t m = __ballot(slot >= 0);
-        if (tid < 128 && (tid & 63) == 0) mask[tid >> 6] = m;
-        __syncthreads();
+// Which of up to 128 samples selected each expert: two ballots an expert give its count and every sample's place in its list
+// (counting through LDS sample by sample took longer than a short contraction).  Called by the whole workgroup of at least
+// 128 threads; ends on a barrier.
+constexpr int KEPT_IDX = 8;   // of a sample's indices, what stays in registers
+__device__ __forceinline__ void expert_masks(uint64_t (*mask)[2], int (&idx)[KEPT_IDX], const int32_t *expert_idx, int nb, int kact, int n, int tid)
+{
+    uint32_t mine = 0;
+#pragma unroll
+    for (int s = 0; s < KEPT_IDX; ++s) {
+        idx[s] = clampi(expert_idx[min(tid, nb - 1) * kact + min(s, kact - 1)], n);   // (unconditional: all in flight together)
+        mine |= 1u << idx[s];
     }
-    __device__ int count() const { return __popcll(mask[0]) + __popcll(mask[1]); }
-    __device__ int before(int q) const   // listed samples below sample q
+    for (int s = KEPT_IDX; s < kact; ++s) mine |= 1u << clampi(expert_idx[min(tid, nb - 1) * kact + s], n);
+    if (tid >= nb) mine = 0;
+    if (tid < 128) {
+        uint64_t keep = 0;
+        for (int e = 0; e < n; ++e) {
+            const uint64_t m = __ballot(mine >> e & 1u);
+            if ((tid & 63) == e) keep = m;
+        }
+        if ((tid & 63) < n) mask[tid & 63][tid >> 6] = keep;
+    }
+    __syncthreads();
+}
+
+// Where an expert's parts lie among a chunk's part ids (lane e of a wave holds expert e's; n <= 32), `each` being 0.  Each lane tries one value
+// of `per`, and the least one that fits the budget is taken.
+struct PartScan {
+    int count, parts, behind;   // selecting samples; parts; first id behind them
+    __device__ PartScan(const uint64_t (*mask)[2], const WgradPlan &w, int n, int lane)
     {
-        return q < 64 ? __popcll(mask[0] & ((1ull << q) - 1)) : __popcll(mask[0]) + __popcll(mask[1] & ((1ull << (q - 64)) - 1));
+        const int e = lane & 31;
+        count = e < n ? __popcll(mask[e][0]) + __popcll(mask[e][1]) : 0;
+        const int items = count * w.items, step = (w.hi - w.lo + 62) / 63;
+        const int per = min(w.lo + lane * step, w.hi);
+        const float inv = __builtin_amdgcn_rcpf((float)per);
+        auto cuts = [](int of, int by, float by_inv) {   // ceil(of / by) for of < 2^23
+            const int x = of + by - 1;
+            int q = (int)((float)x * by_inv);
+            const int r = x - q * by;
+            q += r >= by ? 1 : (r < 0 ? -1 : 0);
+            return q;
+        };
+        int sum = 0;
+        for (int i = 0; i < n; ++i) sum += cuts(__builtin_amdgcn_readlane(items, i), per, inv);
+        const uint64_t fits = __ballot(sum <= w.parts);
+        const int at = fits ? __ffsll((unsigned long long)fits) - 1 : 63;
+        const int best = __builtin_amdgcn_readlane(per, at);
+        parts = cuts(items, best, __builtin_amdgcn_rcpf((float)best));
+        behind = parts;
+#pragma unroll
+        for (int off = 1; off < 32; off <<= 1) {
+            const int t = __shfl_up(behind, off, 32);
+            if (e >= off) behind += t;
+        }
     }
 };
 
-// ---------------------------------------------------------------------------------------------
+// A launch's groups: (set, chunk, place) for gradient tensors of one shape.  Each XCD works on a contiguous eighth of the groups.
+//   IN_ORDER   expert by expert
+//   BY_SAMPLE  places follow where in the sample axis a part begins: the parts that run on an XCD at one time are those of different experts
+//              over the same tokens, whose right operands are the same rows (4 x 8192 tokens, 16 experts of 1024 x 256: 272 -> 254 us)
+//   DEALT      dealt round-robin over the eighths, so that each gets parts of all experts: short parts of patches, where finding the order
+//              by samples takes longer than it saves (8 x 512 tokens, 8 experts, with d_x: 15.0 us in order, 17.8 by sample, 13.3 dealt)
+struct WgradOrder {
+    enum { IN_ORDER, BY_SAMPLE, DEALT };
+    int sets, by;
+    WgradPlan w;
+    int32_t *part_end;   // [chunks, 32] first part id behind an expert's, for the reduction, or NULL: it finds them itself
+    WgradOrder() = default;
+    WgradOrder(int sets_, int by_, const WgradPlan &w_, int32_t *part_end_) : sets(sets_), by(w_.each ? IN_ORDER : by_), w(w_), part_end(part_end_) {}
+    int groups() const { const int g = sets * w.chunks * w.parts; return by == DEALT ? (g + 7) / 8 * 8 : g; }
+    // set in bits 0-1, place in bits 2-14 (at most 32 experts x 128 parts), chunk above
+    __device__ int decode(int g) const
+    {
+        if (by == DEALT) {
+            const int eighth = (sets * w.chunks * w.parts + 7) / 8, o = g % eighth * 8 + g / eighth, r = o / sets, c = r % w.chunks;
+            return (o - r * sets) | (r / w.chunks) << 2 | c << 15;
+        }
+        const int s = g / (w.chunks * w.parts), r = g - s * (w.chunks * w.parts), c = r / w.parts;
+        return s | (r - c * w.parts) << 2 | c << 15;
+    }
+    __device__ int set(int g) const { return g & 3; }
+    __device__ int place(int g) const { return g >> 2 & 0x1FFF; }   // (prepare() puts the part's id there)
+    __device__ int chunk(int g) const { return g >> 15; }
+    __device__ size_t tile(int g) const { return (size_t)(set(g) * w.chunks + chunk(g)) * w.parts + place(g); }   // its partial tile
+};
+
+// The workgroup's part of an expert's list: its partial tile, items [first, last) of the expert, the expert's samples and slots
+struct PartList {
+    uint64_t mask[32][2];
+    uint32_t key[256];
+    int32_t end[32];
+    int16_t slot_of[128];
+    int32_t found;
+    // first item of a part (at most 2^17 items and 2^12 parts; 64-bit divisions took 2 us here)
+    static __device__ int begin_of(int items, int part, int parts) { return (int)((uint32_t)items * (uint32_t)part / (uint32_t)parts); }
+    // false: no such part; else g's place becomes the part's id.  Ends on a barrier.
+    __device__ bool fill(const int32_t *expert_idx, int nb, int kact, int n, const WgradOrder &o, int &g, int tid, int &expert, int &first, int &last)
+    {
+        const WgradPlan &w = o.w;
+        int idx[KEPT_IDX];
+        if (w.each) {   // the expert is known: one ballot, and the slots with it
+            expert = o.place(g) / w.each;
+            const int part = o.place(g) - expert * w.each, at = min(tid, nb - 1) * kact;
+            int slot = -1;
+            for (int s = kact - 1; s >= KEPT_IDX; --s) slot = clampi(expert_idx[at + s], n) == expert ? s : slot;
+#pragma unroll
+            for (int s = KEPT_IDX - 1; s >= 0; --s) {
+                const int t = min(s, kact - 1);
+                slot = clampi(expert_idx[at + t], n) == expert ? t : slot;
+            }
+            if (tid >= nb) slot = -1;
+            const uint64_t m = __ballot(slot >= 0);
+            if (tid < 128 && (tid & 63) == 0) mask[expert][tid >> 6] = m;
+            if (tid < nb) slot_of[tid] = (int16_t)slot;
+            __syncthreads();
+            const int items = (__popcll(mask[expert][0]) + __popcll(mask[expert][1])) * w.items, per = (items + w.each - 1) / w.each;
+            first = __builtin_amdgcn_readfirstlane(min(items, part * per));
+            last = __builtin_amdgcn_readfirstlane(min(items, (part + 1) * per));
+            return true;
+        }
+        expert_masks(mask, idx, expert_idx, nb, kact, n, tid);
+        const PartScan scan(mask, w, n, tid & 63);
+        const int total = __builtin_amdgcn_readlane(scan.behind, 31), q = o.place(g);
+        if (o.part_end && q == 0 && o.set(g) == 0 && tid < 32) o.part_end[o.chunk(g) * 32 + tid] = scan.behind;
+        int mine = q;
+        if (o.by != WgradOrder::BY_SAMPLE || total > 256) {
+            if (q >= total) return false;
+        } else {   // the places that hold a part are spread evenly
+            const int rank = begin_of(total, q, w.parts);
+            if (begin_of(total, q + 1, w.parts) == rank) return false;
+            if (tid < 32) end[tid] = scan.behind;
+            __syncthreads();
+            if (tid < 256) {
+                uint32_t k = ~0u;
+                if (tid < total) {
+                    int e = 0;
+#pragma unroll
+                    for (int s = 16; s; s >>= 1) e += end[e + s - 1] <= tid ? s : 0;
+                    const uint64_t m0 = mask[e][0], m1 = mask[e][1];
+                    const int c0 = __popcll(m0), items = (c0 + __popcll(m1)) * w.items, begin = e ? end[e - 1] : 0;
+                    const int at = begin_of(items, tid - begin, end[e] - begin);
+                    int nth = at / w.items, sample = 0;   // of its first item: the nth listed sample
+                    const int range = at - nth * w.items;
+                    uint64_t m = m0;
+                    if (nth >= c0) { m = m1; nth -= c0; sample = 64; }
+#pragma unroll
+                    for (int s = 32; s; s >>= 1) {
+                        const int low = __popcll(m & ((1ull << s) - 1));
+                        if (nth >= low) { nth -= low; m >>= s; sample += s; }
+                    }
+                    k = (uint32_t)(sample * w.items + range) << 8 | (uint32_t)tid;
+                }
+                key[tid] = k;
+            }
+            __syncthreads();
+            if (tid < total) {
+                const uint32_t k = key[tid];
+                int below = 0;
+                for (int j = 0; j < total; j += 4) {   // (what lies behind the keys is the largest value)
+                    const uint4 v = *reinterpret_cast<const uint4 *>(&key[j]);
+                    below += (v.x < k) + (v.y < k) + (v.z < k) + (v.w < k);
+                }
+                if (below == rank) found = tid;
+            }
+            __syncthreads();
+            mine = found;
+        }
+        mine = __builtin_amdgcn_readfirstlane(mine);
+        expert = __builtin_amdgcn_readfirstlane(__ffs((uint32_t)__ballot(mine < scan.behind)) - 1);
+        const int parts = __builtin_amdgcn_readlane(scan.parts, expert), items = __builtin_amdgcn_readlane(scan.count, expert) * w.items;
+        const int part = mine - (__builtin_amdgcn_readlane(scan.behind, expert) - parts);
+        first = __builtin_amdgcn_readfirstlane(begin_of(items, part, parts));
+        last = __builtin_amdgcn_readfirstlane(begin_of(items, part + 1, parts));
+        g = (g & 3) | mine << 2 | o.chunk(g) << 15;
+        if (tid < nb) {
+            int slot = -1;
+#pragma unroll
+            for (int s = KEPT_IDX - 1; s >= 0; --s) slot = idx[s] == expert ? s : slot;
+            if (slot < 0 && (mask[expert][tid >> 6] >> (tid & 63) & 1ull))
+                for (int s = kact - 1; s >= KEPT_IDX; --s) slot = clampi(expert_idx[tid * kact + s], n) == expert ? s : slot;
+            slot_of[tid] = (int16_t)slot;
+        }
+        __syncthreads();
+        return true;
+    }
+    __device__ int before(int expert, int q) const   // listed samples below sample q
+    {
+        const uint64_t m0 = mask[expert][0];
+        return q < 64 ? __popcll(m0 & ((1ull << q) - 1)) : __popcll(m0) + __popcll(mask[expert][1] & ((1ull << (q - 64)) - 1));
+    }
+};
+
 // Weight gradients of the backward passes, as split contractions over the tokens with fp32 partial
-// tiles.  A launch covers up to four gradient tensors ("sets") of the same shape [n][M][N] at once:
-// group = (set * n + expert) * splits + part, partial tile [group][M][N]; a reduction kernel adds
-// the parts in order.  Both factors are read as the other kernels wrote them, token-major (engine flag GEMM_A_KM):
+// tiles.  A launch covers up to four gradient tensors ("sets") of the same shape [n][M][N] at once, in parts that
+// hold as much of an expert's list each (WgradPlan, WgradOrder); a reduction kernel adds an expert's
+// parts in order.  Both factors are read as the other kernels wrote them, token-major (engine flag GEMM_A_KM):
 // a transposed copy of the left one cost its writer 2-byte scattered LDS or memory stores and a third of its traffic.
 //
 // Expert-selection UoME: for expert i,
 //   dW[M, N] = sum over the (sample b, slot s) pairs with expert_idx[b,s] == i of  L_{b,s}^T R_b
-// contracted over the l tokens of the sample.  K segments = the pairs, found by the workgroup itself
-// (prepare), in sample order, which fixes the summation order; the token axis is cut into `splits`
-// equal ranges, part j contracts range j of every pair.
+// contracted over the l tokens of the sample.  K segments = ranges of a pair's tokens, l / items each, found by the workgroup
+// itself (prepare), in sample order, which fixes the summation order.
 //   set 0: dA^O_i   [d_e, d]:  left = H  [b][l][k*d_e] (columns s*d_e + e of the pair), right = d_out [b][l][d]
 //   set 1: dA^I_i^T [d_e, d]:  left = dZ [b][l][k*d_e] (the same columns),              right = u     [b][l][d]
 template <typename T> struct WgradProblem {
     const T *left[2], *right[2];
     const int32_t *expert_idx;
-    float *partial;        // [sets*n*splits, M, N]
-    int b, l, n, kact, splits;
+    float *partial;        // [sets*parts, M, N]
+    int b, l, n, kact, range;   // range: tokens of an item
+    WgradOrder parts;      // one chunk (b <= 128)
     int M, N;              // rows and columns of one expert's gradient (d_e and d)
 
     static constexpr bool kF32Out = true;
     __device__ int rows(int) const { return M; }
     __device__ int ncols() const { return N; }
-    __device__ int kseg(int) const { return l / splits; }
+    __device__ int kseg(int) const { return range; }
     __device__ long a_stride(int) const { return (long)kact * M; }
     __device__ long b_stride() const { return N; }
     __device__ int kdim(int) const { return 0; }  // prepare() supplies K
     static constexpr bool kPrepare = true;
-    // the samples that selected the expert, in sample order (b <= 128 = the engine's segment table)
-    __device__ int prepare(int g, uint32_t *segtab, int tid, int) const
+    // context of a segment: slot in bits 0-4, sample in bits 5-11, range above
+    __device__ int decode(int g) const { return parts.decode(g); }
+    __device__ int prepare(int &g, uint32_t *segtab, void *scratch, int tid, int) const
     {
-        __shared__ SampleList list;
-        list.fill(expert_idx, b, kact, n, (g % (n * splits)) / splits, tid);
-        if (tid < b && list.slot_of[tid] >= 0) segtab[list.before(tid)] = ((uint32_t)tid << 8) | (uint32_t)list.slot_of[tid];
+        PartList &list = *static_cast<PartList *>(scratch);
+        int expert, first, last;
+        if (!list.fill(expert_idx, b, kact, n, parts, g, tid, expert, first, last)) return -1;
+        if (tid < b && list.slot_of[tid] >= 0) {
+            const int at = list.before(expert, tid) * parts.w.items - first;
+            for (int r = 0; r < parts.w.items; ++r)
+                if (at + r >= 0 && at + r < last - first) segtab[at + r] = ((uint32_t)r << 12) | ((uint32_t)tid << 5) | (uint32_t)list.slot_of[tid];
+        }
         __syncthreads();
-        return list.count() * (l / splits);
+        return (last - first) * range;
     }
     __device__ uint32_t seg_ctx(int, int) const { return 0; }
+    __device__ size_t token(uint32_t ctx) const { return (size_t)(ctx >> 5 & 0x7Fu) * l + (size_t)(ctx >> 12) * range; }
     __device__ const T *a_ptr_ctx(int g, int r, int, uint32_t ctx) const
     {
-        const int bb = (int)(ctx >> 8), s = (int)(ctx & 0xFFu);
-        const T *base = g < n * splits ? left[0] : left[1];
-        return base + (((size_t)bb * l + (size_t)(g % splits) * (l / splits)) * kact + s) * M + r;
+        return (parts.set(g) == 0 ? left[0] : left[1]) + (token(ctx) * kact + (ctx & 0x1Fu)) * M + r;
     }
-    __device__ const T *b_ptr_ctx(int g, int, int nn, uint32_t ctx) const
-    {
-        const int bb = (int)(ctx >> 8);
-        const T *base = g < n * splits ? right[0] : right[1];
-        return base + ((size_t)bb * l + (size_t)(g % splits) * (l / splits)) * N + nn;
-    }
+    __device__ const T *b_ptr_ctx(int g, int, int nn, uint32_t ctx) const { return (parts.set(g) == 0 ? right[0] : right[1]) + token(ctx) * N + nn; }
     static constexpr bool kRowScale = false;
     static constexpr bool kColScale = false;
     __device__ float col_scale(int, int) const { return 1.0f; }
@@ -548,7 +717,7 @@ template <typename T> struct WgradProblem {
     __device__ void put8(int, int, int, uint4) const {}
     __device__ void put4_f32(int g, int r, int nn, float4 v) const
     {
-        *reinterpret_cast<float4 *>(partial + ((size_t)g * M + r) * N + nn) = v;
+        *reinterpret_cast<float4 *>(partial + (parts.tile(g) * M + r) * N + nn) = v;
     }
 };
 
@@ -558,8 +727,7 @@ template <typename T> struct WgradProblem {
 // i.e. the left factor is a per-unit tensor [unit][l_a][columns] (the set's M columns start at col0)
 // and the right factor is a [b, l, d] tensor (x, u or the
 // upstream gradient) whose rows are gathered patch by patch (Eq. 18), never copied.  K segments =
-// (unit, pick) of l_p tokens, in (sample, pick) order; the list is cut into `splits` consecutive
-// parts.
+// (unit, pick) of l_p tokens, in (sample, pick) order.
 //   SMHA, M = d_h:  sets 0-2: dW^{q,k,v}_i^T, left = [dq|dk|dv] [unit][l_a][3d_h] columns set*d_h.., right = x
 //                   set 3:    dW^O_i,         left = gated o    [unit][l_a][d_h],                    right = d_out
 //   UoME, M = d_e:  set 0: dA^O_i, left = H [unit][l_a][d_e], right = d_out;  set 1: dA^I_i^T, left = dZ, right = u
@@ -567,49 +735,49 @@ template <typename T> struct SmhaWgradProblem {
     const T *left[4], *right[4];
     int row_len[4], col0[4];    // elements of a row of left[set]; first column of the set's M
     const int32_t *expert_idx, *patch_idx;
-    float *partial;             // [sets*n*splits, M, d]
-    int b, l, d, n, kact, m, c, l_p, l_a, splits;
+    float *partial;             // [sets*parts, M, d]
+    int b, l, d, n, kact, m, c, l_p, l_a;
+    WgradOrder parts;           // one chunk (b <= 128)
     int M;
 
     static constexpr bool kF32Out = true;
     __device__ int rows(int) const { return M; }
     __device__ int ncols() const { return d; }
     __device__ int kseg(int) const { return l_p; }
-    __device__ long a_stride(int g) const { return row_len[g / (n * splits)]; }
+    __device__ long a_stride(int g) const { return row_len[parts.set(g)]; }
     __device__ long b_stride() const { return d; }
     __device__ int kdim(int) const { return 0; }
     static constexpr bool kPrepare = true;
     // context of a segment: sample in bits 0-6, slot in bits 7-11, pick in bits 12-21, patch in bits 22-31
-    __device__ int prepare(int g, uint32_t *segtab, int tid, int nthreads) const
+    __device__ int decode(int g) const { return parts.decode(g); }
+    __device__ int prepare(int &g, uint32_t *segtab, void *scratch, int tid, int nthreads) const
     {
-        __shared__ SampleList list;
-        const int ge = g % (n * splits), expert = ge / splits, part = ge - expert * splits;
-        list.fill(expert_idx, b, kact, n, expert, tid);
-        const int total = list.count() * c, per = (total + splits - 1) / splits;
-        const int first = part * per, last = min(total, first + per);  // this part's segments
-        // thread (sample bb, pick t): its position in the full list is (units before bb) * c + t
+        PartList &list = *static_cast<PartList *>(scratch);
+        int expert, first, last;
+        if (!list.fill(expert_idx, b, kact, n, parts, g, tid, expert, first, last)) return -1;
+        // thread (sample bb, pick t): its position in the expert's list is (listed samples before bb) * c + t
         for (int idx = tid; idx < b * c; idx += nthreads) {
             const int bb = idx / c, t = idx - bb * c;
             if (list.slot_of[bb] < 0) continue;
-            const int pos = list.before(bb) * c + t;
-            if (pos < first || pos >= last || pos - first >= 128) continue;
+            const int pos = list.before(expert, bb) * c + t;
+            if (pos < first || pos >= last) continue;
             const int p = clampi(patch_idx[((size_t)bb * n + expert) * c + t], m);
             segtab[pos - first] = (uint32_t)bb | ((uint32_t)list.slot_of[bb] << 7) | ((uint32_t)t << 12) | ((uint32_t)p << 22);
         }
         __syncthreads();
-        return max(0, min(last - first, 128)) * l_p;
+        return (last - first) * l_p;
     }
     __device__ uint32_t seg_ctx(int, int) const { return 0; }
     __device__ const T *a_ptr_ctx(int g, int r, int, uint32_t ctx) const
     {
         const int bb = (int)(ctx & 0x7Fu), s = (int)((ctx >> 7) & 0x1Fu), t = (int)((ctx >> 12) & 0x3FFu);
-        const int set = g / (n * splits);
+        const int set = parts.set(g);
         return left[set] + (((size_t)bb * kact + s) * l_a + (size_t)t * l_p) * row_len[set] + col0[set] + r;
     }
     __device__ const T *b_ptr_ctx(int g, int, int nn, uint32_t ctx) const
     {
         const int bb = (int)(ctx & 0x7Fu), p = (int)(ctx >> 22);
-        return right[g / (n * splits)] + ((size_t)bb * l + (size_t)p * l_p) * d + nn;
+        return right[parts.set(g)] + ((size_t)bb * l + (size_t)p * l_p) * d + nn;
     }
     static constexpr bool kRowScale = false;
     static constexpr bool kColScale = false;
@@ -620,7 +788,7 @@ template <typename T> struct SmhaWgradProblem {
     __device__ void put8(int, int, int, uint4) const {}
     __device__ void put4_f32(int g, int r, int nn, float4 v) const
     {
-        *reinterpret_cast<float4 *>(partial + ((size_t)g * M + r) * d + nn) = v;
+        *reinterpret_cast<float4 *>(partial + (parts.tile(g) * M + r) * d + nn) = v;
     }
 };
 

@@ -466,15 +466,16 @@ template <bool PAD> static hipError_t launch_attention_bwd(const AttnBwdArgs &a,
     return launch_attention_bwd_dh<128, PAD>(a, units, st);
 }
 
-int smha_backward_splits(int b, int n, int k, int c)
+WgradPlan smha_backward_wgrad(int b, int n, int k, int c, int sets, int rows, int cols)
 {
-    // parts of an expert's (unit, pick) list: about 8 segments each, at most 8 parts, and never more
-    // than 128 segments in one part even if every sample selected the expert
+    // parts of an average expert's (unit, pick) list: about 8 segments each, and at most 8 parts; not more than two where 256 tiles
+    // of 128 x 128 come of it, a part's fp32 tiles being written and read again (4 x 8192 tokens, 16 experts of 64 x 1024: 4 parts
+    // 66 us and 16 for the reduction, 2 parts 54 and 12; 8 x 512, 8 of 256 x 512: 27 and 23)
     const int avg = (int)(((long)b * k * c + n - 1) / n);
-    int s = avg / 8;
+    const long tiles = (long)sets * n * ((rows + 127) / 128) * ((cols + 127) / 128), most = tiles >= 128 ? 2 : (256 + tiles - 1) / tiles;
+    long s = avg / 8;
     s = s < 1 ? 1 : (s > 8 ? 8 : s);
-    const int need = (b * c + 127) / 128;
-    return s > need ? s : need;
+    return wgrad_plan(b, n, k, (int)(s < most ? s : most), c, 128);
 }
 
 hipError_t launch_smha_backward(const SmhaBwdArgs &a_in, hipStream_t st)
@@ -540,9 +541,9 @@ hipError_t launch_smha_backward(const SmhaBwdArgs &a_in, hipStream_t st)
     wp.row_len[3] = dh; wp.col0[3] = 0;
     wp.expert_idx = f.expert_idx; wp.patch_idx = f.patch_idx; wp.partial = a.partial;
     wp.b = f.b; wp.l = f.l; wp.d = f.d; wp.n = f.n; wp.kact = f.k; wp.m = f.m; wp.c = f.c;
-    wp.l_p = l_p; wp.l_a = l_a; wp.splits = a.splits; wp.M = dh;
+    wp.l_p = l_p; wp.l_a = l_a; wp.parts = WgradOrder(4, WgradOrder::DEALT, a.wgrad, a.part_end); wp.M = dh;
     // one launch with d_x while the weight gradients do not fill the chip's slots (two per compute unit)
-    const int groups = 4 * f.n * a.splits;
+    const int groups = wp.parts.groups();
     typedef GemmTile<SmhaDxProblem<T, 1>, 32, 128, 32, 1, 4, 4, GEMM_B_NK> Dx32;
     typedef GemmTile<SmhaDxProblem<T, 1>, 64, 128, 32, 2, 2, 4, GEMM_B_NK> Dx64;
     typedef GemmTile<SmhaWgradProblem<T>, 64, 128, 32, 2, 2, 4, GEMM_A_KM> Wg;
@@ -552,11 +553,12 @@ hipError_t launch_smha_backward(const SmhaBwdArgs &a_in, hipStream_t st)
     else {
         if (l_p <= 32) err = launch_gemm_dma<SmhaDxProblem<T, 1>, 32, 128, 32, 1, 4, 4, 2, GEMM_B_NK>(xp, f.b * f.m, l_p, f.d, st);
         else err = launch_gemm_dma<SmhaDxProblem<T, 1>, 64, 128, 32, 2, 2, 4, 2, GEMM_B_NK>(xp, f.b * f.m, l_p, f.d, st);
-        if (err == hipSuccess) err = launch_gemm_dma_auto<GEMM_A_KM>(wp, groups, dh, f.d, (long)units * l_a / (f.n * a.splits), l_p, st);
+        if (err == hipSuccess) err = launch_gemm_dma_auto<GEMM_A_KM>(wp, groups, dh, f.d, (long)a.wgrad.lo * l_p, l_p, st);
     }
     if (err != hipSuccess) return err;
     WgradReduceArgs ra{};
-    ra.partial = a.partial; ra.n = f.n; ra.M = dh; ra.N = f.d; ra.splits = a.splits;
+    ra.partial = a.partial; ra.n = f.n; ra.M = dh; ra.N = f.d;
+    ra.w = a.wgrad; ra.part_end = a.part_end;
     ra.dst[0] = a.d_wq; ra.dst[1] = a.d_wk;
     ra.dst[2] = a.d_wv; ra.dst[3] = a.d_wo;
     ra.transposed[0] = ra.transposed[1] = ra.transposed[2] = 1; ra.transposed[3] = 0;

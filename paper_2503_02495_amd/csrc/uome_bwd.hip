@@ -28,14 +28,15 @@
 namespace uoe {
 
 int uome_backward_gate_chunks(int l, int d_e) { return (l / 32) * (d_e / 32); }
-int uome_backward_splits(int b, int l, int d, int n, int k, int d_e)
+WgradPlan uome_backward_wgrad(int b, int l, int d, int n, int k, int d_e)
 {
-    // cut the token axis until the launch has 512 large tiles, while a workgroup keeps on average
-    // >= 1024 of K and the ranges stay multiples of 64
-    int s = 1;
-    const long k_avg = (long)b * k * l / n, tiles = (long)n * ((d_e + 255) / 256) * ((d + 127) / 128);
-    while (s < 8 && tiles * s < 512 && l % (2 * s * 64) == 0 && k_avg / (2 * s) >= 1024) s *= 2;
-    return s;
+    // parts until the launch has 512 large tiles, while one keeps on average >= 1024 of K; pairs are cut into ranges of tokens, a
+    // multiple of 64, until a part has two items (for lists that do not divide evenly)
+    int s = 1, ranges = 1;
+    const long pairs = (long)b * k, k_avg = pairs * l / n, tiles = (long)n * ((d_e + 255) / 256) * ((d + 127) / 128);
+    while (s < 8 && tiles * s < 512 && k_avg / (2 * s) >= 1024) s *= 2;
+    while (pairs * ranges < 2L * n * s && l % (2 * ranges * 64) == 0) ranges *= 2;
+    return wgrad_plan(b, n, k, s, ranges, 128);
 }
 
 // Elementwise middle for 8 elements: dZ, H and the sum of dH * SiLU(Z), an fp32 output.
@@ -270,26 +271,26 @@ hipError_t launch_uome_backward(const UomeBwdArgs &a, hipStream_t st)
     up.u = static_cast<const T *>(a.d_out); up.expert_idx = a.expert_idx; up.out = static_cast<T *>(a.d_u);
     up.l = a.l; up.d = a.d; up.n = a.n; up.kact = a.k; up.d_e = a.d_e; up.flags = a.flags;
 
-    // weight gradients, both in one launch: [d_e, d] tiles per expert, token axis cut into a.splits
-    // ranges; (dA^I_i)^T = sum dZ_{b,s}^T u_b is stored back as [d, d_e] by the reduction
+    // weight gradients, both in one launch: [d_e, d] tiles per part of an expert's tokens; (dA^I_i)^T = sum dZ_{b,s}^T u_b is stored back as [d, d_e] by the reduction
     WgradProblem<T> wp;
     wp.left[0] = static_cast<const T *>(a.h); wp.right[0] = static_cast<const T *>(a.d_out);  // dA^O_i
     wp.left[1] = static_cast<const T *>(a.dz); wp.right[1] = static_cast<const T *>(a.u);     // (dA^I_i)^T
     wp.expert_idx = a.expert_idx; wp.partial = a.partial;
-    wp.b = a.b; wp.l = a.l; wp.n = a.n; wp.kact = a.k; wp.splits = a.splits;
-    wp.M = a.d_e; wp.N = a.d;
+    wp.b = a.b; wp.l = a.l; wp.n = a.n; wp.kact = a.k; wp.parts = WgradOrder(2, WgradOrder::BY_SAMPLE, a.wgrad, a.part_end);
+    wp.M = a.d_e; wp.N = a.d; wp.range = a.l / a.wgrad.items;
     // one launch for d_u and the weight gradients while neither fills the chip's slots (two per compute unit) by itself
-    const int groups = 2 * a.n * a.splits;
+    const int groups = wp.parts.groups(), kseg = wp.range;
     const long du64 = (long)a.b * ((a.l + 63) / 64) * ((a.d + 127) / 128), wg128 = (long)groups * ((a.d_e + 127) / 128) * ((a.d + 127) / 128);
-    if (a.d_e % 64 == 0 && (a.l / a.splits) % 64 == 0 && a.d_e > 64 && du64 <= 512 && wg128 <= 512) {
+    if (a.d_e % 64 == 0 && kseg % 64 == 0 && a.d_e > 64 && du64 <= 512 && wg128 <= 512) {
         typedef GemmTile<UomeDownProblem<T>, 64, 128, 64, 2, 2, 3, GEMM_B_NK> Du;
         typedef GemmTile<WgradProblem<T>, 128, 128, 64, 2, 2, 2, GEMM_A_KM> Wg;
         err = launch_gemm_dma_pair<Wg, Du, 2>(wp, groups, a.d_e, a.d, up, a.b, a.l, a.d, st);
     } else if ((err = launch_gemm_dma_auto<GEMM_B_NK>(up, a.b, a.l, a.d, width, a.d_e, st)) == hipSuccess)
-        err = launch_gemm_dma_auto<GEMM_A_KM>(wp, groups, a.d_e, a.d, (long)a.b * a.k * a.l / (a.n * a.splits), a.l / a.splits, st);
+        err = launch_gemm_dma_auto<GEMM_A_KM>(wp, groups, a.d_e, a.d, (long)a.wgrad.lo * kseg, kseg, st);
     if (err != hipSuccess) return err;
     WgradReduceArgs ra{};
-    ra.partial = a.partial; ra.n = a.n; ra.M = a.d_e; ra.N = a.d; ra.splits = a.splits;
+    ra.partial = a.partial; ra.n = a.n; ra.M = a.d_e; ra.N = a.d;
+    ra.w = a.wgrad; ra.part_end = a.part_end;
     ra.dst[0] = a.d_a_out; ra.transposed[0] = 0;
     ra.dst[1] = a.d_a_in; ra.transposed[1] = 1;
     const int nx = (a.d + RED_T - 1) / RED_T, ny = (a.d_e + RED_T - 1) / RED_T, tiles = nx * ny * 2 * a.n;
@@ -401,9 +402,9 @@ hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st)
     for (int q = 0; q < 4; ++q) { wp.row_len[q] = a.d_e; wp.col0[q] = 0; }
     wp.expert_idx = a.expert_idx; wp.patch_idx = a.patch_idx; wp.partial = a.partial;
     wp.b = a.b; wp.l = a.l; wp.d = a.d; wp.n = a.n; wp.kact = a.k; wp.m = a.m; wp.c = a.c;
-    wp.l_p = l_p; wp.l_a = l_a; wp.splits = a.splits; wp.M = a.d_e;
+    wp.l_p = l_p; wp.l_a = l_a; wp.parts = WgradOrder(2, WgradOrder::DEALT, a.wgrad, a.part_end); wp.M = a.d_e;
     // one launch with d_u while the weight gradients do not fill the chip's slots (two per compute unit)
-    const int groups = 2 * a.n * a.splits;
+    const int groups = wp.parts.groups();
     typedef GemmTile<OutProjProblem<T>, 32, 128, 32, 1, 4, 4, GEMM_B_NK> Du32;
     typedef GemmTile<OutProjProblem<T>, 64, 128, 32, 2, 2, 4, GEMM_B_NK> Du64;
     typedef GemmTile<SmhaWgradProblem<T>, 128, 128, 32, 2, 2, 4, GEMM_A_KM> Wg;
@@ -413,11 +414,12 @@ hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st)
     else {
         if (l_p <= 32) err = launch_gemm_dma<OutProjProblem<T>, 32, 128, 32, 1, 4, 4, 2, GEMM_B_NK>(xp, a.b * a.m, l_p, a.d, st);
         else err = launch_gemm_dma<OutProjProblem<T>, 64, 128, 32, 2, 2, 4, 2, GEMM_B_NK>(xp, a.b * a.m, l_p, a.d, st);
-        if (err == hipSuccess) err = launch_gemm_dma_auto<GEMM_A_KM>(wp, groups, a.d_e, a.d, (long)units * l_a / (a.n * a.splits), l_p, st);
+        if (err == hipSuccess) err = launch_gemm_dma_auto<GEMM_A_KM>(wp, groups, a.d_e, a.d, (long)a.wgrad.lo * l_p, l_p, st);
     }
     if (err != hipSuccess) return err;
     WgradReduceArgs ra{};
-    ra.partial = a.partial; ra.n = a.n; ra.M = a.d_e; ra.N = a.d; ra.splits = a.splits;
+    ra.partial = a.partial; ra.n = a.n; ra.M = a.d_e; ra.N = a.d;
+    ra.w = a.wgrad; ra.part_end = a.part_end;
     ra.dst[0] = a.d_a_out; ra.transposed[0] = 0;
     ra.dst[1] = a.d_a_in; ra.transposed[1] = 1;
     return launch_wgrad_reduce_gates<T>(ra, 2, ga, st);

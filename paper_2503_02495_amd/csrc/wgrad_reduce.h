@@ -2,10 +2,11 @@
 #pragma once
 #include "common.h"
 #include "gemm_mfma.h"
+#include "problems.h"
 
 namespace uoe {
 
-// partial [sets*n*splits][M][N] fp32 -> storage dtype, the parts added in order and rounded once.
+// partial [sets*chunks*parts][M][N] fp32 -> storage dtype, an expert's parts added in order and rounded once.
 // Set s goes to dst[s], stored as [n][M][N] or transposed as [n][N][M].  64x64 tiles, 16-byte loads with four rows of
 // a part in flight per thread, 8-byte stores (bf16; straight, or transposed through LDS): the launch is a plain stream
 // of the partial tiles (134 MB on the largest shape: 47.7 us with 32x32 tiles and 4-byte loads).
@@ -13,7 +14,11 @@ struct WgradReduceArgs {
     const float *partial;
     void *dst[4];   // storage type T of the launch
     int transposed[4];
-    int n, M, N, splits;
+    int n, M, N;
+    const int32_t *part_end;   // [chunks, 32] first part id behind an expert's
+    const int32_t *expert_idx;   // [b, kact] (FIND)
+    int b, kact;
+    WgradPlan w;
 };
 
 constexpr int RED_T = 64;
@@ -23,24 +28,45 @@ template <> __device__ __forceinline__ void store4_as<bf16_t>(bf16_t *p, float4 
 {
     *reinterpret_cast<uint2 *>(p) = make_uint2(pack2_bf16(v.x, v.y), pack2_bf16(v.z, v.w));
 }
-template <typename T> __device__ __forceinline__ void wgrad_reduce_tile(const WgradReduceArgs &a, int bx, int by, int bz)
+// FIND: where an expert's parts lie is found from the selection, not read from part_end (1.7 us)
+template <typename T, bool FIND = false> __device__ __forceinline__ void wgrad_reduce_tile(const WgradReduceArgs &a, int bx, int by, int bz)
 {
     __shared__ float tile[RED_T][RED_T + 1];
     const int set = bz / a.n, e = bz - set * a.n, r0 = by * RED_T, c0 = bx * RED_T;
     const int tx = (threadIdx.x & 15) * 4, ty = threadIdx.x >> 4;
     const int col = c0 + tx;                 // M and N are multiples of 8
     const size_t part = (size_t)a.M * a.N;
-    const float *src = a.partial + (size_t)bz * a.splits * part + min(col, a.N - 4);
     float4 acc[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) acc[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 1
+    for (int chunk = 0; chunk < a.w.chunks; ++chunk) {
+        int first, parts;
+        if (a.w.each) {
+            first = e * a.w.each;
+            parts = a.w.each;
+        } else if constexpr (!FIND) {
+            const int32_t *end = a.part_end + chunk * 32 + e;
+            first = e ? end[-1] : 0;
+            parts = end[0] - first;
+        } else {
+            __shared__ uint64_t mask[32][2];
+            if (chunk) __syncthreads();
+            int idx[KEPT_IDX];
+            expert_masks(mask, idx, a.expert_idx + (size_t)chunk * 128 * a.kact, min(128, a.b - chunk * 128), a.kact, a.n, threadIdx.x);
+            const PartScan scan(mask, a.w, a.n, threadIdx.x & 63);
+            parts = __builtin_amdgcn_readlane(scan.parts, e);
+            first = __builtin_amdgcn_readlane(scan.behind, e) - parts;
+        }
+        const float *src = a.partial + ((size_t)(set * a.w.chunks + chunk) * a.w.parts + first) * part + min(col, a.N - 4);
 #pragma unroll 2
-    for (int j = 0; j < a.splits; ++j) {
-        float4 v[4];
+        for (int j = 0; j < parts; ++j) {
+            float4 v[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = *reinterpret_cast<const float4 *>(src + (size_t)j * part + (size_t)min(r0 + ty + 16 * q, a.M - 1) * a.N);
+            for (int q = 0; q < 4; ++q) v[q] = *reinterpret_cast<const float4 *>(src + (size_t)j * part + (size_t)min(r0 + ty + 16 * q, a.M - 1) * a.N);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) { acc[q].x += v[q].x; acc[q].y += v[q].y; acc[q].z += v[q].z; acc[q].w += v[q].w; }
+            for (int q = 0; q < 4; ++q) { acc[q].x += v[q].x; acc[q].y += v[q].y; acc[q].z += v[q].z; acc[q].w += v[q].w; }
+        }
     }
     T *dst = static_cast<T *>(a.dst[set]) + (size_t)e * part;
     if (!a.transposed[set]) {
@@ -142,14 +168,17 @@ template <typename T> static inline hipError_t launch_wgrad_reduce_gates(const W
     return hipGetLastError();
 }
 
-template <typename T> __global__ __launch_bounds__(256) void wgrad_reduce_kernel(WgradReduceArgs a)
+template <typename T, bool FIND> __global__ __launch_bounds__(256, 6) void wgrad_reduce_kernel(WgradReduceArgs a)
 {
-    wgrad_reduce_tile<T>(a, blockIdx.x, blockIdx.y, blockIdx.z);
+    wgrad_reduce_tile<T, FIND>(a, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
+// (without part_end)
 template <typename T = bf16_t> static inline hipError_t launch_wgrad_reduce(const WgradReduceArgs &a, int sets, hipStream_t st)
 {
-    hipLaunchKernelGGL((wgrad_reduce_kernel<T>), dim3((a.N + RED_T - 1) / RED_T, (a.M + RED_T - 1) / RED_T, sets * a.n), dim3(256), 0, st, a);
+    const dim3 grid((a.N + RED_T - 1) / RED_T, (a.M + RED_T - 1) / RED_T, sets * a.n);
+    if (a.w.each) hipLaunchKernelGGL((wgrad_reduce_kernel<T, false>), grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((wgrad_reduce_kernel<T, true>), grid, dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
