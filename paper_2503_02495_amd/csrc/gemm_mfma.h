@@ -95,11 +95,39 @@ template <typename P> struct takes_pair<P, std::void_t<decltype(P::kPairOut)>> :
 template <typename P, typename = void> struct writes_itself : std::false_type {};
 template <typename P> struct writes_itself<P, std::void_t<decltype(P::kWriteOut)>> : std::true_type {};
 
+// problems whose epilogue reads a tensor of the output's shape: has_early(), early8<ONCE>(g, row, column).  EarlyPieces holds a wave
+// tile's pieces of it where the engine fetches them ahead: the first eight under the last K-step, the others while the tile is staged.
+template <typename P, typename = void> struct has_early_pieces : std::false_type {};
+template <typename P> struct has_early_pieces<P, std::void_t<decltype(&P::has_early)>> : std::true_type {};
+template <int TM, int TN> struct EarlyPieces {
+    static constexpr int N = TM * TN * 2, BATCH = largest_divisor_upto(N, 8);
+    uint4 piece[N];
+    template <bool ONCE, typename P>
+    __device__ __forceinline__ void fetch_as(const P &p, int from, int to, int g, int grow0, int gcol0, int M, int N_, int lane)
+    {
+#pragma unroll
+        for (int t = 0; t < N; ++t) {
+            if (t < from || t >= to) continue;
+            const int c = lane + t * 64, col = gcol0 + c % (TN * 4) * 8;
+            piece[t] = p.template early8<ONCE>(g, min(grow0 + c / (TN * 4), M - 1), col < N_ ? col : 0);   // (unconditional: all in flight together)
+        }
+    }
+    template <typename P> __device__ __forceinline__ void fetch(const P &p, int from, int to, int g, int grow0, int gcol0, int M, int N_, int lane)
+    {
+        if (!p.has_early()) return;
+        if (p.once) fetch_as<true>(p, from, to, g, grow0, gcol0, M, N_, lane);
+        else fetch_as<false>(p, from, to, g, grow0, gcol0, M, N_, lane);
+    }
+};
+struct NoEarlyPieces {};
+
 // second half of the epilogue: the staged wave tile back out of LDS in 16-byte pieces, the residual
 // added, the pieces stored (ONCE: through the problem's non-temporal accessors)
-template <typename P, int TM, int TN, int SPITCH, bool ONCE>
-__device__ __forceinline__ void wave_write_out(const P &p, uint16_t (*stage)[SPITCH], int g, int grow0, int gcol0, int M, int N, int lane)
+template <typename P, int TM, int TN, int SPITCH, bool ONCE, typename EARLY>
+__device__ __forceinline__ void wave_write_out(const P &p, uint16_t (*stage)[SPITCH], int g, int grow0, int gcol0, int M, int N, int lane,
+                                               const EARLY &early)
 {
+    constexpr bool FETCHED = !std::is_same<EARLY, NoEarlyPieces>::value;
     constexpr int WM = TM * 32, WN = TN * 32;
     constexpr int WC = WN / 8;           // 16-byte pieces per staged row
     constexpr int NPIECE = (WM * WC) / 64;
@@ -108,7 +136,10 @@ __device__ __forceinline__ void wave_write_out(const P &p, uint16_t (*stage)[SPI
 #pragma unroll
     for (int t0 = 0; t0 < NPIECE; t0 += BATCH) {
         uint4 r[BATCH];
-        if (res) {
+        if constexpr (FETCHED) {
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) r[u] = early.piece[t0 + u];
+        } else if (res) {
 #pragma unroll
             for (int u = 0; u < BATCH; ++u) {
                 const int c = lane + (t0 + u) * 64;
@@ -156,10 +187,10 @@ __device__ __forceinline__ void stage_plane(uint16_t (*stage)[SPITCH], int lane,
     __builtin_amdgcn_wave_barrier();
 }
 
-template <typename P, int TM, int TN, int SPITCH>
+template <typename P, int TM, int TN, int SPITCH, typename EARLY = NoEarlyPieces>
 __device__ __forceinline__ void wave_epilogue(const P &p, f32x16_t (&acc)[TM][TN], uint16_t (*stage)[SPITCH], const float *coltab,
                                               const float (&rs)[TM], int g, int grow0, int gcol0, int wcol0, int M, int N,
-                                              int lane)
+                                              int lane, const EARLY &early = EARLY())
 {
     const int lr = lane & 31, lh = lane >> 5;
     if constexpr (writes_f32<P>::value) {
@@ -215,12 +246,13 @@ __device__ __forceinline__ void wave_epilogue(const P &p, f32x16_t (&acc)[TM][TN
     // the non-temporal hint; the choice is made here, once per wave, so that each version keeps its
     // batch of residual loads in flight (a test per access would put a branch between them).
     if constexpr (writes_itself<P>::value) {
-        p.template write_out<TM, TN, SPITCH>(stage, coltab + (wcol0 >> 3), rs, g, grow0, gcol0, M, N, lane);
+        if constexpr (has_early_pieces<P>::value) p.template write_out<TM, TN, SPITCH>(stage, coltab + (wcol0 >> 3), rs, g, grow0, gcol0, M, N, lane, early);
+        else p.template write_out<TM, TN, SPITCH>(stage, coltab + (wcol0 >> 3), rs, g, grow0, gcol0, M, N, lane);
     } else if constexpr (streams_once<P>::value) {
-        if (p.once) wave_write_out<P, TM, TN, SPITCH, true>(p, stage, g, grow0, gcol0, M, N, lane);
-        else wave_write_out<P, TM, TN, SPITCH, false>(p, stage, g, grow0, gcol0, M, N, lane);
+        if (p.once) wave_write_out<P, TM, TN, SPITCH, true>(p, stage, g, grow0, gcol0, M, N, lane, early);
+        else wave_write_out<P, TM, TN, SPITCH, false>(p, stage, g, grow0, gcol0, M, N, lane, early);
     } else {
-        wave_write_out<P, TM, TN, SPITCH, false>(p, stage, g, grow0, gcol0, M, N, lane);
+        wave_write_out<P, TM, TN, SPITCH, false>(p, stage, g, grow0, gcol0, M, N, lane, early);
     }
 }
 

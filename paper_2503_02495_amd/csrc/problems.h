@@ -459,6 +459,8 @@ template <typename T> struct UomeDownProblem {
     __device__ bool has_residual() const { return flags & F_RESIDUAL; }
     __device__ uint4 res8(int g, int r, int nn) const { return res8_as<false>(g, r, nn); }
     __device__ void put8(int g, int r, int nn, uint4 piece) const { put8_as<false>(g, r, nn, piece); }
+    __device__ bool has_early() const { return has_residual(); }
+    template <bool ONCE> __device__ uint4 early8(int g, int r, int nn) const { return res8_as<ONCE>(g, r, nn); }
     // ONCE: u's last use and the block's output
     template <bool ONCE> __device__ uint4 res8_as(int g, int r, int nn) const { return load16<ONCE>(u + ((size_t)g * l + r) * d + nn); }
     template <bool ONCE> __device__ void put8_as(int g, int r, int nn, uint4 piece) const { store16<ONCE>(out + ((size_t)g * l + r) * d + nn, piece); }

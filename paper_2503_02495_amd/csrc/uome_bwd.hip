@@ -95,8 +95,11 @@ template <typename T> struct UomeDhProblem {
     }
     __device__ float col_scale(int g, int nn) const { return expert_gate ? expert_gate[(size_t)g * n + expert(g, nn)] : 1.0f; }
     __device__ float epi(float v, float) const { return v; }
-    template <int TM, int TN, int SPITCH>
-    __device__ void write_out(uint16_t (*stage)[SPITCH], const float *colw, const float (&)[TM], int g, int grow0, int gcol0, int M, int N, int lane) const
+    __device__ bool has_early() const { return true; }
+    template <bool ONCE> __device__ uint4 early8(int g, int r, int nn) const { return load16<ONCE>(z + ((size_t)g * l + r) * ((size_t)kact * d_e) + nn); }
+    template <int TM, int TN, int SPITCH, typename EARLY>
+    __device__ void write_out(uint16_t (*stage)[SPITCH], const float *colw, const float (&)[TM], int g, int grow0, int gcol0, int M, int N, int lane,
+                              const EARLY &early) const
     {
         constexpr int WM = TM * 32, WC = TN * 4, NPIECE = WM * WC / 64, BATCH = largest_divisor_upto(NPIECE, 8);
         static_assert(64 % WC == 0, "a lane keeps its 8-column group");
@@ -111,8 +114,8 @@ template <typename T> struct UomeDhProblem {
 #pragma unroll
             for (int u = 0; u < BATCH; ++u) {
                 const int grow = min(grow0 + (lane + (t0 + u) * 64) / WC, M - 1);
-                const T *src = z + ((size_t)g * l + grow) * width + (col_ok ? gcol : 0);
-                zp[u] = once ? load16<true>(src) : load16<false>(src);
+                if constexpr (!std::is_same<EARLY, NoEarlyPieces>::value) zp[u] = early.piece[t0 + u];
+                else zp[u] = once ? early8<true>(g, grow, col_ok ? gcol : 0) : early8<false>(g, grow, col_ok ? gcol : 0);
             }
 #pragma unroll
             for (int u = 0; u < BATCH; ++u) {
