@@ -530,11 +530,13 @@ RouteBwdPlan route_bwd_plan(int b, int l, int d, int n, bool has_e, bool has_d)
     auto up8 = [](long v) { return (int)((v + 7) & ~7L); };
     // chunks per block: the gates are staged once for all of them; 2048 blocks keep every compute unit's slots filled
     auto reps = [](long blocks) { return (int)(blocks < 4096 ? 1 : (blocks > 8 * 2048 ? 8 : blocks / 2048)); };
-    // d_x: 8 samples per thread, 4 where that leaves compute units without a block or half of the lanes' work to
-    // absent samples; at most 32 tokens per block (their rows of U are staged in LDS)
+    // d_x: 4 samples per thread, 16 waves a compute unit; 8, with 12 waves, where W_E is long enough that its second reading costs more than
+    // that gives (launch of 128 x 196 x 384, 6 experts, W_E 0.9 MB: 48.7 us with 8, 47.8 with 4; 16 x 4096 x 256, 8, 17 MB: 61.8 and 58.1;
+    // 32 x 1024 x 512, 8, 8 MB: 62.0 and 56.7; 16 x 2048 x 1024, 16, 67 MB: 142.4 and 146.4; 12 x 4096 x 512, 32, 134 MB: 202.9 and 197.5,
+    // two expert tiles leaving 8 samples 8 waves).  At most 32 tokens per block (their rows of U are staged in LDS)
     p.dx_pieces = 30 * P < 256 ? 30 * P : 256;
     p.dx_chunks = (int)((pieces + p.dx_pieces - 1) / p.dx_pieces);
-    p.dx_bg = (b <= 4 || (long)p.dx_chunks * ((b + 7) / 8) < 256) ? 4 : 8;
+    p.dx_bg = b > 4 && n <= 16 && pieces * n >= 3L << 20 ? 8 : 4;   // W_E of 48 MB in bf16
     p.dx_groups = (b + p.dx_bg - 1) / p.dx_bg;
     p.dx_reps = reps((long)p.dx_chunks * p.dx_groups);
     p.dx_blocks = up8((p.dx_chunks + p.dx_reps - 1) / p.dx_reps) * p.dx_groups;
