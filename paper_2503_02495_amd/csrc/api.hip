@@ -130,7 +130,8 @@ UomeBwdWs uome_bwd_ws(const uoe_block_desc *d)
         const long pairs = (long)(d->b < 128 ? d->b : 128) * d->k;
         long items = (2 * d->n * s + pairs - 1) / pairs;
         if (items > 1) items = (d->l + uome_any_range(d->l, (int)items) - 1) / uome_any_range(d->l, (int)items);   // (as many as there are)
-        w.wgrad = wgrad_plan(d->b, d->n, d->k, (int)s, (int)items, 128);
+        const int range = uome_any_range(d->l, (int)items);
+        w.wgrad = wgrad_plan(d->b, d->n, d->k, (int)s, (int)items, 128, d->dtype == UOE_F32 ? 2 * range : range);
         w.partial = w.total;
         const size_t partial = (size_t)2 * chunks * w.wgrad.parts * d->d * d->width;
         w.total += up(partial * sizeof(float));
@@ -149,7 +150,7 @@ UomeBwdWs uome_bwd_ws(const uoe_block_desc *d)
     w.h = off; off += act;
     // data-selection mode (c < m) works on at most as many rows (units * l_a <= b * k * l) in the same
     // buffers; its weight gradients are cut by (unit, pick) segments instead of token ranges
-    w.wgrad = d->c < d->m ? smha_backward_wgrad(d->b, d->n, d->k, d->c, 2, d->width, d->d) : uome_backward_wgrad(d->b, d->l, d->d, d->n, d->k, d->width);
+    w.wgrad = d->c < d->m ? smha_backward_wgrad(d->b, d->n, d->k, d->c, d->l / d->m, 2, d->width, d->d) : uome_backward_wgrad(d->b, d->l, d->d, d->n, d->k, d->width);
     w.partial = off;
     off += up(2 * (size_t)w.wgrad.parts * d->d * d->width * sizeof(float));  // both weight gradients
     w.part_end = off; off += up(32 * sizeof(int32_t));
@@ -212,7 +213,7 @@ SmhaBwdWs smha_bwd_ws(const uoe_block_desc *d)
         const long avg = ((long)d->b * d->k * d->c / chunks + d->n - 1) / d->n;
         long parts = avg / 8;
         parts = wgrad_parts(d->dtype == UOE_F32, 4 * chunks, d->n, d->width, d->d, parts < 1 ? 1 : (parts > 8 ? 8 : parts));
-        w.wgrad = wgrad_plan(d->b, d->n, d->k, (int)parts, d->c, BWD_ANY_SEGMENTS);
+        w.wgrad = wgrad_plan(d->b, d->n, d->k, (int)parts, d->c, BWD_ANY_SEGMENTS, (d->dtype == UOE_F32 ? 2 : 1) * (d->l / d->m));
         w.partial = off;
         off += up((size_t)4 * chunks * w.wgrad.parts * d->d * d->width * sizeof(float));
         w.part_end = off; off += up((size_t)chunks * 32 * sizeof(int32_t));
@@ -231,7 +232,7 @@ SmhaBwdWs smha_bwd_ws(const uoe_block_desc *d)
     w.og = off; off += one;
     w.dqkv = off; off += 3 * one;
     w.partial = off;
-    w.wgrad = smha_backward_wgrad(d->b, d->n, d->k, d->c, 4, d->width, d->d);
+    w.wgrad = smha_backward_wgrad(d->b, d->n, d->k, d->c, d->l / d->m, 4, d->width, d->d);
     off += up((size_t)4 * w.wgrad.parts * d->width * d->d * sizeof(float));
     w.part_end = off; off += up(32 * sizeof(int32_t));
     w.total = off;

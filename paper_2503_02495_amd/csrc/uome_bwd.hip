@@ -38,7 +38,7 @@ WgradPlan uome_backward_wgrad(int b, int l, int d, int n, int k, int d_e)
     const long pairs = (long)b * k, k_avg = pairs * l / n, tiles = (long)n * ((d_e + 255) / 256) * ((d + 127) / 128);
     while (s < 8 && tiles * s < (s == 1 ? 512 : 256) && k_avg / (2 * s) >= 1024) s *= 2;
     while (pairs * ranges < 2L * n * s && l % (2 * ranges * 64) == 0) ranges *= 2;
-    return wgrad_plan(b, n, k, s, ranges, 128);
+    return wgrad_plan(b, n, k, s, ranges, 128, l / ranges);
 }
 
 // Elementwise middle for 8 elements: dZ, H and the sum of dH * SiLU(Z), an fp32 output.

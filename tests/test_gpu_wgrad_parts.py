@@ -1,6 +1,7 @@
 """Weight gradients whose experts are selected unequally: one by every sample, one by none, the others now and then, so that the parts of
 the experts' lists differ in number and length.  Lists of whole pairs, of ranges of tokens (with a shorter last one), of picked patches;
-more samples than a workgroup's table; as many experts as there may be; experts with so many pairs that all have as many parts."""
+more samples than a workgroup's table; as many experts as there may be; few or short parts and experts with many pairs, where all have
+as many parts (skew), and lists cut into parts of equal length (equal)."""
 import copy
 
 import numpy as np
@@ -24,12 +25,20 @@ UOME = {
     "skew_any_short_range": cfg(3, 397, 72, 5, 2, 56, m=1),
     "skew_f32": cfg(5, 260, 40, 7, 3, 136, dtype=synth.F32),
     "skew_f32_two_chunks": cfg(131, 20, 40, 9, 2, 24, dtype=synth.F32),
+    "equal_by_sample": cfg(6, 2048, 32, 6, 2, 64),
+    "equal_pairs": cfg(24, 512, 32, 4, 2, 32),
+    "equal_any_short_range": cfg(4, 2500, 40, 5, 2, 24, m=1),
+    "equal_f32": cfg(3, 1100, 40, 4, 2, 24, dtype=synth.F32),
+    "equal_two_chunks": cfg(131, 162, 40, 9, 1, 24, dtype=synth.F32),
     "skew_any_many_pairs": cfg(150, 14, 40, 4, 2, 72),
 }
 SMHA = {
     "skew_sm": cfg(6, 256, 64, 5, 2, 64, m=8, c=3),
     "skew_sm_n32": cfg(4, 128, 32, 32, 9, 32, m=4, c=2),
     "skew_sm_long_lists": cfg(20, 512, 32, 6, 2, 32, m=16, c=9),
+    "equal_sm": cfg(6, 512, 64, 5, 2, 64, m=16, c=8),
+    "equal_sm_f32": cfg(5, 240, 40, 7, 3, 24, m=12, c=9, dtype=synth.F32),
+    "equal_sm_two_chunks": cfg(131, 200, 40, 9, 1, 24, m=5, c=4),
     "skew_sm_f32": cfg(5, 77, 40, 7, 3, 24, m=7, c=4, dtype=synth.F32),
     "skew_sm_two_chunks": cfg(131, 14, 40, 9, 2, 24, m=2, c=2),
 }
