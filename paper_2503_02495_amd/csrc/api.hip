@@ -131,7 +131,7 @@ UomeBwdWs uome_bwd_ws(const uoe_block_desc *d)
         long items = (2 * d->n * s + pairs - 1) / pairs;
         if (items > 1) items = (d->l + uome_any_range(d->l, (int)items) - 1) / uome_any_range(d->l, (int)items);   // (as many as there are)
         const int range = uome_any_range(d->l, (int)items);
-        w.wgrad = wgrad_plan(d->b, d->n, d->k, (int)s, (int)items, 128, d->dtype == UOE_F32 ? 2 * range : range);
+        w.wgrad = wgrad_plan(d->b, d->n, d->k, (int)s, (int)items, 128, d->dtype == UOE_F32 ? range / 2 : range);
         w.partial = w.total;
         const size_t partial = (size_t)2 * chunks * w.wgrad.parts * d->d * d->width;
         w.total += up(partial * sizeof(float));
@@ -213,7 +213,7 @@ SmhaBwdWs smha_bwd_ws(const uoe_block_desc *d)
         const long avg = ((long)d->b * d->k * d->c / chunks + d->n - 1) / d->n;
         long parts = avg / 8;
         parts = wgrad_parts(d->dtype == UOE_F32, 4 * chunks, d->n, d->width, d->d, parts < 1 ? 1 : (parts > 8 ? 8 : parts));
-        w.wgrad = wgrad_plan(d->b, d->n, d->k, (int)parts, d->c, BWD_ANY_SEGMENTS, (d->dtype == UOE_F32 ? 2 : 1) * (d->l / d->m));
+        w.wgrad = wgrad_plan(d->b, d->n, d->k, (int)parts, d->c, BWD_ANY_SEGMENTS, d->l / d->m / (d->dtype == UOE_F32 ? 2 : 1));
         w.partial = off;
         off += up((size_t)4 * chunks * w.wgrad.parts * d->d * d->width * sizeof(float));
         w.part_end = off; off += up((size_t)chunks * 32 * sizeof(int32_t));

@@ -87,18 +87,19 @@ inline TailTile tail_tile(bool f32, bool km, bool gaps_nk, long groups, int rows
 // samples go in chunks of 128 (a workgroup's tables); within a chunk an expert has `items` items for each (sample, slot) pair that
 // selected it (picked patches, or ranges of the token axis), in sample order, and its list is cut evenly into parts of at most `per`.
 // Experts are not selected equally often: with the same number of parts for each the launch took as long as the most popular one
-// (4 x 8192 tokens, 8 of 16 experts of 1024 x 256: 352 us, 255 to 268 with equal parts; 8 x 512, fp32, 4 of 8 of 512 x 256: 102 and 74).
+// (4 x 8192 tokens, 8 of 16 experts of 1024 x 256: 352 us, 255 to 268 with equal parts).
 // Finding them takes 1 to 2 us, so experts keep one number of parts (`each`) where that is one, where a part is short (less than 256 tokens
-// on the average, 128 in fp32: 6 x 120 x 608, 6 of 12 experts of 64, 242 us for the layer's forward + backward, 249 with equal parts), and with 20
+// on the average, 512 in fp32: 6 x 120 x 608, 6 of 12 experts of 64, 242 us for the layer's forward + backward, 249 with equal parts), and with 20
 // pairs and more an expert (128 samples, 3 of 6 experts: within 10 % of each other; 96 us became 112 and 99 in the two orders there
-// are for unequal parts; 57 x 128 x 96, 4 of 11: 168.6 -> 174.0 for forward + backward).
+// are for unequal parts; 57 x 128 x 96, 4 of 11: 168.6 -> 174.0 for forward + backward; fp32 8 x 512 x 512, 4 of 8: 559 -> 535 with one selection, 547 -> 556 with
+// another that was nearly even).
 // `per` is the least for which no more than `parts` parts come of it, found by every workgroup from the selection (PartScan).
 struct WgradPlan {
     int chunks, items, parts;
     int lo, hi;        // bounds of `per`: all parts full; feasible for any selection
     int each;          // not 0: an expert has so many parts, whatever its list (experts with many pairs: their lists hardly differ)
 };
-// `splits`: parts of an expert with the average number of pairs; `cap`: entries of a workgroup's segment table; item_k: tokens of an item, twice in fp32
+// `splits`: parts of an expert with the average number of pairs; `cap`: entries of a workgroup's segment table; item_k: tokens of an item, half of them in fp32
 inline WgradPlan wgrad_plan(int b, int n, int k, int splits, int items, int cap, int item_k)
 {
     const int nb = b < 128 ? b : 128, most = nb * items;   // most: an expert every sample selected

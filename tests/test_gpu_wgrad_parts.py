@@ -28,8 +28,8 @@ UOME = {
     "equal_by_sample": cfg(6, 2048, 32, 6, 2, 64),
     "equal_pairs": cfg(24, 512, 32, 4, 2, 32),
     "equal_any_short_range": cfg(4, 2500, 40, 5, 2, 24, m=1),
-    "equal_f32": cfg(3, 1100, 40, 4, 2, 24, dtype=synth.F32),
-    "equal_two_chunks": cfg(131, 162, 40, 9, 1, 24, dtype=synth.F32),
+    "equal_f32": cfg(3, 4400, 40, 4, 2, 24, dtype=synth.F32),
+    "equal_two_chunks": cfg(131, 162, 40, 9, 1, 24),
     "skew_any_many_pairs": cfg(150, 14, 40, 4, 2, 72),
 }
 SMHA = {
@@ -37,7 +37,7 @@ SMHA = {
     "skew_sm_n32": cfg(4, 128, 32, 32, 9, 32, m=4, c=2),
     "skew_sm_long_lists": cfg(20, 512, 32, 6, 2, 32, m=16, c=9),
     "equal_sm": cfg(6, 512, 64, 5, 2, 64, m=16, c=8),
-    "equal_sm_f32": cfg(5, 240, 40, 7, 3, 24, m=12, c=9, dtype=synth.F32),
+    "equal_sm_f32": cfg(5, 768, 40, 7, 3, 24, m=12, c=9, dtype=synth.F32),
     "equal_sm_two_chunks": cfg(131, 200, 40, 9, 1, 24, m=5, c=4),
     "skew_sm_f32": cfg(5, 77, 40, 7, 3, 24, m=7, c=4, dtype=synth.F32),
     "skew_sm_two_chunks": cfg(131, 14, 40, 9, 2, 24, m=2, c=2),
