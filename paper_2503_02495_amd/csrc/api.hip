@@ -126,12 +126,7 @@ UomeBwdWs uome_bwd_ws(const uoe_block_desc *d)
         s = s < 1 ? 1 : (s > 8 ? 8 : s);
         if (s > most) s = most;
         s = wgrad_parts(d->dtype == UOE_F32, 2 * chunks, d->n, d->width, d->d, s / chunks > 1 ? s / chunks : 1);
-        // pairs are cut into ranges of tokens until a part has two items
-        const long pairs = (long)(d->b < 128 ? d->b : 128) * d->k;
-        long items = (2 * d->n * s + pairs - 1) / pairs;
-        if (items > 1) items = (d->l + uome_any_range(d->l, (int)items) - 1) / uome_any_range(d->l, (int)items);   // (as many as there are)
-        const int range = uome_any_range(d->l, (int)items);
-        w.wgrad = wgrad_plan(d->b, d->n, d->k, (int)s, (int)items, 128, d->dtype == UOE_F32 ? range / 2 : range);
+        w.wgrad = uome_any_wgrad(d->b, d->l, d->n, d->k, (int)s, d->dtype == UOE_F32);
         w.partial = w.total;
         const size_t partial = (size_t)2 * chunks * w.wgrad.parts * d->d * d->width;
         w.total += up(partial * sizeof(float));

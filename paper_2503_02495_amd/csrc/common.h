@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stddef.h>
+#include "wgrad_plan.h"
 
 namespace uoe {
 
@@ -81,44 +82,6 @@ inline TailTile tail_tile(bool f32, bool km, bool gaps_nk, long groups, int rows
     if (rows > 64 && tiles(128, 128) >= 512 && padded(128, 128) <= 1.1 && !gaps_nk) return {128, 128, false};
     if (rows > 64 && tiles(64, 128) >= 512 && padded(64, 128) <= 1.1) return {64, 128, false};
     return {64, 64, false};
-}
-
-// How the sums of the weight gradients over an expert's tokens are cut into parts, one fp32 partial tile (or grid of them) each.  The
-// samples go in chunks of 128 (a workgroup's tables); within a chunk an expert has `items` items for each (sample, slot) pair that
-// selected it (picked patches, or ranges of the token axis), in sample order, and its list is cut evenly into parts of at most `per`.
-// Experts are not selected equally often: with the same number of parts for each the launch took as long as the most popular one
-// (4 x 8192 tokens, 8 of 16 experts of 1024 x 256: 352 us, 255 to 268 with equal parts).
-// Finding them takes 1 to 2 us, so experts keep one number of parts (`each`) where that is one, where a part is short (less than 256 tokens
-// on the average, 512 in fp32: 6 x 120 x 608, 6 of 12 experts of 64, 242 us for the layer's forward + backward, 249 with equal parts), and with 20
-// pairs and more an expert (128 samples, 3 of 6 experts: within 10 % of each other; 96 us became 112 and 99 in the two orders there
-// are for unequal parts; 57 x 128 x 96, 4 of 11: 168.6 -> 174.0 for forward + backward; fp32 8 x 512 x 512, 4 of 8: 559 -> 535 with one selection, 547 -> 556 with
-// another that was nearly even).
-// `per` is the least for which no more than `parts` parts come of it, found by every workgroup from the selection (PartScan).
-struct WgradPlan {
-    int chunks, items, parts;
-    int lo, hi;        // bounds of `per`: all parts full; feasible for any selection
-    int each;          // not 0: an expert has so many parts, whatever its list (experts with many pairs: their lists hardly differ)
-};
-// `splits`: parts of an expert with the average number of pairs; `cap`: entries of a workgroup's segment table; item_k: tokens of an item, half of them in fp32
-inline WgradPlan wgrad_plan(int b, int n, int k, int splits, int items, int cap, int item_k)
-{
-    const int nb = b < 128 ? b : 128, most = nb * items;   // most: an expert every sample selected
-    const int need = (most + cap - 1) / cap;
-    splits = splits > need ? splits : need;                // (with `cap` items a part an expert has at most `splits` of them)
-    const long total = (long)nb * k * items, parts = (long)n * splits;
-    const long lo = (total + parts - 1) / parts;
-    // sum over experts of ceil(items of the expert / per) <= total / per + n
-    long hi = splits > 1 ? (total + parts - n - 1) / (parts - n) : most;
-    hi = hi < most ? hi : most;
-    hi = hi < cap ? hi : cap;
-    WgradPlan w;
-    w.chunks = (b + 127) / 128;
-    w.items = items;
-    w.parts = (int)parts;
-    w.each = splits == 1 || total * item_k < 256 * parts || (long)nb * k >= 20L * n ? splits : 0;
-    w.lo = (int)(lo < hi ? lo : hi);
-    w.hi = (int)hi;
-    return w;
 }
 
 __device__ __forceinline__ float to_f32(float x) { return x; }
@@ -388,11 +351,7 @@ hipError_t launch_uome_backward_any(const UomeBwdArgs &a, bool bf16, hipStream_t
 hipError_t launch_smha_backward_any(const SmhaBwdArgs &a, bool bf16, hipStream_t st);
 constexpr int BWD_ANY_SEGMENTS = 1024;        // (unit, pick) entries one part of an expert's weight gradient holds
 hipError_t launch_route_backward(const RouteBwdArgs &a, bool bf16, hipStream_t st);
-WgradPlan smha_backward_wgrad(int b, int n, int k, int c, int l_p, int sets, int rows, int cols);
 int uome_backward_gate_chunks(int l, int d_e);
-WgradPlan uome_backward_wgrad(int b, int l, int d, int n, int k, int d_e);
-// tokens of an item of the any-shape UoME weight gradients, pairs cut into `items`
-inline int uome_any_range(int l, int items) { return items == 1 ? l : ((l + items - 1) / items + 31) / 32 * 32; }
 
 // measurement probes (probe.hip)
 constexpr unsigned PROBE_READ_BLOCKS = 256 * 16, PROBE_MFMA_BLOCKS = 256 * 2;

@@ -466,18 +466,6 @@ template <bool PAD> static hipError_t launch_attention_bwd(const AttnBwdArgs &a,
     return launch_attention_bwd_dh<128, PAD>(a, units, st);
 }
 
-WgradPlan smha_backward_wgrad(int b, int n, int k, int c, int l_p, int sets, int rows, int cols)
-{
-    // parts of an average expert's (unit, pick) list: about 8 segments each, and at most 8 parts; not more than two where 256 tiles
-    // of 128 x 128 come of it, a part's fp32 tiles being written and read again (4 x 8192 tokens, 16 experts of 64 x 1024: 4 parts
-    // 66 us and 16 for the reduction, 2 parts 54 and 12; 8 x 512, 8 of 256 x 512: 27 and 23)
-    const int avg = (int)(((long)b * k * c + n - 1) / n);
-    const long tiles = (long)sets * n * ((rows + 127) / 128) * ((cols + 127) / 128), most = tiles >= 128 ? 2 : (256 + tiles - 1) / tiles;
-    long s = avg / 8;
-    s = s < 1 ? 1 : (s > 8 ? 8 : s);
-    return wgrad_plan(b, n, k, (int)(s < most ? s : most), c, 128, l_p);
-}
-
 hipError_t launch_smha_backward(const SmhaBwdArgs &a_in, hipStream_t st)
 {
     typedef bf16_t T;
