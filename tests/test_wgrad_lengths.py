@@ -1,0 +1,77 @@
+"""How long the parts of the weight gradients' sums are (csrc/wgrad_plan.h, built with g++; the cut that every workgroup derives from the plan and
+the selection is restated here).  A launch waits for its longest part, so no selection may leave one longer than cutting the token axis
+of each of an expert's (sample, slot) pairs into the same number of ranges would, or cutting the list of pairs where there are many."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2503_02495_amd", "csrc")
+SHIM = """
+#include "wgrad_plan.h"
+static void give(const uoe::WgradPlan &w, int *o) { o[0] = w.chunks; o[1] = w.items; o[2] = w.parts; o[3] = w.lo; o[4] = w.hi; o[5] = w.each; }
+extern "C" void any_plan(int b, int l, int n, int k, int s, int f32, int *o) { give(uoe::uome_any_wgrad(b, l, n, k, s, f32 != 0), o); o[6] = uoe::uome_any_range(l, o[1]); }
+"""
+
+
+@pytest.fixture(scope="module")
+def shim(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan")
+    (d / "shim.cc").write_text(SHIM)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC, str(d / "shim.cc"), "-o", str(d / "shim.so")], check=True)
+    return ctypes.CDLL(str(d / "shim.so"))
+
+
+def call(fn, *args):
+    out = (ctypes.c_int * 7)()
+    fn(*args, out)
+    return dict(zip(("chunks", "items", "parts", "lo", "hi", "each", "range"), out))
+
+
+def selections(rng, b, n, k):
+    """Pairs an expert: even, random, and skewed to the first experts."""
+    yield np.bincount(np.arange(b * k) % n, minlength=n)
+    for weight in (np.ones(n), 1.0 / np.arange(1, n + 1)):
+        yield np.bincount(np.concatenate([rng.choice(n, k, replace=False, p=weight / weight.sum()) for _ in range(b)]), minlength=n)
+
+
+def longest(plan, lengths, counts):
+    """Tokens of the longest part; lengths: tokens of a pair's items, counts: pairs an expert."""
+    items = counts * plan["items"]
+    if plan["each"]:
+        per = -(-items // plan["each"])
+        cuts = [np.minimum(np.arange(plan["each"] + 1) * p, i) for i, p in zip(items, per)]
+    else:
+        step = (plan["hi"] - plan["lo"] + 62) // 63
+        tried = [min(plan["lo"] + lane * step, plan["hi"]) for lane in range(64)]
+        fits = [p for p in tried if sum(-(-items // p)) <= plan["parts"]]
+        assert fits
+        parts = -(-items // fits[0])
+        cuts = [np.arange(p + 1) * i // max(p, 1) for i, p in zip(items, parts)]
+    most = 0
+    for c, cut in zip(counts, cuts):
+        ends = np.concatenate([[0], np.cumsum(np.tile(lengths, c))])
+        assert cut[-1] == c * plan["items"] and np.diff(cut).max(initial=0) <= 128
+        most = max(most, int(np.diff(ends[cut]).max(initial=0)))
+    return most
+
+
+ANY = [(8, 512, 8, 4, 8), (4, 770, 5, 2, 8), (6, 1000, 6, 3, 7), (10, 500, 5, 2, 8), (128, 196, 6, 3, 7), (24, 500, 4, 2, 6), (3, 2009, 13, 3, 4), (2, 64, 4, 2, 8),
+       (1, 4096, 32, 1, 8), (16, 140, 12, 5, 3), (57, 128, 11, 4, 2), (100, 77, 4, 2, 5), (128, 300, 32, 7, 8), (12, 2500, 4, 1, 8), (5, 31, 3, 2, 4)]
+
+
+@pytest.mark.parametrize("f32", [0, 1])
+@pytest.mark.parametrize("b,l,n,k,s", ANY)
+def test_any_shape(shim, b, l, n, k, s, f32):
+    plan = call(shim.any_plan, b, l, n, k, s, f32)
+    assert plan["parts"] == n * s
+    lengths = np.minimum(plan["range"], l - np.arange(plan["items"]) * plan["range"])
+    assert lengths.min() > 0 and lengths.sum() == l
+    whole, axis = b * k >= 4 * n * s, min(l, -(-(-(-l // s)) // 32) * 32)
+    rng = np.random.default_rng(l)
+    for _ in range(20):
+        for counts in selections(rng, b, n, k):
+            most = counts.max()
+            assert longest(plan, lengths, counts) <= (-(-most // s) * l if whole else most * axis), (plan, counts)
