@@ -47,11 +47,13 @@ inline WgradPlan uome_backward_wgrad(int b, int l, int d, int n, int k, int d_e)
     // parts until the launch of both gradients has 512 tiles of 256 x 128, while one keeps on average >= 1024 of K; two of them also
     // where one would do, for experts with longer lists.  (Until one gradient has 512: 4 x 8192 tokens, 16 experts of 1024 x 256, 128
     // instead of 64 MB of fp32 tiles written and read again: 1974 against 1944 us for the layer's forward + backward.)  Pairs are cut
-    // into ranges of tokens, a multiple of 64, until a part has two items (for lists that do not divide evenly).
+    // into ranges of tokens, a multiple of 64, until a part has two items (for lists that do not divide evenly) and there are as many as
+    // parts: no part can then be longer than with the token axis cut so often (8 x 512, 4 of 8 experts, whole pairs: the longest part longer
+    // than that for 20 % of random selections).
     int s = 1, ranges = 1;
     const long pairs = (long)b * k, k_avg = pairs * l / n, tiles = (long)n * ((d_e + 255) / 256) * ((d + 127) / 128);
     while (s < 8 && tiles * s < (s == 1 ? 512 : 256) && k_avg / (2 * s) >= 1024) s *= 2;
-    while (pairs * ranges < 2L * n * s && l % (2 * ranges * 64) == 0) ranges *= 2;
+    while ((pairs * ranges < 2L * n * s || ranges < s) && l % (2 * ranges * 64) == 0) ranges *= 2;
     return wgrad_plan(b, n, k, s, ranges, 128, l / ranges);
 }
 

@@ -13,6 +13,7 @@ SHIM = """
 #include "wgrad_plan.h"
 static void give(const uoe::WgradPlan &w, int *o) { o[0] = w.chunks; o[1] = w.items; o[2] = w.parts; o[3] = w.lo; o[4] = w.hi; o[5] = w.each; }
 extern "C" void any_plan(int b, int l, int n, int k, int s, int f32, int *o) { give(uoe::uome_any_wgrad(b, l, n, k, s, f32 != 0), o); o[6] = uoe::uome_any_range(l, o[1]); }
+extern "C" void grid_plan(int b, int l, int d, int n, int k, int d_e, int *o) { give(uoe::uome_backward_wgrad(b, l, d, n, k, d_e), o); o[6] = l / o[1]; }
 """
 
 
@@ -75,3 +76,20 @@ def test_any_shape(shim, b, l, n, k, s, f32):
         for counts in selections(rng, b, n, k):
             most = counts.max()
             assert longest(plan, lengths, counts) <= (-(-most // s) * l if whole else most * axis), (plan, counts)
+
+
+GRID = [(8, 512, 512, 8, 4, 256), (8, 512, 512, 8, 3, 256), (4, 8192, 1024, 16, 8, 256), (16, 4096, 256, 8, 2, 128), (64, 512, 256, 4, 2, 128), (57, 128, 96, 11, 4, 64),
+        (6, 2048, 32, 6, 2, 64), (24, 512, 32, 4, 2, 32), (4, 640, 128, 8, 1, 96), (3, 2720, 416, 12, 5, 96), (128, 1024, 64, 6, 3, 64), (32, 960, 160, 14, 2, 32)]
+
+
+@pytest.mark.parametrize("b,l,d,n,k,d_e", GRID)
+def test_on_the_32_grid(shim, b, l, d, n, k, d_e):
+    plan = call(shim.grid_plan, b, l, d, n, k, d_e)
+    s, axis = plan["parts"] // n, 1
+    assert plan["range"] * plan["items"] == l and (plan["items"] == 1 or plan["range"] % 64 == 0)
+    while 2 * axis <= s and l % (2 * axis * 64) == 0:
+        axis *= 2
+    rng = np.random.default_rng(l)
+    for _ in range(20):
+        for counts in selections(rng, b, n, k):
+            assert longest(plan, np.full(plan["items"], plan["range"]), counts) <= counts.max() * (l // axis), (plan, counts)
