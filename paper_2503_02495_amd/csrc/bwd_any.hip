@@ -226,7 +226,7 @@ template <typename T> struct UomeBwdWgrad : PlainEpilogue {
     const int32_t *expert_idx;
     float *partial;                // [2*chunks*parts, d_e, d]
     int b, l, d, n, kact, d_e, range;   // range: tokens of an item, fewer in a pair's last one
-    WgradOrder parts;
+    WgradOrder<true, false> parts;
     static constexpr bool kF32Out = true, kPrepare = true;
     __device__ int rows(int) const { return d_e; }
     __device__ int ncols() const { return d; }
@@ -381,7 +381,7 @@ template <typename T> hipError_t uome_backward_any(const UomeBwdArgs &a, hipStre
     wp.left[0] = h; wp.right[0] = d_out;
     wp.left[1] = dz; wp.right[1] = u;
     wp.expert_idx = a.expert_idx; wp.partial = a.partial;
-    wp.b = a.b; wp.l = a.l; wp.d = a.d; wp.n = a.n; wp.kact = a.k; wp.d_e = a.d_e; wp.parts = WgradOrder(2, WgradOrder::BY_SAMPLE, a.wgrad, nullptr);
+    wp.b = a.b; wp.l = a.l; wp.d = a.d; wp.n = a.n; wp.kact = a.k; wp.d_e = a.d_e; wp.parts = {2, BY_SAMPLE, a.wgrad, nullptr};
     wp.range = uome_any_range(a.l, a.wgrad.items);
     if ((err = launch_gemm_tail<GEMM_A_KM>(wp, wp.parts.groups(), a.d_e, a.d, st)) != hipSuccess) return err;
     WgradReduceArgs ra{};
@@ -846,7 +846,7 @@ template <typename T> struct SmhaBwdWgrad : PlainEpilogue {
     const int32_t *expert_idx, *patch_idx;
     float *partial;                   // [4*chunks*parts, d_h, d]
     int b, l, d, n, kact, m, c, l_p, l_a, d_h;
-    WgradOrder parts;
+    WgradOrder<true, true> parts;
     static constexpr bool kF32Out = true, kPrepare = true;
     static constexpr int kMaxSegments = BWD_ANY_SEGMENTS;
     __device__ int rows(int) const { return d_h; }
@@ -941,14 +941,14 @@ template <typename T> hipError_t smha_backward_any(const SmhaBwdArgs &a, hipStre
     wp.x = static_cast<const T *>(f.x); wp.d_out = static_cast<const T *>(a.d_out);
     wp.expert_idx = f.expert_idx; wp.patch_idx = f.patch_idx; wp.partial = a.partial;
     wp.b = f.b; wp.l = f.l; wp.d = f.d; wp.n = f.n; wp.kact = f.k; wp.m = f.m; wp.c = f.c;
-    wp.l_p = l_p; wp.l_a = l_a; wp.d_h = dh; wp.parts = WgradOrder(4, WgradOrder::DEALT, a.wgrad, a.part_end);
+    wp.l_p = l_p; wp.l_a = l_a; wp.d_h = dh; wp.parts = {4, DEALT, a.wgrad, a.part_end};
     if ((err = launch_gemm_tail<GEMM_A_KM>(wp, wp.parts.groups(), dh, f.d, st)) != hipSuccess) return err;
     WgradReduceArgs ra{};
     ra.partial = a.partial; ra.n = f.n; ra.M = dh; ra.N = f.d;
     ra.w = a.wgrad; ra.part_end = a.part_end;
     ra.dst[0] = a.d_wq; ra.dst[1] = a.d_wk; ra.dst[2] = a.d_wv; ra.dst[3] = a.d_wo;
     ra.transposed[0] = ra.transposed[1] = ra.transposed[2] = 1; ra.transposed[3] = 0;
-    return launch_wgrad_reduce_gates<T>(ra, 4, a, st);
+    return launch_wgrad_reduce_gates<T, true>(ra, 4, a, st);
 }
 
 }  // namespace

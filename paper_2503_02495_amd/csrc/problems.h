@@ -524,34 +524,55 @@ struct PartScan {
     }
 };
 
+// x / by for x * by < 2^32 by the reciprocal rounded up
+struct Divider {
+    int by;
+    uint32_t inv;   // 0: by one
+    Divider() = default;
+    explicit Divider(int by_) : by(by_), inv(by_ > 1 ? 0xFFFFFFFFu / (uint32_t)by_ + 1u : 0u) {}
+    __device__ int of(int x) const { return inv ? (int)__umulhi((uint32_t)x, inv) : x; }
+};
+
 // A launch's groups: (set, chunk, place) for gradient tensors of one shape.  Each XCD works on a contiguous eighth of the groups.
 //   IN_ORDER   expert by expert
 //   BY_SAMPLE  places follow where in the sample axis a part begins: the parts that run on an XCD at one time are those of different experts
 //              over the same tokens, whose right operands are the same rows (4 x 8192 tokens, 16 experts of 1024 x 256: 272 -> 254 us)
 //   DEALT      dealt round-robin over the eighths, so that each gets parts of all experts: short parts of patches, where finding the order
 //              by samples takes longer than it saves (8 x 512 tokens, 8 experts, with d_x: 15.0 us in order, 17.8 by sample, 13.3 dealt)
-struct WgradOrder {
-    enum { IN_ORDER, BY_SAMPLE, DEALT };
-    int sets, by;
+// CHUNKED: more than 128 samples are possible; MAY_DEAL: the problem asks for DEALT
+enum { IN_ORDER, BY_SAMPLE, DEALT };
+template <bool CHUNKED, bool MAY_DEAL> struct WgradOrder {
+    int sets_log2, by;
     WgradPlan w;
     int32_t *part_end;   // [chunks, 32] first part id behind an expert's, for the reduction, or NULL: it finds them itself
+    Divider parts, eighth, each;   // (five divisions one behind the other were half a microsecond at the start of a short launch)
     WgradOrder() = default;
-    WgradOrder(int sets_, int by_, const WgradPlan &w_, int32_t *part_end_) : sets(sets_), by(w_.each ? IN_ORDER : by_), w(w_), part_end(part_end_) {}
-    int groups() const { const int g = sets * w.chunks * w.parts; return by == DEALT ? (g + 7) / 8 * 8 : g; }
+    WgradOrder(int sets, int by_, const WgradPlan &w_, int32_t *part_end_)
+        : sets_log2(sets == 4 ? 2 : 1), by(w_.each ? IN_ORDER : by_), w(w_), part_end(part_end_), parts(w_.parts), eighth((sets * w_.chunks * w_.parts + 7) / 8),
+          each(w_.each ? w_.each : 1) {}
+    int groups() const { const int g = (w.chunks * w.parts) << sets_log2; return by == DEALT ? (g + 7) / 8 * 8 : g; }
     // set in bits 0-1, place in bits 2-14 (at most 32 experts x 128 parts), chunk above
     __device__ int decode(int g) const
     {
-        if (by == DEALT) {
-            const int eighth = (sets * w.chunks * w.parts + 7) / 8, o = g % eighth * 8 + g / eighth, r = o / sets, c = r % w.chunks;
-            return (o - r * sets) | (r / w.chunks) << 2 | c << 15;
+        if (CHUNKED && w.chunks > 1) {
+            if (MAY_DEAL && by == DEALT) {
+                const int o = g % eighth.by * 8 + g / eighth.by, r = o >> sets_log2, c = r % w.chunks;
+                return (o - (r << sets_log2)) | (r / w.chunks) << 2 | c << 15;
+            }
+            const int s = g / (w.chunks * w.parts), r = g - s * (w.chunks * w.parts), c = r / w.parts;
+            return s | (r - c * w.parts) << 2 | c << 15;
         }
-        const int s = g / (w.chunks * w.parts), r = g - s * (w.chunks * w.parts), c = r / w.parts;
-        return s | (r - c * w.parts) << 2 | c << 15;
+        if (MAY_DEAL && by == DEALT) {   // (fewer than 2^15 groups)
+            const int q = eighth.of(g), o = (g - q * eighth.by) * 8 + q, r = o >> sets_log2;
+            return (o - (r << sets_log2)) | r << 2;
+        }
+        const int s = parts.of(g);
+        return s | (g - s * w.parts) << 2;
     }
     __device__ int set(int g) const { return g & 3; }
     __device__ int place(int g) const { return g >> 2 & 0x1FFF; }   // (prepare() puts the part's id there)
-    __device__ int chunk(int g) const { return g >> 15; }
-    __device__ size_t tile(int g) const { return (size_t)(set(g) * w.chunks + chunk(g)) * w.parts + place(g); }   // its partial tile
+    __device__ int chunk(int g) const { return CHUNKED ? g >> 15 : 0; }
+    __device__ size_t tile(int g) const { return (size_t)(CHUNKED ? set(g) * w.chunks + chunk(g) : set(g)) * w.parts + place(g); }   // its partial tile
 };
 
 // The workgroup's part of an expert's list: its partial tile, items [first, last) of the expert, the expert's samples and slots
@@ -564,12 +585,12 @@ struct PartList {
     // first item of a part (at most 2^17 items and 2^12 parts; 64-bit divisions took 2 us here)
     static __device__ int begin_of(int items, int part, int parts) { return (int)((uint32_t)items * (uint32_t)part / (uint32_t)parts); }
     // false: no such part; else g's place becomes the part's id.  Ends on a barrier.
-    __device__ bool fill(const int32_t *expert_idx, int nb, int kact, int n, const WgradOrder &o, int &g, int tid, int &expert, int &first, int &last)
+    template <typename ORDER> __device__ bool fill(const int32_t *expert_idx, int nb, int kact, int n, const ORDER &o, int &g, int tid, int &expert, int &first, int &last)
     {
         const WgradPlan &w = o.w;
         int idx[KEPT_IDX];
-        if (w.each) {   // the expert is known: one ballot, and the slots with it
-            expert = o.place(g) / w.each;
+        if (__builtin_expect(w.each != 0, 1)) {   // the expert is known: one ballot, and the slots with it (what follows lies out of the way)
+            expert = o.each.of(o.place(g));
             const int part = o.place(g) - expert * w.each, at = min(tid, nb - 1) * kact;
             int slot = -1;
             for (int s = kact - 1; s >= KEPT_IDX; --s) slot = clampi(expert_idx[at + s], n) == expert ? s : slot;
@@ -583,7 +604,7 @@ struct PartList {
             if (tid < 128 && (tid & 63) == 0) mask[expert][tid >> 6] = m;
             if (tid < nb) slot_of[tid] = (int16_t)slot;
             __syncthreads();
-            const int items = (__popcll(mask[expert][0]) + __popcll(mask[expert][1])) * w.items, per = (items + w.each - 1) / w.each;
+            const int items = (__popcll(mask[expert][0]) + __popcll(mask[expert][1])) * w.items, per = o.each.of(items + w.each - 1);
             first = __builtin_amdgcn_readfirstlane(min(items, part * per));
             last = __builtin_amdgcn_readfirstlane(min(items, (part + 1) * per));
             return true;
@@ -593,7 +614,7 @@ struct PartList {
         const int total = __builtin_amdgcn_readlane(scan.behind, 31), q = o.place(g);
         if (o.part_end && q == 0 && o.set(g) == 0 && tid < 32) o.part_end[o.chunk(g) * 32 + tid] = scan.behind;
         int mine = q;
-        if (o.by != WgradOrder::BY_SAMPLE || total > 256) {
+        if (o.by != BY_SAMPLE || total > 256) {
             if (q >= total) return false;
         } else {   // the places that hold a part are spread evenly
             const int rank = begin_of(total, q, w.parts);
@@ -677,7 +698,7 @@ template <typename T> struct WgradProblem {
     const int32_t *expert_idx;
     float *partial;        // [sets*parts, M, N]
     int b, l, n, kact, range;   // range: tokens of an item
-    WgradOrder parts;      // one chunk (b <= 128)
+    WgradOrder<false, false> parts;   // b <= 128
     int M, N;              // rows and columns of one expert's gradient (d_e and d)
 
     static constexpr bool kF32Out = true;
@@ -739,7 +760,7 @@ template <typename T> struct SmhaWgradProblem {
     const int32_t *expert_idx, *patch_idx;
     float *partial;             // [sets*parts, M, d]
     int b, l, d, n, kact, m, c, l_p, l_a;
-    WgradOrder parts;           // one chunk (b <= 128)
+    WgradOrder<false, true> parts;   // b <= 128
     int M;
 
     static constexpr bool kF32Out = true;

@@ -529,7 +529,7 @@ hipError_t launch_smha_backward(const SmhaBwdArgs &a_in, hipStream_t st)
     wp.row_len[3] = dh; wp.col0[3] = 0;
     wp.expert_idx = f.expert_idx; wp.patch_idx = f.patch_idx; wp.partial = a.partial;
     wp.b = f.b; wp.l = f.l; wp.d = f.d; wp.n = f.n; wp.kact = f.k; wp.m = f.m; wp.c = f.c;
-    wp.l_p = l_p; wp.l_a = l_a; wp.parts = WgradOrder(4, WgradOrder::DEALT, a.wgrad, a.part_end); wp.M = dh;
+    wp.l_p = l_p; wp.l_a = l_a; wp.parts = {4, DEALT, a.wgrad, a.part_end}; wp.M = dh;
     // one launch with d_x while the weight gradients do not fill the chip's slots (two per compute unit)
     const int groups = wp.parts.groups();
     typedef GemmTile<SmhaDxProblem<T, 1>, 32, 128, 32, 1, 4, 4, GEMM_B_NK> Dx32;
@@ -550,7 +550,7 @@ hipError_t launch_smha_backward(const SmhaBwdArgs &a_in, hipStream_t st)
     ra.dst[0] = a.d_wq; ra.dst[1] = a.d_wk;
     ra.dst[2] = a.d_wv; ra.dst[3] = a.d_wo;
     ra.transposed[0] = ra.transposed[1] = ra.transposed[2] = 1; ra.transposed[3] = 0;
-    return launch_wgrad_reduce_gates<T>(ra, 4, a, st);
+    return launch_wgrad_reduce_gates<T, false>(ra, 4, a, st);
 }
 
 }  // namespace uoe

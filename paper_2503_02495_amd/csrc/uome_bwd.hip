@@ -224,7 +224,7 @@ __global__ __launch_bounds__(256) void uome_bwd_gate_kernel(UomeBwdArgs a) { uom
 __global__ __launch_bounds__(256) void uome_bwd_finish_kernel(WgradReduceArgs ra, UomeBwdArgs a, int nx, int ny, int gates)
 {
     const int id = (int)blockIdx.x - gates;
-    if (id >= 0) wgrad_reduce_tile<bf16_t>(ra, id % nx, id / nx % ny, id / (nx * ny));
+    if (id >= 0) wgrad_reduce_tile<bf16_t, false>(ra, id % nx, id / nx % ny, id / (nx * ny));
     else uome_bwd_gate_block(a, blockIdx.x % a.k, blockIdx.x / a.k);
 }
 
@@ -269,7 +269,7 @@ hipError_t launch_uome_backward(const UomeBwdArgs &a, hipStream_t st)
     wp.left[0] = static_cast<const T *>(a.h); wp.right[0] = static_cast<const T *>(a.d_out);  // dA^O_i
     wp.left[1] = static_cast<const T *>(a.dz); wp.right[1] = static_cast<const T *>(a.u);     // (dA^I_i)^T
     wp.expert_idx = a.expert_idx; wp.partial = a.partial;
-    wp.b = a.b; wp.l = a.l; wp.n = a.n; wp.kact = a.k; wp.parts = WgradOrder(2, WgradOrder::BY_SAMPLE, a.wgrad, a.part_end);
+    wp.b = a.b; wp.l = a.l; wp.n = a.n; wp.kact = a.k; wp.parts = {2, BY_SAMPLE, a.wgrad, a.part_end};
     wp.M = a.d_e; wp.N = a.d; wp.range = a.l / a.wgrad.items;
     // one launch for d_u and the weight gradients while neither fills the chip's slots (two per compute unit) by itself
     const int groups = wp.parts.groups(), kseg = wp.range;
@@ -395,7 +395,7 @@ hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st)
     for (int q = 0; q < 4; ++q) { wp.row_len[q] = a.d_e; wp.col0[q] = 0; }
     wp.expert_idx = a.expert_idx; wp.patch_idx = a.patch_idx; wp.partial = a.partial;
     wp.b = a.b; wp.l = a.l; wp.d = a.d; wp.n = a.n; wp.kact = a.k; wp.m = a.m; wp.c = a.c;
-    wp.l_p = l_p; wp.l_a = l_a; wp.parts = WgradOrder(2, WgradOrder::DEALT, a.wgrad, a.part_end); wp.M = a.d_e;
+    wp.l_p = l_p; wp.l_a = l_a; wp.parts = {2, DEALT, a.wgrad, a.part_end}; wp.M = a.d_e;
     // one launch with d_u while the weight gradients do not fill the chip's slots (two per compute unit)
     const int groups = wp.parts.groups();
     typedef GemmTile<OutProjProblem<T>, 32, 128, 32, 1, 4, 4, GEMM_B_NK> Du32;
@@ -415,7 +415,7 @@ hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st)
     ra.w = a.wgrad; ra.part_end = a.part_end;
     ra.dst[0] = a.d_a_out; ra.transposed[0] = 0;
     ra.dst[1] = a.d_a_in; ra.transposed[1] = 1;
-    return launch_wgrad_reduce_gates<T>(ra, 2, ga, st);
+    return launch_wgrad_reduce_gates<T, false>(ra, 2, ga, st);
 }
 
 }  // namespace uoe

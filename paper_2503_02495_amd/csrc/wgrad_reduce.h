@@ -28,8 +28,8 @@ template <> __device__ __forceinline__ void store4_as<bf16_t>(bf16_t *p, float4 
 {
     *reinterpret_cast<uint2 *>(p) = make_uint2(pack2_bf16(v.x, v.y), pack2_bf16(v.z, v.w));
 }
-// FIND: where an expert's parts lie is found from the selection, not read from part_end (1.7 us)
-template <typename T, bool FIND = false> __device__ __forceinline__ void wgrad_reduce_tile(const WgradReduceArgs &a, int bx, int by, int bz)
+// FIND: where an expert's parts lie is found from the selection, not read from part_end (1.7 us); CHUNKED: more than 128 samples are possible
+template <typename T, bool CHUNKED, bool FIND = false> __device__ __forceinline__ void wgrad_reduce_tile(const WgradReduceArgs &a, int bx, int by, int bz)
 {
     __shared__ float tile[RED_T][RED_T + 1];
     const int set = bz / a.n, e = bz - set * a.n, r0 = by * RED_T, c0 = bx * RED_T;
@@ -40,9 +40,9 @@ template <typename T, bool FIND = false> __device__ __forceinline__ void wgrad_r
 #pragma unroll
     for (int q = 0; q < 4; ++q) acc[q] = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll 1
-    for (int chunk = 0; chunk < a.w.chunks; ++chunk) {
+    for (int chunk = 0; chunk < (CHUNKED ? a.w.chunks : 1); ++chunk) {
         int first, parts;
-        if (a.w.each) {
+        if (__builtin_expect(a.w.each != 0, 1)) {
             first = e * a.w.each;
             parts = a.w.each;
         } else if constexpr (!FIND) {
@@ -58,7 +58,7 @@ template <typename T, bool FIND = false> __device__ __forceinline__ void wgrad_r
             parts = __builtin_amdgcn_readlane(scan.parts, e);
             first = __builtin_amdgcn_readlane(scan.behind, e) - parts;
         }
-        const float *src = a.partial + ((size_t)(set * a.w.chunks + chunk) * a.w.parts + first) * part + min(col, a.N - 4);
+        const float *src = a.partial + ((size_t)(CHUNKED ? set * a.w.chunks + chunk : set) * a.w.parts + first) * part + min(col, a.N - 4);
 #pragma unroll 2
         for (int j = 0; j < parts; ++j) {
             float4 v[4];
@@ -153,24 +153,24 @@ __device__ __forceinline__ void unit_gate_block(const SmhaBwdArgs &a, int g)
 
 // the last launch of a data-selected block: the gate gradients' units (the longer chains, hence first) and the
 // weight-gradient tiles
-template <typename T> __global__ __launch_bounds__(256) void wgrad_reduce_gates_kernel(WgradReduceArgs ra, SmhaBwdArgs ga, int nx, int ny, int units)
+template <typename T, bool CHUNKED> __global__ __launch_bounds__(256) void wgrad_reduce_gates_kernel(WgradReduceArgs ra, SmhaBwdArgs ga, int nx, int ny, int units)
 {
     const int id = (int)blockIdx.x - units;
-    if (id >= 0) wgrad_reduce_tile<T>(ra, id % nx, id / nx % ny, id / (nx * ny));
+    if (id >= 0) wgrad_reduce_tile<T, CHUNKED>(ra, id % nx, id / nx % ny, id / (nx * ny));
     else unit_gate_block(ga, blockIdx.x);
 }
 
-template <typename T> static inline hipError_t launch_wgrad_reduce_gates(const WgradReduceArgs &ra, int sets, const SmhaBwdArgs &ga, hipStream_t st)
+template <typename T, bool CHUNKED> static inline hipError_t launch_wgrad_reduce_gates(const WgradReduceArgs &ra, int sets, const SmhaBwdArgs &ga, hipStream_t st)
 {
     const int nx = (ra.N + RED_T - 1) / RED_T, ny = (ra.M + RED_T - 1) / RED_T, tiles = nx * ny * sets * ra.n;
     const int units = ga.d_expert_gate || ga.d_patch_gate ? ga.f.b * ga.f.k : 0;
-    hipLaunchKernelGGL((wgrad_reduce_gates_kernel<T>), dim3(tiles + units), dim3(256), 0, st, ra, ga, nx, ny, units);
+    hipLaunchKernelGGL((wgrad_reduce_gates_kernel<T, CHUNKED>), dim3(tiles + units), dim3(256), 0, st, ra, ga, nx, ny, units);
     return hipGetLastError();
 }
 
 template <typename T, bool FIND> __global__ __launch_bounds__(256, 6) void wgrad_reduce_kernel(WgradReduceArgs a)
 {
-    wgrad_reduce_tile<T, FIND>(a, blockIdx.x, blockIdx.y, blockIdx.z);
+    wgrad_reduce_tile<T, true, FIND>(a, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 // (without part_end)
