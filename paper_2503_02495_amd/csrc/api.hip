@@ -130,6 +130,7 @@ UomeBwdWs uome_bwd_ws(const uoe_block_desc *d)
         w.partial = w.total;
         const size_t partial = (size_t)2 * chunks * w.wgrad.parts * d->d * d->width;
         w.total += up(partial * sizeof(float));
+        w.part_end = w.total; w.total += w.wgrad.each ? 0 : up((size_t)chunks * 32 * sizeof(int32_t));   // (of equal parts)
         // the gate gradient's partial sums lie where the partial tiles go later (n >= k and d * d_e >= 64: one sum per
         // (sample, slot) always fits)
         w.gpart = w.partial;
@@ -606,7 +607,7 @@ int uoe_uome_backward(const uoe_block_desc *blk, const void *u, const void *a_in
     if (!uome_bwd_mfma(blk)) {
         a.z = at(ws, w.z); a.dh = at(ws, w.dh);
         a.h_op = at(ws, w.h_op); a.dz_op = at(ws, w.dz_op);
-        a.wgrad = w.wgrad; a.gchunks = w.gchunks;
+        a.wgrad = w.wgrad; a.part_end = reinterpret_cast<int32_t *>(at(ws, w.part_end)); a.gchunks = w.gchunks;
         a.partial = reinterpret_cast<float *>(at(ws, w.partial));
         a.gpart = reinterpret_cast<float *>(at(ws, w.gpart));
         return launch_uome_backward_any(a, blk->dtype == UOE_BF16, static_cast<hipStream_t>(hip_stream)) == hipSuccess

@@ -381,12 +381,12 @@ template <typename T> hipError_t uome_backward_any(const UomeBwdArgs &a, hipStre
     wp.left[0] = h; wp.right[0] = d_out;
     wp.left[1] = dz; wp.right[1] = u;
     wp.expert_idx = a.expert_idx; wp.partial = a.partial;
-    wp.b = a.b; wp.l = a.l; wp.d = a.d; wp.n = a.n; wp.kact = a.k; wp.d_e = a.d_e; wp.parts = {2, BY_SAMPLE, a.wgrad, nullptr};
+    wp.b = a.b; wp.l = a.l; wp.d = a.d; wp.n = a.n; wp.kact = a.k; wp.d_e = a.d_e; wp.parts = {2, BY_SAMPLE, a.wgrad, a.part_end};
     wp.range = uome_any_range(a.l, a.wgrad.items);
     if ((err = launch_gemm_tail<GEMM_A_KM>(wp, wp.parts.groups(), a.d_e, a.d, st)) != hipSuccess) return err;
     WgradReduceArgs ra{};
     ra.partial = a.partial; ra.n = a.n; ra.M = a.d_e; ra.N = a.d;
-    ra.w = a.wgrad; ra.expert_idx = a.expert_idx; ra.b = a.b; ra.kact = a.k;
+    ra.w = a.wgrad; ra.part_end = a.part_end;
     ra.dst[0] = a.d_a_out; ra.transposed[0] = 0;
     ra.dst[1] = a.d_a_in; ra.transposed[1] = 1;
     return launch_wgrad_reduce<T>(ra, 2, st);

@@ -257,7 +257,7 @@ struct UomeBwdArgs {
     void *dh;                                 // any-shape path: dH, fp32
     float *gpart;                             // [b, k, gchunks] partial sums of d_gate
     float *partial;                           // [2*chunks*parts, d_e, d] partial tiles of the two weight gradients
-    int32_t *part_end;                        // [chunks, 32] first part id behind an expert's (NULL on the UoME's any-shape path)
+    int32_t *part_end;                        // [chunks, 32] first part id behind an expert's
     int gchunks;
     WgradPlan wgrad;
     void *h_op, *dz_op;                       // any-shape path: H and dZ as left operands (may be z and dh themselves)
@@ -287,7 +287,7 @@ struct SmhaBwdArgs {
     float *inv_sum;                           // any-shape path: [units, l_a] 1 / softmax row sum; f.lse holds the row maximum there
     int rt_parts;                             // rt is that many arrays to be added (0: one), set by the launcher
     float *partial;                           // [4*chunks*parts, d_h, d] partial tiles of the four weight gradients
-    int32_t *part_end;                        // [chunks, 32] first part id behind an expert's (NULL on the UoME's any-shape path)
+    int32_t *part_end;                        // [chunks, 32] first part id behind an expert's
     WgradPlan wgrad;
     void *og;                                 // w o [units, l_a, d_h]; any-shape path: [units, l_a, parts, d_h], do_raw, q, k, v are
                                               // fp32 there and dqkv is [units, l_a, parts, 3*d_h]

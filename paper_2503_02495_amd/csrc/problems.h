@@ -544,7 +544,7 @@ enum { IN_ORDER, BY_SAMPLE, DEALT };
 template <bool CHUNKED, bool MAY_DEAL> struct WgradOrder {
     int sets_log2, by;
     WgradPlan w;
-    int32_t *part_end;   // [chunks, 32] first part id behind an expert's, for the reduction, or NULL: it finds them itself
+    int32_t *part_end;   // [chunks, 32] first part id behind an expert's, for the reduction
     Divider parts, eighth, each;   // (five divisions one behind the other were half a microsecond at the start of a short launch)
     WgradOrder() = default;
     WgradOrder(int sets, int by_, const WgradPlan &w_, int32_t *part_end_)
@@ -612,7 +612,7 @@ struct PartList {
         expert_masks(mask, idx, expert_idx, nb, kact, n, tid);
         const PartScan scan(mask, w, n, tid & 63);
         const int total = __builtin_amdgcn_readlane(scan.behind, 31), q = o.place(g);
-        if (o.part_end && q == 0 && o.set(g) == 0 && tid < 32) o.part_end[o.chunk(g) * 32 + tid] = scan.behind;
+        if (q == 0 && o.set(g) == 0 && tid < 32) o.part_end[o.chunk(g) * 32 + tid] = scan.behind;
         int mine = q;
         if (o.by != BY_SAMPLE || total > 256) {
             if (q >= total) return false;

@@ -2,7 +2,6 @@
 #pragma once
 #include "common.h"
 #include "gemm_mfma.h"
-#include "problems.h"
 
 namespace uoe {
 
@@ -16,8 +15,6 @@ struct WgradReduceArgs {
     int transposed[4];
     int n, M, N;
     const int32_t *part_end;   // [chunks, 32] first part id behind an expert's
-    const int32_t *expert_idx;   // [b, kact] (FIND)
-    int b, kact;
     WgradPlan w;
 };
 
@@ -28,8 +25,8 @@ template <> __device__ __forceinline__ void store4_as<bf16_t>(bf16_t *p, float4 
 {
     *reinterpret_cast<uint2 *>(p) = make_uint2(pack2_bf16(v.x, v.y), pack2_bf16(v.z, v.w));
 }
-// FIND: where an expert's parts lie is found from the selection, not read from part_end (1.7 us); CHUNKED: more than 128 samples are possible
-template <typename T, bool CHUNKED, bool FIND = false> __device__ __forceinline__ void wgrad_reduce_tile(const WgradReduceArgs &a, int bx, int by, int bz)
+// CHUNKED: more than 128 samples are possible
+template <typename T, bool CHUNKED> __device__ __forceinline__ void wgrad_reduce_tile(const WgradReduceArgs &a, int bx, int by, int bz)
 {
     __shared__ float tile[RED_T][RED_T + 1];
     const int set = bz / a.n, e = bz - set * a.n, r0 = by * RED_T, c0 = bx * RED_T;
@@ -45,18 +42,10 @@ template <typename T, bool CHUNKED, bool FIND = false> __device__ __forceinline_
         if (__builtin_expect(a.w.each != 0, 1)) {
             first = e * a.w.each;
             parts = a.w.each;
-        } else if constexpr (!FIND) {
+        } else {
             const int32_t *end = a.part_end + chunk * 32 + e;
             first = e ? end[-1] : 0;
             parts = end[0] - first;
-        } else {
-            __shared__ uint64_t mask[32][2];
-            if (chunk) __syncthreads();
-            int idx[KEPT_IDX];
-            expert_masks(mask, idx, a.expert_idx + (size_t)chunk * 128 * a.kact, min(128, a.b - chunk * 128), a.kact, a.n, threadIdx.x);
-            const PartScan scan(mask, a.w, a.n, threadIdx.x & 63);
-            parts = __builtin_amdgcn_readlane(scan.parts, e);
-            first = __builtin_amdgcn_readlane(scan.behind, e) - parts;
         }
         const float *src = a.partial + ((size_t)(CHUNKED ? set * a.w.chunks + chunk : set) * a.w.parts + first) * part + min(col, a.N - 4);
 #pragma unroll 2
@@ -168,17 +157,14 @@ template <typename T, bool CHUNKED> static inline hipError_t launch_wgrad_reduce
     return hipGetLastError();
 }
 
-template <typename T, bool FIND> __global__ __launch_bounds__(256, 6) void wgrad_reduce_kernel(WgradReduceArgs a)
+template <typename T> __global__ __launch_bounds__(256) void wgrad_reduce_kernel(WgradReduceArgs a)
 {
-    wgrad_reduce_tile<T, true, FIND>(a, blockIdx.x, blockIdx.y, blockIdx.z);
+    wgrad_reduce_tile<T, true>(a, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
-// (without part_end)
 template <typename T = bf16_t> static inline hipError_t launch_wgrad_reduce(const WgradReduceArgs &a, int sets, hipStream_t st)
 {
-    const dim3 grid((a.N + RED_T - 1) / RED_T, (a.M + RED_T - 1) / RED_T, sets * a.n);
-    if (a.w.each) hipLaunchKernelGGL((wgrad_reduce_kernel<T, false>), grid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((wgrad_reduce_kernel<T, true>), grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL((wgrad_reduce_kernel<T>), dim3((a.N + RED_T - 1) / RED_T, (a.M + RED_T - 1) / RED_T, sets * a.n), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
