@@ -227,11 +227,14 @@ template <typename T> struct UomeBwdWgrad : PlainEpilogue {
     float *partial;                // [2*chunks*parts, d_e, d]
     int b, l, d, n, kact, d_e, range;   // range: tokens of an item, fewer in a pair's last one
     WgradOrder<true, false> parts;
+    Divider items;
     static constexpr bool kF32Out = true, kPrepare = true;
     __device__ int rows(int) const { return d_e; }
     __device__ int ncols() const { return d; }
     __device__ int kseg(int) const { return range; }
     __device__ int seg_len(uint32_t ctx) const { return min(range, l - (int)(ctx >> 12) * range); }
+    // (range is a multiple of 32, or l; one short K-step in 16 and more unbalances the sums of either sign too little to matter)
+    __device__ int seg_tail(int step) const { return range < l && l >= 512 ? 0 : l % step; }
     __device__ int kdim(int) const { return 0; }
     __device__ long b_stride() const { return d; }
     __device__ long a_stride(int) const { return (long)kact * kSegParts * d_e; }
@@ -245,11 +248,13 @@ template <typename T> struct UomeBwdWgrad : PlainEpilogue {
         if (!list.fill(expert_idx + (size_t)base * kact, nb, kact, n, parts, g, tid, expert, first, last)) return -1;
         if (tid < nb && list.slot_of[tid] >= 0) {
             const int at = list.before(expert, tid) * parts.w.items - first;
-            for (int r = 0; r < parts.w.items; ++r)
-                if (at + r >= 0 && at + r < last - first) segtab[at + r] = ((uint32_t)r << 12) | ((uint32_t)tid << 5) | (uint32_t)list.slot_of[tid];
+            for (int r = max(0, -at); r < min(parts.w.items, last - first - at); ++r)
+                segtab[at + r] = ((uint32_t)r << 12) | ((uint32_t)tid << 5) | (uint32_t)list.slot_of[tid];
         }
         __syncthreads();
-        return (last - first) * kSegParts * range;
+        // a K-step is 32 tokens; a pair's last range is shorter
+        const int steps = (range + 31) / 32, steps_last = (l - (parts.w.items - 1) * range + 31) / 32;
+        return ((last - first) * steps - (items.of(last) - items.of(first)) * (steps - steps_last)) * kSegParts * 32;
     }
     __device__ uint32_t seg_ctx(int, int) const { return 0; }
     __device__ size_t token(int g, uint32_t ctx) const
@@ -382,7 +387,7 @@ template <typename T> hipError_t uome_backward_any(const UomeBwdArgs &a, hipStre
     wp.left[1] = dz; wp.right[1] = u;
     wp.expert_idx = a.expert_idx; wp.partial = a.partial;
     wp.b = a.b; wp.l = a.l; wp.d = a.d; wp.n = a.n; wp.kact = a.k; wp.d_e = a.d_e; wp.parts = {2, BY_SAMPLE, a.wgrad, a.part_end};
-    wp.range = uome_any_range(a.l, a.wgrad.items);
+    wp.range = uome_any_range(a.l, a.wgrad.items); wp.items = Divider(a.wgrad.items);
     if ((err = launch_gemm_tail<GEMM_A_KM>(wp, wp.parts.groups(), a.d_e, a.d, st)) != hipSuccess) return err;
     WgradReduceArgs ra{};
     ra.partial = a.partial; ra.n = a.n; ra.M = a.d_e; ra.N = a.d;

@@ -12,7 +12,8 @@
 //   kPrepare / prepare(g, segtab, scratch, tid, nthreads)  the workgroup builds its segment list itself (scratch: the stage buffers' LDS,
 //                                        behind a last barrier theirs again) and returns K (out-projection: which experts picked this patch); -1: there is no such tile
 //   decode(g)                            (optional) what the problem calls the launch's group g
-//   seg_len(ctx)                         (optional, GEMM_A_KM and GEMM_TAIL) a segment's own length, at most kseg(g)
+//   seg_len(ctx), seg_tail(step)         (optional, GEMM_A_KM and GEMM_TAIL) a segment's own length, at most kseg(g), and what the longest tail of one
+//                                        is in a K-step; K is then the sum of the lengths in whole K-steps
 // Its fp32 form writes four columns of a row at a time:
 //   epi_f32(v, scale), put4(g, m, nn, v4)   per-element math; the store (residual included)
 // and its bf16 form 16-byte pieces of output rows:
