@@ -126,7 +126,7 @@ UomeBwdWs uome_bwd_ws(const uoe_block_desc *d)
         s = s < 1 ? 1 : (s > 8 ? 8 : s);
         if (s > most) s = most;
         s = wgrad_parts(d->dtype == UOE_F32, 2 * chunks, d->n, d->width, d->d, s / chunks > 1 ? s / chunks : 1);
-        w.wgrad = uome_any_wgrad(d->b, d->l, d->n, d->k, (int)s, d->dtype == UOE_F32);
+        w.wgrad = uome_any_wgrad(d->b, d->l, d->d, d->n, d->k, (int)s, d->dtype == UOE_F32);
         w.partial = w.total;
         const size_t partial = (size_t)2 * chunks * w.wgrad.parts * d->d * d->width;
         w.total += up(partial * sizeof(float));
@@ -209,7 +209,7 @@ SmhaBwdWs smha_bwd_ws(const uoe_block_desc *d)
         const long avg = ((long)d->b * d->k * d->c / chunks + d->n - 1) / d->n;
         long parts = avg / 8;
         parts = wgrad_parts(d->dtype == UOE_F32, 4 * chunks, d->n, d->width, d->d, parts < 1 ? 1 : (parts > 8 ? 8 : parts));
-        w.wgrad = wgrad_plan(d->b, d->n, d->k, (int)parts, d->c, BWD_ANY_SEGMENTS, d->l / d->m / (d->dtype == UOE_F32 ? 2 : 1));
+        w.wgrad = wgrad_plan(d->b, d->n, d->k, (int)parts, d->c, BWD_ANY_SEGMENTS, (long)d->c * (d->l / d->m), 0);
         w.partial = off;
         off += up((size_t)4 * chunks * w.wgrad.parts * d->d * d->width * sizeof(float));
         w.part_end = off; off += up((size_t)chunks * 32 * sizeof(int32_t));
