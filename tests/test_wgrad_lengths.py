@@ -14,6 +14,7 @@ SHIM = """
 static void give(const uoe::WgradPlan &w, int *o) { o[0] = w.chunks; o[1] = w.items; o[2] = w.parts; o[3] = w.lo; o[4] = w.hi; o[5] = w.each; }
 extern "C" void any_plan(int b, int l, int n, int k, int s, int f32, int *o) { give(uoe::uome_any_wgrad(b, l, 8, n, k, s, f32 != 0), o); o[6] = uoe::uome_any_range(l, o[1]); }
 extern "C" void grid_plan(int b, int l, int d, int n, int k, int d_e, int *o) { give(uoe::uome_backward_wgrad(b, l, d, n, k, d_e), o); o[6] = l / o[1]; }
+extern "C" void patch_plan(int b, int n, int k, int c, int l_p, int sets, int rows, int cols, int *o) { give(uoe::smha_backward_wgrad(b, n, k, c, l_p, sets, rows, cols), o); }
 """
 
 
@@ -109,3 +110,11 @@ def test_on_the_32_grid(shim, b, l, d, n, k, d_e):
     for _ in range(20):
         for counts in selections(rng, b, n, k):
             assert longest(plan, np.full(plan["items"], plan["range"]), counts) <= counts.max() * (l // axis), (plan, counts)
+
+
+@pytest.mark.parametrize("b,l,n,k,c,m,width,d,sets", [(14, 2688, 12, 5, 19, 84, 128, 160, 4), (6, 4096, 8, 4, 32, 128, 64, 256, 4), (9, 3072, 5, 3, 20, 96, 96, 384, 4), (4, 4096, 3, 2, 32, 64, 64, 640, 4)])
+def test_picked_patches_fill_the_last_round(shim, b, l, n, k, c, m, width, d, sets):
+    """128 x 128 tiles on 256 compute units: a second round for a few tiles takes as long as a full one."""
+    plan = call(shim.patch_plan, b, n, k, c, l // m, sets, width, d)
+    tiles = sets * plan["parts"] * -(-width // 128) * -(-d // 128)
+    assert tiles <= 128 or tiles % 256 == 0 or tiles % 256 >= 192 or plan["parts"] >= n * min(8, b * k * c // n // 8)
