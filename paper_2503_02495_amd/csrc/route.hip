@@ -370,7 +370,9 @@ __device__ __forceinline__ void stage_w_b(const RouteArgs &a, unsigned char *wb)
 // v_mfma_f32_16x16x4_f32 for the four tokens j, 4+j, 8+j, 12+j, so that four of them, exact fp32 products, fold 16 tokens onto 16
 // patches; their W_A values are one 2-byte load each, for any m.  The waves' tiles are added in wave order.
 // What bounds it is the chain of dependent steps, on 64 to 512 workgroups: a memory round trip costs 2 us at the start of a launch, so
-// 512 columns of x, W_B and the first 64 columns of W_A are in flight together, and the k-steps' fragments are read four steps ahead of their products.
+// 256 columns of x, W_B and the first 64 columns of W_A are in flight together, and the k-steps' fragments are read four steps ahead of their products.
+// (512 columns take 142 registers, three waves a SIMD instead of four, also for the expert router's workgroups of the same launch: 13 x 2048 x 384,
+// n 12, 20.2 us for both routers and the selection against 17.5, 32 x 1024 x 512 20.1 and 18.9; they gain 0.3 of 13 us on 12 x 1024 x 512.)
 // Both routers' launch, us, against W_A fetched for a fold on the vector ALU behind the products and one set of 128 columns in flight:
 // 8 x 512 x 512, n 8, m 16: 10.2 -> 6.5; 6 x 1000 x 360, n 6, m 25: 12.2 -> 6.7; 128 x 196 x 384, n 6, m 14: 13.7 -> 11.3.
 // LDS: W_B, and in its place at the end the four waves' tiles of n x 64 sums
@@ -386,7 +388,7 @@ template <int NTILE, int KS>
 __device__ __forceinline__ void route_data_mfma_body(const RouteArgs &a, int chunk, int bb, unsigned char *smem)
 {
     constexpr int NP = NTILE * 16, ROWB = NP * 2, BLK = 8 * ROWB + (NP == 16 ? 128 : 32);
-    constexpr int UN = KS == 1 ? 8 : 4, SPAN = UN * 32, UB = 4;   // k-steps of one register set (two sets are in flight); fragments read ahead
+    constexpr int UN = 4, SPAN = UN * 32, UB = 4;           // k-steps of one register set (two sets are in flight); fragments read ahead
     constexpr int TOK = DATA_TOKENS / KS;                   // tokens at a time
     constexpr int FT = DATA_FOLD_TILES, RP = FT * 16 + 4;   // row pitch of the sums in LDS
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -538,7 +540,7 @@ __device__ __forceinline__ void route_data_mfma_body(const RouteArgs &a, int chu
 }
 
 template <int NTILE, int KS>
-__global__ __launch_bounds__(ROUTE_THREADS, NTILE == 1 ? 3 : 2) void route_data_mfma_kernel(RouteArgs a)
+__global__ __launch_bounds__(ROUTE_THREADS, NTILE == 1 ? 4 : 2) void route_data_mfma_kernel(RouteArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     route_data_mfma_body<NTILE, KS>(a, blockIdx.x, blockIdx.y, smem);
@@ -646,7 +648,7 @@ __global__ __launch_bounds__(256) void route_expert_mfma_kernel(RouteArgs a)
 // first, because each is a longer chain of dependent steps - and the rest the expert router
 // (chunk = id' % nchunks, sample group = id' / nchunks).
 template <int RT, int CT, int KS>
-__global__ __launch_bounds__(256, CT == 1 ? 3 : 2) void route_expert_data_kernel(RouteArgs a, int n_data)
+__global__ __launch_bounds__(256, CT == 1 ? 4 : 2) void route_expert_data_kernel(RouteArgs a, int n_data)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const int id = blockIdx.x;
