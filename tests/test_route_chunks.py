@@ -1,0 +1,26 @@
+"""How many tokens a workgroup of the bf16 data router takes, read off the workspace sizes (no GPU)."""
+import pytest
+
+from paper_2503_02495_amd import binding as B
+
+
+def up(nbytes):
+    return -(-nbytes // 256) * 256
+
+
+def chunk_tokens(b, l, d, n, m):
+    """The one of 16, 64 and 128 whose partial logit tiles make up the workspace of a block whose other buffers are known."""
+    got = B.workspace_bytes(None, B.block_desc(b, l, d, n, n, m, m, 8, B.BF16, 0))
+    rest = up(b * l * n * 8 * 2) + up(b * n * 4) * 2 + up(b * n * m * 4) * 3   # hidden activations, routing, summed logits
+    rest += up(-(-l // max(1, l // 512)) * b * n * 4)                          # the expert router's partial sums
+    fits = [t for t in (16, 64, 128) for t1 in (0, up(b * l * n * 4)) if rest + t1 + up(-(-l // t) * b * n * m * 4) == got]
+    assert len(fits) == 1, (got, fits)
+    return fits[0]
+
+
+@pytest.mark.parametrize("b,l,d,n,m,want", [
+    (8, 512, 512, 8, 16, 16), (1, 912, 512, 11, 12, 16), (16, 256, 768, 8, 8, 16), (2, 1024, 1024, 8, 32, 16),
+    (4, 900, 256, 6, 30, 64), (4, 1000, 128, 8, 20, 64), (1, 800, 96, 12, 25, 64), (6, 600, 128, 4, 12, 64), (16, 144, 96, 5, 9, 64)])
+def test_split_columns_where_rows_are_long_for_the_sums(b, l, d, n, m, want):
+    """Up to 4096 tokens: 16 of them while rows are long (d >= 192) and the partial logits few for that (24 a column at most)."""
+    assert chunk_tokens(b, l, d, n, m) == want
