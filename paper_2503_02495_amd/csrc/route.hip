@@ -117,17 +117,18 @@ bool route_stream_pays(int b, int l, int d, int n)
 }
 // Tokens per chunk of the data router: the MFMA kernel's workgroup, also the chunks of route_fold_kernel.  16 (the waves split the
 // columns) up to 256 workgroups, where rows of x are long and the partial tiles, which route_select adds up, few for them: 64 workgroups of 64 keep a
-// quarter of the compute units on x (both routers and the selection, with 16 and with 64: 8 x 512 x 512, 8 x 16 logits, 10.3 and 11.8 us; 1 x 912 x 512, 11 x 12,
-// 12.7 and 13.2; 4 x 900 x 256, 6 x 30, 11.5 and 10.6; 4 x 1000 x 128, 8 x 20, 11.1 and 10.0; 6 x 1000 x 360 6.7 with 64, 7.3 with 16 for the routers).  Two times 64 where the workgroups still
-// fill the chip twice: half of the partial tiles, and on 16 x 4096 x 256, 8 x 64 logits, no launch of route_reduce (119.4 us for the
-// layer's forward against 124.6).
+// quarter of the compute units on x (both routers and the selection, us, with 16 and with 64: 8 x 512 x 512, 8 x 16 logits, 10.3 and 11.8; 1 x 912 x 512, 11 x 12,
+// 12.7 and 13.2; 4 x 900 x 256, 6 x 30, 11.5 and 10.6; 4 x 1000 x 128, 8 x 20, 11.1 and 10.0).  Two times 64 where that saves route_reduce's launch, from
+// 128 workgroups on (16 x 4096 x 256, 8 x 64 logits: 21.2 and 25.9; 5 x 4096 x 128, 8 x 64: 13.0 and 13.6); otherwise it gains nothing (60 x 1000 x 128 16.8 and
+// 16.7, 64 x 1024 x 256 24.5 and 24.4) or loses (32 x 1024 x 512 20.5 and 18.9).
 int route_data_tokens_per_chunk(int b, int l, int d, int n, int m, bool bf16)
 {
     if (route_data_uses_mfma(b, l, d, n, bf16)) {
         const long tokens = (long)b * l;
         const long sums = (long)n * m * ((l + 15) / 16);
         if (tokens <= 4096 && n * m <= 512 && d >= 192 && sums <= 24L * d && sums <= 16384) return DATA_TOKENS / 4;
-        return tokens > 48 * 1024 && m <= DATA_FOLD_TILES * 16 ? 2 * DATA_TOKENS : DATA_TOKENS;
+        const auto selected = [&](int tc) { return n * m <= 512 && (long)n * m * ((l + tc - 1) / tc) <= 16384; };   // (route_select adds them up)
+        return tokens > 16 * 1024 && m <= DATA_FOLD_TILES * 16 && !selected(DATA_TOKENS) && selected(2 * DATA_TOKENS) ? 2 * DATA_TOKENS : DATA_TOKENS;
     }
     if (route_stream_plan(b, l, d, n, bf16, true).ok) return 64;
     return route_tokens_per_chunk(b, l);

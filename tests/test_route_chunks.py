@@ -24,3 +24,11 @@ def chunk_tokens(b, l, d, n, m):
 def test_split_columns_where_rows_are_long_for_the_sums(b, l, d, n, m, want):
     """Up to 4096 tokens: 16 of them while rows are long (d >= 192) and the partial logits few for that (24 a column at most)."""
     assert chunk_tokens(b, l, d, n, m) == want
+
+
+@pytest.mark.parametrize("b,l,d,n,m,want", [
+    (16, 4096, 256, 8, 64, 128), (8, 4096, 256, 8, 64, 128), (6, 4000, 320, 16, 32, 128), (16, 2048, 256, 8, 64, 64), (32, 1024, 512, 8, 16, 64), (60, 1000, 128, 16, 10, 64),
+    (2, 4096, 256, 8, 64, 64), (20, 3000, 192, 6, 60, 128), (8, 8192, 256, 8, 64, 64), (16, 4160, 256, 8, 65, 64)])
+def test_twice_the_tokens_where_that_saves_a_launch(b, l, d, n, m, want):
+    """128 tokens: from 16 K of them on, and only where the selection adds the partial logits up with 128 (512 logits, 16384 sums a sample) and not with 64."""
+    assert chunk_tokens(b, l, d, n, m) == want
