@@ -104,6 +104,34 @@ def test_uome_backward_sigmoid_tail(b, l, d, d_e, m, z):
     assert np.all(np.abs(got - want) <= 1e-4 * abs(want)), (got.ravel()[:2], want)
 
 
+@pytest.mark.parametrize("b,l", [(128, 32), (24, 2048)], ids=["one_launch", "two_launches"])
+def test_uome_backward_sigmoid_over_its_range(b, l):
+    """z sigmoid(z) of up to 4096 pre-activations from -88 to 88 (the fp32 exponential ends at 88.7), alone in d_gate.  Two fp32 roundings of the exponential's argument, |z| 2^-24 each,
+    and some eight of one ulp and less behind them; below 2^-126 the steps of fp32's smallest numbers.  NaN
+    comes out as NaN."""
+    n, d = 32, 32
+    step, top = torch.arange(b, dtype=torch.float32) * (128 // b), torch.tensor([88.0 * 0.75 ** i for i in range(16)])
+    u = torch.zeros((b, l, d), dtype=torch.bfloat16, device="cuda")
+    u[:, 0, 0] = (1.0 - step / 256).to(torch.bfloat16).cuda()                   # 1/256 steps down to 0.5: exact
+    a_in = torch.zeros((n, d, 32), dtype=torch.bfloat16, device="cuda")
+    a_in[:, 0, 0] = torch.cat([top, -top]).to(torch.bfloat16).cuda()
+    z = (u[:, :1, 0].double() * a_in[None, :, 0, 0].double()).to(torch.bfloat16 if l > 32 else torch.float32).double().cpu().numpy()   # Z is stored in bf16 between two launches
+    blk = B.block_desc(b, l, d, n, n, 1, 1, 32, B.BF16, GE)
+    a_out, d_out = one_hot((n, 32, d), (slice(None), 0, 0), 1.0), one_hot((b, l, d), (slice(None), 0, 0), 2.0 ** 40)
+    idx = torch.arange(n, dtype=torch.int32, device="cuda").repeat(b, 1)
+    gate = torch.ones((b, n), device="cuda")
+    d_gate, ws = torch.empty_like(gate), torch.empty(B.uome_backward_workspace_bytes(blk), dtype=torch.uint8, device="cuda")
+    run = lambda: B.uome_backward(blk, u, a_in, a_out, idx, gate, None, None, d_out, torch.empty_like(u), torch.empty_like(a_in), torch.empty_like(a_out), d_gate, None, ws)
+    run()
+    got, want = d_gate.double().cpu().numpy() * 2.0 ** -40, silu64(z)
+    off = np.abs(got - want) - np.abs(want) * (2 * np.abs(z) + 16) * 2.0 ** -24 - np.abs(z) * 2.0 ** -149
+    assert off.max() <= 0, (z.ravel()[off.argmax()], got.ravel()[off.argmax()], want.ravel()[off.argmax()])
+    a_in[0, 0, 0] = float("nan")
+    run()
+    again = d_gate.double().cpu().numpy() * 2.0 ** -40
+    assert np.all(np.isnan(again[:, 0])) and np.array_equal(again[:, 1:], got[:, 1:])
+
+
 @pytest.mark.parametrize("name", ["tiny", "bf16_noise", "bf16_n32"])
 def test_route_backward_any_gates(name):
     """The formula of uoe_route_backward holds for whatever gates a caller hands over, not only for rows that sum to one."""
