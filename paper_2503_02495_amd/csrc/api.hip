@@ -118,7 +118,7 @@ UomeBwdWs uome_bwd_ws(const uoe_block_desc *d)
         if (d->width > 2048 && d->dtype == UOE_BF16) {   // rows of (hi, lo) pairs longer than the kernel rewrites in place
             w.h_op = w.total; w.dz_op = w.total + act32; w.total += 2 * act32;
         }
-        // weight gradients: chunks of 128 samples x ranges of the token axis (at most 8) until about 4096 tiles of
+        // weight gradients: chunks of 128 samples x parts of an average expert's list (at most 8) until about 4096 tiles of
         // 64x64 exist, a few rounds of them per CU; partial tiles in fp32, added in order
         const long tiles = 2L * d->n * ((d->d + 63) / 64) * ((d->width + 63) / 64);
         const int chunks = (d->b + 127) / 128;

@@ -217,7 +217,7 @@ template <typename T> struct UomeBwdDu : PlainEpilogue {
 
 // Weight gradients: dA^O_i [d_e, d] = sum H_{b,s}^T d_out_b (set 0), (dA^I_i)^T [d_e, d] = sum dZ_{b,s}^T u_b (set 1)
 // over the (sample, slot) pairs of expert i, both operands token-major ([k][m] and [k][n]), in parts of the expert's list of ranges of
-// tokens (WgradPlan; a whole pair is one range where there are many).  A K segment costs its lookups and
+// tokens (uome_any_wgrad; whole pairs where there are many).  A K segment costs its lookups and
 // addresses once, so long ones pay: 128 samples of 196 tokens in 8 parts of pairs instead of 32 tokens 150 -> 103 us.
 template <typename T> struct UomeBwdWgrad : PlainEpilogue {
     typedef typename storage_elem<T>::type Elem;
@@ -332,6 +332,7 @@ template <typename T> __global__ __launch_bounds__(256) void uome_bwd_any_mid(Uo
 
 template <typename T> hipError_t uome_backward_any(const UomeBwdArgs &a, hipStream_t st)
 {
+    if (a.wgrad.parts > WGRAD_MAX_PARTS) return hipErrorInvalidValue;
     const int W = a.k * a.d_e;
     hipError_t err;
     const T *u = static_cast<const T *>(a.u), *a_in = static_cast<const T *>(a.a_in), *a_out = static_cast<const T *>(a.a_out);
@@ -901,6 +902,7 @@ template <typename T> struct SmhaBwdWgrad : PlainEpilogue {
 
 template <typename T> hipError_t smha_backward_any(const SmhaBwdArgs &a, hipStream_t st)
 {
+    if (a.wgrad.parts > WGRAD_MAX_PARTS) return hipErrorInvalidValue;
     const SmhaArgs &f = a.f;
     const int l_p = f.l / f.m, l_a = f.c * l_p, units = f.b * f.k, dh = f.d_h;
     hipError_t err;

@@ -549,10 +549,11 @@ template <bool CHUNKED, bool MAY_DEAL> struct WgradOrder {
     Divider parts, eighth, each;   // (five divisions one behind the other were half a microsecond at the start of a short launch)
     WgradOrder() = default;
     WgradOrder(int sets, int by_, const WgradPlan &w_, int32_t *part_end_)
-        : sets_log2(sets == 4 ? 2 : 1), by(w_.each ? IN_ORDER : by_), w(w_), part_end(part_end_), parts(w_.parts), eighth((sets * w_.chunks * w_.parts + 7) / 8),
+        : sets_log2(sets == 4 ? 2 : 1), by(w_.each || (by_ == BY_SAMPLE && w_.parts > 256) ? IN_ORDER : by_), w(w_), part_end(part_end_), parts(w_.parts), eighth((sets * w_.chunks * w_.parts + 7) / 8),
           each(w_.each ? w_.each : 1) {}
     int groups() const { const int g = (w.chunks * w.parts) << sets_log2; return by == DEALT ? (g + 7) / 8 * 8 : g; }
-    // set in bits 0-1, place in bits 2-14 (at most 32 experts x 128 parts), chunk above
+    // Set in bits 0-1, place in bits 2-14, chunk above: up to WGRAD_MAX_PARTS parts a chunk.  Lists of patches come to that many, n x c of them, with 128 samples of
+    // which each part holds 128 entries; n x m <= 8192 is what the entry points accept.
     __device__ int decode(int g) const
     {
         if (CHUNKED && w.chunks > 1) {
@@ -583,7 +584,7 @@ struct PartList {
     int32_t end[32];
     int16_t slot_of[128];
     int32_t found;
-    // first item of a part (at most 2^17 items and 2^12 parts; 64-bit divisions took 2 us here)
+    // first item of a part (at most 2^17 items and 2^13 parts; 64-bit divisions took 2 us here)
     static __device__ int begin_of(int items, int part, int parts) { return (int)((uint32_t)items * (uint32_t)part / (uint32_t)parts); }
     // false: no such part; else g's place becomes the part's id.  Ends on a barrier.
     template <typename ORDER> __device__ bool fill(const int32_t *expert_idx, int nb, int kact, int n, const ORDER &o, int &g, int tid, int &expert, int &first, int &last)
@@ -615,9 +616,9 @@ struct PartList {
         const int total = __builtin_amdgcn_readlane(scan.behind, 31), q = o.place(g);
         if (q == 0 && o.set(g) == 0 && tid < 32) o.part_end[o.chunk(g) * 32 + tid] = scan.behind;
         int mine = q;
-        if (o.by != BY_SAMPLE || total > 256) {
+        if (o.by != BY_SAMPLE) {
             if (q >= total) return false;
-        } else {   // the places that hold a part are spread evenly
+        } else {   // (at most 256 parts) the places that hold a part are spread evenly
             const int rank = begin_of(total, q, w.parts);
             if (begin_of(total, q + 1, w.parts) == rank) return false;
             if (tid < 32) end[tid] = scan.behind;

@@ -473,6 +473,7 @@ hipError_t launch_smha_backward(const SmhaBwdArgs &a_in, hipStream_t st)
     const SmhaArgs &f = a.f;
     const int l_p = f.l / f.m, l_a = f.c * l_p, units = f.b * f.k, dh = f.d_h;
     hipError_t err;
+    if (a.wgrad.parts > WGRAD_MAX_PARTS) return hipErrorInvalidValue;
 
     // forward intermediates: q (scaled for the base-2 softmax), k, v, ungated o = hi + lo, lse
     if (!a.kept && (err = launch_smha_qkv_attention(f, st)) != hipSuccess) return err;
@@ -541,7 +542,7 @@ hipError_t launch_smha_backward(const SmhaBwdArgs &a_in, hipStream_t st)
     else {
         if (l_p <= 32) err = launch_gemm_dma<SmhaDxProblem<T, 1>, 32, 128, 32, 1, 4, 4, 2, GEMM_B_NK>(xp, f.b * f.m, l_p, f.d, st);
         else err = launch_gemm_dma<SmhaDxProblem<T, 1>, 64, 128, 32, 2, 2, 4, 2, GEMM_B_NK>(xp, f.b * f.m, l_p, f.d, st);
-        if (err == hipSuccess) err = launch_gemm_dma_auto<GEMM_A_KM>(wp, groups, dh, f.d, (long)a.wgrad.lo * l_p, l_p, st);
+        if (err == hipSuccess) err = launch_gemm_dma_auto<GEMM_A_KM>(wp, groups, dh, f.d, 0, l_p, st);
     }
     if (err != hipSuccess) return err;
     WgradReduceArgs ra{};

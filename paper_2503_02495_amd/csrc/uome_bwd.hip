@@ -239,6 +239,7 @@ hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st);
 hipError_t launch_uome_backward(const UomeBwdArgs &a, hipStream_t st)
 {
     typedef bf16_t T;
+    if (a.wgrad.parts > WGRAD_MAX_PARTS) return hipErrorInvalidValue;
     if (a.patch_idx) return launch_uome_ds_backward(a, st);
     hipError_t err;
     const int width = a.k * a.d_e;
@@ -279,7 +280,7 @@ hipError_t launch_uome_backward(const UomeBwdArgs &a, hipStream_t st)
         typedef GemmTile<WgradProblem<T>, 128, 128, 64, 2, 2, 2, GEMM_A_KM> Wg;
         err = launch_gemm_dma_pair<Wg, Du, 2>(wp, groups, a.d_e, a.d, up, a.b, a.l, a.d, st);
     } else if ((err = launch_gemm_dma_auto<GEMM_B_NK>(up, a.b, a.l, a.d, width, a.d_e, st)) == hipSuccess)
-        err = launch_gemm_dma_auto<GEMM_A_KM>(wp, groups, a.d_e, a.d, (long)a.wgrad.lo * kseg, kseg, st);
+        err = launch_gemm_dma_auto<GEMM_A_KM>(wp, groups, a.d_e, a.d, 0, kseg, st);
     if (err != hipSuccess) return err;
     WgradReduceArgs ra{};
     ra.partial = a.partial; ra.n = a.n; ra.M = a.d_e; ra.N = a.d;
@@ -407,7 +408,7 @@ hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st)
     else {
         if (l_p <= 32) err = launch_gemm_dma<OutProjProblem<T>, 32, 128, 32, 1, 4, 4, 2, GEMM_B_NK>(xp, a.b * a.m, l_p, a.d, st);
         else err = launch_gemm_dma<OutProjProblem<T>, 64, 128, 32, 2, 2, 4, 2, GEMM_B_NK>(xp, a.b * a.m, l_p, a.d, st);
-        if (err == hipSuccess) err = launch_gemm_dma_auto<GEMM_A_KM>(wp, groups, a.d_e, a.d, (long)a.wgrad.lo * l_p, l_p, st);
+        if (err == hipSuccess) err = launch_gemm_dma_auto<GEMM_A_KM>(wp, groups, a.d_e, a.d, 0, l_p, st);
     }
     if (err != hipSuccess) return err;
     WgradReduceArgs ra{};

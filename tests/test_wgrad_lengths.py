@@ -12,18 +12,22 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 SHIM = """
 #include "wgrad_plan.h"
 static void give(const uoe::WgradPlan &w, int *o) { o[0] = w.chunks; o[1] = w.items; o[2] = w.parts; o[3] = w.lo; o[4] = w.hi; o[5] = w.each; }
-extern "C" void any_plan(int b, int l, int n, int k, int s, int f32, int *o) { give(uoe::uome_any_wgrad(b, l, 8, n, k, s, f32 != 0), o); o[6] = uoe::uome_any_range(l, o[1]); }
+extern "C" void any_plan(int b, int l, int d, int n, int k, int s, int f32, int *o) { give(uoe::uome_any_wgrad(b, l, d, n, k, s, f32 != 0), o); o[6] = uoe::uome_any_range(l, o[1]); }
 extern "C" void grid_plan(int b, int l, int d, int n, int k, int d_e, int *o) { give(uoe::uome_backward_wgrad(b, l, d, n, k, d_e), o); o[6] = l / o[1]; }
 extern "C" void patch_plan(int b, int n, int k, int c, int l_p, int sets, int rows, int cols, int *o) { give(uoe::smha_backward_wgrad(b, n, k, c, l_p, sets, rows, cols), o); }
+extern "C" void any_patch_plan(int b, int n, int k, int c, int l_p, int s, int *o) { give(uoe::wgrad_plan(b, n, k, s, c, 1024, (long)c * l_p, 0), o); }
 """
+
+
+def build(d):
+    (d / "shim.cc").write_text(SHIM)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC, str(d / "shim.cc"), "-o", str(d / "shim.so")], check=True)
+    return ctypes.CDLL(str(d / "shim.so"))
 
 
 @pytest.fixture(scope="module")
 def shim(tmp_path_factory):
-    d = tmp_path_factory.mktemp("plan")
-    (d / "shim.cc").write_text(SHIM)
-    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC, str(d / "shim.cc"), "-o", str(d / "shim.so")], check=True)
-    return ctypes.CDLL(str(d / "shim.so"))
+    return build(tmp_path_factory.mktemp("plan"))
 
 
 def call(fn, *args):
@@ -68,7 +72,7 @@ ANY = [(8, 512, 8, 4, 8), (4, 770, 5, 2, 8), (6, 1000, 6, 3, 7), (10, 500, 5, 2,
 @pytest.mark.parametrize("b,l,n,k,s", ANY)
 def test_any_shape(shim, b, l, n, k, s, f32):
     """K-steps are 32 tokens, a segment's lookups cost as much as 16 (4 in fp32)."""
-    plan, lookup = call(shim.any_plan, b, l, n, k, s, f32), 4 if f32 else 16
+    plan, lookup = call(shim.any_plan, b, l, 8, n, k, s, f32), 4 if f32 else 16
     assert plan["parts"] == n * s
     lengths = np.minimum(plan["range"], l - np.arange(plan["items"]) * plan["range"])
     assert lengths.min() > 0 and lengths.sum() == l and (plan["items"] == 1 or plan["range"] % 32 == 0)
@@ -88,7 +92,7 @@ def test_any_shape(shim, b, l, n, k, s, f32):
 @pytest.mark.parametrize("b,l,n,k,s", [(3, 4400, 4, 2, 8), (2, 30000, 5, 2, 8), (9, 1364, 16, 5, 4), (16, 1504, 16, 6, 4), (12, 2500, 4, 1, 8)])
 def test_equal_parts_are_used(shim, b, l, n, k, s):
     """Parts that stay empty make the others, and the fp32 sums along them, longer."""
-    plan = call(shim.any_plan, b, l, n, k, s, 0)
+    plan = call(shim.any_plan, b, l, 8, n, k, s, 0)
     rng = np.random.default_rng(l)
     for _ in range(20):
         for counts in selections(rng, b, n, k):
@@ -118,3 +122,21 @@ def test_picked_patches_fill_the_last_round(shim, b, l, n, k, c, m, width, d, se
     plan = call(shim.patch_plan, b, n, k, c, l // m, sets, width, d)
     tiles = sets * plan["parts"] * -(-width // 128) * -(-d // 128)
     assert tiles <= 128 or tiles % 256 == 0 or tiles % 256 >= 192 or plan["parts"] >= n * min(8, b * k * c // n // 8)
+
+
+def test_parts_fit_the_groups_coding(shim):
+    """At most 8192 parts a chunk (13 bits), 256 where they are placed by sample: all sizes that the entry points accept (n * m <= 8192, n <= 32, b * m and b * k <= 65535)."""
+    rng, most = np.random.default_rng(3), 0
+    for _ in range(20000):
+        n = int(rng.integers(1, 33))
+        m = min(8192 // n, 1024)
+        c, b = (m, min(65535 // m, 128)) if rng.random() < 0.3 else (int(rng.integers(1, m + 1)), int(rng.integers(1, 129)))
+        k, d, w, l = int(rng.integers(1, n + 1)), 8 * int(rng.integers(1, 200)), 8 * int(rng.integers(1, 33)), int(2 ** rng.uniform(5, 16))
+        parts = call(shim.patch_plan, b, n, k, c, 32, int(rng.choice([2, 4])), w, d)["parts"]
+        most = max(most, parts)
+        assert parts <= 8192, (b, n, k, c)
+        plan = call(shim.grid_plan, b, l // 32 * 32, d, n, k, w)
+        any_plan = call(shim.any_plan, b, l, d, n, k, int(rng.integers(1, 9)), int(rng.integers(0, 2)))
+        assert plan["parts"] <= 256 and any_plan["parts"] <= 256, (b, l, d, n, k, w)
+        assert (min(b, 128) - 1) * any_plan["items"] < 1 << 24 and any_plan["items"] <= 1024   # keys and contexts
+    assert most >= 4096
