@@ -12,7 +12,7 @@ SHAPES = {"rows": (2, 8224, 1024), "columns": (2, 8192, 1056)}   # b, l, d: at l
 N, K, D_E = 5, 4, 256
 
 
-def make(b, l, d, flags):
+def make(b, l, d, flags, D_E=D_E):
     gen = torch.Generator(device="cuda").manual_seed(l + d + flags)
     t = {name: (torch.randn(shape, generator=gen, device="cuda") * std).bfloat16() for name, shape, std in (
         ("u", (b, l, d), 1.0), ("d_out", (b, l, d), 1.0), ("hidden", (b, l, K * D_E), 0.5), ("a_in", (N, d, D_E), 0.03), ("a_out", (N, D_E, d), 0.03))}
@@ -44,9 +44,12 @@ def test_down(name, flags, once, monkeypatch):
         close(out[s], want + t["u"][s].float() if flags else want, f"sample {s}")
 
 
-@pytest.mark.parametrize("name", list(SHAPES))
-def test_backward(name):
-    desc, t, idx, gate = make(*SHAPES[name], R | GE)
+# dH fetches Z: on 256 x 256 tiles with d a multiple of 64; "z_columns": 4 x 288 columns of Z end inside the fifth of them, 32 rows past the last tile too
+@pytest.mark.parametrize("once", [False, True])
+@pytest.mark.parametrize("name", ["rows", "columns", "z_columns"])
+def test_backward(name, once, monkeypatch):
+    monkeypatch.setenv("UOE_STREAM_ONCE_MIN_BYTES", "0" if once else "1e18")
+    desc, t, idx, gate = make(*SHAPES.get(name, SHAPES["rows"]), R | GE, 288 if name == "z_columns" else D_E)
     grads = [torch.full_like(t[k], float("nan")) for k in ("u", "a_in", "a_out")]
     d_gate = torch.full_like(gate, float("nan"))
     ws = torch.empty(B.uome_backward_workspace_bytes(desc), dtype=torch.uint8, device="cuda")

@@ -180,8 +180,11 @@ ROUTE_BWD = {
     # samples shared by eight lanes of dW_E (b >= 8), second expert tile, two column slices, the last one short
     "rb_n17": P.small(b=9, l=65, d=264, n_a=17, d_h=8, m=65, c=2, k_a=2, n_m=2, d_e=8, k_m=1, dtype=BF),
     "rb_f32_n32": P.small(b=13, l=66, d=264, n_a=32, d_h=8, m=33, c=2, k_a=2, n_m=2, d_e=8, k_m=1),
-    # eight samples per d_x thread (256 column chunks and more), the last group of one; chunks of more than one tile
+    # four samples per d_x thread, the last group of one; chunks of more than one tile
     "rb_b9_long": P.small(b=9, l=2100, d=256, n_a=4, d_h=8, m=70, c=2, k_a=2, n_m=2, d_e=8, k_m=1, dtype=BF),
+    # eight samples per d_x thread (b > 4, n <= 16, W_E of 3 * 2^23 elements and more), the last group of one or three
+    "rb_b9_eight": P.small(b=9, l=2100, d=1024, n_a=12, d_h=8, m=70, c=2, k_a=2, n_m=2, d_e=8, k_m=1, dtype=BF),
+    "rb_f32_eight": P.small(b=11, l=3300, d=640, n_a=12, d_h=8, m=60, c=2, k_a=2, n_m=2, d_e=8, k_m=1),
     # 2048 columns: eight slices
     "rb_d2048": P.small(b=2, l=40, d=2048, n_a=5, d_h=8, m=8, c=2, k_a=2, n_m=2, d_e=8, k_m=1, dtype=BF),
 }
