@@ -329,27 +329,18 @@ __device__ __forceinline__ void route_fold(const RouteArgs &a, int chunk, int bb
 // they only feed output columns that are never read), in blocks of 8 rows with a pad after each block
 // (128 bytes for 32-byte rows, 32 bytes for 64-byte rows) so that the row groups of the four k-slices
 // of a transposing read fall into different banks.  Row e starts at (e/8)*BLK + (e%8)*ROWB.
-template <int NP, int NTHREADS, bool BATCHED = true>
+template <int NP, int NTHREADS>
 __device__ __forceinline__ void stage_w_b(const RouteArgs &a, unsigned char *wb)
 {
     constexpr int ROWB = NP * 2, BLK = 8 * ROWB + (NP == 16 ? 128 : 32);
     const int tid = threadIdx.x, n = a.n, d = a.d;
     const uint16_t *w_b = static_cast<const uint16_t *>(a.w_b);
     // the widest piece that never straddles a row; several of them a thread in flight together (a loop's remainder, one at a time, waits
-    // out a memory round trip each).  Not BATCHED: behind transfers to LDS that are awaited in order anyway (the streaming kernel: 4 x 8192 x 1024, n 16,
-    // m 128, 94.2 us for the whole routing, 96.3 in batches; 8 x 8192 x 512 49.2 and 50.2)
+    // out a memory round trip each)
     auto stage = [&](auto piece, int pr) __attribute__((always_inline)) {   // pr pieces a row
         typedef decltype(piece) P;
         constexpr int BATCH = sizeof(P) == 16 ? 4 : 8;
         const int pieces = d * pr;
-        if constexpr (!BATCHED) {
-#pragma unroll 4
-            for (int idx = tid; idx < pieces; idx += NTHREADS) {
-                const int e = idx / pr;
-                *reinterpret_cast<P *>(wb + (e >> 3) * BLK + (e & 7) * ROWB + (idx - e * pr) * (int)sizeof(P)) = reinterpret_cast<const P *>(w_b)[idx];
-            }
-            return;
-        }
         // piece / pr by the reciprocal rounded up: exact below 2^16 pieces (d * n <= 24576)
         const uint32_t inv = pr > 1 ? 0xFFFFFFFFu / (uint32_t)pr + 1u : 0u;
         for (int i0 = tid; i0 < pieces; i0 += BATCH * NTHREADS) {
@@ -366,6 +357,39 @@ __device__ __forceinline__ void stage_w_b(const RouteArgs &a, unsigned char *wb)
     if ((n & 7) == 0) stage(once_u32x4{}, n >> 3);
     else if ((n & 1) == 0) stage(uint32_t{}, n >> 1);
     else stage(uint16_t{}, n);
+}
+
+// The same for the streaming kernel, once in a long workgroup and behind its first transfers to LDS, where batches gain nothing.  Two other forms
+// of these loops, a few instructions shorter, cost that kernel 2 % (4 x 8192 x 1024, n 16, m 128: 94.3 us for the whole routing, 96.2;
+// 8 x 8192 x 512 49.5 and 50.3): its main loop has the same instructions then, but lies otherwise across the lines of the instruction cache.
+template <int NP, int NTHREADS>
+__device__ __forceinline__ void stage_w_b_loop(const RouteArgs &a, unsigned char *wb)
+{
+    constexpr int ROWB = NP * 2, BLK = 8 * ROWB + (NP == 16 ? 128 : 32);
+    const int tid = threadIdx.x, n = a.n, d = a.d;
+    const uint16_t *w_b = static_cast<const uint16_t *>(a.w_b);
+    auto row_at = [&](int e) { return wb + (size_t)(e >> 3) * BLK + (e & 7) * ROWB; };
+    if ((n & 7) == 0) {  // 16-byte pieces never straddle a row
+        const int pr = n >> 3;
+#pragma unroll 4
+        for (int idx = tid; idx < d * pr; idx += NTHREADS) {
+            const int e = idx / pr, pc = idx - e * pr;
+            *reinterpret_cast<uint4 *>(row_at(e) + pc * 16) = *reinterpret_cast<const uint4 *>(w_b + (size_t)idx * 8);
+        }
+    } else if ((n & 1) == 0) {
+        const int pr = n >> 1;
+#pragma unroll 4
+        for (int idx = tid; idx < d * pr; idx += NTHREADS) {
+            const int e = idx / pr, pc = idx - e * pr;
+            *reinterpret_cast<uint32_t *>(row_at(e) + pc * 4) = *reinterpret_cast<const uint32_t *>(w_b + (size_t)idx * 2);
+        }
+    } else {
+#pragma unroll 4
+        for (int idx = tid; idx < d * n; idx += NTHREADS) {
+            const int e = idx / n, i = idx - e * n;
+            *reinterpret_cast<uint16_t *>(row_at(e) + i * 2) = w_b[idx];
+        }
+    }
 }
 
 // Data router (Eq. 13), bf16, MFMA.  Workgroup = four waves = a.tc_d tokens of one sample, 64 at a time (16 per wave), or KS = 4: 16
@@ -761,7 +785,7 @@ __global__ __launch_bounds__(256) void route_stream_kernel(RouteArgs a, int ipw,
 #pragma unroll
     for (int s = 0; s < STAGES - 1; ++s)
         if (s < nst) issue(s, s);
-    if (HAS_D) stage_w_b<NP, 256, false>(a, wb);
+    if (HAS_D) stage_w_b_loop<NP, 256>(a, wb);
 
     rt_f32x4 accz[RT][CT], acct[RT][CT];
 #pragma unroll
