@@ -9,12 +9,13 @@ namespace uoe {
 // Experts are not selected equally often: with the same number of parts for each the launch took as long as the most popular one
 // (4 x 8192 tokens, 8 of 16 experts of 1024 x 256: 352 us, 255 to 268 with equal parts).
 // Finding them takes 1 to 2 us (more off the 32-grid, where the order by samples goes with it and pairs are cut finer), so experts keep one number of
-// parts (`each`) unless equal ones are shorter by 256 tokens (384) than those of an expert with a standard deviation more pairs than the
-// average (68 x 200 x 352, one of 7 experts of 56, 250 and 350 tokens: 52.1 us for the MLP's backward, 49.2 with one number; 18 x 1680 x 288, one of 10
-// of 144, 378 and 840: 97.9 and 112).  With 20 pairs and more an expert lists hardly differ (128 samples, 3 of 6 experts: within 10 %; 96 us
-// became 112 and 99 in the two orders there are for unequal parts), with half a one and less a few experts have all parts, which the reduction adds
-// one after the other (1 x 5040 x 120, one of 6 of 200: 50.6 and 54.7).  Several experts that share the rows of a large tensor have equal parts, whose order
-// brings those rows together, from 256 tokens a part on (13 x 3712 x 768, 3 of 9 experts of 32: 130 and 151; 21 x 1664 x 800, 6 of 13 of 64: 211 and 220).
+// parts (`each`) unless equal ones are shorter by 256 tokens (384 off the grid, 192 in lists of patches) than those of an expert with a standard
+// deviation more pairs than the average (68 x 200 x 352, one of 7 experts of 56, 250 and 350 tokens: 52.1 us for the MLP's backward, 49.2 with one
+// number; 18 x 1680 x 288, one of 10 of 144, 378 and 840: 97.9 and 112; patches 8 x 512 x 512, 4 of 8 of 256, 544 and 768: 47.7 and 48.4).  With 20 pairs
+// and more an expert lists hardly differ (128 samples, 3 of 6 experts: within 10 %; 96 us became 112 and 99 in the two orders there are for
+// unequal parts), with half a one and less a few experts have all parts, which the reduction adds one after the other (1 x 5040 x 120, one of 6 of 200:
+// 50.6 and 54.7).  Several experts that share the rows of a large tensor have equal parts, whose order brings those rows together, from 256 tokens a
+// part on (13 x 3712 x 768, 3 of 9 experts of 32: 130 and 151; 21 x 1664 x 800, 6 of 13 of 64: 211 and 220).
 // `per` is the least for which no more than `parts` parts come of it, found by every workgroup from the selection (PartScan).
 constexpr int WGRAD_MAX_PARTS = 8192;   // of a chunk: what a launch's groups are coded for
 struct WgradPlan {
@@ -91,7 +92,7 @@ inline WgradPlan smha_backward_wgrad(int b, int n, int k, int c, int l_p, int se
     long s = avg / 8, most = tiles >= 128 ? 2 : (256 + tiles - 1) / tiles;
     s = s < 1 ? 1 : (s > 8 ? 8 : s);
     while (tiles < 128 && most < s && (tiles * most - 1) % 256 < 191) ++most;
-    return wgrad_plan(b, n, k, (int)(s < most ? s : most), c, 128, (long)c * l_p, 0);
+    return wgrad_plan(b, n, k, (int)(s < most ? s : most), c, 128, (long)c * l_p, 0, 0, 192);
 }
 
 // Expert-selection UoME of any shape or in fp32, `splits` parts an average expert.  Tokens of an item, a pair being cut into `items`
