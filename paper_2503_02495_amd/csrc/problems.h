@@ -493,7 +493,7 @@ __device__ __forceinline__ void expert_masks(uint64_t (*mask)[2], int (&idx)[KEP
 }
 
 // Where an expert's parts lie among a chunk's part ids (lane e of a wave holds expert e's; n <= 32), `each` being 0.  Each lane tries one value
-// of `per`, and the least one that fits the budget is taken.
+// of `per` from lo to hi, every one where there are at most 64 and equally spaced ones (hi among them) otherwise; the least that fits the budget is taken.
 struct PartScan {
     int count, parts, behind;   // selecting samples; parts; first id behind them
     __device__ PartScan(const uint64_t (*mask)[2], const WgradPlan &w, int n, int lane)

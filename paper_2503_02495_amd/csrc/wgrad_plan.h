@@ -16,12 +16,13 @@ namespace uoe {
 // unequal parts), with half a one and less a few experts have all parts, which the reduction adds one after the other (1 x 5040 x 120, one of 6 of 200:
 // 50.6 and 54.7).  Several experts that share the rows of a large tensor have equal parts, whose order brings those rows together, from 256 tokens a
 // part on (13 x 3712 x 768, 3 of 9 experts of 32: 130 and 151; 21 x 1664 x 800, 6 of 13 of 64: 211 and 220).
-// `per` is the least for which no more than `parts` parts come of it, found by every workgroup from the selection (PartScan).
+// `per` is the least, of up to 64 values evenly between `lo` and `hi`, for which no more than `parts` parts come of it: every workgroup finds it
+// from the selection (PartScan).
 constexpr int WGRAD_MAX_PARTS = 8192;   // of a chunk: what a launch's groups are coded for
 struct WgradPlan {
     int chunks, items, parts;
     int lo, hi;        // bounds of `per`: all parts full; feasible for any selection
-    int each;          // not 0: an expert has so many parts, whatever its list (experts with many pairs: their lists hardly differ)
+    int each;          // not 0: an expert has so many parts, whatever its list
 };
 // the average number of pairs an expert, and a standard deviation more (each rounded up)
 inline long wgrad_pairs(long pairs, int n) { return (pairs + n - 1) / n; }
