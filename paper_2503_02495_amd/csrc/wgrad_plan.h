@@ -86,13 +86,15 @@ inline WgradPlan smha_backward_wgrad(int b, int n, int k, int c, int l_p, int se
 {
     // parts of an average expert's (unit, pick) list: about 8 segments each, and at most 8 parts; not more than two where 256 tiles
     // of 128 x 128 come of it, a part's fp32 tiles being written and read again (4 x 8192 tokens, 16 experts of 64 x 1024: 4 parts
-    // 66 us and 16 for the reduction, 2 parts 54 and 12; 8 x 512, 8 of 256 x 512: 27 and 23); fewer tiles: until the compute units' last round is
-    // three quarters full (14 x 2688, 12 of 128 x 160, 96 tiles: three parts, 32 tiles in a second round, 37 us and 8; eight 28 and 9)
+    // 66 us and 16 for the reduction, 2 parts 54 and 12; 8 x 512, 8 of 256 x 512: 27 and 23); fewer tiles: SMHA's heads of 128, whose launch is then one of
+    // its own, until the compute units' last round is three quarters full (14 x 2688, 12 of 128 x 160, 96 tiles: three parts, 32 tiles in a second round, 37 us
+    // and 8; eight 28 and 9).  The others share the launch with d_x's tiles or have tiles of 64 rows, four to a unit (10 x 1568, 11 of 32 x 64, 44 tiles:
+    // six parts 14.5 us, eight 16.0)
     const int avg = (int)(((long)b * k * c + n - 1) / n);
     const long tiles = (long)sets * n * ((rows + 127) / 128) * ((cols + 127) / 128);
     long s = avg / 8, most = tiles >= 128 ? 2 : (256 + tiles - 1) / tiles;
     s = s < 1 ? 1 : (s > 8 ? 8 : s);
-    while (tiles < 128 && most < s && (tiles * most - 1) % 256 < 191) ++most;
+    while (sets == 4 && rows > 64 && tiles < 128 && most < s && (tiles * most - 1) % 256 < 191) ++most;
     return wgrad_plan(b, n, k, (int)(s < most ? s : most), c, 128, (long)c * l_p, 0, 0, 192);
 }
 

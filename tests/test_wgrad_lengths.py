@@ -116,12 +116,17 @@ def test_on_the_32_grid(shim, b, l, d, n, k, d_e):
             assert longest(plan, np.full(plan["items"], plan["range"]), counts) <= counts.max() * (l // axis), (plan, counts)
 
 
-@pytest.mark.parametrize("b,l,n,k,c,m,width,d,sets", [(14, 2688, 12, 5, 19, 84, 128, 160, 4), (6, 4096, 8, 4, 32, 128, 64, 256, 4), (9, 3072, 5, 3, 20, 96, 96, 384, 4), (4, 4096, 3, 2, 32, 64, 64, 640, 4)])
-def test_picked_patches_fill_the_last_round(shim, b, l, n, k, c, m, width, d, sets):
-    """128 x 128 tiles on 256 compute units: a second round for a few tiles takes as long as a full one."""
+@pytest.mark.parametrize("b,l,n,k,c,m,width,d,sets,own", [(14, 2688, 12, 5, 19, 84, 128, 160, 4, True), (6, 4096, 8, 4, 32, 128, 128, 256, 4, True), (9, 3072, 5, 3, 20, 96, 128, 384, 4, True),
+                                                           (4, 4096, 3, 2, 32, 64, 128, 640, 4, True), (10, 1568, 11, 5, 16, 49, 32, 64, 4, False), (14, 2688, 12, 5, 19, 84, 96, 160, 2, False)])
+def test_picked_patches_fill_the_last_round(shim, b, l, n, k, c, m, width, d, sets, own):
+    """128 x 128 tiles on 256 compute units: a second round for a few tiles takes as long as a full one, unless d_x's tiles share the launch."""
     plan = call(shim.patch_plan, b, n, k, c, l // m, sets, width, d)
-    tiles = sets * plan["parts"] * -(-width // 128) * -(-d // 128)
-    assert tiles <= 128 or tiles % 256 == 0 or tiles % 256 >= 192 or plan["parts"] >= n * min(8, b * k * c // n // 8)
+    an_expert = sets * n * -(-width // 128) * -(-d // 128)
+    tiles = an_expert * plan["parts"] // n
+    if own:
+        assert tiles <= 128 or tiles % 256 == 0 or tiles % 256 >= 192 or plan["parts"] >= n * min(8, b * k * c // n // 8)
+    else:
+        assert 256 <= tiles < 256 + an_expert, plan
 
 
 def test_parts_fit_the_groups_coding(shim):
