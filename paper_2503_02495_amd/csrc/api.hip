@@ -209,7 +209,7 @@ SmhaBwdWs smha_bwd_ws(const uoe_block_desc *d)
         const long avg = ((long)d->b * d->k * d->c / chunks + d->n - 1) / d->n;
         long parts = avg / 8;
         parts = wgrad_parts(d->dtype == UOE_F32, 4 * chunks, d->n, d->width, d->d, parts < 1 ? 1 : (parts > 8 ? 8 : parts));
-        w.wgrad = wgrad_plan(d->b, d->n, d->k, (int)parts, d->c, BWD_ANY_SEGMENTS, (long)d->c * (d->l / d->m), 0);
+        w.wgrad = smha_any_wgrad(d->b, d->n, d->k, d->c, d->l / d->m, (int)parts, BWD_ANY_SEGMENTS);
         w.partial = off;
         off += up((size_t)4 * chunks * w.wgrad.parts * d->d * d->width * sizeof(float));
         w.part_end = off; off += up((size_t)chunks * 32 * sizeof(int32_t));

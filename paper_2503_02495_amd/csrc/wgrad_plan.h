@@ -9,7 +9,7 @@ namespace uoe {
 // Experts are not selected equally often: with the same number of parts for each the launch took as long as the most popular one
 // (4 x 8192 tokens, 8 of 16 experts of 1024 x 256: 352 us, 255 to 268 with equal parts).
 // Finding them takes 1 to 2 us (more off the 32-grid, where the order by samples goes with it and pairs are cut finer), so experts keep one number of
-// parts (`each`) unless equal ones are shorter by 256 tokens (384 off the grid, 192 in lists of patches) than those of an expert with a standard
+// parts (`each`) unless equal ones are shorter by 256 tokens (384 off the grid; lists of patches 192, off the grid 128) than those of an expert with a standard
 // deviation more pairs than the average (68 x 200 x 352, one of 7 experts of 56, 250 and 350 tokens: 52.1 us for the MLP's backward, 49.2 with one
 // number; 18 x 1680 x 288, one of 10 of 144, 378 and 840: 97.9 and 112; patches 8 x 512 x 512, 4 of 8 of 256, 544 and 768: 47.7 and 48.4).  With 20 pairs
 // and more an expert lists hardly differ (128 samples, 3 of 6 experts: within 10 %; 96 us became 112 and 99 in the two orders there are for
@@ -97,6 +97,11 @@ inline WgradPlan smha_backward_wgrad(int b, int n, int k, int c, int l_p, int se
     while (sets == 4 && rows > 64 && tiles < 128 && most < s && (tiles * most - 1) % 256 < 191) ++most;
     return wgrad_plan(b, n, k, (int)(s < most ? s : most), c, 128, (long)c * l_p, 0, 0, 192);
 }
+
+// SMHA of any shape or in fp32, `splits` parts an average expert of at most `cap` (unit, pick) entries.  A token of (hi, lo) pairs or of split
+// products takes twice as long (57 x 840 x 352, one of 12 experts of 32 x 24 patches, three selections: contraction 28.8 us with equal parts and 34 to 36
+// without, the backward pass 136 to 137 and 139 to 145; 10 x 817 x 72 207 to 211 and 213 to 219; threshold 96: 273 random calls 0.02 % faster)
+inline WgradPlan smha_any_wgrad(int b, int n, int k, int c, int l_p, int splits, int cap) { return wgrad_plan(b, n, k, splits, c, cap, (long)c * l_p, 0, 0, 128); }
 
 // Expert-selection UoME of any shape or in fp32, `splits` parts an average expert.  Tokens of an item, a pair being cut into `items`
 inline int uome_any_range(int l, int items) { return items == 1 ? l : ((l + items - 1) / items + 31) / 32 * 32; }

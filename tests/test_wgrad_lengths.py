@@ -15,7 +15,7 @@ static void give(const uoe::WgradPlan &w, int *o) { o[0] = w.chunks; o[1] = w.it
 extern "C" void any_plan(int b, int l, int d, int n, int k, int s, int f32, int *o) { give(uoe::uome_any_wgrad(b, l, d, n, k, s, f32 != 0), o); o[6] = uoe::uome_any_range(l, o[1]); }
 extern "C" void grid_plan(int b, int l, int d, int n, int k, int d_e, int *o) { give(uoe::uome_backward_wgrad(b, l, d, n, k, d_e), o); o[6] = l / o[1]; }
 extern "C" void patch_plan(int b, int n, int k, int c, int l_p, int sets, int rows, int cols, int *o) { give(uoe::smha_backward_wgrad(b, n, k, c, l_p, sets, rows, cols), o); }
-extern "C" void any_patch_plan(int b, int n, int k, int c, int l_p, int s, int *o) { give(uoe::wgrad_plan(b, n, k, s, c, 1024, (long)c * l_p, 0), o); }
+extern "C" void any_patch_plan(int b, int n, int k, int c, int l_p, int s, int *o) { give(uoe::smha_any_wgrad(b, n, k, c, l_p, s, 1024), o); }
 """
 
 
@@ -127,6 +127,13 @@ def test_picked_patches_fill_the_last_round(shim, b, l, n, k, c, m, width, d, se
         assert tiles <= 128 or tiles % 256 == 0 or tiles % 256 >= 192 or plan["parts"] >= n * min(8, b * k * c // n // 8)
     else:
         assert 256 <= tiles < 256 + an_expert, plan
+
+
+@pytest.mark.parametrize("b,n,k,c,l_p,s,equal", [(57, 12, 1, 7, 35, 3, True), (10, 13, 4, 6, 43, 2, True), (9, 5, 2, 7, 37, 3, True), (33, 9, 1, 5, 42, 2, True), (8, 8, 4, 4, 32, 2, False),
+                                                       (4, 4, 2, 3, 15, 3, False), (128, 6, 3, 4, 14, 8, False)])
+def test_any_shape_patches_in_equal_parts(shim, b, n, k, c, l_p, s, equal):
+    """Where an unequal selection makes the longest part 128 tokens and more longer than an equal one; few tokens, or many pairs an expert, are not worth finding them."""
+    assert (call(shim.any_patch_plan, b, n, k, c, l_p, s)["each"] == 0) == equal
 
 
 def test_parts_fit_the_groups_coding(shim):
