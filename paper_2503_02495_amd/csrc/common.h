@@ -188,7 +188,7 @@ struct RouteArgs {
     int b, l, d, n, k, m, c;
     int tc, nchunks;                          // expert router: tokens per chunk, chunks per sample
     int tc_d, nchunks_d;                      // data router: the same
-    float *zpart, *gpart;                     // [nchunks, b, n], [nchunks_d, b, n*m]
+    float *zpart, *gpart;                     // [b, n, nchunks], [nchunks_d, b, n*m]
     float *gred;                              // [b, n*m]
     float *t1;                                // [b, l, n]: per-token expert scores x W_B of the one-pass kernel
     int32_t *expert_idx, *patch_idx;          // outputs (any may be NULL)
@@ -197,6 +197,11 @@ struct RouteArgs {
     int patch_k;                              // experts each patch names in stage 1
     int32_t *capacity;                        // [b]
     float *load_f, *load_p;                   // [b,n] each, or NULL
+};
+// An expert selection that the block's first contraction makes beside its own work (select.h); on 0: it has been launched
+struct RouteSelect {
+    RouteArgs r;
+    int on, has_e;
 };
 
 struct SmhaArgs {
@@ -230,6 +235,7 @@ struct UomeArgs {
     int b, l, d, n, k, d_e;
     uint32_t flags;
     void *hidden;                             // [b, l, k*d_e], storage dtype
+    const RouteSelect *select;                // the block's selection, to be made by the first layer's launch; NULL: it is there
 };
 
 // UoME with patch-wise data selection (Eq. 37-40): routing as for SMHA, hidden per active unit
@@ -328,7 +334,8 @@ struct GatherArgs {
 };
 
 // Launchers: enqueue on `st`, return the runtime's launch status.
-hipError_t launch_route(const RouteArgs &a, bool bf16, hipStream_t st);
+// `beside` not NULL: the block's first contraction can make the selection; where that pays *beside says so and it is not launched
+hipError_t launch_route(const RouteArgs &a, bool bf16, hipStream_t st, RouteSelect *beside = nullptr);
 hipError_t launch_balance_loss(const float *load_f, const float *load_p, float alpha, float *loss, float *d_patch_gate,
                                int b, int n, int m, hipStream_t st);
 hipError_t launch_gather(const GatherArgs &a, bool bf16, hipStream_t st);

@@ -11,6 +11,8 @@
 //   b_stride()                           elements between consecutive K rows of B inside a segment
 //   kPrepare / prepare(g, segtab, scratch, tid, nthreads)  the workgroup builds its segment list itself (scratch: the stage buffers' LDS,
 //                                        behind a last barrier theirs again) and returns K (out-projection: which experts picked this patch); -1: there is no such tile
+//   kSelects / select<NT>(g, tile, scratch, tid)  (optional) the workgroup, `tile` of its group, selects for the group itself first
+//                                        (select.h), in the stage buffers' LDS; NT threads, ends on a barrier
 //   decode(g)                            (optional) what the problem calls the launch's group g
 //   seg_len(ctx), seg_tail(step)         (optional, GEMM_A_KM and GEMM_TAIL) a segment's own length, at most kseg(g), and what the longest tail of one
 //                                        is in a K-step; K is then the sum of the lengths in whole K-steps
@@ -32,6 +34,8 @@
 // 8-element run never straddles two experts.
 #pragma once
 #include "common.h"
+#include "select.h"
+#include <type_traits>
 
 namespace uoe {
 
@@ -318,8 +322,9 @@ template <typename T, int PARTS> struct SmhaDxProblem : OutProjProblem<T> {
 
 // ---------------------------------------------------------------------------------------------
 // UoME Eq. 38: group = sample b; M = l; K = d; N = k*d_e (the sample's active experts side by
-// side); epilogue SiLU and the expert's gate.  EXACT: SiLU by a division also for bf16 storage.
-template <typename T, bool RAW = false, bool EXACT = false> struct UomeUpProblem {
+// side); epilogue SiLU and the expert's gate.  EXACT: SiLU by a division also for bf16 storage.  SEL: the sample's experts and gates come
+// from a selection of the workgroup's own.
+template <typename T, bool RAW = false, bool EXACT = false, bool SEL = false> struct UomeUpProblem {
     typedef typename storage_elem<T>::type Elem;
     bool once = false;   // this launch streams its output (and residual) past the caches: see store16, wave_write_out
     const T *u, *a_in;
@@ -328,6 +333,22 @@ template <typename T, bool RAW = false, bool EXACT = false> struct UomeUpProblem
     T *hidden;                 // [b, l, k*d_e]
     int l, d, n, kact, d_e;
     static constexpr bool raw = RAW;   // true: store the plain product (backward pass), no SiLU, no gate
+    std::conditional_t<SEL, RouteSelect, NoSelect> sel;
+    static constexpr bool kSelects = SEL;
+    __device__ static SelectedExperts &selected()
+    {
+        __shared__ SelectedExperts s;
+        return s;
+    }
+    template <int NT> __device__ void select(int g, int tile, unsigned char *scratch, int tid) const
+    {
+        select_experts_beside<NT>(sel, g, reinterpret_cast<float *>(scratch), selected(), tile == 0, tid);
+    }
+    __device__ int expert(int g, int slot) const
+    {
+        if constexpr (SEL) return clampi(selected().expert[slot], n);
+        else return clampi(expert_idx[g * kact + slot], n);
+    }
 
     __device__ int rows(int) const { return l; }
     __device__ int kdim(int) const { return d; }
@@ -340,8 +361,7 @@ template <typename T, bool RAW = false, bool EXACT = false> struct UomeUpProblem
     __device__ const T *b_ptr_ctx(int g, int, int nn, uint32_t) const
     {
         const int s = nn / d_e;
-        const int i = clampi(expert_idx[g * kact + s], n);
-        return a_in + (size_t)i * d * d_e + (nn - s * d_e);
+        return a_in + (size_t)expert(g, s) * d * d_e + (nn - s * d_e);
     }
     __device__ float epi_f32(float val, float gate) const { return raw ? val : silu(val) * gate; }
     __device__ void put4(int g, int r, int nn, float4 val) const
@@ -354,7 +374,8 @@ template <typename T, bool RAW = false, bool EXACT = false> struct UomeUpProblem
     __device__ float col_scale(int g, int nn) const   // the gate of the column's expert
     {
         if (!expert_gate || raw) return 1.0f;
-        return expert_gate[(size_t)g * n + clampi(expert_idx[g * kact + nn / d_e], n)];
+        if constexpr (SEL) return selected().gate[nn / d_e];
+        else return expert_gate[(size_t)g * n + expert(g, nn / d_e)];
     }
     __device__ float epi(float val, float gate) const { return raw ? val : (EXACT ? silu(val) : silu_fast(val)) * gate; }
     __device__ bool has_residual() const { return false; }

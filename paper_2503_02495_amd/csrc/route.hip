@@ -24,6 +24,7 @@
 //                       a kept index is the number of kept lower indices, so the list comes out
 //                       ascending with no sort and ties go to the lower index by construction.
 #include "common.h"
+#include "select.h"
 #include <cstdlib>
 
 namespace uoe {
@@ -234,7 +235,7 @@ __device__ __forceinline__ void route_partial(const RouteArgs &a, unsigned char 
         float s = 0.f;
 #pragma unroll
         for (int w = 0; w < ROUTE_WAVES; ++w) s += zsh[w * NMAX + tid];
-        a.zpart[((size_t)chunk * a.b + bb) * n + tid] = s;
+        a.zpart[zpart_at(a, chunk, bb, tid)] = s;
     }
     if (HAS_D) {
         const T *w_a = static_cast<const T *>(a.w_a);
@@ -668,7 +669,7 @@ __device__ __forceinline__ void route_expert_mfma_body(const RouteArgs &a, int c
     for (int o = tid; o < RT * 16 * CT * 16; o += 256) {
         const int row = o / (CT * 16), col = o - row * (CT * 16);
         if (b0 + row < b && col < n)
-            a.zpart[((size_t)chunk * b + b0 + row) * n + col] = (zsh[0][row][col] + zsh[1][row][col]) + (zsh[2][row][col] + zsh[3][row][col]);
+            a.zpart[zpart_at(a, chunk, b0 + row, col)] = (zsh[0][row][col] + zsh[1][row][col]) + (zsh[2][row][col] + zsh[3][row][col]);
     }
 }
 
@@ -877,7 +878,7 @@ __global__ __launch_bounds__(256) void route_stream_kernel(RouteArgs a, int ipw,
     for (int o = tid; o < RT * 16 * NP; o += 256) {
         const int row = o / NP, col = o - row * NP;
         if (row < bg && col < n)
-            a.zpart[((size_t)chunk * b + b0 + row) * n + col] = (zsh[0][row][col] + zsh[1][row][col]) + (zsh[2][row][col] + zsh[3][row][col]);
+            a.zpart[zpart_at(a, chunk, b0 + row, col)] = (zsh[0][row][col] + zsh[1][row][col]) + (zsh[2][row][col] + zsh[3][row][col]);
     }
     if (HAS_D) {
         for (int o = tid; o < tcur * bg * n; o += 256) {
@@ -1096,7 +1097,6 @@ __global__ __launch_bounds__(256) void route_reduce_kernel(RouteArgs a)
 // by ballots, and the expert selection runs beside the patch selections instead of behind one of them.
 // Against one chain per workgroup with a value per loop iteration: 16 experts x 128 patches 17.7 -> 9.8 us, 8 x 16
 // 7.6 -> 5.5 us, experts alone 6.0 -> 5.1 us.
-constexpr int SELECT_THREADS = 512;
 
 // max and sum of exp over the experts of one patch, from the staged logits (column j of [n][m])
 __device__ __forceinline__ void column_softmax(const float *col, int n, int m, float &mx, float &den)
@@ -1119,63 +1119,17 @@ __device__ __forceinline__ void column_softmax(const float *col, int n, int m, f
     }
 }
 
-// Expert selection of one sample: Eq. 21 logits (+noise) -> softmax -> Eq. 22 top-k.  The softmax is strictly
-// increasing in the logit within a sample, so the k largest gates are the k largest logits: rank on the logits,
-// which cannot underflow.
+// Expert selection of one sample, by a workgroup of its own.
 __device__ __forceinline__ void select_experts(const RouteArgs &a, int bb, int has_e)
 {
-    __shared__ float zpart_sum[SELECT_THREADS], ge[32];
-    const int tid = threadIdx.x, n = a.n;
-    if (has_e) {  // per-chunk partials in a fixed order: thread = (chunk group, expert), then 16 lanes per expert
-        const int groups = SELECT_THREADS / n;  // >= 16
-        if (tid < groups * n) {
-            const int vi = tid % n, cg = tid / n;
-            const float *src = a.zpart + (size_t)bb * n + vi;
-            const size_t stride = (size_t)a.b * n;
-            float zs = 0.f;
-            for (int c0 = cg; c0 < a.nchunks; c0 += 8 * groups) {
-                float v[8];
-#pragma unroll
-                for (int q = 0; q < 8; ++q) v[q] = src[(size_t)min(c0 + q * groups, a.nchunks - 1) * stride];
-#pragma unroll
-                for (int q = 0; q < 8; ++q) zs += c0 + q * groups < a.nchunks ? v[q] : 0.f;
-            }
-            zpart_sum[tid] = zs;  // index = group * n + expert
-        }
-        const int e = tid / 16, l16 = tid % 16;
-        const float nz = a.noise_e && e < n ? a.noise_e[(size_t)bb * n + e] : 0.f;
-        __syncthreads();
-        float z = 0.f;
-        if (e < n) {
-#pragma unroll 4
-            for (int cg = l16; cg < groups; cg += 16) z += zpart_sum[cg * n + e];
-        }
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1) z += __shfl_xor(z, off, 64);
-        if (e < n && l16 == 0) ge[e] = z + nz;
+    __shared__ float ge[32];
+    const int tid = threadIdx.x;
+    const float noise = expert_noise(a, bb, tid);
+    if (has_e) {
+        expert_logits<SELECT_THREADS>(a, bb, ge, tid);
         __syncthreads();
     }
-    if (tid >= 64) return;
-    const bool in = tid < n;
-    const float z = !in ? -INFINITY : (has_e ? ge[tid] : 0.f);
-    float mx = z;
-#pragma unroll
-    for (int off = 1; off < 32; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-    const float own = in ? expf(z - mx) : 0.f;
-    float den = own;
-#pragma unroll
-    for (int off = 1; off < 32; off <<= 1) den += __shfl_xor(den, off, 64);
-    if (in && a.expert_gate) a.expert_gate[(size_t)bb * n + tid] = has_e ? own / den : 1.0f;
-    int rank = 0;
-#pragma unroll
-    for (int ii = 0; ii < 32; ++ii) {
-        const float w = __shfl(z, ii, 64);
-        rank += ii < n && (w > z || (w == z && ii < tid)) ? 1 : 0;
-    }
-    const bool kept = in && rank < a.k;
-    const uint64_t mask = __ballot(kept);
-    const int pos = __popcll(mask & ((1ull << tid) - 1));
-    if (kept && pos < a.k && a.expert_idx) a.expert_idx[(size_t)bb * a.k + pos] = tid;
+    if (tid < 64) rank_experts(a, bb, has_e, ge, noise, true, nullptr, tid);
 }
 
 // fuse_reduce: the data router's per-chunk partials are summed here (each of the n workgroups of
@@ -1432,8 +1386,9 @@ __global__ __launch_bounds__(SELECT_THREADS) void route_select_all_kernel(RouteA
     route_select<true>(a, has_e, has_d, fuse_reduce, rows);
 }
 
-hipError_t launch_route(const RouteArgs &a_in, bool bf16, hipStream_t st)
+hipError_t launch_route(const RouteArgs &a_in, bool bf16, hipStream_t st, RouteSelect *beside)
 {
+    if (beside) beside->on = 0;
     RouteArgs a = a_in;
     const bool has_e = a.w_e != nullptr, has_d = a.w_b != nullptr;
     hipError_t err = hipSuccess;
@@ -1544,6 +1499,10 @@ hipError_t launch_route(const RouteArgs &a_in, bool bf16, hipStream_t st)
             err = bf16 ? launch_partial_n<bf16_t>(a, false, true, st) : launch_partial_n<float>(a, false, true, st);
             if (err != hipSuccess) return err;
         }
+    }
+    if (beside && !has_d && !a.capacity && a.nchunks * a.n <= SELECT_BESIDE_VALUES) {
+        *beside = {a, 1, (int)has_e};
+        return hipSuccess;
     }
     // patch lists and gates: none when neither is asked for (a capacity call needs row 0)
     const int rows = (a.patch_idx || a.patch_gate) ? a.n : (a.capacity && has_d ? 1 : 0);

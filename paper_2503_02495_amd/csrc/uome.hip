@@ -12,9 +12,10 @@ namespace uoe {
 
 // any width, either storage type (SiLU by a division: the reciprocal of silu_fast is zero where the sigmoid is no normal
 // number, z <= -87.4; 6 x 1000 tokens, d 360, 3 x 232 hidden columns: 2 us of 89 for the layer's forward)
-template <typename T> static hipError_t uome_up_tail(const UomeArgs &a, hipStream_t st)
+template <typename T, bool SEL> static hipError_t uome_up_tail(const UomeArgs &a, hipStream_t st)
 {
-    UomeUpProblem<T, false, true> up;
+    UomeUpProblem<T, false, true, SEL> up;
+    if constexpr (SEL) up.sel = *a.select;
     up.u = static_cast<const T *>(a.u);
     up.a_in = static_cast<const T *>(a.a_in);
     up.expert_idx = a.expert_idx;
@@ -39,9 +40,10 @@ template <typename T> static hipError_t uome_down_tail(const UomeArgs &a, hipStr
 // MFMA path: bf16 storage, and every K segment (d for GEMM-1, d_e for GEMM-2) a multiple of 32
 static bool uome_mfma_ok(const UomeArgs &a, bool bf16) { return bf16 && a.d % 32 == 0 && a.d_e % 32 == 0; }
 
-static hipError_t uome_up_mfma(const UomeArgs &a, hipStream_t st)
+template <bool SEL> static hipError_t uome_up_mfma(const UomeArgs &a, hipStream_t st)
 {
-    UomeUpProblem<bf16_t> up;
+    UomeUpProblem<bf16_t, false, false, SEL> up;
+    if constexpr (SEL) up.sel = *a.select;
     up.u = static_cast<const bf16_t *>(a.u);
     up.a_in = static_cast<const bf16_t *>(a.a_in);
     up.expert_idx = a.expert_idx;
@@ -67,8 +69,9 @@ static hipError_t uome_down_mfma(const UomeArgs &a, hipStream_t st)
 
 hipError_t launch_uome_up(const UomeArgs &a, bool bf16, hipStream_t st)
 {
-    if (uome_mfma_ok(a, bf16)) return uome_up_mfma(a, st);
-    return bf16 ? uome_up_tail<bf16_t>(a, st) : uome_up_tail<float>(a, st);
+    if (uome_mfma_ok(a, bf16)) return a.select ? uome_up_mfma<true>(a, st) : uome_up_mfma<false>(a, st);
+    if (bf16) return a.select ? uome_up_tail<bf16_t, true>(a, st) : uome_up_tail<bf16_t, false>(a, st);
+    return a.select ? uome_up_tail<float, true>(a, st) : uome_up_tail<float, false>(a, st);
 }
 
 hipError_t launch_uome_down(const UomeArgs &a, bool bf16, hipStream_t st)
