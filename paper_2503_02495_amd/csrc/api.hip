@@ -582,10 +582,11 @@ size_t uoe_uome_backward_workspace_bytes(const uoe_block_desc *blk)
     return check_uome_bwd(blk) == UOE_OK ? uome_bwd_ws(blk).total : 0;
 }
 
-int uoe_uome_backward(const uoe_block_desc *blk, const void *u, const void *a_in, const void *a_out,
-                      const int32_t *expert_idx, const float *expert_gate, const int32_t *patch_idx,
-                      const float *patch_gate, const void *d_out, void *d_u, void *d_a_in, void *d_a_out, float *d_gate,
-                      float *d_patch_gate, void *ws, size_t ws_bytes, void *hip_stream)
+// tail: the routers' pass follows in the same chain (BwdTail)
+static int uome_backward(const uoe_block_desc *blk, const void *u, const void *a_in, const void *a_out,
+                         const int32_t *expert_idx, const float *expert_gate, const int32_t *patch_idx,
+                         const float *patch_gate, const void *d_out, void *d_u, void *d_a_in, void *d_a_out, float *d_gate,
+                         float *d_patch_gate, void *ws, size_t ws_bytes, void *hip_stream, BwdTail *tail)
 {
     const int rc = check_uome_bwd(blk);
     if (rc != UOE_OK) return rc;
@@ -611,7 +612,7 @@ int uoe_uome_backward(const uoe_block_desc *blk, const void *u, const void *a_in
         a.wgrad = w.wgrad; a.part_end = reinterpret_cast<int32_t *>(at(ws, w.part_end)); a.gchunks = w.gchunks;
         a.partial = reinterpret_cast<float *>(at(ws, w.partial));
         a.gpart = reinterpret_cast<float *>(at(ws, w.gpart));
-        return launch_uome_backward_any(a, blk->dtype == UOE_BF16, static_cast<hipStream_t>(hip_stream)) == hipSuccess
+        return launch_uome_backward_any(a, blk->dtype == UOE_BF16, static_cast<hipStream_t>(hip_stream), tail) == hipSuccess
                    ? UOE_OK : UOE_ERR_DEVICE;
     }
     a.z = at(ws, w.z); a.dz = at(ws, w.dz); a.h = at(ws, w.h);
@@ -621,7 +622,16 @@ int uoe_uome_backward(const uoe_block_desc *blk, const void *u, const void *a_in
     a.wgrad = w.wgrad; a.part_end = reinterpret_cast<int32_t *>(at(ws, w.part_end));
     a.patch_idx = patch_idx; a.patch_gate = patch_gate; a.d_patch_gate = d_patch_gate;
     a.rt = reinterpret_cast<float *>(at(ws, w.rt)); a.m = blk->m; a.c = blk->c;
-    return launch_uome_backward(a, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? UOE_OK : UOE_ERR_DEVICE;
+    return launch_uome_backward(a, static_cast<hipStream_t>(hip_stream), tail) == hipSuccess ? UOE_OK : UOE_ERR_DEVICE;
+}
+
+int uoe_uome_backward(const uoe_block_desc *blk, const void *u, const void *a_in, const void *a_out,
+                      const int32_t *expert_idx, const float *expert_gate, const int32_t *patch_idx,
+                      const float *patch_gate, const void *d_out, void *d_u, void *d_a_in, void *d_a_out, float *d_gate,
+                      float *d_patch_gate, void *ws, size_t ws_bytes, void *hip_stream)
+{
+    return uome_backward(blk, u, a_in, a_out, expert_idx, expert_gate, patch_idx, patch_gate, d_out, d_u, d_a_in, d_a_out, d_gate, d_patch_gate,
+                         ws, ws_bytes, hip_stream, nullptr);
 }
 
 size_t uoe_smha_backward_workspace_bytes(const uoe_block_desc *blk)
@@ -632,7 +642,7 @@ size_t uoe_smha_backward_workspace_bytes(const uoe_block_desc *blk)
 static int smha_backward(const SmhaKept *kept, const uoe_block_desc *blk, const void *x, const uoe_smha_weights *w, const int32_t *expert_idx,
                       const float *expert_gate, const int32_t *patch_idx, const float *patch_gate, const uint8_t *pad_mask,
                       const void *d_out, void *d_x, const uoe_smha_weight_grads *dw, float *d_expert_gate,
-                      float *d_patch_gate, void *ws, size_t ws_bytes, void *hip_stream)
+                      float *d_patch_gate, void *ws, size_t ws_bytes, void *hip_stream, BwdTail *tail)
 {
     const int rc = check_smha_bwd(blk);
     if (rc != UOE_OK) return rc;
@@ -667,7 +677,7 @@ static int smha_backward(const SmhaKept *kept, const uoe_block_desc *blk, const 
         a.inv_sum = reinterpret_cast<float *>(at(ws, s.g_inv));
         a.wgrad = s.wgrad; a.part_end = reinterpret_cast<int32_t *>(at(ws, s.part_end));
         a.partial = reinterpret_cast<float *>(at(ws, s.partial));
-        return launch_smha_backward_any(a, blk->dtype == UOE_BF16, static_cast<hipStream_t>(hip_stream)) == hipSuccess
+        return launch_smha_backward_any(a, blk->dtype == UOE_BF16, static_cast<hipStream_t>(hip_stream), tail) == hipSuccess
                    ? UOE_OK : UOE_ERR_DEVICE;
     }
     f.q = at(ws, s.fwd.q); f.kk = at(ws, s.fwd.k); f.v = at(ws, s.fwd.v); f.o = at(ws, s.fwd.o); f.o_lo = at(ws, s.fwd.o_lo);
@@ -684,7 +694,7 @@ static int smha_backward(const SmhaKept *kept, const uoe_block_desc *blk, const 
     a.rt = reinterpret_cast<float *>(at(ws, s.rt)); a.dd = reinterpret_cast<float *>(at(ws, s.dd));
     a.partial = reinterpret_cast<float *>(at(ws, s.partial));
     a.wgrad = s.wgrad; a.part_end = reinterpret_cast<int32_t *>(at(ws, s.part_end));
-    return launch_smha_backward(a, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? UOE_OK : UOE_ERR_DEVICE;
+    return launch_smha_backward(a, static_cast<hipStream_t>(hip_stream), tail) == hipSuccess ? UOE_OK : UOE_ERR_DEVICE;
 }
 
 int uoe_smha_backward(const uoe_block_desc *blk, const void *x, const uoe_smha_weights *w, const int32_t *expert_idx,
@@ -693,7 +703,7 @@ int uoe_smha_backward(const uoe_block_desc *blk, const void *x, const uoe_smha_w
                       float *d_patch_gate, void *ws, size_t ws_bytes, void *hip_stream)
 {
     return smha_backward(nullptr, blk, x, w, expert_idx, expert_gate, patch_idx, patch_gate, pad_mask, d_out, d_x, dw,
-                         d_expert_gate, d_patch_gate, ws, ws_bytes, hip_stream);
+                         d_expert_gate, d_patch_gate, ws, ws_bytes, hip_stream, nullptr);
 }
 
 size_t uoe_route_backward_workspace_bytes(const uoe_block_desc *blk)
@@ -701,10 +711,10 @@ size_t uoe_route_backward_workspace_bytes(const uoe_block_desc *blk)
     return check_route_bwd(blk) == UOE_OK ? route_bwd_ws(blk).total : 0;
 }
 
-int uoe_route_backward(const uoe_block_desc *blk, const void *x, const void *w_expert, const void *w_b, const void *w_a,
-                       const float *expert_gate, const float *patch_gate, const float *d_expert_gate,
-                       const float *d_patch_gate, void *d_x, void *d_w_expert, void *d_w_b, void *d_w_a, void *ws,
-                       size_t ws_bytes, void *hip_stream)
+static int route_backward_args(const uoe_block_desc *blk, const void *x, const void *w_expert, const void *w_b, const void *w_a,
+                               const float *expert_gate, const float *patch_gate, const float *d_expert_gate,
+                               const float *d_patch_gate, void *d_x, void *d_w_expert, void *d_w_b, void *d_w_a, void *ws,
+                               size_t ws_bytes, RouteBwdArgs &a)
 {
     const int rc = check_route_bwd(blk);
     if (rc != UOE_OK) return rc;
@@ -717,7 +727,7 @@ int uoe_route_backward(const uoe_block_desc *blk, const void *x, const void *w_e
         if (!aligned16(p)) return UOE_ERR_INVALID_ARG;
     const RouteBwdWs w = route_bwd_ws(blk);
     if (!ws || ws_bytes < w.total || !aligned16(ws)) return UOE_ERR_WORKSPACE;
-    RouteBwdArgs a{};
+    a = RouteBwdArgs{};
     a.x = x; a.w_e = w_expert; a.w_b = w_b; a.w_a = w_a;
     a.g_e = expert_gate; a.g_p = patch_gate; a.d_g_e = d_expert_gate; a.d_g_p = d_patch_gate;
     a.d_x = d_x; a.d_w_e = d_w_expert; a.d_w_b = d_w_b; a.d_w_a = d_w_a;
@@ -725,6 +735,18 @@ int uoe_route_backward(const uoe_block_desc *blk, const void *x, const void *w_e
     a.dl = reinterpret_cast<float *>(at(ws, w.dl)); a.u = reinterpret_cast<float *>(at(ws, w.u));
     a.t1 = reinterpret_cast<float *>(at(ws, w.t1)); a.wb_part = reinterpret_cast<float *>(at(ws, w.wb_part));
     a.wbt = at(ws, w.wbt);
+    return UOE_OK;
+}
+
+int uoe_route_backward(const uoe_block_desc *blk, const void *x, const void *w_expert, const void *w_b, const void *w_a,
+                       const float *expert_gate, const float *patch_gate, const float *d_expert_gate,
+                       const float *d_patch_gate, void *d_x, void *d_w_expert, void *d_w_b, void *d_w_a, void *ws,
+                       size_t ws_bytes, void *hip_stream)
+{
+    RouteBwdArgs a;
+    const int rc = route_backward_args(blk, x, w_expert, w_b, w_a, expert_gate, patch_gate, d_expert_gate, d_patch_gate, d_x, d_w_expert, d_w_b,
+                                       d_w_a, ws, ws_bytes, a);
+    if (rc != UOE_OK) return rc;
     return launch_route_backward(a, blk->dtype == UOE_BF16, static_cast<hipStream_t>(hip_stream)) == hipSuccess
                ? UOE_OK : UOE_ERR_DEVICE;
 }
@@ -862,9 +884,10 @@ int uoe_layer_forward_masked(const uoe_block_desc *smha, const uoe_smha_weights 
     return do_uome(uome, u, wm->a_in, wm->a_out, m_eidx, m_egate, nullptr, nullptr, out, uome_scratch, uome_bytes, st, &beside);
 }
 
-// workspace of the layer backward: [u][d_u][gate gradients][kept by the recomputation of u][the largest of the stages' own scratch]
+// workspace of the layer backward: [u][d_u][gate gradients][kept by the recomputation of u][the larger of the blocks' own
+// scratch][the routers': their first launch runs beside the block's last one]
 struct LayerBwdWs {
-    size_t u, d_u, d_gate_m, d_pgate_m, d_gate_a, d_pgate_a, stage, stage_bytes, total;
+    size_t u, d_u, d_gate_m, d_pgate_m, d_gate_a, d_pgate_a, stage, stage_bytes, route, route_bytes, total;
     size_t keep_q, keep_k, keep_v, keep_o, keep_o_lo, keep_lse;
 };
 // The recomputation of u leaves q, k, v (and the attention's results) to the SMHA backward where both passes hold them in the
@@ -908,10 +931,11 @@ static LayerBwdWs layer_bwd_ws(const uoe_block_desc *smha, const uoe_block_desc 
         }
     }
     size_t stage = smha_ws(smha).total;
-    const size_t others[] = {uoe_uome_backward_workspace_bytes(uome), uoe_smha_backward_workspace_bytes(smha),
-                             uoe_route_backward_workspace_bytes(smha), uoe_route_backward_workspace_bytes(&um)};
-    for (size_t v : others) stage = v > stage ? v : stage;
+    const size_t blocks[] = {uoe_uome_backward_workspace_bytes(uome), uoe_smha_backward_workspace_bytes(smha)};
+    for (size_t v : blocks) stage = v > stage ? v : stage;
     w.stage = off; w.stage_bytes = stage; off += up(stage);
+    const size_t ra = uoe_route_backward_workspace_bytes(smha), rm = uoe_route_backward_workspace_bytes(&um);
+    w.route = off; w.route_bytes = ra > rm ? ra : rm; off += up(w.route_bytes);
     w.total = off;
     return w;
 }
@@ -985,27 +1009,31 @@ int uoe_layer_backward_masked(const uoe_block_desc *smha, const uoe_smha_weights
         if (rc != UOE_OK) return rc;
         u = u_ws;
     }
-    // UoME block and its router: d_out -> d_u
-    rc = uoe_uome_backward(uome, u, wm->a_in, wm->a_out, routing_m->expert_idx, routing_m->expert_gate,
-                           uome_ds ? routing_m->patch_idx : nullptr, uome_ds ? routing_m->patch_gate : nullptr, d_out, d_u,
-                           d_a_in, d_a_out, d_gate_m, uome_ds ? d_pgate_m : nullptr, stage, w.stage_bytes, hip_stream);
+    // UoME block and its router: d_out -> d_u.  The reduction of a block's weight gradients runs beside its routers' pass, and the first
+    // launch of that pass beside the SMHA block's last one: launches of 4 to 8 us each on small shapes, whatever they do
+    // (forward + backward of 8 x 512 x 512 214.6 -> 200.7 us, with data selection in the UoME block 231.6 -> 215.2, 128 x 196 x 384 681 -> 672)
+    void *route_ws = at(ws, w.route);
+    const bool bf16 = smha->dtype == UOE_BF16;
+    RouteBwdArgs rm, ra;
+    BwdTail tail{};
+    const uoe_block_desc um = uome_route_desc(uome);
+    if (route_m && (rc = route_backward_args(&um, u, wm->w_expert, wm->w_b, wm->w_a, routing_m->expert_gate, routing_m->patch_gate, d_gate_m, d_pgate_m,
+                                             d_u, drm->d_w_expert, drm->d_w_b, drm->d_w_a, route_ws, w.route_bytes, rm)) != UOE_OK) return rc;
+    if (route_a && (rc = route_backward_args(smha, x, wa->w_expert, wa->w_b, wa->w_a, routing_a->expert_gate, routing_a->patch_gate, d_gate_a, d_pgate_a,
+                                             d_x, dra->d_w_expert, dra->d_w_b, dra->d_w_a, route_ws, w.route_bytes, ra)) != UOE_OK) return rc;
+    rc = uome_backward(uome, u, wm->a_in, wm->a_out, routing_m->expert_idx, routing_m->expert_gate,
+                       uome_ds ? routing_m->patch_idx : nullptr, uome_ds ? routing_m->patch_gate : nullptr, d_out, d_u,
+                       d_a_in, d_a_out, d_gate_m, uome_ds ? d_pgate_m : nullptr, stage, w.stage_bytes, hip_stream, route_m ? &tail : nullptr);
     if (rc != UOE_OK) return rc;
-    if (route_m) {
-        const uoe_block_desc um = uome_route_desc(uome);
-        rc = uoe_route_backward(&um, u, wm->w_expert, wm->w_b, wm->w_a, routing_m->expert_gate, routing_m->patch_gate,
-                                d_gate_m, d_pgate_m, d_u, drm->d_w_expert, drm->d_w_b, drm->d_w_a, stage, w.stage_bytes,
-                                hip_stream);
-        if (rc != UOE_OK) return rc;
-    }
+    if (route_m && launch_route_backward(rm, bf16, st, &tail) != hipSuccess) return UOE_ERR_DEVICE;
     // SMHA block and its routers: d_u -> d_x
+    tail = BwdTail{};
+    tail.prep = route_a && wa->w_b ? &ra : nullptr;
     rc = smha_backward(kept, smha, x, wa, routing_a->expert_idx, routing_a->expert_gate, routing_a->patch_idx,
-                       routing_a->patch_gate, pad_mask, d_u, d_x, dwa, d_gate_a, d_pgate_a, stage, w.stage_bytes, hip_stream);
+                       routing_a->patch_gate, pad_mask, d_u, d_x, dwa, d_gate_a, d_pgate_a, stage, w.stage_bytes, hip_stream,
+                       route_a ? &tail : nullptr);
     if (rc != UOE_OK) return rc;
-    if (route_a)
-        rc = uoe_route_backward(smha, x, wa->w_expert, wa->w_b, wa->w_a, routing_a->expert_gate, routing_a->patch_gate,
-                                d_gate_a, d_pgate_a, d_x, dra->d_w_expert, dra->d_w_b, dra->d_w_a, stage, w.stage_bytes,
-                                hip_stream);
-    return rc;
+    return route_a && launch_route_backward(ra, bf16, st, &tail) != hipSuccess ? UOE_ERR_DEVICE : UOE_OK;
 }
 
 int uoe_probe_copy(const void *src, void *dst, size_t bytes, void *hip_stream)

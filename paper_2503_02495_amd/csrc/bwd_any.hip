@@ -330,7 +330,7 @@ template <typename T> __global__ __launch_bounds__(256) void uome_bwd_any_mid(Uo
     if (tid == 0) a.gpart[((size_t)bb * a.k + s) * a.gchunks + chunk] = red[0];
 }
 
-template <typename T> hipError_t uome_backward_any(const UomeBwdArgs &a, hipStream_t st)
+template <typename T> hipError_t uome_backward_any(const UomeBwdArgs &a, hipStream_t st, BwdTail *tail)
 {
     if (a.wgrad.parts > WGRAD_MAX_PARTS) return hipErrorInvalidValue;
     const int W = a.k * a.d_e;
@@ -395,7 +395,7 @@ template <typename T> hipError_t uome_backward_any(const UomeBwdArgs &a, hipStre
     ra.w = a.wgrad; ra.part_end = a.part_end;
     ra.dst[0] = a.d_a_out; ra.transposed[0] = 0;
     ra.dst[1] = a.d_a_in; ra.transposed[1] = 1;
-    return launch_wgrad_reduce<T>(ra, 2, st);
+    return launch_wgrad_reduce<T>(ra, 2, st, tail);
 }
 
 // ------------------------------------------------------------------------------------------ SMHA
@@ -448,7 +448,7 @@ __device__ __forceinline__ bool any_key_ok(const SmhaArgs &f, int g, int key, in
 // for four) and the general form's registers one (at 128 no scratch, 156 / 884 bytes before); 384 units of 56 rows, d_h 64: 44.4 -> 27.3
 // us owning queries, 27.1 -> 22.0 owning keys.  vit shape forward + backward 712 -> 698 us.
 template <typename T, int DH, int NQ, int KS, bool KV, bool ONE>
-__global__ __launch_bounds__(NQ *KS * 64, (ONE && DH <= 64) || DH == 32 ? 2 : 1) void attention_bwd_f32_kernel(SmhaBwdArgs a)
+__global__ __launch_bounds__(NQ *KS * 64, (ONE && DH <= 64) || DH == 32 ? 2 : 1) void attention_bwd_f32_kernel(SmhaBwdArgs a, int gate_units)
 {
     constexpr int BT = 32, P = DH + 4, NTH = NQ * 64, NP = BT * DH / 4 / NTH;   // NP: 16-byte pieces per staging thread
     constexpr int TILE = BT * P, SPLIT = 2 * TILE + 4 * BT, SLOT = (KV ? DH : DH / 2) + 2, MERGE = (KS - 1) * NQ * 64 * SLOT;
@@ -459,6 +459,14 @@ __global__ __launch_bounds__(NQ *KS * 64, (ONE && DH <= 64) || DH == 32 ? 2 : 1)
     constexpr int PARTS = parts_of<T>::value;
     const SmhaArgs &f = a.f;
     const int l_p = f.l / f.m, l_a = f.c * l_p, d_h = f.d_h, g = blockIdx.y;
+    if constexpr (KV) {   // the block's gate gradients, behind the units' rows of workgroups (r_t: of the query-owning kernel)
+        static_assert(UnitGates::LDS <= sizeof(lds), "the gate gradients' LDS");
+        if (g >= f.b * f.k) {
+            const int unit = (g - f.b * f.k) * gridDim.x + blockIdx.x;
+            if (unit < gate_units) unit_gate_block<NQ * KS * 64>(a, unit, lds);
+            return;
+        }
+    }
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int split = wave / NQ, qg = wave - split * NQ, stid = tid - split * NTH;
     const int lr = lane & 31, lh = lane >> 5;
@@ -828,10 +836,11 @@ template <typename T, int DH> void launch_attention_bwd_f32_dh(const SmhaBwdArgs
     // block 207, two 214, four 154; causal 169, 182, 155; 768 units, causal 229, 271, 222; in fp32, d_h 120, causal 615, 701, 604.  Longer units:
     // splits while the launch has fewer waves than SIMDs.
     const int ks = l_a <= 32 ? 1 : l_a <= 64 ? 2 : l_a <= 128 || blocks < 512 ? 4 : blocks < 1024 ? 2 : 1;
-    const dim3 grid((l_a + 31) / 32, units);
-#define UOE_ABW(KS, ONE)                                                                                       \
-    hipLaunchKernelGGL((attention_bwd_f32_kernel<T, DH, 1, KS, false, ONE>), grid, dim3(KS * 64), 0, st, a);   \
-    hipLaunchKernelGGL((attention_bwd_f32_kernel<T, DH, 1, KS, true, ONE>), grid, dim3(KS * 64), 0, st, a)
+    const int rows = (l_a + 31) / 32, gates = UnitGates::count(a);
+    const dim3 grid(rows, units), grid_kv(rows, units + (gates + rows - 1) / rows);
+#define UOE_ABW(KS, ONE)                                                                                            \
+    hipLaunchKernelGGL((attention_bwd_f32_kernel<T, DH, 1, KS, false, ONE>), grid, dim3(KS * 64), 0, st, a, 0);     \
+    hipLaunchKernelGGL((attention_bwd_f32_kernel<T, DH, 1, KS, true, ONE>), grid_kv, dim3(KS * 64), 0, st, a, gates)
     const bool one = l_a <= 32 * ks;   // a tile a wave
     if (ks == 1 && one) { UOE_ABW(1, true); }
     else if (ks == 1) { UOE_ABW(1, false); }
@@ -900,7 +909,7 @@ template <typename T> struct SmhaBwdWgrad : PlainEpilogue {
     __device__ void put4_f32(int g, int r, int nn, float4 v) const { put4(g, r, nn, v); }
 };
 
-template <typename T> hipError_t smha_backward_any(const SmhaBwdArgs &a, hipStream_t st)
+template <typename T> hipError_t smha_backward_any(const SmhaBwdArgs &a, hipStream_t st, BwdTail *tail)
 {
     if (a.wgrad.parts > WGRAD_MAX_PARTS) return hipErrorInvalidValue;
     const SmhaArgs &f = a.f;
@@ -955,19 +964,19 @@ template <typename T> hipError_t smha_backward_any(const SmhaBwdArgs &a, hipStre
     ra.w = a.wgrad; ra.part_end = a.part_end;
     ra.dst[0] = a.d_wq; ra.dst[1] = a.d_wk; ra.dst[2] = a.d_wv; ra.dst[3] = a.d_wo;
     ra.transposed[0] = ra.transposed[1] = ra.transposed[2] = 1; ra.transposed[3] = 0;
-    return launch_wgrad_reduce_gates<T, true>(ra, 4, a, st);
+    return launch_wgrad_reduce<T>(ra, 4, st, tail);
 }
 
 }  // namespace
 
-hipError_t launch_uome_backward_any(const UomeBwdArgs &a, bool bf16, hipStream_t st)
+hipError_t launch_uome_backward_any(const UomeBwdArgs &a, bool bf16, hipStream_t st, BwdTail *tail)
 {
-    return bf16 ? uome_backward_any<bf16_t>(a, st) : uome_backward_any<float>(a, st);
+    return bf16 ? uome_backward_any<bf16_t>(a, st, tail) : uome_backward_any<float>(a, st, tail);
 }
 
-hipError_t launch_smha_backward_any(const SmhaBwdArgs &a, bool bf16, hipStream_t st)
+hipError_t launch_smha_backward_any(const SmhaBwdArgs &a, bool bf16, hipStream_t st, BwdTail *tail)
 {
-    return bf16 ? smha_backward_any<bf16_t>(a, st) : smha_backward_any<float>(a, st);
+    return bf16 ? smha_backward_any<bf16_t>(a, st, tail) : smha_backward_any<float>(a, st, tail);
 }
 
 }  // namespace uoe

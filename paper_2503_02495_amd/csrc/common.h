@@ -299,6 +299,16 @@ struct SmhaBwdArgs {
                                               // fp32 there and dqkv is [units, l_a, parts, 3*d_h]
 };
 
+// Reduction of split weight-gradient tiles (wgrad_reduce.h): partial [sets*chunks*parts][M][N] fp32 -> storage dtype
+struct WgradReduceArgs {
+    const float *partial;
+    void *dst[4];   // storage type T of the launch
+    int transposed[4];
+    int n, M, N;
+    const int32_t *part_end;   // [chunks, 32] first part id behind an expert's
+    WgradPlan w;
+};
+
 // Launch shape of the routers' backward pass: d_x in chunks of pieces (8 columns) x groups of samples, dW_E in chunks
 // of pieces x groups of 8 experts, t1 and dW_B in chunks of the b*l tokens x slices of columns
 constexpr int ROUTE_BWD_TILE = 32, ROUTE_BWD_SLICE = 256;
@@ -326,6 +336,15 @@ struct RouteBwdArgs {
     RouteBwdPlan plan;                        // set by the launcher
 };
 
+// What a block's backward pass leaves to, or does for, the routers' backward pass that follows it in a chain of calls: the reduction of the
+// weight gradients runs beside that pass's main launch, and where the block's last launch has room, that pass's first one beside it
+struct BwdTail {
+    WgradReduceArgs reduce;
+    int sets;                  // of the reduction, 0: it has been launched
+    const RouteBwdArgs *prep;  // in: the routers' pass, NULL: it has no data router
+    int prep_done;
+};
+
 struct GatherArgs {
     const void *x;
     const int32_t *expert_idx, *patch_idx;
@@ -347,17 +366,18 @@ hipError_t launch_uome(const UomeArgs &a, bool bf16, hipStream_t st);
 hipError_t launch_uome_up(const UomeArgs &a, bool bf16, hipStream_t st);    // Eq. 38 only
 hipError_t launch_uome_down(const UomeArgs &a, bool bf16, hipStream_t st);  // Eq. 39-40 only
 hipError_t launch_uome_ds(const UomeDsArgs &a, bool bf16, hipStream_t st);
-hipError_t launch_uome_backward(const UomeBwdArgs &a, hipStream_t st);
-hipError_t launch_smha_backward(const SmhaBwdArgs &a, hipStream_t st);
+hipError_t launch_uome_backward(const UomeBwdArgs &a, hipStream_t st, BwdTail *tail = nullptr);
+hipError_t launch_smha_backward(const SmhaBwdArgs &a, hipStream_t st, BwdTail *tail = nullptr);
 // d_gate from the partial sums a.gpart [b, k, gchunks]
 hipError_t launch_uome_gate_grad(const UomeBwdArgs &a, hipStream_t st);
 // rotary embedding (Eq. 32) of fp32 q and k with rows of d_h
 hipError_t launch_rope_f32(const SmhaArgs &a, hipStream_t st);
 // backward passes for the shapes and storage types the 32-multiple bf16 kernels do not take
-hipError_t launch_uome_backward_any(const UomeBwdArgs &a, bool bf16, hipStream_t st);
-hipError_t launch_smha_backward_any(const SmhaBwdArgs &a, bool bf16, hipStream_t st);
+hipError_t launch_uome_backward_any(const UomeBwdArgs &a, bool bf16, hipStream_t st, BwdTail *tail = nullptr);
+hipError_t launch_smha_backward_any(const SmhaBwdArgs &a, bool bf16, hipStream_t st, BwdTail *tail = nullptr);
 constexpr int BWD_ANY_SEGMENTS = 1024;        // (unit, pick) entries one part of an expert's weight gradient holds
-hipError_t launch_route_backward(const RouteBwdArgs &a, bool bf16, hipStream_t st);
+// `tail`: of the block's backward pass before it (at most 128 samples)
+hipError_t launch_route_backward(const RouteBwdArgs &a, bool bf16, hipStream_t st, const BwdTail *tail = nullptr);
 int uome_backward_gate_chunks(int l, int d_e);
 
 // measurement probes (probe.hip)

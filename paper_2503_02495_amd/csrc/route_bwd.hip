@@ -14,6 +14,8 @@
 // adds in fp32 and takes one scalar per lane and operand, so a plain row-major LDS tile serves as left operand
 // in either orientation.  Summation orders are fixed: no atomics.
 #include "common.h"
+#include "route_prep.h"
+#include "wgrad_reduce.h"
 #include <type_traits>
 
 namespace uoe {
@@ -62,96 +64,14 @@ template <bool ONCE> __device__ __forceinline__ void store8_w(bf16_t *p, const f
     store16<ONCE>(p, make_uint4(w[0], w[1], w[2], w[3]));
 }
 
-typedef float rb_f32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ rb_f32x4 mfma_f32(float x, float y, rb_f32x4 c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, c, 0, 0, 0);  // lane: row / column lane & 15, k lane >> 4
-}
-
 template <typename T> struct RawPiece;   // 8 elements as loaded
 template <> struct RawPiece<bf16_t> { uint4 v[1]; };
 template <> struct RawPiece<float> { uint4 v[2]; };
 
-// Softmax backward of one logit, dz_i = g_i (dg_i - sum_j g_j dg_j) for any gates, evaluated as
-// g_i (sum_j g_j (dg_i - dg_j) + (1 - sum_j g_j) dg_i): with one gate close to 1 the first form subtracts two nearly equal
-// numbers, the second adds small terms of mixed sign only.  Gates of a softmax sum to one up to their rounding, (n + 1) 2^-23 at
-// most (a division, and the sums in the forward pass and here); that much of the last term is rounding, not gate, and left out.
-__device__ __forceinline__ float softmax_bwd(const float *g, const float *dg, int n, int stride, int i)
+template <typename T> __global__ __launch_bounds__(256) void route_bwd_prep_kernel(RoutePrep<T> p)
 {
-    const float mine = dg[i * stride];
-    float s = 0.f, rest = 1.f;
-    for (int q = 0; q < n; ++q) {
-        s = fmaf(g[q * stride], mine - dg[q * stride], s);
-        rest -= g[q * stride];
-    }
-    if (fabsf(rest) > (float)(n + 1) * 1.1920929e-7f) s = fmaf(mine, rest, s);
-    return g[i * stride] * s;
-}
-
-constexpr int PREP_TOK = 64, PREP_J = 64, PREP_ST = PREP_J + 4;  // row stride = 4 mod 64 banks: 16 rows x 4 k, no conflict
-// Block (token tile, sample): the sample's dL (Eq. 14 backwards) and U = W_A dL^T for 64 tokens, 64 patches at a
-// time.  Blocks behind the last token tile write W_B^T (the d_x workgroups read 8 of its columns per 16 bytes).
-template <typename T> __global__ __launch_bounds__(256) void route_bwd_prep_kernel(RouteBwdArgs a)
-{
-    __shared__ float gs[2][32][PREP_J], dls[32][PREP_ST], was[PREP_TOK][PREP_ST];
-    const int tid = threadIdx.x, bb = blockIdx.y, tiles = (a.l + PREP_TOK - 1) / PREP_TOK;
-    if ((int)blockIdx.x >= tiles) {
-        const int step = (int)(gridDim.x - tiles) * a.b * 256;
-        for (int idx = (((int)blockIdx.x - tiles) * a.b + bb) * 256 + tid; idx < a.d * a.n; idx += step) {
-            const int i = idx / a.d, e = idx - i * a.d;
-            static_cast<T *>(a.wbt)[idx] = static_cast<const T *>(a.w_b)[(size_t)e * a.n + i];
-        }
-        return;
-    }
-    const int t0 = blockIdx.x * PREP_TOK, wave = tid >> 6, r = tid & 15, q = (tid & 63) >> 4;
-    const float *g = a.g_p + (size_t)bb * a.n * a.m, *dg = a.d_g_p + (size_t)bb * a.n * a.m;
-    const int rows = (a.n + 15) & ~15;
-    rb_f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-    for (int j0 = 0; j0 < a.m; j0 += PREP_J) {
-        const int nj = min(PREP_J, a.m - j0);
-        const int jj = tid % PREP_J, row = tid / PREP_J;
-        const size_t j = j0 + min(jj, nj - 1);  // clamped, unconditional loads: all of them in flight at once
-        T wv[16];
-        float gv[8], dgv[8];
-#pragma unroll
-        for (int v = 0; v < 8; ++v) {
-            const int i = min(row + 4 * v, a.n - 1);
-            gv[v] = g[i * a.m + j];
-            dgv[v] = dg[i * a.m + j];
-        }
-#pragma unroll
-        for (int v = 0; v < 16; ++v) wv[v] = static_cast<const T *>(a.w_a)[(size_t)min(t0 + row + 4 * v, a.l - 1) * a.m + j];
-#pragma unroll
-        for (int v = 0; v < 8; ++v) {
-            gs[0][row + 4 * v][jj] = gv[v];
-            gs[1][row + 4 * v][jj] = dgv[v];
-        }
-#pragma unroll
-        for (int v = 0; v < 16; ++v) was[row + 4 * v][jj] = jj < nj ? to_f32(wv[v]) : 0.f;
-        __syncthreads();
-        for (int i = row; i < rows; i += 4) {
-            float v = 0.f;
-            if (i < a.n && jj < nj) {
-                v = softmax_bwd(&gs[0][0][jj], &gs[1][0][jj], a.n, PREP_J, i);
-                if (blockIdx.x == 0) a.dl[((size_t)bb * a.n + i) * a.m + j0 + jj] = v;
-            }
-            dls[i][jj] = v;
-        }
-        __syncthreads();
-        for (int s = 0; s < (nj + 3) / 4; ++s) {
-            const float av = was[16 * wave + r][4 * s + q];
-            acc[0] = mfma_f32(av, dls[r][4 * s + q], acc[0]);
-            if (a.n > 16) acc[1] = mfma_f32(av, dls[16 + r][4 * s + q], acc[1]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int t = t0 + 16 * wave + 4 * q + e, i = 16 * nt + r;
-            if (t < a.l && i < a.n) a.u[((size_t)bb * a.l + t) * a.n + i] = acc[nt][e];
-        }
+    __shared__ __align__(16) unsigned char lds[RoutePrep<T>::LDS];
+    p.template run<256>(blockIdx.x, lds);
 }
 
 // gates and gate gradients of nb samples into LDS: softmax_bwd walks a row n times
@@ -431,7 +351,7 @@ template <typename T, int NT> __device__ __forceinline__ void bwd_data(const Rou
 // the two streaming kinds live on loads in flight.
 constexpr int main_waves(int bg, bool f32, int nt) { return (bg == 4 ? 4 : 3) - f32 - (nt == 2) < 2 ? 2 : (bg == 4 ? 4 : 3) - f32 - (nt == 2); }
 template <typename T, int BG, bool ONCE, int NT>
-__global__ __launch_bounds__(256, main_waves(BG, sizeof(T) == 4, NT)) void route_bwd_main_kernel(RouteBwdArgs a)
+__global__ __launch_bounds__(256, main_waves(BG, sizeof(T) == 4, NT)) void route_bwd_main_kernel(RouteBwdArgs a, WgradReduceArgs ra, int rx, int ry)
 {
     extern __shared__ __align__(16) float smem[];
     const RouteBwdPlan &p = a.plan;
@@ -449,8 +369,13 @@ __global__ __launch_bounds__(256, main_waves(BG, sizeof(T) == 4, NT)) void route
         return;
     }
     id -= p.dx_blocks;
-    const int o = id / 8, chunk = (o / p.w_groups) * 8 * p.w_reps + id % 8;
-    if (chunk < p.w_chunks) bwd_wexpert<T, ONCE>(a, smem, chunk, (o % p.w_groups) * 8);
+    if (id < p.w_blocks) {
+        const int o = id / 8, chunk = (o / p.w_groups) * 8 * p.w_reps + id % 8;
+        if (chunk < p.w_chunks) bwd_wexpert<T, ONCE>(a, smem, chunk, (o % p.w_groups) * 8);
+        return;
+    }
+    id -= p.w_blocks;   // the block's weight gradients (BwdTail)
+    wgrad_reduce_tile<T, false>(ra, reinterpret_cast<RedTile>(smem), id % rx, id / rx % ry, id / (rx * ry));
 }
 
 // dW_A[t,j] = sum over k = (sample, expert) of t1[t,k] dL[k,j]: block = 16 tokens x up to 128 patches; its 8 waves
@@ -559,14 +484,14 @@ RouteBwdPlan route_bwd_plan(int b, int l, int d, int n, bool has_e, bool has_d)
     return p;
 }
 
-template <typename T> static hipError_t route_backward(RouteBwdArgs a, hipStream_t st)
+template <typename T> static hipError_t route_backward(RouteBwdArgs a, hipStream_t st, const BwdTail *tail)
 {
     hipError_t err;
     a.plan = route_bwd_plan(a.b, a.l, a.d, a.n, a.w_e != nullptr, a.w_b != nullptr);
     const RouteBwdPlan &p = a.plan;
-    if (a.w_b) {
-        const int extra = (a.d * a.n + 2048 * a.b - 1) / (2048 * a.b);  // 8 elements of W_B^T per thread
-        hipLaunchKernelGGL((route_bwd_prep_kernel<T>), dim3((a.l + PREP_TOK - 1) / PREP_TOK + extra, a.b), dim3(256), 0, st, a);
+    if (a.w_b && !(tail && tail->prep_done)) {
+        const RoutePrep<T> prep(a);
+        hipLaunchKernelGGL((route_bwd_prep_kernel<T>), dim3(prep.blocks()), dim3(256), 0, st, prep);
         if ((err = hipGetLastError()) != hipSuccess) return err;
     }
     size_t floats = 0;
@@ -576,15 +501,23 @@ template <typename T> static hipError_t route_backward(RouteBwdArgs a, hipStream
     const int P = a.d / 8, ntok = (p.dx_pieces + P - 2) / P + 1;  // tokens a d_x block can touch
     need((size_t)a.n * p.dx_bg * (1 + (a.w_b ? ntok : 0)));
     if (a.w_b) need((size_t)BT * bwd_stride<T>() * sizeof(T) / 4 + 4 * BT * (((a.n + 15) & ~15) + 1));
-    const dim3 grid(p.data_blocks + p.dx_blocks + p.w_blocks);
+    WgradReduceArgs ra{};
+    int rx = 1, ry = 1, tiles = 0;
+    if (tail && tail->sets) {
+        const RedGrid g(tail->reduce, tail->sets);
+        ra = tail->reduce;
+        rx = g.nx; ry = g.ny; tiles = g.tiles;
+        need(RED_LDS / sizeof(float));
+    }
+    const dim3 grid(p.data_blocks + p.dx_blocks + p.w_blocks + tiles);
     const bool once = a.w_e && sizeof(T) == 2 && stream_once((size_t)a.n * a.l * a.d * sizeof(T));
     const size_t lds = floats * sizeof(float);
     auto launch = [&](auto bg, auto hint) {
         constexpr int BG = decltype(bg)::value;
         constexpr bool ONCE = decltype(hint)::value && sizeof(T) == 2;
-        if (!a.w_b) hipLaunchKernelGGL((route_bwd_main_kernel<T, BG, ONCE, 0>), grid, dim3(256), lds, st, a);
-        else if (a.n <= 16) hipLaunchKernelGGL((route_bwd_main_kernel<T, BG, ONCE, 1>), grid, dim3(256), lds, st, a);
-        else hipLaunchKernelGGL((route_bwd_main_kernel<T, BG, ONCE, 2>), grid, dim3(256), lds, st, a);
+        if (!a.w_b) hipLaunchKernelGGL((route_bwd_main_kernel<T, BG, ONCE, 0>), grid, dim3(256), lds, st, a, ra, rx, ry);
+        else if (a.n <= 16) hipLaunchKernelGGL((route_bwd_main_kernel<T, BG, ONCE, 1>), grid, dim3(256), lds, st, a, ra, rx, ry);
+        else hipLaunchKernelGGL((route_bwd_main_kernel<T, BG, ONCE, 2>), grid, dim3(256), lds, st, a, ra, rx, ry);
     };
     using std::integral_constant;
     if (p.dx_bg == 4) once ? launch(integral_constant<int, 4>{}, std::true_type{}) : launch(integral_constant<int, 4>{}, std::false_type{});
@@ -598,9 +531,9 @@ template <typename T> static hipError_t route_backward(RouteBwdArgs a, hipStream
     return hipSuccess;
 }
 
-hipError_t launch_route_backward(const RouteBwdArgs &a, bool bf16, hipStream_t st)
+hipError_t launch_route_backward(const RouteBwdArgs &a, bool bf16, hipStream_t st, const BwdTail *tail)
 {
-    return bf16 ? route_backward<bf16_t>(a, st) : route_backward<float>(a, st);
+    return bf16 ? route_backward<bf16_t>(a, st, tail) : route_backward<float>(a, st, tail);
 }
 
 }  // namespace uoe

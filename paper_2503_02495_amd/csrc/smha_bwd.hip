@@ -18,6 +18,7 @@
 #include "gemm_mfma.h"
 #include "gemm_dma.h"
 #include "wgrad_reduce.h"
+#include "route_prep.h"
 
 namespace uoe {
 
@@ -121,7 +122,7 @@ struct AttnBwdArgs {
     const float *lse;
     float *dd;              // [units, l_a]: written by the query-owning kernel, read by the key-owning one
     bf16_t *dqkv;           // [units, l_a, 3*d_h]
-    int l_a, causal;
+    int units, l_a, causal;
     int rope_dim;           // Eq. 32: dq and dk are rotated back (the transposed rotation) on the way out
     // Eq. 41: padded keys are out of every softmax.  pad_mask [b,l] (1 = token) or NULL, looked up
     // through the unit's patch indices
@@ -137,7 +138,7 @@ __device__ __forceinline__ bool bwd_key_is_token(const AttnBwdArgs &a, int g, in
     return a.pad_mask[(size_t)bb * a.l + p * a.l_p + key % a.l_p] != 0;
 }
 
-template <int DH, int NW, int KS, bool KV, bool PAD> __global__ __launch_bounds__(NW * KS * 64, DH <= 64 && NW == 4 ? 2 : 1) void attention_bwd_kernel(AttnBwdArgs a)
+template <int DH, int NW, int KS, bool KV, bool PAD> __global__ __launch_bounds__(NW * KS * 64, DH <= 64 && NW == 4 ? 2 : 1) void attention_bwd_kernel(AttnBwdArgs a, UnitGates gates)
 {
     constexpr int BT = 64, KP = DH + 8, VP = 2 * b_pitch_dwords(DH), NT = NW * 64;
     constexpr int CHUNKS = BT * DH / 8, PER_T = (CHUNKS + NT - 1) / NT;
@@ -153,6 +154,13 @@ template <int DH, int NW, int KS, bool KV, bool PAD> __global__ __launch_bounds_
     __shared__ float Dred[KV ? 1 : KS][NW * 32];
 
     const int g = blockIdx.y, l_a = a.l_a;
+    if constexpr (KV) {   // the block's gate gradients, behind the units' rows of workgroups (r_t is there since dO was formed)
+        static_assert(UnitGates::LDS <= sizeof(lds), "the gate gradients' LDS");
+        if (g >= a.units) {
+            gates.run<NW * KS * 64>((g - a.units) * gridDim.x + blockIdx.x, lds);
+            return;
+        }
+    }
     const int split = KS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / NT) : 0;
     const int tid = threadIdx.x - split * NT, lane = tid & 63, wave = tid >> 6;   // within the group
     Tiles &T = reinterpret_cast<Tiles *>(lds)[split];
@@ -433,40 +441,41 @@ template <int DH, int NW, int KS, bool KV, bool PAD> __global__ __launch_bounds_
     }
 }
 
-template <int DH, int NW, int KS, bool PAD> static hipError_t launch_attention_bwd_as(const AttnBwdArgs &a, int units, hipStream_t st)
+template <int DH, int NW, int KS, bool PAD> static hipError_t launch_attention_bwd_as(const AttnBwdArgs &a, const UnitGates &gates, hipStream_t st)
 {
-    const dim3 grid((a.l_a + 32 * NW - 1) / (32 * NW), units);
-    hipLaunchKernelGGL((attention_bwd_kernel<DH, NW, KS, false, PAD>), grid, dim3(NW * KS * 64), 0, st, a);
-    hipLaunchKernelGGL((attention_bwd_kernel<DH, NW, KS, true, PAD>), grid, dim3(NW * KS * 64), 0, st, a);
+    const int blocks = (a.l_a + 32 * NW - 1) / (32 * NW), more = (gates.units + blocks - 1) / blocks;
+    hipLaunchKernelGGL((attention_bwd_kernel<DH, NW, KS, false, PAD>), dim3(blocks, a.units), dim3(NW * KS * 64), 0, st, a, gates);
+    hipLaunchKernelGGL((attention_bwd_kernel<DH, NW, KS, true, PAD>), dim3(blocks, a.units + more), dim3(NW * KS * 64), 0, st, a, gates);
     return hipGetLastError();
 }
 
 // Two groups of waves per own block while one would leave SIMDs with less than two waves (2048 on the chip) and there
 // is a second tile to stream; then as many own blocks per workgroup (they share the streamed tiles) as still give every
 // compute unit a workgroup.  Heads of 128 stay with one group: two would not fit the register file.
-template <int DH, bool PAD> static hipError_t launch_attention_bwd_dh(const AttnBwdArgs &a, int units, hipStream_t st)
+template <int DH, bool PAD> static hipError_t launch_attention_bwd_dh(const AttnBwdArgs &a, const UnitGates &gates, hipStream_t st)
 {
+    const int units = a.units;
     const long wide = (long)((a.l_a + 127) / 128) * units, mid = (long)((a.l_a + 63) / 64) * units;
     if constexpr (DH <= 64) {
         if (a.l_a > 64 && (long)((a.l_a + 31) / 32) * units < 2048) {
-            if (wide >= 256) return launch_attention_bwd_as<DH, 4, 2, PAD>(a, units, st);
-            if (mid >= 256) return launch_attention_bwd_as<DH, 2, 2, PAD>(a, units, st);
-            return launch_attention_bwd_as<DH, 1, 2, PAD>(a, units, st);
+            if (wide >= 256) return launch_attention_bwd_as<DH, 4, 2, PAD>(a, gates, st);
+            if (mid >= 256) return launch_attention_bwd_as<DH, 2, 2, PAD>(a, gates, st);
+            return launch_attention_bwd_as<DH, 1, 2, PAD>(a, gates, st);
         }
     }
-    if (wide >= 128) return launch_attention_bwd_as<DH, 4, 1, PAD>(a, units, st);
-    if (mid >= 64) return launch_attention_bwd_as<DH, 2, 1, PAD>(a, units, st);
-    return launch_attention_bwd_as<DH, 1, 1, PAD>(a, units, st);
+    if (wide >= 128) return launch_attention_bwd_as<DH, 4, 1, PAD>(a, gates, st);
+    if (mid >= 64) return launch_attention_bwd_as<DH, 2, 1, PAD>(a, gates, st);
+    return launch_attention_bwd_as<DH, 1, 1, PAD>(a, gates, st);
 }
 
-template <bool PAD> static hipError_t launch_attention_bwd(const AttnBwdArgs &a, int dh, int units, hipStream_t st)
+template <bool PAD> static hipError_t launch_attention_bwd(const AttnBwdArgs &a, int dh, const UnitGates &gates, hipStream_t st)
 {
-    if (dh == 32) return launch_attention_bwd_dh<32, PAD>(a, units, st);
-    if (dh == 64) return launch_attention_bwd_dh<64, PAD>(a, units, st);
-    return launch_attention_bwd_dh<128, PAD>(a, units, st);
+    if (dh == 32) return launch_attention_bwd_dh<32, PAD>(a, gates, st);
+    if (dh == 64) return launch_attention_bwd_dh<64, PAD>(a, gates, st);
+    return launch_attention_bwd_dh<128, PAD>(a, gates, st);
 }
 
-hipError_t launch_smha_backward(const SmhaBwdArgs &a_in, hipStream_t st)
+hipError_t launch_smha_backward(const SmhaBwdArgs &a_in, hipStream_t st, BwdTail *tail)
 {
     typedef bf16_t T;
     SmhaBwdArgs a = a_in;
@@ -503,10 +512,11 @@ hipError_t launch_smha_backward(const SmhaBwdArgs &a_in, hipStream_t st)
     ab.q = static_cast<const T *>(f.q); ab.k = static_cast<const T *>(f.kk); ab.v = static_cast<const T *>(f.v);
     ab.d_o = static_cast<const T *>(a.d_o); ab.lse = f.lse; ab.dd = a.dd;
     ab.dqkv = static_cast<T *>(a.dqkv);
-    ab.l_a = l_a; ab.causal = (f.flags & F_CAUSAL) ? 1 : 0; ab.rope_dim = f.rope_dim;
+    ab.units = units; ab.l_a = l_a; ab.causal = (f.flags & F_CAUSAL) ? 1 : 0; ab.rope_dim = f.rope_dim;
     ab.pad_mask = f.pad_mask; ab.expert_idx = f.expert_idx; ab.patch_idx = f.patch_idx;
     ab.l = f.l; ab.n = f.n; ab.kact = f.k; ab.c = f.c; ab.m = f.m; ab.l_p = l_p;
-    err = ab.pad_mask ? launch_attention_bwd<true>(ab, dh, units, st) : launch_attention_bwd<false>(ab, dh, units, st);
+    const UnitGates gates{a, UnitGates::count(a)};
+    err = ab.pad_mask ? launch_attention_bwd<true>(ab, dh, gates, st) : launch_attention_bwd<false>(ab, dh, gates, st);
     if (err != hipSuccess) return err;
 
     // d_x = (G) + scatter-add of dq W^q^T + dk W^k^T + dv W^v^T
@@ -536,10 +546,17 @@ hipError_t launch_smha_backward(const SmhaBwdArgs &a_in, hipStream_t st)
     typedef GemmTile<SmhaDxProblem<T, 1>, 32, 128, 32, 1, 4, 4, GEMM_B_NK> Dx32;
     typedef GemmTile<SmhaDxProblem<T, 1>, 64, 128, 32, 2, 2, 4, GEMM_B_NK> Dx64;
     typedef GemmTile<SmhaWgradProblem<T>, 64, 128, 32, 2, 2, 4, GEMM_A_KM> Wg;
-    if ((long)groups * ((dh + 63) / 64) * ((f.d + 127) / 128) <= 512)
-        err = l_p <= 32 ? launch_gemm_dma_pair<Wg, Dx32, 2>(wp, groups, dh, f.d, xp, f.b * f.m, l_p, f.d, st)
-                        : launch_gemm_dma_pair<Wg, Dx64, 2>(wp, groups, dh, f.d, xp, f.b * f.m, l_p, f.d, st);
-    else {
+    if ((long)groups * ((dh + 63) / 64) * ((f.d + 127) / 128) <= 512) {
+        RoutePrep<T> prep{};   // and with the first launch of the data router's pass, whose gate gradients are there
+        int prep_blocks = 0;
+        if (tail && tail->prep) {
+            prep = RoutePrep<T>(*tail->prep);
+            prep_blocks = prep.blocks();
+            tail->prep_done = 1;
+        }
+        err = l_p <= 32 ? launch_gemm_dma_pair<Wg, Dx32, 2>(wp, groups, dh, f.d, xp, f.b * f.m, l_p, f.d, st, prep, prep_blocks)
+                        : launch_gemm_dma_pair<Wg, Dx64, 2>(wp, groups, dh, f.d, xp, f.b * f.m, l_p, f.d, st, prep, prep_blocks);
+    } else {
         if (l_p <= 32) err = launch_gemm_dma<SmhaDxProblem<T, 1>, 32, 128, 32, 1, 4, 4, 2, GEMM_B_NK>(xp, f.b * f.m, l_p, f.d, st);
         else err = launch_gemm_dma<SmhaDxProblem<T, 1>, 64, 128, 32, 2, 2, 4, 2, GEMM_B_NK>(xp, f.b * f.m, l_p, f.d, st);
         if (err == hipSuccess) err = launch_gemm_dma_auto<GEMM_A_KM>(wp, groups, dh, f.d, 0, l_p, st);
@@ -551,7 +568,7 @@ hipError_t launch_smha_backward(const SmhaBwdArgs &a_in, hipStream_t st)
     ra.dst[0] = a.d_wq; ra.dst[1] = a.d_wk;
     ra.dst[2] = a.d_wv; ra.dst[3] = a.d_wo;
     ra.transposed[0] = ra.transposed[1] = ra.transposed[2] = 1; ra.transposed[3] = 0;
-    return launch_wgrad_reduce_gates<T, false>(ra, 4, a, st);
+    return launch_wgrad_reduce<T>(ra, 4, st, tail);
 }
 
 }  // namespace uoe

@@ -194,9 +194,8 @@ template <typename T> struct UomeDhPairProblem : UomeDhProblem<T> {
 // d_gate [b,n]: block (slot s, sample b) adds the slot's partial sums (each thread a strided
 // subset in index order, then a fixed tree) into the entry of the slot's expert; the block of slot 0
 // also writes the zeros of the experts the sample did not select (all of them without the gate flag).
-__device__ __forceinline__ void uome_bwd_gate_block(const UomeBwdArgs &a, int s, int bb)
+__device__ __forceinline__ void uome_bwd_gate_block(const UomeBwdArgs &a, int s, int bb, float *red)   // red: 256 floats of LDS
 {
-    __shared__ float red[256];
     const int tid = threadIdx.x;
     const bool gated = a.flags & F_GATE_EXPERT;
     if (s == 0 && tid < a.n) {
@@ -218,15 +217,32 @@ __device__ __forceinline__ void uome_bwd_gate_block(const UomeBwdArgs &a, int s,
     if (tid == 0) a.d_gate[(size_t)bb * a.n + clampi(a.expert_idx[bb * a.k + s], a.n)] = red[0];
 }
 
-__global__ __launch_bounds__(256) void uome_bwd_gate_kernel(UomeBwdArgs a) { uome_bwd_gate_block(a, blockIdx.x, blockIdx.y); }
+__global__ __launch_bounds__(256) void uome_bwd_gate_kernel(UomeBwdArgs a)
+{
+    __shared__ float red[256];
+    uome_bwd_gate_block(a, blockIdx.x, blockIdx.y, red);
+}
 
-// the last launch of the expert-selection pass: the gate gradient's blocks and the weight-gradient tiles
+// the last launch of the expert-selection pass where the gates did not fit beside another: the gate gradient's blocks and the
+// weight-gradient tiles
 __global__ __launch_bounds__(256) void uome_bwd_finish_kernel(WgradReduceArgs ra, UomeBwdArgs a, int nx, int ny, int gates)
 {
+    __shared__ __align__(16) unsigned char lds[RED_LDS];
     const int id = (int)blockIdx.x - gates;
-    if (id >= 0) wgrad_reduce_tile<bf16_t, false>(ra, id % nx, id / nx % ny, id / (nx * ny));
-    else uome_bwd_gate_block(a, blockIdx.x % a.k, blockIdx.x / a.k);
+    if (id >= 0) wgrad_reduce_tile<bf16_t, false>(ra, reinterpret_cast<RedTile>(lds), id % nx, id / nx % ny, id / (nx * ny));
+    else uome_bwd_gate_block(a, blockIdx.x % a.k, blockIdx.x / a.k, reinterpret_cast<float *>(lds));
 }
+
+// the gate gradient's blocks behind the tiles of another launch
+struct UomeGates {
+    static constexpr size_t LDS = 256 * sizeof(float);
+    UomeBwdArgs a;
+    template <int NT> __device__ __forceinline__ void run(int block, void *lds) const
+    {
+        static_assert(NT == 256, "256 threads");
+        uome_bwd_gate_block(a, block % a.k, block / a.k, static_cast<float *>(lds));
+    }
+};
 
 hipError_t launch_uome_gate_grad(const UomeBwdArgs &a, hipStream_t st)
 {
@@ -234,13 +250,13 @@ hipError_t launch_uome_gate_grad(const UomeBwdArgs &a, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st);
+hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st, BwdTail *tail);
 
-hipError_t launch_uome_backward(const UomeBwdArgs &a, hipStream_t st)
+hipError_t launch_uome_backward(const UomeBwdArgs &a, hipStream_t st, BwdTail *tail)
 {
     typedef bf16_t T;
     if (a.wgrad.parts > WGRAD_MAX_PARTS) return hipErrorInvalidValue;
-    if (a.patch_idx) return launch_uome_ds_backward(a, st);
+    if (a.patch_idx) return launch_uome_ds_backward(a, st, tail);
     hipError_t err;
     const int width = a.k * a.d_e;
     UomeUpProblem<T, true> zp;  // Z = u W1_b (plain product)
@@ -274,11 +290,14 @@ hipError_t launch_uome_backward(const UomeBwdArgs &a, hipStream_t st)
     wp.M = a.d_e; wp.N = a.d; wp.range = a.l / a.wgrad.items;
     // one launch for d_u and the weight gradients while neither fills the chip's slots (two per compute unit) by itself
     const int groups = wp.parts.groups(), kseg = wp.range;
+    int gates = a.d_gate ? a.b * a.k : 0;
     const long du64 = (long)a.b * ((a.l + 63) / 64) * ((a.d + 127) / 128), wg128 = (long)groups * ((a.d_e + 127) / 128) * ((a.d + 127) / 128);
     if (a.d_e % 64 == 0 && kseg % 64 == 0 && a.d_e > 64 && du64 <= 512 && wg128 <= 512) {
         typedef GemmTile<UomeDownProblem<T>, 64, 128, 64, 2, 2, 3, GEMM_B_NK> Du;
         typedef GemmTile<WgradProblem<T>, 128, 128, 64, 2, 2, 2, GEMM_A_KM> Wg;
-        err = launch_gemm_dma_pair<Wg, Du, 2>(wp, groups, a.d_e, a.d, up, a.b, a.l, a.d, st);
+        // (the gate gradient beside them, in whose launch the chip is busy; it took the reduction's out of the chain to the routers' pass)
+        err = launch_gemm_dma_pair<Wg, Du, 2>(wp, groups, a.d_e, a.d, up, a.b, a.l, a.d, st, UomeGates{a}, gates);
+        gates = 0;
     } else if ((err = launch_gemm_dma_auto<GEMM_B_NK>(up, a.b, a.l, a.d, width, a.d_e, st)) == hipSuccess)
         err = launch_gemm_dma_auto<GEMM_A_KM>(wp, groups, a.d_e, a.d, 0, kseg, st);
     if (err != hipSuccess) return err;
@@ -287,9 +306,9 @@ hipError_t launch_uome_backward(const UomeBwdArgs &a, hipStream_t st)
     ra.w = a.wgrad; ra.part_end = a.part_end;
     ra.dst[0] = a.d_a_out; ra.transposed[0] = 0;
     ra.dst[1] = a.d_a_in; ra.transposed[1] = 1;
-    const int nx = (a.d + RED_T - 1) / RED_T, ny = (a.d_e + RED_T - 1) / RED_T, tiles = nx * ny * 2 * a.n;
-    const int gates = a.d_gate ? a.b * a.k : 0;
-    hipLaunchKernelGGL(uome_bwd_finish_kernel, dim3(tiles + gates), dim3(256), 0, st, ra, a, nx, ny, gates);
+    if (!gates) return launch_wgrad_reduce<T>(ra, 2, st, tail);
+    const RedGrid g(ra, 2);
+    hipLaunchKernelGGL(uome_bwd_finish_kernel, dim3(g.tiles + gates), dim3(256), 0, st, ra, a, g.nx, g.ny, gates);
     return hipGetLastError();
 }
 
@@ -347,7 +366,7 @@ template <typename T> struct UomeDsDhProblem : UomeDsUpProblem<T> {   // u = d_o
     }
 };
 
-hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st)
+hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st, BwdTail *tail)
 {
     typedef bf16_t T;
     hipError_t err;
@@ -402,10 +421,12 @@ hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st)
     typedef GemmTile<OutProjProblem<T>, 32, 128, 32, 1, 4, 4, GEMM_B_NK> Du32;
     typedef GemmTile<OutProjProblem<T>, 64, 128, 32, 2, 2, 4, GEMM_B_NK> Du64;
     typedef GemmTile<SmhaWgradProblem<T>, 128, 128, 32, 2, 2, 4, GEMM_A_KM> Wg;
-    if (a.d_e > 64 && (long)groups * ((a.d_e + 127) / 128) * ((a.d + 127) / 128) <= 512)
-        err = l_p <= 32 ? launch_gemm_dma_pair<Wg, Du32, 2>(wp, groups, a.d_e, a.d, xp, a.b * a.m, l_p, a.d, st)
-                        : launch_gemm_dma_pair<Wg, Du64, 2>(wp, groups, a.d_e, a.d, xp, a.b * a.m, l_p, a.d, st);
-    else {
+    const bool pair = a.d_e > 64 && (long)groups * ((a.d_e + 127) / 128) * ((a.d + 127) / 128) <= 512;
+    if (pair) {   // (and with the gate gradients)
+        const UnitGates gates{ga, UnitGates::count(ga)};
+        err = l_p <= 32 ? launch_gemm_dma_pair<Wg, Du32, 2>(wp, groups, a.d_e, a.d, xp, a.b * a.m, l_p, a.d, st, gates, gates.units)
+                        : launch_gemm_dma_pair<Wg, Du64, 2>(wp, groups, a.d_e, a.d, xp, a.b * a.m, l_p, a.d, st, gates, gates.units);
+    } else {
         if (l_p <= 32) err = launch_gemm_dma<OutProjProblem<T>, 32, 128, 32, 1, 4, 4, 2, GEMM_B_NK>(xp, a.b * a.m, l_p, a.d, st);
         else err = launch_gemm_dma<OutProjProblem<T>, 64, 128, 32, 2, 2, 4, 2, GEMM_B_NK>(xp, a.b * a.m, l_p, a.d, st);
         if (err == hipSuccess) err = launch_gemm_dma_auto<GEMM_A_KM>(wp, groups, a.d_e, a.d, 0, l_p, st);
@@ -416,7 +437,7 @@ hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st)
     ra.w = a.wgrad; ra.part_end = a.part_end;
     ra.dst[0] = a.d_a_out; ra.transposed[0] = 0;
     ra.dst[1] = a.d_a_in; ra.transposed[1] = 1;
-    return launch_wgrad_reduce_gates<T, false>(ra, 2, ga, st);
+    return pair ? launch_wgrad_reduce<T>(ra, 2, st, tail) : launch_wgrad_reduce_gates<T, false>(ra, 2, ga, st);
 }
 
 }  // namespace uoe

@@ -9,15 +9,6 @@ namespace uoe {
 // Set s goes to dst[s], stored as [n][M][N] or transposed as [n][N][M].  64x64 tiles, 16-byte loads with four rows of
 // a part in flight per thread, 8-byte stores (bf16; straight, or transposed through LDS): the launch is a plain stream
 // of the partial tiles (134 MB on the largest shape: 47.7 us with 32x32 tiles and 4-byte loads).
-struct WgradReduceArgs {
-    const float *partial;
-    void *dst[4];   // storage type T of the launch
-    int transposed[4];
-    int n, M, N;
-    const int32_t *part_end;   // [chunks, 32] first part id behind an expert's
-    WgradPlan w;
-};
-
 constexpr int RED_T = 64;
 template <typename T> __device__ __forceinline__ void store4_as(T *p, float4 v);
 template <> __device__ __forceinline__ void store4_as<float>(float *p, float4 v) { *reinterpret_cast<float4 *>(p) = v; }
@@ -26,9 +17,10 @@ template <> __device__ __forceinline__ void store4_as<bf16_t>(bf16_t *p, float4 
     *reinterpret_cast<uint2 *>(p) = make_uint2(pack2_bf16(v.x, v.y), pack2_bf16(v.z, v.w));
 }
 // CHUNKED: more than 128 samples are possible
-template <typename T, bool CHUNKED> __device__ __forceinline__ void wgrad_reduce_tile(const WgradReduceArgs &a, int bx, int by, int bz)
+typedef float (*RedTile)[RED_T + 1];   // the workgroup's RED_T x RED_T tile in LDS
+constexpr size_t RED_LDS = sizeof(float) * RED_T * (RED_T + 1);
+template <typename T, bool CHUNKED> __device__ __forceinline__ void wgrad_reduce_tile(const WgradReduceArgs &a, RedTile tile, int bx, int by, int bz)
 {
-    __shared__ float tile[RED_T][RED_T + 1];
     const int set = bz / a.n, e = bz - set * a.n, r0 = by * RED_T, c0 = bx * RED_T;
     const int tx = (threadIdx.x & 15) * 4, ty = threadIdx.x >> 4;
     const int col = c0 + tx;                 // M and N are multiples of 8
@@ -80,13 +72,17 @@ template <typename T, bool CHUNKED> __device__ __forceinline__ void wgrad_reduce
     }
 }
 
-// Gate gradients of one unit (sample, slot) of a data-selected block from the row sums r_t = dL/dw_t: wave w takes
-// picks w, w+4, ...; d_patch_gate of the unit's expert [m] (zero where it picked nothing) and its d_expert_gate.  The
+// Gate gradients of one unit (sample, slot) of a data-selected block from the row sums r_t = dL/dw_t, by NT threads: wave w takes
+// picks w, w + waves, ...; d_patch_gate of the unit's expert [m] (zero where it picked nothing) and its d_expert_gate.  The
 // unit of slot 0 also writes the zeros of the experts its sample did not select.
-__device__ __forceinline__ void unit_gate_block(const SmhaBwdArgs &a, int g)
+struct UnitGateLds {
+    float ps[1024], row[1024];
+    uint32_t chosen;
+};
+template <int NT> __device__ __forceinline__ void unit_gate_block(const SmhaBwdArgs &a, int g, void *lds)
 {
-    __shared__ float ps[1024], row[1024];
-    __shared__ uint32_t chosen;
+    float *const ps = static_cast<UnitGateLds *>(lds)->ps, *const row = static_cast<UnitGateLds *>(lds)->row;
+    uint32_t &chosen = static_cast<UnitGateLds *>(lds)->chosen;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = a.f.n, m = a.f.m, c = a.f.c;
     const int l_p = a.f.l / m, l_a = c * l_p;
     const int bb = g / a.f.k, i = clampi(a.f.expert_idx[g], n);
@@ -100,20 +96,20 @@ __device__ __forceinline__ void unit_gate_block(const SmhaBwdArgs &a, int g)
             if (chosen >> e & 1u) continue;
             if (a.d_expert_gate && tid == 0) a.d_expert_gate[(size_t)bb * n + e] = 0.f;
             if (a.d_patch_gate)
-                for (int j = tid; j < m; j += 256) a.d_patch_gate[((size_t)bb * n + e) * m + j] = 0.f;
+                for (int j = tid; j < m; j += NT) a.d_patch_gate[((size_t)bb * n + e) * m + j] = 0.f;
         }
     }
-    for (int j = tid; j < m; j += 256) row[j] = 0.f;
+    for (int j = tid; j < m; j += NT) row[j] = 0.f;
     if (!ge_on && !gp_on) {
         if (a.d_expert_gate && tid == 0) a.d_expert_gate[(size_t)bb * n + i] = 0.f;
         if (a.d_patch_gate)
-            for (int j = tid; j < m; j += 256) a.d_patch_gate[((size_t)bb * n + i) * m + j] = 0.f;
+            for (int j = tid; j < m; j += NT) a.d_patch_gate[((size_t)bb * n + i) * m + j] = 0.f;
         return;
     }
     const float *rt = a.rt + (size_t)g * l_a;
     const int parts = a.rt_parts > 1 ? a.rt_parts : 1;
     const size_t part_stride = (size_t)a.f.b * a.f.k * l_a;
-    for (int t = wave; t < c; t += 4) {
+    for (int t = wave; t < c; t += NT / 64) {
         float v = 0.f;
         for (int q = lane; q < l_p; q += 64)
 #pragma unroll 4
@@ -127,9 +123,9 @@ __device__ __forceinline__ void unit_gate_block(const SmhaBwdArgs &a, int g)
     if (a.d_patch_gate) {
         const float ge = ge_on ? a.expert_gate[(size_t)bb * n + i] : 1.0f;
         if (gp_on)
-            for (int t = tid; t < c; t += 256) row[clampi(pid[t], m)] = ge * ps[t];
+            for (int t = tid; t < c; t += NT) row[clampi(pid[t], m)] = ge * ps[t];
         __syncthreads();
-        for (int j = tid; j < m; j += 256) a.d_patch_gate[((size_t)bb * n + i) * m + j] = row[j];
+        for (int j = tid; j < m; j += NT) a.d_patch_gate[((size_t)bb * n + i) * m + j] = row[j];
     }
     if (a.d_expert_gate && wave == 0) {
         float v = 0.f;
@@ -140,31 +136,59 @@ __device__ __forceinline__ void unit_gate_block(const SmhaBwdArgs &a, int g)
     }
 }
 
-// the last launch of a data-selected block: the gate gradients' units (the longer chains, hence first) and the
-// weight-gradient tiles
+// Gate gradients beside another launch's work: `units` workgroups behind its own
+struct UnitGates {
+    static constexpr size_t LDS = sizeof(UnitGateLds);
+    SmhaBwdArgs a;
+    int units;
+    template <int NT> __device__ __forceinline__ void run(int block, void *lds) const
+    {
+        if (block < units) unit_gate_block<NT>(a, block, lds);
+    }
+    static __host__ int count(const SmhaBwdArgs &a) { return a.d_expert_gate || a.d_patch_gate ? a.f.b * a.f.k : 0; }
+};
+
+// tiles of a reduction: columns, rows, all
+struct RedGrid {
+    int nx, ny, tiles;
+    RedGrid(const WgradReduceArgs &ra, int sets) : nx((ra.N + RED_T - 1) / RED_T), ny((ra.M + RED_T - 1) / RED_T), tiles(nx * ny * sets * ra.n) {}
+};
+
+// the last launch of a data-selected block whose gates did not fit beside another: the gate gradients' units (the longer chains, hence
+// first) and the weight-gradient tiles
 template <typename T, bool CHUNKED> __global__ __launch_bounds__(256) void wgrad_reduce_gates_kernel(WgradReduceArgs ra, SmhaBwdArgs ga, int nx, int ny, int units)
 {
+    __shared__ __align__(16) unsigned char lds[RED_LDS > sizeof(UnitGateLds) ? RED_LDS : sizeof(UnitGateLds)];
     const int id = (int)blockIdx.x - units;
-    if (id >= 0) wgrad_reduce_tile<T, CHUNKED>(ra, id % nx, id / nx % ny, id / (nx * ny));
-    else unit_gate_block(ga, blockIdx.x);
+    if (id >= 0) wgrad_reduce_tile<T, CHUNKED>(ra, reinterpret_cast<RedTile>(lds), id % nx, id / nx % ny, id / (nx * ny));
+    else unit_gate_block<256>(ga, blockIdx.x, lds);
 }
 
 template <typename T, bool CHUNKED> static inline hipError_t launch_wgrad_reduce_gates(const WgradReduceArgs &ra, int sets, const SmhaBwdArgs &ga, hipStream_t st)
 {
-    const int nx = (ra.N + RED_T - 1) / RED_T, ny = (ra.M + RED_T - 1) / RED_T, tiles = nx * ny * sets * ra.n;
-    const int units = ga.d_expert_gate || ga.d_patch_gate ? ga.f.b * ga.f.k : 0;
-    hipLaunchKernelGGL((wgrad_reduce_gates_kernel<T, CHUNKED>), dim3(tiles + units), dim3(256), 0, st, ra, ga, nx, ny, units);
+    const RedGrid g(ra, sets);
+    const int units = UnitGates::count(ga);
+    hipLaunchKernelGGL((wgrad_reduce_gates_kernel<T, CHUNKED>), dim3(g.tiles + units), dim3(256), 0, st, ra, ga, g.nx, g.ny, units);
     return hipGetLastError();
 }
 
-template <typename T> __global__ __launch_bounds__(256) void wgrad_reduce_kernel(WgradReduceArgs a)
+template <typename T> __global__ __launch_bounds__(256) void wgrad_reduce_kernel(WgradReduceArgs a, int nx, int ny)
 {
-    wgrad_reduce_tile<T, true>(a, blockIdx.x, blockIdx.y, blockIdx.z);
+    __shared__ __align__(16) unsigned char lds[RED_LDS];
+    const int id = blockIdx.x;
+    wgrad_reduce_tile<T, true>(a, reinterpret_cast<RedTile>(lds), id % nx, id / nx % ny, id / (nx * ny));
 }
 
-template <typename T = bf16_t> static inline hipError_t launch_wgrad_reduce(const WgradReduceArgs &a, int sets, hipStream_t st)
+// tail not NULL: left to the launch that follows
+template <typename T> static inline hipError_t launch_wgrad_reduce(const WgradReduceArgs &a, int sets, hipStream_t st, BwdTail *tail)
 {
-    hipLaunchKernelGGL((wgrad_reduce_kernel<T>), dim3((a.N + RED_T - 1) / RED_T, (a.M + RED_T - 1) / RED_T, sets * a.n), dim3(256), 0, st, a);
+    if (tail && a.w.chunks == 1) {
+        tail->reduce = a;
+        tail->sets = sets;
+        return hipSuccess;
+    }
+    const RedGrid g(a, sets);
+    hipLaunchKernelGGL((wgrad_reduce_kernel<T>), dim3(g.tiles), dim3(256), 0, st, a, g.nx, g.ny);
     return hipGetLastError();
 }
 
