@@ -363,6 +363,8 @@ hipError_t launch_smha(const SmhaArgs &a, bool bf16, hipStream_t st);
 // the caller has checked bf16 storage, d % 32 == 0 and d_h in {32, 64, 128}
 hipError_t launch_smha_qkv_attention(const SmhaArgs &a, hipStream_t st);
 hipError_t launch_uome(const UomeArgs &a, bool bf16, hipStream_t st);
+int uome_mlp_waves(const UomeArgs &a);                                      // not 0: both layers in one launch (uome_mlp.hip), bf16
+hipError_t launch_uome_mlp(const UomeArgs &a, hipStream_t st);
 hipError_t launch_uome_up(const UomeArgs &a, bool bf16, hipStream_t st);    // Eq. 38 only
 hipError_t launch_uome_down(const UomeArgs &a, bool bf16, hipStream_t st);  // Eq. 39-40 only
 hipError_t launch_uome_ds(const UomeDsArgs &a, bool bf16, hipStream_t st);

@@ -82,6 +82,7 @@ hipError_t launch_uome_down(const UomeArgs &a, bool bf16, hipStream_t st)
 
 hipError_t launch_uome(const UomeArgs &a, bool bf16, hipStream_t st)
 {
+    if (bf16 && uome_mlp_waves(a)) return launch_uome_mlp(a, st);
     const hipError_t err = launch_uome_up(a, bf16, st);
     return err != hipSuccess ? err : launch_uome_down(a, bf16, st);
 }
