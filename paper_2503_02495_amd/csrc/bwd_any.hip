@@ -66,7 +66,7 @@ template <typename T, bool NK> struct UomeBwdProj : PlainEpilogue {
     static constexpr bool kF32Out = true, kPrepare = false;
     __device__ int rows(int) const { return l; }
     __device__ int ncols() const { return kact * d_e; }
-    __device__ int kseg(int) const { return d; }
+    __host__ __device__ int kseg(int) const { return d; }
     __device__ int kdim(int) const { return d; }
     __device__ long b_stride() const { return d_e; }
     __device__ uint32_t seg_ctx(int, int) const { return 0; }
@@ -193,7 +193,7 @@ template <typename T> struct UomeBwdDu : PlainEpilogue {
     static constexpr bool kPrepare = false;
     __device__ int rows(int) const { return l; }
     __device__ int ncols() const { return d; }
-    __device__ int kseg(int) const { return d_e; }
+    __host__ __device__ int kseg(int) const { return d_e; }
     __device__ int kdim(int) const { return kact * kSegParts * d_e; }
     __device__ long b_stride() const { return 0; }
     // the engine asks for segment `seg`'s context directly before its loop and for table entry e = seg / parts in it:
@@ -231,7 +231,7 @@ template <typename T> struct UomeBwdWgrad : PlainEpilogue {
     static constexpr bool kF32Out = true, kPrepare = true;
     __device__ int rows(int) const { return d_e; }
     __device__ int ncols() const { return d; }
-    __device__ int kseg(int) const { return range; }
+    __host__ __device__ int kseg(int) const { return range; }
     __device__ int seg_len(uint32_t ctx) const { return min(range, l - (int)(ctx >> 12) * range); }
     // (range is a multiple of 32, or l; one short K-step in 16 and more unbalances the sums of either sign too little to matter)
     __device__ int seg_tail(int step) const { return range < l && l >= 512 ? 0 : l % step; }
@@ -347,7 +347,6 @@ template <typename T> hipError_t uome_backward_any(const UomeBwdArgs &a, hipStre
     T *h = static_cast<T *>(a.h_op), *dz = static_cast<T *>(a.dz_op);
     UomeBwdArgs ga = a;   // for the gate gradient
     constexpr bool F32 = std::is_same<T, float>::value;
-    constexpr int FZ = GEMM_TAIL, FH = GEMM_TAIL | GEMM_B_NK;
     const bool large = a.l > 64 && (long)a.b * ((a.l + 127) / 128) * ((W + 127) / 128) >= 256;
     // one launch for Z, dH and what becomes of them, where tiles of 64 rows and more are the choice anyway and the gate
     // gradient's sums fit the room they have (a wave's rows: 64 of the large tiles, 32 of the small ones)
@@ -356,16 +355,20 @@ template <typename T> hipError_t uome_backward_any(const UomeBwdArgs &a, hipStre
     if (a.l > 32 && sums <= room) {
         hp.expert_gate = (a.flags & F_GATE_EXPERT) ? a.expert_gate : nullptr;
         hp.h = h; hp.dz = dz; hp.gpart = a.gpart; hp.gchunks = ga.gchunks = (int)sums;
-        if constexpr (F32) {
-            // (few tiles, on the fp32 instruction as in tail_tile: 8 x 77 x 200 x 272 47.3 -> 44.8 us for the pass)
-            const bool few = (long)a.b * ((a.l + 63) / 64) * ((W + 63) / 64) <= 256;
-            err = large ? launch_gemm_dma_dual<FZ, FH, 128, 128, 32, 2, 4, 2, 2>(zp, hp, a.b, a.l, W, st)
-                  : few ? launch_gemm_dma_dual<FZ | GEMM_EXACT, FH | GEMM_EXACT, 64, 64, 32, 2, 2, 3, 2>(zp, hp, a.b, a.l, W, st)
-                        : launch_gemm_dma_dual<FZ, FH, 64, 64, 32, 2, 2, 3, 2>(zp, hp, a.b, a.l, W, st);
-        }
-        else
-            err = large ? launch_gemm_dma_dual<FZ, FH, 128, 128, 32, 2, 4, 3, 4>(zp, hp, a.b, a.l, W, st)
-                        : launch_gemm_dma_dual<FZ, FH, 64, 128, 32, 2, 2, 4, 2>(zp, hp, a.b, a.l, W, st);
+        const auto both = [&](auto tail) {
+            constexpr int FZ = decltype(tail)::value, FH = FZ | GEMM_B_NK;
+            if constexpr (F32) {
+                // (few tiles, on the fp32 instruction as in tail_tile: 8 x 77 x 200 x 272 47.3 -> 44.8 us for the pass)
+                const bool few = (long)a.b * ((a.l + 63) / 64) * ((W + 63) / 64) <= 256;
+                return large ? launch_gemm_dma_dual<FZ, FH, 128, 128, 32, 2, 4, 2, 2>(zp, hp, a.b, a.l, W, st)
+                      : few ? launch_gemm_dma_dual<FZ | GEMM_EXACT, FH | GEMM_EXACT, 64, 64, 32, 2, 2, 3, 2>(zp, hp, a.b, a.l, W, st)
+                            : launch_gemm_dma_dual<FZ, FH, 64, 64, 32, 2, 2, 3, 2>(zp, hp, a.b, a.l, W, st);
+            }
+            else
+                return large ? launch_gemm_dma_dual<FZ, FH, 128, 128, 32, 2, 4, 3, 4>(zp, hp, a.b, a.l, W, st)
+                            : launch_gemm_dma_dual<FZ, FH, 64, 128, 32, 2, 2, 4, 2>(zp, hp, a.b, a.l, W, st);
+        };
+        err = a.d % 32 ? both(std::integral_constant<int, GEMM_TAIL>{}) : both(std::integral_constant<int, 0>{});   // (as launch_gemm_tail)
         if (err != hipSuccess) return err;
     } else {
         if ((err = launch_gemm_tail<0>(zp, a.b, a.l, W, st)) != hipSuccess) return err;
@@ -866,7 +869,7 @@ template <typename T> struct SmhaBwdWgrad : PlainEpilogue {
     static constexpr int kMaxSegments = BWD_ANY_SEGMENTS;
     __device__ int rows(int) const { return d_h; }
     __device__ int ncols() const { return d; }
-    __device__ int kseg(int) const { return l_p; }
+    __host__ __device__ int kseg(int) const { return l_p; }
     __device__ int kdim(int) const { return 0; }
     __device__ long b_stride() const { return d; }
     __device__ int width(int g) const { return parts.set(g) < 3 ? 3 * d_h : d_h; }

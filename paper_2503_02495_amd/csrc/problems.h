@@ -130,7 +130,7 @@ template <typename T, bool F32 = false, bool ROPE = false> struct QkvProblem {
         const int t = r / l_p;
         return clampi(patch_idx[((size_t)bb * n + i) * c + t], m) * l_p + (r - t * l_p);
     }
-    __device__ int kseg(int) const { return d; }
+    __host__ __device__ int kseg(int) const { return d; }
     __device__ long b_stride() const { return d_h; }
     // K is one segment, rows and columns are resolved once before the loop
     __device__ uint32_t seg_ctx(int, int) const { return 0; }
@@ -218,7 +218,7 @@ template <typename T> struct OutProjProblem {
     __device__ int rows(int g) const { return min(gp, m - first_patch(g)) * l_p; }
     __device__ int kdim(int) const { return 0; }  // prepare() supplies K
     __device__ int ncols() const { return d; }
-    __device__ int kseg(int) const { return d_h; }
+    __host__ __device__ int kseg(int) const { return d_h; }
     __device__ long b_stride() const { return d; }
     __device__ float epi_f32(float val, float) const { return val; }
     __device__ void put4(int g, int r, int nn, float4 val) const
@@ -353,7 +353,7 @@ template <typename T, bool RAW = false, bool EXACT = false, bool SEL = false> st
     __device__ int rows(int) const { return l; }
     __device__ int kdim(int) const { return d; }
     __device__ int ncols() const { return kact * d_e; }
-    __device__ int kseg(int) const { return d; }
+    __host__ __device__ int kseg(int) const { return d; }
     __device__ long b_stride() const { return d_e; }
     // no per-segment lookups (K is one segment; the column's expert is resolved once, before the loop)
     __device__ uint32_t seg_ctx(int, int) const { return 0; }
@@ -404,7 +404,7 @@ template <typename T, bool EXACT = false> struct UomeDsUpProblem {
     __device__ int rows(int) const { return l_a; }
     __device__ int kdim(int) const { return d; }
     __device__ int ncols() const { return d_e; }
-    __device__ int kseg(int) const { return d; }
+    __host__ __device__ int kseg(int) const { return d; }
     __device__ long b_stride() const { return d_e; }
     __device__ int expert(int g) const { return clampi(expert_idx[g], n); }
     __device__ int patch(int g, int r) const
@@ -457,7 +457,7 @@ template <typename T> struct UomeDownProblem {
     __device__ int rows(int) const { return l; }
     __device__ int kdim(int) const { return kact * d_e; }
     __device__ int ncols() const { return d; }
-    __device__ int kseg(int) const { return d_e; }
+    __host__ __device__ int kseg(int) const { return d_e; }
     __device__ long b_stride() const { return d; }
     // the segment's expert, looked up once before the loop
     __device__ uint32_t seg_ctx(int g, int seg) const { return (uint32_t)clampi(expert_idx[g * kact + clampi(seg, kact)], n); }
@@ -727,7 +727,7 @@ template <typename T> struct WgradProblem {
     static constexpr bool kF32Out = true;
     __device__ int rows(int) const { return M; }
     __device__ int ncols() const { return N; }
-    __device__ int kseg(int) const { return range; }
+    __host__ __device__ int kseg(int) const { return range; }
     __device__ long a_stride(int) const { return (long)kact * M; }
     __device__ long b_stride() const { return N; }
     __device__ int kdim(int) const { return 0; }  // prepare() supplies K
@@ -789,7 +789,7 @@ template <typename T> struct SmhaWgradProblem {
     static constexpr bool kF32Out = true;
     __device__ int rows(int) const { return M; }
     __device__ int ncols() const { return d; }
-    __device__ int kseg(int) const { return l_p; }
+    __host__ __device__ int kseg(int) const { return l_p; }
     __device__ long a_stride(int g) const { return row_len[parts.set(g)]; }
     __device__ long b_stride() const { return d; }
     __device__ int kdim(int) const { return 0; }

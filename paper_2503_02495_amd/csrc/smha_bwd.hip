@@ -39,7 +39,7 @@ template <typename T> struct SmhaDoProblem {
     __device__ int rows(int) const { return l_a; }
     __device__ int kdim(int) const { return d; }
     __device__ int ncols() const { return d_h; }
-    __device__ int kseg(int) const { return d; }
+    __host__ __device__ int kseg(int) const { return d; }
     __device__ long b_stride() const { return 0; }
     __device__ uint32_t seg_ctx(int, int) const { return 0; }
     __device__ int expert(int g) const { return clampi(expert_idx[g], n); }

@@ -74,7 +74,7 @@ template <typename T> struct UomeDhProblem {
     __device__ int rows(int) const { return l; }
     __device__ int kdim(int) const { return d; }
     __device__ int ncols() const { return kact * d_e; }
-    __device__ int kseg(int) const { return d; }
+    __host__ __device__ int kseg(int) const { return d; }
     __device__ long b_stride() const { return 0; }
     __device__ uint32_t seg_ctx(int, int) const { return 0; }
     __device__ int expert(int g, int nn) const { return clampi(expert_idx[g * kact + nn / d_e], n); }
