@@ -86,8 +86,8 @@ template <typename T, bool NK> struct UomeBwdProj : PlainEpilogue {
 // dH again, with the tile of Z in the accumulators beside it: H = w SiLU(Z), dZ = w dH SiLU'(Z) (operand layout [b, l, k,
 // parts, d_e]) and the sums of dH SiLU(Z) for the gate gradient, one per wave's rows and 8 columns (a wave's 32 columns may
 // belong to several experts, 8 never do).  Neither Z nor dH reaches memory: 8 bytes written per element instead of
-// 8 written, 8 read and 8 written (uome_bwd_any_mid): 128 x 196 x 384 x 768 in bf16 34.9 + 42.9 + 56.9 -> 100.7 us, bound by the
-// epilogue's arithmetic (exact exponential and division) and its stores; with 8-byte stores straight from the
+// 8 written, 8 read and 8 written (uome_bwd_any_mid): 128 x 196 x 384 x 768 in bf16 34.9 + 42.9 + 56.9 -> 88 us, bound by the
+// epilogue's arithmetic (exact exponential and reciprocal) and its stores; with 8-byte stores straight from the
 // accumulators, 16 bytes of a row at a time, the vit layer's forward + backward gained 11 us instead of 34.
 template <typename T> struct UomeBwdDhPair : UomeBwdProj<T, true> {
     static constexpr bool kPairOut = true, kColScale = true;
@@ -103,59 +103,74 @@ template <typename T> struct UomeBwdDhPair : UomeBwdProj<T, true> {
     __device__ void pair_out(f32x16_t (&acc)[TM][TN], f32x16_t *z, uint16_t (*stage)[SPITCH], const float *colw, int g, int grow0, int gcol0, int M, int N,
                              int lane) const
     {
-        constexpr int PARTS = parts_of<T>::value;
-        const int lr = lane & 31, lh = lane >> 5, d_e = this->d_e;
-        auto at = [&](int grow, int col) {   // operand layout, first part
-            const int s = col / d_e;
-            return (((size_t)g * this->l + grow) * this->kact + s) * PARTS * d_e + (col - s * d_e);
-        };
+        constexpr int PARTS = parts_of<T>::value, WC = TN * 4;
+        const int lr = lane & 31, lh = lane >> 5, d_e = this->d_e, rows = M - grow0;
+        if (rows <= 0) return;
+        // operand layout, first part: the tile's rows from `first` on, `step` apart, and a place in a row.  Divisions by d_e are vector work of 20
+        // instructions each: one a lane, and a walk over the wave's columns (with one for each 16-byte piece, the sigmoid by a
+        // division and the blocks of rows behind the sample's end worked as well, Z and dH of 128 x 196 x 384 x 768 took 98 us, vector instructions issuing
+        // 74 % of it; 88 so)
+        const uint32_t step = (uint32_t)this->kact * PARTS * d_e;
+        const size_t first = ((size_t)g * this->l + grow0) * step;
         // in place: z becomes H, the accumulators dZ
+        int s = gcol0 / d_e, c = gcol0 - s * d_e;   // the slot and its column of 8 columns of the wave's (uniform)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int c8 = gcol0 + j * 32 + q * 8;   // uniform over the wave
-                if (c8 >= N) continue;
+                if (gcol0 + j * 32 + q * 8 >= N) continue;
                 const float w = colw[j * 4 + q];
                 float part = 0.f;
 #pragma unroll
                 for (int i = 0; i < TM; ++i) {
-                    const int grow = grow0 + i * 32 + lr;
+                    if (i && i * 32 >= rows) break;
                     float ps = 0.f;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const float zv = z[i * TN + j][q * 4 + e], dv = acc[i][j][q * 4 + e];
-                        const float sig = 1.0f / (1.0f + expf(-zv)), v = zv * sig;
+                        const float sig = sigmoid_of(expf(-zv)), v = zv * sig;
                         ps = fmaf(dv, v, ps);
                         z[i * TN + j][q * 4 + e] = v * w;
                         acc[i][j][q * 4 + e] = dv * w * (sig * (1.0f + zv * (1.0f - sig)));
                     }
-                    if (grow < M) part += ps;
+                    if (i * 32 + lr < rows) part += ps;
                 }
 #pragma unroll
                 for (int off = 1; off < 64; off <<= 1) part += __shfl_xor(part, off, 64);
-                if (lane == 0 && grow0 < M) {
-                    const int s = c8 / d_e;
-                    gpart[((size_t)g * this->kact + s) * gchunks + (size_t)(grow0 / (TM * 32)) * (d_e / 8) + (c8 - s * d_e) / 8] = part;
+                if (lane == 0) gpart[((size_t)g * this->kact + s) * gchunks + (size_t)(grow0 / (TM * 32)) * (d_e / 8) + c / 8] = part;
+                c += 8;
+                if (c >= d_e) {
+                    c = 0;
+                    ++s;
                 }
             }
         if constexpr (PARTS == 1) {
+            s = gcol0 / d_e;
+            c = gcol0 - s * d_e;
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
+                for (int q = 0; q < 4; ++q) {
 #pragma unroll
                     for (int i = 0; i < TM; ++i) {
-                        const int grow = grow0 + i * 32 + lr, col = gcol0 + j * 32 + q * 8 + lh * 4;
-                        if (grow >= M || col >= N) continue;
+                        if (i * 32 + lr >= rows || gcol0 + j * 32 + q * 8 >= N) continue;
+                        const size_t to = first + (size_t)(i * 32 + lr) * step + s * d_e + c + lh * 4;
                         const f32x16_t &hv = z[i * TN + j], &gv = acc[i][j];
-                        *reinterpret_cast<float4 *>(h + at(grow, col)) = make_float4(hv[q * 4], hv[q * 4 + 1], hv[q * 4 + 2], hv[q * 4 + 3]);
-                        *reinterpret_cast<float4 *>(dz + at(grow, col)) = make_float4(gv[q * 4], gv[q * 4 + 1], gv[q * 4 + 2], gv[q * 4 + 3]);
+                        *reinterpret_cast<float4 *>(h + to) = make_float4(hv[q * 4], hv[q * 4 + 1], hv[q * 4 + 2], hv[q * 4 + 3]);
+                        *reinterpret_cast<float4 *>(dz + to) = make_float4(gv[q * 4], gv[q * 4 + 1], gv[q * 4 + 2], gv[q * 4 + 3]);
                     }
+                    c += 8;
+                    if (c >= d_e) {
+                        c = 0;
+                        ++s;
+                    }
+                }
         } else {
+            const int col = gcol0 + lane % WC * 8, sl = col / d_e;
+            const uint32_t place = sl * PARTS * d_e + (col - sl * d_e);
             auto plane = [&](T *dst, auto value, bool low) {
                 stage_plane<TM, TN, SPITCH>(
-                    stage, lane,
+                    stage, lane, rows,
                     [&](int i, int j, int q) {
                         const f32x16_t &v = value(i, j);
                         uint32_t o[2];
@@ -167,8 +182,8 @@ template <typename T> struct UomeBwdDhPair : UomeBwdProj<T, true> {
                         }
                         return make_uint2(o[0], o[1]);
                     },
-                    [&](int row, int col, uint4 piece) {
-                        if (grow0 + row < M && gcol0 + col < N) store16<false>(dst + at(grow0 + row, gcol0 + col) + (low ? d_e : 0), piece);
+                    [&](int row, int, uint4 piece) {
+                        if (row < rows && col < N) store16<false>(dst + first + (size_t)row * step + place + (low ? d_e : 0), piece);
                     });
             };
             auto hv = [&](int i, int j) -> const f32x16_t & { return z[i * TN + j]; };

@@ -140,12 +140,13 @@ __device__ __forceinline__ float silu(float z) { return z / (1.0f + __expf(-z));
 // scaled back at the end, so that results below 2^-126 (z <= -87.4, where the reciprocal alone is zero) come out as a division
 // rounds them and infinite e gives 0.  The reciprocal is good to an ulp, the step squares that: what is left is one rounding, as in a
 // division, with five instructions less (layer forward + backward of the lm shape 215.9 -> 214.9 us).  The minimum hands NaN through.
-__device__ __forceinline__ float sigmoid(float z)
+__device__ __forceinline__ float sigmoid_of(float e)   // 1 / (1 + e), e >= 0
 {
     constexpr float scale = 2.3283064365386963e-10f;   // 2^-32
-    const float d = __builtin_elementwise_minimum(fmaf(__expf(-z), scale, scale), 8.507059173023462e37f), r = __builtin_amdgcn_rcpf(d);
+    const float d = __builtin_elementwise_minimum(fmaf(e, scale, scale), 8.507059173023462e37f), r = __builtin_amdgcn_rcpf(d);
     return fmaf(r, fmaf(-d, r, 1.0f), r) * scale;
 }
+__device__ __forceinline__ float sigmoid(float z) { return sigmoid_of(__expf(-z)); }
 // SiLU with the hardware exp2 and reciprocal (about 1 ulp each): for epilogues that round the
 // result to bf16 anyway
 __device__ __forceinline__ float silu_fast(float z)

@@ -166,22 +166,27 @@ __device__ __forceinline__ void wave_write_out(const P &p, uint16_t (*stage)[SPI
 
 // One 16-bit plane of a wave tile from the accumulators' layout to rows, through the wave's staging tile: words(i, j, q) are
 // the lane's 4 values of row i*32 + lr, columns j*32 + q*8 + lh*4; put(row, first column, 8 values) takes 16-byte pieces, whose
-// neighbouring lanes complete 64 bytes and more of a row (straight from the accumulators two lanes complete 16).
+// neighbouring lanes complete 64 bytes and more of a row (straight from the accumulators two lanes complete 16).  A lane's pieces are all of
+// the same columns.  rows: of the tile, that are any; blocks of 32 behind them are left out.
 template <int TM, int TN, int SPITCH, typename Words, typename Put>
-__device__ __forceinline__ void stage_plane(uint16_t (*stage)[SPITCH], int lane, Words words, Put put)
+__device__ __forceinline__ void stage_plane(uint16_t (*stage)[SPITCH], int lane, int rows, Words words, Put put)
 {
     constexpr int WC = TN * 4, NPIECE = TM * 32 * WC / 64;
     const int lr = lane & 31, lh = lane >> 5;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i) {
+        if (i && i * 32 >= rows) break;
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int q = 0; q < 4; ++q) *reinterpret_cast<uint2 *>(&stage[i * 32 + lr][j * 32 + q * 8 + lh * 4]) = words(i, j, q);
+    }
     __builtin_amdgcn_wave_barrier();
+    static_assert(64 % WC == 0, "a lane keeps its columns");
 #pragma unroll
     for (int t = 0; t < NPIECE; ++t) {
         const int c = lane + t * 64, row = c / WC, col = c % WC * 8;
+        if (t * 64 / WC % 32 == 0 && t && t * 64 / WC >= rows) break;
         put(row, col, *reinterpret_cast<const uint4 *>(&stage[row][col]));
     }
     __builtin_amdgcn_wave_barrier();

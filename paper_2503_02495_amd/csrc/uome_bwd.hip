@@ -176,7 +176,7 @@ template <typename T> struct UomeDhPairProblem : UomeDhProblem<T> {
         }
         auto plane = [&](T *dst, auto value) {
             stage_plane<TM, TN, SPITCH>(
-                stage, lane,
+                stage, lane, M - grow0,
                 [&](int i, int j, int q) {
                     const f32x16_t &v = value(i, j);
                     return make_uint2(pack2_bf16(v[q * 4], v[q * 4 + 1]), pack2_bf16(v[q * 4 + 2], v[q * 4 + 3]));

@@ -7,7 +7,8 @@
 // through LDS: 64 hidden columns of the sample's experts a stage, both layers' slices, copied by all eight waves two stages deep,
 // one barrier a stage; every fragment read feeds one product, so LDS and matrix pipes are about equally busy, and the two waves of a SIMD run
 // their SiLU under each other's products.
-// 16 x 4096 x 256, 2 of 8 experts of 128: MLP_LONGRANGE
+// 16 x 4096 x 256, 2 of 8 experts of 128: 41.8 -> 30.9 us (u and out 67 MB, 12.4; with 16 x 256 hidden columns 1.05 PFLOP/s); 16 x 4096 x 64, 4 of 256,
+// 71 -> 32 (uome_mlp_waves has more).  Four waves of 32 tokens, one a SIMD, where eight would leave compute units without work.
 #include "common.h"
 #include "problems.h"
 #include "gemm_mfma.h"
