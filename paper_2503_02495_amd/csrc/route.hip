@@ -41,11 +41,14 @@ __host__ __device__ constexpr int b_pitch16(int cols)
 int route_tokens_per_chunk(int b, int l)
 {
     // aim for >= ~512 workgroups but keep a chunk within [16, 64] tokens (longer chunks stream
-    // better: measured 3.3 / 3.6 / 3.9 TB/s at 16 / 32 / 64 tokens on the largest shape)
+    // better: measured 3.3 / 3.6 / 3.9 TB/s at 16 / 32 / 64 tokens on the largest shape); from 4 on below 8192 tokens, where 16
+    // leave compute units idle and a chunk is a chain of its own (fp32 forward, 16 / 8 / 4 tokens at least: 2 x 64 x 64 46.8 / 43.0 / 41.7 us, 2 x 512 x 512
+    // 101.5 / 95.2 / 93.9, 4 x 512 x 256 56.7 / 53.0 / 52.3, 8 x 512 x 512, which takes 8, 147.1 / 143.7)
     long tc = ((long)b * l) / 512;
     if (tc > l / 8) tc = l / 8;  // at least ~8 chunks per sample so the last, short chunk does not dominate
     tc = (tc / 4) * 4;
-    if (tc < 16) tc = 16;
+    const int least = (long)b * l < 8192 ? 4 : 16;
+    if (tc < least) tc = least;
     if (tc > 64) tc = 64;
     if (tc > l) tc = l;
     return (int)tc;
@@ -132,7 +135,10 @@ int route_data_tokens_per_chunk(int b, int l, int d, int n, int m, bool bf16)
         return tokens > 16 * 1024 && m <= DATA_FOLD_TILES * 16 && !selected(DATA_TOKENS) && selected(2 * DATA_TOKENS) ? 2 * DATA_TOKENS : DATA_TOKENS;
     }
     if (route_stream_plan(b, l, d, n, bf16, true).ok) return 64;
-    return route_tokens_per_chunk(b, l);
+    // chunks of fewer than 16 tokens only where route_select still adds up the partials
+    int tc = route_tokens_per_chunk(b, l);
+    while (tc < 16 && tc < l && (n * m > 512 || (long)n * m * ((l + tc - 1) / tc) > 16384)) tc = 2 * tc < l ? 2 * tc : l;
+    return tc < 16 ? tc : (tc > 16 && (long)b * l < 8192 ? 16 : tc);
 }
 
 constexpr int ROUTE_THREADS = 256;
