@@ -679,11 +679,20 @@ __device__ __forceinline__ void route_expert_mfma_body(const RouteArgs &a, int c
     }
 }
 
+// Workgroups are dealt round the eight XCDs: consecutive chunks go to the workgroups of one, whose L2 then completes the 128-byte lines
+// that 32 chunks' partials of one (sample, expert) share; with the chunk as the block index a line is written from eight L2s.  Forward of
+// 128 x 196 x 384: 131.0 -> 129.7 us, 8 x 512 x 512: 59.2 -> 58.7, 16 x 4096 x 256: 103.1 -> 102.6, 6 x 1000 x 360: 73.3 -> 72.7.
+__device__ __forceinline__ int chunk_of(int id, int nchunks)
+{
+    const int x = id & 7;
+    return x * (nchunks / 8) + min(x, nchunks % 8) + (id >> 3);
+}
+
 template <int RT, int CT>
 __global__ __launch_bounds__(256) void route_expert_mfma_kernel(RouteArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    route_expert_mfma_body<RT, CT>(a, blockIdx.x, blockIdx.y * RT * 16, smem);
+    route_expert_mfma_body<RT, CT>(a, chunk_of(blockIdx.x, a.nchunks), blockIdx.y * RT * 16, smem);
 }
 
 // Both routers of a block in one launch (they are independent and both stream x): workgroups
@@ -699,7 +708,7 @@ __global__ __launch_bounds__(256, CT == 1 ? 4 : 2) void route_expert_data_kernel
         route_data_mfma_body<CT, KS>(a, id % a.nchunks_d, id / a.nchunks_d, smem);
     } else {
         const int f = id - n_data;
-        route_expert_mfma_body<RT, CT>(a, f % a.nchunks, (f / a.nchunks) * RT * 16, smem);
+        route_expert_mfma_body<RT, CT>(a, chunk_of(f % a.nchunks, a.nchunks), (f / a.nchunks) * RT * 16, smem);
     }
 }
 
