@@ -295,7 +295,7 @@ hipError_t launch_uome_backward(const UomeBwdArgs &a, hipStream_t st, BwdTail *t
     if (a.d_e % 64 == 0 && kseg % 64 == 0 && a.d_e > 64 && du64 <= 512 && wg128 <= 512) {
         typedef GemmTile<UomeDownProblem<T>, 64, 128, 64, 2, 2, 3, GEMM_B_NK> Du;
         typedef GemmTile<WgradProblem<T>, 128, 128, 64, 2, 2, 2, GEMM_A_KM> Wg;
-        // (the gate gradient beside them, in whose launch the chip is busy; it took the reduction's out of the chain to the routers' pass)
+        // (and the gate gradient, which the routers' pass waits for: the reduction can then run beside that pass)
         err = launch_gemm_dma_pair<Wg, Du, 2>(wp, groups, a.d_e, a.d, up, a.b, a.l, a.d, st, UomeGates{a}, gates);
         gates = 0;
     } else if ((err = launch_gemm_dma_auto<GEMM_B_NK>(up, a.b, a.l, a.d, width, a.d_e, st)) == hipSuccess)
@@ -437,7 +437,7 @@ hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st, BwdTail
     ra.w = a.wgrad; ra.part_end = a.part_end;
     ra.dst[0] = a.d_a_out; ra.transposed[0] = 0;
     ra.dst[1] = a.d_a_in; ra.transposed[1] = 1;
-    return pair ? launch_wgrad_reduce<T>(ra, 2, st, tail) : launch_wgrad_reduce_gates<T, false>(ra, 2, ga, st);
+    return pair ? launch_wgrad_reduce<T>(ra, 2, st, tail) : launch_wgrad_reduce_gates<T>(ra, 2, ga, st);
 }
 
 }  // namespace uoe

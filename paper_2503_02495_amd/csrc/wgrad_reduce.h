@@ -154,21 +154,21 @@ struct RedGrid {
     RedGrid(const WgradReduceArgs &ra, int sets) : nx((ra.N + RED_T - 1) / RED_T), ny((ra.M + RED_T - 1) / RED_T), tiles(nx * ny * sets * ra.n) {}
 };
 
-// the last launch of a data-selected block whose gates did not fit beside another: the gate gradients' units (the longer chains, hence
-// first) and the weight-gradient tiles
-template <typename T, bool CHUNKED> __global__ __launch_bounds__(256) void wgrad_reduce_gates_kernel(WgradReduceArgs ra, SmhaBwdArgs ga, int nx, int ny, int units)
+// the last launch of a data-selected MLP block whose gates did not fit beside another (at most 128 samples): the gate gradients' units
+// (the longer chains, hence first) and the weight-gradient tiles
+template <typename T> __global__ __launch_bounds__(256) void wgrad_reduce_gates_kernel(WgradReduceArgs ra, SmhaBwdArgs ga, int nx, int ny, int units)
 {
     __shared__ __align__(16) unsigned char lds[RED_LDS > sizeof(UnitGateLds) ? RED_LDS : sizeof(UnitGateLds)];
     const int id = (int)blockIdx.x - units;
-    if (id >= 0) wgrad_reduce_tile<T, CHUNKED>(ra, reinterpret_cast<RedTile>(lds), id % nx, id / nx % ny, id / (nx * ny));
+    if (id >= 0) wgrad_reduce_tile<T, false>(ra, reinterpret_cast<RedTile>(lds), id % nx, id / nx % ny, id / (nx * ny));
     else unit_gate_block<256>(ga, blockIdx.x, lds);
 }
 
-template <typename T, bool CHUNKED> static inline hipError_t launch_wgrad_reduce_gates(const WgradReduceArgs &ra, int sets, const SmhaBwdArgs &ga, hipStream_t st)
+template <typename T> static inline hipError_t launch_wgrad_reduce_gates(const WgradReduceArgs &ra, int sets, const SmhaBwdArgs &ga, hipStream_t st)
 {
     const RedGrid g(ra, sets);
     const int units = UnitGates::count(ga);
-    hipLaunchKernelGGL((wgrad_reduce_gates_kernel<T, CHUNKED>), dim3(g.tiles + units), dim3(256), 0, st, ra, ga, g.nx, g.ny, units);
+    hipLaunchKernelGGL((wgrad_reduce_gates_kernel<T>), dim3(g.tiles + units), dim3(256), 0, st, ra, ga, g.nx, g.ny, units);
     return hipGetLastError();
 }
 
