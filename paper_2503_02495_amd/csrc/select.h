@@ -1,6 +1,6 @@
 // The expert selection (Eq. 21, 22): a launch of its own (route_select), or beside the first contraction of a block that selects experts only.
 //
-// As a launch it is 4 to 5 us of a chain of nine launches of 4 to 12 us, most of that its start, and the contraction behind it
+// As a launch it is 4 to 5 us of a chain of launches of 4 to 12 us, most of that its start, and the contraction behind it
 // begins with lookups of what it wrote.  Every workgroup of the UoME block's first layer can instead add up its sample's partial logits
 // (16 KB from L2 on the small shapes, four chunks a lane and load) and rank them for itself; the first one of a sample also writes the
 // results.  Forward of 8 x 512 x 512 59.2 -> 57.2 us (5.0 + 12.2 -> 14.6 traced), 6 x 1000 x 360 76.1 -> 73.2.  With the patches as well (the SMHA block's projection) the chain was as long as the
