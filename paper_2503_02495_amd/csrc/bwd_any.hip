@@ -18,6 +18,7 @@
 #include "gemm_mfma.h"
 #include "gemm_dma.h"
 #include "wgrad_reduce.h"
+#include "route_prep.h"
 
 namespace uoe {
 
@@ -394,12 +395,11 @@ template <typename T> hipError_t uome_backward_any(const UomeBwdArgs &a, hipStre
         hipLaunchKernelGGL((uome_bwd_any_mid<T>), dim3(a.gchunks, a.k, a.b), dim3(256), 0, st, a, h, dz, lpr, per_chunk);
         if ((err = hipGetLastError()) != hipSuccess) return err;
     }
-    if (a.d_gate && (err = launch_uome_gate_grad(ga, st)) != hipSuccess) return err;
-
     UomeBwdDu<T> up;
     up.dz = dz; up.a_in = a_in; up.d_out = d_out; up.expert_idx = a.expert_idx; up.d_u = static_cast<T *>(a.d_u);
     up.l = a.l; up.d = a.d; up.n = a.n; up.kact = a.k; up.d_e = a.d_e; up.flags = a.flags;
-    if ((err = launch_gemm_tail<GEMM_B_NK>(up, a.b, a.l, a.d, st)) != hipSuccess) return err;
+    Beside<UomeGates> gates{{ga}, a.d_gate ? a.b * a.k : 0};   // (before the weight gradients, whose partial tiles take the place of its sums)
+    if ((err = launch_gemm_tail<GEMM_B_NK>(up, a.b, a.l, a.d, st, &gates)) != hipSuccess) return err;
 
     UomeBwdWgrad<T> wp;
     wp.left[0] = h; wp.right[0] = d_out;
@@ -976,7 +976,13 @@ template <typename T> hipError_t smha_backward_any(const SmhaBwdArgs &a, hipStre
     wp.expert_idx = f.expert_idx; wp.patch_idx = f.patch_idx; wp.partial = a.partial;
     wp.b = f.b; wp.l = f.l; wp.d = f.d; wp.n = f.n; wp.kact = f.k; wp.m = f.m; wp.c = f.c;
     wp.l_p = l_p; wp.l_a = l_a; wp.d_h = dh; wp.parts = {4, DEALT, a.wgrad, a.part_end};
-    if ((err = launch_gemm_tail<GEMM_A_KM>(wp, wp.parts.groups(), dh, f.d, st)) != hipSuccess) return err;
+    Beside<RoutePrep<T>> prep{};
+    if (tail && tail->prep) {
+        prep.side = RoutePrep<T>(*tail->prep);
+        prep.blocks = prep.side.blocks();
+    }
+    if ((err = launch_gemm_tail<GEMM_A_KM>(wp, wp.parts.groups(), dh, f.d, st, &prep)) != hipSuccess) return err;
+    if (tail && tail->prep && !prep.blocks) tail->prep_done = 1;
     WgradReduceArgs ra{};
     ra.partial = a.partial; ra.n = f.n; ra.M = dh; ra.N = f.d;
     ra.w = a.wgrad; ra.part_end = a.part_end;

@@ -372,7 +372,6 @@ hipError_t launch_uome_ds(const UomeDsArgs &a, bool bf16, hipStream_t st);
 hipError_t launch_uome_backward(const UomeBwdArgs &a, hipStream_t st, BwdTail *tail = nullptr);
 hipError_t launch_smha_backward(const SmhaBwdArgs &a, hipStream_t st, BwdTail *tail = nullptr);
 // d_gate from the partial sums a.gpart [b, k, gchunks]
-hipError_t launch_uome_gate_grad(const UomeBwdArgs &a, hipStream_t st);
 // rotary embedding (Eq. 32) of fp32 q and k with rows of d_h
 hipError_t launch_rope_f32(const SmhaArgs &a, hipStream_t st);
 // backward passes for the shapes and storage types the 32-multiple bf16 kernels do not take

@@ -191,38 +191,6 @@ template <typename T> struct UomeDhPairProblem : UomeDhProblem<T> {
     }
 };
 
-// d_gate [b,n]: block (slot s, sample b) adds the slot's partial sums (each thread a strided
-// subset in index order, then a fixed tree) into the entry of the slot's expert; the block of slot 0
-// also writes the zeros of the experts the sample did not select (all of them without the gate flag).
-__device__ __forceinline__ void uome_bwd_gate_block(const UomeBwdArgs &a, int s, int bb, float *red)   // red: 256 floats of LDS
-{
-    const int tid = threadIdx.x;
-    const bool gated = a.flags & F_GATE_EXPERT;
-    if (s == 0 && tid < a.n) {
-        bool chosen = false;
-#pragma unroll 8
-        for (int q = 0; q < a.k; ++q) chosen |= clampi(a.expert_idx[bb * a.k + q], a.n) == tid;
-        if (!chosen || !gated) a.d_gate[(size_t)bb * a.n + tid] = 0.f;
-    }
-    if (!gated) return;
-    const float *src = a.gpart + ((size_t)bb * a.k + s) * a.gchunks;
-    float v = 0.f;
-    for (int c = tid; c < a.gchunks; c += 256) v += src[c];
-    red[tid] = v;
-    __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-        if (tid < st) red[tid] += red[tid + st];
-        __syncthreads();
-    }
-    if (tid == 0) a.d_gate[(size_t)bb * a.n + clampi(a.expert_idx[bb * a.k + s], a.n)] = red[0];
-}
-
-__global__ __launch_bounds__(256) void uome_bwd_gate_kernel(UomeBwdArgs a)
-{
-    __shared__ float red[256];
-    uome_bwd_gate_block(a, blockIdx.x, blockIdx.y, red);
-}
-
 // the last launch of the expert-selection pass where the gates did not fit beside another: the gate gradient's blocks and the
 // weight-gradient tiles
 __global__ __launch_bounds__(256) void uome_bwd_finish_kernel(WgradReduceArgs ra, UomeBwdArgs a, int nx, int ny, int gates)
@@ -230,24 +198,7 @@ __global__ __launch_bounds__(256) void uome_bwd_finish_kernel(WgradReduceArgs ra
     __shared__ __align__(16) unsigned char lds[RED_LDS];
     const int id = (int)blockIdx.x - gates;
     if (id >= 0) wgrad_reduce_tile<bf16_t, false>(ra, reinterpret_cast<RedTile>(lds), id % nx, id / nx % ny, id / (nx * ny));
-    else uome_bwd_gate_block(a, blockIdx.x % a.k, blockIdx.x / a.k, reinterpret_cast<float *>(lds));
-}
-
-// the gate gradient's blocks behind the tiles of another launch
-struct UomeGates {
-    static constexpr size_t LDS = 256 * sizeof(float);
-    UomeBwdArgs a;
-    template <int NT> __device__ __forceinline__ void run(int block, void *lds) const
-    {
-        static_assert(NT == 256, "256 threads");
-        uome_bwd_gate_block(a, block % a.k, block / a.k, static_cast<float *>(lds));
-    }
-};
-
-hipError_t launch_uome_gate_grad(const UomeBwdArgs &a, hipStream_t st)
-{
-    hipLaunchKernelGGL(uome_bwd_gate_kernel, dim3(a.k, a.b), dim3(256), 0, st, a);
-    return hipGetLastError();
+    else uome_bwd_gate_block<256>(a, blockIdx.x % a.k, blockIdx.x / a.k, reinterpret_cast<float *>(lds));
 }
 
 hipError_t launch_uome_ds_backward(const UomeBwdArgs &a, hipStream_t st, BwdTail *tail);
