@@ -189,6 +189,8 @@ struct RouteArgs {
     int b, l, d, n, k, m, c;
     int tc, nchunks;                          // expert router: tokens per chunk, chunks per sample
     int tc_d, nchunks_d;                      // data router: the same
+    int zgroups, zlen, zmore;                 // zpart's order along a row (select.h); zinv = 1 / zlen, zinv_more = 1 / (zlen + 1)
+    float zinv, zinv_more;
     float *zpart, *gpart;                     // [b, n, nchunks], [nchunks_d, b, n*m]
     float *gred;                              // [b, n*m]
     float *t1;                                // [b, l, n]: per-token expert scores x W_B of the one-pass kernel
@@ -389,7 +391,7 @@ hipError_t launch_probe_read(const void *src, size_t bytes, uint32_t *sink, hipS
 hipError_t launch_probe_mfma(const void *operands, int iters, float *sink, hipStream_t st);
 
 // host-side sizing shared by api.hip and the launchers
-int route_tokens_per_chunk(int b, int l);
+int route_tokens_per_chunk(int b, int l, bool bf16);
 int route_expert_mfma_tokens_per_chunk(int b, int l, int d, int n);
 int route_data_tokens_per_chunk(int b, int l, int d, int n, int m, bool bf16);
 // streaming router kernel: applicability and launch shape (host side)

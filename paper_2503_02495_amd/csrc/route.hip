@@ -38,16 +38,16 @@ __host__ __device__ constexpr int b_pitch16(int cols)
     return p;
 }
 
-int route_tokens_per_chunk(int b, int l)
+int route_tokens_per_chunk(int b, int l, bool bf16)
 {
     // aim for >= ~512 workgroups but keep a chunk within [16, 64] tokens (longer chunks stream
-    // better: measured 3.3 / 3.6 / 3.9 TB/s at 16 / 32 / 64 tokens on the largest shape); from 4 on below 8192 tokens, where 16
+    // better: measured 3.3 / 3.6 / 3.9 TB/s at 16 / 32 / 64 tokens on the largest shape); fp32: from 4 on below 8192 tokens, where 16
     // leave compute units idle and a chunk is a chain of its own (fp32 forward, 16 / 8 / 4 tokens at least: 2 x 64 x 64 46.8 / 43.0 / 41.7 us, 2 x 512 x 512
     // 101.5 / 95.2 / 93.9, 4 x 512 x 256 56.7 / 53.0 / 52.3, 8 x 512 x 512, which takes 8, 147.1 / 143.7)
     long tc = ((long)b * l) / 512;
     if (tc > l / 8) tc = l / 8;  // at least ~8 chunks per sample so the last, short chunk does not dominate
     tc = (tc / 4) * 4;
-    const int least = (long)b * l < 8192 ? 4 : 16;
+    const int least = !bf16 && (long)b * l < 8192 ? 4 : 16;
     if (tc < least) tc = least;
     if (tc > 64) tc = 64;
     if (tc > l) tc = l;
@@ -136,7 +136,7 @@ int route_data_tokens_per_chunk(int b, int l, int d, int n, int m, bool bf16)
     }
     if (route_stream_plan(b, l, d, n, bf16, true).ok) return 64;
     // chunks of fewer than 16 tokens only where route_select still adds up the partials
-    int tc = route_tokens_per_chunk(b, l);
+    int tc = route_tokens_per_chunk(b, l, bf16);
     while (tc < 16 && tc < l && (n * m > 512 || (long)n * m * ((l + tc - 1) / tc) > 16384)) tc = 2 * tc < l ? 2 * tc : l;
     return tc < 16 ? tc : (tc > 16 && (long)b * l < 8192 ? 16 : tc);
 }
@@ -241,7 +241,7 @@ __device__ __forceinline__ void route_partial(const RouteArgs &a, unsigned char 
         float s = 0.f;
 #pragma unroll
         for (int w = 0; w < ROUTE_WAVES; ++w) s += zsh[w * NMAX + tid];
-        a.zpart[zpart_at(a, chunk, bb, tid)] = s;
+        a.zpart[zpart_at(a, zpart_place(a, chunk), bb, tid)] = s;
     }
     if (HAS_D) {
         const T *w_a = static_cast<const T *>(a.w_a);
@@ -600,8 +600,9 @@ __global__ __launch_bounds__(ROUTE_THREADS, NTILE == 1 ? 4 : 2) void route_data_
 template <int RT, int CT> constexpr size_t route_expert_mfma_lds() { return sizeof(float) * 4 * RT * 16 * (CT * 16 + 1); }
 
 template <int RT, int CT>
-__device__ __forceinline__ void route_expert_mfma_body(const RouteArgs &a, int chunk, int b0, unsigned char *smem)
+__device__ __forceinline__ void route_expert_mfma_body(const RouteArgs &a, int place, int b0, unsigned char *smem)
 {
+    const int chunk = zpart_chunk(a, place);
     float(*zsh)[RT * 16][CT * 16 + 1] = reinterpret_cast<float(*)[RT * 16][CT * 16 + 1]>(smem);  // [4 waves]
     constexpr int U = RT == 4 ? 2 : 4;  // steps whose loads are in flight together (four: no third wave a SIMD beside 64 samples' rows)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -675,14 +676,13 @@ __device__ __forceinline__ void route_expert_mfma_body(const RouteArgs &a, int c
     for (int o = tid; o < RT * 16 * CT * 16; o += 256) {
         const int row = o / (CT * 16), col = o - row * (CT * 16);
         if (b0 + row < b && col < n)
-            a.zpart[zpart_at(a, chunk, b0 + row, col)] = (zsh[0][row][col] + zsh[1][row][col]) + (zsh[2][row][col] + zsh[3][row][col]);
+            a.zpart[zpart_at(a, place, b0 + row, col)] = (zsh[0][row][col] + zsh[1][row][col]) + (zsh[2][row][col] + zsh[3][row][col]);
     }
 }
 
-// Workgroups are dealt round the eight XCDs: consecutive chunks go to the workgroups of one, whose L2 then completes the 128-byte lines
-// that 32 chunks' partials of one (sample, expert) share; with the chunk as the block index a line is written from eight L2s.  Forward of
-// 128 x 196 x 384: 131.0 -> 129.7 us, 8 x 512 x 512: 59.2 -> 58.7, 16 x 4096 x 256: 103.1 -> 102.6, 6 x 1000 x 360: 73.3 -> 72.7.
-__device__ __forceinline__ int chunk_of(int id, int nchunks)
+// Workgroups are dealt round the eight XCDs: chunks whose partials lie side by side go to the workgroups of one, whose L2 then completes the
+// 128-byte lines that 32 of them share; with the place as the block index a line is written from eight L2s.
+__device__ __forceinline__ int place_of(int id, int nchunks)
 {
     const int x = id & 7;
     return x * (nchunks / 8) + min(x, nchunks % 8) + (id >> 3);
@@ -692,7 +692,7 @@ template <int RT, int CT>
 __global__ __launch_bounds__(256) void route_expert_mfma_kernel(RouteArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    route_expert_mfma_body<RT, CT>(a, chunk_of(blockIdx.x, a.nchunks), blockIdx.y * RT * 16, smem);
+    route_expert_mfma_body<RT, CT>(a, place_of(blockIdx.x, a.nchunks), blockIdx.y * RT * 16, smem);
 }
 
 // Both routers of a block in one launch (they are independent and both stream x): workgroups
@@ -708,7 +708,7 @@ __global__ __launch_bounds__(256, CT == 1 ? 4 : 2) void route_expert_data_kernel
         route_data_mfma_body<CT, KS>(a, id % a.nchunks_d, id / a.nchunks_d, smem);
     } else {
         const int f = id - n_data;
-        route_expert_mfma_body<RT, CT>(a, chunk_of(f % a.nchunks, a.nchunks), (f / a.nchunks) * RT * 16, smem);
+        route_expert_mfma_body<RT, CT>(a, place_of(f % a.nchunks, a.nchunks), (f / a.nchunks) * RT * 16, smem);
     }
 }
 
@@ -890,10 +890,11 @@ __global__ __launch_bounds__(256) void route_stream_kernel(RouteArgs a, int ipw,
 #pragma unroll
             for (int v = 0; v < 4; ++v) zsh[wave][t * 16 + q4 * 4 + v][u * 16 + r] = accz[t][u][v];
     __syncthreads();
+    const int place = zpart_place(a, chunk);
     for (int o = tid; o < RT * 16 * NP; o += 256) {
         const int row = o / NP, col = o - row * NP;
         if (row < bg && col < n)
-            a.zpart[zpart_at(a, chunk, b0 + row, col)] = (zsh[0][row][col] + zsh[1][row][col]) + (zsh[2][row][col] + zsh[3][row][col]);
+            a.zpart[zpart_at(a, place, b0 + row, col)] = (zsh[0][row][col] + zsh[1][row][col]) + (zsh[2][row][col] + zsh[3][row][col]);
     }
     if (HAS_D) {
         for (int o = tid; o < tcur * bg * n; o += 256) {
@@ -1405,6 +1406,7 @@ hipError_t launch_route(const RouteArgs &a_in, bool bf16, hipStream_t st, RouteS
 {
     if (beside) beside->on = 0;
     RouteArgs a = a_in;
+    zpart_order(a);
     const bool has_e = a.w_e != nullptr, has_d = a.w_b != nullptr;
     hipError_t err = hipSuccess;
     const bool data_mfma = has_d && route_data_uses_mfma(a.b, a.l, a.d, a.n, bf16);
@@ -1417,6 +1419,7 @@ hipError_t launch_route(const RouteArgs &a_in, bool bf16, hipStream_t st, RouteS
         // streaming kernel: expert router and the data router's first map in one pass over x, then the fold
         a.tc = sp.tpc;
         a.nchunks = sp.nchunks;
+        zpart_order(a);
         const dim3 grid(sp.nchunks, (a.b + sp.rt * 16 - 1) / (sp.rt * 16));
 #define UOE_STREAM(RT, CT, RB)                                                                                              \
     do {                                                                                                                    \

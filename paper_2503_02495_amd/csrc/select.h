@@ -2,7 +2,7 @@
 //
 // As a launch it is 4 to 5 us of a chain of launches of 4 to 12 us, most of that its start, and the contraction behind it
 // begins with lookups of what it wrote.  Every workgroup of the UoME block's first layer can instead add up its sample's partial logits
-// (16 KB from L2 on the small shapes, four chunks a lane and load) and rank them for itself; the first one of a sample also writes the
+// (16 KB from L2 on the small shapes, 16 bytes a lane and load) and rank them for itself; the first one of a sample also writes the
 // results.  Forward of 8 x 512 x 512 59.2 -> 57.2 us (5.0 + 12.2 -> 14.6 traced), 6 x 1000 x 360 76.1 -> 73.2.  With the patches as well (the SMHA block's projection) the chain was as long as the
 // launch: 8 x 512 x 512, 8 x 16 logits 7.1 + 5.8 -> 13.2 us, 16 x 4096 x 256, 8 x 64 6.6 + 6.7 -> 23.
 #pragma once
@@ -14,44 +14,96 @@ constexpr int SELECT_THREADS = 512;
 constexpr int SELECT_BESIDE_VALUES = 16 * 1024;   // partial logits of a sample that a workgroup adds up beside its work
 typedef float part4_t __attribute__((ext_vector_type(4), aligned(4)));   // four partials in a row, from any of them on
 
-// Where a chunk's partial expert logits lie: a sample's and expert's of all chunks in a row, as the selection adds them up
-__device__ __forceinline__ size_t zpart_at(const RouteArgs &a, int chunk, int bb, int e) { return ((size_t)bb * a.n + e) * a.nchunks + chunk; }
+// Order of a sample's expert logits: chunks whose numbers are equal modulo zgroups (512 / n of them) are added one after the other, then the sums
+// of groups equal modulo 16, then these 16 by halves; the same bits whoever selects.  The partials that are added first lie side by side: a
+// sample's and expert's of all chunks in a row, by group and in a group by chunk (the first zmore groups have one more than zlen).
+inline void zpart_order(RouteArgs &a)
+{
+    a.zgroups = SELECT_THREADS / a.n;
+    a.zlen = a.nchunks / a.zgroups;
+    a.zmore = a.nchunks % a.zgroups;
+    a.zinv = 1.0f / (float)(a.zlen > 0 ? a.zlen : 1);
+    a.zinv_more = 1.0f / (float)(a.zlen + 1);
+}
+__device__ __forceinline__ int zpart_place(const RouteArgs &a, int chunk)
+{
+    const int i = chunk / a.zgroups, g = chunk - i * a.zgroups;
+    return g * a.zlen + min(g, a.zmore) + i;
+}
+__device__ __forceinline__ int zpart_chunk(const RouteArgs &a, int place)   // zpart_place backwards, for at most 2^20 chunks (a quotient in fp32)
+{
+    const int head = a.zmore * (a.zlen + 1), in_head = place < head, p = in_head ? place : place - head;
+    const int g = (int)(((float)p + 0.5f) * (in_head ? a.zinv_more : a.zinv));
+    return (p - g * (a.zlen + in_head)) * a.zgroups + g + (in_head ? 0 : a.zmore);
+}
+__device__ __forceinline__ size_t zpart_at(const RouteArgs &a, int place, int bb, int e) { return ((size_t)bb * a.n + e) * a.nchunks + place; }
 
-// The logits of a sample (without the noise) from its chunks' partials, by NT threads: a wave takes every NT/64th expert, a lane four chunks and the
-// wave 256 a pass, then the lanes' sums are added.  The order does not depend on NT.
+// a lane's value plus that of the lane whose number differs in one bit, 16 lanes at a time: after the steps before, all lanes of a quad (and of
+// half a row) hold the same, so that the mirrored lane's is the same number
+template <int CTRL> __device__ __forceinline__ float add_dpp(float v)
+{
+    return v + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float row_sum(float v)
+{
+    v = add_dpp<0xB1>(v);      // quad_perm 1 0 3 2
+    v = add_dpp<0x4E>(v);      // quad_perm 2 3 0 1
+    v = add_dpp<0x141>(v);     // row_half_mirror
+    return add_dpp<0x140>(v);  // row_mirror
+}
+
+// The logits of a sample (without the noise) from its chunks' partials, by NT threads: lane = group, 64 of an expert's a wave, or all of two or four
+// experts where there are at most 32 or 16; ITEMS such rounds and up to 16 partials of each a lane in flight.
 template <int NT> __device__ __forceinline__ void expert_logits(const RouteArgs &a, int bb, float *logit, int tid)
 {
-    constexpr int W = NT / 64, E = W >= 8 ? 1 : 2, PASSES = 2;   // E x PASSES loads in flight
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), at = (tid & 63) * 4, chunks = a.nchunks;
-    for (int e0 = wave; e0 < a.n; e0 += E * W) {
-        const float *src[E];
-        float s[E];
+    constexpr int W = NT / 64, ITEMS = 2, PASSES = 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = a.n;
+    const int bits = a.zgroups > 32 ? 6 : (a.zgroups > 16 ? 5 : 4), experts = 64 >> bits, sub = lane >> bits, cl = lane - (sub << bits);
+    const int groups = min(a.zgroups, a.nchunks), rounds = (groups + 63) / 64, longest = a.zlen + (a.zmore > 0);
+    float z = 0.f;
+    for (int e0 = wave * experts, round = 0; e0 < n;) {
+        int e[ITEMS], rd[ITEMS], len[ITEMS];
+        const float *src[ITEMS];
+        float s[ITEMS];
 #pragma unroll
-        for (int i = 0; i < E; ++i) {
-            src[i] = a.zpart + zpart_at(a, 0, bb, min(e0 + i * W, a.n - 1));
-            s[i] = 0.f;
-        }
-        for (int c0 = at; c0 < chunks; c0 += PASSES * 256) {
-            part4_t v[E][PASSES];
-#pragma unroll
-            for (int j = 0; j < PASSES; ++j)
-                // the last lane's load may reach three values behind its row: the next row, or the workspace's next array
-#pragma unroll
-                for (int i = 0; i < E; ++i) v[i][j] = *reinterpret_cast<const part4_t *>(src[i] + (c0 + j * 256 < chunks ? c0 + j * 256 : c0));
-#pragma unroll
-            for (int j = 0; j < PASSES; ++j) {
-                const int c = c0 + j * 256;
-#pragma unroll
-                for (int i = 0; i < E; ++i) {
-                    const float two = (c + 2 < chunks ? v[i][j].z : 0.f) + (c + 3 < chunks ? v[i][j].w : 0.f);
-                    s[i] += c < chunks ? (v[i][j].x + (c + 1 < chunks ? v[i][j].y : 0.f)) + two : 0.f;
-                }
+        for (int i = 0; i < ITEMS; ++i) {
+            const int g = round * 64 + cl;
+            e[i] = e0; rd[i] = round; s[i] = 0.f;
+            len[i] = g < groups && e0 + sub < n ? a.zlen + (g < a.zmore) : 0;
+            src[i] = a.zpart + zpart_at(a, min(g * a.zlen + min(g, a.zmore), a.nchunks - 1), bb, min(e0 + sub, n - 1));
+            if (++round == rounds) {
+                round = 0;
+                e0 += experts * W;
             }
         }
+        for (int j0 = 0; j0 < longest; j0 += PASSES * 4) {
+            part4_t v[ITEMS][PASSES];
 #pragma unroll
-        for (int i = 0; i < E; ++i) {
-            const float z = wave_sum(s[i]);
-            if ((tid & 63) == 0 && e0 + i * W < a.n) logit[e0 + i * W] = z;
+            for (int q = 0; q < PASSES; ++q)
+                // a load may reach three values behind the row: the next row, or the workspace's next array
+                if (q == 0 || j0 + q * 4 < longest)
+#pragma unroll
+                    for (int i = 0; i < ITEMS; ++i) v[i][q] = *reinterpret_cast<const part4_t *>(src[i] + (j0 + q * 4 < len[i] ? j0 + q * 4 : 0));
+#pragma unroll
+            for (int q = 0; q < PASSES; ++q)
+                if (q == 0 || j0 + q * 4 < longest)
+#pragma unroll
+                    for (int i = 0; i < ITEMS; ++i)
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) s[i] += j0 + q * 4 + c < len[i] ? v[i][q][c] : 0.f;
+        }
+        float part[ITEMS][4];   // the groups' sums of every row of 16 lanes
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i)
+#pragma unroll
+            for (int h = 0; h < 4; ++h) part[i][h] = __shfl(s[i], (lane - cl + h * 16 + (lane & 15)) & 63, 64);
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+            z = rd[i] ? z + part[i][0] : 0.f + part[i][0];
+            if (bits > 4) z += part[i][1];
+            if (bits > 5) z = (z + part[i][2]) + part[i][3];
+            const float t = row_sum(z);
+            if (rd[i] == rounds - 1 && cl == 0 && e[i] + sub < n) logit[e[i] + sub] = t;
         }
     }
 }

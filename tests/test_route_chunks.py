@@ -32,3 +32,9 @@ def test_split_columns_where_rows_are_long_for_the_sums(b, l, d, n, m, want):
 def test_twice_the_tokens_where_that_saves_a_launch(b, l, d, n, m, want):
     """128 tokens: from 16 K of them on, and only where the selection adds the partial logits up with 128 (512 logits, 16384 sums a sample) and not with 64."""
     assert chunk_tokens(b, l, d, n, m) == want
+
+
+@pytest.mark.parametrize("b,l,d,n,m", [(2, 96, 1032, 17, 6), (1, 200, 1016, 24, 8), (3, 250, 1400, 17, 5)])
+def test_sixteen_tokens_off_the_matrix_cores(b, l, d, n, m):
+    """bf16 with W_B too large for the matrix-core kernel: 16 tokens a chunk also below 8192 of them (the shorter chunks are fp32's)."""
+    assert chunk_tokens(b, l, d, n, m) == 16
