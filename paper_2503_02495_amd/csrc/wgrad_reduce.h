@@ -148,10 +148,11 @@ struct UnitGates {
     static __host__ int count(const SmhaBwdArgs &a) { return a.d_expert_gate || a.d_patch_gate ? a.f.b * a.f.k : 0; }
 };
 
-// d_gate [b,n]: block (slot s, sample b) adds the slot's partial sums (each thread a strided
-// subset in index order, then a fixed tree) into the entry of the slot's expert; the block of slot 0
+// d_gate [b,n]: block (slot s, sample b) adds the slot's partial sums (256 strided subsets in index order, then a fixed tree: one order for
+// any number of threads) into the entry of the slot's expert; the block of slot 0
 // also writes the zeros of the experts the sample did not select (all of them without the gate flag).
-template <int NT> __device__ __forceinline__ void uome_bwd_gate_block(const UomeBwdArgs &a, int s, int bb, float *red)   // NT threads, red: NT floats of LDS
+constexpr int GATE_SUMS = 256;
+template <int NT> __device__ __forceinline__ void uome_bwd_gate_block(const UomeBwdArgs &a, int s, int bb, float *red)   // NT threads, red: GATE_SUMS floats of LDS
 {
     const int tid = threadIdx.x;
     const bool gated = a.flags & F_GATE_EXPERT;
@@ -163,12 +164,14 @@ template <int NT> __device__ __forceinline__ void uome_bwd_gate_block(const Uome
     }
     if (!gated) return;
     const float *src = a.gpart + ((size_t)bb * a.k + s) * a.gchunks;
-    float v = 0.f;
-    for (int c = tid; c < a.gchunks; c += NT) v += src[c];
-    red[tid] = v;
+    for (int i = tid; i < GATE_SUMS; i += NT) {
+        float v = 0.f;
+        for (int c = i; c < a.gchunks; c += GATE_SUMS) v += src[c];
+        red[i] = v;
+    }
     __syncthreads();
-    for (int st = NT / 2; st > 0; st >>= 1) {
-        if (tid < st) red[tid] += red[tid + st];
+    for (int st = GATE_SUMS / 2; st > 0; st >>= 1) {
+        for (int i = tid; i < st; i += NT) red[i] += red[i + st];
         __syncthreads();
     }
     if (tid == 0) a.d_gate[(size_t)bb * a.n + clampi(a.expert_idx[bb * a.k + s], a.n)] = red[0];
@@ -177,11 +180,11 @@ template <int NT> __device__ __forceinline__ void uome_bwd_gate_block(const Uome
 // the gate gradient's blocks behind the tiles of another launch
 struct UomeGates {
     static constexpr int THREADS = 0;
-    static constexpr size_t LDS = 512 * sizeof(float);
+    static constexpr size_t LDS = GATE_SUMS * sizeof(float);
     UomeBwdArgs a;
     template <int NT> __device__ __forceinline__ void run(int block, void *lds) const
     {
-        static_assert(NT >= 64 && NT * sizeof(float) <= LDS, "a wave for the experts, a float a thread");
+        static_assert(NT >= 64, "a wave for the experts");
         uome_bwd_gate_block<NT>(a, block % a.k, block / a.k, static_cast<float *>(lds));
     }
 };
