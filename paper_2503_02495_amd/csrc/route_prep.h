@@ -99,6 +99,7 @@ template <typename T> __device__ __forceinline__ void route_prep_block(const Rou
 
 template <typename T> struct RoutePrep {
     static constexpr int THREADS = 256;
+    static constexpr bool OPTIONAL = true;   // (BwdTail::prep_done)
     static constexpr size_t LDS = sizeof(RoutePrepLds);
     RouteBwdArgs a;
     int nx;

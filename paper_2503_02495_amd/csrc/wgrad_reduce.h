@@ -180,6 +180,7 @@ template <int NT> __device__ __forceinline__ void uome_bwd_gate_block(const Uome
 // the gate gradient's blocks behind the tiles of another launch
 struct UomeGates {
     static constexpr int THREADS = 0;
+    static constexpr bool OPTIONAL = false;
     static constexpr size_t LDS = GATE_SUMS * sizeof(float);
     UomeBwdArgs a;
     template <int NT> __device__ __forceinline__ void run(int block, void *lds) const
