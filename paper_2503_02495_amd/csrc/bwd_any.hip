@@ -19,6 +19,7 @@
 #include "gemm_dma.h"
 #include "wgrad_reduce.h"
 #include "route_prep.h"
+#include "unit_grid.h"
 
 namespace uoe {
 
@@ -466,7 +467,7 @@ __device__ __forceinline__ bool any_key_ok(const SmhaArgs &f, int g, int key, in
 // for four) and the general form's registers one (at 128 no scratch, 156 / 884 bytes before); 384 units of 56 rows, d_h 64: 44.4 -> 27.3
 // us owning queries, 27.1 -> 22.0 owning keys.  vit shape forward + backward 712 -> 698 us.
 template <typename T, int DH, int NQ, int KS, bool KV, bool ONE>
-__global__ __launch_bounds__(NQ *KS * 64, (ONE && DH <= 64) || DH == 32 ? 2 : 1) void attention_bwd_f32_kernel(SmhaBwdArgs a, int gate_units)
+__global__ __launch_bounds__(NQ *KS * 64, (ONE && DH <= 64) || DH == 32 ? 2 : 1) void attention_bwd_f32_kernel(SmhaBwdArgs a, UnitGrid grid)
 {
     constexpr int BT = 32, P = DH + 4, NTH = NQ * 64, NP = BT * DH / 4 / NTH;   // NP: 16-byte pieces per staging thread
     constexpr int TILE = BT * P, SPLIT = 2 * TILE + 4 * BT, SLOT = (KV ? DH : DH / 2) + 2, MERGE = (KS - 1) * NQ * 64 * SLOT;
@@ -476,19 +477,18 @@ __global__ __launch_bounds__(NQ *KS * 64, (ONE && DH <= 64) || DH == 32 ? 2 : 1)
     float *const merged = KEEP ? lds + KS * TILE : lds;
     constexpr int PARTS = parts_of<T>::value;
     const SmhaArgs &f = a.f;
-    const int l_p = f.l / f.m, l_a = f.c * l_p, d_h = f.d_h, g = blockIdx.y;
-    if constexpr (KV) {   // the block's gate gradients, behind the units' rows of workgroups (r_t: of the query-owning kernel)
+    if constexpr (KV) {   // the block's gate gradients, behind the units' workgroups (r_t: of the query-owning kernel)
         static_assert(UnitGates::LDS <= sizeof(lds), "the gate gradients' LDS");
-        if (g >= f.b * f.k) {
-            const int unit = (g - f.b * f.k) * gridDim.x + blockIdx.x;
-            if (unit < gate_units) unit_gate_block<NQ * KS * 64>(a, unit, lds);
+        if (blockIdx.x >= grid.own()) {
+            unit_gate_block<NQ * KS * 64>(a, (int)(blockIdx.x - grid.own()), lds);
             return;
         }
     }
+    const int l_p = f.l / f.m, l_a = f.c * l_p, d_h = f.d_h, g = grid.unit(blockIdx.x), block = grid.block(blockIdx.x);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int split = wave / NQ, qg = wave - split * NQ, stid = tid - split * NTH;
     const int lr = lane & 31, lh = lane >> 5;
-    const int own = blockIdx.x * (32 * NQ) + qg * 32 + lr, own_c = min(own, l_a - 1);
+    const int own = block * (32 * NQ) + qg * 32 + lr, own_c = min(own, l_a - 1);
     // [TA of every split][TB][R0 to R3]
     float *TA = lds + split * TILE, *TB = TA + KS * TILE, *R0 = lds + 2 * KS * TILE + split * 4 * BT, *R1 = R0 + BT, *R2 = R1 + BT, *R3 = R2 + BT;
     const size_t ubase = (size_t)g * l_a * d_h;
@@ -517,7 +517,7 @@ __global__ __launch_bounds__(NQ *KS * 64, (ONE && DH <= 64) || DH == 32 ? 2 : 1)
     const bool own_ok = own < l_a && (!KV || any_key_ok(f, g, own_c, l_p));
 
     // streamed tiles: under the causal mask a query sees keys <= itself
-    const int blk0 = blockIdx.x * 32 * NQ, blk1 = min(l_a, blk0 + 32 * NQ);
+    const int blk0 = block * 32 * NQ, blk1 = min(l_a, blk0 + 32 * NQ);
     int t_begin = 0, t_end = (l_a + BT - 1) / BT;
     if (causal) {
         if (KV) t_begin = blk0 / BT;
@@ -854,11 +854,10 @@ template <typename T, int DH> void launch_attention_bwd_f32_dh(const SmhaBwdArgs
     // block 207, two 214, four 154; causal 169, 182, 155; 768 units, causal 229, 271, 222; in fp32, d_h 120, causal 615, 701, 604.  Longer units:
     // splits while the launch has fewer waves than SIMDs.
     const int ks = l_a <= 32 ? 1 : l_a <= 64 ? 2 : l_a <= 128 || blocks < 512 ? 4 : blocks < 1024 ? 2 : 1;
-    const int rows = (l_a + 31) / 32, gates = UnitGates::count(a);
-    const dim3 grid(rows, units), grid_kv(rows, units + (gates + rows - 1) / rows);
+    const UnitGrid grid{(l_a + 31) / 32, units, 0}, grid_kv{grid.rows, units, UnitGates::count(a)};
 #define UOE_ABW(KS, ONE)                                                                                            \
-    hipLaunchKernelGGL((attention_bwd_f32_kernel<T, DH, 1, KS, false, ONE>), grid, dim3(KS * 64), 0, st, a, 0);     \
-    hipLaunchKernelGGL((attention_bwd_f32_kernel<T, DH, 1, KS, true, ONE>), grid_kv, dim3(KS * 64), 0, st, a, gates)
+    hipLaunchKernelGGL((attention_bwd_f32_kernel<T, DH, 1, KS, false, ONE>), dim3(grid.workgroups()), dim3(KS * 64), 0, st, a, grid);     \
+    hipLaunchKernelGGL((attention_bwd_f32_kernel<T, DH, 1, KS, true, ONE>), dim3(grid_kv.workgroups()), dim3(KS * 64), 0, st, a, grid_kv)
     const bool one = l_a <= 32 * ks;   // a tile a wave
     if (ks == 1 && one) { UOE_ABW(1, true); }
     else if (ks == 1) { UOE_ABW(1, false); }
