@@ -64,6 +64,15 @@ RouteWs route_ws(int b, int l, int d, int n, int m, bool bf16)
     return w;
 }
 
+// Room for the UoME block's routers: a block that selects experts only has them routed with one patch, whatever its m, and either plan may
+// be the larger one (chunks get longer where the patches' partial sums are many).
+size_t uome_route_bytes(const uoe_block_desc *d)
+{
+    const bool bf16 = d->dtype == UOE_BF16;
+    const size_t own = route_ws(d->b, d->l, d->d, d->n, d->m, bf16).total, one = route_ws(d->b, d->l, d->d, d->n, 1, bf16).total;
+    return d->c == d->m && one > own ? one : own;
+}
+
 struct SmhaWs {
     size_t q, k, v, o, o_lo, total;
 };
@@ -443,7 +452,7 @@ size_t uoe_workspace_bytes(const uoe_block_desc *smha, const uoe_block_desc *uom
     }
     if (uome) {
         if (check_desc(uome, DESC_UOME) != UOE_OK) return 0;
-        total += route_ws(uome->b, uome->l, uome->d, uome->n, uome->m, uome->dtype == UOE_BF16).total + uome_ws(uome) +
+        total += uome_route_bytes(uome) + uome_ws(uome) +
                  routing_buf(uome, uome->m, uome->c).total;
     }
     if (smha && uome) total += up((size_t)smha->b * smha->l * smha->d * elem_size(smha->dtype));  // u
@@ -845,7 +854,7 @@ int uoe_layer_forward_masked(const uoe_block_desc *smha, const uoe_smha_weights 
     void *route_a_ws = at(ws, off); off += route_a_bytes;
     const size_t smha_bytes = smha_ws(smha).total;
     void *smha_scratch = at(ws, off); off += smha_bytes;
-    const size_t route_m_bytes = route_ws(uome->b, uome->l, uome->d, uome->n, uome->m, uome->dtype == UOE_BF16).total;
+    const size_t route_m_bytes = uome_route_bytes(uome);
     void *route_m_ws = at(ws, off); off += route_m_bytes;
     void *uome_scratch = at(ws, off);
     const size_t uome_bytes = uome_ws(uome);
