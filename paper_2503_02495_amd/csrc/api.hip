@@ -883,14 +883,12 @@ int uoe_layer_forward_masked(const uoe_block_desc *smha, const uoe_smha_weights 
         return do_uome(uome, u, wm->a_in, wm->a_out, m_eidx, m_egate, m_pidx, m_pgate, out, uome_scratch, uome_bytes, st);
     }
     // expert-selection mode: one patch = the sample
-    // The experts are selected beside the first layer's own work up to 16 M hidden values, about one round of workgroups, 3 M in fp32, one round of its smaller
-    // ones: every workgroup pays for it (forward, us: 16 x 4096 x 256 113.9 -> 112.7; 128 x 196 x 768, d 384, 18 M, 127.7 -> 128.0 and 123.3 -> 122.4 on
-    // two boxes; 13 x 1408 x 224, d 96, in fp32 131.8 -> 133.5; 15 x 1856 x 800, d 960, one workgroup a compute unit, 281.3 -> 283.6; 4 x 8192 x 2048, four
-    // rounds, 499 -> 504)
+    UomeArgs shape{};
+    shape.b = uome->b; shape.l = uome->l; shape.d = uome->d; shape.n = uome->n; shape.k = uome->k; shape.d_e = uome->width;
     RouteSelect beside{};
-    const bool can = (double)uome->b * uome->l * uome->k * uome->width <= (uome->dtype == UOE_F32 ? 3.0 : 16.0) * 1048576.0;
+    beside.most = uome_select_values(shape, uome->dtype == UOE_BF16);
     rc = do_route(uome, 1, 1, u, wm->w_expert, nullptr, nullptr, noise_m_expert, nullptr, m_eidx, m_egate,
-                  nullptr, nullptr, route_m_ws, route_m_bytes, st, can ? &beside : nullptr);
+                  nullptr, nullptr, route_m_ws, route_m_bytes, st, &beside);
     if (rc != UOE_OK) return rc;
     return do_uome(uome, u, wm->a_in, wm->a_out, m_eidx, m_egate, nullptr, nullptr, out, uome_scratch, uome_bytes, st, &beside);
 }

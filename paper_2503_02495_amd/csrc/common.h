@@ -205,6 +205,7 @@ struct RouteArgs {
 struct RouteSelect {
     RouteArgs r;
     int on, has_e;
+    int most;   // in: with more partial logits a sample it is launched (uome_select_values)
 };
 
 struct SmhaArgs {
@@ -368,12 +369,12 @@ hipError_t launch_smha_qkv_attention(const SmhaArgs &a, hipStream_t st);
 hipError_t launch_uome(const UomeArgs &a, bool bf16, hipStream_t st);
 int uome_mlp_waves(const UomeArgs &a);                                      // not 0: both layers in one launch (uome_mlp.hip), bf16
 hipError_t launch_uome_mlp(const UomeArgs &a, hipStream_t st);
+int uome_select_values(const UomeArgs &a, bool bf16);                       // RouteSelect::most for the block's first launch; 0: never
 hipError_t launch_uome_up(const UomeArgs &a, bool bf16, hipStream_t st);    // Eq. 38 only
 hipError_t launch_uome_down(const UomeArgs &a, bool bf16, hipStream_t st);  // Eq. 39-40 only
 hipError_t launch_uome_ds(const UomeDsArgs &a, bool bf16, hipStream_t st);
 hipError_t launch_uome_backward(const UomeBwdArgs &a, hipStream_t st, BwdTail *tail = nullptr);
 hipError_t launch_smha_backward(const SmhaBwdArgs &a, hipStream_t st, BwdTail *tail = nullptr);
-// d_gate from the partial sums a.gpart [b, k, gchunks]
 // rotary embedding (Eq. 32) of fp32 q and k with rows of d_h
 hipError_t launch_rope_f32(const SmhaArgs &a, hipStream_t st);
 // backward passes for the shapes and storage types the 32-multiple bf16 kernels do not take

@@ -1404,6 +1404,7 @@ __global__ __launch_bounds__(SELECT_THREADS) void route_select_all_kernel(RouteA
 
 hipError_t launch_route(const RouteArgs &a_in, bool bf16, hipStream_t st, RouteSelect *beside)
 {
+    const int most = beside ? beside->most : 0;
     if (beside) beside->on = 0;
     RouteArgs a = a_in;
     zpart_order(a);
@@ -1518,8 +1519,8 @@ hipError_t launch_route(const RouteArgs &a_in, bool bf16, hipStream_t st, RouteS
             if (err != hipSuccess) return err;
         }
     }
-    if (beside && !has_d && !a.capacity && a.nchunks * a.n <= SELECT_BESIDE_VALUES) {
-        *beside = {a, 1, (int)has_e};
+    if (beside && !has_d && !a.capacity && a.nchunks * a.n <= most) {
+        *beside = {a, 1, (int)has_e, most};
         return hipSuccess;
     }
     // patch lists and gates: none when neither is asked for (a capacity call needs row 0)

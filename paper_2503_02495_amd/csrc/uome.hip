@@ -67,6 +67,19 @@ static hipError_t uome_down_mfma(const UomeArgs &a, hipStream_t st)
     return launch_gemm_dma_auto(dn, a.b, a.l, a.d, (long)a.k * a.d_e, a.d_e, st);  // K segments = the active experts' d_e rows
 }
 
+// Selecting beside the first layer saves 1 to 2 us of a launch's 4 to 5; the rest goes with every workgroup's own sums.  It does while the workgroups start
+// at about the same time (counted in 128 x 128 tiles, 64 x 64 in fp32, or in those of both layers' launch) and have few partials to add up.  Forward,
+// us, with a launch and beside (tiles, partials): 19 x 628 x 704, W (hidden columns) 960 (760, 7536) 114.8 and 113.7; 32 x 944 x 72, W 480 (1024, 7552)
+// 74.9 and 76.2; 13 x 680 x 160, W 320 (234, 16320) 59.8 and 62.6; 2 x 572 x 224, W 2304 (180, 13728) 60.8 and 61.8; 5 x 700 x 208, W 1568 (546, 11200)
+// 68.1 and 67.0; fp32 26 x 1132 x 128, W 88 (936, 252) 138.7 and 140.5, 23 x 156 x 248, W 672 (759, 468) 92.5 and 91.1; both layers in one launch, 16 x
+// 4096 x 256, W 256 and 1024 (256, 4096) 89.7 and 88.6, 133.7 and 132.2.
+int uome_select_values(const UomeArgs &a, bool bf16)
+{
+    const int waves = bf16 ? uome_mlp_waves(a) : 0, tile = bf16 ? 128 : 64;
+    const long wgs = waves ? (long)a.b * ((a.l + waves * 32 - 1) / (waves * 32)) : (long)a.b * ((a.l + tile - 1) / tile) * ((a.k * a.d_e + tile - 1) / tile);
+    return wgs <= 768 ? 12 * 1024 : 0;
+}
+
 hipError_t launch_uome_up(const UomeArgs &a, bool bf16, hipStream_t st)
 {
     if (uome_mfma_ok(a, bf16)) return a.select ? uome_up_mfma<true>(a, st) : uome_up_mfma<false>(a, st);
