@@ -51,7 +51,7 @@ struct RouteWs {
 RouteWs route_ws(int b, int l, int d, int n, int m, bool bf16)
 {
     RouteWs w;
-    w.tc = bf16 ? route_expert_mfma_tokens_per_chunk(b, l, d, n) : route_tokens_per_chunk(b, l, false);
+    w.tc = bf16 ? route_expert_mfma_tokens_per_chunk(b, l, d, n) : route_tokens_per_chunk(b, l, d, n, m, false);
     w.nchunks = (l + w.tc - 1) / w.tc;
     w.tc_d = route_data_tokens_per_chunk(b, l, d, n, m, bf16);
     w.nchunks_d = (l + w.tc_d - 1) / w.tc_d;

@@ -392,7 +392,7 @@ hipError_t launch_probe_read(const void *src, size_t bytes, uint32_t *sink, hipS
 hipError_t launch_probe_mfma(const void *operands, int iters, float *sink, hipStream_t st);
 
 // host-side sizing shared by api.hip and the launchers
-int route_tokens_per_chunk(int b, int l, bool bf16);
+int route_tokens_per_chunk(int b, int l, int d, int n, int m, bool bf16);
 int route_expert_mfma_tokens_per_chunk(int b, int l, int d, int n);
 int route_data_tokens_per_chunk(int b, int l, int d, int n, int m, bool bf16);
 // streaming router kernel: applicability and launch shape (host side)

@@ -38,17 +38,46 @@ __host__ __device__ constexpr int b_pitch16(int cols)
     return p;
 }
 
-int route_tokens_per_chunk(int b, int l, bool bf16)
+// Chunks of fewer than 16 tokens only where route_select still adds up the data router's partials
+static int route_data_short(int l, int n, int m, int tc)
+{
+    while (tc < 16 && tc < l && (n * m > 512 || (long)n * m * ((l + tc - 1) / tc) > 16384)) tc = 2 * tc < l ? 2 * tc : l;
+    return tc > 16 ? 16 : tc;
+}
+
+// Tokens per chunk of fp32 routers with fewer than 8192 tokens: 4, 8, 12 or 16.  16 leave compute units idle and a chunk is a chain of its own, but it has
+// its fixed work too, some four tokens', and route_partial deals chunks to the XCDs whole, all samples' of one to the same.  Counted in tokens of the
+// XCD with the most: the work, or the longest chain in three quarters of the workgroups that fit, whichever is more; whole rounds of the long
+// workgroups of more than 16 experts.  Less than 16 only if that gains a tenth.  The data router takes the expert router's chunks unless its partial sums
+// are many.  Forward, us, 16 tokens / all that are idle otherwise, from 4 on / these: 2 x 64 x 64 46.8 / 41.7 / 41.7; 8 x 512 x 512, 8 experts 147.1 / 143.7 /
+// 143.7; 28 x 217 x 184, 14 experts 104.2 / 110.3 / 104.1; 61 x 72 x 280, 6 and 16 79.2 / 83.5 / 75.7; 15 x 288 x 360, 32 and 2 112.0 / 115.2 / 110.9;
+// 1 x 2006 x 784, 12 (W_E 75 MB: longer runs of it stream better) 112.3 / 125.7 / 111.4.
+static int route_short_tokens_per_chunk(int b, int l, int d, int n, int m)
+{
+    const int regs = n <= 4 ? 7 : (n <= 8 || (n > 16 && n <= 24) ? 5 : (n <= 12 || n > 16 ? 4 : 3));   // workgroups a compute unit's registers hold
+    const int lds = m > 1 ? 160 * 1024 / (n * d * 4 + 2048) : regs;                                    // and its LDS, with W_B
+    const long fit = 32L * (lds < regs ? lds : regs);
+    const auto load = [&](int tc) { return (long)(((l + tc - 1) / tc + 7) / 8) * b; };
+    const auto cost = [&](int tc) {
+        const int tc_d = m > 1 ? route_data_short(l, n, m, tc) : 0, longest = tc_d > tc ? tc_d : tc;
+        const long data = m > 1 ? load(tc_d) : 0, work = load(tc) * (tc + 4) + data * (tc_d + 4), chain = fit * 3 / 4 * (longest + 4);
+        if (n > 16) return (load(tc) + data + fit - 1) / fit * (tc + 4);
+        return work > chain ? work : chain;
+    };
+    int best = 16;
+    for (int tc = n > 16 ? 8 : 12; tc >= 4; tc -= 4)
+        if (cost(tc) < cost(best) && cost(tc) * 10 < cost(16) * 9 && (n <= 16 || tc > 4 || cost(tc) == tc + 4)) best = tc;
+    return best;
+}
+
+int route_tokens_per_chunk(int b, int l, int d, int n, int m, bool bf16)
 {
     // aim for >= ~512 workgroups but keep a chunk within [16, 64] tokens (longer chunks stream
-    // better: measured 3.3 / 3.6 / 3.9 TB/s at 16 / 32 / 64 tokens on the largest shape); fp32: from 4 on below 8192 tokens, where 16
-    // leave compute units idle and a chunk is a chain of its own (fp32 forward, 16 / 8 / 4 tokens at least: 2 x 64 x 64 46.8 / 43.0 / 41.7 us, 2 x 512 x 512
-    // 101.5 / 95.2 / 93.9, 4 x 512 x 256 56.7 / 53.0 / 52.3, 8 x 512 x 512, which takes 8, 147.1 / 143.7)
+    // better: measured 3.3 / 3.6 / 3.9 TB/s at 16 / 32 / 64 tokens on the largest shape)
     long tc = ((long)b * l) / 512;
     if (tc > l / 8) tc = l / 8;  // at least ~8 chunks per sample so the last, short chunk does not dominate
     tc = (tc / 4) * 4;
-    const int least = !bf16 && (long)b * l < 8192 ? 4 : 16;
-    if (tc < least) tc = least;
+    if (tc < 16) tc = !bf16 && (long)b * l < 8192 && (n > 16 || (double)n * l * d * sizeof(float) <= 16e6) ? route_short_tokens_per_chunk(b, l, d, n, m) : 16;
     if (tc > 64) tc = 64;
     if (tc > l) tc = l;
     return (int)tc;
@@ -135,10 +164,8 @@ int route_data_tokens_per_chunk(int b, int l, int d, int n, int m, bool bf16)
         return tokens > 16 * 1024 && m <= DATA_FOLD_TILES * 16 && !selected(DATA_TOKENS) && selected(2 * DATA_TOKENS) ? 2 * DATA_TOKENS : DATA_TOKENS;
     }
     if (route_stream_plan(b, l, d, n, bf16, true).ok) return 64;
-    // chunks of fewer than 16 tokens only where route_select still adds up the partials
-    int tc = route_tokens_per_chunk(b, l, bf16);
-    while (tc < 16 && tc < l && (n * m > 512 || (long)n * m * ((l + tc - 1) / tc) > 16384)) tc = 2 * tc < l ? 2 * tc : l;
-    return tc < 16 ? tc : (tc > 16 && (long)b * l < 8192 ? 16 : tc);
+    const int tc = route_tokens_per_chunk(b, l, d, n, m, bf16);
+    return tc < 16 ? route_data_short(l, n, m, tc) : tc;
 }
 
 constexpr int ROUTE_THREADS = 256;
