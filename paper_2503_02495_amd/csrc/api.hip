@@ -48,12 +48,13 @@ struct RouteWs {
     int tc, nchunks, tc_d, nchunks_d;
     size_t zpart, gpart, gred, t1, total;
 };
-RouteWs route_ws(int b, int l, int d, int n, int m, bool bf16)
+// shorter: fp32 chunks of fewer than 16 tokens, where the call wants them
+static RouteWs route_ws_of(int b, int l, int d, int n, int m, bool bf16, bool shorter)
 {
     RouteWs w;
-    w.tc = bf16 ? route_expert_mfma_tokens_per_chunk(b, l, d, n) : route_tokens_per_chunk(b, l, d, n, m, false);
+    w.tc = bf16 ? route_expert_mfma_tokens_per_chunk(b, l, d, n) : route_tokens_per_chunk(b, l, d, n, m, !shorter);
     w.nchunks = (l + w.tc - 1) / w.tc;
-    w.tc_d = route_data_tokens_per_chunk(b, l, d, n, m, bf16);
+    w.tc_d = bf16 || shorter ? route_data_tokens_per_chunk(b, l, d, n, m, bf16) : w.tc;
     w.nchunks_d = (l + w.tc_d - 1) / w.tc_d;
     size_t off = 0;
     w.zpart = off; off += up((size_t)w.nchunks * b * n * sizeof(float));
@@ -62,6 +63,12 @@ RouteWs route_ws(int b, int l, int d, int n, int m, bool bf16)
     w.t1 = off;    off += route_stream_plan(b, l, d, n, bf16, true).ok ? up((size_t)b * l * n * sizeof(float)) : 0;
     w.total = off;
     return w;
+}
+// uoe_route_static's scratch holds what it held with chunks of 16
+RouteWs route_ws(int b, int l, int d, int n, int m, bool bf16)
+{
+    const RouteWs w = route_ws_of(b, l, d, n, m, bf16, true);
+    return bf16 || w.tc >= 16 || w.total <= (size_t)UOE_ROUTE_STATIC_SCRATCH_BYTES ? w : route_ws_of(b, l, d, n, m, bf16, false);
 }
 
 // Room for the UoME block's routers: a block that selects experts only has them routed with one patch, whatever its m, and either plan may

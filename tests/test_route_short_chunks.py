@@ -24,6 +24,7 @@ def chunk_tokens(b, l, d, n, m):
     (15, 504, 1032, 8, 14, (16, 16)),                    # W_B leaves room for four workgroups a compute unit
     (1, 2006, 784, 12, 34, (16, 16)), (1, 1632, 992, 11, 51, (16, 16)),   # a large W_E is read in longer runs
     (6, 442, 488, 14, 34, (16, 16)),                     # 476 logits: the data router keeps its 16 tokens, and the launch is as long as they take
+    (2, 2816, 232, 23, 256, (16, 16)),                   # 30 KB more for shorter chunks would not fit the fixed scratch of uoe_route_static
     (33, 162, 56, 32, 3, (8, 8)), (20, 406, 104, 24, 14, (16, 16)),       # whole rounds of workgroups with more than 16 experts
 ])
 def test_tokens_of_a_chunk(b, l, d, n, m, want):
