@@ -189,8 +189,7 @@ struct RouteArgs {
     int b, l, d, n, k, m, c;
     int tc, nchunks;                          // expert router: tokens per chunk, chunks per sample
     int tc_d, nchunks_d;                      // data router: the same
-    int zgroups, zlen, zmore;                 // zpart's order along a row (select.h); zinv = 1 / zlen, zinv_more = 1 / (zlen + 1)
-    float zinv, zinv_more;
+    int zgroups;                              // 512 / n: the order of the logits' sums (select.h)
     float *zpart, *gpart;                     // [b, n, nchunks], [nchunks_d, b, n*m]
     float *gred;                              // [b, n*m]
     float *t1;                                // [b, l, n]: per-token expert scores x W_B of the one-pass kernel

@@ -268,7 +268,7 @@ __device__ __forceinline__ void route_partial(const RouteArgs &a, unsigned char 
         float s = 0.f;
 #pragma unroll
         for (int w = 0; w < ROUTE_WAVES; ++w) s += zsh[w * NMAX + tid];
-        a.zpart[zpart_at(a, zpart_place(a, chunk), bb, tid)] = s;
+        a.zpart[zpart_at(a, chunk, bb, tid)] = s;
     }
     if (HAS_D) {
         const T *w_a = static_cast<const T *>(a.w_a);
@@ -627,9 +627,8 @@ __global__ __launch_bounds__(ROUTE_THREADS, NTILE == 1 ? 4 : 2) void route_data_
 template <int RT, int CT> constexpr size_t route_expert_mfma_lds() { return sizeof(float) * 4 * RT * 16 * (CT * 16 + 1); }
 
 template <int RT, int CT>
-__device__ __forceinline__ void route_expert_mfma_body(const RouteArgs &a, int place, int b0, unsigned char *smem)
+__device__ __forceinline__ void route_expert_mfma_body(const RouteArgs &a, int chunk, int b0, unsigned char *smem)
 {
-    const int chunk = zpart_chunk(a, place);
     float(*zsh)[RT * 16][CT * 16 + 1] = reinterpret_cast<float(*)[RT * 16][CT * 16 + 1]>(smem);  // [4 waves]
     constexpr int U = RT == 4 ? 2 : 4;  // steps whose loads are in flight together (four: no third wave a SIMD beside 64 samples' rows)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -703,13 +702,13 @@ __device__ __forceinline__ void route_expert_mfma_body(const RouteArgs &a, int p
     for (int o = tid; o < RT * 16 * CT * 16; o += 256) {
         const int row = o / (CT * 16), col = o - row * (CT * 16);
         if (b0 + row < b && col < n)
-            a.zpart[zpart_at(a, place, b0 + row, col)] = (zsh[0][row][col] + zsh[1][row][col]) + (zsh[2][row][col] + zsh[3][row][col]);
+            a.zpart[zpart_at(a, chunk, b0 + row, col)] = (zsh[0][row][col] + zsh[1][row][col]) + (zsh[2][row][col] + zsh[3][row][col]);
     }
 }
 
-// Workgroups are dealt round the eight XCDs: chunks whose partials lie side by side go to the workgroups of one, whose L2 then completes the
-// 128-byte lines that 32 of them share; with the place as the block index a line is written from eight L2s.
-__device__ __forceinline__ int place_of(int id, int nchunks)
+// Workgroups are dealt round the eight XCDs: consecutive chunks go to the workgroups of one, whose L2 then completes the 128-byte lines
+// that 32 chunks' partials of one (sample, expert) share; with the chunk as the block index a line is written from eight L2s.
+__device__ __forceinline__ int chunk_of(int id, int nchunks)
 {
     const int x = id & 7;
     return x * (nchunks / 8) + min(x, nchunks % 8) + (id >> 3);
@@ -719,7 +718,7 @@ template <int RT, int CT>
 __global__ __launch_bounds__(256) void route_expert_mfma_kernel(RouteArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    route_expert_mfma_body<RT, CT>(a, place_of(blockIdx.x, a.nchunks), blockIdx.y * RT * 16, smem);
+    route_expert_mfma_body<RT, CT>(a, chunk_of(blockIdx.x, a.nchunks), blockIdx.y * RT * 16, smem);
 }
 
 // Both routers of a block in one launch (they are independent and both stream x): workgroups
@@ -735,7 +734,7 @@ __global__ __launch_bounds__(256, CT == 1 ? 4 : 2) void route_expert_data_kernel
         route_data_mfma_body<CT, KS>(a, id % a.nchunks_d, id / a.nchunks_d, smem);
     } else {
         const int f = id - n_data;
-        route_expert_mfma_body<RT, CT>(a, place_of(f % a.nchunks, a.nchunks), (f / a.nchunks) * RT * 16, smem);
+        route_expert_mfma_body<RT, CT>(a, chunk_of(f % a.nchunks, a.nchunks), (f / a.nchunks) * RT * 16, smem);
     }
 }
 
@@ -917,11 +916,10 @@ __global__ __launch_bounds__(256) void route_stream_kernel(RouteArgs a, int ipw,
 #pragma unroll
             for (int v = 0; v < 4; ++v) zsh[wave][t * 16 + q4 * 4 + v][u * 16 + r] = accz[t][u][v];
     __syncthreads();
-    const int place = zpart_place(a, chunk);
     for (int o = tid; o < RT * 16 * NP; o += 256) {
         const int row = o / NP, col = o - row * NP;
         if (row < bg && col < n)
-            a.zpart[zpart_at(a, place, b0 + row, col)] = (zsh[0][row][col] + zsh[1][row][col]) + (zsh[2][row][col] + zsh[3][row][col]);
+            a.zpart[zpart_at(a, chunk, b0 + row, col)] = (zsh[0][row][col] + zsh[1][row][col]) + (zsh[2][row][col] + zsh[3][row][col]);
     }
     if (HAS_D) {
         for (int o = tid; o < tcur * bg * n; o += 256) {
@@ -1434,7 +1432,7 @@ hipError_t launch_route(const RouteArgs &a_in, bool bf16, hipStream_t st, RouteS
     const int most = beside ? beside->most : 0;
     if (beside) beside->on = 0;
     RouteArgs a = a_in;
-    zpart_order(a);
+    a.zgroups = SELECT_THREADS / a.n;
     const bool has_e = a.w_e != nullptr, has_d = a.w_b != nullptr;
     hipError_t err = hipSuccess;
     const bool data_mfma = has_d && route_data_uses_mfma(a.b, a.l, a.d, a.n, bf16);
@@ -1447,7 +1445,6 @@ hipError_t launch_route(const RouteArgs &a_in, bool bf16, hipStream_t st, RouteS
         // streaming kernel: expert router and the data router's first map in one pass over x, then the fold
         a.tc = sp.tpc;
         a.nchunks = sp.nchunks;
-        zpart_order(a);
         const dim3 grid(sp.nchunks, (a.b + sp.rt * 16 - 1) / (sp.rt * 16));
 #define UOE_STREAM(RT, CT, RB)                                                                                              \
     do {                                                                                                                    \

@@ -2,7 +2,7 @@
 //
 // As a launch it is 4 to 5 us of a chain of launches of 4 to 12 us, most of that its start, and the contraction behind it
 // begins with lookups of what it wrote.  Every workgroup of the UoME block's first layer can instead add up its sample's partial logits
-// (16 KB from L2 on the small shapes, 16 bytes a lane and load) and rank them for itself; the first one of a sample also writes the
+// (16 KB from L2 on the small shapes) and rank them for itself; the first one of a sample also writes the
 // results.  Forward of 8 x 512 x 512 59.2 -> 57.2 us (5.0 + 12.2 -> 14.6 traced), 6 x 1000 x 360 76.1 -> 73.2.  With the patches as well (the SMHA block's projection) the chain was as long as the
 // launch: 8 x 512 x 512, 8 x 16 logits 7.1 + 5.8 -> 13.2 us, 16 x 4096 x 256, 8 x 64 6.6 + 6.7 -> 23.
 #pragma once
@@ -11,31 +11,9 @@
 namespace uoe {
 
 constexpr int SELECT_THREADS = 512;
-typedef float part4_t __attribute__((ext_vector_type(4), aligned(4)));   // four partials in a row, from any of them on
 
-// Order of a sample's expert logits: chunks whose numbers are equal modulo zgroups (512 / n of them) are added one after the other, then the sums
-// of groups equal modulo 16, then these 16 by halves; the same bits whoever selects.  The partials that are added first lie side by side: a
-// sample's and expert's of all chunks in a row, by group and in a group by chunk (the first zmore groups have one more than zlen).
-inline void zpart_order(RouteArgs &a)
-{
-    a.zgroups = SELECT_THREADS / a.n;
-    a.zlen = a.nchunks / a.zgroups;
-    a.zmore = a.nchunks % a.zgroups;
-    a.zinv = 1.0f / (float)(a.zlen > 0 ? a.zlen : 1);
-    a.zinv_more = 1.0f / (float)(a.zlen + 1);
-}
-__device__ __forceinline__ int zpart_place(const RouteArgs &a, int chunk)
-{
-    const int i = chunk / a.zgroups, g = chunk - i * a.zgroups;
-    return g * a.zlen + min(g, a.zmore) + i;
-}
-__device__ __forceinline__ int zpart_chunk(const RouteArgs &a, int place)   // zpart_place backwards, for at most 2^20 chunks (a quotient in fp32)
-{
-    const int head = a.zmore * (a.zlen + 1), in_head = place < head, p = in_head ? place : place - head;
-    const int g = (int)(((float)p + 0.5f) * (in_head ? a.zinv_more : a.zinv));
-    return (p - g * (a.zlen + in_head)) * a.zgroups + g + (in_head ? 0 : a.zmore);
-}
-__device__ __forceinline__ size_t zpart_at(const RouteArgs &a, int place, int bb, int e) { return ((size_t)bb * a.n + e) * a.nchunks + place; }
+// Where a chunk's partial expert logits lie: a sample's and expert's of all chunks in a row
+__device__ __forceinline__ size_t zpart_at(const RouteArgs &a, int chunk, int bb, int e) { return ((size_t)bb * a.n + e) * a.nchunks + chunk; }
 
 // a lane's value plus that of the lane whose number differs in one bit, 16 lanes at a time: after the steps before, all lanes of a quad (and of
 // half a row) hold the same, so that the mirrored lane's is the same number
@@ -51,45 +29,49 @@ __device__ __forceinline__ float row_sum(float v)
     return add_dpp<0x140>(v);  // row_mirror
 }
 
-// The logits of a sample (without the noise) from its chunks' partials, by NT threads: lane = group, 64 of an expert's a wave, or all of two or four
-// experts where there are at most 32 or 16; ITEMS such rounds and up to 16 partials of each a lane in flight.
+// The logits of a sample (without the noise) from its chunks' partials, by NT threads, in one order whoever selects: chunks whose numbers are equal
+// modulo zgroups (512 / n of them) one after the other, then the sums of groups equal modulo 16, then these 16 by halves.  Lane = group, so that a
+// load's lanes read chunks side by side: 64 of an expert's a wave, or all of two or four experts where there are at most 32 or 16; ITEMS such rounds
+// and up to 16 partials of each a lane in flight.  (In rows sorted by group a lane has 16 bytes a load, but the expert router then either writes its
+// partials scattered or takes its chunks out of order: forward of 4 x 8192 x 1024 520.9 -> 525.0 us, 20 x 1440 x 704 158.6 -> 163.7.)
 template <int NT> __device__ __forceinline__ void expert_logits(const RouteArgs &a, int bb, float *logit, int tid)
 {
     constexpr int W = NT / 64, ITEMS = 2, PASSES = 4;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = a.n;
-    const int bits = a.zgroups > 32 ? 6 : (a.zgroups > 16 ? 5 : 4), experts = 64 >> bits, sub = lane >> bits, cl = lane - (sub << bits);
-    const int groups = min(a.zgroups, a.nchunks), rounds = (groups + 63) / 64, longest = a.zlen + (a.zmore > 0);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = a.n, step = a.zgroups;
+    const int bits = step > 32 ? 6 : (step > 16 ? 5 : 4), experts = 64 >> bits, sub = lane >> bits, cl = lane - (sub << bits);
+    const int groups = min(step, a.nchunks), rounds = (groups + 63) / 64;
     float z = 0.f;
     for (int e0 = wave * experts, round = 0; e0 < n;) {
-        int e[ITEMS], rd[ITEMS], len[ITEMS];
+        int e[ITEMS], rd[ITEMS], left[ITEMS];   // left: chunks of the row from the lane's first on; 0: none of its own
         const float *src[ITEMS];
         float s[ITEMS];
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i) {
             const int g = round * 64 + cl;
             e[i] = e0; rd[i] = round; s[i] = 0.f;
-            len[i] = g < groups && e0 + sub < n ? a.zlen + (g < a.zmore) : 0;
-            src[i] = a.zpart + zpart_at(a, min(g * a.zlen + min(g, a.zmore), a.nchunks - 1), bb, min(e0 + sub, n - 1));
+            left[i] = g < groups && e0 + sub < n ? a.nchunks - g : 0;
+            src[i] = a.zpart + zpart_at(a, min(g, a.nchunks - 1), bb, min(e0 + sub, n - 1));
             if (++round == rounds) {
                 round = 0;
                 e0 += experts * W;
             }
         }
-        for (int j0 = 0; j0 < longest; j0 += PASSES * 4) {
-            part4_t v[ITEMS][PASSES];
+        for (int at = 0; at < a.nchunks; at += PASSES * 4 * step) {
+            float v[ITEMS][PASSES][4];
 #pragma unroll
             for (int q = 0; q < PASSES; ++q)
-                // a load may reach three values behind the row: the next row, or the workspace's next array
-                if (q == 0 || j0 + q * 4 < longest)
+                if (q == 0 || at + q * 4 * step < a.nchunks)
 #pragma unroll
-                    for (int i = 0; i < ITEMS; ++i) v[i][q] = *reinterpret_cast<const part4_t *>(src[i] + (j0 + q * 4 < len[i] ? j0 + q * 4 : 0));
+                    for (int c = 0; c < 4; ++c)
+#pragma unroll
+                        for (int i = 0; i < ITEMS; ++i) v[i][q][c] = src[i][at + (q * 4 + c) * step < left[i] ? at + (q * 4 + c) * step : 0];
 #pragma unroll
             for (int q = 0; q < PASSES; ++q)
-                if (q == 0 || j0 + q * 4 < longest)
+                if (q == 0 || at + q * 4 * step < a.nchunks)
 #pragma unroll
                     for (int i = 0; i < ITEMS; ++i)
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) s[i] += j0 + q * 4 + c < len[i] ? v[i][q][c] : 0.f;
+                        for (int c = 0; c < 4; ++c) s[i] += at + (q * 4 + c) * step < left[i] ? v[i][q][c] : 0.f;
         }
         float part[ITEMS][4];   // the groups' sums of every row of 16 lanes
 #pragma unroll
