@@ -4,7 +4,7 @@
 // bound by that traffic and by their epilogues.  Here a wave owns 32 tokens from u to out, as the attention kernel owns queries: its rows of u
 // stay in registers as the second operand of (u W1)^T = W1^T u^T, whose accumulators, through SiLU and packed in place, are the second operand
 // of out^T = W2^T h^T, which stays in accumulators over all hidden columns (16 registers per 32 columns of d: what bounds d).  Only the weights go
-// through LDS: 64 hidden columns of the sample's experts a stage, both layers' slices, copied by all eight waves two stages deep,
+// through LDS: 64 hidden columns of the sample's experts a stage, both layers' slices, copied by all waves two stages deep,
 // one barrier a stage; every fragment read feeds one product, so LDS and matrix pipes are about equally busy, and the two waves of a SIMD run
 // their SiLU under each other's products.
 // 16 x 4096 x 256, 2 of 8 experts of 128: 41.8 -> 30.9 us (u and out 67 MB, 12.4; with 16 x 256 hidden columns 1.05 PFLOP/s); 16 x 4096 x 64, 4 of 256,
@@ -219,14 +219,16 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void uome_mlp_kernel(UomeUpProblem
 //   128 x 196 x 192, W 768 (0.38; four: 0.77)     41.5  39.6  34.4      24 x 1024 x 128, W 1024 (0.38; 0.75)     37.6  39.7  34.3
 //   128 x 196 x 256, W 384 (0.38; 0.77)           26.1  30.6  25.9      20 x 1024 x 128, W 1024 (0.31; 0.63)     33.8  40.0  34.1
 //   8 x 2048 x 256, W 1024 (0.25; 0.5)            33.6  58.8  50.1      128 x 100 x 192, W 768 (0.2; 0.39)       25.5  27.5  32.5
+// Four waves are alone on their SIMDs and not for d = 256, where they gain 7 % at the most, nor for more than two rounds of d > 128 unless the rounds are full
+// (forward, two launches and four waves: 10 x 7556 x 224, W 576, 600 workgroups, 180 and 192; 23 x 3244 x 192, W 96, 598, 101 and 106; 54 x 1132 x 192,
+// W 448, 486, 122 and 116; 89 x 1300 x 224, W 32, 979, 159 and 146; 12 x 6472 x 128, W 800, 612, 163 and 137).
 int uome_mlp_waves(const UomeArgs &a)
 {
     if (a.d > 256 || a.d % 32 || a.d_e % 32 || (double)a.n * a.d * a.d_e * sizeof(bf16_t) > 4.0e9) return 0;   // (32-bit offsets into a weight)
-    const auto full = [&](int rows) {
-        const long wgs = (long)a.b * ((a.l + rows - 1) / rows);
-        return (double)a.b * a.l / ((double)((wgs + 255) / 256) * 256 * rows);
-    };
-    return full(256) >= 0.6 ? 8 : (a.d <= 224 && full(128) >= 0.75 ? 4 : 0);
+    const auto wgs = [&](int rows) { return (long)a.b * ((a.l + rows - 1) / rows); };
+    const auto full = [&](int rows) { return (double)a.b * a.l / ((double)((wgs(rows) + 255) / 256) * 256 * rows); };
+    if (full(256) >= 0.6) return 8;
+    return a.d <= 224 && full(128) >= (a.d > 128 && wgs(128) > 512 ? 0.85 : 0.75) ? 4 : 0;
 }
 
 template <int DT, int NW, bool SEL> static hipError_t launch_mlp_as(const UomeUpProblem<bf16_t, false, false, SEL> &up, const UomeDownProblem<bf16_t> &dn, int b, hipStream_t st)
@@ -239,7 +241,9 @@ template <int DT, int NW, bool SEL> static hipError_t launch_mlp_as(const UomeUp
 }
 template <int DT, bool SEL> static hipError_t launch_mlp(const UomeUpProblem<bf16_t, false, false, SEL> &up, const UomeDownProblem<bf16_t> &dn, int b, bool four, hipStream_t st)
 {
-    return four ? launch_mlp_as<DT, 4, SEL>(up, dn, b, st) : launch_mlp_as<DT, 8, SEL>(up, dn, b, st);
+    if constexpr (DT < 8)   // (uome_mlp_waves)
+        if (four) return launch_mlp_as<DT, 4, SEL>(up, dn, b, st);
+    return launch_mlp_as<DT, 8, SEL>(up, dn, b, st);
 }
 
 template <bool SEL> static hipError_t launch_uome_mlp_as(const UomeArgs &a, hipStream_t st)
