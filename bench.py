@@ -70,6 +70,9 @@ def kernel_work(c, es: int) -> dict:
         "uome_up": dict(eq="Eq. 38", flops=2 * bld * c.k_m * c.d_e, bytes=(bld + c.n_m * c.d * c.d_e + hidden) * es),
         "uome_down": dict(eq="Eq. 39-40", flops=2 * bld * c.k_m * c.d_e,
                           bytes=(hidden + c.n_m * c.d_e * c.d + 2 * bld) * es),
+        # both layers as the layer call has them: for narrow bf16 tokens (d <= 256) that may be one launch, and the two above are
+        # calls of their own
+        "uome": dict(eq="Eq. 38-40", flops=4 * bld * c.k_m * c.d_e, bytes=(2 * bld + 2 * c.n_m * c.d * c.d_e) * es),
     }
 
 
@@ -426,7 +429,7 @@ def main() -> int:
         tpath = os.path.join(ROOT, "profiles", "traffic.json")
         measured_traffic = json.load(open(tpath)) if os.path.exists(tpath) else {}
         for name in ("route_expert_a", "route_data_a", "route_a", "gather", "smha_qkv", "smha_attention", "smha_out",
-                     "route_m", "uome_up", "uome_down"):
+                     "route_m", "uome_up", "uome_down", "uome"):
             if name not in calls:
                 continue
             fn, w = calls[name], work[name]
@@ -447,9 +450,10 @@ def main() -> int:
                                      "route_data_a": "data router + reduction + selection kernels",
                                      "route_a": "the whole SMHA routing call (both routers, selection)",
                                      "route_m": "UoME expert router + its selection kernel",
+                                     "uome": "both layers as the layer call has them",
                                      "gather": "standalone Eq. 18 copy; the layer call folds it into smha_qkv"}.get(name)})
         # the dominant kernel: the single-kernel stage that takes the most time
-        single = [k for k in kernels if k["kernel"] not in ("route_a", "gather")]
+        single = [k for k in kernels if k["kernel"] not in ("route_a", "gather", "uome")]
         dom = max(single, key=lambda k: k["us_per_launch"])
         traffic = measured_traffic.get(f"{dom['kernel']}:{cfg.name}")
         roofline = {"kernel": f"{dom['kernel']} ({dom['eq']})", "bound": dom["bound"], "achieved": dom["achieved"],

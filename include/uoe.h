@@ -245,8 +245,11 @@ int uoe_uome_forward(const uoe_block_desc *blk, const void *u, const void *a_in,
                      void *hip_stream);
 
 /*
- * The two contractions of uoe_uome_forward as separate calls (same kernels), for callers that
- * keep the hidden activations or time the steps one by one.
+ * The two contractions of uoe_uome_forward as separate calls, for callers that keep the hidden
+ * activations or time the steps one by one.  uoe_uome_forward runs the same kernels, or for
+ * UOE_BF16 and narrow tokens (d <= 256, widths that are multiples of 32) both contractions in one
+ * that keeps the hidden activations (rounded to bf16 alike) on chip and adds up in another order:
+ * results may then differ by a rounding of the last bit.
  *   uoe_uome_up   (Eq. 38): hidden[b,l,s*d_e + j] = gate * SiLU(u[b] A^I_i)[.,j] for the sample's
  *                 s-th active expert i = expert_idx[b,s]; hidden is [b,l,k*d_e] in the storage
  *                 dtype, written in full.  expert_gate may be NULL without UOE_FLAG_GATE_EXPERT.

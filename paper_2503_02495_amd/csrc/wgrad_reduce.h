@@ -5,10 +5,6 @@
 
 namespace uoe {
 
-// partial [sets*chunks*parts][M][N] fp32 -> storage dtype, an expert's parts added in order and rounded once.
-// Set s goes to dst[s], stored as [n][M][N] or transposed as [n][N][M].  64x64 tiles, 16-byte loads with four rows of
-// a part in flight per thread, 8-byte stores (bf16; straight, or transposed through LDS): the launch is a plain stream
-// of the partial tiles (134 MB on the largest shape: 47.7 us with 32x32 tiles and 4-byte loads).
 constexpr int RED_T = 64;
 template <typename T> __device__ __forceinline__ void store4_as(T *p, float4 v);
 template <> __device__ __forceinline__ void store4_as<float>(float *p, float4 v) { *reinterpret_cast<float4 *>(p) = v; }
@@ -16,9 +12,13 @@ template <> __device__ __forceinline__ void store4_as<bf16_t>(bf16_t *p, float4 
 {
     *reinterpret_cast<uint2 *>(p) = make_uint2(pack2_bf16(v.x, v.y), pack2_bf16(v.z, v.w));
 }
-// CHUNKED: more than 128 samples are possible
 typedef float (*RedTile)[RED_T + 1];   // the workgroup's RED_T x RED_T tile in LDS
 constexpr size_t RED_LDS = sizeof(float) * RED_T * (RED_T + 1);
+// partial [sets*chunks*parts][M][N] fp32 -> storage dtype, an expert's parts added in order and rounded once.
+// Set s goes to dst[s], stored as [n][M][N] or transposed as [n][N][M].  64x64 tiles, 16-byte loads with four rows of
+// a part in flight per thread, 8-byte stores (bf16; straight, or transposed through LDS): the launch is a plain stream
+// of the partial tiles (134 MB on the largest shape: 47.7 us with 32x32 tiles and 4-byte loads).
+// CHUNKED: more than 128 samples are possible
 template <typename T, bool CHUNKED> __device__ __forceinline__ void wgrad_reduce_tile(const WgradReduceArgs &a, RedTile tile, int bx, int by, int bz)
 {
     const int set = bz / a.n, e = bz - set * a.n, r0 = by * RED_T, c0 = bx * RED_T;
