@@ -1163,11 +1163,11 @@ __device__ __forceinline__ void column_softmax(const float *col, int n, int m, f
 // Expert selection of one sample, by a workgroup of its own.
 __device__ __forceinline__ void select_experts(const RouteArgs &a, int bb, int has_e)
 {
-    __shared__ float ge[32];
+    __shared__ float sums[SELECT_THREADS], ge[32];
     const int tid = threadIdx.x;
     const float noise = expert_noise(a, bb, tid);
     if (has_e) {
-        expert_logits<SELECT_THREADS>(a, bb, ge, tid);
+        expert_logits<SELECT_THREADS>(a, bb, sums, ge, tid);
         __syncthreads();
     }
     if (tid < 64) rank_experts(a, bb, has_e, ge, noise, true, nullptr, tid);

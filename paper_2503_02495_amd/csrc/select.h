@@ -30,62 +30,56 @@ __device__ __forceinline__ float row_sum(float v)
 }
 
 // The logits of a sample (without the noise) from its chunks' partials, by NT threads, in one order whoever selects: chunks whose numbers are equal
-// modulo zgroups (512 / n of them) one after the other, then the sums of groups equal modulo 16, then these 16 by halves.  Lane = group, so that a
-// load's lanes read chunks side by side: 64 of an expert's a wave, or all of two or four experts where there are at most 32 or 16; ITEMS such rounds
-// and up to 16 partials of each a lane in flight.  (In rows sorted by group a lane has 16 bytes a load, but the expert router then either writes its
-// partials scattered or takes its chunks out of order: forward of 4 x 8192 x 1024 520.9 -> 525.0 us, 20 x 1440 x 704 158.6 -> 163.7.)
-template <int NT> __device__ __forceinline__ void expert_logits(const RouteArgs &a, int bb, float *logit, int tid)
+// modulo zgroups (512 / n of them) one after the other, then the sums of groups equal modulo 16, then these 16 by halves.  A thread has 512 / NT
+// (expert, group) pairs, neighbours' groups side by side as their chunks in memory, and all their partials in flight up to 32 or 16 each (as many as
+// leave a contraction's occupancy alone).  sums: 512 floats of LDS.
+// (In rows sorted by group a thread has 16 bytes a load, but the expert router then either writes its partials scattered or takes its chunks out of
+// order: forward of 4 x 8192 x 1024 520.9 -> 525.0 us, 20 x 1440 x 704 158.6 -> 163.7.  A wave an expert and 16 in flight: 2 x 960 x 160, 10 and 13
+// experts, 52.5 us.)
+template <int NT> __device__ __forceinline__ void expert_logits(const RouteArgs &a, int bb, float *sums, float *logit, int tid)
 {
-    constexpr int W = NT / 64, ITEMS = 2, PASSES = 4;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = a.n, step = a.zgroups;
-    const int bits = step > 32 ? 6 : (step > 16 ? 5 : 4), experts = 64 >> bits, sub = lane >> bits, cl = lane - (sub << bits);
-    const int groups = min(step, a.nchunks), rounds = (groups + 63) / 64;
-    float z = 0.f;
-    for (int e0 = wave * experts, round = 0; e0 < n;) {
-        int e[ITEMS], rd[ITEMS], left[ITEMS];   // left: chunks of the row from the lane's first on; 0: none of its own
-        const float *src[ITEMS];
-        float s[ITEMS];
+    constexpr int ITEMS = SELECT_THREADS / NT, PASSES = ITEMS > 2 ? 4 : 8;
+    const int n = a.n, step = a.zgroups;
+    const float inv = __builtin_amdgcn_rcpf((float)step);   // (good enough for quotients of up to 512)
+    int left[ITEMS];   // chunks of the row from the pair's first on; 0: none of its own
+    const float *src[ITEMS];
+    float s[ITEMS];
 #pragma unroll
-        for (int i = 0; i < ITEMS; ++i) {
-            const int g = round * 64 + cl;
-            e[i] = e0; rd[i] = round; s[i] = 0.f;
-            left[i] = g < groups && e0 + sub < n ? a.nchunks - g : 0;
-            src[i] = a.zpart + zpart_at(a, min(g, a.nchunks - 1), bb, min(e0 + sub, n - 1));
-            if (++round == rounds) {
-                round = 0;
-                e0 += experts * W;
-            }
-        }
-        for (int at = 0; at < a.nchunks; at += PASSES * 4 * step) {
-            float v[ITEMS][PASSES][4];
+    for (int i = 0; i < ITEMS; ++i) {
+        const int p = tid + i * NT, e = (int)((p + 0.5f) * inv), g = p - e * step;
+        left[i] = e < n ? max(a.nchunks - g, 0) : 0;
+        src[i] = a.zpart + zpart_at(a, min(g, a.nchunks - 1), bb, min(e, n - 1));
+        s[i] = 0.f;
+    }
+    for (int at = 0; at < a.nchunks; at += PASSES * 4 * step) {
+        float v[ITEMS][PASSES][4];
 #pragma unroll
-            for (int q = 0; q < PASSES; ++q)
-                if (q == 0 || at + q * 4 * step < a.nchunks)
+        for (int q = 0; q < PASSES; ++q)
+            if (q == 0 || at + q * 4 * step < a.nchunks)
 #pragma unroll
-                    for (int c = 0; c < 4; ++c)
+                for (int i = 0; i < ITEMS; ++i)
 #pragma unroll
-                        for (int i = 0; i < ITEMS; ++i) v[i][q][c] = src[i][at + (q * 4 + c) * step < left[i] ? at + (q * 4 + c) * step : 0];
+                    for (int c = 0; c < 4; ++c) v[i][q][c] = src[i][at + (q * 4 + c) * step < left[i] ? at + (q * 4 + c) * step : 0];
 #pragma unroll
-            for (int q = 0; q < PASSES; ++q)
-                if (q == 0 || at + q * 4 * step < a.nchunks)
+        for (int q = 0; q < PASSES; ++q)
+            if (q == 0 || at + q * 4 * step < a.nchunks)
 #pragma unroll
-                    for (int i = 0; i < ITEMS; ++i)
+                for (int i = 0; i < ITEMS; ++i)
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) s[i] += at + (q * 4 + c) * step < left[i] ? v[i][q][c] : 0.f;
-        }
-        float part[ITEMS][4];   // the groups' sums of every row of 16 lanes
+                    for (int c = 0; c < 4; ++c) s[i] += at + (q * 4 + c) * step < left[i] ? v[i][q][c] : 0.f;
+    }
 #pragma unroll
-        for (int i = 0; i < ITEMS; ++i)
+    for (int i = 0; i < ITEMS; ++i) sums[tid + i * NT] = s[i];
+    __syncthreads();
 #pragma unroll
-            for (int h = 0; h < 4; ++h) part[i][h] = __shfl(s[i], (lane - cl + h * 16 + (lane & 15)) & 63, 64);
-#pragma unroll
-        for (int i = 0; i < ITEMS; ++i) {
-            z = rd[i] ? z + part[i][0] : 0.f + part[i][0];
-            if (bits > 4) z += part[i][1];
-            if (bits > 5) z = (z + part[i][2]) + part[i][3];
-            const float t = row_sum(z);
-            if (rd[i] == rounds - 1 && cl == 0 && e[i] + sub < n) logit[e[i] + sub] = t;
-        }
+    for (int i = 0; i < ITEMS; ++i) {
+        const int e = (tid + i * NT) / 16, l16 = tid & 15;
+        if (e >= n) break;
+        float z = 0.f;
+#pragma unroll 4
+        for (int g = l16; g < step; g += 16) z += sums[e * step + g];
+        z = row_sum(z);
+        if (l16 == 0) logit[e] = z;
     }
 }
 
@@ -136,17 +130,17 @@ __device__ __forceinline__ void rank_experts(const RouteArgs &a, int bb, int has
     if (write && a.expert_idx) a.expert_idx[(size_t)bb * a.k + pos] = lane;
 }
 
-// The selection of sample bb by a workgroup of NT threads for itself; `write`: also to the routing results.  scratch: 32 floats of LDS.
+// The selection of sample bb by a workgroup of NT threads for itself; `write`: also to the routing results.  scratch: 544 floats of LDS.
 // Ends on a barrier.
 template <int NT>
 __device__ __forceinline__ void select_experts_beside(const RouteSelect &s, int bb, float *scratch, SelectedExperts &out, bool write, int tid)
 {
     const float noise = expert_noise(s.r, bb, tid);
     if (s.has_e) {
-        expert_logits<NT>(s.r, bb, scratch, tid);
+        expert_logits<NT>(s.r, bb, scratch, scratch + SELECT_THREADS, tid);
         __syncthreads();
     }
-    if (tid < 64) rank_experts(s.r, bb, s.has_e, scratch, noise, write, &out, tid);
+    if (tid < 64) rank_experts(s.r, bb, s.has_e, scratch + SELECT_THREADS, noise, write, &out, tid);
     // Nothing of it may be in flight for the compiler (vmcnt 0, in a form that it reads): partials that not all lanes' sums took stay so, and its
     // wait before their registers' next use stood in the contraction's loop, where it waits for the copies of every K-step
     // (30 x 156 tokens, d 928, 96 hidden columns: the layer's forward 68.4 us, 66.1 with the selection as a launch).
