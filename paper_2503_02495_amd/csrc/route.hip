@@ -51,7 +51,8 @@ static int route_data_short(int l, int n, int m, int tc)
 // workgroups of more than 16 experts.  Less than 16 only if that gains a tenth.  The data router takes the expert router's chunks unless its partial sums
 // are many.  Forward, us, 16 tokens / all that are idle otherwise, from 4 on / these: 2 x 64 x 64 46.8 / 41.7 / 41.7; 8 x 512 x 512, 8 experts 147.1 / 143.7 /
 // 143.7; 28 x 217 x 184, 14 experts 104.2 / 110.3 / 104.1; 61 x 72 x 280, 6 and 16 79.2 / 83.5 / 75.7; 15 x 288 x 360, 32 and 2 112.0 / 115.2 / 110.9;
-// 1 x 2006 x 784, 12 (W_E 75 MB: longer runs of it stream better) 112.3 / 125.7 / 111.4.
+// 1 x 2006 x 784, 12 (W_E 75 MB, more than 1024 tokens a sample: longer runs of it stream better) 112.3 / 125.7 / 111.4; 2 x 530 x 992, 12 119 / 102 / 101;
+// 1 x 3913 x 576, 16 154 / 167 / 150.
 static int route_short_tokens_per_chunk(int b, int l, int d, int n, int m)
 {
     const int regs = n <= 4 ? 7 : (n <= 8 || (n > 16 && n <= 24) ? 5 : (n <= 12 || n > 16 ? 4 : 3));   // workgroups a compute unit's registers hold
@@ -77,7 +78,7 @@ int route_tokens_per_chunk(int b, int l, int d, int n, int m, bool bf16)
     long tc = ((long)b * l) / 512;
     if (tc > l / 8) tc = l / 8;  // at least ~8 chunks per sample so the last, short chunk does not dominate
     tc = (tc / 4) * 4;
-    if (tc < 16) tc = !bf16 && (long)b * l < 8192 && (n > 16 || (double)n * l * d * sizeof(float) <= 16e6) ? route_short_tokens_per_chunk(b, l, d, n, m) : 16;
+    if (tc < 16) tc = !bf16 && (long)b * l < 8192 && (n > 16 || l <= 1024 || (double)n * l * d * sizeof(float) <= 16e6) ? route_short_tokens_per_chunk(b, l, d, n, m) : 16;
     if (tc > 64) tc = 64;
     if (tc > l) tc = l;
     return (int)tc;
