@@ -3,7 +3,7 @@
 // As a launch it is 4 to 5 us of a chain of launches of 4 to 12 us, most of that its start, and the contraction behind it
 // begins with lookups of what it wrote.  Every workgroup of the UoME block's first layer can instead add up its sample's partial logits
 // (16 KB from L2 on the small shapes) and rank them for itself; the first one of a sample also writes the
-// results.  Forward of 8 x 512 x 512 59.2 -> 57.2 us (5.0 + 12.2 -> 14.6 traced), 6 x 1000 x 360 76.1 -> 73.2.  With the patches as well (the SMHA block's projection) the chain was as long as the
+// results.  Forward of 8 x 512 x 512 59.2 -> 57.4 us (5.0 + 12.2 -> 14.6 traced), 6 x 1000 x 360 76.1 -> 73.2.  With the patches as well (the SMHA block's projection) the chain was as long as the
 // launch: 8 x 512 x 512, 8 x 16 logits 7.1 + 5.8 -> 13.2 us, 16 x 4096 x 256, 8 x 64 6.6 + 6.7 -> 23.
 #pragma once
 #include "common.h"
